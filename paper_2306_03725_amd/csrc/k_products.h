@@ -1,0 +1,20 @@
+// Kernels of the two products, handed out by the files that instantiate them.
+#pragma once
+
+namespace usl_products {
+
+struct ProductKernel {
+    const void* fn;        // nullptr: no such kernel
+    int K, LPT, NT;        // padded fan-in, labels per lane, lanes
+    int transpose_bytes;   // LDS its prologue and epilogue need
+};
+
+ProductKernel kernel_f32_q4(bool backward, int K, int shape);
+ProductKernel kernel_f32_q2(bool backward, int K, int shape);
+ProductKernel kernel_f32_q1(bool backward, int K, int shape);
+ProductKernel kernel_f32_halves(bool backward, int K, int shape);
+ProductKernel kernel_bf16_q4(bool backward, int K, int shape);
+ProductKernel kernel_bf16_q2(bool backward, int K, int shape);
+ProductKernel kernel_bf16_q1(bool backward, int K, int shape);
+
+}  // namespace usl_products

@@ -1,90 +1,85 @@
-// Device helpers shared by the forward / backward-weight kernels: LDS staging of activation rows,
-// coalesced movement of idx / W / grad_W rows through an LDS transposition buffer, and the private
-// slot order of a label.
+// Device code of the forward and weight-gradient kernels.
+//
+// Both walk the same gather: for a pair (instance i, label j) the k values x[i][idx[j][t]].  A workgroup owns a block
+// of labels and keeps their indices (two 16-bit columns per register) and weights -- or gradient sums -- in registers
+// for its whole life; the activations stream through LDS, and every gather is an LDS read.
+//
+// What bounds it is the number of LDS reads, not their width: a ds_read_b64 of 64 random addresses takes as long as a
+// ds_read_b32 (7.8 against 7.9 lanes per clock and compute unit; 15.7 against 21 when no two lanes of a pass meet in a
+// bank), a ds_read_b128 little longer (5.0 and 13.4).  So the activations are interleaved: Q instances form a group,
+// and the group's row holds x[i0][c], x[i0+1][c], ... side by side, one unit of 4, 8 or 16 bytes per column, which one
+// read brings to a lane.  A row of units has to fit LDS (160 KB):
+//     float32   Q = 4 up to d = 10 200,  Q = 2 up to 20 400,  Q = 1 up to 40 800,  beyond that the row in two halves
+//     bfloat16  Q = 4 up to d = 20 400,  Q = 2 up to 40 800,  Q = 1 up to 65 536
+// The interleaved copy of x (k_interleave, [groups][row], rows padded to 16 bytes and, where the fan-in is padded, by a
+// column of zeros) costs one pass over b * d values; it also takes the alignment of d out of the row copies.  Q = 1
+// needs no copy when rows of x are 16-byte aligned already.
+//
+// Fan-ins are padded to K, the next multiple of 8 up to 64; padding slots have weight 0 and read the column of zeros.
 #pragma once
 #include "usl_internal.h"
 
 namespace usl_products {
 
-// Copies n elements from global memory into LDS.  With 16-byte alignment the bulk goes through
-// global_load_lds_dwordx4: each wavefront moves 1 KiB per instruction straight into LDS (the LDS
-// address is wave-uniform, the hardware adds lane*16), no VGPRs are used and all of a lane's loads
-// are in flight together.  The caller's barrier follows the vmcnt wait.
-// WAIT = false leaves the copies in flight: the caller waits (vmcnt) before its barrier.
-template <typename TS, int NT, bool WAIT = true>
-__device__ __forceinline__ void stage(const TS* __restrict__ src, TS* __restrict__ lds, int n,
-                                      bool vec_ok, int tid = (int)threadIdx.x) {
-    if (vec_ok) {
-        const uint4* s = reinterpret_cast<const uint4*>(src);
-        uint4* dd = reinterpret_cast<uint4*>(lds);
-        const int nv = (int)((size_t)n * sizeof(TS) / 16);
-        const int full = nv & ~63;
-        const int lane = tid & 63;
-        for (int v = (tid >> 6) * 64; v < full; v += NT)
-            __builtin_amdgcn_global_load_lds(
-                (const __attribute__((address_space(1))) void*)(s + v + lane),
-                (__attribute__((address_space(3))) void*)(dd + v), 16, 0, 0);
-        for (int v = full + tid; v < nv; v += NT) dd[v] = s[v];
-        if (WAIT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    } else {
-        for (int c = tid; c < n; c += NT) lds[c] = src[c];
+struct Geom {
+    int row_bytes;         // bytes from one group's row to the next in the interleaved activations (a multiple of 16)
+    int tile_rows;         // rows staged together (small rows)
+    int nbuf;              // 2: the next tile is copied in while this one is gathered
+    int buf_bytes;         // LDS bytes from one buffer to the next
+    int groups;            // instance groups of the batch
+    int groups_per_block;  // ... that one blockIdx.y walks
+    int share;             // workgroups resident together on one XCD: they split the warm-up of the next row
+    int zero_col;          // column that padding slots read (a unit of zeros)
+    int dummy;             // 256 bytes of LDS that the warm-up loads are thrown into
+};
+
+static constexpr int ROW_LDS_MAX = 160 * 1024 - 512;    // largest tile
+static constexpr int HALF_COLS = 32768;                 // columns per half of a row in two halves
+
+// --------------------------------------------------------------------------------------------- row copies
+// nbytes (a multiple of 16) from global memory to LDS, both 16-byte aligned, by global_load_lds_dwordx4: each wavefront
+// moves 1 KiB per instruction, no registers are used, all of it is in flight together.  In the last instruction the
+// lanes past the end are masked off.  The caller waits (vmcnt) before its barrier.  Inline assembly: behind the builtin
+// the compiler waits for the copy before the next LDS read of any address, so nothing would overlap it.
+template <int NT>
+__device__ __forceinline__ void stage_async(const char* __restrict__ src, uint32_t lds, int nbytes, int tid) {
+    for (int v = (tid >> 6) * 1024; v < nbytes; v += (NT / 64) * 1024) {
+        const uint32_t off = (uint32_t)(v + (tid & 63) * 16);
+        const uint32_t to = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds + (uint32_t)v));
+        if ((int)off < nbytes)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(off), "s"(src) : "memory");
     }
 }
 
-// The same with the byte offset of the element instead of its column (indices scaled once, outside the loop).
-__device__ __forceinline__ float lds_at(const float* row, uint32_t byte_off) {
-    return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(row) + byte_off);
-}
-__device__ __forceinline__ float lds_at(const uint16_t* row, uint32_t byte_off) {
-    return usl_bf16_to_f32(*reinterpret_cast<const uint16_t*>(reinterpret_cast<const char*>(row) + byte_off));
-}
-__device__ __forceinline__ float lds_val(const float* row, uint32_t c) { return row[c]; }
-__device__ __forceinline__ float lds_val(const uint16_t* row, uint32_t c) {
-    return usl_bf16_to_f32(row[c]);
+// Touches one word of every 128-byte line of [row + first line * 128, + n lines): the words go to `dummy` (256 bytes of
+// LDS that nobody reads), so no register waits for them.
+template <int NT>
+__device__ __forceinline__ void touch_lines(const char* __restrict__ row, int first, int n, uint32_t dummy, int tid) {
+    const uint32_t to = (uint32_t)__builtin_amdgcn_readfirstlane((int)dummy);
+    for (int l = tid; l < n; l += NT)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(to), "v"((uint32_t)(first + l) * 128u), "s"(row) : "memory");
 }
 
-// Rows [row0, row0+NT) of a row-major [m][KW] matrix of 32-bit words (KW % 4 == 0, base 16-byte
-// aligned) are copied into LDS with coalesced 16-byte loads, one padding word per row, so that
-// afterwards lane r can read "its" row word by word without bank conflicts (stride KW+1).
-template <int KW, int NT>
-__device__ __forceinline__ void rows_to_lds(const uint32_t* __restrict__ src, int64_t row0,
-                                            int64_t m, uint32_t* __restrict__ lds) {
-    int64_t nvalid = m - row0;
-    nvalid = nvalid < 0 ? 0 : (nvalid > NT ? NT : nvalid);
-    const int nv = (int)(nvalid * KW / 4);
-    const uint4* s = reinterpret_cast<const uint4*>(src + row0 * KW);
-    for (int v = threadIdx.x; v < nv; v += NT) {
-        const uint4 q = s[v];
-        const int f = v * 4, r = f / KW, t = f % KW;
-        uint32_t* p = lds + r * (KW + 1) + t;
-        p[0] = q.x; p[1] = q.y; p[2] = q.z; p[3] = q.w;
+// Warms the L2 of this workgroup's XCD with a share of the next tile.  All workgroups walk the batch in step, so without
+// this every row is first touched by all of them at once and the whole chip waits out an HBM round trip per row.
+// Workgroups are dealt to the 8 XCDs round robin; those of one XCD that are resident together (consecutive in
+// blockIdx.x) split the row between them, one load per 128-byte line.
+struct WarmShare {
+    int slice, slices;
+    __device__ __forceinline__ explicit WarmShare(int share) {
+        slices = max(1, min((int)(gridDim.x >> 3), share));
+        slice = (int)(blockIdx.x >> 3) % slices;
     }
-}
-// The reverse: every lane has put its KW words at lds[lane*(KW+1) ..]; rows leave with coalesced
-// 16-byte stores, or float atomic adds when several workgroups share the destination.
-template <int KW, int NT, bool ATOMIC>
-__device__ __forceinline__ void lds_to_rows(const uint32_t* __restrict__ lds, float* __restrict__ dst,
-                                            int64_t row0, int64_t m) {
-    int64_t nvalid = m - row0;
-    nvalid = nvalid < 0 ? 0 : (nvalid > NT ? NT : nvalid);
-    const int nv = (int)(nvalid * KW / 4);
-    float* base = dst + row0 * KW;
-    for (int v = threadIdx.x; v < nv; v += NT) {
-        const int f = v * 4, r = f / KW, t = f % KW;
-        const uint32_t* p = lds + r * (KW + 1) + t;
-        const float4 q = make_float4(__uint_as_float(p[0]), __uint_as_float(p[1]),
-                                     __uint_as_float(p[2]), __uint_as_float(p[3]));
-        if (ATOMIC) {
-            unsafeAtomicAdd(base + f, q.x); unsafeAtomicAdd(base + f + 1, q.y);
-            unsafeAtomicAdd(base + f + 2, q.z); unsafeAtomicAdd(base + f + 3, q.w);
-        } else {
-            reinterpret_cast<float4*>(base)[v] = q;
-        }
-    }
+    // first and number of this workgroup's lines of a tile of nbytes
+    __device__ __forceinline__ int per(int nbytes) const { return ((nbytes + 127) / 128 + slices - 1) / slices; }
+};
+template <int NT>
+__device__ __forceinline__ void warm_slice(const char* __restrict__ row, int nbytes, int per, int slice, uint32_t dummy, int tid) {
+    touch_lines<NT>(row, slice * per, min(per, (nbytes + 127) / 128 - slice * per), dummy, tid);
 }
 
-// Private slot order of one label: K bytes (slot visited at step s), held as K/4 words while the
-// registers are being filled.  A null table means natural order.
+// --------------------------------------------------------------------------------------------- labels into registers
+// Private slot order of one label: K bytes (slot visited at step s).  A null table means stored order.
 template <int K>
 struct SlotOrder {
     uint32_t w[K / 4];
@@ -92,120 +87,734 @@ struct SlotOrder {
     __device__ __forceinline__ void load(const uint8_t* __restrict__ perm, int64_t j, bool valid) {
         on = perm != nullptr;
         if (on) {
-            const uint32_t* p = reinterpret_cast<const uint32_t*>(perm + j * K);
+            const uint2* p = reinterpret_cast<const uint2*>(perm + j * K);
 #pragma unroll
-            for (int q = 0; q < K / 4; ++q) w[q] = valid ? p[q] : (0x03020100u + 0x04040404u * q);
+            for (int q = 0; q < K / 8; ++q) {
+                const uint2 u = valid ? p[q] : make_uint2(0x03020100u + 0x08080808u * q, 0x07060504u + 0x08080808u * q);
+                w[2 * q] = u.x;
+                w[2 * q + 1] = u.y;
+            }
         }
     }
-    __device__ __forceinline__ int at(int s) const {
-        return on ? (int)((w[s >> 2] >> (8 * (s & 3))) & 0xFFu) : s;
+    __device__ __forceinline__ int at(int s) const { return on ? (int)((w[s >> 2] >> (8 * (s & 3))) & 0xFFu) : s; }
+};
+
+// The rows of 64 consecutive labels go through a piece of LDS that belongs to the wavefront alone: coalesced loads in,
+// every lane reads its own row out (odd row strides, no bank conflicts), no barrier of the workgroup in between.
+// Rows of 32-bit words take more LDS than rows of 16-bit ones, so for K > 32 the wavefronts take two turns.
+template <int K> constexpr int turns_of() { return K > 32 ? 2 : 1; }
+template <int K> constexpr int words_stride() { return K + 1; }        // words per row of 32-bit values
+template <int K> constexpr int halves_stride() { return K / 2 + 1; }   // words per row of 16-bit values
+// LDS one wavefront's rows take (32-bit rows, shared between the turns)
+template <int K, int NT> constexpr int transpose_bytes() {
+    constexpr int waves = NT / 64;
+    constexpr int w32 = (waves + turns_of<K>() - 1) / turns_of<K>() * 64 * words_stride<K>() * 4;
+    constexpr int w16 = waves * 64 * halves_stride<K>() * 4;
+    return w32 > w16 ? w32 : w16;
+}
+
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The prologue brings the rows of a wavefront's 64 labels in: order, indices and weights are requested together
+// (coalesced; one trip to memory instead of three in a row), then indices and weights go through LDS.
+template <typename TS, int K, int NT> constexpr bool raw_rows() {
+    return (K & (K - 1)) == 0 && (sizeof(TS) == 2 || (K <= 32 && NT < 1024));
+}
+template <typename TS, int K>
+struct RawRows {
+    SlotOrder<K> so;
+    uint32_t idx[K];
+    uint32_t w[sizeof(TS) == 4 ? K : K / 2];
+
+    // 16-byte (bfloat16: 8-byte) pieces where k is a multiple of 4, single values elsewhere
+    __device__ __forceinline__ void load_idx(const uint8_t* __restrict__ perm, const int32_t* __restrict__ ip, int64_t row0, int64_t m,
+                                             int k, uint32_t zero_col) {
+        const int lane = threadIdx.x & 63;
+        const int64_t wrow0 = row0 + (threadIdx.x & ~63);
+        so.load(perm, row0 + threadIdx.x, row0 + threadIdx.x < m);
+        if ((k & 3) == 0) {
+            constexpr int U = K / 4;   // 4-slot pieces per (padded) row
+#pragma unroll
+            for (int it = 0; it < U; ++it) {
+                const int u = it * 64 + lane, r = u / U, t = (u % U) * 4;
+                uint4 q = make_uint4(zero_col, zero_col, zero_col, zero_col);
+                if (wrow0 + r < m && t < k) q = *reinterpret_cast<const uint4*>(ip + (wrow0 + r) * k + t);
+                idx[4 * it] = q.x; idx[4 * it + 1] = q.y; idx[4 * it + 2] = q.z; idx[4 * it + 3] = q.w;
+            }
+        } else {
+#pragma unroll
+            for (int it = 0; it < K; ++it) {
+                const int u = it * 64 + lane, r = u / K, t = u % K;
+                idx[it] = wrow0 + r < m && t < k ? (uint32_t)ip[(wrow0 + r) * k + t] : zero_col;
+            }
+        }
+    }
+    __device__ __forceinline__ void load_w(const TS* __restrict__ W, int64_t row0, int64_t m, int k) {
+        const int lane = threadIdx.x & 63;
+        const int64_t wrow0 = row0 + (threadIdx.x & ~63);
+        if ((k & 3) == 0) {
+            constexpr int U = K / 4;
+#pragma unroll
+            for (int it = 0; it < U; ++it) {
+                const int u = it * 64 + lane, r = u / U, t = (u % U) * 4;
+                const bool in = wrow0 + r < m && t < k;
+                if constexpr (sizeof(TS) == 4) {
+                    uint4 v = make_uint4(0, 0, 0, 0);
+                    if (in) v = *reinterpret_cast<const uint4*>(W + (wrow0 + r) * k + t);
+                    w[4 * it] = v.x; w[4 * it + 1] = v.y; w[4 * it + 2] = v.z; w[4 * it + 3] = v.w;
+                } else {
+                    uint2 v = make_uint2(0, 0);
+                    if (in) v = *reinterpret_cast<const uint2*>(W + (wrow0 + r) * k + t);
+                    w[2 * it] = v.x; w[2 * it + 1] = v.y;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int it = 0; it < K; ++it) {
+                const int u = it * 64 + lane, r = u / K, t = u % K;
+                const bool in = wrow0 + r < m && t < k;
+                if constexpr (sizeof(TS) == 4) w[it] = in ? __float_as_uint(W[(wrow0 + r) * k + t]) : 0u;
+                else if (it & 1) w[it / 2] |= in ? (uint32_t)W[(wrow0 + r) * k + t] << 16 : 0u;
+                else w[it / 2] = in ? (uint32_t)W[(wrow0 + r) * k + t] : 0u;
+            }
+        }
     }
 };
 
-// Brings the k indices of NT consecutive labels into registers, two 16-bit indices per register,
-// in the label's private slot order.
-template <int K, int NT>
-__device__ __forceinline__ void fetch_idx_packed(const int32_t* __restrict__ idx, int64_t row0,
-                                                 int64_t m, uint32_t* lds, const SlotOrder<K>& so,
-                                                 uint32_t (&pk)[K / 2]) {
-    __syncthreads();
-    rows_to_lds<K, NT>(reinterpret_cast<const uint32_t*>(idx), row0, m, lds);
-    __syncthreads();
-    const bool valid = row0 + threadIdx.x < m;
-    const uint32_t* p = lds + threadIdx.x * (K + 1);
+// pk[q] = columns of steps 2q, 2q+1 of label row0 + threadIdx.x (16 bits each), in the label's slot order.
+template <int K, typename TS>
+__device__ __forceinline__ void unpack_idx(const RawRows<TS, K>& raw, int k, uint32_t* lds, uint32_t (&pk)[K / 2]) {
+    constexpr int S = halves_stride<K>();
+    const int lane = threadIdx.x & 63;
+    uint16_t* mine = reinterpret_cast<uint16_t*>(lds + (threadIdx.x >> 6) * 64 * S);
+    if ((k & 3) == 0) {
+        constexpr int U = K / 4;
 #pragma unroll
-    for (int q = 0; q < K / 2; ++q)
-        pk[q] = valid ? (p[so.at(2 * q)] | (p[so.at(2 * q + 1)] << 16)) : 0u;
-}
-template <int K>
-__device__ __forceinline__ uint32_t col_of(const uint32_t (&pk)[K / 2], int t) {
-    return (t & 1) ? (pk[t >> 1] >> 16) : (pk[t >> 1] & 0xFFFFu);
-}
-
-// Byte offset (column * 4) of slot t in a float32 row.  The 16-bit half of the packed word is
-// selected and shifted by one instruction (sub-dword operand select) where mask-and-shift takes two.
-template <int K>
-__device__ __forceinline__ uint32_t byte_off4(const uint32_t (&pk)[K / 2], int t) {
-    uint32_t a;
-    const uint32_t two = 2;
-    if (t & 1)
-        asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
-            : "=v"(a) : "s"(two), "v"(pk[t >> 1]));
-    else
-        asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0"
-            : "=v"(a) : "s"(two), "v"(pk[t >> 1]));
-    return a;
-}
-// Slot t of the float32 row that starts at the very beginning of the workgroup's LDS: the byte offset
-// is the LDS address itself, so no base is added (one vector instruction per gather instead of two).
-// Kernels that use it have no static LDS, which puts their dynamic LDS at address 0; they check that
-// once (lds_starts_at_zero) before relying on it.
-typedef const __attribute__((address_space(3))) float lds_f32_t;
-template <int K>
-__device__ __forceinline__ float gather_row0(const uint32_t (&pk)[K / 2], int t) {
-    return *reinterpret_cast<lds_f32_t*>(static_cast<uintptr_t>(byte_off4<K>(pk, t)));
-}
-// A float32 row cut into two halves of 32768 columns (the LDS budget): slot t of the half that is staged,
-// or, for a slot of the other half, the lane's word of zeros behind the buffer (zbyte >= 131072 is its LDS
-// address).  While the upper half is staged the packed indices have bit 15 flipped, so "in this half" is
-// "column < 32768" both times and the choice is one unsigned minimum.
-template <int K>
-__device__ __forceinline__ float gather_half(const uint32_t (&pk)[K / 2], int t, uint32_t zbyte) {
-    const uint32_t off = byte_off4<K>(pk, t);
-    return *reinterpret_cast<lds_f32_t*>(static_cast<uintptr_t>(off < zbyte ? off : zbyte));
-}
-template <int N>
-__device__ __forceinline__ void flip_half(uint32_t (&pk)[N]) {
+        for (int it = 0; it < U; ++it) {
+            const int u = it * 64 + lane, r = u / U, t = (u % U) * 4;
+            uint32_t* p = reinterpret_cast<uint32_t*>(mine) + r * S + t / 2;
+            p[0] = (raw.idx[4 * it] & 0xFFFFu) | (raw.idx[4 * it + 1] << 16);
+            p[1] = (raw.idx[4 * it + 2] & 0xFFFFu) | (raw.idx[4 * it + 3] << 16);
+        }
+    } else {
 #pragma unroll
-    for (int q = 0; q < N; ++q) pk[q] ^= 0x80008000u;
-}
-__device__ __forceinline__ bool lds_starts_at_zero(const void* dyn_lds) {
-    return (uint32_t)(uintptr_t)((const __attribute__((address_space(3))) void*)dyn_lds) == 0u;
-}
-
-template <int K, int NT>
-__device__ __forceinline__ void fetch_w(const float* __restrict__ W, int64_t row0, int64_t m,
-                                        uint32_t* lds, const SlotOrder<K>& so, float (&w)[K]) {
-    __syncthreads();
-    rows_to_lds<K, NT>(reinterpret_cast<const uint32_t*>(W), row0, m, lds);
-    __syncthreads();
-    const bool valid = row0 + threadIdx.x < m;
-    const uint32_t* p = lds + threadIdx.x * (K + 1);
-#pragma unroll
-    for (int t = 0; t < K; ++t) w[t] = valid ? __uint_as_float(p[so.at(t)]) : 0.f;
-}
-// bfloat16 rows are widened to float32 words on their way into the transposition buffer, so the
-// per-lane part is the same as for float32.
-template <int K, int NT>
-__device__ __forceinline__ void fetch_w(const uint16_t* __restrict__ W, int64_t row0, int64_t m,
-                                        uint32_t* lds, const SlotOrder<K>& so, float (&w)[K]) {
-    __syncthreads();
-    {
-        int64_t nvalid = m - row0;
-        nvalid = nvalid < 0 ? 0 : (nvalid > NT ? NT : nvalid);
-        const int nv = (int)(nvalid * K / 8);
-        const uint4* s = reinterpret_cast<const uint4*>(W + row0 * K);
-        for (int v = threadIdx.x; v < nv; v += NT) {
-            const uint4 q = s[v];
-            const int f = v * 8, r = f / K, t = f % K;
-            uint32_t* p = lds + r * (K + 1) + t;
-            p[0] = q.x << 16; p[1] = q.x & 0xFFFF0000u; p[2] = q.y << 16; p[3] = q.y & 0xFFFF0000u;
-            p[4] = q.z << 16; p[5] = q.z & 0xFFFF0000u; p[6] = q.w << 16; p[7] = q.w & 0xFFFF0000u;
+        for (int it = 0; it < K; ++it) {
+            const int u = it * 64 + lane, r = u / K, t = u % K;
+            mine[r * 2 * S + t] = (uint16_t)raw.idx[it];
         }
     }
-    __syncthreads();
-    const bool valid = row0 + threadIdx.x < m;
-    const uint32_t* p = lds + threadIdx.x * (K + 1);
+    wave_sync();
+    const uint16_t* p = mine + lane * 2 * S;
 #pragma unroll
-    for (int t = 0; t < K; ++t) w[t] = valid ? __uint_as_float(p[so.at(t)]) : 0.f;
+    for (int q = 0; q < K / 2; ++q) {
+        pk[q] = (uint32_t)p[raw.so.at(2 * q)] | ((uint32_t)p[raw.so.at(2 * q + 1)] << 16);
+        if ((q & 3) == 3) __builtin_amdgcn_sched_barrier(0);   // a few addresses at a time: all of them would not fit
+    }
+    wave_sync();
 }
 
-// Stops the compiler from hoisting the unpacked indices out of the instance loop: unpacking is two
-// cheap VALU operations per gather, holding all k unpacked indices would double the register need.
+// w[s] = weight of step s, float32 (0 for padding slots and labels past m).  All threads of the workgroup call it.
+template <int K, int NT>
+__device__ __forceinline__ void unpack_w(const RawRows<float, K>& raw, int k, uint32_t* lds, float (&w)[K]) {
+    constexpr int S = words_stride<K>(), T = turns_of<K>(), WAVES = NT / 64, PER = (WAVES + T - 1) / T;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t* mine = lds + (wave % PER) * 64 * S;
+#pragma unroll 1
+    for (int turn = 0; turn < T; ++turn) {
+        __syncthreads();
+        if (wave / PER != turn) continue;
+        if ((k & 3) == 0) {
+            constexpr int U = K / 4;
+#pragma unroll
+            for (int it = 0; it < U; ++it) {
+                const int u = it * 64 + lane, r = u / U, t = (u % U) * 4;
+                uint32_t* p = mine + r * S + t;
+                p[0] = raw.w[4 * it]; p[1] = raw.w[4 * it + 1]; p[2] = raw.w[4 * it + 2]; p[3] = raw.w[4 * it + 3];
+            }
+        } else {
+#pragma unroll
+            for (int it = 0; it < K; ++it) {
+                const int u = it * 64 + lane, r = u / K, t = u % K;
+                mine[r * S + t] = raw.w[it];
+            }
+        }
+        wave_sync();
+        const uint32_t* p = mine + lane * S;
+#pragma unroll
+        for (int s = 0; s < K; ++s) {
+            w[s] = __uint_as_float(p[raw.so.at(s)]);
+            if ((s & 7) == 7) __builtin_amdgcn_sched_barrier(0);
+        }
+        wave_sync();
+    }
+    __syncthreads();
+}
+// The same two where the raw rows would not fit beside what is resident (K > 32, or 128 registers a lane), a few pieces at
+// a time, and for a K that is no power of two: there the unrolled address arithmetic made the raw form slower (75 -> 97 us
+// for the forward product at m = 70k, d = 10k, k = 48, b = 100).
+template <int K>
+__device__ __forceinline__ void fetch_idx(const int32_t* __restrict__ idx, int64_t row0, int64_t m, int k, uint32_t zero_col,
+                                          uint32_t* lds, const SlotOrder<K>& so, uint32_t (&pk)[K / 2]) {
+    constexpr int S = halves_stride<K>();
+    const int lane = threadIdx.x & 63;
+    uint16_t* mine = reinterpret_cast<uint16_t*>(lds + (threadIdx.x >> 6) * 64 * S);
+    const int64_t wrow0 = row0 + (threadIdx.x & ~63);
+    if ((k & 3) == 0) {
+        constexpr int U = K / 4;
+#pragma unroll 4
+        for (int it = 0; it < U; ++it) {
+            const int u = it * 64 + lane, r = u / U, t = (u % U) * 4;
+            uint4 q = make_uint4(zero_col, zero_col, zero_col, zero_col);
+            if (wrow0 + r < m && t < k) q = *reinterpret_cast<const uint4*>(idx + (wrow0 + r) * k + t);
+            uint32_t* p = reinterpret_cast<uint32_t*>(mine) + r * S + t / 2;
+            p[0] = (q.x & 0xFFFFu) | (q.y << 16);
+            p[1] = (q.z & 0xFFFFu) | (q.w << 16);
+        }
+    } else {
+#pragma unroll 4
+        for (int it = 0; it < K; ++it) {
+            const int u = it * 64 + lane, r = u / K, t = u % K;
+            mine[r * 2 * S + t] = (uint16_t)(wrow0 + r < m && t < k ? (uint32_t)idx[(wrow0 + r) * k + t] : zero_col);
+        }
+    }
+    wave_sync();
+    const uint16_t* p = mine + lane * 2 * S;
+#pragma unroll
+    for (int q = 0; q < K / 2; ++q) {
+        pk[q] = (uint32_t)p[so.at(2 * q)] | ((uint32_t)p[so.at(2 * q + 1)] << 16);
+        if ((q & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+    wave_sync();
+}
+template <int K, int NT>
+__device__ __forceinline__ void fetch_w(const float* __restrict__ W, int64_t row0, int64_t m, int k, uint32_t* lds,
+                                        const SlotOrder<K>& so, float (&w)[K]) {
+    constexpr int S = words_stride<K>(), T = turns_of<K>(), WAVES = NT / 64, PER = (WAVES + T - 1) / T;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t wrow0 = row0 + (threadIdx.x & ~63);
+    uint32_t* mine = lds + (wave % PER) * 64 * S;
+#pragma unroll 1
+    for (int turn = 0; turn < T; ++turn) {
+        __syncthreads();
+        if (wave / PER != turn) continue;
+        if ((k & 3) == 0) {
+            constexpr int U = K / 4;
+#pragma unroll 4
+            for (int it = 0; it < U; ++it) {
+                const int u = it * 64 + lane, r = u / U, t = (u % U) * 4;
+                uint4 q = make_uint4(0, 0, 0, 0);
+                if (wrow0 + r < m && t < k) q = *reinterpret_cast<const uint4*>(W + (wrow0 + r) * k + t);
+                uint32_t* p = mine + r * S + t;
+                p[0] = q.x; p[1] = q.y; p[2] = q.z; p[3] = q.w;
+            }
+        } else {
+#pragma unroll 4
+            for (int it = 0; it < K; ++it) {
+                const int u = it * 64 + lane, r = u / K, t = u % K;
+                mine[r * S + t] = wrow0 + r < m && t < k ? __float_as_uint(W[(wrow0 + r) * k + t]) : 0u;
+            }
+        }
+        wave_sync();
+        const uint32_t* p = mine + lane * S;
+#pragma unroll
+        for (int s = 0; s < K; ++s) {
+            w[s] = __uint_as_float(p[so.at(s)]);
+            if ((s & 7) == 7) __builtin_amdgcn_sched_barrier(0);
+        }
+        wave_sync();
+    }
+    __syncthreads();
+}
+template <int K, int NT>
+__device__ __forceinline__ void fetch_w(const uint16_t* __restrict__ W, int64_t row0, int64_t m, int k, uint32_t* lds,
+                                        const SlotOrder<K>& so, uint32_t (&wp)[K / 2]) {
+    constexpr int S = halves_stride<K>();
+    const int lane = threadIdx.x & 63;
+    uint16_t* mine = reinterpret_cast<uint16_t*>(lds + (threadIdx.x >> 6) * 64 * S);
+    const int64_t wrow0 = row0 + (threadIdx.x & ~63);
+    if ((k & 3) == 0) {
+        constexpr int U = K / 4;
+#pragma unroll 4
+        for (int it = 0; it < U; ++it) {
+            const int u = it * 64 + lane, r = u / U, t = (u % U) * 4;
+            uint2 q = make_uint2(0, 0);
+            if (wrow0 + r < m && t < k) q = *reinterpret_cast<const uint2*>(W + (wrow0 + r) * k + t);
+            uint32_t* p = reinterpret_cast<uint32_t*>(mine) + r * S + t / 2;
+            p[0] = q.x; p[1] = q.y;
+        }
+    } else {
+#pragma unroll 4
+        for (int it = 0; it < K; ++it) {
+            const int u = it * 64 + lane, r = u / K, t = u % K;
+            mine[r * 2 * S + t] = wrow0 + r < m && t < k ? W[(wrow0 + r) * k + t] : (uint16_t)0;
+        }
+    }
+    wave_sync();
+    const uint16_t* p = mine + lane * 2 * S;
+#pragma unroll
+    for (int q = 0; q < K / 2; ++q) {
+        wp[q] = (uint32_t)p[so.at(2 * q)] | ((uint32_t)p[so.at(2 * q + 1)] << 16);
+        if ((q & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+    wave_sync();
+}
+// bfloat16 weights stay in pairs: wp[q] = weights of steps 2q (low half) and 2q+1.
+template <int K, int NT>
+__device__ __forceinline__ void unpack_w(const RawRows<uint16_t, K>& raw, int k, uint32_t* lds, uint32_t (&wp)[K / 2]) {
+    constexpr int S = halves_stride<K>();
+    const int lane = threadIdx.x & 63;
+    uint16_t* mine = reinterpret_cast<uint16_t*>(lds + (threadIdx.x >> 6) * 64 * S);
+    if ((k & 3) == 0) {
+        constexpr int U = K / 4;
+#pragma unroll
+        for (int it = 0; it < U; ++it) {
+            const int u = it * 64 + lane, r = u / U, t = (u % U) * 4;
+            uint32_t* p = reinterpret_cast<uint32_t*>(mine) + r * S + t / 2;
+            p[0] = raw.w[2 * it]; p[1] = raw.w[2 * it + 1];
+        }
+    } else {
+#pragma unroll
+        for (int it = 0; it < K; ++it) {
+            const int u = it * 64 + lane, r = u / K, t = u % K;
+            mine[r * 2 * S + t] = (uint16_t)(raw.w[it / 2] >> (16 * (it & 1)));
+        }
+    }
+    wave_sync();
+    const uint16_t* p = mine + lane * 2 * S;
+#pragma unroll
+    for (int q = 0; q < K / 2; ++q) {
+        wp[q] = (uint32_t)p[raw.so.at(2 * q)] | ((uint32_t)p[raw.so.at(2 * q + 1)] << 16);
+        if ((q & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+    wave_sync();
+}
+// The reverse: acc[s] of every lane becomes row row0 + threadIdx.x of dst[m][k].  All threads of the workgroup call it.
+template <int K, int NT>
+__device__ __forceinline__ void store_rows(const float (&acc)[K], float* __restrict__ dst, int64_t row0, int64_t m, int k,
+                                           uint32_t* lds, const SlotOrder<K>& so) {
+    constexpr int S = words_stride<K>(), T = turns_of<K>(), WAVES = NT / 64, PER = (WAVES + T - 1) / T;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t wrow0 = row0 + (threadIdx.x & ~63);
+    uint32_t* mine = lds + (wave % PER) * 64 * S;
+    for (int turn = 0; turn < T; ++turn) {
+        __syncthreads();
+        if (wave / PER != turn) continue;
+        uint32_t* p = mine + lane * S;
+#pragma unroll
+        for (int s = 0; s < K; ++s) {
+            p[so.at(s)] = __float_as_uint(acc[s]);
+            if ((s & 7) == 7) __builtin_amdgcn_sched_barrier(0);
+        }
+        wave_sync();
+        if ((k & 3) == 0) {
+            constexpr int U = K / 4;
+#pragma unroll 4
+            for (int it = 0; it < U; ++it) {
+                const int u = it * 64 + lane, r = u / U, t = (u % U) * 4;
+                const uint32_t* q = mine + r * S + t;
+                if (wrow0 + r < m && t < k)
+                    *reinterpret_cast<float4*>(dst + (wrow0 + r) * k + t) =
+                        make_float4(__uint_as_float(q[0]), __uint_as_float(q[1]), __uint_as_float(q[2]), __uint_as_float(q[3]));
+            }
+        } else {
+#pragma unroll 4
+            for (int it = 0; it < K; ++it) {
+                const int u = it * 64 + lane, r = u / K, t = u % K;
+                if (wrow0 + r < m && t < k) dst[(wrow0 + r) * k + t] = __uint_as_float(mine[r * S + t]);
+            }
+        }
+        wave_sync();
+    }
+    __syncthreads();
+}
+
+// --------------------------------------------------------------------------------------------- gathers
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+template <typename TS, int Q> struct Unit;                      // what one LDS read brings: Q instances of one column
+template <> struct Unit<float, 1> { typedef float T; };
+template <> struct Unit<float, 2> { typedef f32x2 T; };
+template <> struct Unit<float, 4> { typedef f32x4 T; };
+template <> struct Unit<uint16_t, 1> { typedef uint16_t T; };
+template <> struct Unit<uint16_t, 2> { typedef uint32_t T; };
+template <> struct Unit<uint16_t, 4> { typedef u32x2 T; };
+
+template <typename T>
+__device__ __forceinline__ T lds_read(uint32_t byte_addr) {
+    typedef const __attribute__((address_space(3))) T lds_t;
+    return *reinterpret_cast<lds_t*>(static_cast<uintptr_t>(byte_addr));
+}
+
+// LDS address of step t: base + column * BYTES, one instruction (16-bit multiply-add that picks either half of the word).
+template <int BYTES, int N>
+__device__ __forceinline__ uint32_t unit_addr(const uint32_t (&pk)[N], int t, uint32_t base) {
+    uint32_t a;
+    if (t & 1) asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(a) : "v"(pk[t >> 1]), "n"(BYTES), "s"(base));
+    else       asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(a) : "v"(pk[t >> 1]), "n"(BYTES), "s"(base));
+    return a;
+}
+
+// Stops the compiler from hoisting the unpacked addresses out of the loop over the batch: rebuilding one is a single
+// instruction, holding all of them would double the register need.
 template <int N>
 __device__ __forceinline__ void keep_packed(uint32_t (&pk)[N]) {
 #pragma unroll
     for (int q = 0; q < N; ++q) asm volatile("" : "+v"(pk[q]));
+}
+// Reads in flight per wavefront: their results would otherwise crowd out the resident indices and weights.
+template <typename TS, int Q> constexpr int batch_of() { return sizeof(typename Unit<TS, Q>::T) == 16 ? 4 : 8; }
+
+// HALVES: a float32 row of more than ROW_LDS_MAX in two halves of HALF_COLS columns; a step of the half that is not
+// staged reads one word of zeros behind the buffer (the same word for every lane: one broadcast).  While the upper
+// half is staged the base is HALF_COLS words lower, so a column of the lower half wraps round to a huge address, and "in
+// this half" is one unsigned minimum both times.
+template <typename TS, int Q, bool HALVES, int N>
+__device__ __forceinline__ typename Unit<TS, Q>::T gather(const uint32_t (&pk)[N], int t, uint32_t base, uint32_t zbyte) {
+    typedef typename Unit<TS, Q>::T U;
+    uint32_t a = unit_addr<(int)sizeof(U)>(pk, t, base);
+    if (HALVES) a = a < zbyte ? a : zbyte;
+    return lds_read<U>(a);
+}
+
+template <bool HALVES, int B, int ARITH>
+__device__ __forceinline__ void schedule_batch() {   // the addresses of a batch, its reads, then the arithmetic
+    __builtin_amdgcn_sched_group_barrier(0x002, HALVES ? 2 * B : B, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, B, 0);
+    __builtin_amdgcn_sched_group_barrier(0x002, ARITH, 0);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// acc[q] += sum over the label's steps of w * x[instance q]
+template <int K, int Q, bool HALVES>
+__device__ __forceinline__ void label_dot(const uint32_t (&pk)[K / 2], const float (&w)[K], uint32_t base, uint32_t zbyte, float (&acc)[Q]) {
+    constexpr int B = batch_of<float, Q>();
+    typedef typename Unit<float, Q>::T U;
+#pragma unroll
+    for (int t0 = 0; t0 < K; t0 += B) {
+        U v[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) v[u] = gather<float, Q, HALVES>(pk, t0 + u, base, zbyte);
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            if constexpr (Q == 1) acc[0] = fmaf(w[t0 + u], v[u], acc[0]);
+            else {
+#pragma unroll
+                for (int q = 0; q < Q; ++q) acc[q] = fmaf(w[t0 + u], v[u][q], acc[q]);
+            }
+        }
+        schedule_batch<HALVES, B, B * Q>();
+    }
+}
+// bfloat16: the activations of two steps are joined per instance and one dot-product instruction does both
+// multiply-adds in float32.
+__device__ __forceinline__ float dot2(uint32_t x2, uint32_t w2, float acc) {
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, x2), __builtin_bit_cast(bf16x2, w2), acc, false);
+}
+__device__ __forceinline__ uint32_t join_lo(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
+__device__ __forceinline__ uint32_t join_hi(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+template <int K, int Q, bool HALVES>
+__device__ __forceinline__ void label_dot(const uint32_t (&pk)[K / 2], const uint32_t (&wp)[K / 2], uint32_t base, uint32_t zbyte, float (&acc)[Q]) {
+    constexpr int B = 8;
+    typedef typename Unit<uint16_t, Q>::T U;
+#pragma unroll
+    for (int t0 = 0; t0 < K; t0 += B) {
+        U v[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) v[u] = gather<uint16_t, Q, HALVES>(pk, t0 + u, base, zbyte);
+#pragma unroll
+        for (int u = 0; u < B; u += 2) {
+            const uint32_t w2 = wp[(t0 + u) / 2];
+            if constexpr (Q == 1) acc[0] = dot2((uint32_t)v[u] | ((uint32_t)v[u + 1] << 16), w2, acc[0]);
+            else if constexpr (Q == 2) {
+                acc[0] = dot2(join_lo(v[u], v[u + 1]), w2, acc[0]);
+                acc[1] = dot2(join_hi(v[u], v[u + 1]), w2, acc[1]);
+            } else {
+                acc[0] = dot2(join_lo(v[u].x, v[u + 1].x), w2, acc[0]);
+                acc[1] = dot2(join_hi(v[u].x, v[u + 1].x), w2, acc[1]);
+                acc[2] = dot2(join_lo(v[u].y, v[u + 1].y), w2, acc[2]);
+                acc[3] = dot2(join_hi(v[u].y, v[u + 1].y), w2, acc[3]);
+            }
+        }
+        schedule_batch<HALVES, B, B * Q>();
+    }
+}
+
+// acc[s] += sum over the group's instances of g[q] * x[instance q]
+template <int K, typename TS, int Q, bool HALVES>
+__device__ __forceinline__ void label_outer(const uint32_t (&pk)[K / 2], const float (&gv)[Q], uint32_t base, uint32_t zbyte, float (&acc)[K]) {
+    constexpr int B = batch_of<TS, Q>();
+    typedef typename Unit<TS, Q>::T U;
+#pragma unroll
+    for (int t0 = 0; t0 < K; t0 += B) {
+        U v[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) v[u] = gather<TS, Q, HALVES>(pk, t0 + u, base, zbyte);
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            float& a = acc[t0 + u];
+            if constexpr (sizeof(TS) == 4 && Q == 1) a = fmaf(gv[0], v[u], a);
+            else if constexpr (sizeof(TS) == 4) {
+#pragma unroll
+                for (int q = 0; q < Q; ++q) a = fmaf(gv[q], v[u][q], a);
+            } else if constexpr (Q == 1) a = fmaf(gv[0], usl_bf16_to_f32(v[u]), a);
+            else if constexpr (Q == 2) {
+                a = fmaf(gv[0], __uint_as_float(v[u] << 16), a);
+                a = fmaf(gv[1], __uint_as_float(v[u] & 0xFFFF0000u), a);
+            } else {
+                a = fmaf(gv[0], __uint_as_float(v[u].x << 16), a);
+                a = fmaf(gv[1], __uint_as_float(v[u].x & 0xFFFF0000u), a);
+                a = fmaf(gv[2], __uint_as_float(v[u].y << 16), a);
+                a = fmaf(gv[3], __uint_as_float(v[u].y & 0xFFFF0000u), a);
+            }
+        }
+        schedule_batch<HALVES, B, B * Q>();
+    }
+}
+
+// --------------------------------------------------------------------------------------------- the walk over the batch
+// Calls body(group, first LDS byte of its row, part) for every instance group of this blockIdx.y, with the rows staged
+// tile by tile; late(first group of the tile, groups in it, lane) right after a tile has arrived.
+// MULTI = false: one row fills the buffer (tiles of one row, one buffer); HALVES: part 0 / 1 of every row.
+template <int NT, bool MULTI, bool HALVES, typename BODY, typename LATE>
+__device__ __forceinline__ void walk(const char* __restrict__ xi, uint32_t lds0, const Geom& tg, int g0, int g1, BODY body, LATE late) {
+    const uint32_t dummy = lds0 + (uint32_t)tg.dummy;
+    const WarmShare ws(tg.share);
+    if (!MULTI) {
+        const int per = ws.per(tg.row_bytes);
+        constexpr int HB = HALF_COLS * 4;
+        const char* row = xi + (size_t)g0 * tg.row_bytes;
+#pragma unroll 1
+        for (int g = g0; g < g1; ++g, row += tg.row_bytes) {
+#pragma unroll 1
+            for (int part = 0; part < (HALVES ? 2 : 1); ++part) {
+                // the lane number is taken afresh every time: addresses derived from it are then rebuilt with a few
+                // instructions instead of living in a dozen registers across the gathers, which need them more
+                int tid = (int)threadIdx.x;
+                asm volatile("" : "+v"(tid));
+                __syncthreads();
+                if (HALVES) stage_async<NT>(row + (part ? HB : 0), lds0, part ? tg.row_bytes - HB : HB, tid);
+                else stage_async<NT>(row, lds0, tg.row_bytes, tid);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __syncthreads();
+                if ((!HALVES || part == 1) && g + 1 < g1) warm_slice<NT>(row + tg.row_bytes, tg.row_bytes, per, ws.slice, dummy, tid);
+                if (part == 0) late(g, 1, tid);
+                body(g, part ? lds0 - (uint32_t)HB : lds0, part);
+            }
+        }
+        return;
+    }
+    // one or two buffers: with two, the next tile is copied in while this one is gathered
+    const bool two = tg.nbuf == 2;
+    const int per = ws.per(tg.tile_rows * tg.row_bytes);
+    uint32_t base = lds0, other = lds0 + (uint32_t)tg.buf_bytes;
+    __syncthreads();
+    if (two && g0 < g1) stage_async<NT>(xi + (size_t)g0 * tg.row_bytes, base, min(tg.tile_rows, g1 - g0) * tg.row_bytes, (int)threadIdx.x);
+#pragma unroll 1
+    for (int t = g0; t < g1; t += tg.tile_rows) {
+        int tid = (int)threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const int rows = min(tg.tile_rows, g1 - t), next = t + tg.tile_rows, after = two ? next + tg.tile_rows : next;
+        if (!two) {
+            __syncthreads();   // the buffer is no longer read
+            stage_async<NT>(xi + (size_t)t * tg.row_bytes, base, rows * tg.row_bytes, tid);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this tile has landed
+        __syncthreads();                                   // (two buffers: and the other one is no longer read)
+        if (two && next < g1)
+            stage_async<NT>(xi + (size_t)next * tg.row_bytes, other, min(tg.tile_rows, g1 - next) * tg.row_bytes, tid);
+        if (after < g1)
+            warm_slice<NT>(xi + (size_t)after * tg.row_bytes, min(tg.tile_rows, g1 - after) * tg.row_bytes, per, ws.slice, dummy, tid);
+        late(t, rows, tid);
+#pragma unroll 1
+        for (int r = 0; r < rows; ++r) body(t + r, base + (uint32_t)r * (uint32_t)tg.row_bytes, 0);
+        if (two) { const uint32_t s = base; base = other; other = s; }
+    }
+}
+
+template <typename TS, int K> struct WReg;                      // weights of one label in registers
+template <int K> struct WReg<float, K> { float v[K]; };
+template <int K> struct WReg<uint16_t, K> { uint32_t v[K / 2]; };
+
+__device__ __forceinline__ uint32_t lds_base(const void* p) {
+    return (uint32_t)(uintptr_t)((const __attribute__((address_space(3))) void*)p);
+}
+
+// ------------------------------------------------------------------------------------------------ forward
+// out[i][j] = sum_t W[j][t] x[i][idx[j][t]].  grid (label blocks, groups of the batch).
+template <int K, int LPT, int NT, typename TS, int Q, bool HALVES>
+__global__ void __launch_bounds__(NT)
+k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS* __restrict__ W, float* __restrict__ out,
+          int64_t m, int k, int b, Geom tg, const uint8_t* __restrict__ perm) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    const uint32_t lds0 = lds_base(lds_raw);
+    const int64_t j0 = (int64_t)blockIdx.x * (NT * LPT);
+    uint32_t pk[LPT][K / 2];
+    WReg<TS, K> w[LPT];
+#pragma unroll
+    for (int l = 0; l < LPT; ++l) {
+        const int64_t row0 = j0 + (int64_t)l * NT;
+        if constexpr (raw_rows<TS, K, NT>()) {
+            RawRows<TS, K> raw;
+            raw.load_idx(perm, idx, row0, m, k, (uint32_t)tg.zero_col);
+            raw.load_w(W, row0, m, k);
+            unpack_idx<K, TS>(raw, k, reinterpret_cast<uint32_t*>(lds_raw), pk[l]);
+            unpack_w<K, NT>(raw, k, reinterpret_cast<uint32_t*>(lds_raw), w[l].v);
+        } else {
+            SlotOrder<K> so;
+            so.load(perm, row0 + threadIdx.x, row0 + threadIdx.x < m);
+            if (l) __syncthreads();
+            fetch_idx<K>(idx, row0, m, k, (uint32_t)tg.zero_col, reinterpret_cast<uint32_t*>(lds_raw), so, pk[l]);
+            fetch_w<K, NT>(W, row0, m, k, reinterpret_cast<uint32_t*>(lds_raw), so, w[l].v);
+        }
+    }
+    const uint32_t zbyte = lds0 + HALF_COLS * 4u;
+    if (HALVES) {
+        __syncthreads();
+        if (threadIdx.x < 4) reinterpret_cast<uint32_t*>(lds_raw)[HALF_COLS + threadIdx.x] = 0u;
+    }
+    const int g0 = blockIdx.y * tg.groups_per_block, g1 = min(tg.groups, g0 + tg.groups_per_block);
+    const int nlab = (int)min((int64_t)NT * LPT, m - j0);
+    // Q <= 2: the scores of a group are written while the next group is gathered, between two labels' gathers (a store
+    // right before the next copy would make that copy's wait include it; four stores in a row would hold the wavefront
+    // at the memory pipeline).  Q = 4 has no registers left for that, and a quarter of the waits.
+    constexpr bool DELAY = Q <= 2;
+    float prev[DELAY ? LPT : 1][Q] = {};
+    auto put = [&](int g, int l, const float (&v)[Q]) {
+        int jl = (int)threadIdx.x + l * NT;   // rebuilt here: kept, every label's offset would be a register across the gathers
+        asm volatile("" : "+v"(jl));
+        if (jl < nlab) {
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (g * Q + q < b) (out + ((size_t)(g * Q + q) * m + j0))[(uint32_t)jl] = v[q];
+        }
+    };
+    walk<NT, (Q > 1), HALVES>(xi, lds0, tg, g0, g1,
+        [&](int g, uint32_t base, int part) {
+#pragma unroll
+            for (int l = 0; l < LPT; ++l) {
+                if (DELAY && part == 0 && g > g0) put(g - 1, l, prev[DELAY ? l : 0]);
+                float acc[Q];
+#pragma unroll
+                for (int q = 0; q < Q; ++q) acc[q] = HALVES && part ? prev[DELAY ? l : 0][q] : 0.f;   // the first half's sums
+                keep_packed(pk[l]);
+                label_dot<K, Q, HALVES>(pk[l], w[l].v, base, zbyte, acc);
+                // finish the sums here; left alone the compiler sinks the multiply-adds into the guarded store
+                // and keeps every gathered value alive until then
+#pragma unroll
+                for (int q = 0; q < Q; ++q) asm volatile("" : "+v"(acc[q]));
+                if (DELAY) {
+#pragma unroll
+                    for (int q = 0; q < Q; ++q) prev[DELAY ? l : 0][q] = acc[q];
+                } else {
+                    put(g, l, acc);
+                }
+            }
+        },
+        [&](int, int, int) {});
+    if (DELAY && g1 > g0) {
+#pragma unroll
+        for (int l = 0; l < LPT; ++l) put(g1 - 1, l, prev[DELAY ? l : 0]);
+    }
+}
+
+// ------------------------------------------------------------------------------------------------ weight gradient
+// grad_W[j][t] = sum_i g[i][j] x[i][idx[j][t]].  With the batch split over blockIdx.y every part of it leaves a partial
+// gradient (part_stride elements apart) that a later kernel adds up in a fixed order.  A label whose gradients of a
+// group are zero in all 64 lanes skips its gathers (Algorithm 3 skips zero entries).
+template <int K, int LPT, int NT, typename TS, int Q, bool HALVES>
+__global__ void __launch_bounds__(NT)
+k_backward_weight(const float* __restrict__ g, const char* __restrict__ xi, const int32_t* __restrict__ idx, float* __restrict__ grad_W,
+                  int64_t m, int k, int b, Geom tg, const uint8_t* __restrict__ perm, size_t part_stride, const uint32_t* __restrict__ gate) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    if (gate && *gate == 0) return;   // the gradient is almost all zeros: the kernels over its nonzeros do the work
+    const uint32_t lds0 = lds_base(lds_raw);
+    const int64_t j0 = (int64_t)blockIdx.x * (NT * LPT);
+    uint32_t pk[LPT][K / 2];
+    float acc[LPT][K];
+#pragma unroll
+    for (int l = 0; l < LPT; ++l) {
+        const int64_t row0 = j0 + (int64_t)l * NT;
+        if constexpr (raw_rows<float, K, NT>()) {
+            RawRows<TS, K> raw;
+            raw.load_idx(perm, idx, row0, m, k, (uint32_t)tg.zero_col);
+            unpack_idx<K, TS>(raw, k, reinterpret_cast<uint32_t*>(lds_raw), pk[l]);
+        } else {
+            SlotOrder<K> so;
+            so.load(perm, row0 + threadIdx.x, row0 + threadIdx.x < m);
+            fetch_idx<K>(idx, row0, m, k, (uint32_t)tg.zero_col, reinterpret_cast<uint32_t*>(lds_raw), so, pk[l]);
+        }
+#pragma unroll
+        for (int t = 0; t < K; ++t) acc[l][t] = 0.f;
+    }
+    const uint32_t zbyte = lds0 + HALF_COLS * 4u;
+    if (HALVES) {
+        __syncthreads();
+        if (threadIdx.x < 4) reinterpret_cast<uint32_t*>(lds_raw)[HALF_COLS + threadIdx.x] = 0u;
+    }
+    const int g0 = blockIdx.y * tg.groups_per_block, g1 = min(tg.groups, g0 + tg.groups_per_block);
+    const int nlab = (int)min((int64_t)NT * LPT, m - j0);
+    // The gradients of the next group come from HBM and are requested one group ahead, right after this group's row
+    // copy: before it, the copy's wait would wait for them too.  (Q = 4 on wide blocks has no registers for that: their
+    // lines are brought to the L2 one group ahead instead and read behind the copy.)
+    constexpr bool AHEAD = LPT * Q <= 4;
+    float gnext[AHEAD ? LPT : 1][Q], gv[LPT][Q];
+    auto load_g = [&](int grp, int l, float (&v)[Q]) {
+        int jl = (int)threadIdx.x + l * NT;
+        asm volatile("" : "+v"(jl));
+#pragma unroll
+        for (int q = 0; q < Q; ++q) v[q] = jl < nlab && grp < g1 && grp * Q + q < b ? (g + ((size_t)(grp * Q + q) * m + j0))[(uint32_t)jl] : 0.f;
+    };
+    if (AHEAD) {
+#pragma unroll
+        for (int l = 0; l < LPT; ++l) load_g(g0, l, gnext[AHEAD ? l : 0]);
+    }
+    walk<NT, (Q > 1), HALVES>(xi, lds0, tg, g0, g1,
+        [&](int grp, uint32_t base, int part) {
+            if (part == 0) {
+                if (AHEAD) {
+#pragma unroll
+                    for (int l = 0; l < LPT; ++l) {
+#pragma unroll
+                        for (int q = 0; q < Q; ++q) gv[l][q] = gnext[AHEAD ? l : 0][q];
+                        load_g(grp + 1, l, gnext[AHEAD ? l : 0]);
+                    }
+                } else {
+#pragma unroll
+                    for (int l = 0; l < LPT; ++l) load_g(grp, l, gv[l]);
+                }
+            }
+#pragma unroll
+            for (int l = 0; l < LPT; ++l) {
+                bool any = false;
+#pragma unroll
+                for (int q = 0; q < Q; ++q) any = any || gv[l][q] != 0.f;
+                if (!__any(any)) continue;
+                keep_packed(pk[l]);
+                label_outer<K, TS, Q, HALVES>(pk[l], gv[l], base, zbyte, acc[l]);
+            }
+        },
+        [&](int t, int rows, int tid) {
+            if (!AHEAD) {   // one load per 128-byte line of the next tile's gradients
+                for (int q = 0; q < Q * rows; ++q) {
+                    const int64_t i = (int64_t)(t + rows) * Q + q;
+                    if (i < b && i < (int64_t)g1 * Q)
+                        touch_lines<NT>(reinterpret_cast<const char*>(g + i * m + j0), 0, nlab * 4 / 128, lds0 + (uint32_t)tg.dummy, tid);
+                }
+            }
+        });
+#pragma unroll
+    for (int l = 0; l < LPT; ++l) {
+        const int64_t row0 = j0 + (int64_t)l * NT;
+        SlotOrder<K> so;
+        so.load(perm, row0 + threadIdx.x, row0 + threadIdx.x < m);
+        store_rows<K, NT>(acc[l], grad_W + (size_t)blockIdx.y * part_stride, row0, m, k, reinterpret_cast<uint32_t*>(lds_raw), so);
+    }
 }
 
 }  // namespace usl_products

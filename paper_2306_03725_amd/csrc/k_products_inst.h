@@ -1,0 +1,52 @@
+// Instances of the forward and weight-gradient kernels for one (storage type, instances per group), included by one
+// source file each so that they compile side by side.  Defines a function that hands out the kernels by fan-in and
+// workgroup shape:  shape 0 = 256 lanes x 1 label,  1 = 512 x 64 / K,  2 = 1024 x 64 / K (64 slots of 6 bytes take 96 of
+// the 128 registers a lane of a full compute unit has; twice the slots in 512 lanes of 256 registers was slower
+// everywhere but in the forward product at K = 64).
+// Rows that leave room for one workgroup per compute unit (Q = 1) come in the wide shapes only.
+#pragma once
+#include "k_products_common.h"
+#include "k_products.h"
+
+namespace usl_products {
+
+constexpr int labels_per_lane(int K, int slots) { return slots / K < 1 ? 1 : slots / K > 8 ? 8 : slots / K; }
+
+template <int K, typename TS, int Q, bool HALVES>
+ProductKernel pick(bool backward, int shape) {
+    constexpr int L = K == 8 ? 4 : labels_per_lane(K, 64), L2 = labels_per_lane(K, 128);
+#define USL_PICK(LPT, NT)                                                                                      \
+    ProductKernel{backward ? (const void*)k_backward_weight<K, LPT, NT, TS, Q, HALVES>                          \
+                           : (const void*)k_forward<K, LPT, NT, TS, Q, HALVES>, K, LPT, NT, transpose_bytes<K, NT>()}
+    if constexpr (Q > 1) {
+        if (shape == 0) return USL_PICK(1, 256);
+        if (shape == 1) return USL_PICK(L, 512);
+        if constexpr (K == 64) {
+            if (shape == 2 && !backward) return USL_PICK(L2, 512);
+        }
+        if (shape == 2) return USL_PICK(L, 1024);
+    } else if constexpr (K < 64) {
+        if (shape == 1) return USL_PICK(1, 1024);
+        if (shape == 2 && L > 1) return USL_PICK(L, 1024);
+    } else {   // 64 slots in 128 registers would spill
+        if (shape == 1) return USL_PICK(1, 512);
+        if (shape == 2) return USL_PICK(L2, 512);
+    }
+#undef USL_PICK
+    return ProductKernel{nullptr, 0, 0, 0, 0};
+}
+
+template <typename TS, int Q, bool HALVES>
+ProductKernel pick_k(bool backward, int K, int shape) {
+    switch (K) {
+        case 8: return pick<8, TS, Q, HALVES>(backward, shape);
+        case 16: return pick<16, TS, Q, HALVES>(backward, shape);
+        case 24: return pick<24, TS, Q, HALVES>(backward, shape);
+        case 32: return pick<32, TS, Q, HALVES>(backward, shape);
+        case 48: return pick<48, TS, Q, HALVES>(backward, shape);
+        case 64: return pick<64, TS, Q, HALVES>(backward, shape);
+        default: return ProductKernel{nullptr, 0, 0, 0, 0};
+    }
+}
+
+}  // namespace usl_products

@@ -1,9 +1,10 @@
 // Bank-aware slot order for the LDS gathers of forward / backward-weight.
 //
-// In those kernels the 32 lanes of a half-wavefront own 32 consecutive labels and, at step s, all
-// read slot order[s] of their own label from the activation row in LDS.  With the slots in their
-// natural order the 32 addresses are random and collide in the 32 LDS banks (a step then costs as
-// many cycles as the fullest bank, 3.5 on average).  The sum over a label's slots may be taken in
+// In those kernels the lanes of a wavefront own consecutive labels and, at step s, all read slot
+// order[s] of their own label from the activation row in LDS: one unit of 4, 8 or 16 bytes, from bank
+// column mod 32 of 32 (of twice the width where units are 8 bytes), or column mod 16 of 16 (16 bytes).
+// With the slots in their natural order the addresses of a pass are random and collide (a step then
+// costs as many cycles as the fullest bank, 3.5 on average for 32 labels and 32 banks).  The sum over a label's slots may be taken in
 // any order, so each label gets a private permutation of its slots, chosen so that the lanes of a
 // half-wavefront hit different banks at the same step as far as possible.
 //
@@ -24,31 +25,45 @@
 
 namespace {
 
-constexpr int SCHED_GROUPS = 8;   // groups of 32 labels per workgroup of 256 lanes
+constexpr int SCHED_NT = 256;
 
-template <int K>
-__global__ void __launch_bounds__(SCHED_GROUPS * 32)
-k_schedule(const int32_t* __restrict__ idx, int64_t m, int shift, int rounds, uint8_t* __restrict__ perm) {
-    constexpr int G = SCHED_GROUPS;
+// The lanes whose reads meet in one pass of the LDS: 32 consecutive lanes (ds_read_b32, ds_read_b64), or, for
+// ds_read_b128, 16 lanes of a half-wavefront: 0-3, 12-15, 20-27 and the other 16 (measured: two lanes with different
+// rows of one bank cost a pass exactly when both are in one of these sets).  Position p of a group -> lane of the
+// half-wavefront.
+template <int GS>
+__device__ __forceinline__ int lane_of_position(int p32) {
+    if (GS == 32) return p32;
+    const int p = p32 & 15;
+    if (p32 < 16) return p < 4 ? p : p < 8 ? p + 8 : p + 12;      // 0-3, 12-15, 20-27
+    return p < 8 ? p + 4 : p < 12 ? p + 8 : p + 16;               // 4-11, 16-19, 28-31
+}
+
+// K = padded fan-in, GS = labels and banks of a group (32, or 16 where a read is 16 bytes wide); k real slots.
+template <int K, int GS>
+__global__ void __launch_bounds__(SCHED_NT)
+k_schedule(const int32_t* __restrict__ idx, int64_t m, int k, int shift, int rounds, uint8_t* __restrict__ perm) {
+    constexpr int G = SCHED_NT / GS;
+    constexpr uint32_t ALL = GS == 32 ? 0xFFFFFFFFu : (1u << (GS & 31)) - 1u;
     // per label (rows padded by 4 bytes: lanes of a group then hit different LDS banks)
-    __shared__ uint8_t slots[G][32][K + 4];   // first the bank of every slot, then my slots sorted by bank
-    __shared__ uint8_t ord[G][32][K + 4];     // slot read at step s
-    __shared__ uint8_t left_in[G][32][36];    // unused slots of mine per bank
-    __shared__ uint8_t end_of[G][32][36];     // where bank b's slots end in the sorted list
-    __shared__ int deg0[G][32];
-    __shared__ int win[G][32];
-    const int gl = threadIdx.x >> 5, lane = threadIdx.x & 31;
-    const int hs = threadIdx.x & 32;        // where my group's 32 bits sit in a wavefront ballot
-    const int64_t j = ((int64_t)blockIdx.x * G + gl) * 32 + lane;
+    __shared__ uint8_t slots[G][GS][K + 4];   // first the bank of every slot, then my slots sorted by bank
+    __shared__ __align__(16) uint8_t ord[G][GS][K + 4];     // slot read at step s
+    __shared__ uint8_t left_in[G][GS][GS + 4];    // unused slots of mine per bank
+    __shared__ uint8_t end_of[G][GS][GS + 4];     // where bank b's slots end in the sorted list
+    __shared__ int deg0[G][GS];
+    __shared__ int win[G][GS];
+    const int gl = threadIdx.x / GS, lane = threadIdx.x & (GS - 1);
+    const int hs = threadIdx.x & 63 & ~(GS - 1);        // where my group's bits sit in a wavefront ballot
+    const int64_t j = (int64_t)blockIdx.x * SCHED_NT + (threadIdx.x & ~31) + lane_of_position<GS>(threadIdx.x & 31);
     const bool valid = j < m;
     deg0[gl][lane] = 0;
-    for (int b = 0; b < 32; ++b) left_in[gl][lane][b] = 0;
+    for (int b = 0; b < GS; ++b) left_in[gl][lane][b] = 0;
     __syncthreads();
     uint8_t* mine = slots[gl][lane];
     uint8_t* cnt = left_in[gl][lane];
     uint8_t* ends = end_of[gl][lane];
-    for (int t = 0; t < K; ++t) {
-        const int b = valid ? ((idx[j * K + t] >> shift) & 31) : ((lane + t) & 31);
+    for (int t = 0; t < k; ++t) {
+        const int b = valid ? ((idx[j * k + t] >> shift) & (GS - 1)) : ((lane + t) & (GS - 1));
         mine[t] = (uint8_t)b;
         ++cnt[b];
         atomicAdd(&deg0[gl][b], 1);
@@ -56,18 +71,18 @@ k_schedule(const int32_t* __restrict__ idx, int64_t m, int shift, int rounds, ui
     uint32_t avail = 0;           // banks my unused slots read
     {   // counting sort of my slots by bank, in place through ord (free until the first step)
         int run = 0;
-        for (int b = 0; b < 32; ++b) { run += cnt[b]; ends[b] = (uint8_t)run; if (cnt[b]) avail |= 1u << b; }
+        for (int b = 0; b < GS; ++b) { run += cnt[b]; ends[b] = (uint8_t)run; if (cnt[b]) avail |= 1u << b; }
         uint8_t* tmp = ord[gl][lane];
-        for (int t = 0; t < K; ++t) tmp[t] = mine[t];
-        for (int t = K - 1; t >= 0; --t) { const int b = tmp[t]; ends[b] = (uint8_t)(ends[b] - 1); mine[ends[b]] = (uint8_t)t; }
-        for (int b = 0; b < 32; ++b) ends[b] = (uint8_t)(ends[b] + cnt[b]);   // back from starts to ends
+        for (int t = 0; t < k; ++t) tmp[t] = mine[t];
+        for (int t = k - 1; t >= 0; --t) { const int b = tmp[t]; ends[b] = (uint8_t)(ends[b] - 1); mine[ends[b]] = (uint8_t)t; }
+        for (int b = 0; b < GS; ++b) ends[b] = (uint8_t)(ends[b] + cnt[b]);   // back from starts to ends
     }
     __syncthreads();
-    auto gballot = [&](bool p) -> uint32_t { return (uint32_t)(__ballot(p) >> hs); };
+    auto gballot = [&](bool p) -> uint32_t { return (uint32_t)(__ballot(p) >> hs) & ALL; };
     volatile int* gwin = win[gl];
     // bank role
     int mydeg = deg0[gl][lane];   // slots of the group that read bank `lane` and are not used yet
-    for (int s = 0; s < K; ++s) {
+    for (int s = 0; s < k; ++s) {
         int mb = -1;              // label role: my bank at this step
         int ml = -1;              // bank role: the label that reads me at this step
         for (int r = 0; r < rounds; ++r) {
@@ -76,13 +91,13 @@ k_schedule(const int32_t* __restrict__ idx, int64_t m, int shift, int rounds, ui
             int prop = -1;
             const uint32_t cand = mb < 0 ? (avail & freeb) : 0u;
             if (cand) {           // first candidate bank at or after a lane- and round-dependent start
-                const int sh = (lane + 7 * r) & 31;
-                const uint32_t rc = (cand >> sh) | (cand << ((32 - sh) & 31));
-                prop = (__ffs(rc) - 1 + sh) & 31;
+                const int sh = (lane + 7 * r) & (GS - 1);
+                const uint32_t rc = ((cand >> sh) | (cand << ((GS - sh) & (GS - 1)))) & ALL;
+                prop = (__ffs(rc) - 1 + sh) & (GS - 1);
                 atomicMin(&win[gl][prop], lane);
             }
             const int w = gwin[lane];
-            if (ml < 0 && w < 32) ml = w;
+            if (ml < 0 && w < GS) ml = w;
             if (prop >= 0 && gwin[prop] == lane) mb = prop;
         }
         // augmenting paths from the banks still free
@@ -99,7 +114,7 @@ k_schedule(const int32_t* __restrict__ idx, int64_t m, int shift, int rounds, ui
                 if (reach) par = __ffs(avail & front) - 1;
                 const uint32_t fresh = gballot(reach);
                 const uint32_t fresh_free = gballot(reach && mb < 0);
-                const uint32_t next = gballot(ml >= 0 && ((fresh >> (ml & 31)) & 1u));
+                const uint32_t next = gballot(ml >= 0 && ((fresh >> (ml & (GS - 1))) & 1u));
                 seen |= fresh;
                 if (searching) {
                     if (fresh_free) { found = __ffs(fresh_free) - 1; searching = false; }
@@ -111,8 +126,8 @@ k_schedule(const int32_t* __restrict__ idx, int64_t m, int shift, int rounds, ui
             while (__any(cur >= 0)) {
                 const bool a = cur >= 0;
                 const int cl = a ? cur : 0;
-                const int b = __shfl(par, cl, 32) & 31;
-                const int prev = __shfl(ml, b, 32);
+                const int b = __shfl(par, cl, GS) & (GS - 1);
+                const int prev = __shfl(ml, b, GS);
                 if (a) {
                     if (lane == cl) mb = b;
                     if (lane == b) ml = cl;
@@ -127,12 +142,12 @@ k_schedule(const int32_t* __restrict__ idx, int64_t m, int shift, int rounds, ui
             const bool a = left != 0;
             const int l = a ? __ffs(left) - 1 : 0;
             left &= left - 1;
-            const uint32_t av = (uint32_t)__shfl((int)avail, l, 32);
+            const uint32_t av = (uint32_t)__shfl((int)avail, l, GS);
             int key = (a && ((av >> lane) & 1u)) ? (((255 - myload) << 17) | (mydeg << 5) | lane) : -1;
 #pragma unroll
-            for (int o = 16; o > 0; o >>= 1) key = max(key, __shfl_xor(key, o, 32));
+            for (int o = GS / 2; o > 0; o >>= 1) key = max(key, __shfl_xor(key, o, GS));
             if (a && key >= 0) {
-                const int bb = key & 31;
+                const int bb = key & (GS - 1);
                 if (lane == l) mb = bb;
                 if (lane == bb) ++myload;
             }
@@ -143,43 +158,48 @@ k_schedule(const int32_t* __restrict__ idx, int64_t m, int shift, int rounds, ui
         ord[gl][lane][s] = (uint8_t)pick;
         mydeg -= myload;
     }
-    if (valid)
-        for (int s = 0; s < K; ++s) perm[j * K + s] = ord[gl][lane][s];
+    if (valid) {   // steps past k: the padding slots
+        for (int s = k; s < K; ++s) ord[gl][lane][s] = (uint8_t)s;
+        const uint32_t* from = reinterpret_cast<const uint32_t*>(ord[gl][lane]);
+        uint32_t* to = reinterpret_cast<uint32_t*>(perm + j * K);
+#pragma unroll
+        for (int q = 0; q < K / 4; ++q) to[q] = from[q];
+    }
 }
 
 // slots in stored order (tuning aid: what the gathers cost without a bank-aware order)
-__global__ void k_identity_order(int64_t m, int k, uint8_t* __restrict__ perm) {
-    const int64_t N = m * k;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < N; e += (int64_t)gridDim.x * blockDim.x)
-        perm[e] = (uint8_t)(e % k);
+__global__ void k_identity_order(int64_t n, int K, uint8_t* __restrict__ perm) {
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x)
+        perm[e] = (uint8_t)(e % K);
 }
 
 }  // namespace
 
-// Fills ctx->slot_order for the connectivity in idx (fast-path shapes only: k in {8,16,32,64}).
-usl_status usl_build_slot_order(usl_ctx* c, const int32_t* idx) {
-    const size_t N = (size_t)c->m * c->k;
-    if (!c->slot_order) {
-        size_t cap = 0;
-        USL_TRY(usl_reserve(c, (void**)&c->slot_order, &cap, N));
-    }
-    const int shift = c->storage == USL_F32 ? 0 : 1;  // two bfloat16 columns share a bank word
+// Fills ctx->slot_order for the connectivity in idx.
+usl_status usl_build_slot_order(usl_ctx* c, const int32_t* idx, int K, int unit) {
+    USL_TRY(usl_reserve(c, (void**)&c->slot_order, &c->slot_order_cap, (size_t)c->m * K));
+    const int shift = unit == 2 ? 1 : 0;  // two single bfloat16 columns share a bank word
     int rounds = 3;
     if (const char* e = getenv("USL_TUNE_ROUNDS")) rounds = atoi(e);   // 0 = slots in stored order
-    const int64_t groups = (c->m + 31) / 32;
-    const unsigned grid = (unsigned)((groups + SCHED_GROUPS - 1) / SCHED_GROUPS);
+    const unsigned grid = (unsigned)((c->m + SCHED_NT - 1) / SCHED_NT);
     if (rounds <= 0) {
-        hipLaunchKernelGGL(k_identity_order, dim3(c->num_cu * 4), dim3(256), 0, c->stream, c->m, c->k, c->slot_order);
+        hipLaunchKernelGGL(k_identity_order, dim3(c->num_cu * 4), dim3(256), 0, c->stream, c->m * K, K, c->slot_order);
     } else {
-#define USL_SCHED(K) \
-    hipLaunchKernelGGL((k_schedule<K>), dim3(grid), dim3(SCHED_GROUPS * 32), 0, c->stream, idx, c->m, shift, rounds, \
-                       c->slot_order)
-        switch (c->k) {
-            case 8: USL_SCHED(8); break;
-            case 16: USL_SCHED(16); break;
-            case 32: USL_SCHED(32); break;
-            case 64: USL_SCHED(64); break;
-            default: USL_FAIL(c, USL_EUNSUPPORTED, "no slot order for k=%d", c->k);
+#define USL_SCHED(KK)                                                                                                          \
+    case KK:                                                                                                                   \
+        if (unit == 16)                                                                                                        \
+            hipLaunchKernelGGL((k_schedule<KK, 16>), dim3(grid), dim3(SCHED_NT), 0, c->stream, idx, c->m, c->k, shift, rounds, c->slot_order); \
+        else                                                                                                                   \
+            hipLaunchKernelGGL((k_schedule<KK, 32>), dim3(grid), dim3(SCHED_NT), 0, c->stream, idx, c->m, c->k, shift, rounds, c->slot_order); \
+        break
+        switch (K) {
+            USL_SCHED(8);
+            USL_SCHED(16);
+            USL_SCHED(24);
+            USL_SCHED(32);
+            USL_SCHED(48);
+            USL_SCHED(64);
+            default: USL_FAIL(c, USL_EUNSUPPORTED, "no slot order for a padded fan-in of %d", K);
         }
 #undef USL_SCHED
     }

@@ -33,7 +33,7 @@ extern "C" usl_status usl_destroy(usl_ctx* c) {
         void* bufs[] = {c->bce_partials, c->sel_hist, c->prune_flags, c->tie_counts, c->counter64,
                         c->csc_ptr, c->csc_cursor, c->csc_order, c->csc_slot, c->csc_w, c->gT, c->gxT, c->nz_flags,
                         c->slot_order, c->topk_cand, c->sub_idx, c->sub_W, c->predict_out, c->gw_part,
-                        c->nz_state, c->nz_lab, c->nz_val, c->idx_print};
+                        c->nz_state, c->nz_lab, c->nz_val, c->idx_print, c->xi};
         (void)hipStreamSynchronize(c->stream);
         for (void* p : bufs)
             if (p) (void)hipFree(p);
@@ -259,6 +259,7 @@ static usl_status subset_context(usl_ctx* c, int64_t n, const int32_t* idx, cons
     }
     usl_ctx* sub = c->sub;
     sub->stream = c->stream;
+    sub->no_order = true;
     usl_status s = usl_prepare_device(sub);
     if (s != USL_OK) USL_FAIL(c, s, "%s", sub->err);
     sub->csc_built_for = nullptr;
@@ -387,6 +388,12 @@ extern "C" usl_status usl_train_step(usl_ctx* c, const void* x, const int32_t* i
     if (!(eps >= 0.f) || !(lr == lr)) USL_FAIL(c, USL_EINVAL, "eps < 0 or lr is NaN");
     USL_TRY(check_batch(c, b));
     USL_TRY(usl_prepare_device(c));
+    // the interleaved copy of x that forward makes serves the weight gradient of this call too
+    struct KeepX {
+        usl_ctx* c;
+        explicit KeepX(usl_ctx* c_) : c(c_) { c->xi_keep = true; c->xi_of = nullptr; }
+        ~KeepX() { c->xi_keep = false; c->xi_of = nullptr; }
+    } keep_x(c);
     USL_TRY(usl_launch_forward(c, x, idx, W, g, b));
     if (grad_x) {
         // The loss writes the gradient in place and, group of 256 instances by group, as the tile-major pieces the

@@ -37,8 +37,12 @@ struct usl_ctx {
     int csc_win_labels;       // labels per window the lists were built with
     const int32_t* csc_built_for;  // idx pointer the lists were built from (NULL = stale)
     // bank-aware order in which a label's slots are visited by the LDS gathers (performance only)
-    uint8_t* slot_order;           // [m*k] slot read at step s
+    uint8_t* slot_order;      size_t slot_order_cap;   // [m][padded k] slot read at step s
     const int32_t* slot_order_for; // idx pointer it was computed from (NULL = stale)
+    bool no_order;                 // label-subset context: idx is new on every call, an order would not pay
+    void* xi;                 size_t xi_cap;   // activations interleaved for the LDS gathers (k_products.hip)
+    bool xi_keep;                  // inside usl_train_step: the copy that forward makes serves the weight gradient
+    const void* xi_of;             // x that xi holds (only set inside usl_train_step), else NULL
     float* gT;                size_t gT_cap;   // [tiles][m][32] upstream gradient, one 128-byte piece per (tile of 32 instances, label)
     uint8_t* nz_flags;        size_t nz_flags_cap;   // [tiles][m] 1 = that 32-instance piece of gT is not all zero
     // label-subset calls: a child context sized for the subset, and the subset's rows of idx / W
@@ -107,7 +111,8 @@ usl_status usl_prepare_device(usl_ctx* ctx);
 usl_status usl_reserve(usl_ctx* ctx, void** buf, size_t* cap, size_t bytes);
 usl_status usl_check_launch(usl_ctx* ctx, const char* what);
 
-usl_status usl_build_slot_order(usl_ctx* ctx, const int32_t* idx);
+// K = padded fan-in, unit = bytes per column of the rows that will be gathered (4, 8 or 16; 2: single bfloat16)
+usl_status usl_build_slot_order(usl_ctx* ctx, const int32_t* idx, int K, int unit);
 
 // Kernel launchers (one per file).  All take validated arguments.
 usl_status usl_launch_forward(usl_ctx* ctx, const void* x, const int32_t* idx, const void* W,
