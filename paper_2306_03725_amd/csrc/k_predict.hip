@@ -10,8 +10,8 @@
 namespace {
 
 constexpr int TK_NT = 256;             // lanes per workgroup
-constexpr int TK_EPT = 64;             // scores a lane holds in registers
-constexpr int TK_SEG = TK_NT * TK_EPT; // labels per workgroup
+// scores a lane holds in registers: 64, or 8 where that would leave most of the chip without a workgroup
+constexpr int TK_EPT = 64, TK_EPT_FEW = 8;
 constexpr int TK_MAX = 32;             // largest kk
 
 __device__ __forceinline__ uint64_t score_key(float z, uint32_t label) {
@@ -37,20 +37,21 @@ __device__ __forceinline__ uint64_t block_max(uint64_t v, uint64_t* red) {
     return r;
 }
 
-// The kk best keys of one segment of TK_SEG labels of one row, best first, into cand[row][segment][kk]
+// The kk best keys of one segment of 256 * TK_EPT labels of one row, best first, into cand[row][segment][kk]
 // (0 where the segment has fewer than kk labels).
-//   1. every lane loads its 64 scores (all loads in flight at once) and finds its own best key;
+//   1. every lane loads its TK_EPT scores (all loads in flight at once) and finds its own best key;
 //   2. tau = the kk-th best of the 256 lane maxima: at least kk keys of the segment are >= tau, and
-//      every key >= tau belongs to one of the kk lanes whose maximum is >= tau, so at most kk*64 keys pass;
+//      every key >= tau belongs to one of the kk lanes whose maximum is >= tau, so at most kk*TK_EPT keys pass;
 //   3. those keys are collected in LDS and the best kk are peeled off one by one ("largest key below the
 //      previous winner": keys are distinct, so nothing has to be removed).
-// VEC: rows are 16-byte aligned and m % 4 == 0, so a lane reads 16 groups of 4 consecutive labels.
-template <bool VEC>
+// VEC: rows are 16-byte aligned and m % 4 == 0, so a lane reads groups of 4 consecutive labels.
+template <bool VEC, int TK_EPT>
 __global__ void __launch_bounds__(TK_NT)
 k_topk_segments(const float* __restrict__ out, int64_t m, int kk, int nseg, uint64_t* __restrict__ cand) {
     __shared__ uint64_t red[TK_NT / 64];
     __shared__ uint64_t list[TK_MAX * TK_EPT];
     __shared__ uint32_t count;
+    constexpr int TK_SEG = TK_NT * TK_EPT;   // labels per workgroup
     const int64_t seg0 = (int64_t)blockIdx.x * TK_SEG;
     const float* row = out + (int64_t)blockIdx.y * m + seg0;
     const int lim = (int)min((int64_t)TK_SEG, m - seg0);   // labels of this segment that exist
@@ -116,21 +117,30 @@ k_topk_segments(const float* __restrict__ out, int64_t m, int kk, int nseg, uint
 }
 
 // One workgroup per row: the best kk of the row's nseg*kk candidate keys, unpacked.  The score is read
-// back from out so that it keeps its own bits (a -0 stays -0).
+// back from out so that it keeps its own bits (a -0 stays -0).  A launch of its own: merged by the workgroup
+// that finishes a row's last segment, one row of 500k scores took 14.6 us instead of 7.5 + 5.2 (the
+// candidates then have to be made visible across the L2s by every workgroup).
 __global__ void __launch_bounds__(TK_NT)
 k_topk_merge(const uint64_t* __restrict__ cand, int n, int kk, const float* __restrict__ out, int64_t m,
              int32_t* __restrict__ top_lab, float* __restrict__ top_val) {
     __shared__ uint64_t red[TK_NT / 64];
     const uint64_t* c = cand + (size_t)blockIdx.x * n;
+    constexpr int HELD = 8;   // candidates a lane keeps in registers; only very wide rows have more
+    uint64_t mine[HELD];
+#pragma unroll
+    for (int e = 0; e < HELD; ++e) mine[e] = e * TK_NT + (int)threadIdx.x < n ? c[e * TK_NT + threadIdx.x] : 0ull;
     uint64_t prev = ~0ull;
     for (int r = 0; r < kk; ++r) {
         uint64_t best = 0;
-        for (int q = threadIdx.x; q < n; q += TK_NT) {
+#pragma unroll
+        for (int e = 0; e < HELD; ++e)
+            if (mine[e] < prev && mine[e] > best) best = mine[e];
+        for (int q = HELD * TK_NT + (int)threadIdx.x; q < n; q += TK_NT) {
             const uint64_t key = c[q];
             if (key < prev && key > best) best = key;
         }
         prev = block_max(best, red);
-        if (threadIdx.x == 0) {
+        if ((int)threadIdx.x == r) {   // a lane per rank: the reads of the scores do not wait for each other
             const uint32_t label = ~(uint32_t)prev;
             top_lab[(size_t)blockIdx.x * kk + r] = (int32_t)label;
             top_val[(size_t)blockIdx.x * kk + r] = out[(int64_t)blockIdx.x * m + label];
@@ -161,15 +171,21 @@ int usl_topk_max(void) { return TK_MAX; }
 
 usl_status usl_launch_topk(usl_ctx* c, const float* out, int32_t b, int32_t kk, int32_t* top_lab,
                            float* top_val) {
-    const int nseg = (int)((c->m + TK_SEG - 1) / TK_SEG);
+    auto segments = [&](int ept) { return (int)((c->m + TK_NT * ept - 1) / (TK_NT * ept)); };
+    // short segments where long ones would not give every compute unit a workgroup (one row of 500k scores: 31 of 256
+    // busy, 11 us; 7.5 with short ones)
+    const bool few = (int64_t)segments(TK_EPT) * b < c->num_cu;
+    const int nseg = segments(few ? TK_EPT_FEW : TK_EPT);
     // sized once for the largest batch and the largest kk, so that no later call has to grow it (growing waits for the stream)
-    USL_TRY(usl_reserve(c, (void**)&c->topk_cand, &c->topk_cand_cap, (size_t)c->max_b * nseg * TK_MAX * 8));
-    if (c->m % 4 == 0 && (uintptr_t)out % 16 == 0)
-        hipLaunchKernelGGL(k_topk_segments<true>, dim3((unsigned)nseg, (unsigned)b), dim3(TK_NT), 0, c->stream, out,
-                           c->m, (int)kk, nseg, c->topk_cand);
-    else
-        hipLaunchKernelGGL(k_topk_segments<false>, dim3((unsigned)nseg, (unsigned)b), dim3(TK_NT), 0, c->stream, out,
-                           c->m, (int)kk, nseg, c->topk_cand);
+    const size_t most = (size_t)segments(TK_EPT) * c->max_b, most_few = (size_t)segments(TK_EPT_FEW) * (c->num_cu / segments(TK_EPT) + 1);
+    USL_TRY(usl_reserve(c, (void**)&c->topk_cand, &c->topk_cand_cap, (most > most_few ? most : most_few) * TK_MAX * 8));
+    const bool vec = c->m % 4 == 0 && (uintptr_t)out % 16 == 0;
+#define USL_TOPK(VEC, EPT)                                                                                                   \
+    hipLaunchKernelGGL((k_topk_segments<VEC, EPT>), dim3((unsigned)nseg, (unsigned)b), dim3(TK_NT), 0, c->stream, out, c->m, \
+                       (int)kk, nseg, c->topk_cand)
+    if (few) { if (vec) USL_TOPK(true, TK_EPT_FEW); else USL_TOPK(false, TK_EPT_FEW); }
+    else { if (vec) USL_TOPK(true, TK_EPT); else USL_TOPK(false, TK_EPT); }
+#undef USL_TOPK
     hipLaunchKernelGGL(k_topk_merge, dim3((unsigned)b), dim3(TK_NT), 0, c->stream, c->topk_cand, nseg * kk,
                        (int)kk, out, c->m, top_lab, top_val);
     return usl_check_launch(c, "topk");

@@ -41,9 +41,8 @@ static constexpr int HALF_COLS = 32768;                 // columns per half of a
 // moves 1 KiB per instruction, no registers are used, all of it is in flight together.  In the last instruction the
 // lanes past the end are masked off.  The caller waits (vmcnt) before its barrier.  Inline assembly: behind the builtin
 // the compiler waits for the copy before the next LDS read of any address, so nothing would overlap it.
-template <int NT>
-__device__ __forceinline__ void stage_async(const char* __restrict__ src, uint32_t lds, int nbytes, int tid) {
-    for (int v = (tid >> 6) * 1024; v < nbytes; v += (NT / 64) * 1024) {
+__device__ __forceinline__ void stage_async(const char* __restrict__ src, uint32_t lds, int nbytes, int tid, int nt) {
+    for (int v = (tid >> 6) * 1024; v < nbytes; v += (nt / 64) * 1024) {
         const uint32_t off = (uint32_t)(v + (tid & 63) * 16);
         const uint32_t to = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds + (uint32_t)v));
         if ((int)off < nbytes)
@@ -598,8 +597,8 @@ __device__ __forceinline__ void walk(const char* __restrict__ xi, uint32_t lds0,
                 int tid = (int)threadIdx.x;
                 asm volatile("" : "+v"(tid));
                 __syncthreads();
-                if (HALVES) stage_async<NT>(row + (part ? HB : 0), lds0, part ? tg.row_bytes - HB : HB, tid);
-                else stage_async<NT>(row, lds0, tg.row_bytes, tid);
+                if (HALVES) stage_async(row + (part ? HB : 0), lds0, part ? tg.row_bytes - HB : HB, tid, NT);
+                else stage_async(row, lds0, tg.row_bytes, tid, NT);
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 __syncthreads();
                 if ((!HALVES || part == 1) && g + 1 < g1) warm_slice<NT>(row + tg.row_bytes, tg.row_bytes, per, ws.slice, dummy, tid);
@@ -614,7 +613,7 @@ __device__ __forceinline__ void walk(const char* __restrict__ xi, uint32_t lds0,
     const int per = ws.per(tg.tile_rows * tg.row_bytes);
     uint32_t base = lds0, other = lds0 + (uint32_t)tg.buf_bytes;
     __syncthreads();
-    if (two && g0 < g1) stage_async<NT>(xi + (size_t)g0 * tg.row_bytes, base, min(tg.tile_rows, g1 - g0) * tg.row_bytes, (int)threadIdx.x);
+    if (two && g0 < g1) stage_async(xi + (size_t)g0 * tg.row_bytes, base, min(tg.tile_rows, g1 - g0) * tg.row_bytes, (int)threadIdx.x, NT);
 #pragma unroll 1
     for (int t = g0; t < g1; t += tg.tile_rows) {
         int tid = (int)threadIdx.x;
@@ -622,12 +621,12 @@ __device__ __forceinline__ void walk(const char* __restrict__ xi, uint32_t lds0,
         const int rows = min(tg.tile_rows, g1 - t), next = t + tg.tile_rows, after = two ? next + tg.tile_rows : next;
         if (!two) {
             __syncthreads();   // the buffer is no longer read
-            stage_async<NT>(xi + (size_t)t * tg.row_bytes, base, rows * tg.row_bytes, tid);
+            stage_async(xi + (size_t)t * tg.row_bytes, base, rows * tg.row_bytes, tid, NT);
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this tile has landed
         __syncthreads();                                   // (two buffers: and the other one is no longer read)
         if (two && next < g1)
-            stage_async<NT>(xi + (size_t)next * tg.row_bytes, other, min(tg.tile_rows, g1 - next) * tg.row_bytes, tid);
+            stage_async(xi + (size_t)next * tg.row_bytes, other, min(tg.tile_rows, g1 - next) * tg.row_bytes, tid, NT);
         if (after < g1)
             warm_slice<NT>(xi + (size_t)after * tg.row_bytes, min(tg.tile_rows, g1 - after) * tg.row_bytes, per, ws.slice, dummy, tid);
         late(t, rows, tid);

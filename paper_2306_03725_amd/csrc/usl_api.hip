@@ -205,7 +205,10 @@ extern "C" usl_status usl_predict(usl_ctx* c, const void* x, const int32_t* idx,
     const size_t xrow = (size_t)c->d * (c->storage == USL_F32 ? 4 : 2);
     for (int i0 = 0; i0 < b; i0 += chunk) {
         const int n = b - i0 < chunk ? b - i0 : chunk;
-        USL_TRY(usl_launch_forward(c, (const char*)x + (size_t)i0 * xrow, idx, W, c->predict_out, n));
+        c->part_of_batch = n < b;
+        const usl_status s = usl_launch_forward(c, (const char*)x + (size_t)i0 * xrow, idx, W, c->predict_out, n);
+        c->part_of_batch = false;
+        USL_TRY(s);
         USL_TRY(usl_launch_topk(c, c->predict_out, n, kk, top_lab + (size_t)i0 * kk, top_val + (size_t)i0 * kk));
     }
     return USL_OK;

@@ -39,6 +39,7 @@ struct usl_ctx {
     // bank-aware order in which a label's slots are visited by the LDS gathers (performance only)
     uint8_t* slot_order;      size_t slot_order_cap;   // [m][padded k] slot read at step s
     const int32_t* slot_order_for; // idx pointer it was computed from (NULL = stale)
+    bool part_of_batch;            // usl_predict's chunks: the sums are taken in the order of a whole batch's, however short the chunk
     bool no_order;                 // label-subset context: idx is new on every call, an order would not pay
     void* xi;                 size_t xi_cap;   // activations interleaved for the LDS gathers (k_products.hip)
     bool xi_keep;                  // inside usl_train_step: the copy that forward makes serves the weight gradient
