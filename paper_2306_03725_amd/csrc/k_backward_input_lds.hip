@@ -44,16 +44,16 @@ constexpr uint32_t PAD_SLOT = 0xFFFFFFFFu;
 constexpr size_t LDS_BYTES = (size_t)32768 * 4 + (size_t)2048 * 4 + (size_t)1024 * 4 + (size_t)1024 * 8 + (size_t)1024 * 8 + 128;
 constexpr uint32_t ZERO_LABEL = (uint32_t)((LDS_BYTES - 128) / 4);
 static_assert(ZERO_LABEL % 32 == 0 && ZERO_LABEL + 31 < 65536 && LDS_BYTES <= 160 * 1024, "zero words: bank b, 16-bit label, inside LDS");
-// LDS of the kernel for both backward products, which stages two rows of g at a time: two row buffers RS2 bytes apart
-// (so that one address and the 16-bit offset field of a ds_read reach both), each ending in 32 zero words (ZERO_LABEL2
-// is their "label": a window has at most that many labels), 2 * NF floats for the sums of the two instances, NT words
+// LDS of the kernel for both backward products, which stages two rows of g at a time, interleaved: label l's two values are
+// the 8 bytes at 8 * l (one ds_read_b64 brings both), behind them 32 pairs of zeros (ZERO_LABEL2 is their "label": a window
+// has at most that many labels); RS2 bytes per row; 2 * NF floats for the sums of the two instances, NT words
 // (features), NEAR2 overflow entries of 8 bytes, 2 * NT words (each lane's share of them), NEAR2 floats (their
 // weight-gradient sums).
 constexpr int RS2 = 64000;
 constexpr uint32_t ZERO_LABEL2 = (RS2 - 128) / 4;
 constexpr int NEAR2 = 512;
 constexpr size_t LDS2_BYTES = (size_t)2 * RS2 + (size_t)2 * 2048 * 4 + (size_t)1024 * 4 + (size_t)NEAR2 * 8 + (size_t)2 * 1024 * 4 + (size_t)NEAR2 * 4;
-static_assert(ZERO_LABEL2 % 32 == 0 && RS2 < 65536 && RS2 % 16 == 0 && LDS2_BYTES <= 160 * 1024, "two row buffers within one ds_read offset, inside LDS");
+static_assert(ZERO_LABEL2 % 32 == 0 && RS2 % 16 == 0 && LDS2_BYTES <= 160 * 1024, "zero pairs on their banks, a row of units inside LDS");
 template <int KT> struct ListLayout;   // what depends on which kernel the lists are for
 template <> struct ListLayout<68> { static constexpr uint32_t zero_label = ZERO_LABEL; static constexpr uint32_t near = 1024; };
 template <> struct ListLayout<36> { static constexpr uint32_t zero_label = ZERO_LABEL2; static constexpr uint32_t near = NEAR2; };
@@ -683,54 +683,49 @@ k_bwi_lds(const float* __restrict__ g, const TS* __restrict__ W, int64_t m, int 
 // that the lane keeps per slot over the whole batch (Algorithm 3) and stores at the end -- every slot of the layer
 // belongs to exactly one list of one workgroup, so every weight gradient is written once, without atomics.  The third
 // register per slot halves the slots (KT_BOTH = 36) and with them the windows; the row buffer then has room for the
-// slices of two instances, RS2 bytes apart, and a pass of the loop does two instances: one address, two reads (the
-// second through the instruction's offset field), four multiply-adds.  A pass is then long enough again for the
-// warm-up of the next rows to arrive in time (with one instance per pass of half the length it was not: the kernel
-// took 1.46 ms at m = 500k).
+// slices of two instances, and a pass of the loop does two instances.  They lie interleaved, so a slot costs one address,
+// one ds_read_b64 and four multiply-adds: 64 random 8-byte reads take LDS no longer than 64 random 4-byte ones (before,
+// with the slices one behind the other and two ds_read_b32, usl_backward took 1408 us at m = 500k, d = 32k, k = 32,
+// b = 256 and 6662 us at m = 670k, k = 64, b = 512; now 1319 and 6068).  What bounds it now: a pass of 3.3 us is about
+// 1.4 us of row copies at the L2 -> LDS rate, 1.3 of gathers, the rest barriers and the sums on their way out, one after the
+// other; with neither copies nor gathers 1.7 us remain, the trip to memory of the warm-up loads.
 // The sums of overflow entries live in LDS (ov_sum) or, beyond the NEAR2 that LDS holds, in memory (ovgw).
 __device__ __forceinline__ void gather4_two(float& acc0, float& acc1, float& s0, float& s1, float& s2, float& s3,
                                             uint32_t p0, uint32_t p1, float w0, float w1, float w2, float w3, float x0, float x1) {
-    uint32_t a0, a1, a2, a3, b0, b1, b2, b3;
-    const uint32_t two = 2;
+    const uint32_t three = 3;
     asm volatile(
-        "v_lshlrev_b32_sdwa %6, %14, %15 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
-        "v_lshlrev_b32_sdwa %7, %14, %15 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
-        "v_lshlrev_b32_sdwa %8, %14, %16 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
-        "v_lshlrev_b32_sdwa %9, %14, %16 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
-        "ds_read_b32 %10, %6 offset:64000\n\t"
-        "ds_read_b32 %6, %6\n\t"
-        "ds_read_b32 %11, %7 offset:64000\n\t"
-        "ds_read_b32 %7, %7\n\t"
-        "ds_read_b32 %12, %8 offset:64000\n\t"
-        "ds_read_b32 %8, %8\n\t"
-        "ds_read_b32 %13, %9 offset:64000\n\t"
-        "ds_read_b32 %9, %9\n\t"
-        "s_waitcnt lgkmcnt(6)\n\t"
-        "v_fmac_f32 %0, %17, %6\n\t"
-        "v_fmac_f32 %1, %17, %10\n\t"
-        "v_fmac_f32 %2, %21, %6\n\t"
-        "v_fmac_f32 %2, %22, %10\n\t"
-        "s_waitcnt lgkmcnt(4)\n\t"
-        "v_fmac_f32 %0, %18, %7\n\t"
-        "v_fmac_f32 %1, %18, %11\n\t"
-        "v_fmac_f32 %3, %21, %7\n\t"
-        "v_fmac_f32 %3, %22, %11\n\t"
+        "v_lshlrev_b32_sdwa v112, %6, %7 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
+        "v_lshlrev_b32_sdwa v114, %6, %7 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
+        "v_lshlrev_b32_sdwa v116, %6, %8 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
+        "v_lshlrev_b32_sdwa v118, %6, %8 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
+        "ds_read_b64 v[112:113], v112\n\t"
+        "ds_read_b64 v[114:115], v114\n\t"
+        "ds_read_b64 v[116:117], v116\n\t"
+        "ds_read_b64 v[118:119], v118\n\t"
+        "s_waitcnt lgkmcnt(3)\n\t"
+        "v_fmac_f32 %0, %9, v112\n\t"
+        "v_fmac_f32 %1, %9, v113\n\t"
+        "v_fmac_f32 %2, %13, v112\n\t"
+        "v_fmac_f32 %2, %14, v113\n\t"
         "s_waitcnt lgkmcnt(2)\n\t"
-        "v_fmac_f32 %0, %19, %8\n\t"
-        "v_fmac_f32 %1, %19, %12\n\t"
-        "v_fmac_f32 %4, %21, %8\n\t"
-        "v_fmac_f32 %4, %22, %12\n\t"
+        "v_fmac_f32 %0, %10, v114\n\t"
+        "v_fmac_f32 %1, %10, v115\n\t"
+        "v_fmac_f32 %3, %13, v114\n\t"
+        "v_fmac_f32 %3, %14, v115\n\t"
+        "s_waitcnt lgkmcnt(1)\n\t"
+        "v_fmac_f32 %0, %11, v116\n\t"
+        "v_fmac_f32 %1, %11, v117\n\t"
+        "v_fmac_f32 %4, %13, v116\n\t"
+        "v_fmac_f32 %4, %14, v117\n\t"
         "s_waitcnt lgkmcnt(0)\n\t"
-        "v_fmac_f32 %0, %20, %9\n\t"
-        "v_fmac_f32 %1, %20, %13\n\t"
-        "v_fmac_f32 %5, %21, %9\n\t"
-        "v_fmac_f32 %5, %22, %13"
-        : "+v"(acc0), "+v"(acc1), "+v"(s0), "+v"(s1), "+v"(s2), "+v"(s3),
-          "=&v"(a0), "=&v"(a1), "=&v"(a2), "=&v"(a3), "=&v"(b0), "=&v"(b1), "=&v"(b2), "=&v"(b3)
-        : "s"(two), "v"(p0), "v"(p1), "v"(w0), "v"(w1), "v"(w2), "v"(w3), "v"(x0), "v"(x1)
-        : "memory");
+        "v_fmac_f32 %0, %12, v118\n\t"
+        "v_fmac_f32 %1, %12, v119\n\t"
+        "v_fmac_f32 %5, %13, v118\n\t"
+        "v_fmac_f32 %5, %14, v119"
+        : "+v"(acc0), "+v"(acc1), "+v"(s0), "+v"(s1), "+v"(s2), "+v"(s3)
+        : "s"(three), "v"(p0), "v"(p1), "v"(w0), "v"(w1), "v"(w2), "v"(w3), "v"(x0), "v"(x1)
+        : "memory", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119");
 }
-static_assert(RS2 == 64000, "the offset of the second row buffer is written into gather4_two");
 
 template <typename TS>
 __global__ void __launch_bounds__(NT)
@@ -772,27 +767,26 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
         }
     }
     const uint32_t ov0 = ov_base[wg], ov_n = ov_base[wg + 1] - ov0;
-    float* row = reinterpret_cast<float*>(lds_raw);                       // row[label], row[RS2 / 4 + label]
+    float2* row = reinterpret_cast<float2*>(lds_raw);                     // row[label]: the two instances of a pass
     float* outbuf = reinterpret_cast<float*>(lds_raw + 2 * RS2);          // [2][NF]
     uint32_t* feat_of = reinterpret_cast<uint32_t*>(outbuf + 2 * NF);     // [NT]
-    uint2* ov_near = reinterpret_cast<uint2*>(feat_of + NT);              // [NEAR2] {address of the label in row 0, weight}
+    uint2* ov_near = reinterpret_cast<uint2*>(feat_of + NT);              // [NEAR2] {address of the label in the row, weight}
     uint32_t* ovr_a = reinterpret_cast<uint32_t*>(ov_near + NEAR2);       // [NT] start | n << 16
     uint32_t* ovr_b = ovr_a + NT;
     float* ov_sum = reinterpret_cast<float*>(ovr_b + NT);                 // [NEAR2]
     feat_of[threadIdx.x] = (uint32_t)feat[(wg * 2 + 0) * NT + threadIdx.x] | (uint32_t)feat[(wg * 2 + 1) * NT + threadIdx.x] << 16;
     if (threadIdx.x < NEAR2) {
-        uint2 e = make_uint2(ZERO_LABEL2 * 4u, 0u);
+        uint2 e = make_uint2(ZERO_LABEL2 * 8u, 0u);
         if (threadIdx.x < ov_n) {
             const OvEntry o = ov[(size_t)ov0 + threadIdx.x];
-            e = make_uint2((uint32_t)o.label * 4u, o.slot == PAD_SLOT ? 0u : __float_as_uint(usl_load_f32<TS>(W, (size_t)o.slot)));
+            e = make_uint2((uint32_t)o.label * 8u, o.slot == PAD_SLOT ? 0u : __float_as_uint(usl_load_f32<TS>(W, (size_t)o.slot)));
         }
         ov_near[threadIdx.x] = e;
         ov_sum[threadIdx.x] = 0.f;
     }
     ovr_a[threadIdx.x] = ovr[(wg * 2 + 0) * NT + threadIdx.x];
     ovr_b[threadIdx.x] = ovr[(wg * 2 + 1) * NT + threadIdx.x];
-    if (threadIdx.x < 64)   // the zero words behind both row buffers
-        reinterpret_cast<uint32_t*>(lds_raw)[ZERO_LABEL2 + (threadIdx.x >> 5) * (RS2 / 4) + (threadIdx.x & 31)] = 0u;
+    if (threadIdx.x < 32) row[ZERO_LABEL2 + threadIdx.x] = make_float2(0.f, 0.f);   // what empty places read
     for (uint32_t q = NEAR2 + threadIdx.x; q < ov_n; q += NT) ovgw[(size_t)ov0 + q] = 0.f;   // entry q is lane q % NT's
     const int nl = (int)min((int64_t)wl, m - (int64_t)w * wl);   // labels of this window (the last one may be short)
     const int nv = nl / 4;                                       // 16-byte pieces of a row slice
@@ -802,10 +796,8 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
     auto more = [&](float& acc0, float& acc1, uint32_t r, float x0, float x1) {
         for (uint32_t q = r & 0xFFFFu, e = q + (r >> 16); q < e; q += 2) {
             const uint2 o0 = ov_near[q], o1 = ov_near[q + 1];
-            const float u0 = *reinterpret_cast<lds_f32_t*>(static_cast<uintptr_t>(o0.x));
-            const float u1 = *reinterpret_cast<lds_f32_t*>(static_cast<uintptr_t>(o0.x + RS2));
-            const float v0 = *reinterpret_cast<lds_f32_t*>(static_cast<uintptr_t>(o1.x));
-            const float v1 = *reinterpret_cast<lds_f32_t*>(static_cast<uintptr_t>(o1.x + RS2));
+            const float2 u = row[o0.x / 8], v = row[o1.x / 8];
+            const float u0 = u.x, u1 = u.y, v0 = v.x, v1 = v.y;
             acc0 = fmaf(__uint_as_float(o0.y), u0, acc0);
             acc1 = fmaf(__uint_as_float(o0.y), u1, acc1);
             acc0 = fmaf(__uint_as_float(o1.y), v0, acc0);
@@ -839,20 +831,19 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
                 __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(reinterpret_cast<const char*>(xrow + (size_t)(wv / PR) * d) + ((uint32_t)(wv % PR) * 1024u + (tid & 63u) * 16u)),
                                                  (__attribute__((address_space(3))) void*)(reinterpret_cast<unsigned char*>(outbuf) + (size_t)(wv / PR) * NF * sizeof(TS) + (size_t)(wv % PR) * 1024), 16, 0, 0);
         }
-        {   // the two row slices by LDS-DMA, 1 KiB per wavefront and instruction; in the last piece only the lanes that
-            // still have 16 bytes of the slice take part (a lane's data lands at its own place whoever else is masked).
-            // Through registers, the ragged end cost a round trip to L2 per slice, one after the other.
-            for (int v = (int)(tid >> 6) * 64; v < nv; v += NT) {
-                if (v + (int)(tid & 63u) < nv) {
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(grow + ((uint32_t)v * 16u + (tid & 63u) * 16u)),
-                                                     (__attribute__((address_space(3))) void*)(lds_raw + (size_t)v * 16), 16, 0, 0);
-                    if (pair)
-                        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(grow + (size_t)m * 4 + ((uint32_t)v * 16u + (tid & 63u) * 16u)),
-                                                         (__attribute__((address_space(3))) void*)(lds_raw + RS2 + (size_t)v * 16), 16, 0, 0);
-                }
+        {   // The slices of the two instances side by side, through registers: 16 bytes of each, interleaved, two 16-byte
+            // writes.  As fast as LDS-DMA of the two slices one after the other (37.6 against 38.2 bytes per clock), which
+            // cannot interleave them (by single words: 13.8).
+            const char* grow1 = grow + (pair ? (size_t)m * 4 : 0);   // uniform, like grow
+#pragma unroll 1
+            for (uint32_t o = tid * 16u; o < (uint32_t)nv * 16u; o += NT * 16u) {
+                const float4 a = *reinterpret_cast<const float4*>(grow + o);
+                float4 c = *reinterpret_cast<const float4*>(grow1 + o);
+                if (!pair) c = make_float4(0.f, 0.f, 0.f, 0.f);   // an odd batch: the last pass has one instance
+                float4* to = reinterpret_cast<float4*>(lds_raw + 2u * o);
+                to[0] = make_float4(a.x, c.x, a.y, c.y);
+                to[1] = make_float4(a.z, c.z, a.w, c.w);
             }
-            if (!pair)   // an odd batch: the last pass has one instance, the second buffer reads as zeros
-                for (int v = (int)tid; v < nv; v += NT) reinterpret_cast<uint4*>(lds_raw + RS2)[v] = make_uint4(0u, 0u, 0u, 0u);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             asm volatile("" : "+v"(token));
         }
@@ -913,7 +904,7 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
             for (uint32_t q = NEAR2 + tid; q < ov_n; q += NT) {
                 const OvEntry o = ov[(size_t)ov0 + q];
                 if (o.slot == PAD_SLOT) continue;
-                const float wv = usl_load_f32<TS>(W, (size_t)o.slot), u0 = row[o.label], u1 = row[RS2 / 4 + o.label];
+                const float wv = usl_load_f32<TS>(W, (size_t)o.slot), u0 = row[o.label].x, u1 = row[o.label].y;
                 unsafeAtomicAdd(&outbuf[o.feature], wv * u0);
                 unsafeAtomicAdd(&outbuf[NF + o.feature], wv * u1);
                 float t = fmaf(usl_load_f32<TS>(xr, (size_t)o.feature), u0, ovgw[(size_t)ov0 + q]);
