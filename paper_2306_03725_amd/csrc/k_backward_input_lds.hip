@@ -34,7 +34,7 @@ constexpr int WL = 32768;      // most labels a window has: one float32 row of 1
 constexpr int NF = 2048;       // features per workgroup (two per lane)
 constexpr int NT = 1024;
 constexpr int KT_BWI = 68;     // list slots per lane, shared by its two lists (with the rest of the kernel: the 128 registers a lane has)
-constexpr int KT_BOTH = 36;    // ... in the kernel that also keeps a weight-gradient sum per slot (windows of half the length)
+constexpr int KT_BOTH = 36, KT_BOTH4 = 32;    // ... in the kernel that also keeps a weight-gradient sum per slot (windows of half the length)
 constexpr uint32_t PAD_SLOT = 0xFFFFFFFFu;
 // LDS of the gather kernel: the row slice, NF floats through which the sums are un-permuted, NT words (the features of
 // every lane), NT entries of 8 bytes (the nearest part of the overflow list), 2 * NT words (each lane's share of it) and
@@ -44,20 +44,39 @@ constexpr uint32_t PAD_SLOT = 0xFFFFFFFFu;
 constexpr size_t LDS_BYTES = (size_t)32768 * 4 + (size_t)2048 * 4 + (size_t)1024 * 4 + (size_t)1024 * 8 + (size_t)1024 * 8 + 128;
 constexpr uint32_t ZERO_LABEL = (uint32_t)((LDS_BYTES - 128) / 4);
 static_assert(ZERO_LABEL % 32 == 0 && ZERO_LABEL + 31 < 65536 && LDS_BYTES <= 160 * 1024, "zero words: bank b, 16-bit label, inside LDS");
-// LDS of the kernel for both backward products, which stages two rows of g at a time, interleaved: label l's two values are
-// the 8 bytes at 8 * l (one ds_read_b64 brings both), behind them 32 pairs of zeros (ZERO_LABEL2 is their "label": a window
-// has at most that many labels); RS2 bytes per row; 2 * NF floats for the sums of the two instances, NT words
-// (features), NEAR2 overflow entries of 8 bytes, 2 * NT words (each lane's share of them), NEAR2 floats (their
-// weight-gradient sums).
-constexpr int RS2 = 64000;
-constexpr uint32_t ZERO_LABEL2 = (RS2 - 128) / 4;
+// LDS of the kernel for both backward products.  It stages the slices of Q instances interleaved: label l's Q values are the
+// 4 Q bytes at 4 Q l (one ds_read_b64 or ds_read_b128 brings them), behind them 32 units of zeros (zero_label is their
+// "label": a window has at most that many labels).  Then Q * NF floats for the sums of the instances, for Q = 4 the
+// activations of the block's features (for Q = 2 they lie in the place of the sums until those are ready: there is no room
+// for both beside windows of 16k labels), NT words (features; for Q = 4 another NT: their places among the activations),
+// NEAR2 overflow entries of 8 bytes, 2 * NT words (each lane's share of them), NEAR2 floats (their weight-gradient sums).
 constexpr int NEAR2 = 512;
-constexpr size_t LDS2_BYTES = (size_t)2 * RS2 + (size_t)2 * 2048 * 4 + (size_t)1024 * 4 + (size_t)NEAR2 * 8 + (size_t)2 * 1024 * 4 + (size_t)NEAR2 * 4;
-static_assert(ZERO_LABEL2 % 32 == 0 && RS2 % 16 == 0 && LDS2_BYTES <= 160 * 1024, "zero pairs on their banks, a row of units inside LDS");
+template <int Q> struct BothLayout;
+template <> struct BothLayout<2> { static constexpr uint32_t zero_label = 15968, row_bytes = (zero_label + 32) * 8, x_bytes = 0, feat_words = 1024; };
+template <> struct BothLayout<4> { static constexpr uint32_t zero_label = 4672, row_bytes = (zero_label + 32) * 16, x_bytes = 4 * 2048 * 4, feat_words = 2048; };
+template <int Q> constexpr size_t both_lds_bytes() {
+    return (size_t)BothLayout<Q>::row_bytes + (size_t)Q * 2048 * 4 + BothLayout<Q>::x_bytes + (size_t)BothLayout<Q>::feat_words * 4 +
+           (size_t)NEAR2 * 8 + (size_t)2 * 1024 * 4 + (size_t)NEAR2 * 4;
+}
+static_assert(BothLayout<2>::zero_label % 32 == 0 && BothLayout<4>::zero_label % 32 == 0, "zero units on the banks of their number");
+static_assert(both_lds_bytes<2>() <= 160 * 1024 && both_lds_bytes<4>() <= 160 * 1024, "inside LDS");
 template <int KT> struct ListLayout;   // what depends on which kernel the lists are for
-template <> struct ListLayout<68> { static constexpr uint32_t zero_label = ZERO_LABEL; static constexpr uint32_t near = 1024; };
-template <> struct ListLayout<36> { static constexpr uint32_t zero_label = ZERO_LABEL2; static constexpr uint32_t near = NEAR2; };
+template <> struct ListLayout<68> { static constexpr uint32_t near = 1024; };
+template <> struct ListLayout<36> { static constexpr uint32_t near = NEAR2; };
+template <> struct ListLayout<32> { static constexpr uint32_t near = NEAR2; };
 constexpr int CHUNK = 32768;   // features per LDS histogram
+
+// How a layer is cut up.  A workgroup owns a window of wl labels and a block of NF features.  Where the layer is narrower
+// than a block, the window consists of S runs of `run` labels, and the features count S times over, once for every run
+// ("virtual" features run * d + c, vd = S * d of them): the lists stay of the length that the registers are made for.
+// The sums of the runs are added up on their way out of the workgroup.
+// fpb: features of a block, a multiple of 32 (whole lines of x), at most NF.
+struct Cut {
+    int run, S, wl, nwin, vd, nfb, fpb;
+    __host__ __device__ __forceinline__ uint32_t vfeat(uint32_t col, uint32_t label_in_window, int d) const {
+        return S == 1 ? col : col + label_in_window / (uint32_t)run * (uint32_t)d;
+    }
+};
 
 __global__ void k_fill_u32(uint32_t* p, size_t n, uint32_t v) {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = v;
@@ -76,19 +95,20 @@ __device__ __forceinline__ void share_of(int64_t m, int k, int wl, int splits, s
 // count[w][c] += connections of this workgroup's share that lead into feature c (LDS histogram, then one global
 // atomic per feature that occurs).  grid (nwin * splits, feature chunks).
 __global__ void __launch_bounds__(NT)
-k_lf_count(const int32_t* __restrict__ idx, int64_t m, int k, int d, int wl, int splits, uint32_t* __restrict__ count) {
+k_lf_count(const int32_t* __restrict__ idx, int64_t m, int k, int d, Cut cut, int splits, uint32_t* __restrict__ count) {
     extern __shared__ uint32_t hist[];
-    const int c0 = blockIdx.y * CHUNK, nc = min(CHUNK, d - c0);
+    const int c0 = blockIdx.y * CHUNK, nc = min(CHUNK, cut.vd - c0);
+    const uint32_t j0 = (uint32_t)(blockIdx.x / splits) * (uint32_t)cut.wl;
     size_t e0, e1;
-    share_of(m, k, wl, splits, &e0, &e1);
+    share_of(m, k, cut.wl, splits, &e0, &e1);
     for (int q = threadIdx.x; q < nc; q += NT) hist[q] = 0;
     __syncthreads();
     for (size_t e = e0 + threadIdx.x; e < e1; e += NT) {
-        const uint32_t c = (uint32_t)(idx[e] - c0);
+        const uint32_t c = cut.vfeat((uint32_t)idx[e], (uint32_t)(e / (uint32_t)k) - j0, d) - (uint32_t)c0;
         if (c < (uint32_t)nc) atomicAdd(&hist[c], 1u);
     }
     __syncthreads();
-    uint32_t* dst = count + (size_t)(blockIdx.x / splits) * d + c0;
+    uint32_t* dst = count + (size_t)(blockIdx.x / splits) * cut.vd + c0;
     for (int q = threadIdx.x; q < nc; q += NT)
         if (hist[q]) atomicAdd(&dst[q], hist[q]);
 }
@@ -105,7 +125,7 @@ k_lf_count(const int32_t* __restrict__ idx, int64_t m, int k, int d, int wl, int
 //                       gather kernel keeps in LDS and the list's own lane adds up)
 template <int KTOT>
 __global__ void __launch_bounds__(NT)
-k_lf_plan(const uint32_t* __restrict__ count, int d, int nfb, uint32_t* __restrict__ where, uint32_t* __restrict__ ov_off,
+k_lf_plan(const uint32_t* __restrict__ count, int vd, int nfb, int fpb, uint32_t* __restrict__ where, uint32_t* __restrict__ ov_off,
           uint16_t* __restrict__ feat, uint32_t* __restrict__ caps, uint32_t* __restrict__ n_ent,
           uint32_t* __restrict__ n_ov, uint32_t* __restrict__ ovr) {
     __shared__ uint32_t start[256];
@@ -113,13 +133,14 @@ k_lf_plan(const uint32_t* __restrict__ count, int d, int nfb, uint32_t* __restri
     __shared__ uint16_t len_of[2][NT];
     __shared__ uint32_t cap_of[NT / 64];
     const int wg = blockIdx.x, w = wg / nfb, fb = wg % nfb;
-    const uint32_t* cnt = count + (size_t)w * d + (size_t)fb * NF;
+    const uint32_t* cnt = count + (size_t)w * vd + (size_t)fb * fpb;
+    const int nf = min(fpb, vd - fb * fpb);   // features of the block that exist; the others have empty lists
     if (threadIdx.x < 256) start[threadIdx.x] = 0;
     __syncthreads();
     uint32_t n[2];
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-        n[q] = cnt[threadIdx.x + q * NT];
+        n[q] = (int)threadIdx.x + q * NT < nf ? cnt[threadIdx.x + q * NT] : 0u;
         atomicAdd(&start[min(n[q], 255u)], 1u);
     }
     __syncthreads();
@@ -187,11 +208,11 @@ k_lf_plan(const uint32_t* __restrict__ count, int d, int nfb, uint32_t* __restri
         }
         return scan[threadIdx.x];
     };
-    const size_t bin = (size_t)w * d + (size_t)fb * NF + threadIdx.x;
+    const size_t bin = (size_t)w * vd + (size_t)fb * fpb + threadIdx.x;
     {
         const uint32_t incl = block_scan(n[0] + n[1]);
-        where[bin] = incl - n[0] - n[1];
-        where[bin + NT] = incl - n[1];
+        if ((int)threadIdx.x < nf) where[bin] = incl - n[0] - n[1];
+        if ((int)threadIdx.x + NT < nf) where[bin + NT] = incl - n[1];
         if (threadIdx.x == NT - 1) n_ent[wg] = incl;
     }
     {
@@ -199,7 +220,7 @@ k_lf_plan(const uint32_t* __restrict__ count, int d, int nfb, uint32_t* __restri
         uint32_t at = incl - ov[0] - ov[1];
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            ov_off[bin + q * NT] = at;
+            if ((int)threadIdx.x + q * NT < nf) ov_off[bin + q * NT] = at;
             const uint32_t first = min(at, ListLayout<KTOT>::near);
             ovr[((size_t)wg * 2 + zone_of[q]) * NT + lane_of[q]] = first | (min(ov[q], ListLayout<KTOT>::near - first) << 16);
             at += ov[q];
@@ -235,28 +256,29 @@ k_lf_scan(const uint32_t* __restrict__ ov_count, int nwg, uint32_t* __restrict__
 // per feature, then handed out from LDS cursors.
 struct OvEntry { uint16_t feature; uint16_t label; uint32_t slot; };
 __global__ void __launch_bounds__(NT)
-k_lf_fill(const int32_t* __restrict__ idx, int64_t m, int k, int d, int wl, int nfb, int splits, const uint32_t* __restrict__ where,
+k_lf_fill(const int32_t* __restrict__ idx, int64_t m, int k, int d, Cut cut, int splits, const uint32_t* __restrict__ where,
           uint32_t* __restrict__ taken, const uint32_t* __restrict__ ent_base, uint32_t* __restrict__ ent) {
     extern __shared__ uint32_t cur[];
-    const int c0 = blockIdx.y * CHUNK, nc = min(CHUNK, d - c0);
+    const int c0 = blockIdx.y * CHUNK, nc = min(CHUNK, cut.vd - c0);
     const int w = blockIdx.x / splits;
+    const uint32_t j0 = (uint32_t)w * (uint32_t)cut.wl;
     size_t e0, e1;
-    share_of(m, k, wl, splits, &e0, &e1);
+    share_of(m, k, cut.wl, splits, &e0, &e1);
     for (int q = threadIdx.x; q < nc; q += NT) cur[q] = 0;
     __syncthreads();
     for (size_t e = e0 + threadIdx.x; e < e1; e += NT) {
-        const uint32_t c = (uint32_t)(idx[e] - c0);
+        const uint32_t c = cut.vfeat((uint32_t)idx[e], (uint32_t)(e / (uint32_t)k) - j0, d) - (uint32_t)c0;
         if (c < (uint32_t)nc) atomicAdd(&cur[c], 1u);
     }
     __syncthreads();
-    const size_t bin0 = (size_t)w * d + c0;
+    const size_t bin0 = (size_t)w * cut.vd + c0;
     for (int q = threadIdx.x; q < nc; q += NT) {   // from here cur[q] = where this share's part of the list starts
         const uint32_t n = cur[q];
-        if (n) cur[q] = atomicAdd(&taken[bin0 + q], n) + where[bin0 + q] + ent_base[(size_t)w * nfb + (c0 + q) / NF];
+        if (n) cur[q] = atomicAdd(&taken[bin0 + q], n) + where[bin0 + q] + ent_base[(size_t)w * cut.nfb + (c0 + q) / cut.fpb];
     }
     __syncthreads();
     for (size_t e = e0 + threadIdx.x; e < e1; e += NT) {
-        const uint32_t c = (uint32_t)(idx[e] - c0);
+        const uint32_t c = cut.vfeat((uint32_t)idx[e], (uint32_t)(e / (uint32_t)k) - j0, d) - (uint32_t)c0;
         if (c < (uint32_t)nc) ent[atomicAdd(&cur[c], 1u)] = (uint32_t)e;
     }
 }
@@ -266,29 +288,30 @@ k_lf_fill(const int32_t* __restrict__ idx, int64_t m, int k, int d, int wl, int 
 // ent), and within it in the order of their flat slots, up to the order inside a run of SEG slots.  The Adam kernel,
 // which goes through the slots in order, then reads 16 or so neighbouring places from each of the window's nfb
 // workgroups per wavefront -- whole lines; in the order of the lists it would fetch a line per value.
+// slot_at[place] is the way back: the kernel reads the weights in the order of the places, for the same reason.
 // Three kernels: the counts of every run per feature block, their running sums, the places.
 constexpr int SEG = 256;   // slots of a run: one wavefront, four per lane
-__device__ __forceinline__ bool seg_of_wave(int64_t m, int k, int wl, int nseg, int64_t total, int* w, int* seg, size_t* s0, size_t* s1) {
+__device__ __forceinline__ bool seg_of_wave(int64_t m, int k, const Cut& cut, int nseg, int64_t total, int* w, int* seg, size_t* s0, size_t* s1) {
     const int64_t gs = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (gs >= total) return false;
     *w = (int)(gs / nseg); *seg = (int)(gs % nseg);
-    const size_t w0 = (size_t)*w * wl * k, w1 = (size_t)min((int64_t)(*w + 1) * wl, m) * k;
+    const size_t w0 = (size_t)*w * cut.wl * k, w1 = (size_t)min((int64_t)(*w + 1) * cut.wl, m) * k;
     *s0 = min(w0 + (size_t)*seg * SEG, w1);
     *s1 = min(*s0 + SEG, w1);
     return true;
 }
 __global__ void __launch_bounds__(256)
-k_lf_seg_count(const int32_t* __restrict__ idx, int64_t m, int k, int wl, int nfb, int nseg, int64_t total, uint32_t* __restrict__ segcnt) {
+k_lf_seg_count(const int32_t* __restrict__ idx, int64_t m, int k, Cut cut, int nseg, int64_t total, uint32_t* __restrict__ segcnt) {
     __shared__ uint32_t h[4][32];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     if (lane < 32) h[wave][lane] = 0;
     __syncthreads();
     int w, seg; size_t s0, s1;
-    const bool on = seg_of_wave(m, k, wl, nseg, total, &w, &seg, &s0, &s1);
+    const bool on = seg_of_wave(m, k, cut, nseg, total, &w, &seg, &s0, &s1);
     if (on)
-        for (size_t e = s0 + lane; e < s1; e += 64) atomicAdd(&h[wave][min((uint32_t)idx[e] / NF, 31u)], 1u);
+        for (size_t e = s0 + lane; e < s1; e += 64) atomicAdd(&h[wave][cut.S > 1 ? 0u : min((uint32_t)idx[e] / (uint32_t)cut.fpb, 31u)], 1u);
     __syncthreads();
-    if (on && lane < nfb) segcnt[((size_t)w * nfb + lane) * nseg + seg] = h[wave][lane];
+    if (on && lane < cut.nfb) segcnt[((size_t)w * cut.nfb + lane) * nseg + seg] = h[wave][lane];
 }
 // segcnt[wg][seg] -> ent_base[wg] + the counts of the runs before seg (in place).  One block per workgroup wg.
 __global__ void __launch_bounds__(256)
@@ -313,16 +336,20 @@ k_lf_seg_scan(uint32_t* __restrict__ segcnt, int nseg, const uint32_t* __restric
     }
 }
 __global__ void __launch_bounds__(256)
-k_lf_seg_place(const int32_t* __restrict__ idx, int64_t m, int k, int wl, int nfb, int nseg, int64_t total,
-               const uint32_t* __restrict__ segbase, uint32_t* __restrict__ pos) {
+k_lf_seg_place(const int32_t* __restrict__ idx, int64_t m, int k, Cut cut, int nseg, int64_t total,
+               const uint32_t* __restrict__ segbase, uint32_t* __restrict__ pos, uint32_t* __restrict__ slot_at) {
     __shared__ uint32_t h[4][32];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     int w, seg; size_t s0, s1;
-    const bool on = seg_of_wave(m, k, wl, nseg, total, &w, &seg, &s0, &s1);
-    if (on && lane < nfb) h[wave][lane] = segbase[((size_t)w * nfb + lane) * nseg + seg];
+    const bool on = seg_of_wave(m, k, cut, nseg, total, &w, &seg, &s0, &s1);
+    if (on && lane < cut.nfb) h[wave][lane] = segbase[((size_t)w * cut.nfb + lane) * nseg + seg];
     __syncthreads();
     if (on)
-        for (size_t e = s0 + lane; e < s1; e += 64) pos[e] = atomicAdd(&h[wave][min((uint32_t)idx[e] / NF, 31u)], 1u);
+        for (size_t e = s0 + lane; e < s1; e += 64) {
+            const uint32_t p = atomicAdd(&h[wave][cut.S > 1 ? 0u : min((uint32_t)idx[e] / (uint32_t)cut.fpb, 31u)], 1u);
+            pos[e] = p;
+            slot_at[p] = (uint32_t)e;
+        }
 }
 
 // Bank-aware order of the entries in every lane's lists.  At step t of the gathers the 32 lanes of a half-wavefront
@@ -340,34 +367,40 @@ k_lf_seg_place(const int32_t* __restrict__ idx, int64_t m, int k, int wl, int nf
 // outcome is a valid order: it changes speed, never results.  rounds = 0: the lists stay in the order of ent.
 // pos (if given, see k_lf_seg_place): every entry's place among its workgroup's weight gradients goes along, into rk
 // (beside lab / slot) or ovrk (beside ov); an empty place gets PAD_SLOT.
-constexpr int SG = 8;   // half-wavefronts per workgroup
-template <int KTOT>
-__global__ void __launch_bounds__(SG * 32)
+// GS = lanes and banks of a group: 32, or 16 where the gathers are 16 bytes wide (the lanes of a half-wavefront that such a
+// read serves together: 0-3, 12-15, 20-27 and the other 16).
+constexpr int SG_NT = 256;   // lanes per workgroup
+template <int KTOT, int GS>
+__global__ void __launch_bounds__(SG_NT)
 k_lf_schedule(const uint32_t* __restrict__ ent, const uint32_t* __restrict__ ent_base, const uint32_t* __restrict__ where,
               const uint32_t* __restrict__ count, const uint16_t* __restrict__ feat, const uint32_t* __restrict__ caps,
-              const uint32_t* __restrict__ ov_base, const uint32_t* __restrict__ ov_off, int k, int d, int wl, int nfb,
-              int rounds, uint16_t* __restrict__ lab, uint32_t* __restrict__ slot, OvEntry* __restrict__ ov,
+              const uint32_t* __restrict__ ov_base, const uint32_t* __restrict__ ov_off, int k, Cut cut,
+              uint32_t zero_label, int rounds, uint16_t* __restrict__ lab, uint32_t* __restrict__ slot, OvEntry* __restrict__ ov,
               const uint32_t* __restrict__ pos, uint32_t* __restrict__ rk, uint32_t* __restrict__ ovrk) {
-    __shared__ uint8_t slots[SG][32][KTOT + 4];   // my entries sorted by bank
-    __shared__ uint8_t left_in[SG][32][36];       // entries of mine not placed yet, per bank
-    __shared__ uint8_t end_of[SG][32][36];        // where bank b's entries end in the sorted list
-    __shared__ int deg0[SG][32];
-    __shared__ int win[SG][32];
-    const int gl = threadIdx.x >> 5, lane = threadIdx.x & 31;
-    const int hs = threadIdx.x & 32;              // where my group's 32 bits sit in a wavefront ballot
-    const size_t gid = (size_t)blockIdx.x * SG + gl;
+    constexpr int SG = SG_NT / GS;
+    constexpr uint32_t ALL = GS == 32 ? 0xFFFFFFFFu : (1u << (GS & 31)) - 1u;
+    __shared__ uint8_t slots[SG][GS][KTOT + 4];   // my entries sorted by bank
+    __shared__ uint8_t left_in[SG][GS][GS + 4];   // entries of mine not placed yet, per bank
+    __shared__ uint8_t end_of[SG][GS][GS + 4];    // where bank b's entries end in the sorted list
+    __shared__ int deg0[SG][GS];
+    __shared__ int win[SG][GS];
+    const int gl = threadIdx.x / GS, lane = threadIdx.x & (GS - 1);
+    const int hs = threadIdx.x & 63 & ~(GS - 1);  // where my group's bits sit in a wavefront ballot
+    const size_t gid = (size_t)blockIdx.x * (SG_NT / 32) + (threadIdx.x >> 5);   // half-wavefront of the gather kernel
     const size_t wg = gid >> 6;
     const int zone = (int)(gid >> 5) & 1, half = (int)gid & 31;   // the two halves of a wavefront are neighbours: same allowance
+    const int mypos = half * 32 + usl_lane_of_position<GS>(threadIdx.x & 31);
     const uint32_t cw = caps[wg * (NT / 64) + (half >> 1)];
     const int cap = zone ? (int)(cw >> 8) : (int)(cw & 0xFFu);
-    const int w = (int)(wg / nfb), fb = (int)(wg % nfb);
-    auto at = [&](int p) -> size_t { return (wg * KTOT + (zone ? KTOT - 1 - p : p)) * NT + half * 32 + lane; };
+    const int w = (int)(wg / cut.nfb), fb = (int)(wg % cut.nfb);
+    auto at = [&](int p) -> size_t { return (wg * KTOT + (zone ? KTOT - 1 - p : p)) * NT + mypos; };
     // my list: feature, length, where its entries are; label of an entry = its flat slot / k, counted from the window's first
-    const uint32_t f = feat[(wg * 2 + zone) * NT + half * 32 + lane];
-    const size_t bin = (size_t)w * d + (size_t)fb * NF + f;
-    const uint32_t len = count[bin];
-    const uint32_t* my = ent + ent_base[wg] + where[bin];
-    auto label_of = [&](uint32_t e) -> uint32_t { return e / (uint32_t)k - (uint32_t)w * (uint32_t)wl; };
+    const uint32_t f = feat[(wg * 2 + zone) * NT + mypos];
+    const bool exists = (int)f < min(cut.fpb, cut.vd - fb * cut.fpb);
+    const size_t bin = exists ? (size_t)w * cut.vd + (size_t)fb * cut.fpb + f : 0;
+    const uint32_t len = exists ? count[bin] : 0u;
+    const uint32_t* my = ent + ent_base[wg] + (exists ? where[bin] : 0u);
+    auto label_of = [&](uint32_t e) -> uint32_t { return e / (uint32_t)k - (uint32_t)w * (uint32_t)cut.wl; };
     const int n = (int)min(len, (uint32_t)cap);     // entries that get a register slot
     for (uint32_t p = (uint32_t)cap; p < len; ++p) {   // the others: to the list's part of the overflow list
         OvEntry o;
@@ -377,26 +410,26 @@ k_lf_schedule(const uint32_t* __restrict__ ent, const uint32_t* __restrict__ ent
     }
     if (len > (uint32_t)cap && ((len - (uint32_t)cap) & 1u)) {   // an odd number: one empty place behind them
         OvEntry o;
-        o.feature = (uint16_t)f; o.label = (uint16_t)ListLayout<KTOT>::zero_label; o.slot = PAD_SLOT;
+        o.feature = (uint16_t)f; o.label = (uint16_t)zero_label; o.slot = PAD_SLOT;
         ov[(size_t)ov_base[wg] + ov_off[bin] + (len - (uint32_t)cap)] = o;
         if (pos) ovrk[(size_t)ov_base[wg] + ov_off[bin] + (len - (uint32_t)cap)] = PAD_SLOT;
     }
     if (rounds <= 0) {
         for (int s = 0; s < cap; ++s) {
-            lab[at(s)] = s < n ? (uint16_t)label_of(my[s]) : (uint16_t)ListLayout<KTOT>::zero_label;
-            slot[at(s)] = s < n ? my[s] : PAD_SLOT;
+            lab[at(s)] = s < n ? (uint16_t)label_of(my[s]) : (uint16_t)zero_label;
+            if (slot) slot[at(s)] = s < n ? my[s] : PAD_SLOT;
             if (pos) rk[at(s)] = s < n ? pos[my[s]] - ent_base[wg] : PAD_SLOT;
         }
         return;   // the whole wavefront: rounds is the same for all
     }
     deg0[gl][lane] = 0;
-    for (int b = 0; b < 32; ++b) left_in[gl][lane][b] = 0;
+    for (int b = 0; b < GS; ++b) left_in[gl][lane][b] = 0;
     __syncthreads();
     uint8_t* mine = slots[gl][lane];
     uint8_t* cnt = left_in[gl][lane];
     uint8_t* ends = end_of[gl][lane];
     for (int p = 0; p < n; ++p) {
-        const int b = (int)(label_of(my[p]) & 31u);
+        const int b = (int)(label_of(my[p]) & (GS - 1u));
         ++cnt[b];
         atomicAdd(&deg0[gl][b], 1);
     }
@@ -404,12 +437,12 @@ k_lf_schedule(const uint32_t* __restrict__ ent, const uint32_t* __restrict__ ent
     uint32_t avail = 0;            // banks my unplaced entries read
     {   // counting sort of my entries by bank (their banks are read a second time: no room to keep them)
         int run = 0;
-        for (int b = 0; b < 32; ++b) { run += cnt[b]; ends[b] = (uint8_t)run; if (cnt[b]) avail |= 1u << b; }
-        for (int p = n - 1; p >= 0; --p) { const int b = (int)(label_of(my[p]) & 31u); ends[b] = (uint8_t)(ends[b] - 1); mine[ends[b]] = (uint8_t)p; }
-        for (int b = 0; b < 32; ++b) ends[b] = (uint8_t)(ends[b] + cnt[b]);   // back from starts to ends
+        for (int b = 0; b < GS; ++b) { run += cnt[b]; ends[b] = (uint8_t)run; if (cnt[b]) avail |= 1u << b; }
+        for (int p = n - 1; p >= 0; --p) { const int b = (int)(label_of(my[p]) & (GS - 1u)); ends[b] = (uint8_t)(ends[b] - 1); mine[ends[b]] = (uint8_t)p; }
+        for (int b = 0; b < GS; ++b) ends[b] = (uint8_t)(ends[b] + cnt[b]);   // back from starts to ends
     }
     __syncthreads();
-    auto gballot = [&](bool p) -> uint32_t { return (uint32_t)(__ballot(p) >> hs); };
+    auto gballot = [&](bool p) -> uint32_t { return (uint32_t)(__ballot(p) >> hs) & ALL; };
     volatile int* gwin = win[gl];
     int mydeg = deg0[gl][lane];    // bank role: entries of the group that read bank `lane` and are not placed yet
     for (int s = 0; s < cap; ++s) {
@@ -421,13 +454,13 @@ k_lf_schedule(const uint32_t* __restrict__ ent, const uint32_t* __restrict__ ent
             int prop = -1;
             const uint32_t cand = mb < 0 ? (avail & freeb) : 0u;
             if (cand) {            // first candidate bank at or after a lane- and round-dependent start
-                const int sh = (lane + 7 * r) & 31;
-                const uint32_t rc = (cand >> sh) | (cand << ((32 - sh) & 31));
-                prop = (__ffs(rc) - 1 + sh) & 31;
+                const int sh = (lane + 7 * r) & (GS - 1);
+                const uint32_t rc = ((cand >> sh) | (cand << ((GS - sh) & (GS - 1)))) & ALL;
+                prop = (__ffs(rc) - 1 + sh) & (GS - 1);
                 atomicMin(&win[gl][prop], lane);
             }
             const int wnr = gwin[lane];
-            if (ml < 0 && wnr < 32) ml = wnr;
+            if (ml < 0 && wnr < GS) ml = wnr;
             if (prop >= 0 && gwin[prop] == lane) mb = prop;
         }
         // augmenting paths from the banks still free
@@ -444,7 +477,7 @@ k_lf_schedule(const uint32_t* __restrict__ ent, const uint32_t* __restrict__ ent
                 if (reach) par = __ffs(avail & front) - 1;
                 const uint32_t fresh = gballot(reach);
                 const uint32_t fresh_free = gballot(reach && mb < 0);
-                const uint32_t next = gballot(ml >= 0 && ((fresh >> (ml & 31)) & 1u));
+                const uint32_t next = gballot(ml >= 0 && ((fresh >> (ml & (GS - 1))) & 1u));
                 seen |= fresh;
                 if (searching) {
                     if (fresh_free) { found = __ffs(fresh_free) - 1; searching = false; }
@@ -456,8 +489,8 @@ k_lf_schedule(const uint32_t* __restrict__ ent, const uint32_t* __restrict__ ent
             while (__any(cur >= 0)) {
                 const bool a = cur >= 0;
                 const int cl = a ? cur : 0;
-                const int b = __shfl(par, cl, 32) & 31;
-                const int prev = __shfl(ml, b, 32);
+                const int b = __shfl(par, cl, GS) & (GS - 1);
+                const int prev = __shfl(ml, b, GS);
                 if (a) {
                     if (lane == cl) mb = b;
                     if (lane == b) ml = cl;
@@ -485,25 +518,25 @@ k_lf_schedule(const uint32_t* __restrict__ ent, const uint32_t* __restrict__ ent
             const bool a = left != 0;
             const int l = a ? __ffs(left) - 1 : 0;
             left &= left - 1;
-            const uint32_t av = (uint32_t)__shfl((int)avail, l, 32);
+            const uint32_t av = (uint32_t)__shfl((int)avail, l, GS);
             int key = (a && ((av >> lane) & 1u)) ? (((255 - myload) << 17) | (mydeg << 5) | lane) : -1;
 #pragma unroll
-            for (int o = 16; o > 0; o >>= 1) key = max(key, __shfl_xor(key, o, 32));
+            for (int o = GS / 2; o > 0; o >>= 1) key = max(key, __shfl_xor(key, o, GS));
             if (a && key >= 0) {
-                const int bb = key & 31;
+                const int bb = key & (GS - 1);
                 if (lane == l) mb = bb;
                 if (lane == bb) ++myload;
             }
         }
         if (wb >= 0) {             // an empty place: the zero word of the free bank, no weight
-            lab[at(s)] = (uint16_t)(ListLayout<KTOT>::zero_label + (uint32_t)wb);
-            slot[at(s)] = PAD_SLOT;
+            lab[at(s)] = (uint16_t)(zero_label + (uint32_t)wb);
+            if (slot) slot[at(s)] = PAD_SLOT;
             if (pos) rk[at(s)] = PAD_SLOT;
         } else {                   // my next unplaced entry in that bank
             const int pick = mine[ends[mb] - cnt[mb]];
             if (--cnt[mb] == 0) avail &= ~(1u << mb);
             lab[at(s)] = (uint16_t)label_of(my[pick]);
-            slot[at(s)] = my[pick];
+            if (slot) slot[at(s)] = my[pick];
             if (pos) rk[at(s)] = pos[my[pick]] - ent_base[wg];
         }
         mydeg -= myload;
@@ -727,122 +760,277 @@ __device__ __forceinline__ void gather4_two(float& acc0, float& acc1, float& s0,
         : "memory", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119");
 }
 
-template <typename TS>
+// The same for four instances: 16-byte reads, eight multiply-adds per slot.
+__device__ __forceinline__ void gather4_four(float (&acc)[4], float& s0, float& s1, float& s2, float& s3, uint32_t p0, uint32_t p1,
+                                             float w0, float w1, float w2, float w3, const float (&x)[4]) {
+    const uint32_t four = 4;
+    asm volatile(
+        "v_lshlrev_b32_sdwa v112, %8, %9 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
+        "v_lshlrev_b32_sdwa v116, %8, %9 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
+        "v_lshlrev_b32_sdwa v120, %8, %10 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
+        "v_lshlrev_b32_sdwa v124, %8, %10 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
+        "ds_read_b128 v[112:115], v112\n\t"
+        "ds_read_b128 v[116:119], v116\n\t"
+        "ds_read_b128 v[120:123], v120\n\t"
+        "ds_read_b128 v[124:127], v124\n\t"
+        "s_waitcnt lgkmcnt(3)\n\t"
+        "v_fmac_f32 %0, %11, v112\n\t"
+        "v_fmac_f32 %1, %11, v113\n\t"
+        "v_fmac_f32 %2, %11, v114\n\t"
+        "v_fmac_f32 %3, %11, v115\n\t"
+        "v_fmac_f32 %4, %15, v112\n\t"
+        "v_fmac_f32 %4, %16, v113\n\t"
+        "v_fmac_f32 %4, %17, v114\n\t"
+        "v_fmac_f32 %4, %18, v115\n\t"
+        "s_waitcnt lgkmcnt(2)\n\t"
+        "v_fmac_f32 %0, %12, v116\n\t"
+        "v_fmac_f32 %1, %12, v117\n\t"
+        "v_fmac_f32 %2, %12, v118\n\t"
+        "v_fmac_f32 %3, %12, v119\n\t"
+        "v_fmac_f32 %5, %15, v116\n\t"
+        "v_fmac_f32 %5, %16, v117\n\t"
+        "v_fmac_f32 %5, %17, v118\n\t"
+        "v_fmac_f32 %5, %18, v119\n\t"
+        "s_waitcnt lgkmcnt(1)\n\t"
+        "v_fmac_f32 %0, %13, v120\n\t"
+        "v_fmac_f32 %1, %13, v121\n\t"
+        "v_fmac_f32 %2, %13, v122\n\t"
+        "v_fmac_f32 %3, %13, v123\n\t"
+        "v_fmac_f32 %6, %15, v120\n\t"
+        "v_fmac_f32 %6, %16, v121\n\t"
+        "v_fmac_f32 %6, %17, v122\n\t"
+        "v_fmac_f32 %6, %18, v123\n\t"
+        "s_waitcnt lgkmcnt(0)\n\t"
+        "v_fmac_f32 %0, %14, v124\n\t"
+        "v_fmac_f32 %1, %14, v125\n\t"
+        "v_fmac_f32 %2, %14, v126\n\t"
+        "v_fmac_f32 %3, %14, v127\n\t"
+        "v_fmac_f32 %7, %15, v124\n\t"
+        "v_fmac_f32 %7, %16, v125\n\t"
+        "v_fmac_f32 %7, %17, v126\n\t"
+        "v_fmac_f32 %7, %18, v127"
+        : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(s0), "+v"(s1), "+v"(s2), "+v"(s3)
+        : "s"(four), "v"(p0), "v"(p1), "v"(w0), "v"(w1), "v"(w2), "v"(w3), "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3])
+        : "memory", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119", "v120", "v121", "v122", "v123", "v124", "v125", "v126", "v127");
+}
+template <int Q>
+__device__ __forceinline__ void gather_group(float (&acc)[Q], float& s0, float& s1, float& s2, float& s3, uint32_t p0, uint32_t p1,
+                                             float w0, float w1, float w2, float w3, const float (&x)[Q]) {
+    if constexpr (Q == 2) gather4_two(acc[0], acc[1], s0, s1, s2, s3, p0, p1, w0, w1, w2, w3, x[0], x[1]);
+    else gather4_four(acc, s0, s1, s2, s3, p0, p1, w0, w1, w2, w3, x);
+}
+// The values of Q instances at one place of LDS.
+__device__ __forceinline__ void unit_of(const float* p, float (&v)[2]) { const float2 t = *reinterpret_cast<const float2*>(p); v[0] = t.x; v[1] = t.y; }
+__device__ __forceinline__ void unit_of(const float* p, float (&v)[4]) { const float4 t = *reinterpret_cast<const float4*>(p); v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w; }
+__device__ __forceinline__ void unit_of(const uint16_t* p, float (&v)[4]) {
+    const uint2 t = *reinterpret_cast<const uint2*>(p);
+    v[0] = __uint_as_float(t.x << 16); v[1] = __uint_as_float(t.x & 0xFFFF0000u);
+    v[2] = __uint_as_float(t.y << 16); v[3] = __uint_as_float(t.y & 0xFFFF0000u);
+}
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // 16 bytes of a row that starts anywhere
+
+// Q = 2: windows of up to 15 968 labels (wide layers), x as rows of x_stride elements, 16-byte aligned.
+// Q = 4: windows of up to 4 672 labels, x interleaved by fours (x_stride = elements from group to group, k_interleave).
+// grid: at least windows * parts of the batch * feature blocks, a multiple of 8.  A part of the batch (rows_per_part
+// instances, a multiple of Q) leaves its weight gradient at stage + part * part_stride.
+template <typename TS, int Q>
 __global__ void __launch_bounds__(NT)
-k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __restrict__ x, int64_t m, int k, int rows, int d,
-           int wl, int nfb, int nwin, const uint16_t* __restrict__ lab, const uint32_t* __restrict__ slot,
+k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __restrict__ x, size_t x_stride, int64_t m, int k, int rows, int d,
+           int dp, Cut cut, const uint16_t* __restrict__ lab, const uint32_t* __restrict__ slot_at,
            const uint16_t* __restrict__ feat, const uint32_t* __restrict__ caps, const uint32_t* __restrict__ ov_base,
            const OvEntry* __restrict__ ov, const uint32_t* __restrict__ ovr, float* __restrict__ partial,
            const uint32_t* __restrict__ rk, const uint32_t* __restrict__ ovrk, const uint32_t* __restrict__ ent_base,
-           float* __restrict__ stage, float* __restrict__ ovgw, const uint32_t* __restrict__ gate, int accumulate) {
-    constexpr int KT = KT_BOTH;
+           float* __restrict__ stage, float* __restrict__ ovgw, int parts, int rows_per_part, size_t part_stride, size_t ov_stride,
+           const uint32_t* __restrict__ gate, int accumulate) {
+    constexpr int KT = Q == 4 ? KT_BOTH4 : KT_BOTH;   // (with four instances 36 slots spill)
+    constexpr uint32_t ZL = BothLayout<Q>::zero_label, U = 4 * Q;   // U: bytes of a unit
     extern __shared__ __align__(16) unsigned char lds_raw[];
     if (gate && *gate == 0) return;   // the kernels over the nonzero gradients do this call's work
-    const int w = (blockIdx.x & 7) + 8 * (blockIdx.x / (8 * nfb)), fb = (blockIdx.x >> 3) % nfb;
-    if (w >= nwin) return;
+    const int nfb = cut.nfb;
+    // workgroup b runs on XCD b % 8: an XCD takes an eighth of the tiles (window, part, feature block) in this order, so that
+    // the blocks of a window, which read the same slices of g, and its parts, which read the same lists, share an L2
+    const int per_xcd = (int)gridDim.x / 8, tile = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    const int w = tile / (parts * nfb), part = tile / nfb % parts, fb = tile % nfb;
+    if (w >= cut.nwin) return;
+    const int i_begin = part * rows_per_part, i_end = min(rows, i_begin + rows_per_part);
+    stage += (size_t)part * part_stride;
+    ovgw += (size_t)part * ov_stride;
     const size_t wg = (size_t)w * nfb + fb;
     const uint32_t cw = caps[wg * (NT / 64) + (threadIdx.x >> 6)];
     const int acap = __builtin_amdgcn_readfirstlane((int)(cw & 0xFFu)), bcap = __builtin_amdgcn_readfirstlane((int)(cw >> 8));
     uint32_t pk[KT / 2];
     float wt[KT], gw[KT];
-    const uint32_t last_slot = (uint32_t)(m * k - 1);
+    // The weights come in the order of the places (slot_at; rk: see the end of the kernel) and are picked up from LDS: in the
+    // order of the lists every value was a 128-byte line of its own (96 of 1320 us at m = 500k, d = 32k, k = 32, 25 of 210 at
+    // m = 200k, d = 8k, b = 64).  All loads of a batch are in flight together, those of slots that the wavefront does not
+    // visit included (their places hold anything).
+    constexpr int PB = KT % 12 == 0 ? 12 : 8;
+    constexpr uint32_t CH = (uint32_t)((both_lds_bytes<Q>() - (size_t)NEAR2 * 4) / 4);   // places LDS holds at a time
+    float* perm = reinterpret_cast<float*>(lds_raw);
+    const uint32_t e0 = ent_base[wg], n_ent = ent_base[wg + 1] - e0;
 #pragma unroll
-    for (int q = 0; q < KT / 4; ++q) {
-        const bool used = q * 4 < acap || q * 4 >= KT - bcap;   // the same for the whole wavefront
+    for (int t = 0; t < KT; ++t) wt[t] = gw[t] = 0.f;
+    for (uint32_t c0 = 0; c0 < n_ent; c0 += CH) {
+        const uint32_t n = min(CH, n_ent - c0);
+        __syncthreads();
+        for (uint32_t r0 = threadIdx.x; r0 < n; r0 += 8 * NT) {
+            uint32_t sl[8];
+            float v[8];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int t = q * 4 + u;
-            uint32_t l16 = 0;
-            float wv = 0.f;
-            if (used) {
-                const size_t at = (wg * KT + t) * NT + threadIdx.x;
-                l16 = lab[at];
-                const uint32_t s = slot[at];
-                wv = usl_load_f32<TS>(W, (size_t)min(s, last_slot));   // an empty place reads some weight and drops it
-                wv = s != PAD_SLOT ? wv : 0.f;
+            for (int u = 0; u < 8; ++u) sl[u] = (slot_at + e0 + c0)[min(r0 + u * NT, n - 1)];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = usl_load_f32<TS>(W, (size_t)sl[u]);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (r0 + u * NT < n) perm[r0 + u * NT] = v[u];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int t0 = 0; t0 < KT; t0 += PB) {
+            uint32_t r[PB];
+#pragma unroll
+            for (int u = 0; u < PB; ++u) r[u] = (rk + wg * KT * NT)[(uint32_t)(t0 + u) * NT + threadIdx.x] - c0;   // an empty place: far beyond
+#pragma unroll
+            for (int u = 0; u < PB; ++u) {
+                const int t = t0 + u;
+                const bool used = t / 4 * 4 < acap || t / 4 * 4 >= KT - bcap;   // the same for the whole wavefront
+                if (used && r[u] < n) wt[t] = perm[r[u]];
             }
-            if (t & 1) pk[t >> 1] |= l16 << 16; else pk[t >> 1] = l16;
-            wt[t] = wv;
-            gw[t] = 0.f;
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
+#pragma unroll
+    for (int t0 = 0; t0 < KT; t0 += PB) {
+        uint32_t lb[PB];
+#pragma unroll
+        for (int u = 0; u < PB; ++u) lb[u] = (lab + wg * KT * NT)[(uint32_t)(t0 + u) * NT + threadIdx.x];
+#pragma unroll
+        for (int u = 0; u < PB; ++u) {
+            const int t = t0 + u;
+            const bool used = t / 4 * 4 < acap || t / 4 * 4 >= KT - bcap;
+            const uint32_t l16 = used ? lb[u] : 0u;
+            if (t & 1) pk[t >> 1] |= l16 << 16; else pk[t >> 1] = l16;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __syncthreads();   // LDS is free
     const uint32_t ov0 = ov_base[wg], ov_n = ov_base[wg + 1] - ov0;
-    float2* row = reinterpret_cast<float2*>(lds_raw);                     // row[label]: the two instances of a pass
-    float* outbuf = reinterpret_cast<float*>(lds_raw + 2 * RS2);          // [2][NF]
-    uint32_t* feat_of = reinterpret_cast<uint32_t*>(outbuf + 2 * NF);     // [NT]
-    uint2* ov_near = reinterpret_cast<uint2*>(feat_of + NT);              // [NEAR2] {address of the label in the row, weight}
+    const float* row = reinterpret_cast<const float*>(lds_raw);           // row[Q * label + q]: instance q of a pass
+    float* outbuf = reinterpret_cast<float*>(lds_raw + BothLayout<Q>::row_bytes);   // [Q][NF]
+    TS* xbuf = reinterpret_cast<TS*>(outbuf + (BothLayout<Q>::x_bytes ? Q * NF : 0));   // Q = 4: [NF][4]; Q = 2: [2][NF], in the place of the sums
+    uint32_t* feat_of = reinterpret_cast<uint32_t*>(reinterpret_cast<unsigned char*>(outbuf + Q * NF) + BothLayout<Q>::x_bytes);   // [NT]
+    uint2* ov_near = reinterpret_cast<uint2*>(feat_of + BothLayout<Q>::feat_words);   // [NEAR2] {address of the label in the row, weight}
     uint32_t* ovr_a = reinterpret_cast<uint32_t*>(ov_near + NEAR2);       // [NT] start | n << 16
     uint32_t* ovr_b = ovr_a + NT;
     float* ov_sum = reinterpret_cast<float*>(ovr_b + NT);                 // [NEAR2]
-    feat_of[threadIdx.x] = (uint32_t)feat[(wg * 2 + 0) * NT + threadIdx.x] | (uint32_t)feat[(wg * 2 + 1) * NT + threadIdx.x] << 16;
+    {
+        const uint32_t fa = feat[(wg * 2 + 0) * NT + threadIdx.x], fbb = feat[(wg * 2 + 1) * NT + threadIdx.x];
+        feat_of[threadIdx.x] = fa | fbb << 16;
+        // Q = 4: where the features' activations are (a list of a feature that does not exist reads some place, and is empty)
+        if (Q == 4) feat_of[NT + threadIdx.x] = cut.S == 1 ? fa | fbb << 16 : fa % (uint32_t)d | fbb % (uint32_t)d << 16;
+    }
     if (threadIdx.x < NEAR2) {
-        uint2 e = make_uint2(ZERO_LABEL2 * 8u, 0u);
+        uint2 e = make_uint2(ZL * U, 0u);
         if (threadIdx.x < ov_n) {
             const OvEntry o = ov[(size_t)ov0 + threadIdx.x];
-            e = make_uint2((uint32_t)o.label * 8u, o.slot == PAD_SLOT ? 0u : __float_as_uint(usl_load_f32<TS>(W, (size_t)o.slot)));
+            e = make_uint2((uint32_t)o.label * U, o.slot == PAD_SLOT ? 0u : __float_as_uint(usl_load_f32<TS>(W, (size_t)o.slot)));
         }
         ov_near[threadIdx.x] = e;
         ov_sum[threadIdx.x] = 0.f;
     }
     ovr_a[threadIdx.x] = ovr[(wg * 2 + 0) * NT + threadIdx.x];
     ovr_b[threadIdx.x] = ovr[(wg * 2 + 1) * NT + threadIdx.x];
-    if (threadIdx.x < 32) row[ZERO_LABEL2 + threadIdx.x] = make_float2(0.f, 0.f);   // what empty places read
+    if (threadIdx.x < 32 * Q) reinterpret_cast<uint32_t*>(lds_raw)[ZL * Q + threadIdx.x] = 0u;   // what empty places read
     for (uint32_t q = NEAR2 + threadIdx.x; q < ov_n; q += NT) ovgw[(size_t)ov0 + q] = 0.f;   // entry q is lane q % NT's
-    const int nl = (int)min((int64_t)wl, m - (int64_t)w * wl);   // labels of this window (the last one may be short)
-    const int nv = nl / 4;                                       // 16-byte pieces of a row slice
+    const int nl = (int)min((int64_t)cut.wl, m - (int64_t)w * cut.wl);   // labels of this window (the last one may be short)
+    const int nv = nl / 4;                                               // whole 16-byte pieces of a row slice
+    const int nf = min(cut.fpb, cut.vd - fb * cut.fpb);                            // features of this block that exist
+    const int nx = cut.S > 1 ? d : nf;                                   // ... and activations
     const int lines = (nl * 4 + 127) / 128, per = (lines + nfb - 1) / nfb;   // 128-byte lines; this workgroup's share of the warm-up
-    constexpr int XL = NF * (int)sizeof(TS) / 128;   // 128-byte lines of a feature block's activations
+    const int xlines = ((Q == 4 ? Q : 1) * nx * (int)sizeof(TS) + 127) / 128;    // 128-byte lines of the block's activations (per row of x)
     // the rest of a list (r = start | n << 16 in ov_near, n even), two entries in flight at a time
-    auto more = [&](float& acc0, float& acc1, uint32_t r, float x0, float x1) {
-        for (uint32_t q = r & 0xFFFFu, e = q + (r >> 16); q < e; q += 2) {
-            const uint2 o0 = ov_near[q], o1 = ov_near[q + 1];
-            const float2 u = row[o0.x / 8], v = row[o1.x / 8];
-            const float u0 = u.x, u1 = u.y, v0 = v.x, v1 = v.y;
-            acc0 = fmaf(__uint_as_float(o0.y), u0, acc0);
-            acc1 = fmaf(__uint_as_float(o0.y), u1, acc1);
-            acc0 = fmaf(__uint_as_float(o1.y), v0, acc0);
-            acc1 = fmaf(__uint_as_float(o1.y), v1, acc1);
-            ov_sum[q] = fmaf(x1, u1, fmaf(x0, u0, ov_sum[q]));           // the entries of a list are its lane's alone
-            ov_sum[q + 1] = fmaf(x1, v1, fmaf(x0, v0, ov_sum[q + 1]));
+    auto more = [&](float (&acc)[Q], uint32_t r, const float (&xv)[Q]) {
+        constexpr int AT_ONCE = Q == 2 ? 2 : 1;   // (four instances leave no registers for two)
+#pragma unroll 1
+        for (uint32_t q = r & 0xFFFFu, e = q + (r >> 16); q < e; q += AT_ONCE) {
+            uint2 o[AT_ONCE];
+            float u[AT_ONCE][Q], t[AT_ONCE];
+#pragma unroll
+            for (int a = 0; a < AT_ONCE; ++a) o[a] = ov_near[q + a];
+#pragma unroll
+            for (int a = 0; a < AT_ONCE; ++a) { unit_of(row + o[a].x / 4, u[a]); t[a] = ov_sum[q + a]; }   // the entries of a list are its lane's alone
+#pragma unroll
+            for (int a = 0; a < AT_ONCE; ++a) {
+#pragma unroll
+                for (int i = 0; i < Q; ++i) {
+                    acc[i] = fmaf(__uint_as_float(o[a].y), u[a][i], acc[i]);
+                    t[a] = fmaf(xv[i], u[a][i], t[a]);
+                }
+                ov_sum[q + a] = t[a];
+            }
         }
     };
-    // the activations of the lane's two features for the two instances of a pass
-    float xa0 = 0.f, xb0 = 0.f, xa1 = 0.f, xb1 = 0.f;
     // receives the L2 warm-up loads (issued from inline assembly, see k_bwi_lds; the build checks this kernel too)
     uint32_t token = 0;
-    for (int i = 0; i < rows; i += 2) {
-        const bool pair = i + 1 < rows;
-        const char* grow = reinterpret_cast<const char*>(g + (size_t)w * wl + (size_t)i * m);   // uniform
-        const TS* xrow = x + (size_t)i * d + (size_t)fb * NF;
+    for (int i = i_begin; i < i_end; i += Q) {
+        const int have = min(Q, i_end - i);                              // instances of this pass; the others read as zeros
+        const char* grow = reinterpret_cast<const char*>(g + (size_t)w * cut.wl + (size_t)i * m);   // uniform
+        const TS* xrow = Q == 4 ? x + (size_t)(i / Q) * x_stride + (size_t)fb * cut.fpb * Q : x + (size_t)i * x_stride + (size_t)fb * cut.fpb;
         // The lane's number, taken afresh in each part of a pass: whatever is computed from it (addresses in LDS, offsets
         // of copies) is then computed there, in a few instructions, and not kept in a register of its own across the
         // gathers -- there are none to spare, and a value that is spilled comes back through a load whose wait also
         // waits for the warm-up loads.
         uint32_t tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
-        {   // the block's activations of the two instances: 1 KiB pieces by LDS-DMA into the place of the sums (free
+        if (Q == 2) {   // the block's activations of the two instances: 1 KiB pieces by LDS-DMA into the place of the sums (free
             // until the gathers are done); read from memory by feature they cost as much as the slices of g.
             // Wavefront v overwrites bytes [1024 v, 1024 v + 1024) of that place: the piece that it alone read when the
             // sums of the pass before left (no barrier since then), so nobody else's sums are lost.
             static_assert(2 * NF / 4 == NT, "a lane copies out one float4 of the sums: wavefront v the v-th KiB");
             constexpr int PR = NF * (int)sizeof(TS) / 1024;
-            const int wv = (int)(tid >> 6);
-            if (wv < (pair ? 2 : 1) * PR)
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(reinterpret_cast<const char*>(xrow + (size_t)(wv / PR) * d) + ((uint32_t)(wv % PR) * 1024u + (tid & 63u) * 16u)),
+            const int wv = (int)(tid >> 6), piece = (wv % PR) * 1024 + (int)(tid & 63u) * 16;
+            if (wv < have * PR && piece < nx * (int)sizeof(TS))
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(reinterpret_cast<const char*>(xrow + (size_t)(wv / PR) * x_stride) + piece),
                                                  (__attribute__((address_space(3))) void*)(reinterpret_cast<unsigned char*>(outbuf) + (size_t)(wv / PR) * NF * sizeof(TS) + (size_t)(wv % PR) * 1024), 16, 0, 0);
+        } else {
+            const int bytes = nx * Q * (int)sizeof(TS);
+            for (int v = (int)(tid >> 6) * 1024; v < bytes; v += NT * 16)
+                if (v + (int)(tid & 63u) * 16 < bytes)
+                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(reinterpret_cast<const char*>(xrow) + v + (tid & 63u) * 16),
+                                                     (__attribute__((address_space(3))) void*)(reinterpret_cast<unsigned char*>(xbuf) + v), 16, 0, 0);
         }
-        {   // The slices of the two instances side by side, through registers: 16 bytes of each, interleaved, two 16-byte
-            // writes.  As fast as LDS-DMA of the two slices one after the other (37.6 against 38.2 bytes per clock), which
-            // cannot interleave them (by single words: 13.8).
-            const char* grow1 = grow + (pair ? (size_t)m * 4 : 0);   // uniform, like grow
+        {   // The slices of the instances side by side, through registers: 16 bytes of each, interleaved, Q writes of 16
+            // bytes.  As fast as LDS-DMA of the slices one after the other (37.6 against 38.2 bytes per clock), which
+            // cannot interleave them (by single words: 13.8), and for rows of any alignment.
+            const size_t rb = (size_t)m * 4;
+            if constexpr (Q == 2) {
+                const char* grow1 = grow + (have > 1 ? rb : 0);
 #pragma unroll 1
-            for (uint32_t o = tid * 16u; o < (uint32_t)nv * 16u; o += NT * 16u) {
-                const float4 a = *reinterpret_cast<const float4*>(grow + o);
-                float4 c = *reinterpret_cast<const float4*>(grow1 + o);
-                if (!pair) c = make_float4(0.f, 0.f, 0.f, 0.f);   // an odd batch: the last pass has one instance
-                float4* to = reinterpret_cast<float4*>(lds_raw + 2u * o);
-                to[0] = make_float4(a.x, c.x, a.y, c.y);
-                to[1] = make_float4(a.z, c.z, a.w, c.w);
+                for (uint32_t o = tid * 16u; o < (uint32_t)nv * 16u; o += NT * 16u) {
+                    const f32x4_any a = *reinterpret_cast<const f32x4_any*>(grow + o);
+                    f32x4_any c = *reinterpret_cast<const f32x4_any*>(grow1 + o);
+                    if (have < 2) c = (f32x4_any){0.f, 0.f, 0.f, 0.f};
+                    float4* to = reinterpret_cast<float4*>(lds_raw + 2u * o);
+                    to[0] = make_float4(a.x, c.x, a.y, c.y);
+                    to[1] = make_float4(a.z, c.z, a.w, c.w);
+                }
+            } else {
+                // (a label per lane: its unit is one 16-byte write, next to its neighbours'; 16 bytes of a row per lane would
+                // put the writes of a pass 64 bytes apart, four to a bank)
+                const char *grow1 = grow + (have > 1 ? rb : 0), *grow2 = grow + (have > 2 ? 2 * rb : 0), *grow3 = grow + (have > 3 ? 3 * rb : 0);
+#pragma unroll 2
+                for (uint32_t o = tid * 4u; o < (uint32_t)nl * 4u; o += NT * 4u) {
+                    float4 v = make_float4(*reinterpret_cast<const float*>(grow + o), *reinterpret_cast<const float*>(grow1 + o),
+                                           *reinterpret_cast<const float*>(grow2 + o), *reinterpret_cast<const float*>(grow3 + o));
+                    if (have < 2) v.y = 0.f;
+                    if (have < 3) v.z = 0.f;
+                    if (have < 4) v.w = 0.f;
+                    *reinterpret_cast<float4*>(lds_raw + 4u * o) = v;
+                }
+            }
+            if (Q == 2 && (int)tid < (nl & 3) * Q) {   // the last labels of a slice that is no multiple of four
+                const int l = nv * 4 + (int)tid / Q, q = (int)tid % Q;
+                reinterpret_cast<float*>(lds_raw)[l * Q + q] = q < have ? *reinterpret_cast<const float*>(grow + (size_t)q * rb + (size_t)l * 4) : 0.f;
             }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             asm volatile("" : "+v"(token));
@@ -850,73 +1038,108 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
         __syncthreads();
         tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
-        {
+        // the activations of the lane's features (Q = 2: of both, before their place is needed for the sums)
+        float xa[Q], xb[Q];
+        if constexpr (Q == 2) {
             const uint32_t f = feat_of[tid];
-            const TS* xbuf = reinterpret_cast<const TS*>(outbuf);
-            xa0 = usl_load_f32<TS>(xbuf, (size_t)(f & 0xFFFFu));
-            xb0 = usl_load_f32<TS>(xbuf, (size_t)(f >> 16));
-            xa1 = pair ? usl_load_f32<TS>(xbuf, (size_t)NF + (f & 0xFFFFu)) : 0.f;
-            xb1 = pair ? usl_load_f32<TS>(xbuf, (size_t)NF + (f >> 16)) : 0.f;
+            xa[0] = usl_load_f32<TS>(xbuf, (size_t)(f & 0xFFFFu));
+            xb[0] = usl_load_f32<TS>(xbuf, (size_t)(f >> 16));
+            xa[1] = have > 1 ? usl_load_f32<TS>(xbuf, (size_t)NF + (f & 0xFFFFu)) : 0.f;
+            xb[1] = have > 1 ? usl_load_f32<TS>(xbuf, (size_t)NF + (f >> 16)) : 0.f;
         }
-        if (i + 2 < rows) {   // one load per 128-byte line of what the next pass reads: the window's workgroups share
-            // the lines of its two slices of g, then come the block's own lines of the two rows of x
-            for (int j = (int)tid; j < 2 * per + 2 * XL; j += NT) {   // (no divisions: every lane comes through here)
-                const bool of_g = j < 2 * per;
-                const int jj = of_g ? j : j - 2 * per, half = of_g ? per : XL;
-                const int r = jj >= half ? 1 : 0, c = (of_g ? fb * per : 0) + jj - r * half;
-                const char* line = (of_g ? grow + (size_t)m * 4 * (2 + r) : reinterpret_cast<const char*>(xrow + (size_t)(2 + r) * d)) + (size_t)c * 128;
-                if (i + 2 + r < rows && (!of_g || c < lines))
+        if (i + Q < i_end) {   // one load per 128-byte line of what the next pass reads: the window's workgroups share
+            // the lines of its slices of g, then come the block's own lines of x
+            constexpr int XR = Q == 4 ? 1 : Q;
+            for (int j = (int)tid; j < Q * per + XR * xlines; j += NT) {   // (no divisions: every lane comes through here)
+                const bool of_g = j < Q * per;
+                const int jj = of_g ? j : j - Q * per, half = of_g ? per : xlines;
+                int r = 0;
+#pragma unroll
+                for (int q = 1; q < Q; ++q) r += jj >= q * half ? 1 : 0;
+                const int c = (of_g ? fb * per : 0) + jj - r * half;
+                const char* line = (of_g ? grow + (size_t)m * 4 * (Q + r) : reinterpret_cast<const char*>(xrow + (Q == 4 ? x_stride : (size_t)(Q + r) * x_stride))) + (size_t)c * 128;
+                if (i + Q + r < i_end && (!of_g || c < lines))
                     asm volatile("global_load_dword %0, %1, off" : "+v"(token) : "v"(line));
             }
         }
-        float acc_a0 = 0.f, acc_a1 = 0.f, acc_b0 = 0.f, acc_b1 = 0.f;
+        float acc_a[Q] = {}, acc_b[Q] = {};
         int ac = acap, bc = bcap;   // compared afresh in every pass, see k_bwi_lds
         asm volatile("" : "+s"(ac), "+s"(bc));
+        if constexpr (Q == 4) unit_of(xbuf + (size_t)(feat_of[NT + tid] & 0xFFFFu) * 4, xa);
 #pragma unroll
         for (int q = 0; q < KT / 4; ++q) {
             if (q * 4 < ac)
-                gather4_two(acc_a0, acc_a1, gw[q * 4], gw[q * 4 + 1], gw[q * 4 + 2], gw[q * 4 + 3], pk[q * 2], pk[q * 2 + 1],
-                            wt[q * 4], wt[q * 4 + 1], wt[q * 4 + 2], wt[q * 4 + 3], xa0, xa1);
+                gather_group<Q>(acc_a, gw[q * 4], gw[q * 4 + 1], gw[q * 4 + 2], gw[q * 4 + 3], pk[q * 2], pk[q * 2 + 1],
+                                wt[q * 4], wt[q * 4 + 1], wt[q * 4 + 2], wt[q * 4 + 3], xa);
+        }
+        if constexpr (Q == 4) {   // the first list's sums leave before the second list begins: their registers are needed
+            tid = threadIdx.x;
+            asm volatile("" : "+v"(tid));
+            if (ov_n) more(acc_a, ovr_a[tid], xa);
+            const uint32_t f = feat_of[tid] & 0xFFFFu;
+#pragma unroll
+            for (int j = 0; j < Q; ++j) outbuf[j * NF + f] = acc_a[j];
+            unit_of(xbuf + (size_t)(feat_of[NT + tid] >> 16) * 4, xb);
         }
 #pragma unroll
         for (int q = 0; q < KT / 4; ++q) {
             if (q * 4 >= KT - bc)
-                gather4_two(acc_b0, acc_b1, gw[q * 4], gw[q * 4 + 1], gw[q * 4 + 2], gw[q * 4 + 3], pk[q * 2], pk[q * 2 + 1],
-                            wt[q * 4], wt[q * 4 + 1], wt[q * 4 + 2], wt[q * 4 + 3], xb0, xb1);
+                gather_group<Q>(acc_b, gw[q * 4], gw[q * 4 + 1], gw[q * 4 + 2], gw[q * 4 + 3], pk[q * 2], pk[q * 2 + 1],
+                                wt[q * 4], wt[q * 4 + 1], wt[q * 4 + 2], wt[q * 4 + 3], xb);
         }
         tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
-        if (ov_n) {   // the same for the whole workgroup: the few lanes whose lists did not fit go on through LDS
-            more(acc_a0, acc_a1, ovr_a[tid], xa0, xa1);
-            more(acc_b0, acc_b1, ovr_b[tid], xb0, xb1);
-        }
-        __syncthreads();   // every lane has taken its activations from the place of the sums
-        {
+        if constexpr (Q == 2) {
+            if (ov_n) {   // the same for the whole workgroup: the few lanes whose lists did not fit go on through LDS
+                more(acc_a, ovr_a[tid], xa);
+                more(acc_b, ovr_b[tid], xb);
+            }
+            __syncthreads();   // every lane has taken its activations from the place of the sums
             const uint32_t f = feat_of[tid];
-            outbuf[f & 0xFFFFu] = acc_a0;
-            outbuf[NF + (f & 0xFFFFu)] = acc_a1;
-            outbuf[f >> 16] = acc_b0;
-            outbuf[NF + (f >> 16)] = acc_b1;
+            outbuf[f & 0xFFFFu] = acc_a[0];
+            outbuf[NF + (f & 0xFFFFu)] = acc_a[1];
+            outbuf[f >> 16] = acc_b[0];
+            outbuf[NF + (f >> 16)] = acc_b[1];
+        } else {
+            if (ov_n) more(acc_b, ovr_b[tid], xb);
+            const uint32_t f = feat_of[tid] >> 16;
+#pragma unroll
+            for (int j = 0; j < Q; ++j) outbuf[j * NF + f] = acc_b[j];
         }
         if (ov_n > (uint32_t)NEAR2) {   // only a skewed connectivity gets here: what LDS does not hold, by atomics
             __syncthreads();
-            const TS* xr = xrow;
             for (uint32_t q = NEAR2 + tid; q < ov_n; q += NT) {
                 const OvEntry o = ov[(size_t)ov0 + q];
                 if (o.slot == PAD_SLOT) continue;
-                const float wv = usl_load_f32<TS>(W, (size_t)o.slot), u0 = row[o.label].x, u1 = row[o.label].y;
-                unsafeAtomicAdd(&outbuf[o.feature], wv * u0);
-                unsafeAtomicAdd(&outbuf[NF + o.feature], wv * u1);
-                float t = fmaf(usl_load_f32<TS>(xr, (size_t)o.feature), u0, ovgw[(size_t)ov0 + q]);
-                if (pair) t = fmaf(usl_load_f32<TS>(xr + d, (size_t)o.feature), u1, t);
+                const float wv = usl_load_f32<TS>(W, (size_t)o.slot);
+                float u[Q];
+                unit_of(row + (size_t)o.label * Q, u);
+                float t = ovgw[(size_t)ov0 + q];
+                const size_t xf = cut.S > 1 ? o.feature % (uint32_t)d : o.feature;
+#pragma unroll
+                for (int j = 0; j < Q; ++j) {
+                    unsafeAtomicAdd(&outbuf[j * NF + o.feature], wv * u[j]);
+                    if (j < have) t = fmaf(usl_load_f32<TS>(xrow, Q == 4 ? xf * Q + j : (size_t)j * x_stride + xf), u[j], t);
+                }
                 ovgw[(size_t)ov0 + q] = t;
             }
         }
         __syncthreads();
-        {   // the block's sums of the two instances leave as two contiguous runs
-            float* dst = partial + ((size_t)w * rows + i) * d + (size_t)fb * NF;
-            for (int v = (int)tid; v < (pair ? 2 : 1) * (NF / 4); v += NT)
-                reinterpret_cast<float4*>(dst + (size_t)(v / (NF / 4)) * d)[v % (NF / 4)] = reinterpret_cast<const float4*>(outbuf)[v];
+        if (Q == 2 || cut.S == 1) {   // the block's sums leave as contiguous runs (rows of dp floats, dp a multiple of 4)
+            float* dst = partial + ((size_t)w * rows + i) * dp + (size_t)fb * cut.fpb;
+            for (int v = (int)tid; v < have * (NF / 4); v += NT)
+                if (v % (NF / 4) * 4 < nf)
+                    reinterpret_cast<float4*>(dst + (size_t)(v / (NF / 4)) * dp)[v % (NF / 4)] = reinterpret_cast<const float4*>(outbuf)[v];
+        } else {                      // ... those of the window's runs added up
+            float* dst = partial + ((size_t)w * rows + i) * dp;
+            for (int v = (int)tid; v < have * NT; v += NT) {
+                const int j = v / NT, c = v % NT;   // d <= NT where there is more than one run
+                if (c < d) {
+                    float t = 0.f;
+                    for (int r = 0; r < cut.S; ++r) t += outbuf[j * NF + r * d + c];
+                    dst[(size_t)j * dp + c] = t;
+                }
+            }
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -926,19 +1149,18 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
     // they would be 4 bytes each into lines that 16 workgroups share (0.29 ms at m = 500k, a fifth of this kernel); the
     // Adam kernel picks them up through pos instead, and finds neighbours there.  As many places at a time as LDS
     // holds below ov_sum (all of them, unless the connectivity is skewed).
-    constexpr uint32_t CH = (uint32_t)((LDS2_BYTES - (size_t)NEAR2 * 4) / 4);
-    float* perm = reinterpret_cast<float*>(lds_raw);
-    const uint32_t e0 = ent_base[wg], n_ent = ent_base[wg + 1] - e0;
     for (uint32_t c0 = 0; c0 < n_ent; c0 += CH) {
         __syncthreads();   // the last pass's reads of LDS, the owners' last additions to ov_sum; the copy before
 #pragma unroll
-        for (int q = 0; q < KT / 4; ++q) {
-            if (q * 4 < acap || q * 4 >= KT - bcap) {
+        for (int t0 = 0; t0 < KT; t0 += PB) {
+            uint32_t r[PB];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const uint32_t r = rk[(wg * KT + q * 4 + u) * NT + threadIdx.x] - c0;   // an empty place: far beyond
-                    if (r < CH) perm[r] = gw[q * 4 + u];
-                }
+            for (int u = 0; u < PB; ++u) r[u] = (rk + wg * KT * NT)[(uint32_t)(t0 + u) * NT + threadIdx.x] - c0;   // an empty place: far beyond
+#pragma unroll
+            for (int u = 0; u < PB; ++u) {
+                const int t = t0 + u;
+                const bool used = t / 4 * 4 < acap || t / 4 * 4 >= KT - bcap;
+                if (used && r[u] < CH) perm[r[u]] = gw[t];
             }
         }
         for (uint32_t q = threadIdx.x; q < ov_n; q += NT) {
@@ -951,11 +1173,12 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
     }
 }
 
-// grad_x[i][c] = sum over the windows of partial[w][i][c].  BOTH only names the kernel after the one whose sums it
-// adds (twice the windows there), so that a profile tells the two apart.
+// grad_x[i][c] = sum over the windows of partial[w][i][c], i < rows; a row of partial is dp floats (d rounded up to a
+// multiple of 4).  BOTH only names the kernel after the one whose sums it adds, so that a profile tells the two apart.
+// vec: rows of grad_x are 16-byte aligned too.
 template <bool BOTH>
 __global__ void __launch_bounds__(256)
-k_lf_reduce(const float4* __restrict__ partial, int nwin, size_t n4, float4* __restrict__ out,
+k_lf_reduce(const float4* __restrict__ partial, int nwin, size_t n4, int d, int dp, bool vec, float* __restrict__ out,
             const uint32_t* __restrict__ gate, const uint32_t* __restrict__ stale) {
     if (gate && *gate == 0) return;
     const bool poison = *stale != 0;   // the lists were built from other contents of idx: no number is better than a wrong one
@@ -968,34 +1191,77 @@ k_lf_reduce(const float4* __restrict__ partial, int nwin, size_t n4, float4* __r
             a.x += t.x; a.y += t.y; a.z += t.z; a.w += t.w;
         }
         if (poison) a.x = a.y = a.z = a.w = __uint_as_float(0x7FC00000u);
-        out[v] = a;
+        if (vec) {
+            reinterpret_cast<float4*>(out)[v] = a;
+        } else {
+            const uint32_t row4 = (uint32_t)dp / 4, i = (uint32_t)(v / row4), c = (uint32_t)(v % row4) * 4;
+            float* to = out + (size_t)i * d + c;
+            const float r[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if ((int)c + q < d) to[q] = r[q];
+        }
     }
 }
 
 }  // namespace
 
-// Windows: as many labels as send about 32 connections into a feature (the registers of a lane hold two such lists;
-// 16 connections for the lists of the kernel that keeps a weight-gradient sum per slot as well), at most WL (the LDS
-// row; ZERO_LABEL2 there, two rows), a multiple of 4 (16-byte copies); a layer's windows are of equal size.
-static int lf_window_cap(const usl_ctx* c, int set) {
-    const int64_t by_lists = (int64_t)(set ? 16 : 32) * c->d / c->k, most = set ? (int64_t)ZERO_LABEL2 : (int64_t)WL;
-    return (int)((by_lists < most ? by_lists : most) / 4 * 4);
+// ---- how a layer is cut up for either form --------------------------------------------------------------------
+
+// (window, feature block) workgroups run in rounds of one per compute unit: a last round that is not full takes as
+// long as a full one, so the windows are made a little shorter until the rounds are full (up to a quarter more
+// windows: more than that and the extra partial sums cost what the shorter lists save).
+static int64_t full_rounds(const usl_ctx* c, int64_t nwin, int64_t nfb) {
+    const int64_t cu = c->num_cu > 0 ? c->num_cu : 1;
+    const int64_t rounds = (nwin * nfb + cu - 1) / cu, full = rounds * cu / nfb;
+    return full > nwin && full * 4 <= nwin * 5 ? full : nwin;
 }
-static int lf_windows(const usl_ctx* c, int set) {
-    const int cap = lf_window_cap(c, set);
-    int64_t nwin = (c->m + cap - 1) / cap;
-    // (window, feature block) workgroups run in rounds of one per compute unit: a last round that is not full takes as
-    // long as a full one, so the windows are made a little shorter until the rounds are full (up to a quarter more
-    // windows: more than that and the extra partial sums cost what the shorter lists save)
-    const int64_t nfb = c->d / NF, cu = c->num_cu > 0 ? c->num_cu : 1;
-    const int64_t rounds = (nwin * nfb + cu - 1) / cu;
-    const int64_t full = rounds * cu / nfb;
-    if (full > nwin && full * 4 <= nwin * 5) nwin = full;
-    return (int)nwin;
+
+// usl_backward_input's form: windows of as many labels as send about 32 connections into a feature (the registers of a
+// lane hold two such lists), at most WL (the LDS row), a multiple of 4 (16-byte copies), all of equal size.
+static Cut bwi_cut(const usl_ctx* c) {
+    const int64_t by_lists = (int64_t)32 * c->d / c->k, cap = (by_lists < WL ? by_lists : WL) / 4 * 4;
+    Cut cut;
+    cut.S = 1;
+    cut.vd = c->d;
+    cut.nfb = (c->d + NF - 1) / NF;
+    cut.fpb = NF;
+    cut.nwin = (int)full_rounds(c, (c->m + cap - 1) / cap, cut.nfb);
+    cut.run = cut.wl = (int)(((c->m + cut.nwin - 1) / cut.nwin + 3) / 4 * 4);
+    return cut;
 }
-static int lf_window_labels(const usl_ctx* c, int set) {
-    const int64_t nwin = lf_windows(c, set);
-    return (int)(((c->m + nwin - 1) / nwin + 3) / 4 * 4);
+
+// Instances that a pass of the kernel for both products takes together: four where windows that send 11 connections into
+// a feature fit LDS four rows at a time, else two.  A pass is a chain of waits, so the fewer the better; with shorter lists
+// there are too many windows (backward, m = 100k, d = 20k, k = 48 (lists of 11), b = 64: 167 us with four, 195 with two;
+// m = 300k, d = 14k, k = 32 (10.7): 362 and 365; m = 670k, d = 16k, k = 32 (9.1): 472 and 414).
+static int both_q(const usl_ctx* c) {
+    return c->d <= NT || (int64_t)11 * c->d / c->k <= (int64_t)BothLayout<4>::zero_label ? 4 : 2;
+}
+// The form for both products: lists of 16 connections (half the registers go to the weight-gradient sums; with four
+// instances a lane has 32 slots instead of 36, hence 14), longer where the features do not fill the lanes twice over;
+// blocks of equal size; S runs where the layer is narrower than half a block.
+static Cut both_cut(const usl_ctx* c) {
+    Cut cut;
+    cut.S = c->d <= NT ? NF / c->d : 1;
+    cut.vd = cut.S * c->d;
+    cut.nfb = (cut.vd + NF - 1) / NF;
+    cut.fpb = ((cut.vd + cut.nfb - 1) / cut.nfb + 31) / 32 * 32;
+    const int64_t mean = both_q(c) == 4 ? 14 : 16, longest = both_q(c) == 4 ? 21 : 24;
+    const int64_t lists = mean * NF / cut.fpb < longest ? mean * NF / cut.fpb : longest;
+    const int64_t most = (int64_t)(both_q(c) == 4 ? BothLayout<4>::zero_label : BothLayout<2>::zero_label) / cut.S;
+    int64_t run = lists * c->d / c->k;
+    run = run < most ? run : most;
+    run = run >= 4 ? run / 4 * 4 : 4;
+    if (cut.S == 1) {
+        cut.nwin = (int)full_rounds(c, (c->m + run - 1) / run, cut.nfb);
+        cut.run = cut.wl = (int)(((c->m + cut.nwin - 1) / cut.nwin + 3) / 4 * 4);
+    } else {
+        cut.run = (int)run;
+        cut.wl = cut.run * cut.S;
+        cut.nwin = (int)((c->m + cut.wl - 1) / cut.wl);
+    }
+    return cut;
 }
 
 // The most that the partial sums of a pass over the batch may take: 16 GiB on a device with 128 GiB or more (every
@@ -1012,52 +1278,49 @@ static size_t lf_partial_bytes() {
 }
 
 // runs of SEG slots in a window of the lists for both products
-static int lf_runs(const usl_ctx* c) { return (int)(((int64_t)lf_window_labels(c, 1) * c->k + SEG - 1) / SEG); }
+static int lf_runs(const usl_ctx* c, const Cut& cut) { return (int)(((int64_t)cut.wl * c->k + SEG - 1) / SEG); }
 
-static bool lf_shape_ok(const usl_ctx* c, int set) {
-    const int64_t lists = (int64_t)(set ? 16 : 32) * c->d / c->k;   // labels that send that many connections into a feature
-    return c->d % NF == 0 && c->d <= 65536 && c->m % 4 == 0 && lists >= 2048 && lists <= WL &&
-           c->m * (int64_t)c->k < (int64_t)PAD_SLOT;
-}
+static int padded_d(const usl_ctx* c) { return (c->d + 3) / 4 * 4; }
 
-// Is this layer one for the LDS form?  Lists of about 32 entries per (window, feature) from windows of 16384 to
+// Is this layer one for the one-product form?  Lists of about 32 entries per (window, feature) from windows of 16384 to
 // 32768 labels (k / d between 1/1024 and 1/512: longer windows do not fit LDS, with shorter ones the partial sums of
 // the many windows outweigh the gain), whole feature blocks, 16-byte aligned rows of g, and enough (window, feature
 // block) workgroups to fill the chip.  USL_TUNE_BWI=lds forces it where the shape allows at all, =l2 forbids it.
 bool usl_bwi_lds_applies(const usl_ctx* c) {
-    if (!lf_shape_ok(c, 0)) return false;
+    const int64_t lists = (int64_t)32 * c->d / c->k;   // labels that send that many connections into a feature
+    if (!(c->d % NF == 0 && c->d <= 65536 && c->m % 4 == 0 && lists >= 2048 && lists <= WL && c->m * (int64_t)c->k < (int64_t)PAD_SLOT))
+        return false;
     if (const char* e = getenv("USL_TUNE_BWI")) {
         if (!strcmp(e, "lds")) return true;
         if (!strcmp(e, "l2")) return false;
     }
-    return (int64_t)32 * c->d / c->k >= 16384 && (int64_t)lf_windows(c, 0) * (c->d / NF) * 4 >= (int64_t)c->num_cu * 3;
+    const Cut cut = bwi_cut(c);
+    return lists >= 16384 && (int64_t)cut.nwin * cut.nfb * 4 >= (int64_t)c->num_cu * 3;
 }
 
-// ... and one for the kernel that computes both backward products from one pass of gathers?  The same with lists of
-// 16 entries or fewer from windows of 8192 to 15968 labels (k / d of 1/512 or less: twice the windows, twice the
-// partial sums).
+// ... and one for the kernel that computes both backward products from one pass of gathers?
 // USL_TUNE_BOTH=on forces it where the shape allows at all, =off forbids it.
-static bool lf_a_pass_fits(const usl_ctx* c);
 bool usl_both_lds_applies(const usl_ctx* c) {
-    if (!lf_shape_ok(c, 1) || !lf_a_pass_fits(c)) return false;
+    if (c->d > 65536 || c->m * (int64_t)c->k >= (int64_t)PAD_SLOT || c->no_order) return false;
+    const Cut cut = both_cut(c);
+    // the partial sums of a pass of 64 instances (the fewest a pass takes) must fit the allowance
+    if ((size_t)cut.nwin * 64 * (size_t)padded_d(c) * 4 > lf_partial_bytes()) return false;
     if (const char* e = getenv("USL_TUNE_BOTH")) {
         if (!strcmp(e, "on")) return true;
         if (!strcmp(e, "off")) return false;
     }
-    return (int64_t)16 * c->d / c->k >= 8192 && (int64_t)lf_windows(c, 1) * (c->d / NF) * 4 >= (int64_t)c->num_cu * 3;
-}
-
-// The partial sums of a pass of 64 instances (the fewest a pass takes) must fit the allowance.
-static bool lf_a_pass_fits(const usl_ctx* c) {
-    return (size_t)lf_windows(c, 1) * 64 * (size_t)c->d * 4 <= lf_partial_bytes();
+    // (its fixed cost is some 5 us more than that of the two kernels: backward at m = 1000, d = 64, k = 8, b = 100: 32.9 us
+    // against 27.9; m = 4000, d = 768, k = 16, b = 32: 32.1 against 27.5; m = 2000, d = 8000, k = 8, b = 512: 55 against 86)
+    return c->m * (int64_t)c->k * c->max_b >= (int64_t)4 << 20;
 }
 
 template <int KT>
-static usl_status lf_build_t(usl_ctx* c, const int32_t* idx, int set) {
+static usl_status lf_build_t(usl_ctx* c, const int32_t* idx, int set, const Cut& cut) {
     auto& L = c->lf[set];
     const size_t N = (size_t)c->m * c->k;
-    const int nwin = lf_windows(c, set), wl = lf_window_labels(c, set), nfb = c->d / NF, nwg = nwin * nfb;
-    const size_t nbins = (size_t)nwin * c->d;
+    const int nwin = cut.nwin, nfb = cut.nfb, nwg = nwin * nfb;
+    const size_t nbins = (size_t)nwin * cut.vd;
+    const int Q = set == 1 ? both_q(c) : 1;
     USL_TRY(usl_reserve(c, (void**)&L.count, &L.count_cap, nbins * 4));
     USL_TRY(usl_reserve(c, (void**)&L.taken, &L.taken_cap, nbins * 4));
     USL_TRY(usl_reserve(c, (void**)&L.where, &L.where_cap, nbins * 4));
@@ -1066,52 +1329,53 @@ static usl_status lf_build_t(usl_ctx* c, const int32_t* idx, int set) {
     USL_TRY(usl_reserve(c, (void**)&L.ov_base, &L.ov_base_cap, ((size_t)nwg * 4 + 2) * 4));
     USL_TRY(usl_reserve(c, (void**)&L.ovr, &L.ovr_cap, (size_t)nwg * 2 * NT * 4));
     USL_TRY(usl_reserve(c, (void**)&L.lab, &L.lab_cap, (size_t)nwg * KT * NT * 2));
-    USL_TRY(usl_reserve(c, (void**)&L.slot, &L.slot_cap, (size_t)nwg * KT * NT * 4));
+    USL_TRY(usl_reserve(c, (void**)&L.slot, &L.slot_cap, (set == 1 ? N : (size_t)nwg * KT * NT) * 4));   // by place, or by list
     USL_TRY(usl_reserve(c, (void**)&L.ent, &L.ent_cap, N * 4));
     USL_TRY(usl_reserve(c, (void**)&L.ovoff, &L.ovoff_cap, nbins * 4));
     USL_TRY(usl_reserve(c, (void**)&L.ov, &L.ov_cap, (N + nbins) * sizeof(OvEntry)));   // worst case, + an empty place per list
-    if (set == 1) {
-        // stage [N], the sums of the overflow entries beyond LDS [N + nbins]; pos [N], rk [nwg][KT][NT], ovrk [N + nbins],
-        // the counts of the runs [nwg][nseg]
-        USL_TRY(usl_reserve(c, (void**)&L.stage, &L.stage_cap, (N + N + nbins) * 4));
-        USL_TRY(usl_reserve(c, (void**)&L.pos, &L.pos_cap, (N + (size_t)nwg * KT * NT + N + nbins + (size_t)nwg * lf_runs(c)) * 4));
-    }
+    if (set == 1)   // pos [N], rk [nwg][KT][NT], ovrk [N + nbins], the counts of the runs [nwg][nseg]
+        USL_TRY(usl_reserve(c, (void**)&L.pos, &L.pos_cap, (N + (size_t)nwg * KT * NT + N + nbins + (size_t)nwg * lf_runs(c, cut)) * 4));
     int rounds = 3;                // of proposals per step of the bank-aware order; 0 = lists stay as filled
     if (const char* e = getenv("USL_TUNE_ROUNDS")) rounds = atoi(e);
     uint32_t* ov_base = L.ov_base;                   // [nwg + 1]
     uint32_t* n_ov = ov_base + nwg + 1;              // [nwg]
     uint32_t* ent_base = n_ov + nwg;                 // [nwg + 1]
     uint32_t* n_ent = ent_base + nwg + 1;            // [nwg]
-    const unsigned chunks = (unsigned)((c->d + CHUNK - 1) / CHUNK);
+    const unsigned chunks = (unsigned)((cut.vd + CHUNK - 1) / CHUNK);
     int splits = (int)((size_t)c->num_cu / ((size_t)nwin * chunks));
     splits = splits < 1 ? 1 : splits > 16 ? 16 : splits;
     const dim3 grid((unsigned)(nwin * splits), chunks);
-    const size_t lds = (size_t)(c->d < CHUNK ? c->d : CHUNK) * 4;
+    const size_t lds = (size_t)(cut.vd < CHUNK ? cut.vd : CHUNK) * 4;
     USL_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(k_lf_count), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     USL_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(k_lf_fill), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     const dim3 fillg(c->num_cu * 4), fillb(256);
     hipLaunchKernelGGL(k_fill_u32, fillg, fillb, 0, c->stream, L.count, nbins, 0u);
     hipLaunchKernelGGL(k_fill_u32, fillg, fillb, 0, c->stream, L.taken, nbins, 0u);
-    hipLaunchKernelGGL(k_lf_count, grid, dim3(NT), lds, c->stream, idx, c->m, c->k, c->d, wl, splits, L.count);
-    hipLaunchKernelGGL(k_lf_plan<KT>, dim3((unsigned)nwg), dim3(NT), 0, c->stream, L.count, c->d, nfb, L.where, L.ovoff,
+    hipLaunchKernelGGL(k_lf_count, grid, dim3(NT), lds, c->stream, idx, c->m, c->k, c->d, cut, splits, L.count);
+    hipLaunchKernelGGL(k_lf_plan<KT>, dim3((unsigned)nwg), dim3(NT), 0, c->stream, L.count, cut.vd, nfb, cut.fpb, L.where, L.ovoff,
                        L.feat, L.caps, n_ent, n_ov, L.ovr);
     hipLaunchKernelGGL(k_lf_scan, dim3(1), dim3(1024), 0, c->stream, n_ov, nwg, ov_base);
     hipLaunchKernelGGL(k_lf_scan, dim3(1), dim3(1024), 0, c->stream, n_ent, nwg, ent_base);
-    hipLaunchKernelGGL(k_lf_fill, grid, dim3(NT), lds, c->stream, idx, c->m, c->k, c->d, wl, nfb, splits, L.where, L.taken,
+    hipLaunchKernelGGL(k_lf_fill, grid, dim3(NT), lds, c->stream, idx, c->m, c->k, c->d, cut, splits, L.where, L.taken,
                        ent_base, L.ent);
     if (set == 1) {   // where the weight gradients go (before the order of the lists, which hands the places on)
-        const int nseg = lf_runs(c);
+        const int nseg = lf_runs(c, cut);
         const int64_t total = (int64_t)nwin * nseg;
         uint32_t* segcnt = L.pos + N + (size_t)nwg * KT * NT + N + nbins;
         const dim3 sg((unsigned)((total + 3) / 4));
-        hipLaunchKernelGGL(k_lf_seg_count, sg, dim3(256), 0, c->stream, idx, c->m, c->k, wl, nfb, nseg, total, segcnt);
+        hipLaunchKernelGGL(k_lf_seg_count, sg, dim3(256), 0, c->stream, idx, c->m, c->k, cut, nseg, total, segcnt);
         hipLaunchKernelGGL(k_lf_seg_scan, dim3((unsigned)nwg), dim3(256), 0, c->stream, segcnt, nseg, ent_base);
-        hipLaunchKernelGGL(k_lf_seg_place, sg, dim3(256), 0, c->stream, idx, c->m, c->k, wl, nfb, nseg, total, segcnt, L.pos);
+        hipLaunchKernelGGL(k_lf_seg_place, sg, dim3(256), 0, c->stream, idx, c->m, c->k, cut, nseg, total, segcnt, L.pos, L.slot);
     }
-    hipLaunchKernelGGL(k_lf_schedule<KT>, dim3((unsigned)(nwg * 64 / SG)), dim3(SG * 32), 0, c->stream, L.ent, ent_base,
-                       L.where, L.count, L.feat, L.caps, ov_base, L.ovoff, c->k, c->d, wl, nfb, rounds,
-                       L.lab, L.slot, reinterpret_cast<OvEntry*>(L.ov), set == 1 ? L.pos : nullptr,
-                       set == 1 ? L.pos + N : nullptr, set == 1 ? L.pos + N + (size_t)nwg * KT * NT : nullptr);
+    const uint32_t zero_label = set == 0 ? ZERO_LABEL : Q == 4 ? BothLayout<4>::zero_label : BothLayout<2>::zero_label;
+#define USL_LF_SCHED(GS)                                                                                                    \
+    hipLaunchKernelGGL((k_lf_schedule<KT, GS>), dim3((unsigned)(nwg * 64 / (SG_NT / 32))), dim3(SG_NT), 0, c->stream, L.ent, \
+                       ent_base, L.where, L.count, L.feat, L.caps, ov_base, L.ovoff, c->k, cut, zero_label, rounds,          \
+                       L.lab, set == 1 ? nullptr : L.slot, reinterpret_cast<OvEntry*>(L.ov), set == 1 ? L.pos : nullptr,      \
+                       set == 1 ? L.pos + N : nullptr, set == 1 ? L.pos + N + (size_t)nwg * KT * NT : nullptr)
+    if (Q == 4) USL_LF_SCHED(16);
+    else USL_LF_SCHED(32);
+#undef USL_LF_SCHED
     USL_TRY(usl_idx_fingerprint(c, idx, 1));
     USL_TRY(usl_check_launch(c, "register lists of the input gradient"));
     // one fingerprint: it belongs to the lists built last
@@ -1121,89 +1385,147 @@ static usl_status lf_build_t(usl_ctx* c, const int32_t* idx, int set) {
     return USL_OK;
 }
 
-// One or both backward products through the register lists (set 0: grad_x only; set 1: grad_x and grad_W).
-template <int KT, bool BOTH>
-static usl_status lf_run_t(usl_ctx* c, int set, const float* g, const void* x, const int32_t* idx, const void* W,
-                           float* grad_x, int32_t b, const uint32_t* gate) {
-    auto& L = c->lf[set];
-    // same address as when the lists were built: check that the contents are the same (else grad_x becomes NaN and
-    // usl_check reports it)
-    if (L.built_for != idx) USL_TRY(lf_build_t<KT>(c, idx, set));
-    else USL_TRY(usl_idx_fingerprint(c, idx, 0));
-    const uint32_t* stale = reinterpret_cast<const uint32_t*>(c->idx_print) + 4;
-    const int nwin = lf_windows(c, set), wl = lf_window_labels(c, set), nfb = c->d / NF;
-    // instances per pass: every pass loads the lists and the weights anew, and its partial sums are nwin * G * d
-    // floats; as many as the allowance for partial sums admits, sized once for max_b.  The weight gradient is a sum over the
-    // whole batch, kept in registers during a pass: a later pass adds its sums to what the earlier ones left.
-    int G = (int)(lf_partial_bytes() / ((size_t)nwin * c->d * 4));
+// same address as when the lists were built: check that the contents are the same (else grad_x becomes NaN and usl_check
+// reports it)
+template <int KT>
+static usl_status lf_ready(usl_ctx* c, const int32_t* idx, int set, const Cut& cut) {
+    if (c->lf[set].built_for != idx) return lf_build_t<KT>(c, idx, set, cut);
+    return usl_idx_fingerprint(c, idx, 0);
+}
+
+// Instances per pass over the batch: every pass loads the lists and the weights anew, and its partial sums are nwin * G * d
+// floats; as many as the allowance for partial sums admits, sized once for max_b, a multiple of `step`.
+static int pass_rows(const usl_ctx* c, const Cut& cut, int step) {
+    int G = (int)(lf_partial_bytes() / ((size_t)cut.nwin * padded_d(c) * 4) > (size_t)c->max_b
+                      ? (size_t)c->max_b : lf_partial_bytes() / ((size_t)cut.nwin * padded_d(c) * 4));
     if (const char* e = getenv("USL_TUNE_BWI_ROWS")) G = atoi(e) < G ? atoi(e) : G;   // tests: several passes on a small layer
     G = G < 64 ? 64 : G;
     G = G > c->max_b ? c->max_b : G;
-    if (BOTH && G > 1) G &= ~1;   // two instances per pass of the loop: an even number, so that only the last pass over the batch has an odd one left
-    USL_TRY(usl_reserve(c, (void**)&L.partial, &L.partial_cap, (size_t)nwin * G * c->d * 4));
-    const size_t lds = BOTH ? LDS2_BYTES : LDS_BYTES, N = (size_t)c->m * c->k;
-    const unsigned grid = (unsigned)(((nwin + 7) / 8) * 8 * nfb);
-    static bool checked[2] = {false, false};
-    for (int i0 = 0; i0 < b; i0 += G) {
-        const int rows = b - i0 < G ? b - i0 : G;
-#define USL_LDS_FORM(TS, WHICH, KERNEL, ...)                                                                             \
-        do {                                                                                                             \
-            if (!checked[WHICH]) {                                                                                       \
-                hipFuncAttributes fa;                                                                                    \
-                USL_HIP(c, hipFuncGetAttributes(&fa, reinterpret_cast<const void*>(KERNEL<TS>)));                        \
-                if (fa.sharedSizeBytes != 0)                                                                             \
-                    USL_FAIL(c, USL_EUNSUPPORTED, "backward_input (LDS form): the kernel has static LDS, its row buffer " \
-                                                  "does not start at LDS address 0");                                    \
-                USL_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(KERNEL<TS>),                                \
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));                   \
-                checked[WHICH] = true;                                                                                   \
-            }                                                                                                            \
-            hipLaunchKernelGGL(KERNEL<TS>, dim3(grid), dim3(NT), lds, c->stream, g + (size_t)i0 * c->m, (const TS*)W,    \
-                               __VA_ARGS__);                                                                             \
-        } while (0)
-        if (BOTH) {
-            if (c->storage == USL_F32)
-                USL_LDS_FORM(float, 0, k_both_lds, (const float*)x + (size_t)i0 * c->d, c->m, c->k, rows, c->d, wl, nfb, nwin, L.lab,
-                             L.slot, L.feat, L.caps, L.ov_base, reinterpret_cast<const OvEntry*>(L.ov), L.ovr, L.partial, L.pos + N,
-                             L.pos + N + (size_t)nwin * nfb * KT * NT, L.ov_base + 2 * ((size_t)nwin * nfb) + 1, L.stage,
-                             L.stage + N, gate, i0 > 0 ? 1 : 0);
-            else
-                USL_LDS_FORM(uint16_t, 1, k_both_lds, (const uint16_t*)x + (size_t)i0 * c->d, c->m, c->k, rows, c->d, wl, nfb, nwin,
-                             L.lab, L.slot, L.feat, L.caps, L.ov_base, reinterpret_cast<const OvEntry*>(L.ov), L.ovr, L.partial,
-                             L.pos + N, L.pos + N + (size_t)nwin * nfb * KT * NT, L.ov_base + 2 * ((size_t)nwin * nfb) + 1,
-                             L.stage, L.stage + N, gate, i0 > 0 ? 1 : 0);
-        } else {
-            if (c->storage == USL_F32)
-                USL_LDS_FORM(float, 0, k_bwi_lds, c->m, c->k, rows, c->d, wl, nfb, nwin, L.lab, L.slot, L.feat, L.caps, L.ov_base,
-                             reinterpret_cast<const OvEntry*>(L.ov), L.ovr, L.partial, gate);
-            else
-                USL_LDS_FORM(uint16_t, 1, k_bwi_lds, c->m, c->k, rows, c->d, wl, nfb, nwin, L.lab, L.slot, L.feat, L.caps, L.ov_base,
-                             reinterpret_cast<const OvEntry*>(L.ov), L.ovr, L.partial, gate);
-        }
-#undef USL_LDS_FORM
-        const size_t n4 = (size_t)rows * c->d / 4;
-        hipLaunchKernelGGL(k_lf_reduce<BOTH>, dim3(c->num_cu * 8), dim3(256), 0, c->stream,
-                           reinterpret_cast<const float4*>(L.partial), nwin, n4,
-                           reinterpret_cast<float4*>(grad_x + (size_t)i0 * c->d), gate, stale);
-    }
-    return usl_check_launch(c, BOTH ? "backward products (LDS form)" : "backward_input (LDS form)");
+    // several passes over the batch: only the last has a pass of the loop that is not full
+    return G < c->max_b && G > step ? G / step * step : G;
+}
+
+static void lf_reduce(usl_ctx* c, const float* partial, const Cut& cut, int rows, bool both, float* grad_x, const uint32_t* gate) {
+    const int dp = padded_d(c);
+    const size_t n4 = (size_t)rows * dp / 4;
+    const bool vec = dp == c->d && (uintptr_t)grad_x % 16 == 0;
+    const uint32_t* stale = reinterpret_cast<const uint32_t*>(c->idx_print) + 4;
+    size_t blocks = (n4 + 255) / 256;
+    if (blocks > (size_t)c->num_cu * 8) blocks = (size_t)c->num_cu * 8;
+    if (both)
+        hipLaunchKernelGGL(k_lf_reduce<true>, dim3((unsigned)blocks), dim3(256), 0, c->stream,
+                           reinterpret_cast<const float4*>(partial), cut.nwin, n4, c->d, dp, vec, grad_x, gate, stale);
+    else
+        hipLaunchKernelGGL(k_lf_reduce<false>, dim3((unsigned)blocks), dim3(256), 0, c->stream,
+                           reinterpret_cast<const float4*>(partial), cut.nwin, n4, c->d, dp, vec, grad_x, gate, stale);
+}
+
+// The one-product form needs its row buffer at LDS address 0 (a label's byte offset is the address); all need the LDS.
+template <typename KERNEL>
+static usl_status lf_kernel_ready(usl_ctx* c, KERNEL kern, size_t lds) {
+    hipFuncAttributes fa;
+    USL_HIP(c, hipFuncGetAttributes(&fa, reinterpret_cast<const void*>(kern)));
+    if (fa.sharedSizeBytes != 0)
+        USL_FAIL(c, USL_EUNSUPPORTED, "backward_input (LDS form): the kernel has static LDS, its row buffer does not start at LDS address 0");
+    USL_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    return USL_OK;
 }
 
 // grad_x[b][d] from g[b][m] (row-major).  gate as for the other dense kernels.
 usl_status usl_bwi_lds_run(usl_ctx* c, const float* g, const int32_t* idx, const void* W, float* grad_x, int32_t b,
                            const uint32_t* gate) {
-    return lf_run_t<KT_BWI, false>(c, 0, g, nullptr, idx, W, grad_x, b, gate);
+    auto& L = c->lf[0];
+    const Cut cut = bwi_cut(c);
+    USL_TRY(lf_ready<KT_BWI>(c, idx, 0, cut));
+    const int G = pass_rows(c, cut, 1);
+    USL_TRY(usl_reserve(c, (void**)&L.partial, &L.partial_cap, (size_t)cut.nwin * G * padded_d(c) * 4));
+    const unsigned grid = (unsigned)(((cut.nwin + 7) / 8) * 8 * cut.nfb);
+    static bool checked[2] = {false, false};
+    for (int i0 = 0; i0 < b; i0 += G) {
+        const int rows = b - i0 < G ? b - i0 : G;
+#define USL_BWI(TS, WHICH)                                                                                                \
+        do {                                                                                                              \
+            if (!checked[WHICH]) USL_TRY(lf_kernel_ready(c, k_bwi_lds<TS>, LDS_BYTES));                                   \
+            checked[WHICH] = true;                                                                                        \
+            hipLaunchKernelGGL(k_bwi_lds<TS>, dim3(grid), dim3(NT), LDS_BYTES, c->stream, g + (size_t)i0 * c->m, (const TS*)W, \
+                               c->m, c->k, rows, c->d, cut.wl, cut.nfb, cut.nwin, L.lab, L.slot, L.feat, L.caps, L.ov_base, \
+                               reinterpret_cast<const OvEntry*>(L.ov), L.ovr, L.partial, gate);                           \
+        } while (0)
+        if (c->storage == USL_F32) USL_BWI(float, 0);
+        else USL_BWI(uint16_t, 1);
+#undef USL_BWI
+        lf_reduce(c, L.partial, cut, rows, false, grad_x + (size_t)i0 * c->d, gate);
+    }
+    return usl_check_launch(c, "backward_input (LDS form)");
+}
+
+// Parts of the batch in k_both_lds: more than one where the (window, feature block) workgroups leave compute
+// units idle.  A workgroup loads its lists and weights and hands out its sums in about 20 us, a pass of its loop takes
+// about 4.4 (m = 31k, d = 1k, k = 32, b = 128: 187 us with 1 part, 117 with 2, 83 with 4, 75 with 6, 100 with 8, which are
+// two rounds); every part writes a weight gradient of its own, which the reader adds up.
+static int both_parts(const usl_ctx* c, const Cut& cut, int rows, int Q) {
+    const int64_t wgs = (int64_t)cut.nwin * cut.nfb, passes = (rows + Q - 1) / Q, cu = c->num_cu;
+    if (const char* e = getenv("USL_TUNE_BOTH_PARTS")) return atoi(e) > 0 ? (atoi(e) < passes ? atoi(e) : (int)passes) : 1;
+    int best = 1;
+    double best_t = 0.0;
+    for (int P = 1; P <= 32 && P <= passes; ++P) {
+        if ((size_t)P * c->m * c->k * 4 > ((size_t)1 << 28) && P > 1) break;
+        const double rounds = (double)((wgs * P + cu - 1) / cu);
+        const double t = rounds * (20.0 + 4.4 * (double)((passes + P - 1) / P)) + (double)P * c->m * c->k * 8 / 4e6;
+        if (P == 1 || t < best_t) { best = P; best_t = t; }
+    }
+    return best;
 }
 
 // grad_x[b][d] and the weight gradient from g[b][m] and x[b][d].  The weight gradient is left in the order of the lists:
-// slot f's is (*stage)[(*pos)[f]] (usl_launch_adam_staged takes it from there); both arrays belong to the context and
-// hold until the next call or a change of idx.  A stale idx (see usl_check) poisons grad_x here; *stale is the device
-// word that says so, for whoever picks up the weight gradient.
+// slot f's is the sum over p < *parts of (*stage)[p * *part_stride + (*pos)[f]] (usl_launch_adam_staged takes it from
+// there); both arrays belong to the context and hold until the next call or a change of idx.  A stale idx (see usl_check)
+// poisons grad_x here; *stale is the device word that says so, for whoever picks up the weight gradient.
 usl_status usl_both_lds_run(usl_ctx* c, const float* g, const void* x, const int32_t* idx, const void* W, float* grad_x,
-                            int32_t b, const uint32_t* gate, const float** stage, const uint32_t** pos, const uint32_t** stale) {
-    USL_TRY((lf_run_t<KT_BOTH, true>(c, 1, g, x, idx, W, grad_x, b, gate)));
-    *stage = c->lf[1].stage;
-    *pos = c->lf[1].pos;
-    *stale = reinterpret_cast<const uint32_t*>(c->idx_print) + 4;
-    return USL_OK;
+                            int32_t b, const uint32_t* gate, usl_staged* out) {
+    auto& L = c->lf[1];
+    const Cut cut = both_cut(c);
+    const int Q = both_q(c), dp = padded_d(c);
+    const size_t N = (size_t)c->m * c->k, nbins = (size_t)cut.nwin * cut.vd, rkn = (size_t)cut.nwin * cut.nfb * (Q == 4 ? KT_BOTH4 : KT_BOTH) * NT;
+    if (Q == 4) USL_TRY(lf_ready<KT_BOTH4>(c, idx, 1, cut));
+    else USL_TRY(lf_ready<KT_BOTH>(c, idx, 1, cut));
+    const int G = pass_rows(c, cut, Q);
+    const int parts = b <= G ? both_parts(c, cut, b, Q) : 1;
+    const int most = c->max_b <= G ? both_parts(c, cut, c->max_b, Q) : 1;   // scratch for the largest batch too
+    USL_TRY(usl_reserve(c, (void**)&L.partial, &L.partial_cap, (size_t)cut.nwin * G * dp * 4));
+    // per part: stage [N], the sums of the overflow entries beyond LDS [N + nbins]
+    const size_t keep = (size_t)(parts > most ? parts : most);
+    USL_TRY(usl_reserve(c, (void**)&L.stage, &L.stage_cap, keep * (N + N + nbins) * 4));
+    float* ovgw = L.stage + keep * N;
+    const void* xs = nullptr;
+    size_t x_stride = 0;
+    USL_TRY(usl_activation_rows(c, x, b, Q == 4 ? 4 : 1, &xs, &x_stride));
+    static bool checked[4] = {false, false, false, false};
+    for (int i0 = 0; i0 < b; i0 += G) {
+        const int rows = b - i0 < G ? b - i0 : G;
+        const int per_part = ((rows + parts - 1) / parts + Q - 1) / Q * Q;
+        // whole windows to an XCD where that leaves no XCD more rounds (of 32 compute units) than even shares
+        const int64_t even = ((int64_t)cut.nwin * parts * cut.nfb + 7) / 8, whole = ((int64_t)cut.nwin * parts + 7) / 8 * cut.nfb;
+        const dim3 grid((unsigned)(8 * ((whole + 31) / 32 == (even + 31) / 32 ? whole : even)));
+#define USL_BOTH(TS, QQ, WHICH)                                                                                             \
+        do {                                                                                                                \
+            if (!checked[WHICH]) USL_TRY(lf_kernel_ready(c, k_both_lds<TS, QQ>, both_lds_bytes<QQ>()));                      \
+            checked[WHICH] = true;                                                                                          \
+            hipLaunchKernelGGL((k_both_lds<TS, QQ>), grid, dim3(NT), both_lds_bytes<QQ>(), c->stream, g + (size_t)i0 * c->m, \
+                               (const TS*)W, (const TS*)xs + (size_t)(QQ == 4 ? i0 / 4 : i0) * x_stride, x_stride, c->m, c->k, rows, c->d, \
+                               dp, cut, L.lab, L.slot, L.feat, L.caps, L.ov_base, reinterpret_cast<const OvEntry*>(L.ov), L.ovr, \
+                               L.partial, L.pos + N, L.pos + N + rkn, L.ov_base + 2 * ((size_t)cut.nwin * cut.nfb) + 1, L.stage, \
+                               ovgw, parts, per_part, N, N + nbins, gate, i0 > 0 ? 1 : 0);                                         \
+        } while (0)
+        if (c->storage == USL_F32) { if (Q == 4) USL_BOTH(float, 4, 0); else USL_BOTH(float, 2, 1); }
+        else { if (Q == 4) USL_BOTH(uint16_t, 4, 2); else USL_BOTH(uint16_t, 2, 3); }
+#undef USL_BOTH
+        lf_reduce(c, L.partial, cut, rows, true, grad_x + (size_t)i0 * c->d, gate);
+    }
+    out->stage = L.stage;
+    out->pos = L.pos;
+    out->stale = reinterpret_cast<const uint32_t*>(c->idx_print) + 4;
+    out->parts = parts;
+    out->part_stride = N;
+    return usl_check_launch(c, "backward products (LDS form)");
 }

@@ -269,20 +269,41 @@ k_adam(TS* __restrict__ W, const float* __restrict__ gW, float* __restrict__ m1,
     }
 }
 
+// The weight gradient of slots f .. f+3 out of the order of the lists: the parts' values at the slots' places, added in
+// a fixed order.
+__device__ __forceinline__ float4 staged4(const float* __restrict__ stage, uint4 p4, int parts, size_t part_stride) {
+    float4 g4 = make_float4(stage[p4.x], stage[p4.y], stage[p4.z], stage[p4.w]);
+    for (int p = 1; p < parts; ++p) {
+        stage += part_stride;
+        g4.x += stage[p4.x]; g4.y += stage[p4.y]; g4.z += stage[p4.z]; g4.w += stage[p4.w];
+    }
+    return g4;
+}
+__device__ __forceinline__ float staged1(const float* __restrict__ stage, uint32_t p, int parts, size_t part_stride) {
+    float s = stage[p];
+    for (int q = 1; q < parts; ++q) s += stage[(size_t)q * part_stride + p];
+    return s;
+}
+
 // grad_W[f] = stage[pos[f]]: the weight gradient of k_both_lds brought into the order of the slots (for callers of
 // usl_backward; usl_train_step lets Adam do it in passing).  Blocks and XCDs as in k_adam_staged.
 __global__ void __launch_bounds__(256)
-k_unstage(const float* __restrict__ stage, const uint32_t* __restrict__ pos, const uint32_t* __restrict__ gate,
-          const uint32_t* __restrict__ stale, float* __restrict__ gW, size_t n4) {
+k_unstage(const float* __restrict__ stage, const uint32_t* __restrict__ pos, int parts, size_t part_stride, const uint32_t* __restrict__ gate,
+          const uint32_t* __restrict__ stale, float* __restrict__ gW, size_t n) {
     if (gate && *gate == 0) return;
     const bool poison = *stale != 0;   // the lists were built from other contents of idx: no number is better than a wrong one
+    const float nan = __uint_as_float(0x7FC00000u);
+    const size_t n4 = n / 4;
     const size_t per_xcd = (n4 + 7) / 8, first = (size_t)(blockIdx.x & 7) * per_xcd;
     const size_t last = first + per_xcd < n4 ? first + per_xcd : n4;
     const size_t stride = (size_t)(gridDim.x / 8) * 256;
     for (size_t v = first + (size_t)(blockIdx.x >> 3) * 256 + threadIdx.x; v < last; v += stride) {
         const uint4 p4 = reinterpret_cast<const uint4*>(pos)[v];
-        const float nan = __uint_as_float(0x7FC00000u);
-        reinterpret_cast<float4*>(gW)[v] = poison ? make_float4(nan, nan, nan, nan) : make_float4(stage[p4.x], stage[p4.y], stage[p4.z], stage[p4.w]);
+        reinterpret_cast<float4*>(gW)[v] = poison ? make_float4(nan, nan, nan, nan) : staged4(stage, p4, parts, part_stride);
+    }
+    if (blockIdx.x == 0 && threadIdx.x < (n & 3)) {   // the ragged end
+        const size_t f = n4 * 4 + threadIdx.x;
+        gW[f] = poison ? nan : staged1(stage, pos[f], parts, part_stride);
     }
 }
 
@@ -296,28 +317,40 @@ k_unstage(const float* __restrict__ stage, const uint32_t* __restrict__ pos, con
 // m1, m2 stay as they are -- a step from a wrong gradient could not be taken back.
 template <typename TS>
 __global__ void __launch_bounds__(256)
-k_adam_staged(TS* __restrict__ W, const float* __restrict__ stage, const uint32_t* __restrict__ pos,
+k_adam_staged(TS* __restrict__ W, const float* __restrict__ stage, const uint32_t* __restrict__ pos, int parts, size_t part_stride,
               const uint32_t* __restrict__ gate, const uint32_t* __restrict__ stale, float* __restrict__ gW,
-              float* __restrict__ m1, float* __restrict__ m2, size_t n4, float lr, float b1, float b2, float eps, float ic1,
+              float* __restrict__ m1, float* __restrict__ m2, size_t n, float lr, float b1, float b2, float eps, float ic1,
               float ic2) {
     const bool listed = gate && *gate == 0;
     const bool poison = !listed && *stale != 0;
+    const float nan = __uint_as_float(0x7FC00000u);
+    const size_t n4 = n / 4;
     const size_t per_xcd = (n4 + 7) / 8, first = (size_t)(blockIdx.x & 7) * per_xcd;
     const size_t last = first + per_xcd < n4 ? first + per_xcd : n4;
     const size_t stride = (size_t)(gridDim.x / 8) * 256;
+    if (blockIdx.x == 0 && threadIdx.x < (n & 3)) {   // the ragged end
+        const size_t f = n4 * 4 + threadIdx.x;
+        if (poison) {
+            gW[f] = nan;
+        } else {
+            const float gv = listed ? gW[f] : staged1(stage, pos[f], parts, part_stride);
+            float a = m1[f], v = m2[f];
+            const float w = adam_one(WIo<TS>::get(W, f), gv, a, v, lr, b1, b2, eps, ic1, ic2);
+            gW[f] = gv; m1[f] = a; m2[f] = v;
+            WIo<TS>::put(W, f, w);
+        }
+    }
     for (size_t v = first + (size_t)(blockIdx.x >> 3) * 256 + threadIdx.x; v < last; v += stride) {
         const size_t f = v * 4;
         float4 g4;
         if (listed) {
             g4 = *reinterpret_cast<const float4*>(gW + f);
         } else {
-            const uint4 p4 = *reinterpret_cast<const uint4*>(pos + f);
             if (poison) {
-                const float nan = __uint_as_float(0x7FC00000u);
                 *reinterpret_cast<float4*>(gW + f) = make_float4(nan, nan, nan, nan);
                 continue;
             }
-            g4 = make_float4(stage[p4.x], stage[p4.y], stage[p4.z], stage[p4.w]);
+            g4 = staged4(stage, *reinterpret_cast<const uint4*>(pos + f), parts, part_stride);
             *reinterpret_cast<float4*>(gW + f) = g4;
         }
         float4 a4 = *reinterpret_cast<const float4*>(m1 + f);
@@ -460,31 +493,34 @@ usl_status usl_launch_adam(usl_ctx* c, void* W, const float* grad_W, float* m1, 
     return usl_check_launch(c, "adam");
 }
 
-usl_status usl_launch_unstage(usl_ctx* c, const float* stage, const uint32_t* pos, const uint32_t* gate, const uint32_t* stale,
-                              float* grad_W) {
+// blocks of the two kernels that pick up a staged gradient: a multiple of 8 (one eighth of them per XCD)
+static unsigned staged_blocks(const usl_ctx* c, size_t n) {
+    const size_t most = (size_t)(c->num_cu > 0 ? c->num_cu : 8) * 16, want = (n / 4 + 255) / 256;
+    return (unsigned)(((want < most ? want : most) + 7) / 8 * 8 + (want == 0 ? 8 : 0));
+}
+
+usl_status usl_launch_unstage(usl_ctx* c, const usl_staged& st, const uint32_t* gate, float* grad_W) {
     const size_t n = (size_t)c->m * c->k;
-    if ((uintptr_t)grad_W % 16 || n % 4) USL_FAIL(c, USL_EINVAL, "grad_W must be 16-byte aligned, m * k a multiple of 4");
-    const unsigned blocks = (unsigned)(c->num_cu > 0 ? c->num_cu : 8) * 16 / 8 * 8;
-    hipLaunchKernelGGL(k_unstage, dim3(blocks), dim3(256), 0, c->stream, stage, pos, gate, stale, grad_W, n / 4);
+    if ((uintptr_t)grad_W % 16) USL_FAIL(c, USL_EINVAL, "grad_W must be 16-byte aligned");
+    hipLaunchKernelGGL(k_unstage, dim3(staged_blocks(c, n)), dim3(256), 0, c->stream, st.stage, st.pos, st.parts, st.part_stride, gate,
+                       st.stale, grad_W, n);
     return usl_check_launch(c, "weight gradient into slot order");
 }
 
-// Adam from a weight gradient in list order (see k_adam_staged); m * k must be a multiple of 4 (the list form's
-// shapes are).  grad_W is written (or, behind a zero gate, read).
-usl_status usl_launch_adam_staged(usl_ctx* c, void* W, const float* stage, const uint32_t* pos, const uint32_t* gate,
-                                  const uint32_t* stale, float* grad_W, float* m1, float* m2, float lr, float beta1, float beta2, float eps,
-                                  float inv_c1, float inv_c2) {
+// Adam from a weight gradient in list order (see k_adam_staged).  grad_W is written (or, behind a zero gate, read).
+usl_status usl_launch_adam_staged(usl_ctx* c, void* W, const usl_staged& st, const uint32_t* gate, float* grad_W, float* m1, float* m2,
+                                  float lr, float beta1, float beta2, float eps, float inv_c1, float inv_c2) {
     const size_t n = (size_t)c->m * c->k;
     const bool aligned = ((uintptr_t)W % 16 == 0) && ((uintptr_t)grad_W % 16 == 0) &&
                          ((uintptr_t)m1 % 16 == 0) && ((uintptr_t)m2 % 16 == 0);
-    if (!aligned || n % 4) USL_FAIL(c, USL_EINVAL, "W, grad_W, m1, m2 must be 16-byte aligned, m * k a multiple of 4");
-    const unsigned blocks = (unsigned)(c->num_cu > 0 ? c->num_cu : 8) * 16 / 8 * 8;
+    if (!aligned) USL_FAIL(c, USL_EINVAL, "W, grad_W, m1, m2 must be 16-byte aligned");
+    const unsigned blocks = staged_blocks(c, n);
     if (c->storage == USL_F32)
-        hipLaunchKernelGGL(k_adam_staged<float>, dim3(blocks), dim3(256), 0, c->stream, (float*)W, stage, pos, gate,
-                           stale, grad_W, m1, m2, n / 4, lr, beta1, beta2, eps, inv_c1, inv_c2);
+        hipLaunchKernelGGL(k_adam_staged<float>, dim3(blocks), dim3(256), 0, c->stream, (float*)W, st.stage, st.pos, st.parts, st.part_stride,
+                           gate, st.stale, grad_W, m1, m2, n, lr, beta1, beta2, eps, inv_c1, inv_c2);
     else
-        hipLaunchKernelGGL(k_adam_staged<uint16_t>, dim3(blocks), dim3(256), 0, c->stream, (uint16_t*)W, stage, pos, gate,
-                           stale, grad_W, m1, m2, n / 4, lr, beta1, beta2, eps, inv_c1, inv_c2);
+        hipLaunchKernelGGL(k_adam_staged<uint16_t>, dim3(blocks), dim3(256), 0, c->stream, (uint16_t*)W, st.stage, st.pos, st.parts,
+                           st.part_stride, gate, st.stale, grad_W, m1, m2, n, lr, beta1, beta2, eps, inv_c1, inv_c2);
     return usl_check_launch(c, "adam (staged gradient)");
 }
 

@@ -461,24 +461,30 @@ usl_status launch(usl_ctx* c, const Launch& p, void** args, const char* what) {
     return usl_check_launch(c, what);
 }
 
+usl_status interleave(usl_ctx* c, const void* x, int b, int Q, int row_bytes, void** to, size_t* cap) {
+    const int es = c->storage == USL_F32 ? 4 : 2, groups = (b + Q - 1) / Q, cols = row_bytes / (Q * es);
+    const int qmax = 4;   // sized once, for the largest batch any later call can bring
+    const size_t need = (size_t)((c->max_b + qmax - 1) / qmax) * qmax * ((size_t)c->d + 16) * es;
+    USL_TRY(usl_reserve(c, to, cap, max_sz(need, (size_t)groups * row_bytes)));
+    const dim3 grid((unsigned)((cols + 255) / 256), (unsigned)groups);
+#define USL_IL(TS, QQ) hipLaunchKernelGGL((k_interleave<TS, QQ>), grid, dim3(256), 0, c->stream, (const TS*)x, (TS*)*to, b, c->d, cols)
+    if (es == 4) { if (Q == 4) USL_IL(float, 4); else if (Q == 2) USL_IL(float, 2); else USL_IL(float, 1); }
+    else { if (Q == 4) USL_IL(uint16_t, 4); else if (Q == 2) USL_IL(uint16_t, 2); else USL_IL(uint16_t, 1); }
+#undef USL_IL
+    return usl_check_launch(c, "activations");
+}
+
 // The interleaved activations of this call, in scratch of the context (or x itself, if it is laid out that way).
-// Inside usl_train_step the copy that forward made serves the weight gradient too.
+// Inside usl_train_step the copy that forward made serves the backward products too.
 usl_status activations(usl_ctx* c, const Layout& L, const void* x, int b, const void** xi) {
     *xi = x;
     if (!L.copy) return USL_OK;
-    const int es = c->storage == USL_F32 ? 4 : 2, groups = (b + L.Q - 1) / L.Q, cols = L.row_bytes / (L.Q * es);
-    if (c->xi_of == x) { *xi = c->xi; return USL_OK; }
-    const int qmax = 4;   // sized once, for the largest batch any later call can bring
-    const size_t need = (size_t)((c->max_b + qmax - 1) / qmax) * qmax * ((size_t)c->d + 16) * es;
-    USL_TRY(usl_reserve(c, &c->xi, &c->xi_cap, max_sz(need, (size_t)groups * L.row_bytes)));
-    const dim3 grid((unsigned)((cols + 255) / 256), (unsigned)groups);
-#define USL_IL(TS, Q) hipLaunchKernelGGL((k_interleave<TS, Q>), grid, dim3(256), 0, c->stream, (const TS*)x, (TS*)c->xi, b, c->d, cols)
-    if (es == 4) { if (L.Q == 4) USL_IL(float, 4); else if (L.Q == 2) USL_IL(float, 2); else USL_IL(float, 1); }
-    else { if (L.Q == 4) USL_IL(uint16_t, 4); else if (L.Q == 2) USL_IL(uint16_t, 2); else USL_IL(uint16_t, 1); }
-#undef USL_IL
+    if (c->xi_of != x || c->xi_q != L.Q || c->xi_row_bytes != L.row_bytes) USL_TRY(interleave(c, x, b, L.Q, L.row_bytes, &c->xi, &c->xi_cap));
     *xi = c->xi;
-    if (c->xi_keep) c->xi_of = x;
-    return usl_check_launch(c, "activations");
+    c->xi_of = c->xi_keep ? x : nullptr;
+    c->xi_q = L.Q;
+    c->xi_row_bytes = L.row_bytes;
+    return USL_OK;
 }
 
 // The register-resident kernels need k <= 64, columns that fit 16 bits, and 16-byte aligned idx / W / grad_W.
@@ -561,6 +567,25 @@ usl_status usl_launch_forward(usl_ctx* c, const void* x, const int32_t* idx, con
     Geom tg = p.geom;
     void* args[] = {&xi, &idx, &W, &out, &m, &k, &bb, &tg, &perm};
     return launch(c, p, args, "forward");
+}
+
+usl_status usl_activation_rows(usl_ctx* c, const void* x, int32_t b, int Q, const void** rows, size_t* stride) {
+    const int es = c->storage == USL_F32 ? 4 : 2;
+    if (Q == 1 && (size_t)c->d * es % 16 == 0 && (uintptr_t)x % 16 == 0) {
+        *rows = x;
+        *stride = (size_t)c->d;
+        return USL_OK;
+    }
+    if (c->xi_of == x && c->xi_q == Q) {   // usl_train_step: the copy that forward made
+        *rows = c->xi;
+        *stride = (size_t)c->xi_row_bytes / es;
+        return USL_OK;
+    }
+    const int per = 16 / (Q * es), cols = (c->d + per - 1) / per * per;
+    USL_TRY(interleave(c, x, b, Q, cols * Q * es, &c->xr, &c->xr_cap));
+    *rows = c->xr;
+    *stride = (size_t)cols * Q;
+    return USL_OK;
 }
 
 usl_status usl_launch_backward_weight(usl_ctx* c, const float* g, const void* x, const int32_t* idx, float* grad_W, int32_t b, bool dense) {

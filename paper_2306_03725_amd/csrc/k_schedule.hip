@@ -27,18 +27,6 @@ namespace {
 
 constexpr int SCHED_NT = 256;
 
-// The lanes whose reads meet in one pass of the LDS: 32 consecutive lanes (ds_read_b32, ds_read_b64), or, for
-// ds_read_b128, 16 lanes of a half-wavefront: 0-3, 12-15, 20-27 and the other 16 (measured: two lanes with different
-// rows of one bank cost a pass exactly when both are in one of these sets).  Position p of a group -> lane of the
-// half-wavefront.
-template <int GS>
-__device__ __forceinline__ int lane_of_position(int p32) {
-    if (GS == 32) return p32;
-    const int p = p32 & 15;
-    if (p32 < 16) return p < 4 ? p : p < 8 ? p + 8 : p + 12;      // 0-3, 12-15, 20-27
-    return p < 8 ? p + 4 : p < 12 ? p + 8 : p + 16;               // 4-11, 16-19, 28-31
-}
-
 // K = padded fan-in, GS = labels and banks of a group (32, or 16 where a read is 16 bytes wide); k real slots.
 template <int K, int GS>
 __global__ void __launch_bounds__(SCHED_NT)
@@ -54,7 +42,7 @@ k_schedule(const int32_t* __restrict__ idx, int64_t m, int k, int shift, int rou
     __shared__ int win[G][GS];
     const int gl = threadIdx.x / GS, lane = threadIdx.x & (GS - 1);
     const int hs = threadIdx.x & 63 & ~(GS - 1);        // where my group's bits sit in a wavefront ballot
-    const int64_t j = (int64_t)blockIdx.x * SCHED_NT + (threadIdx.x & ~31) + lane_of_position<GS>(threadIdx.x & 31);
+    const int64_t j = (int64_t)blockIdx.x * SCHED_NT + (threadIdx.x & ~31) + usl_lane_of_position<GS>(threadIdx.x & 31);
     const bool valid = j < m;
     deg0[gl][lane] = 0;
     for (int b = 0; b < GS; ++b) left_in[gl][lane][b] = 0;

@@ -33,7 +33,7 @@ extern "C" usl_status usl_destroy(usl_ctx* c) {
         void* bufs[] = {c->bce_partials, c->sel_hist, c->prune_flags, c->tie_counts, c->counter64,
                         c->csc_ptr, c->csc_cursor, c->csc_order, c->csc_slot, c->csc_w, c->gT, c->gxT, c->nz_flags,
                         c->slot_order, c->topk_cand, c->sub_idx, c->sub_W, c->predict_out, c->gw_part,
-                        c->nz_state, c->nz_lab, c->nz_val, c->idx_print, c->xi};
+                        c->nz_state, c->nz_lab, c->nz_val, c->idx_print, c->xi, c->xr};
         (void)hipStreamSynchronize(c->stream);
         for (void* p : bufs)
             if (p) (void)hipFree(p);
@@ -286,20 +286,19 @@ static usl_status subset_context(usl_ctx* c, int64_t n, const int32_t* idx, cons
 // usl_train_step); the kernels over the lists and the dense ones stand on either side of the gate.
 static usl_status backward_both(usl_ctx* c, const float* g, const void* x, const int32_t* idx, const void* W, float* grad_W,
                                 float* grad_x, int32_t b, bool lists, bool dense, const uint32_t** gate_out,
-                                const float** stage, const uint32_t** pos, const uint32_t** stale) {
+                                usl_staged* staged) {
     const uint32_t* gate = nullptr;
     if (lists) USL_TRY(usl_sparse_compact(c, g, b, &gate));
     c->nz_lists_of = g;
     c->nz_lists_tried = gate != nullptr;
     usl_status s = USL_OK;
-    *stage = nullptr;
-    *pos = nullptr;
-    if (usl_both_lds_applies(c) && (uintptr_t)g % 16 == 0 && (uintptr_t)grad_x % 16 == 0 && (uintptr_t)x % 16 == 0) {
+    staged->stage = nullptr;
+    if (usl_both_lds_applies(c) && (uintptr_t)grad_W % 16 == 0) {
         // both products from one pass of gathers over the rows of g (k_backward_input_lds.hip); behind the gate like
         // the two dense kernels it stands for.  The weight gradient is left in the order of the lists.
         if (gate) s = usl_sparse_backward_weight(c, x, idx, grad_W, b);
         if (gate && s == USL_OK) s = usl_sparse_backward_input(c, idx, W, grad_x, b);
-        if (s == USL_OK) s = usl_both_lds_run(c, g, x, idx, W, grad_x, b, gate, stage, pos, stale);
+        if (s == USL_OK) s = usl_both_lds_run(c, g, x, idx, W, grad_x, b, gate, staged);
     } else {
         s = usl_launch_backward_weight(c, g, x, idx, grad_W, b, dense);
         if (s == USL_OK) s = usl_launch_backward_input(c, g, idx, W, grad_x, b);
@@ -316,11 +315,9 @@ extern "C" usl_status usl_backward(usl_ctx* c, const float* g, const void* x, co
     USL_TRY(check_batch(c, b));
     USL_TRY(usl_prepare_device(c));
     const uint32_t* gate = nullptr;
-    const float* stage = nullptr;
-    const uint32_t* pos = nullptr;
-    const uint32_t* stale = nullptr;
-    USL_TRY(backward_both(c, g, x, idx, W, grad_W, grad_x, b, usl_sparse_supported(c), false, &gate, &stage, &pos, &stale));
-    if (stage) USL_TRY(usl_launch_unstage(c, stage, pos, gate, stale, grad_W));
+    usl_staged staged;
+    USL_TRY(backward_both(c, g, x, idx, W, grad_W, grad_x, b, usl_sparse_supported(c), false, &gate, &staged));
+    if (staged.stage) USL_TRY(usl_launch_unstage(c, staged, gate, grad_W));
     return USL_OK;
 }
 
@@ -412,14 +409,12 @@ extern "C" usl_status usl_train_step(usl_ctx* c, const void* x, const int32_t* i
             USL_TRY(usl_launch_loss(c, loss_kind, g, tgt_off, tgt_lab, scale, g, loss, b));
             // (the same order of calls where the input gradient reads g row-major: its register-list form)
             const uint32_t* gate = nullptr;
-            const float* stage = nullptr;
-            const uint32_t* pos = nullptr;
-            const uint32_t* stale = nullptr;
-            USL_TRY(backward_both(c, g, x, idx, W, grad_W, grad_x, b, lists, loss_kind == 0, &gate, &stage, &pos, &stale));
-            if (stage) {   // the weight gradient is in the order of the lists: Adam picks it up there and writes grad_W
+            usl_staged staged;
+            USL_TRY(backward_both(c, g, x, idx, W, grad_W, grad_x, b, lists, loss_kind == 0, &gate, &staged));
+            if (staged.stage) {   // the weight gradient is in the order of the lists: Adam picks it up there and writes grad_W
                 const double c1 = 1.0 - pow((double)beta1, (double)t);
                 const double c2 = 1.0 - pow((double)beta2, (double)t);
-                return usl_launch_adam_staged(c, W, stage, pos, gate, stale, grad_W, m1, m2, lr, beta1, beta2, eps, (float)(1.0 / c1),
+                return usl_launch_adam_staged(c, W, staged, gate, grad_W, m1, m2, lr, beta1, beta2, eps, (float)(1.0 / c1),
                                               (float)(1.0 / c2));
             }
         } else {

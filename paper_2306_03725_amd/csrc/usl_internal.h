@@ -44,6 +44,8 @@ struct usl_ctx {
     void* xi;                 size_t xi_cap;   // activations interleaved for the LDS gathers (k_products.hip)
     bool xi_keep;                  // inside usl_train_step: the copy that forward makes serves the weight gradient
     const void* xi_of;             // x that xi holds (only set inside usl_train_step), else NULL
+    int xi_q, xi_row_bytes;        // ... its instances per group and bytes per row
+    void* xr;                 size_t xr_cap;   // activations in the layout of the backward kernel, where that is another one
     float* gT;                size_t gT_cap;   // [tiles][m][32] upstream gradient, one 128-byte piece per (tile of 32 instances, label)
     uint8_t* nz_flags;        size_t nz_flags_cap;   // [tiles][m] 1 = that 32-instance piece of gT is not all zero
     // label-subset calls: a child context sized for the subset, and the subset's rows of idx / W
@@ -76,7 +78,7 @@ struct usl_ctx {
         uint32_t* ov_base;    size_t ov_base_cap;  // [wg+1] start of a workgroup's overflow entries, [wg] their number; the same two for all its entries
         uint32_t* ovr;        size_t ovr_cap;      // [wg][2][1024] a lane's lists' share of the overflow entries held in LDS
         uint16_t* lab;        size_t lab_cap;      // [wg][slots][1024] label within the window
-        uint32_t* slot;       size_t slot_cap;     // [wg][slots][1024] flat slot j*k+t (where the weight lives)
+        uint32_t* slot;       size_t slot_cap;     // flat slot j*k+t (where the weight lives): [0] [wg][slots][1024]; [1] [m*k], by place
         uint32_t* ent;        size_t ent_cap;      // [m*k] flat slots grouped by (workgroup, feature), before the bank-aware order
         uint32_t* ovoff;      size_t ovoff_cap;    // [nwin*d] where a list's overflow starts in its workgroup's
         void* ov;             size_t ov_cap;       // overflow entries
@@ -147,14 +149,24 @@ usl_status usl_bwi_lds_run(usl_ctx* ctx, const float* g, const int32_t* idx, con
 // Both backward products from one pass of gathers through register lists of half the length (k_backward_input_lds.hip):
 // grad_W[m][k] and grad_x[b][d] from g[b][m] and x[b][d]; for layers with k / d <= 1/1024, one pass over the batch.
 bool usl_both_lds_applies(const usl_ctx* ctx);
+// Where k_both_lds left the weight gradient: slot f's is the sum over p < parts of stage[p * part_stride + pos[f]].
+// stale: device word, not 0 = the lists were built from other contents of idx.
+struct usl_staged {
+    const float* stage;
+    const uint32_t* pos;
+    const uint32_t* stale;
+    int parts;
+    size_t part_stride;
+};
 usl_status usl_both_lds_run(usl_ctx* ctx, const float* g, const void* x, const int32_t* idx, const void* W, float* grad_x,
-                            int32_t b, const uint32_t* gate, const float** stage, const uint32_t** pos, const uint32_t** stale);
-// grad_W[f] = stage[pos[f]] (behind a zero gate: nothing, the kernels over the listed nonzeros wrote grad_W)
-usl_status usl_launch_unstage(usl_ctx* ctx, const float* stage, const uint32_t* pos, const uint32_t* gate, const uint32_t* stale,
-                              float* grad_W);
-usl_status usl_launch_adam_staged(usl_ctx* ctx, void* W, const float* stage, const uint32_t* pos, const uint32_t* gate,
-                                  const uint32_t* stale, float* grad_W, float* m1, float* m2, float lr, float beta1, float beta2, float eps,
-                                  float inv_c1, float inv_c2);
+                            int32_t b, const uint32_t* gate, usl_staged* out);
+// x in rows of *stride elements, 16-byte aligned: by itself (Q = 1), or interleaved by Q instances ([group][column][Q],
+// *stride elements from group to group); x itself where it is that already, else a copy in scratch.
+usl_status usl_activation_rows(usl_ctx* ctx, const void* x, int32_t b, int Q, const void** rows, size_t* stride);
+// grad_W[f] = the staged gradient of slot f (behind a zero gate: nothing, the kernels over the listed nonzeros wrote grad_W)
+usl_status usl_launch_unstage(usl_ctx* ctx, const usl_staged& st, const uint32_t* gate, float* grad_W);
+usl_status usl_launch_adam_staged(usl_ctx* ctx, void* W, const usl_staged& st, const uint32_t* gate, float* grad_W, float* m1, float* m2,
+                                  float lr, float beta1, float beta2, float eps, float inv_c1, float inv_c2);
 // Records (store = 1) the fingerprint of idx in ctx->idx_print, or compares with the recorded one (store = 0) and
 // raises the stale word (32-bit word 4 of idx_print) on a difference.
 usl_status usl_idx_fingerprint(usl_ctx* ctx, const int32_t* idx, int store);
@@ -211,3 +223,15 @@ template <> __device__ __forceinline__ float usl_load_f32<float>(const float* p,
 template <> __device__ __forceinline__ float usl_load_f32<uint16_t>(const uint16_t* p, size_t i) {
     return usl_bf16_to_f32(p[i]);
 }
+// The lanes whose reads meet in one pass of the LDS: 32 consecutive lanes (ds_read_b32, ds_read_b64), or, for
+// ds_read_b128, 16 lanes of a half-wavefront: 0-3, 12-15, 20-27 and the other 16 (measured: two lanes with different
+// rows of one bank cost a pass exactly when both are in one of these sets).  Position p of a group -> lane of the
+// half-wavefront.
+template <int GS>
+__device__ __forceinline__ int usl_lane_of_position(int p32) {
+    if (GS == 32) return p32;
+    const int p = p32 & 15;
+    if (p32 < 16) return p < 4 ? p : p < 8 ? p + 8 : p + 12;      // 0-3, 12-15, 20-27
+    return p < 8 ? p + 4 : p < 12 ? p + 8 : p + 16;               // 4-11, 16-19, 28-31
+}
+

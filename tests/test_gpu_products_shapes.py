@@ -1,0 +1,47 @@
+"""Forward and weight gradient at the edges of their kernels: the fan-ins between the unrolled ones (padded slots), the
+widths at which an interleaved row of 4, 2 or 1 instances stops fitting LDS, the batches around a group of instances
+(the streaming forward and its tail), and every launch shape by hand.  Against the oracle, element by element."""
+import pytest
+
+import workloads as wl
+from helpers import assert_close
+
+pytestmark = pytest.mark.gpu
+
+# (m, d, k, b, storage)
+SHAPES = [(3001, 300, k, 7, st) for k, st in [(1, "f32"), (2, "bf16"), (4, "f32"), (5, "f32"), (9, "bf16"), (17, "f32"), (24, "bf16"), (25, "f32"),
+                                               (47, "bf16"), (48, "f32"), (49, "f32"), (63, "bf16"), (64, "f32")]]
+SHAPES += [(5003, d, 12, b, "f32") for d, b in [(10176, 5), (10239, 4), (10240, 6), (10241, 5), (20479, 3), (20481, 3), (40703, 2), (40961, 2), (65536, 1)]]
+SHAPES += [(5003, d, 16, b, "bf16") for d, b in [(20352, 5), (20480, 4), (20481, 5), (40960, 3), (40961, 3), (65535, 2), (65536, 2)]]
+SHAPES += [(70001, 1000, 8, b, "f32") for b in (1, 2, 3, 4, 5, 8, 9)]
+
+
+def compare(orc, gu, cfg, m, d, k, b, storage):
+    from paper_2306_03725_amd import usl
+    idx, W, x, g = wl.gen_idx(cfg), wl.gen_W(cfg), wl.gen_x(cfg), wl.gen_g(cfg)
+    L = usl.Layer(m, d, k, b, storage)
+    d_idx, d_W, d_x, d_g = gu.dev(idx), gu.dev(W), gu.dev(x), gu.dev(g)
+    out, gW = gu.empty((b, m)).fill_(float("nan")), gu.empty((m, k)).fill_(float("nan"))
+    L.forward(d_x, d_idx, d_W, out, b)
+    assert_close(gu.host(out), orc.forward(x, idx, W), 1e-5, "scores")
+    L.backward_weight(d_g, d_x, d_idx, gW, b)
+    assert_close(gu.host(gW), orc.backward_weight(g, x, idx), 1e-5, "grad_W")
+    L.close()
+
+
+@pytest.mark.parametrize("m,d,k,b,storage", SHAPES)
+def test_products_at_their_edges(orc, m, d, k, b, storage):
+    import gpu_util as gu
+    print("products", m, d, k, b, storage, flush=True)
+    compare(orc, gu, wl.custom(m, d, k, b, storage=storage, positives=3, index=740 + SHAPES.index((m, d, k, b, storage))), m, d, k, b, storage)
+
+
+@pytest.mark.parametrize("split", [1, 3])
+@pytest.mark.parametrize("shape", [0, 1, 2])
+def test_products_in_every_launch_shape(orc, shape, split, monkeypatch):
+    import gpu_util as gu
+    monkeypatch.setenv("USL_TUNE_SHAPE", str(shape))
+    monkeypatch.setenv("USL_TUNE_SPLIT", str(split))
+    for q, (m, d, k, b, storage) in enumerate([(2500, 4096, 32, 13, "f32"), (2500, 15000, 20, 13, "bf16"), (2500, 40000, 64, 5, "f32")]):
+        print("products", m, d, k, b, storage, shape, split, flush=True)
+        compare(orc, gu, wl.custom(m, d, k, b, storage=storage, positives=3, index=790 + q), m, d, k, b, storage)
