@@ -35,49 +35,9 @@ __global__ void k_zero_u32(uint32_t* p, size_t n) {
     for (; i < n; i += s) p[i] = 0;
 }
 
-// Fingerprint of idx: a sum of mixed 16-byte groups at up to 4096 evenly spaced places (64 KiB read by one
-// workgroup, every load in flight at once: a few microseconds).  store = 1 records it when the column lists
-// are built; store = 0 compares on a later call and raises print[2] (as a 32-bit word) when the contents are
-// no longer those the lists were built from: a new tensor at a recycled address, a checkpoint copied in, ...
-// A single edited entry can slip through the sample; wholesale replacement cannot.
-__device__ __forceinline__ void idx_fingerprint_block(const uint32_t* __restrict__ idx, size_t n_words,
-                                                      uint64_t* __restrict__ print, int store) {   // 1024 lanes
-    __shared__ uint64_t red[16];
-    const size_t groups = n_words / 4;
-    const size_t samples = groups < 4096 ? groups : 4096;
-    const size_t stride = samples ? groups / samples : 1;   // >= 1
-    uint4 v[4];
-    size_t at[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const size_t s = (size_t)q * 1024 + threadIdx.x;
-        at[q] = s < samples ? s * stride : 0;
-        v[q] = s < samples ? reinterpret_cast<const uint4*>(idx)[at[q]] : make_uint4(0, 0, 0, 0);
-    }
-    uint64_t h = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        if ((size_t)q * 1024 + threadIdx.x >= samples) continue;
-        uint64_t a = ((uint64_t)v[q].x << 32 | v[q].y) ^ (at[q] * 0x9E3779B97F4A7C15ull);
-        uint64_t b2 = ((uint64_t)v[q].z << 32 | v[q].w) + (at[q] << 7);
-        a ^= a >> 31; a *= 0xD6E8FEB86659FD93ull; a ^= a >> 29;
-        b2 ^= b2 >> 33; b2 *= 0xC2B2AE3D27D4EB4Full; b2 ^= b2 >> 30;
-        h += a + (b2 << 1 | b2 >> 63);
-    }
-    for (size_t w = groups * 4 + threadIdx.x; w < n_words; w += 1024) h += (uint64_t)idx[w] * 0xFF51AFD7ED558CCDull;   // ragged tail
-    for (int o = 32; o > 0; o >>= 1) h += __shfl_down(h, o);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = h;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint64_t t = 0;
-        for (int q = 0; q < 16; ++q) t += red[q];
-        if (store) { print[0] = t; }
-        else if (print[0] != t) reinterpret_cast<uint32_t*>(print)[4] = 1u;
-    }
-}
 __global__ void __launch_bounds__(1024)
 k_idx_fingerprint(const uint32_t* __restrict__ idx, size_t n_words, uint64_t* __restrict__ print, int store) {
-    idx_fingerprint_block(idx, n_words, print, store);
+    usl_idx_fingerprint_block(idx, n_words, print, store);
 }
 
 // Lists are grouped by (label window, feature).  A workgroup takes one of `splits` equal shares of
@@ -247,8 +207,8 @@ k_gather_w(const TS* __restrict__ W, const uint32_t* __restrict__ slot, const ui
            int d, int nwin, float* __restrict__ wl, int bpw, const uint32_t* __restrict__ gate,
            const uint32_t* __restrict__ idx_check /* or NULL */, size_t n_words, uint64_t* __restrict__ print) {
     if (gate && *gate == 0) return;   // the sparse kernels do this call's work
-    // the first workgroup also checks that idx still holds what the lists were built from (see idx_fingerprint_block)
-    if (idx_check && blockIdx.x == 0) idx_fingerprint_block(idx_check, n_words, print, 0);
+    // the first workgroup also checks that idx still holds what the lists were built from (see usl_idx_fingerprint_block)
+    if (idx_check && blockIdx.x == 0) usl_idx_fingerprint_block(idx_check, n_words, print, 0);
     int w, local;
     if (nwin >= 8) {
         const int xcd = blockIdx.x & 7;

@@ -829,6 +829,10 @@ __device__ __forceinline__ void unit_of(const uint16_t* p, float (&v)[4]) {
 }
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // 16 bytes of a row that starts anywhere
 
+// base is the same for all lanes, byte the lane's offset: one 32-bit register, no 64-bit address per load
+template <typename T>
+__device__ __forceinline__ T at_byte(const T* base, uint32_t byte) { return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + byte); }
+
 // Q = 2: windows of up to 15 968 labels (wide layers), x as rows of x_stride elements, 16-byte aligned.
 // Q = 4: windows of up to 4 672 labels, x interleaved by fours (x_stride = elements from group to group, k_interleave).
 // grid: at least windows * parts of the batch * feature blocks, a multiple of 8.  A part of the batch (rows_per_part
@@ -841,7 +845,7 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
            const OvEntry* __restrict__ ov, const uint32_t* __restrict__ ovr, float* __restrict__ partial,
            const uint32_t* __restrict__ rk, const uint32_t* __restrict__ ovrk, const uint32_t* __restrict__ ent_base,
            float* __restrict__ stage, float* __restrict__ ovgw, int parts, int rows_per_part, size_t part_stride, size_t ov_stride,
-           const uint32_t* __restrict__ gate, int accumulate) {
+           const uint32_t* __restrict__ gate, int accumulate, const uint32_t* __restrict__ stale) {
     constexpr int KT = Q == 4 ? KT_BOTH4 : KT_BOTH;   // (with four instances 36 slots spill)
     constexpr uint32_t ZL = BothLayout<Q>::zero_label, U = 4 * Q;   // U: bytes of a unit
     extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -855,21 +859,24 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
     const int i_begin = part * rows_per_part, i_end = min(rows, i_begin + rows_per_part);
     stage += (size_t)part * part_stride;
     ovgw += (size_t)part * ov_stride;
-    const size_t wg = (size_t)w * nfb + fb;
+    if (stale && *stale != 0) {   // one window: partial is grad_x itself, and this kernel does k_lf_reduce's check
+        for (size_t v = threadIdx.x; v < (size_t)max(i_end - i_begin, 0) * dp; v += NT) partial[(size_t)i_begin * dp + v] = __uint_as_float(0x7FC00000u);
+        return;
+    }
+    const size_t wg = (size_t)__builtin_amdgcn_readfirstlane(w * nfb + fb);
     const uint32_t cw = caps[wg * (NT / 64) + (threadIdx.x >> 6)];
     const int acap = __builtin_amdgcn_readfirstlane((int)(cw & 0xFFu)), bcap = __builtin_amdgcn_readfirstlane((int)(cw >> 8));
     uint32_t pk[KT / 2];
     float wt[KT], gw[KT];
     // The weights come in the order of the places (slot_at; rk: see the end of the kernel) and are picked up from LDS: in the
     // order of the lists every value was a 128-byte line of its own (96 of 1320 us at m = 500k, d = 32k, k = 32, 25 of 210 at
-    // m = 200k, d = 8k, b = 64).  All loads of a batch are in flight together, those of slots that the wavefront does not
-    // visit included (their places hold anything).
-    constexpr int PB = KT % 12 == 0 ? 12 : 8;
+    // m = 200k, d = 8k, b = 64).  All loads are in flight together, those of slots that the wavefront does not visit included
+    // (their places hold anything): in batches, or behind branches, they would wait out a memory latency each.
     constexpr uint32_t CH = (uint32_t)((both_lds_bytes<Q>() - (size_t)NEAR2 * 4) / 4);   // places LDS holds at a time
     float* perm = reinterpret_cast<float*>(lds_raw);
     const uint32_t e0 = ent_base[wg], n_ent = ent_base[wg + 1] - e0;
 #pragma unroll
-    for (int t = 0; t < KT; ++t) wt[t] = gw[t] = 0.f;
+    for (int t = 0; t < KT; ++t) wt[t] = 0.f;
     for (uint32_t c0 = 0; c0 < n_ent; c0 += CH) {
         const uint32_t n = min(CH, n_ent - c0);
         __syncthreads();
@@ -885,33 +892,35 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
                 if (r0 + u * NT < n) perm[r0 + u * NT] = v[u];
         }
         __syncthreads();
+        uint32_t tid4 = threadIdx.x * 4u;   // taken afresh: addresses are rebuilt from it, not kept (and spilled)
+        asm volatile("" : "+v"(tid4));
+        uint32_t r[KT];
 #pragma unroll
-        for (int t0 = 0; t0 < KT; t0 += PB) {
-            uint32_t r[PB];
+        for (int t = 0; t < KT; ++t) r[t] = at_byte(rk + (wg * KT + t) * NT, tid4) - c0;   // an empty place: far beyond
 #pragma unroll
-            for (int u = 0; u < PB; ++u) r[u] = (rk + wg * KT * NT)[(uint32_t)(t0 + u) * NT + threadIdx.x] - c0;   // an empty place: far beyond
-#pragma unroll
-            for (int u = 0; u < PB; ++u) {
-                const int t = t0 + u;
-                const bool used = t / 4 * 4 < acap || t / 4 * 4 >= KT - bcap;   // the same for the whole wavefront
-                if (used && r[u] < n) wt[t] = perm[r[u]];
-            }
-            __builtin_amdgcn_sched_barrier(0);
+        for (int t = 0; t < KT; ++t) {
+            const bool used = t / 4 * 4 < acap || t / 4 * 4 >= KT - bcap;   // the same for the whole wavefront
+            if (used && r[t] < n) wt[t] = perm[r[t]];
         }
+        __builtin_amdgcn_sched_barrier(0);
     }
+    {
+        uint32_t lb[KT];
 #pragma unroll
-    for (int t0 = 0; t0 < KT; t0 += PB) {
-        uint32_t lb[PB];
+        for (int t = 0; t < KT; ++t) lb[t] = (lab + wg * KT * NT)[(uint32_t)t * NT + threadIdx.x];
 #pragma unroll
-        for (int u = 0; u < PB; ++u) lb[u] = (lab + wg * KT * NT)[(uint32_t)(t0 + u) * NT + threadIdx.x];
-#pragma unroll
-        for (int u = 0; u < PB; ++u) {
-            const int t = t0 + u;
+        for (int t = 0; t < KT; ++t) {
             const bool used = t / 4 * 4 < acap || t / 4 * 4 >= KT - bcap;
-            const uint32_t l16 = used ? lb[u] : 0u;
+            const uint32_t l16 = used ? lb[t] : 0u;
             if (t & 1) pk[t >> 1] |= l16 << 16; else pk[t >> 1] = l16;
         }
         __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int t = 0; t < KT; ++t) {   // (written here, not by the compiler at the top: there the registers are needed)
+        float zero = 0.f;
+        asm volatile("" : "+v"(zero));
+        gw[t] = zero;
     }
     __syncthreads();   // LDS is free
     const uint32_t ov0 = ov_base[wg], ov_n = ov_base[wg + 1] - ov0;
@@ -1151,17 +1160,15 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
     // holds below ov_sum (all of them, unless the connectivity is skewed).
     for (uint32_t c0 = 0; c0 < n_ent; c0 += CH) {
         __syncthreads();   // the last pass's reads of LDS, the owners' last additions to ov_sum; the copy before
+        uint32_t tid4 = threadIdx.x * 4u;   // taken afresh: addresses are rebuilt from it, not kept (and spilled)
+        asm volatile("" : "+v"(tid4));
+        uint32_t r[KT];
 #pragma unroll
-        for (int t0 = 0; t0 < KT; t0 += PB) {
-            uint32_t r[PB];
+        for (int t = 0; t < KT; ++t) r[t] = at_byte(rk + (wg * KT + t) * NT, tid4) - c0;   // an empty place: far beyond
 #pragma unroll
-            for (int u = 0; u < PB; ++u) r[u] = (rk + wg * KT * NT)[(uint32_t)(t0 + u) * NT + threadIdx.x] - c0;   // an empty place: far beyond
-#pragma unroll
-            for (int u = 0; u < PB; ++u) {
-                const int t = t0 + u;
-                const bool used = t / 4 * 4 < acap || t / 4 * 4 >= KT - bcap;
-                if (used && r[u] < CH) perm[r[u]] = gw[t];
-            }
+        for (int t = 0; t < KT; ++t) {
+            const bool used = t / 4 * 4 < acap || t / 4 * 4 >= KT - bcap;
+            if (used && r[t] < CH) perm[r[t]] = gw[t];
         }
         for (uint32_t q = threadIdx.x; q < ov_n; q += NT) {
             const uint32_t r = ovrk[(size_t)ov0 + q] - c0;
@@ -1309,9 +1316,7 @@ bool usl_both_lds_applies(const usl_ctx* c) {
         if (!strcmp(e, "on")) return true;
         if (!strcmp(e, "off")) return false;
     }
-    // (its fixed cost is some 5 us more than that of the two kernels: backward at m = 1000, d = 64, k = 8, b = 100: 32.9 us
-    // against 27.9; m = 4000, d = 768, k = 16, b = 32: 32.1 against 27.5; m = 2000, d = 8000, k = 8, b = 512: 55 against 86)
-    return c->m * (int64_t)c->k * c->max_b >= (int64_t)4 << 20;
+    return true;
 }
 
 template <int KT>
@@ -1390,7 +1395,7 @@ static usl_status lf_build_t(usl_ctx* c, const int32_t* idx, int set, const Cut&
 template <int KT>
 static usl_status lf_ready(usl_ctx* c, const int32_t* idx, int set, const Cut& cut) {
     if (c->lf[set].built_for != idx) return lf_build_t<KT>(c, idx, set, cut);
-    return usl_idx_fingerprint(c, idx, 0);
+    return set == 1 && c->print_done ? USL_OK : usl_idx_fingerprint(c, idx, 0);
 }
 
 // Instances per pass over the batch: every pass loads the lists and the weights anew, and its partial sums are nwin * G * d
@@ -1500,6 +1505,8 @@ usl_status usl_both_lds_run(usl_ctx* c, const float* g, const void* x, const int
     const void* xs = nullptr;
     size_t x_stride = 0;
     USL_TRY(usl_activation_rows(c, x, b, Q == 4 ? 4 : 1, &xs, &x_stride));
+    out->stale = reinterpret_cast<const uint32_t*>(c->idx_print) + 4;
+    const bool direct = cut.nwin == 1 && dp == c->d && (uintptr_t)grad_x % 16 == 0;   // nothing to add up
     static bool checked[4] = {false, false, false, false};
     for (int i0 = 0; i0 < b; i0 += G) {
         const int rows = b - i0 < G ? b - i0 : G;
@@ -1514,17 +1521,16 @@ usl_status usl_both_lds_run(usl_ctx* c, const float* g, const void* x, const int
             hipLaunchKernelGGL((k_both_lds<TS, QQ>), grid, dim3(NT), both_lds_bytes<QQ>(), c->stream, g + (size_t)i0 * c->m, \
                                (const TS*)W, (const TS*)xs + (size_t)(QQ == 4 ? i0 / 4 : i0) * x_stride, x_stride, c->m, c->k, rows, c->d, \
                                dp, cut, L.lab, L.slot, L.feat, L.caps, L.ov_base, reinterpret_cast<const OvEntry*>(L.ov), L.ovr, \
-                               L.partial, L.pos + N, L.pos + N + rkn, L.ov_base + 2 * ((size_t)cut.nwin * cut.nfb) + 1, L.stage, \
-                               ovgw, parts, per_part, N, N + nbins, gate, i0 > 0 ? 1 : 0);                                         \
+                               direct ? grad_x + (size_t)i0 * c->d : L.partial, L.pos + N, L.pos + N + rkn, L.ov_base + 2 * ((size_t)cut.nwin * cut.nfb) + 1, L.stage, \
+                               ovgw, parts, per_part, N, N + nbins, gate, i0 > 0 ? 1 : 0, direct ? out->stale : nullptr);                                         \
         } while (0)
         if (c->storage == USL_F32) { if (Q == 4) USL_BOTH(float, 4, 0); else USL_BOTH(float, 2, 1); }
         else { if (Q == 4) USL_BOTH(uint16_t, 4, 2); else USL_BOTH(uint16_t, 2, 3); }
 #undef USL_BOTH
-        lf_reduce(c, L.partial, cut, rows, true, grad_x + (size_t)i0 * c->d, gate);
+        if (!direct) lf_reduce(c, L.partial, cut, rows, true, grad_x + (size_t)i0 * c->d, gate);
     }
     out->stage = L.stage;
     out->pos = L.pos;
-    out->stale = reinterpret_cast<const uint32_t*>(c->idx_print) + 4;
     out->parts = parts;
     out->part_stride = N;
     return usl_check_launch(c, "backward products (LDS form)");

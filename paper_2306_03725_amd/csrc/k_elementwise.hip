@@ -10,28 +10,7 @@ constexpr int BCE_PER_THREAD = 16;  // labels per lane, as 4 groups of 4
 constexpr int BCE_CHUNK = BCE_NT * BCE_PER_THREAD;
 constexpr int BCE_MAX_HITS = 512;
 
-struct Bce1 { float g, l; };
 enum { LOSS_BCE = 0, LOSS_SQH = 1 };
-// y is 0 or 1.
-// BCE:           l = max(z,0) - z*y + log(1 + exp(-|z|));  dl/dz = sigmoid(z) - y
-// squared hinge: s = 2y-1, l = max(0, 1 - s*z)^2;          dl/dz = -2*s*max(0, 1 - s*z)  (exact zeros)
-template <int LOSS>
-__device__ __forceinline__ Bce1 bce_one(float z, float y, float scale) {
-    Bce1 o;
-    if (LOSS == LOSS_BCE) {
-        const float e = __expf(-fabsf(z));
-        const float r = __frcp_rn(1.f + e);
-        const float sig = z >= 0.f ? r : e * r;
-        o.g = scale * (sig - y);
-        o.l = fmaxf(z, 0.f) - z * y + __logf(1.f + e);
-    } else {
-        const float sgn = 2.f * y - 1.f;
-        const float margin = fmaxf(0.f, fmaf(-sgn, z, 1.f));
-        o.g = scale * (-2.f * sgn * margin);
-        o.l = margin * margin;
-    }
-    return o;
-}
 
 // grid (label chunks, b).  The positives of the instance that fall into the block's label range
 // are collected in LDS first; nearly always there are none, so the per-element test is free.
@@ -80,13 +59,13 @@ k_bce(const float* out, const int64_t* __restrict__ tgt_off, const int32_t* __re
         }
         if (VEC && j + 4 <= j1) {
             const float4 z = *reinterpret_cast<const float4*>(zrow + j);
-            const Bce1 a = bce_one<LOSS>(z.x, y[0], scale), b2 = bce_one<LOSS>(z.y, y[1], scale),
-                       c = bce_one<LOSS>(z.z, y[2], scale), dd = bce_one<LOSS>(z.w, y[3], scale);
+            const usl_loss_of a = usl_loss_one(LOSS, z.x, y[0], scale), b2 = usl_loss_one(LOSS, z.y, y[1], scale),
+                       c = usl_loss_one(LOSS, z.z, y[2], scale), dd = usl_loss_one(LOSS, z.w, y[3], scale);
             *reinterpret_cast<float4*>(grow + j) = make_float4(a.g, b2.g, c.g, dd.g);
             lsum += (a.l + b2.l) + (c.l + dd.l);
         } else {
             for (int q = 0; q < 4 && j + q < j1; ++q) {
-                const Bce1 a = bce_one<LOSS>(zrow[j + q], y[q], scale);
+                const usl_loss_of a = usl_loss_one(LOSS, zrow[j + q], y[q], scale);
                 grow[j + q] = a.g;
                 lsum += a.l;
             }
@@ -145,8 +124,8 @@ k_loss_tiles(float* zg, const int64_t* __restrict__ tgt_off, const int32_t* __re
                 float4* p = reinterpret_cast<float4*>(zg + (size_t)i * m + j0 + c4);
                 const float4 z = *p;
                 const uint32_t yb = ybits[ii][c4 >> 5] >> (c4 & 31);
-                const Bce1 a = bce_one<LOSS>(z.x, (float)(yb & 1u), scale), b2 = bce_one<LOSS>(z.y, (float)((yb >> 1) & 1u), scale),
-                           c = bce_one<LOSS>(z.z, (float)((yb >> 2) & 1u), scale), dd = bce_one<LOSS>(z.w, (float)((yb >> 3) & 1u), scale);
+                const usl_loss_of a = usl_loss_one(LOSS, z.x, (float)(yb & 1u), scale), b2 = usl_loss_one(LOSS, z.y, (float)((yb >> 1) & 1u), scale),
+                           c = usl_loss_one(LOSS, z.z, (float)((yb >> 2) & 1u), scale), dd = usl_loss_one(LOSS, z.w, (float)((yb >> 3) & 1u), scale);
                 gv = make_float4(a.g, b2.g, c.g, dd.g);
                 *p = gv;
                 lsum += (a.l + b2.l) + (c.l + dd.l);
@@ -161,7 +140,7 @@ k_loss_tiles(float* zg, const int64_t* __restrict__ tgt_off, const int32_t* __re
             float gv = 0.f;
             if (i < b && cc < nl) {
                 float* p = zg + (size_t)i * m + j0 + cc;
-                const Bce1 a = bce_one<LOSS>(*p, (float)((ybits[ii][cc >> 5] >> (cc & 31)) & 1u), scale);
+                const usl_loss_of a = usl_loss_one(LOSS, *p, (float)((ybits[ii][cc >> 5] >> (cc & 31)) & 1u), scale);
                 gv = a.g;
                 *p = gv;
                 lsum += a.l;
@@ -192,20 +171,22 @@ k_loss_tiles(float* zg, const int64_t* __restrict__ tgt_off, const int32_t* __re
 }
 
 // One block adds the per-block sums in a fixed order: the loss is reproducible run to run.
-__global__ void __launch_bounds__(1024)
-k_bce_finish(const double* __restrict__ partials, size_t n, float scale, float* __restrict__ loss) {
-    __shared__ double red[16];
+template <int NT_>
+__device__ __forceinline__ void sum_loss(const usl_loss_sum& sum) {
+    __shared__ double red[NT_ / 64];
     double s = 0.0;
-    for (size_t q = threadIdx.x; q < n; q += 1024) s += partials[q];
+    for (size_t q = threadIdx.x; q < sum.n; q += NT_) s += sum.partials[q];
     for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     __syncthreads();
     if (threadIdx.x == 0) {
         double t = 0.0;
-        for (int q = 0; q < 16; ++q) t += red[q];
-        *loss = (float)((double)scale * t);
+        for (int q = 0; q < NT_ / 64; ++q) t += red[q];
+        *sum.loss = (float)((double)sum.scale * t);
     }
 }
+__global__ void __launch_bounds__(1024)
+k_bce_finish(usl_loss_sum sum) { sum_loss<1024>(sum); }
 
 template <typename TS> struct WIo;
 template <> struct WIo<float> {
@@ -228,7 +209,8 @@ template <typename TS>
 __global__ void __launch_bounds__(256)
 k_adam(TS* __restrict__ W, const float* __restrict__ gW, float* __restrict__ m1,
        float* __restrict__ m2, size_t n, float lr, float b1, float b2, float eps, float ic1,
-       float ic2) {
+       float ic2, usl_loss_sum sum) {
+    if (sum.partials && blockIdx.x == gridDim.x - 1) sum_loss<256>(sum);
     const size_t stride = (size_t)gridDim.x * 256 * 4;
     for (size_t f = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4; f < n; f += stride) {
         if (f + 4 <= n) {
@@ -320,7 +302,8 @@ __global__ void __launch_bounds__(256)
 k_adam_staged(TS* __restrict__ W, const float* __restrict__ stage, const uint32_t* __restrict__ pos, int parts, size_t part_stride,
               const uint32_t* __restrict__ gate, const uint32_t* __restrict__ stale, float* __restrict__ gW,
               float* __restrict__ m1, float* __restrict__ m2, size_t n, float lr, float b1, float b2, float eps, float ic1,
-              float ic2) {
+              float ic2, usl_loss_sum sum) {
+    if (sum.partials && blockIdx.x == gridDim.x - 1) sum_loss<256>(sum);
     const bool listed = gate && *gate == 0;
     const bool poison = !listed && *stale != 0;
     const float nan = __uint_as_float(0x7FC00000u);
@@ -405,7 +388,7 @@ usl_status usl_launch_loss(usl_ctx* c, int loss_kind, const float* out, const in
     else                       { if (vec) USL_LOSS(true, LOSS_SQH); else USL_LOSS(false, LOSS_SQH); }
 #undef USL_LOSS
     USL_TRY(usl_check_launch(c, "loss"));
-    hipLaunchKernelGGL(k_bce_finish, dim3(1), dim3(1024), 0, c->stream, c->bce_partials, nblk, scale, loss);
+    hipLaunchKernelGGL(k_bce_finish, dim3(1), dim3(1024), 0, c->stream, usl_loss_sum{c->bce_partials, nblk, scale, loss});
     return usl_check_launch(c, "loss_finish");
 }
 
@@ -446,7 +429,7 @@ usl_status usl_launch_loss_noalloc(usl_ctx* c, int loss_kind, const float* out, 
     else                       { if (vec) USL_LOSS(true, LOSS_SQH); else USL_LOSS(false, LOSS_SQH); }
 #undef USL_LOSS
     USL_TRY(usl_check_launch(c, "loss (static scratch)"));
-    hipLaunchKernelGGL(k_bce_finish, dim3(1), dim3(1024), 0, c->stream, partials, nblk, scale, loss);
+    hipLaunchKernelGGL(k_bce_finish, dim3(1), dim3(1024), 0, c->stream, usl_loss_sum{partials, nblk, scale, loss});
     return usl_check_launch(c, "loss_finish (static scratch)");
 }
 
@@ -469,13 +452,14 @@ usl_status usl_launch_loss_tiles(usl_ctx* c, int loss_kind, float* zg, const int
     *sampled_labels = (uint64_t)((nlb + LT_SAMPLE - 1) / LT_SAMPLE) * LT_TL;
     if (b_end >= b) {   // the last group: every tile of the batch has left its sums
         const size_t nblk = (size_t)nlb * (size_t)((b + 31) / 32);
-        hipLaunchKernelGGL(k_bce_finish, dim3(1), dim3(1024), 0, c->stream, c->bce_partials, nblk, scale, loss);
+        hipLaunchKernelGGL(k_bce_finish, dim3(1), dim3(1024), 0, c->stream, usl_loss_sum{c->bce_partials, nblk, scale, loss});
     }
     return usl_check_launch(c, "loss_finish");
 }
 
 usl_status usl_launch_adam(usl_ctx* c, void* W, const float* grad_W, float* m1, float* m2, float lr,
-                           float beta1, float beta2, float eps, float inv_c1, float inv_c2) {
+                           float beta1, float beta2, float eps, float inv_c1, float inv_c2,
+                           const usl_loss_sum& sum) {
     const size_t n = (size_t)c->m * c->k;
     size_t blocks = (n / 4 + 255) / 256;
     const size_t cap = (size_t)c->num_cu * 16;
@@ -486,10 +470,10 @@ usl_status usl_launch_adam(usl_ctx* c, void* W, const float* grad_W, float* m1, 
     if (!aligned) USL_FAIL(c, USL_EINVAL, "W, grad_W, m1, m2 must be 16-byte aligned");
     if (c->storage == USL_F32)
         hipLaunchKernelGGL(k_adam<float>, dim3((unsigned)blocks), dim3(256), 0, c->stream, (float*)W,
-                           grad_W, m1, m2, n, lr, beta1, beta2, eps, inv_c1, inv_c2);
+                           grad_W, m1, m2, n, lr, beta1, beta2, eps, inv_c1, inv_c2, sum);
     else
         hipLaunchKernelGGL(k_adam<uint16_t>, dim3((unsigned)blocks), dim3(256), 0, c->stream,
-                           (uint16_t*)W, grad_W, m1, m2, n, lr, beta1, beta2, eps, inv_c1, inv_c2);
+                           (uint16_t*)W, grad_W, m1, m2, n, lr, beta1, beta2, eps, inv_c1, inv_c2, sum);
     return usl_check_launch(c, "adam");
 }
 
@@ -509,7 +493,8 @@ usl_status usl_launch_unstage(usl_ctx* c, const usl_staged& st, const uint32_t* 
 
 // Adam from a weight gradient in list order (see k_adam_staged).  grad_W is written (or, behind a zero gate, read).
 usl_status usl_launch_adam_staged(usl_ctx* c, void* W, const usl_staged& st, const uint32_t* gate, float* grad_W, float* m1, float* m2,
-                                  float lr, float beta1, float beta2, float eps, float inv_c1, float inv_c2) {
+                                  float lr, float beta1, float beta2, float eps, float inv_c1, float inv_c2,
+                           const usl_loss_sum& sum) {
     const size_t n = (size_t)c->m * c->k;
     const bool aligned = ((uintptr_t)W % 16 == 0) && ((uintptr_t)grad_W % 16 == 0) &&
                          ((uintptr_t)m1 % 16 == 0) && ((uintptr_t)m2 % 16 == 0);
@@ -517,10 +502,10 @@ usl_status usl_launch_adam_staged(usl_ctx* c, void* W, const usl_staged& st, con
     const unsigned blocks = staged_blocks(c, n);
     if (c->storage == USL_F32)
         hipLaunchKernelGGL(k_adam_staged<float>, dim3(blocks), dim3(256), 0, c->stream, (float*)W, st.stage, st.pos, st.parts, st.part_stride,
-                           gate, st.stale, grad_W, m1, m2, n, lr, beta1, beta2, eps, inv_c1, inv_c2);
+                           gate, st.stale, grad_W, m1, m2, n, lr, beta1, beta2, eps, inv_c1, inv_c2, sum);
     else
         hipLaunchKernelGGL(k_adam_staged<uint16_t>, dim3(blocks), dim3(256), 0, c->stream, (uint16_t*)W, st.stage, st.pos, st.parts,
-                           st.part_stride, gate, st.stale, grad_W, m1, m2, n, lr, beta1, beta2, eps, inv_c1, inv_c2);
+                           st.part_stride, gate, st.stale, grad_W, m1, m2, n, lr, beta1, beta2, eps, inv_c1, inv_c2, sum);
     return usl_check_launch(c, "adam (staged gradient)");
 }
 

@@ -552,11 +552,86 @@ usl_status run_forward_few(usl_ctx* c, const Layout& L, const void* x, const int
 
 }  // namespace
 
-usl_status usl_launch_forward(usl_ctx* c, const void* x, const int32_t* idx, const void* W, float* out, int32_t b) {
-    if (!fast_path_ok(c, idx, W))
-        return c->storage == USL_F32 ? run_forward_generic<float>(c, x, idx, W, out, b) : run_forward_generic<uint16_t>(c, x, idx, W, out, b);
-    const Layout L = layout_of(c, b, x);
-    if (b <= L.Q && !L.halves && !c->part_of_batch) return run_forward_few(c, L, x, idx, W, out, b);
+namespace {
+
+// What k_forward's loss leaves to do: the gradient and the loss of the targets, a few per instance.  Their scores are taken
+// once more, in k_forward's order of additions (the same bits): 16 lanes bring the slots of a target, in the order of
+// their steps, and one of them adds up.  A label listed twice for an instance counts once: the exchange shows who came
+// second, for the gradient of a target is never what it is without one.  Block i of the first b: instance i, its change
+// of the loss goes to partials[i].  Block b, if there is one, compares the fingerprint of idx for the backward product
+// (a launch of its own took 4 to 8 us).
+template <typename TS>
+__global__ void __launch_bounds__(1024)
+k_loss_positives(const TS* __restrict__ x, const int32_t* __restrict__ idx, const TS* __restrict__ W, float* __restrict__ g, int64_t m,
+                 int d, int k, int K, bool halves, const uint8_t* __restrict__ perm, int b, const int64_t* __restrict__ tgt_off,
+                 const int32_t* __restrict__ tgt_lab, int kind, float scale, double* __restrict__ partials, size_t n_words,
+                 uint64_t* __restrict__ print) {
+    constexpr int PER = 64;   // targets at a time
+    __shared__ float2 slots[PER][65];        // {weight, activation} of a slot; zeros behind the last one
+    __shared__ uint8_t upper[PER][64];       // whether its column is in the second half of a row in two halves
+    __shared__ uint8_t order[PER][64];       // slot of a step
+    __shared__ double red[16];
+    const int i = blockIdx.x;
+    if (i == b) {
+        usl_idx_fingerprint_block(reinterpret_cast<const uint32_t*>(idx), n_words, print, 0);
+        return;
+    }
+    const int64_t p1 = tgt_off[i + 1];
+    const TS* row = x + (size_t)i * d;
+    const int q16 = threadIdx.x >> 4;
+    const float2* mine = slots[q16];
+    double delta = 0.0;
+    for (int64_t p = tgt_off[i] + (threadIdx.x >> 4); p < p1; p += PER) {   // the lanes of a target are of one wavefront
+        const int64_t j = tgt_lab[p];
+        if (j < 0 || j >= m) continue;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {   // (order, indices and weights are under way together)
+            const int s = q * 16 + (int)(threadIdx.x & 15);
+            if (s >= K) continue;
+            order[q16][s] = perm ? perm[j * K + s] : (uint8_t)s;
+            float2 v = make_float2(0.f, 0.f);
+            int col = 0;
+            if (s < k) {
+                col = idx[j * k + s];
+                v = make_float2(usl_load_f32<TS>(W, (size_t)j * k + s), usl_load_f32<TS>(row, (size_t)col));
+            }
+            slots[q16][s] = v;
+            upper[q16][s] = col >= HALF_COLS ? 1 : 0;
+        }
+        wave_sync();
+        if ((threadIdx.x & 15) == 0) {
+            float z = 0.f;
+            if (sizeof(TS) == 4) {
+                for (int part = 0; part < (halves ? 2 : 1); ++part)
+                    for (int s = 0; s < K; ++s) {
+                        const int t = order[q16][s];
+                        if (!halves || upper[q16][t] == part) z = fmaf(mine[t].x, mine[t].y, z);
+                    }
+            } else {
+                for (int s = 0; s < K; s += 2) {
+                    const float2 u = mine[order[q16][s]], v = mine[order[q16][s + 1]];
+                    z = dot2(__float_as_uint(u.y) >> 16 | __float_as_uint(v.y), __float_as_uint(u.x) >> 16 | __float_as_uint(v.x), z);
+                }
+            }
+            const usl_loss_of without = usl_loss_one(kind, z, 0.f, scale), with = usl_loss_one(kind, z, 1.f, scale);
+            const float before = atomicExch(g + (size_t)i * m + j, with.g);
+            if (__float_as_uint(before) != __float_as_uint(with.g)) delta += (double)with.l - (double)without.l;
+        }
+        wave_sync();
+    }
+    for (int o = 32; o > 0; o >>= 1) delta += __shfl_down(delta, o);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = delta;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+        for (int q = 0; q < 16; ++q) t += red[q];
+        partials[i] = t;
+    }
+}
+
+// the forward kernel over the whole batch, with or without the loss
+usl_status run_forward(usl_ctx* c, const Layout& L, const void* x, const int32_t* idx, const void* W, float* out, int32_t b, LossArgs loss,
+                       size_t* blocks) {
     const Launch p = choose(c, L, b, false);
     const uint8_t* perm = nullptr;
     const void* xi = nullptr;
@@ -565,8 +640,48 @@ usl_status usl_launch_forward(usl_ctx* c, const void* x, const int32_t* idx, con
     int64_t m = c->m;
     int k = c->k, bb = b;
     Geom tg = p.geom;
-    void* args[] = {&xi, &idx, &W, &out, &m, &k, &bb, &tg, &perm};
+    if (loss.kind >= 0) {   // sized once for max_b: a part of the batch to every block, or parts until the chip is full several times
+        const size_t most = (size_t)((c->m + 255) / 256) + (size_t)c->num_cu * 32 + (size_t)c->max_b;
+        *blocks = (size_t)p.nblk * (size_t)p.G;
+        USL_TRY(usl_reserve(c, (void**)&c->bce_partials, &c->bce_partials_cap, max_sz(most, *blocks + (size_t)b) * sizeof(double)));
+        loss.partials = c->bce_partials;
+    }
+    void* args[] = {&xi, &idx, &W, &out, &m, &k, &bb, &tg, &perm, &loss};
     return launch(c, p, args, "forward");
+}
+
+bool streams(const usl_ctx* c, const Layout& L, int b) { return b <= L.Q && !L.halves && !c->part_of_batch; }
+
+}  // namespace
+
+usl_status usl_launch_forward(usl_ctx* c, const void* x, const int32_t* idx, const void* W, float* out, int32_t b) {
+    if (!fast_path_ok(c, idx, W))
+        return c->storage == USL_F32 ? run_forward_generic<float>(c, x, idx, W, out, b) : run_forward_generic<uint16_t>(c, x, idx, W, out, b);
+    const Layout L = layout_of(c, b, x);
+    if (streams(c, L, b)) return run_forward_few(c, L, x, idx, W, out, b);
+    return run_forward(c, L, x, idx, W, out, b, LossArgs{-1, 0.f, nullptr}, nullptr);
+}
+
+bool usl_forward_loss_applies(const usl_ctx* c, const void* x, const int32_t* idx, const void* W, int32_t b) {
+    return fast_path_ok(c, idx, W) && !streams(c, layout_of(c, b, x), b);
+}
+
+usl_status usl_launch_forward_loss(usl_ctx* c, const void* x, const int32_t* idx, const void* W, float* g, int32_t b, int loss_kind,
+                                   const int64_t* tgt_off, const int32_t* tgt_lab, float scale, float* loss, usl_loss_sum* sum) {
+    size_t blocks = 0;
+    const Layout L = layout_of(c, b, x);
+    USL_TRY(run_forward(c, L, x, idx, W, g, b, LossArgs{loss_kind, scale, nullptr}, &blocks));
+    const bool check = c->lf[1].built_for == idx;   // lists that the backward product will use
+    const dim3 grid((unsigned)(b + (check ? 1 : 0)));
+#define USL_POS(TS)                                                                                                              \
+    hipLaunchKernelGGL(k_loss_positives<TS>, grid, dim3(1024), 0, c->stream, (const TS*)x, idx, (const TS*)W, g, c->m, c->d, c->k, L.K,   \
+                       L.halves, c->no_order ? nullptr : c->slot_order, b, tgt_off, tgt_lab, loss_kind, scale, c->bce_partials + blocks, \
+                       (size_t)c->m * c->k, c->idx_print)
+    if (c->storage == USL_F32) USL_POS(float); else USL_POS(uint16_t);
+#undef USL_POS
+    c->print_done = check;
+    *sum = usl_loss_sum{c->bce_partials, blocks + (size_t)b, scale, loss};
+    return usl_check_launch(c, "loss of the targets");
 }
 
 usl_status usl_activation_rows(usl_ctx* c, const void* x, int32_t b, int Q, const void** rows, size_t* stride) {

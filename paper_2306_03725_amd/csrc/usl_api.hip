@@ -369,7 +369,7 @@ extern "C" usl_status usl_adam_step(usl_ctx* c, void* W, const float* grad_W, fl
     double c1 = 1.0 - pow((double)beta1, (double)t);
     double c2 = 1.0 - pow((double)beta2, (double)t);
     return usl_launch_adam(c, W, grad_W, m1, m2, lr, beta1, beta2, eps, (float)(1.0 / c1),
-                           (float)(1.0 / c2));
+                           (float)(1.0 / c2), usl_loss_sum{});
 }
 
 extern "C" usl_status usl_train_step(usl_ctx* c, const void* x, const int32_t* idx, void* W, float* m1,
@@ -392,21 +392,31 @@ extern "C" usl_status usl_train_step(usl_ctx* c, const void* x, const int32_t* i
     struct KeepX {
         usl_ctx* c;
         explicit KeepX(usl_ctx* c_) : c(c_) { c->xi_keep = true; c->xi_of = nullptr; }
-        ~KeepX() { c->xi_keep = false; c->xi_of = nullptr; }
+        ~KeepX() { c->xi_keep = false; c->xi_of = nullptr; c->print_done = false; }
     } keep_x(c);
-    USL_TRY(usl_launch_forward(c, x, idx, W, g, b));
+    // Where the backward products read g row-major, the loss is part of the forward kernel; the tile-major form of the
+    // input gradient has a loss kernel of its own that writes g both ways.
+    usl_loss_sum sum = {};
+    const bool lists = loss_kind == 1 && usl_sparse_supported(c);
+    const bool by_rows = !grad_x || usl_bwi_lds_applies(c) || usl_both_lds_applies(c) ||
+                         (lists && (b > usl_bwd_input_group_rows() || usl_sparse_expected(c)));
+    const bool fused = by_rows && usl_forward_loss_applies(c, x, idx, W, b);
+    if (fused) {
+        USL_TRY(usl_launch_forward_loss(c, x, idx, W, g, b, loss_kind, tgt_off, tgt_lab, scale, loss, &sum));
+    } else {
+        USL_TRY(usl_launch_forward(c, x, idx, W, g, b));
+        if (by_rows) USL_TRY(usl_launch_loss(c, loss_kind, g, tgt_off, tgt_lab, scale, g, loss, b));
+    }
     if (grad_x) {
         // The loss writes the gradient in place and, group of 256 instances by group, as the tile-major pieces the
         // input-gradient gathers read; the gathers of a group run before the next group's pieces replace them.
         // Squared hinge: the gradient of a trained layer is almost all zeros (Section 3.3); when the context expects
         // that, its nonzeros are listed once and both backward products try the lists first (k_sparse_grad.hip).
         const int G = usl_bwd_input_group_rows();
-        const bool lists = loss_kind == 1 && usl_sparse_supported(c);
-        if (usl_bwi_lds_applies(c) || usl_both_lds_applies(c) || (lists && (b > G || usl_sparse_expected(c)))) {
+        if (by_rows) {
             // squared hinge where a gradient of almost only zeros is expected (or the batch has several groups, and
             // the look at the gradient needs all of it): the loss writes the gradient row-major only, its nonzeros are
             // listed once, and both backward products use the lists (the dense kernels stand by behind the gate)
-            USL_TRY(usl_launch_loss(c, loss_kind, g, tgt_off, tgt_lab, scale, g, loss, b));
             // (the same order of calls where the input gradient reads g row-major: its register-list form)
             const uint32_t* gate = nullptr;
             usl_staged staged;
@@ -415,7 +425,7 @@ extern "C" usl_status usl_train_step(usl_ctx* c, const void* x, const int32_t* i
                 const double c1 = 1.0 - pow((double)beta1, (double)t);
                 const double c2 = 1.0 - pow((double)beta2, (double)t);
                 return usl_launch_adam_staged(c, W, staged, gate, grad_W, m1, m2, lr, beta1, beta2, eps, (float)(1.0 / c1),
-                                              (float)(1.0 / c2));
+                                              (float)(1.0 / c2), sum);
             }
         } else {
             USL_TRY(usl_bwd_input_prepare(c, idx, b));
@@ -440,12 +450,11 @@ extern "C" usl_status usl_train_step(usl_ctx* c, const void* x, const int32_t* i
             USL_TRY(s);
         }
     } else {
-        USL_TRY(usl_launch_loss(c, loss_kind, g, tgt_off, tgt_lab, scale, g, loss, b));
         USL_TRY(usl_launch_backward_weight(c, g, x, idx, grad_W, b, loss_kind == 0));   // BCE gradients are dense
     }
     const double c1 = 1.0 - pow((double)beta1, (double)t);
     const double c2 = 1.0 - pow((double)beta2, (double)t);
-    return usl_launch_adam(c, W, grad_W, m1, m2, lr, beta1, beta2, eps, (float)(1.0 / c1), (float)(1.0 / c2));
+    return usl_launch_adam(c, W, grad_W, m1, m2, lr, beta1, beta2, eps, (float)(1.0 / c1), (float)(1.0 / c2), sum);
 }
 
 extern "C" usl_status usl_redistribute(usl_ctx* c, int32_t* idx, void* W, float* m1, float* m2,

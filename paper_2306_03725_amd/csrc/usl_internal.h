@@ -32,6 +32,7 @@ struct usl_ctx {
     uint32_t* csc_order;      size_t csc_order_cap;   // [3][nwin*d] features of each window by falling list length; rank of each feature; list length by rank
     uint32_t* csc_slot;       // [m*k] flat slot j*k+t, grouped by (label window, feature)
     float* csc_w;             // [m*k] W of that slot (refreshed by every backward_input)
+    bool print_done;          // inside usl_train_step: the fingerprint of idx has been compared
     uint64_t* idx_print;      // [0] fingerprint of idx when the lists were built; word [2] (32 bits): 1 = a later call found idx changed
     const int32_t* idx_to_check;  // idx whose fingerprint the next weight gather compares (NULL right after a build)
     int csc_win_labels;       // labels per window the lists were built with
@@ -120,6 +121,18 @@ usl_status usl_build_slot_order(usl_ctx* ctx, const int32_t* idx, int K, int uni
 // Kernel launchers (one per file).  All take validated arguments.
 usl_status usl_launch_forward(usl_ctx* ctx, const void* x, const int32_t* idx, const void* W,
                               float* out, int32_t b);
+// forward and loss in one: out receives the gradient of the loss by the scores.  A later kernel of the same step has to
+// turn *sum into the loss (usl_launch_adam and usl_launch_adam_staged do).  Also compares the fingerprint of idx if lists
+// for it stand (ctx->print_done says so).  usl_forward_loss_applies: else forward and loss are called one after the other.
+struct usl_loss_sum {
+    const double* partials;   // the loss = scale * the sum of n partial sums; nullptr: nothing left to add up
+    size_t n;
+    float scale;
+    float* loss;
+};
+bool usl_forward_loss_applies(const usl_ctx* ctx, const void* x, const int32_t* idx, const void* W, int32_t b);
+usl_status usl_launch_forward_loss(usl_ctx* ctx, const void* x, const int32_t* idx, const void* W, float* g, int32_t b, int loss_kind,
+                                   const int64_t* tgt_off, const int32_t* tgt_lab, float scale, float* loss, usl_loss_sum* sum);
 // dense = the caller knows that g holds (almost) no exact zeros: the zero-skipping tests are left out
 usl_status usl_launch_backward_weight(usl_ctx* ctx, const float* g, const void* x,
                                       const int32_t* idx, float* grad_W, int32_t b, bool dense = false);
@@ -166,7 +179,7 @@ usl_status usl_activation_rows(usl_ctx* ctx, const void* x, int32_t b, int Q, co
 // grad_W[f] = the staged gradient of slot f (behind a zero gate: nothing, the kernels over the listed nonzeros wrote grad_W)
 usl_status usl_launch_unstage(usl_ctx* ctx, const usl_staged& st, const uint32_t* gate, float* grad_W);
 usl_status usl_launch_adam_staged(usl_ctx* ctx, void* W, const usl_staged& st, const uint32_t* gate, float* grad_W, float* m1, float* m2,
-                                  float lr, float beta1, float beta2, float eps, float inv_c1, float inv_c2);
+                                  float lr, float beta1, float beta2, float eps, float inv_c1, float inv_c2, const usl_loss_sum& sum);
 // Records (store = 1) the fingerprint of idx in ctx->idx_print, or compares with the recorded one (store = 0) and
 // raises the stale word (32-bit word 4 of idx_print) on a difference.
 usl_status usl_idx_fingerprint(usl_ctx* ctx, const int32_t* idx, int store);
@@ -188,7 +201,7 @@ usl_status usl_launch_loss_noalloc(usl_ctx* ctx, int loss_kind, const float* out
                                    const int32_t* tgt_lab, float scale, float* g, float* loss, int32_t b);
 usl_status usl_launch_adam(usl_ctx* ctx, void* W, const float* grad_W, float* m1, float* m2,
                            float lr, float beta1, float beta2, float eps, float inv_c1,
-                           float inv_c2);
+                           float inv_c2, const usl_loss_sum& sum);
 usl_status usl_launch_redistribute(usl_ctx* ctx, int32_t* idx, void* W, float* m1, float* m2,
                                    int64_t n, uint64_t seed, uint64_t epoch);
 usl_status usl_launch_redistribute_rows(usl_ctx* ctx, int32_t* idx, void* W, float* m1, float* m2,
@@ -216,12 +229,74 @@ __device__ __forceinline__ uint16_t usl_f32_to_bf16(float f) {  // nearest, ties
     u += 0x7FFFu + ((u >> 16) & 1u);
     return (uint16_t)(u >> 16);
 }
+// The losses of one score z against its target y, 0 or 1: l and the gradient by z times scale.  (In the forward kernel the
+// arithmetic counts: with the division of the standard library the step took 2 to 4 % longer where rows are short.)
+// 0, binary cross-entropy: l = max(z,0) - z*y + log(1 + exp(-|z|));  dl/dz = sigmoid(z) - y
+// 1, squared hinge: s = 2y-1, l = max(0, 1 - s*z)^2;                 dl/dz = -2*s*max(0, 1 - s*z)  (exact zeros)
+struct usl_loss_of { float g, l; };
+__device__ __forceinline__ usl_loss_of usl_loss_one(int kind, float z, float y, float scale) {
+    usl_loss_of o;
+    if (kind == 0) {
+        const float e = __expf(-fabsf(z)), p = 1.f + e;   // p in [1, 2]
+        // 1 / p: the hardware's estimate (1 ulp) and a Newton step, within a hair of half an ulp
+        const float r0 = __builtin_amdgcn_rcpf(p), r = fmaf(r0, fmaf(-p, r0, 1.f), r0);
+        const float sig = z >= 0.f ? r : e * r;
+        o.g = scale * (sig - y);
+        o.l = fmaxf(z, 0.f) - (y != 0.f ? z : 0.f) + __logf(p);
+    } else {
+        const float sgn = 2.f * y - 1.f;
+        const float margin = fmaxf(0.f, fmaf(-sgn, z, 1.f));
+        o.g = scale * (-2.f * sgn * margin);
+        o.l = margin * margin;
+    }
+    return o;
+}
 template <typename TS> __device__ __forceinline__ float usl_load_f32(const TS* p, size_t i);
 template <> __device__ __forceinline__ float usl_load_f32<float>(const float* p, size_t i) {
     return p[i];
 }
 template <> __device__ __forceinline__ float usl_load_f32<uint16_t>(const uint16_t* p, size_t i) {
     return usl_bf16_to_f32(p[i]);
+}
+// Fingerprint of idx: a sum of mixed 16-byte groups at up to 4096 evenly spaced places (64 KiB read by one
+// workgroup, every load in flight at once: a few microseconds).  store = 1 records it when the column lists
+// are built; store = 0 compares on a later call and raises print[2] (as a 32-bit word) when the contents are
+// no longer those the lists were built from: a new tensor at a recycled address, a checkpoint copied in, ...
+// A single edited entry can slip through the sample; wholesale replacement cannot.
+__device__ __forceinline__ void usl_idx_fingerprint_block(const uint32_t* __restrict__ idx, size_t n_words,
+                                                      uint64_t* __restrict__ print, int store) {   // 1024 lanes
+    __shared__ uint64_t red[16];
+    const size_t groups = n_words / 4;
+    const size_t samples = groups < 4096 ? groups : 4096;
+    const size_t stride = samples ? groups / samples : 1;   // >= 1
+    uint4 v[4];
+    size_t at[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const size_t s = (size_t)q * 1024 + threadIdx.x;
+        at[q] = s < samples ? s * stride : 0;
+        v[q] = s < samples ? reinterpret_cast<const uint4*>(idx)[at[q]] : make_uint4(0, 0, 0, 0);
+    }
+    uint64_t h = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if ((size_t)q * 1024 + threadIdx.x >= samples) continue;
+        uint64_t a = ((uint64_t)v[q].x << 32 | v[q].y) ^ (at[q] * 0x9E3779B97F4A7C15ull);
+        uint64_t b2 = ((uint64_t)v[q].z << 32 | v[q].w) + (at[q] << 7);
+        a ^= a >> 31; a *= 0xD6E8FEB86659FD93ull; a ^= a >> 29;
+        b2 ^= b2 >> 33; b2 *= 0xC2B2AE3D27D4EB4Full; b2 ^= b2 >> 30;
+        h += a + (b2 << 1 | b2 >> 63);
+    }
+    for (size_t w = groups * 4 + threadIdx.x; w < n_words; w += 1024) h += (uint64_t)idx[w] * 0xFF51AFD7ED558CCDull;   // ragged tail
+    for (int o = 32; o > 0; o >>= 1) h += __shfl_down(h, o);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = h;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint64_t t = 0;
+        for (int q = 0; q < 16; ++q) t += red[q];
+        if (store) { print[0] = t; }
+        else if (print[0] != t) reinterpret_cast<uint32_t*>(print)[4] = 1u;
+    }
 }
 // The lanes whose reads meet in one pass of the LDS: 32 consecutive lanes (ds_read_b32, ds_read_b64), or, for
 // ds_read_b128, 16 lanes of a half-wavefront: 0-3, 12-15, 20-27 and the other 16 (measured: two lanes with different
