@@ -25,7 +25,7 @@
 // per compute unit) for everything else; the gathers are therefore written out in assembly, four in flight.
 #include <stdlib.h>
 
-#include "usl_internal.h"
+#include "k_matching.h"
 
 namespace {
 
@@ -82,14 +82,31 @@ __global__ void k_fill_u32(uint32_t* p, size_t n, uint32_t v) {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = v;
 }
 
-// The slots of one window's labels, cut into `splits` contiguous shares.
-__device__ __forceinline__ void share_of(int64_t m, int k, int wl, int splits, size_t* e0, size_t* e1) {
-    const int w = blockIdx.x / splits, s = blockIdx.x % splits;
+// The slots of one window's labels, cut into `splits` contiguous shares.  Returns the window.  An XCD (blockIdx.x % 8) takes
+// an eighth of the shares in order: the shares of a window write into the same lines, through one L2.
+__device__ __forceinline__ int share_of(int64_t m, int k, int wl, int splits, size_t* e0, size_t* e1) {
+    const int t = (int)(blockIdx.x & 7) * ((int)gridDim.x / 8) + (int)(blockIdx.x >> 3);
+    const int w = t / splits, s = t % splits;
     const size_t w0 = (size_t)w * wl * k;
     const size_t w1 = (size_t)min((int64_t)(w + 1) * wl, m) * k;
     const size_t per = (w1 - w0 + splits - 1) / splits;
     *e0 = min(w0 + per * s, w1);
     *e1 = min(*e0 + per, w1);
+    return w;
+}
+
+// f(slot, its virtual feature counted from c0) for the slots [e0, e1) of a share: eight of a lane's loads in flight together
+// (one at a time, the latency of memory was most of the time of these kernels)
+template <typename F>
+__device__ __forceinline__ void for_share(const int32_t* __restrict__ idx, size_t e0, size_t e1, int k, int d, const Cut& cut, uint32_t j0, int c0, F f) {
+    for (size_t e = e0 + threadIdx.x; e < e1; e += 8 * NT) {
+        uint32_t col[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) col[u] = e + u * NT < e1 ? (uint32_t)idx[e + u * NT] : 0u;
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (e + u * NT < e1) f(e + u * NT, cut.S == 1 ? col[u] - (uint32_t)c0 : cut.vfeat(col[u], (uint32_t)(e + u * NT) / (uint32_t)k - j0, d) - (uint32_t)c0);
+    }
 }
 
 // count[w][c] += connections of this workgroup's share that lead into feature c (LDS histogram, then one global
@@ -98,17 +115,17 @@ __global__ void __launch_bounds__(NT)
 k_lf_count(const int32_t* __restrict__ idx, int64_t m, int k, int d, Cut cut, int splits, uint32_t* __restrict__ count) {
     extern __shared__ uint32_t hist[];
     const int c0 = blockIdx.y * CHUNK, nc = min(CHUNK, cut.vd - c0);
-    const uint32_t j0 = (uint32_t)(blockIdx.x / splits) * (uint32_t)cut.wl;
     size_t e0, e1;
-    share_of(m, k, cut.wl, splits, &e0, &e1);
+    const int w = share_of(m, k, cut.wl, splits, &e0, &e1);
+    if (w >= cut.nwin) return;
+    const uint32_t j0 = (uint32_t)w * (uint32_t)cut.wl;
     for (int q = threadIdx.x; q < nc; q += NT) hist[q] = 0;
     __syncthreads();
-    for (size_t e = e0 + threadIdx.x; e < e1; e += NT) {
-        const uint32_t c = cut.vfeat((uint32_t)idx[e], (uint32_t)(e / (uint32_t)k) - j0, d) - (uint32_t)c0;
+    for_share(idx, e0, e1, k, d, cut, j0, c0, [&](size_t, uint32_t c) {
         if (c < (uint32_t)nc) atomicAdd(&hist[c], 1u);
-    }
+    });
     __syncthreads();
-    uint32_t* dst = count + (size_t)(blockIdx.x / splits) * cut.vd + c0;
+    uint32_t* dst = count + (size_t)w * cut.vd + c0;
     for (int q = threadIdx.x; q < nc; q += NT)
         if (hist[q]) atomicAdd(&dst[q], hist[q]);
 }
@@ -260,27 +277,33 @@ k_lf_fill(const int32_t* __restrict__ idx, int64_t m, int k, int d, Cut cut, int
           uint32_t* __restrict__ taken, const uint32_t* __restrict__ ent_base, uint32_t* __restrict__ ent) {
     extern __shared__ uint32_t cur[];
     const int c0 = blockIdx.y * CHUNK, nc = min(CHUNK, cut.vd - c0);
-    const int w = blockIdx.x / splits;
-    const uint32_t j0 = (uint32_t)w * (uint32_t)cut.wl;
     size_t e0, e1;
-    share_of(m, k, cut.wl, splits, &e0, &e1);
+    const int w = share_of(m, k, cut.wl, splits, &e0, &e1);
+    if (w >= cut.nwin) return;
+    const uint32_t j0 = (uint32_t)w * (uint32_t)cut.wl;
     for (int q = threadIdx.x; q < nc; q += NT) cur[q] = 0;
     __syncthreads();
-    for (size_t e = e0 + threadIdx.x; e < e1; e += NT) {
-        const uint32_t c = cut.vfeat((uint32_t)idx[e], (uint32_t)(e / (uint32_t)k) - j0, d) - (uint32_t)c0;
+    for_share(idx, e0, e1, k, d, cut, j0, c0, [&](size_t, uint32_t c) {
         if (c < (uint32_t)nc) atomicAdd(&cur[c], 1u);
-    }
+    });
     __syncthreads();
     const size_t bin0 = (size_t)w * cut.vd + c0;
-    for (int q = threadIdx.x; q < nc; q += NT) {   // from here cur[q] = where this share's part of the list starts
-        const uint32_t n = cur[q];
-        if (n) cur[q] = atomicAdd(&taken[bin0 + q], n) + where[bin0 + q] + ent_base[(size_t)w * cut.nfb + (c0 + q) / cut.fpb];
+    for (int q0 = threadIdx.x; q0 < nc; q0 += 8 * NT) {   // from here cur[q] = where this share's part of the list starts
+        uint32_t at[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int q = q0 + u * NT;
+            const uint32_t n = q < nc ? cur[q] : 0u;
+            at[u] = n ? atomicAdd(&taken[bin0 + q], n) + where[bin0 + q] + ent_base[(size_t)w * cut.nfb + (c0 + q) / cut.fpb] : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (q0 + u * NT < nc) cur[q0 + u * NT] = at[u];
     }
     __syncthreads();
-    for (size_t e = e0 + threadIdx.x; e < e1; e += NT) {
-        const uint32_t c = cut.vfeat((uint32_t)idx[e], (uint32_t)(e / (uint32_t)k) - j0, d) - (uint32_t)c0;
+    for_share(idx, e0, e1, k, d, cut, j0, c0, [&](size_t e, uint32_t c) {
         if (c < (uint32_t)nc) ent[atomicAdd(&cur[c], 1u)] = (uint32_t)e;
-    }
+    });
 }
 
 // Where the kernel for both products leaves the weight gradient of every connection (pos[flat slot], a place in an
@@ -356,9 +379,8 @@ k_lf_seg_place(const int32_t* __restrict__ idx, int64_t m, int k, Cut cut, int n
 // read slot t of their own lists; the sum does not depend on the order of a list, so each list is permuted so that
 // the 32 addresses of a step fall into different LDS banks as far as possible (a step costs as many LDS cycles as its
 // fullest bank has lanes).  The order is built step by step as a sequence of matchings between the 32 lanes and the
-// 32 banks over the entries not placed yet -- a few rounds of proposals, then augmenting paths from the banks still
-// free, then lanes whose banks are all taken double up on the least loaded one --, the same construction as for the
-// slots of a label in the forward product, with one addition: a list shorter than the wavefront's allowance has
+// 32 banks over the entries not placed yet (k_matching.h), the same construction as for the slots of a label in the
+// forward product, with one addition: a list shorter than the wavefront's allowance has
 // empty places, which may go to any step and read any bank.  A lane that finds no bank among its entries spends an
 // empty place (it then reads the zero word of a free bank, see ZERO_LABEL) while it has one.
 // One half-wavefront per (workgroup of the gather kernel, zone, 32 lanes); lane i is list i and also bank i.
@@ -378,15 +400,15 @@ k_lf_schedule(const uint32_t* __restrict__ ent, const uint32_t* __restrict__ ent
               uint32_t zero_label, int rounds, uint16_t* __restrict__ lab, uint32_t* __restrict__ slot, OvEntry* __restrict__ ov,
               const uint32_t* __restrict__ pos, uint32_t* __restrict__ rk, uint32_t* __restrict__ ovrk) {
     constexpr int SG = SG_NT / GS;
-    constexpr uint32_t ALL = GS == 32 ? 0xFFFFFFFFu : (1u << (GS & 31)) - 1u;
-    __shared__ uint8_t slots[SG][GS][KTOT + 4];   // my entries sorted by bank
-    __shared__ uint8_t left_in[SG][GS][GS + 4];   // entries of mine not placed yet, per bank
-    __shared__ uint8_t end_of[SG][GS][GS + 4];    // where bank b's entries end in the sorted list
-    __shared__ int deg0[SG][GS];
-    __shared__ int win[SG][GS];
+    typedef usl_bank_lists<GS, KTOT> Lists;
+    __shared__ typename Lists::Lane lists[SG][GS];
+    __shared__ uint8_t ord[SG][GS][KTOT + 4];     // first the bank of every entry of mine, then the entry at step s (128 + b: none, bank b)
+    __shared__ int deg0[SG][GS];                  // entries of the group that read a bank and are not placed yet
+    __shared__ uint32_t win[SG][GS];
     const int gl = threadIdx.x / GS, lane = threadIdx.x & (GS - 1);
-    const int hs = threadIdx.x & 63 & ~(GS - 1);  // where my group's bits sit in a wavefront ballot
-    const size_t gid = (size_t)blockIdx.x * (SG_NT / 32) + (threadIdx.x >> 5);   // half-wavefront of the gather kernel
+    // half-wavefront of the gather kernel; an XCD (blockIdx.x % 8) takes an eighth of them in this order: the places that the
+    // lists of a window look up (pos) are then read through one L2
+    const size_t gid = ((size_t)(blockIdx.x & 7) * (gridDim.x / 8) + (blockIdx.x >> 3)) * (SG_NT / 32) + (threadIdx.x >> 5);
     const size_t wg = gid >> 6;
     const int zone = (int)(gid >> 5) & 1, half = (int)gid & 31;   // the two halves of a wavefront are neighbours: same allowance
     const int mypos = half * 32 + usl_lane_of_position<GS>(threadIdx.x & 31);
@@ -400,7 +422,12 @@ k_lf_schedule(const uint32_t* __restrict__ ent, const uint32_t* __restrict__ ent
     const size_t bin = exists ? (size_t)w * cut.vd + (size_t)fb * cut.fpb + f : 0;
     const uint32_t len = exists ? count[bin] : 0u;
     const uint32_t* my = ent + ent_base[wg] + (exists ? where[bin] : 0u);
-    auto label_of = [&](uint32_t e) -> uint32_t { return e / (uint32_t)k - (uint32_t)w * (uint32_t)cut.wl; };
+    const uint32_t inv_k = k > 1 ? (uint32_t)(0x100000000ull / (uint32_t)k) : 0xFFFFFFFFu;   // the same for all lanes
+    auto label_of = [&](uint32_t e) -> uint32_t {   // e / k, at most one too low at first
+        uint32_t q = __umulhi(e, inv_k);
+        if (e - q * (uint32_t)k >= (uint32_t)k) ++q;
+        return q - (uint32_t)w * (uint32_t)cut.wl;
+    };
     const int n = (int)min(len, (uint32_t)cap);     // entries that get a register slot
     for (uint32_t p = (uint32_t)cap; p < len; ++p) {   // the others: to the list's part of the overflow list
         OvEntry o;
@@ -423,123 +450,43 @@ k_lf_schedule(const uint32_t* __restrict__ ent, const uint32_t* __restrict__ ent
         return;   // the whole wavefront: rounds is the same for all
     }
     deg0[gl][lane] = 0;
-    for (int b = 0; b < GS; ++b) left_in[gl][lane][b] = 0;
     __syncthreads();
-    uint8_t* mine = slots[gl][lane];
-    uint8_t* cnt = left_in[gl][lane];
-    uint8_t* ends = end_of[gl][lane];
-    for (int p = 0; p < n; ++p) {
-        const int b = (int)(label_of(my[p]) & (GS - 1u));
-        ++cnt[b];
-        atomicAdd(&deg0[gl][b], 1);
-    }
+    uint32_t avail = Lists::build(lists[gl][lane], ord[gl][lane], n, deg0[gl], [&](int p) { return (int)(label_of(my[p]) & (GS - 1u)); });
     int wild = cap - n;            // empty places left
-    uint32_t avail = 0;            // banks my unplaced entries read
-    {   // counting sort of my entries by bank (their banks are read a second time: no room to keep them)
-        int run = 0;
-        for (int b = 0; b < GS; ++b) { run += cnt[b]; ends[b] = (uint8_t)run; if (cnt[b]) avail |= 1u << b; }
-        for (int p = n - 1; p >= 0; --p) { const int b = (int)(label_of(my[p]) & (GS - 1u)); ends[b] = (uint8_t)(ends[b] - 1); mine[ends[b]] = (uint8_t)p; }
-        for (int b = 0; b < GS; ++b) ends[b] = (uint8_t)(ends[b] + cnt[b]);   // back from starts to ends
-    }
     __syncthreads();
-    auto gballot = [&](bool p) -> uint32_t { return (uint32_t)(__ballot(p) >> hs) & ALL; };
-    volatile int* gwin = win[gl];
-    int mydeg = deg0[gl][lane];    // bank role: entries of the group that read bank `lane` and are not placed yet
+    usl_matching<GS> match(win[gl], lane);
     for (int s = 0; s < cap; ++s) {
-        int mb = -1;               // list role: my bank at this step
-        int ml = -1;               // bank role: the list that reads me at this step
-        for (int r = 0; r < rounds; ++r) {
-            const uint32_t freeb = gballot(ml < 0);
-            gwin[lane] = 255;
-            int prop = -1;
-            const uint32_t cand = mb < 0 ? (avail & freeb) : 0u;
-            if (cand) {            // first candidate bank at or after a lane- and round-dependent start
-                const int sh = (lane + 7 * r) & (GS - 1);
-                const uint32_t rc = ((cand >> sh) | (cand << ((GS - sh) & (GS - 1)))) & ALL;
-                prop = (__ffs(rc) - 1 + sh) & (GS - 1);
-                atomicMin(&win[gl][prop], lane);
-            }
-            const int wnr = gwin[lane];
-            if (ml < 0 && wnr < GS) ml = wnr;
-            if (prop >= 0 && gwin[prop] == lane) mb = prop;
-        }
-        // augmenting paths from the banks still free
-        uint32_t todo = gballot(ml < 0 && mydeg > 0);
-        while (__any(todo != 0)) {
-            const bool act = todo != 0;
-            const int b0 = act ? __ffs(todo) - 1 : 0;
-            todo &= todo - 1;
-            uint32_t front = act ? (1u << b0) : 0u, seen = 0;
-            int par = -1, found = -1;
-            bool searching = act;
-            while (__any(searching)) {
-                const bool reach = searching && !((seen >> lane) & 1u) && (avail & front) != 0;
-                if (reach) par = __ffs(avail & front) - 1;
-                const uint32_t fresh = gballot(reach);
-                const uint32_t fresh_free = gballot(reach && mb < 0);
-                const uint32_t next = gballot(ml >= 0 && ((fresh >> (ml & (GS - 1))) & 1u));
-                seen |= fresh;
-                if (searching) {
-                    if (fresh_free) { found = __ffs(fresh_free) - 1; searching = false; }
-                    else if (next == 0) searching = false;
-                    else front = next;
-                }
-            }
-            int cur = found;       // walk back: every list on the path takes the bank it was reached through
-            while (__any(cur >= 0)) {
-                const bool a = cur >= 0;
-                const int cl = a ? cur : 0;
-                const int b = __shfl(par, cl, GS) & (GS - 1);
-                const int prev = __shfl(ml, b, GS);
-                if (a) {
-                    if (lane == cl) mb = b;
-                    if (lane == b) ml = cl;
-                    cur = b == b0 ? -1 : prev;
-                }
-            }
-        }
+        match.run(avail, rounds);
         // lists without a bank: an empty place if one is left, on a bank nobody reads (there are as many free banks as
         // lists without one)
-        int wb = -1;
-        {
-            const bool spend = mb < 0 && wild > 0;
-            const uint32_t spenders = gballot(spend);
-            uint32_t fb = gballot(ml < 0);
+        const bool spend = match.mb < 0 && wild > 0;
+        int wb = 0;
+        if (__any(spend)) {
+            const uint32_t spenders = match.ballot(spend);
+            uint32_t fb = match.ballot(match.ml < 0);
             if (spend) {
                 for (int q = __popc(spenders & ((1u << lane) - 1u)); q > 0; --q) fb &= fb - 1;
-                wb = __ffs(fb) - 1;
+                wb = __ffs((int)fb) - 1;
                 --wild;
             }
         }
-        // the others double up: least loaded reachable bank, then the fullest
-        int myload = ml >= 0 ? 1 : 0;
-        uint32_t left = gballot(mb < 0 && wb < 0);
-        while (__any(left != 0)) {
-            const bool a = left != 0;
-            const int l = a ? __ffs(left) - 1 : 0;
-            left &= left - 1;
-            const uint32_t av = (uint32_t)__shfl((int)avail, l, GS);
-            int key = (a && ((av >> lane) & 1u)) ? (((255 - myload) << 17) | (mydeg << 5) | lane) : -1;
-#pragma unroll
-            for (int o = GS / 2; o > 0; o >>= 1) key = max(key, __shfl_xor(key, o, GS));
-            if (a && key >= 0) {
-                const int bb = key & (GS - 1);
-                if (lane == l) mb = bb;
-                if (lane == bb) ++myload;
-            }
-        }
-        if (wb >= 0) {             // an empty place: the zero word of the free bank, no weight
-            lab[at(s)] = (uint16_t)(zero_label + (uint32_t)wb);
-            if (slot) slot[at(s)] = PAD_SLOT;
-            if (pos) rk[at(s)] = PAD_SLOT;
+        const int mb = match.double_up(avail, match.mb < 0 && !spend, deg0[gl], cap - s);
+        if (spend) {               // the zero word of the free bank
+            ord[gl][lane][s] = (uint8_t)(128 + wb);
         } else {                   // my next unplaced entry in that bank
-            const int pick = mine[ends[mb] - cnt[mb]];
-            if (--cnt[mb] == 0) avail &= ~(1u << mb);
-            lab[at(s)] = (uint16_t)label_of(my[pick]);
-            if (slot) slot[at(s)] = my[pick];
-            if (pos) rk[at(s)] = pos[my[pick]] - ent_base[wg];
+            ord[gl][lane][s] = (uint8_t)Lists::take(lists[gl][lane], mb, avail);
+            atomicSub(&deg0[gl][mb], 1);
         }
-        mydeg -= myload;
+    }
+    // out, several places' loads in flight together
+#pragma unroll 4
+    for (int s = 0; s < cap; ++s) {
+        const int pick = ord[gl][lane][s];
+        const bool real = pick < 128;
+        const uint32_t e = real ? my[pick] : 0u;
+        lab[at(s)] = real ? (uint16_t)label_of(e) : (uint16_t)(zero_label + (uint32_t)(pick - 128));
+        if (slot) slot[at(s)] = real ? e : PAD_SLOT;
+        if (pos) rk[at(s)] = real ? pos[e] - ent_base[wg] : PAD_SLOT;
     }
 }
 
@@ -1347,9 +1294,9 @@ static usl_status lf_build_t(usl_ctx* c, const int32_t* idx, int set, const Cut&
     uint32_t* ent_base = n_ov + nwg;                 // [nwg + 1]
     uint32_t* n_ent = ent_base + nwg + 1;            // [nwg]
     const unsigned chunks = (unsigned)((cut.vd + CHUNK - 1) / CHUNK);
-    int splits = (int)((size_t)c->num_cu / ((size_t)nwin * chunks));
+    int splits = (int)((size_t)2 * c->num_cu / ((size_t)nwin * chunks));
     splits = splits < 1 ? 1 : splits > 16 ? 16 : splits;
-    const dim3 grid((unsigned)(nwin * splits), chunks);
+    const dim3 grid((unsigned)((nwin * splits + 7) / 8 * 8), chunks);
     const size_t lds = (size_t)(cut.vd < CHUNK ? cut.vd : CHUNK) * 4;
     USL_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(k_lf_count), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     USL_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(k_lf_fill), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));

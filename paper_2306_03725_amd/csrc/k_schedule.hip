@@ -11,17 +11,14 @@
 // A step costs as many LDS cycles as its fullest bank holds lanes, so what counts is the number of steps with
 // a collision, not the number of collisions: banks that the group's 32*k slots over-subscribe must collide
 // somewhere, and the aim is to gather those collisions in few steps.  The order is therefore built step by
-// step as a sequence of bipartite matchings between the 32 labels and the 32 banks (over the slots not used
-// yet): a few rounds of proposals match most labels, augmenting paths (breadth-first, one per bank still
-// free) complete the matching, and the labels that cannot be matched -- their banks are all taken -- double
-// up on the least loaded bank they can reach.  One half-wavefront works on one group: lane i is label i and
-// also bank i, all state is in registers and moves by ballots and shuffles; only a label's own bank list and
-// the proposal slots live in LDS.  The result is a deterministic function of idx.  Any outcome is a valid
-// permutation: it changes speed, never results.  (A local search on the sum of squared bank counts, used
-// before, spread the unavoidable collisions over all steps: 2.0 cycles per step against 1.5 now.)
+// step as a sequence of bipartite matchings between the 32 labels and the 32 banks over the slots not used yet
+// (k_matching.h); the labels that cannot be matched -- their banks are all taken -- double up.  One half-wavefront
+// works on one group: lane i is label i and also bank i.  Any outcome is a valid permutation: it changes speed, never
+// results.  (A local search on the sum of squared bank counts, used before, spread the unavoidable collisions over all
+// steps: 2.0 cycles per step against 1.5 now.)
 #include <stdlib.h>
 
-#include "usl_internal.h"
+#include "k_matching.h"
 
 namespace {
 
@@ -32,119 +29,25 @@ template <int K, int GS>
 __global__ void __launch_bounds__(SCHED_NT)
 k_schedule(const int32_t* __restrict__ idx, int64_t m, int k, int shift, int rounds, uint8_t* __restrict__ perm) {
     constexpr int G = SCHED_NT / GS;
-    constexpr uint32_t ALL = GS == 32 ? 0xFFFFFFFFu : (1u << (GS & 31)) - 1u;
-    // per label (rows padded by 4 bytes: lanes of a group then hit different LDS banks)
-    __shared__ uint8_t slots[G][GS][K + 4];   // first the bank of every slot, then my slots sorted by bank
-    __shared__ __align__(16) uint8_t ord[G][GS][K + 4];     // slot read at step s
-    __shared__ uint8_t left_in[G][GS][GS + 4];    // unused slots of mine per bank
-    __shared__ uint8_t end_of[G][GS][GS + 4];     // where bank b's slots end in the sorted list
-    __shared__ int deg0[G][GS];
-    __shared__ int win[G][GS];
+    typedef usl_bank_lists<GS, K> Lists;
+    __shared__ typename Lists::Lane lists[G][GS];
+    __shared__ __align__(16) uint8_t ord[G][GS][K + 4];     // first the bank of every slot, then the slot read at step s
+    __shared__ int deg0[G][GS];                             // slots of the group that read a bank and are not used yet
+    __shared__ uint32_t win[G][GS];
     const int gl = threadIdx.x / GS, lane = threadIdx.x & (GS - 1);
-    const int hs = threadIdx.x & 63 & ~(GS - 1);        // where my group's bits sit in a wavefront ballot
     const int64_t j = (int64_t)blockIdx.x * SCHED_NT + (threadIdx.x & ~31) + usl_lane_of_position<GS>(threadIdx.x & 31);
     const bool valid = j < m;
     deg0[gl][lane] = 0;
-    for (int b = 0; b < GS; ++b) left_in[gl][lane][b] = 0;
     __syncthreads();
-    uint8_t* mine = slots[gl][lane];
-    uint8_t* cnt = left_in[gl][lane];
-    uint8_t* ends = end_of[gl][lane];
-    for (int t = 0; t < k; ++t) {
-        const int b = valid ? ((idx[j * k + t] >> shift) & (GS - 1)) : ((lane + t) & (GS - 1));
-        mine[t] = (uint8_t)b;
-        ++cnt[b];
-        atomicAdd(&deg0[gl][b], 1);
-    }
-    uint32_t avail = 0;           // banks my unused slots read
-    {   // counting sort of my slots by bank, in place through ord (free until the first step)
-        int run = 0;
-        for (int b = 0; b < GS; ++b) { run += cnt[b]; ends[b] = (uint8_t)run; if (cnt[b]) avail |= 1u << b; }
-        uint8_t* tmp = ord[gl][lane];
-        for (int t = 0; t < k; ++t) tmp[t] = mine[t];
-        for (int t = k - 1; t >= 0; --t) { const int b = tmp[t]; ends[b] = (uint8_t)(ends[b] - 1); mine[ends[b]] = (uint8_t)t; }
-        for (int b = 0; b < GS; ++b) ends[b] = (uint8_t)(ends[b] + cnt[b]);   // back from starts to ends
-    }
+    uint32_t avail = Lists::build(lists[gl][lane], ord[gl][lane], k, deg0[gl],
+                                  [&](int t) { return valid ? ((idx[j * k + t] >> shift) & (GS - 1)) : ((lane + t) & (GS - 1)); });
     __syncthreads();
-    auto gballot = [&](bool p) -> uint32_t { return (uint32_t)(__ballot(p) >> hs) & ALL; };
-    volatile int* gwin = win[gl];
-    // bank role
-    int mydeg = deg0[gl][lane];   // slots of the group that read bank `lane` and are not used yet
+    usl_matching<GS> match(win[gl], lane);
     for (int s = 0; s < k; ++s) {
-        int mb = -1;              // label role: my bank at this step
-        int ml = -1;              // bank role: the label that reads me at this step
-        for (int r = 0; r < rounds; ++r) {
-            const uint32_t freeb = gballot(ml < 0);
-            gwin[lane] = 255;
-            int prop = -1;
-            const uint32_t cand = mb < 0 ? (avail & freeb) : 0u;
-            if (cand) {           // first candidate bank at or after a lane- and round-dependent start
-                const int sh = (lane + 7 * r) & (GS - 1);
-                const uint32_t rc = ((cand >> sh) | (cand << ((GS - sh) & (GS - 1)))) & ALL;
-                prop = (__ffs(rc) - 1 + sh) & (GS - 1);
-                atomicMin(&win[gl][prop], lane);
-            }
-            const int w = gwin[lane];
-            if (ml < 0 && w < GS) ml = w;
-            if (prop >= 0 && gwin[prop] == lane) mb = prop;
-        }
-        // augmenting paths from the banks still free
-        uint32_t todo = gballot(ml < 0 && mydeg > 0);
-        while (__any(todo != 0)) {
-            const bool act = todo != 0;
-            const int b0 = act ? __ffs(todo) - 1 : 0;
-            todo &= todo - 1;
-            uint32_t front = act ? (1u << b0) : 0u, seen = 0;
-            int par = -1, found = -1;
-            bool searching = act;
-            while (__any(searching)) {
-                const bool reach = searching && !((seen >> lane) & 1u) && (avail & front) != 0;
-                if (reach) par = __ffs(avail & front) - 1;
-                const uint32_t fresh = gballot(reach);
-                const uint32_t fresh_free = gballot(reach && mb < 0);
-                const uint32_t next = gballot(ml >= 0 && ((fresh >> (ml & (GS - 1))) & 1u));
-                seen |= fresh;
-                if (searching) {
-                    if (fresh_free) { found = __ffs(fresh_free) - 1; searching = false; }
-                    else if (next == 0) searching = false;
-                    else front = next;
-                }
-            }
-            int cur = found;      // walk back: every label on the path takes the bank it was reached through
-            while (__any(cur >= 0)) {
-                const bool a = cur >= 0;
-                const int cl = a ? cur : 0;
-                const int b = __shfl(par, cl, GS) & (GS - 1);
-                const int prev = __shfl(ml, b, GS);
-                if (a) {
-                    if (lane == cl) mb = b;
-                    if (lane == b) ml = cl;
-                    cur = b == b0 ? -1 : prev;
-                }
-            }
-        }
-        // labels without a bank of their own double up: least loaded reachable bank, then the fullest
-        int myload = ml >= 0 ? 1 : 0;
-        uint32_t left = gballot(mb < 0);
-        while (__any(left != 0)) {
-            const bool a = left != 0;
-            const int l = a ? __ffs(left) - 1 : 0;
-            left &= left - 1;
-            const uint32_t av = (uint32_t)__shfl((int)avail, l, GS);
-            int key = (a && ((av >> lane) & 1u)) ? (((255 - myload) << 17) | (mydeg << 5) | lane) : -1;
-#pragma unroll
-            for (int o = GS / 2; o > 0; o >>= 1) key = max(key, __shfl_xor(key, o, GS));
-            if (a && key >= 0) {
-                const int bb = key & (GS - 1);
-                if (lane == l) mb = bb;
-                if (lane == bb) ++myload;
-            }
-        }
-        // my next unused slot in that bank (slots of a bank are used in rising slot number)
-        const int pick = mine[ends[mb] - cnt[mb]];
-        if (--cnt[mb] == 0) avail &= ~(1u << mb);
-        ord[gl][lane][s] = (uint8_t)pick;
-        mydeg -= myload;
+        match.run(avail, rounds);
+        const int mb = match.double_up(avail, match.mb < 0, deg0[gl], k - s);
+        ord[gl][lane][s] = (uint8_t)Lists::take(lists[gl][lane], mb, avail);
+        atomicSub(&deg0[gl][mb], 1);
     }
     if (valid) {   // steps past k: the padding slots
         for (int s = k; s < K; ++s) ord[gl][lane][s] = (uint8_t)s;
