@@ -25,6 +25,8 @@
 // per compute unit) for everything else; the gathers are therefore written out in assembly, four in flight.
 #include <stdlib.h>
 
+#include <type_traits>
+
 #include "k_matching.h"
 
 namespace {
@@ -1273,20 +1275,31 @@ static usl_status lf_build_t(usl_ctx* c, const int32_t* idx, int set, const Cut&
     const int nwin = cut.nwin, nfb = cut.nfb, nwg = nwin * nfb;
     const size_t nbins = (size_t)nwin * cut.vd;
     const int Q = set == 1 ? both_q(c) : 1;
-    USL_TRY(usl_reserve(c, (void**)&L.count, &L.count_cap, nbins * 4));
-    USL_TRY(usl_reserve(c, (void**)&L.taken, &L.taken_cap, nbins * 4));
-    USL_TRY(usl_reserve(c, (void**)&L.where, &L.where_cap, nbins * 4));
-    USL_TRY(usl_reserve(c, (void**)&L.feat, &L.feat_cap, (size_t)nwg * 2 * NT * 2));
-    USL_TRY(usl_reserve(c, (void**)&L.caps, &L.caps_cap, (size_t)nwg * (NT / 64) * 4));
-    USL_TRY(usl_reserve(c, (void**)&L.ov_base, &L.ov_base_cap, ((size_t)nwg * 4 + 2) * 4));
-    USL_TRY(usl_reserve(c, (void**)&L.ovr, &L.ovr_cap, (size_t)nwg * 2 * NT * 4));
-    USL_TRY(usl_reserve(c, (void**)&L.lab, &L.lab_cap, (size_t)nwg * KT * NT * 2));
-    USL_TRY(usl_reserve(c, (void**)&L.slot, &L.slot_cap, (set == 1 ? N : (size_t)nwg * KT * NT) * 4));   // by place, or by list
-    USL_TRY(usl_reserve(c, (void**)&L.ent, &L.ent_cap, N * 4));
-    USL_TRY(usl_reserve(c, (void**)&L.ovoff, &L.ovoff_cap, nbins * 4));
-    USL_TRY(usl_reserve(c, (void**)&L.ov, &L.ov_cap, (N + nbins) * sizeof(OvEntry)));   // worst case, + an empty place per list
-    if (set == 1)   // pos [N], rk [nwg][KT][NT], ovrk [N + nbins], the counts of the runs [nwg][nseg]
-        USL_TRY(usl_reserve(c, (void**)&L.pos, &L.pos_cap, (N + (size_t)nwg * KT * NT + N + nbins + (size_t)nwg * lf_runs(c, cut)) * 4));
+    {   // all of it in one allocation: thirteen of them were a third of the first call's time on a small layer
+        size_t total = 0;
+        auto share = [&](auto** to, size_t bytes) {   // twice: first the sizes, then the addresses
+            *to = reinterpret_cast<std::remove_reference_t<decltype(*to)>>(static_cast<char*>(L.mem) + total);
+            total += (bytes + 255) / 256 * 256;
+        };
+        for (int turn = 0; turn < 2; ++turn) {
+            total = 0;
+            share(&L.count, nbins * 4);
+            share(&L.taken, nbins * 4);
+            share(&L.where, nbins * 4);
+            share(&L.ovoff, nbins * 4);
+            share(&L.feat, (size_t)nwg * 2 * NT * 2);
+            share(&L.caps, (size_t)nwg * (NT / 64) * 4);
+            share(&L.ov_base, ((size_t)nwg * 4 + 2) * 4);
+            share(&L.ovr, (size_t)nwg * 2 * NT * 4);
+            share(&L.lab, (size_t)nwg * KT * NT * 2);
+            share(&L.slot, (set == 1 ? N : (size_t)nwg * KT * NT) * 4);   // by place, or by list
+            share(&L.ent, N * 4);
+            share(&L.ov, (N + nbins) * sizeof(OvEntry));   // worst case, + an empty place per list
+            if (set == 1)   // pos [N], rk [nwg][KT][NT], ovrk [N + nbins], the counts of the runs [nwg][nseg]
+                share(&L.pos, (N + (size_t)nwg * KT * NT + N + nbins + (size_t)nwg * lf_runs(c, cut)) * 4);
+            if (turn == 0) USL_TRY(usl_reserve(c, &L.mem, &L.mem_cap, total));
+        }
+    }
     int rounds = 3;                // of proposals per step of the bank-aware order; 0 = lists stay as filled
     if (const char* e = getenv("USL_TUNE_ROUNDS")) rounds = atoi(e);
     uint32_t* ov_base = L.ov_base;                   // [nwg + 1]
@@ -1301,8 +1314,7 @@ static usl_status lf_build_t(usl_ctx* c, const int32_t* idx, int set, const Cut&
     USL_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(k_lf_count), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     USL_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(k_lf_fill), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     const dim3 fillg(c->num_cu * 4), fillb(256);
-    hipLaunchKernelGGL(k_fill_u32, fillg, fillb, 0, c->stream, L.count, nbins, 0u);
-    hipLaunchKernelGGL(k_fill_u32, fillg, fillb, 0, c->stream, L.taken, nbins, 0u);
+    hipLaunchKernelGGL(k_fill_u32, fillg, fillb, 0, c->stream, L.count, (size_t)(L.taken - L.count) + nbins, 0u);   // both: neighbours
     hipLaunchKernelGGL(k_lf_count, grid, dim3(NT), lds, c->stream, idx, c->m, c->k, c->d, cut, splits, L.count);
     hipLaunchKernelGGL(k_lf_plan<KT>, dim3((unsigned)nwg), dim3(NT), 0, c->stream, L.count, cut.vd, nfb, cut.fpb, L.where, L.ovoff,
                        L.feat, L.caps, n_ent, n_ov, L.ovr);

@@ -38,8 +38,7 @@ extern "C" usl_status usl_destroy(usl_ctx* c) {
         for (void* p : bufs)
             if (p) (void)hipFree(p);
         for (auto& L : c->lf) {
-            void* lists[] = {L.count, L.taken, L.where, L.feat, L.caps, L.ov_base, L.ovr, L.lab, L.slot, L.ent, L.ovoff,
-                             L.ov, L.stage, L.pos, L.partial};
+            void* lists[] = {L.mem, L.stage, L.partial};
             for (void* p : lists)
                 if (p) (void)hipFree(p);
         }

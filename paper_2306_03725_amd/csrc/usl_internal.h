@@ -71,20 +71,21 @@ struct usl_ctx {
     // windows of up to 32768 labels, for usl_backward_input; [1] lists of 36 slots from windows of half that length, for
     // the kernel of usl_train_step that computes the weight gradient from the same gathers
     struct usl_lf {
-        uint32_t* count;      size_t count_cap;    // [nwin*d] list lengths
-        uint32_t* taken;      size_t taken_cap;    // [nwin*d] positions handed out while filling
-        uint32_t* where;      size_t where_cap;    // [nwin*d] where a feature's list starts among its workgroup's entries
-        uint16_t* feat;       size_t feat_cap;     // [wg][2][1024] feature of a lane's list
-        uint32_t* caps;       size_t caps_cap;     // [wg][16] slots the wavefronts visit
-        uint32_t* ov_base;    size_t ov_base_cap;  // [wg+1] start of a workgroup's overflow entries, [wg] their number; the same two for all its entries
-        uint32_t* ovr;        size_t ovr_cap;      // [wg][2][1024] a lane's lists' share of the overflow entries held in LDS
-        uint16_t* lab;        size_t lab_cap;      // [wg][slots][1024] label within the window
-        uint32_t* slot;       size_t slot_cap;     // flat slot j*k+t (where the weight lives): [0] [wg][slots][1024]; [1] [m*k], by place
-        uint32_t* ent;        size_t ent_cap;      // [m*k] flat slots grouped by (workgroup, feature), before the bank-aware order
-        uint32_t* ovoff;      size_t ovoff_cap;    // [nwin*d] where a list's overflow starts in its workgroup's
-        void* ov;             size_t ov_cap;       // overflow entries
+        void* mem;            size_t mem_cap;      // holds count .. pos
+        uint32_t* count;                           // [nwin*d] list lengths
+        uint32_t* taken;                           // [nwin*d] positions handed out while filling
+        uint32_t* where;                           // [nwin*d] where a feature's list starts among its workgroup's entries
+        uint16_t* feat;                            // [wg][2][1024] feature of a lane's list
+        uint32_t* caps;                            // [wg][16] slots the wavefronts visit
+        uint32_t* ov_base;                         // [wg+1] start of a workgroup's overflow entries, [wg] their number; the same two for all its entries
+        uint32_t* ovr;                             // [wg][2][1024] a lane's lists' share of the overflow entries held in LDS
+        uint16_t* lab;                             // [wg][slots][1024] label within the window
+        uint32_t* slot;                            // flat slot j*k+t (where the weight lives): [0] [wg][slots][1024]; [1] [m*k], by place
+        uint32_t* ent;                             // [m*k] flat slots grouped by (workgroup, feature), before the bank-aware order
+        uint32_t* ovoff;                           // [nwin*d] where a list's overflow starts in its workgroup's
+        void* ov;                                  // overflow entries
         float* stage;         size_t stage_cap;    // [1] only: the weight gradient in list order, [wg][slots][1024], then one per overflow entry
-        uint32_t* pos;        size_t pos_cap;      // [1] only: [m*k] where a slot's weight gradient is in stage
+        uint32_t* pos;                             // [1] only: [m*k] where a slot's weight gradient is in stage
         float* partial;       size_t partial_cap;  // [nwin][rows of a pass][d]
         const int32_t* built_for;                  // idx pointer the lists were built from (NULL = stale)
     } lf[2];
