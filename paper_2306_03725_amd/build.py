@@ -64,7 +64,24 @@ def scan_listing_for_untracked_load(lines, lst="listing"):
                 note += " " + lines[j]
                 j += 1
             blocks.append((h, end, note))
+
+        def parents(header):   # the loops around the loop of this header, outside in
+            head = next(b for b in blocks if lines[b[0]].startswith(".L" + header + ":"))
+            return re.findall(r"Parent Loop (BB\d+_\d+) Depth=", head[2])
+
+        def inside(block, header):
+            if lines[block[0]].startswith(".L" + header + ":"):
+                return True
+            own = re.search(r"in Loop: Header=(BB\d+_\d+)", block[2])
+            up = [own.group(1)] + parents(own.group(1)) if own else re.findall(r"Parent Loop (BB\d+_\d+) Depth=", block[2])
+            return header in up
+
         loads = [i for i in range(f0, f1) if "ASMSTART" in lines[i - 1] and re.search(r"global_load_dword v\d+, (v\d+, s\[|v\[\d+:\d+\], off)", lines[i])]
+        if not loads and "k_both_lds" in lines[f0]:   # its warm-up loads are plain ones, which the compiler keeps track of
+            inner = [i for b in blocks if re.search(r"Depth=[2-9]", b[2]) for i in range(b[0], b[1]) if "scratch_load" in lines[i].split(";")[0]]
+            if inner:
+                raise RuntimeError("check_untracked_load: register reloads in the passes of k_both_lds (%s lines %s)" % (lst, [i + 1 for i in inner]))
+            continue
         if len(loads) < 1:
             raise RuntimeError("check_untracked_load: no warm-up load found in %s" % lines[f0])
         for ld in loads:
@@ -73,16 +90,14 @@ def scan_listing_for_untracked_load(lines, lst="listing"):
             m_ = re.search(r"Header=(BB\d+_\d+) Depth=(\d+)", mine[2])
             if not m_:
                 raise RuntimeError("check_untracked_load: the warm-up load is not inside a loop")
-            header = m_.group(1)
-            if m_.group(2) != "1":   # in a loop inside the loop over the passes: the outermost one is meant
-                inner = next(b for b in blocks if lines[b[0]].startswith("." + "L" + header + ":"))
-                m_ = re.search(r"Parent Loop (BB\d+_\d+) Depth=1", inner[2])
-                if not m_:
-                    raise RuntimeError("check_untracked_load: no outermost loop found around the warm-up load")
-                header = m_.group(1)
-            # the loop's blocks: from its header to the last block that names it (loops are laid out in one piece)
-            first = next(b[0] for b in blocks if lines[b[0]].startswith("." + "L" + header + ":"))
-            last = max(b[1] for b in blocks if ("Header=%s " % header) in b[2] + " " or ("Parent Loop %s " % header) in b[2] + " ")
+            # the loops around it, inside out; the loop over the passes is the innermost with a barrier (the loads stand in a
+            # loop over lines, and the passes in a loop over windows)
+            around = [m_.group(1)] + parents(m_.group(1))[::-1]
+            for header in around:
+                span = [b for b in blocks if inside(b, header)]
+                first, last = span[0][0], max(b[1] for b in span)   # (loops are laid out in one piece)
+                if any("s_barrier" in l for l in lines[first:last]):
+                    break
             in_loop = [b for b in blocks if first <= b[0] < last]
 
             def mentions(text):

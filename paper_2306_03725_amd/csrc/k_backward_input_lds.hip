@@ -793,7 +793,7 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
            const uint16_t* __restrict__ feat, const uint32_t* __restrict__ caps, const uint32_t* __restrict__ ov_base,
            const OvEntry* __restrict__ ov, const uint32_t* __restrict__ ovr, float* __restrict__ partial,
            const uint32_t* __restrict__ rk, const uint32_t* __restrict__ ovrk, const uint32_t* __restrict__ ent_base,
-           float* __restrict__ stage, float* __restrict__ ovgw, int parts, int rows_per_part, size_t part_stride, size_t ov_stride,
+           float* __restrict__ stage, float* __restrict__ ovgw, int chains, int parts, int rows_per_part, size_t part_stride, size_t ov_stride,
            const uint32_t* __restrict__ gate, int accumulate, const uint32_t* __restrict__ stale) {
     constexpr int KT = Q == 4 ? KT_BOTH4 : KT_BOTH;   // (with four instances 36 slots spill)
     constexpr uint32_t ZL = BothLayout<Q>::zero_label, U = 4 * Q;   // U: bytes of a unit
@@ -803,8 +803,8 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
     // workgroup b runs on XCD b % 8: an XCD takes an eighth of the tiles (window, part, feature block) in this order, so that
     // the blocks of a window, which read the same slices of g, and its parts, which read the same lists, share an L2
     const int per_xcd = (int)gridDim.x / 8, tile = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
-    const int w = tile / (parts * nfb), part = tile / nfb % parts, fb = tile % nfb;
-    if (w >= cut.nwin) return;
+    const int chain = tile / (parts * nfb), part = tile / nfb % parts, fb = tile % nfb;
+    if (chain >= chains) return;
     const int i_begin = part * rows_per_part, i_end = min(rows, i_begin + rows_per_part);
     stage += (size_t)part * part_stride;
     ovgw += (size_t)part * ov_stride;
@@ -812,8 +812,14 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
         for (size_t v = threadIdx.x; v < (size_t)max(i_end - i_begin, 0) * dp; v += NT) partial[(size_t)i_begin * dp + v] = __uint_as_float(0x7FC00000u);
         return;
     }
+    // One window after the other: windows chain, chain + chains, ...  The sums of the later ones are added to the first one's
+    // (every value by the lane that wrote it), so that there is one set of partial sums for each chain, not for each window.
+#pragma unroll 1
+    for (int w = chain; w < cut.nwin; w += chains) {
+    uint32_t lane = threadIdx.x;   // taken afresh for each window: nothing computed from it lives through the passes
+    asm volatile("" : "+v"(lane));
     const size_t wg = (size_t)__builtin_amdgcn_readfirstlane(w * nfb + fb);
-    const uint32_t cw = caps[wg * (NT / 64) + (threadIdx.x >> 6)];
+    const uint32_t cw = caps[wg * (NT / 64) + (lane >> 6)];
     const int acap = __builtin_amdgcn_readfirstlane((int)(cw & 0xFFu)), bcap = __builtin_amdgcn_readfirstlane((int)(cw >> 8));
     uint32_t pk[KT / 2];
     float wt[KT], gw[KT];
@@ -829,7 +835,7 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
     for (uint32_t c0 = 0; c0 < n_ent; c0 += CH) {
         const uint32_t n = min(CH, n_ent - c0);
         __syncthreads();
-        for (uint32_t r0 = threadIdx.x; r0 < n; r0 += 8 * NT) {
+        for (uint32_t r0 = lane; r0 < n; r0 += 8 * NT) {
             uint32_t sl[8];
             float v[8];
 #pragma unroll
@@ -856,7 +862,7 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
     {
         uint32_t lb[KT];
 #pragma unroll
-        for (int t = 0; t < KT; ++t) lb[t] = (lab + wg * KT * NT)[(uint32_t)t * NT + threadIdx.x];
+        for (int t = 0; t < KT; ++t) lb[t] = (lab + wg * KT * NT)[(uint32_t)t * NT + lane];
 #pragma unroll
         for (int t = 0; t < KT; ++t) {
             const bool used = t / 4 * 4 < acap || t / 4 * 4 >= KT - bcap;
@@ -882,29 +888,30 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
     uint32_t* ovr_b = ovr_a + NT;
     float* ov_sum = reinterpret_cast<float*>(ovr_b + NT);                 // [NEAR2]
     {
-        const uint32_t fa = feat[(wg * 2 + 0) * NT + threadIdx.x], fbb = feat[(wg * 2 + 1) * NT + threadIdx.x];
-        feat_of[threadIdx.x] = fa | fbb << 16;
+        const uint32_t fa = feat[(wg * 2 + 0) * NT + lane], fbb = feat[(wg * 2 + 1) * NT + lane];
+        feat_of[lane] = fa | fbb << 16;
         // Q = 4: where the features' activations are (a list of a feature that does not exist reads some place, and is empty)
-        if (Q == 4) feat_of[NT + threadIdx.x] = cut.S == 1 ? fa | fbb << 16 : fa % (uint32_t)d | fbb % (uint32_t)d << 16;
+        if (Q == 4) feat_of[NT + lane] = cut.S == 1 ? fa | fbb << 16 : fa % (uint32_t)d | fbb % (uint32_t)d << 16;
     }
-    if (threadIdx.x < NEAR2) {
+    if (lane < NEAR2) {
         uint2 e = make_uint2(ZL * U, 0u);
-        if (threadIdx.x < ov_n) {
-            const OvEntry o = ov[(size_t)ov0 + threadIdx.x];
+        if (lane < ov_n) {
+            const OvEntry o = ov[(size_t)ov0 + lane];
             e = make_uint2((uint32_t)o.label * U, o.slot == PAD_SLOT ? 0u : __float_as_uint(usl_load_f32<TS>(W, (size_t)o.slot)));
         }
-        ov_near[threadIdx.x] = e;
-        ov_sum[threadIdx.x] = 0.f;
+        ov_near[lane] = e;
+        ov_sum[lane] = 0.f;
     }
-    ovr_a[threadIdx.x] = ovr[(wg * 2 + 0) * NT + threadIdx.x];
-    ovr_b[threadIdx.x] = ovr[(wg * 2 + 1) * NT + threadIdx.x];
-    if (threadIdx.x < 32 * Q) reinterpret_cast<uint32_t*>(lds_raw)[ZL * Q + threadIdx.x] = 0u;   // what empty places read
-    for (uint32_t q = NEAR2 + threadIdx.x; q < ov_n; q += NT) ovgw[(size_t)ov0 + q] = 0.f;   // entry q is lane q % NT's
+    ovr_a[lane] = ovr[(wg * 2 + 0) * NT + lane];
+    ovr_b[lane] = ovr[(wg * 2 + 1) * NT + lane];
+    if (lane < 32 * Q) reinterpret_cast<uint32_t*>(lds_raw)[ZL * Q + lane] = 0u;   // what empty places read
+    for (uint32_t q = NEAR2 + lane; q < ov_n; q += NT) ovgw[(size_t)ov0 + q] = 0.f;   // entry q is lane q % NT's
     const int nl = (int)min((int64_t)cut.wl, m - (int64_t)w * cut.wl);   // labels of this window (the last one may be short)
     const int nv = nl / 4;                                               // whole 16-byte pieces of a row slice
     const int nf = min(cut.fpb, cut.vd - fb * cut.fpb);                            // features of this block that exist
     const int nx = cut.S > 1 ? d : nf;                                   // ... and activations
     const int lines = (nl * 4 + 127) / 128, per = (lines + nfb - 1) / nfb;   // 128-byte lines; this workgroup's share of the warm-up
+    const int plines = w >= chains && cut.S == 1 ? (nf * 4 + 127) / 128 : 0;   // ... and of its earlier sums (per instance)
     const int xlines = ((Q == 4 ? Q : 1) * nx * (int)sizeof(TS) + 127) / 128;    // 128-byte lines of the block's activations (per row of x)
     // the rest of a list (r = start | n << 16 in ov_near, n even), two entries in flight at a time
     auto more = [&](float (&acc)[Q], uint32_t r, const float (&xv)[Q]) {
@@ -928,12 +935,12 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
             }
         }
     };
-    // receives the L2 warm-up loads (issued from inline assembly, see k_bwi_lds; the build checks this kernel too)
-    uint32_t token = 0;
+    uint32_t token = 0;   // receives the L2 warm-up loads
     for (int i = i_begin; i < i_end; i += Q) {
         const int have = min(Q, i_end - i);                              // instances of this pass; the others read as zeros
         const char* grow = reinterpret_cast<const char*>(g + (size_t)w * cut.wl + (size_t)i * m);   // uniform
         const TS* xrow = Q == 4 ? x + (size_t)(i / Q) * x_stride + (size_t)fb * cut.fpb * Q : x + (size_t)i * x_stride + (size_t)fb * cut.fpb;
+        float* dst = partial + ((size_t)chain * rows + i) * dp + (size_t)fb * cut.fpb;   // (one block where S > 1)
         // The lane's number, taken afresh in each part of a pass: whatever is computed from it (addresses in LDS, offsets
         // of copies) is then computed there, in a few instructions, and not kept in a register of its own across the
         // gathers -- there are none to spare, and a value that is spilled comes back through a load whose wait also
@@ -1005,20 +1012,48 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
             xa[1] = have > 1 ? usl_load_f32<TS>(xbuf, (size_t)NF + (f & 0xFFFFu)) : 0.f;
             xb[1] = have > 1 ? usl_load_f32<TS>(xbuf, (size_t)NF + (f >> 16)) : 0.f;
         }
-        if (i + Q < i_end) {   // one load per 128-byte line of what the next pass reads: the window's workgroups share
-            // the lines of its slices of g, then come the block's own lines of x
+        // the earlier windows' sums, on their way during the gathers
+        float4 prior[Q / 2];
+#pragma unroll
+        for (int u = 0; u < Q / 2; ++u) prior[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        // One load per 128-byte line of what the next pass reads: the window's workgroups share the lines of its slices of g, then
+        // come the block's own lines of x and those of its earlier sums.  Exactly one in every wavefront (of any line, where
+        // there is none to warm up), so that the compiler's wait for `prior`, which is older, can leave it in flight: it comes
+        // from memory and takes longer than the gathers (waited for, it cost 130 of 1140 us at m = 500k, d = 32k, k = 32, b = 256).
+        {
             constexpr int XR = Q == 4 ? 1 : Q;
-            for (int j = (int)tid; j < Q * per + XR * xlines; j += NT) {   // (no divisions: every lane comes through here)
-                const bool of_g = j < Q * per;
-                const int jj = of_g ? j : j - Q * per, half = of_g ? per : xlines;
+            const char* line = grow;
+            auto item = [&](int j) {   // (no divisions: every lane comes through here)
+                const bool of_g = j < Q * per, of_p = j >= Q * per + XR * xlines;
+                const int jj = of_g ? j : of_p ? j - Q * per - XR * xlines : j - Q * per, half = of_g ? per : of_p ? plines : xlines;
                 int r = 0;
 #pragma unroll
                 for (int q = 1; q < Q; ++q) r += jj >= q * half ? 1 : 0;
                 const int c = (of_g ? fb * per : 0) + jj - r * half;
-                const char* line = (of_g ? grow + (size_t)m * 4 * (Q + r) : reinterpret_cast<const char*>(xrow + (Q == 4 ? x_stride : (size_t)(Q + r) * x_stride))) + (size_t)c * 128;
-                if (i + Q + r < i_end && (!of_g || c < lines))
-                    asm volatile("global_load_dword %0, %1, off" : "+v"(token) : "v"(line));
+                const char* at = (of_g   ? grow + (size_t)m * 4 * (Q + r)
+                                  : of_p ? reinterpret_cast<const char*>(dst + (size_t)(Q + r) * dp)
+                                         : reinterpret_cast<const char*>(xrow + (Q == 4 ? x_stride : (size_t)(Q + r) * x_stride))) + (size_t)c * 128;
+                return i + Q + r < i_end && (!of_g || c < lines) ? at : grow;
+            };
+            const int items = i + Q < i_end ? Q * per + XR * xlines + Q * plines : 0;
+            if (__builtin_amdgcn_readfirstlane((int)tid) < items && (int)tid < items) line = item((int)tid);
+            // (the last lines of more than NT, possible where one block is the whole layer, stay cold)
+        if (w >= chains) {
+            if (Q == 2 || cut.S == 1) {
+#pragma unroll
+                for (int u = 0; u < Q / 2; ++u) {
+                    const int v = (int)tid + u * NT;
+                    if (v < have * (NF / 4) && v % (NF / 4) * 4 < nf)
+                        prior[u] = reinterpret_cast<const float4*>(dst + (size_t)(v / (NF / 4)) * dp)[v % (NF / 4)];
+                }
+            } else if ((int)tid < d) {
+                float* p = &prior[0].x;
+#pragma unroll
+                for (int j = 0; j < Q; ++j)
+                    if (j < have) p[j] = dst[(size_t)j * dp + tid];
             }
+        }
+            token = *reinterpret_cast<const uint32_t*>(line);
         }
         float acc_a[Q] = {}, acc_b[Q] = {};
         int ac = acap, bc = bcap;   // compared afresh in every pass, see k_bwi_lds
@@ -1084,20 +1119,24 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
         }
         __syncthreads();
         if (Q == 2 || cut.S == 1) {   // the block's sums leave as contiguous runs (rows of dp floats, dp a multiple of 4)
-            float* dst = partial + ((size_t)w * rows + i) * dp + (size_t)fb * cut.fpb;
-            for (int v = (int)tid; v < have * (NF / 4); v += NT)
-                if (v % (NF / 4) * 4 < nf)
-                    reinterpret_cast<float4*>(dst + (size_t)(v / (NF / 4)) * dp)[v % (NF / 4)] = reinterpret_cast<const float4*>(outbuf)[v];
-        } else {                      // ... those of the window's runs added up
-            float* dst = partial + ((size_t)w * rows + i) * dp;
-            for (int v = (int)tid; v < have * NT; v += NT) {
-                const int j = v / NT, c = v % NT;   // d <= NT where there is more than one run
-                if (c < d) {
-                    float t = 0.f;
-                    for (int r = 0; r < cut.S; ++r) t += outbuf[j * NF + r * d + c];
-                    dst[(size_t)j * dp + c] = t;
+#pragma unroll
+            for (int u = 0; u < Q / 2; ++u) {
+                const int v = (int)tid + u * NT;
+                if (v < have * (NF / 4) && v % (NF / 4) * 4 < nf) {
+                    const float4 t = reinterpret_cast<const float4*>(outbuf)[v];
+                    reinterpret_cast<float4*>(dst + (size_t)(v / (NF / 4)) * dp)[v % (NF / 4)] =
+                        make_float4(prior[u].x + t.x, prior[u].y + t.y, prior[u].z + t.z, prior[u].w + t.w);
                 }
             }
+        } else if ((int)tid < d) {    // ... those of the window's runs added up (d <= NT where there is more than one run)
+            const float* p = &prior[0].x;
+#pragma unroll
+            for (int j = 0; j < Q; ++j)
+                if (j < have) {
+                    float t = 0.f;
+                    for (int r = 0; r < cut.S; ++r) t += outbuf[j * NF + r * d + tid];
+                    dst[(size_t)j * dp + tid] = p[j] + t;
+                }
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1127,9 +1166,10 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
         for (uint32_t r = threadIdx.x; r < min(CH, n_ent - c0); r += NT)   // a later pass over the batch adds to the earlier ones
             stage[(size_t)e0 + c0 + r] = accumulate ? stage[(size_t)e0 + c0 + r] + perm[r] : perm[r];
     }
+    }
 }
 
-// grad_x[i][c] = sum over the windows of partial[w][i][c], i < rows; a row of partial is dp floats (d rounded up to a
+// grad_x[i][c] = sum over the windows (chains of them, in the kernel for both products) of partial[w][i][c], i < rows; a row of partial is dp floats (d rounded up to a
 // multiple of 4).  BOTH only names the kernel after the one whose sums it adds, so that a profile tells the two apart.
 // vec: rows of grad_x are 16-byte aligned too.
 template <bool BOTH>
@@ -1357,11 +1397,11 @@ static usl_status lf_ready(usl_ctx* c, const int32_t* idx, int set, const Cut& c
     return set == 1 && c->print_done ? USL_OK : usl_idx_fingerprint(c, idx, 0);
 }
 
-// Instances per pass over the batch: every pass loads the lists and the weights anew, and its partial sums are nwin * G * d
+// Instances per pass over the batch: every pass loads the lists and the weights anew, and its partial sums are sets * G * d
 // floats; as many as the allowance for partial sums admits, sized once for max_b, a multiple of `step`.
-static int pass_rows(const usl_ctx* c, const Cut& cut, int step) {
-    int G = (int)(lf_partial_bytes() / ((size_t)cut.nwin * padded_d(c) * 4) > (size_t)c->max_b
-                      ? (size_t)c->max_b : lf_partial_bytes() / ((size_t)cut.nwin * padded_d(c) * 4));
+static int pass_rows(const usl_ctx* c, int sets, int step) {
+    const size_t most = lf_partial_bytes() / ((size_t)sets * padded_d(c) * 4);
+    int G = (int)(most > (size_t)c->max_b ? (size_t)c->max_b : most);
     if (const char* e = getenv("USL_TUNE_BWI_ROWS")) G = atoi(e) < G ? atoi(e) : G;   // tests: several passes on a small layer
     G = G < 64 ? 64 : G;
     G = G > c->max_b ? c->max_b : G;
@@ -1369,7 +1409,7 @@ static int pass_rows(const usl_ctx* c, const Cut& cut, int step) {
     return G < c->max_b && G > step ? G / step * step : G;
 }
 
-static void lf_reduce(usl_ctx* c, const float* partial, const Cut& cut, int rows, bool both, float* grad_x, const uint32_t* gate) {
+static void lf_reduce(usl_ctx* c, const float* partial, int sets, int rows, bool both, float* grad_x, const uint32_t* gate) {
     const int dp = padded_d(c);
     const size_t n4 = (size_t)rows * dp / 4;
     const bool vec = dp == c->d && (uintptr_t)grad_x % 16 == 0;
@@ -1378,10 +1418,10 @@ static void lf_reduce(usl_ctx* c, const float* partial, const Cut& cut, int rows
     if (blocks > (size_t)c->num_cu * 8) blocks = (size_t)c->num_cu * 8;
     if (both)
         hipLaunchKernelGGL(k_lf_reduce<true>, dim3((unsigned)blocks), dim3(256), 0, c->stream,
-                           reinterpret_cast<const float4*>(partial), cut.nwin, n4, c->d, dp, vec, grad_x, gate, stale);
+                           reinterpret_cast<const float4*>(partial), sets, n4, c->d, dp, vec, grad_x, gate, stale);
     else
         hipLaunchKernelGGL(k_lf_reduce<false>, dim3((unsigned)blocks), dim3(256), 0, c->stream,
-                           reinterpret_cast<const float4*>(partial), cut.nwin, n4, c->d, dp, vec, grad_x, gate, stale);
+                           reinterpret_cast<const float4*>(partial), sets, n4, c->d, dp, vec, grad_x, gate, stale);
 }
 
 // The one-product form needs its row buffer at LDS address 0 (a label's byte offset is the address); all need the LDS.
@@ -1401,7 +1441,7 @@ usl_status usl_bwi_lds_run(usl_ctx* c, const float* g, const int32_t* idx, const
     auto& L = c->lf[0];
     const Cut cut = bwi_cut(c);
     USL_TRY(lf_ready<KT_BWI>(c, idx, 0, cut));
-    const int G = pass_rows(c, cut, 1);
+    const int G = pass_rows(c, cut.nwin, 1);
     USL_TRY(usl_reserve(c, (void**)&L.partial, &L.partial_cap, (size_t)cut.nwin * G * padded_d(c) * 4));
     const unsigned grid = (unsigned)(((cut.nwin + 7) / 8) * 8 * cut.nfb);
     static bool checked[2] = {false, false};
@@ -1418,7 +1458,7 @@ usl_status usl_bwi_lds_run(usl_ctx* c, const float* g, const int32_t* idx, const
         if (c->storage == USL_F32) USL_BWI(float, 0);
         else USL_BWI(uint16_t, 1);
 #undef USL_BWI
-        lf_reduce(c, L.partial, cut, rows, false, grad_x + (size_t)i0 * c->d, gate);
+        lf_reduce(c, L.partial, cut.nwin, rows, false, grad_x + (size_t)i0 * c->d, gate);
     }
     return usl_check_launch(c, "backward_input (LDS form)");
 }
@@ -1441,6 +1481,13 @@ static int both_parts(const usl_ctx* c, const Cut& cut, int rows, int Q) {
     return best;
 }
 
+// Chains of windows in k_both_lds: as many as the compute units have room for, where there are more windows than that.
+static int both_chains(const usl_ctx* c, const Cut& cut) {
+    const int at_once = c->num_cu > cut.nfb ? c->num_cu / cut.nfb : 1;
+    const int rounds = (cut.nwin + at_once - 1) / at_once;
+    return (cut.nwin + rounds - 1) / rounds;
+}
+
 // grad_x[b][d] and the weight gradient from g[b][m] and x[b][d].  The weight gradient is left in the order of the lists:
 // slot f's is the sum over p < *parts of (*stage)[p * *part_stride + (*pos)[f]] (usl_launch_adam_staged takes it from
 // there); both arrays belong to the context and hold until the next call or a change of idx.  A stale idx (see usl_check)
@@ -1453,10 +1500,13 @@ usl_status usl_both_lds_run(usl_ctx* c, const float* g, const void* x, const int
     const size_t N = (size_t)c->m * c->k, nbins = (size_t)cut.nwin * cut.vd, rkn = (size_t)cut.nwin * cut.nfb * (Q == 4 ? KT_BOTH4 : KT_BOTH) * NT;
     if (Q == 4) USL_TRY(lf_ready<KT_BOTH4>(c, idx, 1, cut));
     else USL_TRY(lf_ready<KT_BOTH>(c, idx, 1, cut));
-    const int G = pass_rows(c, cut, Q);
+    const int chains_of_all = both_chains(c, cut);
+    const int G = pass_rows(c, chains_of_all, Q);
     const int parts = b <= G ? both_parts(c, cut, b, Q) : 1;
     const int most = c->max_b <= G ? both_parts(c, cut, c->max_b, Q) : 1;   // scratch for the largest batch too
-    USL_TRY(usl_reserve(c, (void**)&L.partial, &L.partial_cap, (size_t)cut.nwin * G * dp * 4));
+    const int chains = parts > 1 ? cut.nwin : chains_of_all;
+    USL_TRY(usl_reserve(c, (void**)&L.partial, &L.partial_cap, (size_t)(most > 1 ? cut.nwin : chains_of_all) * G * dp * 4));
+    if (chains > chains_of_all) USL_TRY(usl_reserve(c, (void**)&L.partial, &L.partial_cap, (size_t)chains * b * dp * 4));
     // per part: stage [N], the sums of the overflow entries beyond LDS [N + nbins]
     const size_t keep = (size_t)(parts > most ? parts : most);
     USL_TRY(usl_reserve(c, (void**)&L.stage, &L.stage_cap, keep * (N + N + nbins) * 4));
@@ -1465,13 +1515,13 @@ usl_status usl_both_lds_run(usl_ctx* c, const float* g, const void* x, const int
     size_t x_stride = 0;
     USL_TRY(usl_activation_rows(c, x, b, Q == 4 ? 4 : 1, &xs, &x_stride));
     out->stale = reinterpret_cast<const uint32_t*>(c->idx_print) + 4;
-    const bool direct = cut.nwin == 1 && dp == c->d && (uintptr_t)grad_x % 16 == 0;   // nothing to add up
+    const bool direct = chains == 1 && dp == c->d && (uintptr_t)grad_x % 16 == 0;   // nothing to add up
     static bool checked[4] = {false, false, false, false};
     for (int i0 = 0; i0 < b; i0 += G) {
         const int rows = b - i0 < G ? b - i0 : G;
         const int per_part = ((rows + parts - 1) / parts + Q - 1) / Q * Q;
         // whole windows to an XCD where that leaves no XCD more rounds (of 32 compute units) than even shares
-        const int64_t even = ((int64_t)cut.nwin * parts * cut.nfb + 7) / 8, whole = ((int64_t)cut.nwin * parts + 7) / 8 * cut.nfb;
+        const int64_t even = ((int64_t)chains * parts * cut.nfb + 7) / 8, whole = ((int64_t)chains * parts + 7) / 8 * cut.nfb;
         const dim3 grid((unsigned)(8 * ((whole + 31) / 32 == (even + 31) / 32 ? whole : even)));
 #define USL_BOTH(TS, QQ, WHICH)                                                                                             \
         do {                                                                                                                \
@@ -1481,12 +1531,12 @@ usl_status usl_both_lds_run(usl_ctx* c, const float* g, const void* x, const int
                                (const TS*)W, (const TS*)xs + (size_t)(QQ == 4 ? i0 / 4 : i0) * x_stride, x_stride, c->m, c->k, rows, c->d, \
                                dp, cut, L.lab, L.slot, L.feat, L.caps, L.ov_base, reinterpret_cast<const OvEntry*>(L.ov), L.ovr, \
                                direct ? grad_x + (size_t)i0 * c->d : L.partial, L.pos + N, L.pos + N + rkn, L.ov_base + 2 * ((size_t)cut.nwin * cut.nfb) + 1, L.stage, \
-                               ovgw, parts, per_part, N, N + nbins, gate, i0 > 0 ? 1 : 0, direct ? out->stale : nullptr);                                         \
+                               ovgw, chains, parts, per_part, N, N + nbins, gate, i0 > 0 ? 1 : 0, direct ? out->stale : nullptr);                                         \
         } while (0)
         if (c->storage == USL_F32) { if (Q == 4) USL_BOTH(float, 4, 0); else USL_BOTH(float, 2, 1); }
         else { if (Q == 4) USL_BOTH(uint16_t, 4, 2); else USL_BOTH(uint16_t, 2, 3); }
 #undef USL_BOTH
-        if (!direct) lf_reduce(c, L.partial, cut, rows, true, grad_x + (size_t)i0 * c->d, gate);
+        if (!direct) lf_reduce(c, L.partial, chains, rows, true, grad_x + (size_t)i0 * c->d, gate);
     }
     out->stage = L.stage;
     out->pos = L.pos;
