@@ -27,14 +27,15 @@
 
 #include <type_traits>
 
+#include "usl_internal.h"
+
+#include "k_lists_cut.h"
 #include "k_matching.h"
+
+using namespace usl_lists;
 
 namespace {
 
-constexpr int WL = 32768;      // most labels a window has: one float32 row of 128 KiB in LDS.  A layer's windows are of equal
-                               // size wl <= WL (a multiple of 4): no short last window whose workgroups idle
-constexpr int NF = 2048;       // features per workgroup (two per lane)
-constexpr int NT = 1024;
 constexpr int KT_BWI = 68;     // list slots per lane, shared by its two lists (with the rest of the kernel: the 128 registers a lane has)
 constexpr int KT_BOTH = 36, KT_BOTH4 = 32;    // ... in the kernel that also keeps a weight-gradient sum per slot (windows of half the length)
 constexpr uint32_t PAD_SLOT = 0xFFFFFFFFu;
@@ -54,8 +55,8 @@ static_assert(ZERO_LABEL % 32 == 0 && ZERO_LABEL + 31 < 65536 && LDS_BYTES <= 16
 // NEAR2 overflow entries of 8 bytes, 2 * NT words (each lane's share of them), NEAR2 floats (their weight-gradient sums).
 constexpr int NEAR2 = 512;
 template <int Q> struct BothLayout;
-template <> struct BothLayout<2> { static constexpr uint32_t zero_label = 15968, row_bytes = (zero_label + 32) * 8, x_bytes = 0, feat_words = 1024; };
-template <> struct BothLayout<4> { static constexpr uint32_t zero_label = 4672, row_bytes = (zero_label + 32) * 16, x_bytes = 4 * 2048 * 4, feat_words = 2048; };
+template <> struct BothLayout<2> { static constexpr uint32_t zero_label = BOTH2_LABELS, row_bytes = (zero_label + 32) * 8, x_bytes = 0, feat_words = 1024; };
+template <> struct BothLayout<4> { static constexpr uint32_t zero_label = BOTH4_LABELS, row_bytes = (zero_label + 32) * 16, x_bytes = 4 * 2048 * 4, feat_words = 2048; };
 template <int Q> constexpr size_t both_lds_bytes() {
     return (size_t)BothLayout<Q>::row_bytes + (size_t)Q * 2048 * 4 + BothLayout<Q>::x_bytes + (size_t)BothLayout<Q>::feat_words * 4 +
            (size_t)NEAR2 * 8 + (size_t)2 * 1024 * 4 + (size_t)NEAR2 * 4;
@@ -68,18 +69,6 @@ template <> struct ListLayout<36> { static constexpr uint32_t near = NEAR2; };
 template <> struct ListLayout<32> { static constexpr uint32_t near = NEAR2; };
 constexpr int CHUNK = 32768;   // features per LDS histogram
 
-// How a layer is cut up.  A workgroup owns a window of wl labels and a block of NF features.  Where the layer is narrower
-// than a block, the window consists of S runs of `run` labels, and the features count S times over, once for every run
-// ("virtual" features run * d + c, vd = S * d of them): the lists stay of the length that the registers are made for.
-// The sums of the runs are added up on their way out of the workgroup.
-// fpb: features of a block, a multiple of 32 (whole lines of x), at most NF.
-struct Cut {
-    int run, S, wl, nwin, vd, nfb, fpb;
-    __host__ __device__ __forceinline__ uint32_t vfeat(uint32_t col, uint32_t label_in_window, int d) const {
-        return S == 1 ? col : col + label_in_window / (uint32_t)run * (uint32_t)d;
-    }
-};
-
 __global__ void k_fill_u32(uint32_t* p, size_t n, uint32_t v) {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = v;
 }
@@ -89,7 +78,7 @@ __global__ void k_fill_u32(uint32_t* p, size_t n, uint32_t v) {
 __device__ __forceinline__ int share_of(int64_t m, int k, int wl, int splits, size_t* e0, size_t* e1) {
     const int t = (int)(blockIdx.x & 7) * ((int)gridDim.x / 8) + (int)(blockIdx.x >> 3);
     const int w = t / splits, s = t % splits;
-    const size_t w0 = (size_t)w * wl * k;
+    const size_t w0 = (size_t)min((int64_t)w * wl, m) * k;   // (a window behind the last one: no slots)
     const size_t w1 = (size_t)min((int64_t)(w + 1) * wl, m) * k;
     const size_t per = (w1 - w0 + splits - 1) / splits;
     *e0 = min(w0 + per * s, w1);
@@ -582,7 +571,7 @@ k_bwi_lds(const float* __restrict__ g, const TS* __restrict__ W, int64_t m, int 
     ovr_a[threadIdx.x] = ovr[(wg * 2 + 0) * NT + threadIdx.x];
     ovr_b[threadIdx.x] = ovr[(wg * 2 + 1) * NT + threadIdx.x];
     if (threadIdx.x < 32) reinterpret_cast<uint32_t*>(lds_raw)[ZERO_LABEL + threadIdx.x] = 0u;
-    const int nl = (int)min((int64_t)wl, m - (int64_t)w * wl);   // labels of this window (the last one may be short)
+    const int nl = (int)max((int64_t)0, min((int64_t)wl, m - (int64_t)w * wl));   // labels of this window (the last one may be short)
     const int nv = nl / 4, full = nv & ~63;                      // 16-byte pieces of a row slice; those in whole 1 KiB runs
     const int lines = (nl * 4 + 127) / 128, per = (lines + nfb - 1) / nfb;   // 128-byte lines; this workgroup's share of the warm-up
     const bool warms = (int)threadIdx.x < per && fb * per + (int)threadIdx.x < lines;
@@ -906,7 +895,7 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
     ovr_b[lane] = ovr[(wg * 2 + 1) * NT + lane];
     if (lane < 32 * Q) reinterpret_cast<uint32_t*>(lds_raw)[ZL * Q + lane] = 0u;   // what empty places read
     for (uint32_t q = NEAR2 + lane; q < ov_n; q += NT) ovgw[(size_t)ov0 + q] = 0.f;   // entry q is lane q % NT's
-    const int nl = (int)min((int64_t)cut.wl, m - (int64_t)w * cut.wl);   // labels of this window (the last one may be short)
+    const int nl = (int)max((int64_t)0, min((int64_t)cut.wl, m - (int64_t)w * cut.wl));   // labels of this window (the last one may be short)
     const int nv = nl / 4;                                               // whole 16-byte pieces of a row slice
     const int nf = min(cut.fpb, cut.vd - fb * cut.fpb);                            // features of this block that exist
     const int nx = cut.S > 1 ? d : nf;                                   // ... and activations
@@ -1204,61 +1193,9 @@ k_lf_reduce(const float4* __restrict__ partial, int nwin, size_t n4, int d, int 
 
 // ---- how a layer is cut up for either form --------------------------------------------------------------------
 
-// (window, feature block) workgroups run in rounds of one per compute unit: a last round that is not full takes as
-// long as a full one, so the windows are made a little shorter until the rounds are full (up to a quarter more
-// windows: more than that and the extra partial sums cost what the shorter lists save).
-static int64_t full_rounds(const usl_ctx* c, int64_t nwin, int64_t nfb) {
-    const int64_t cu = c->num_cu > 0 ? c->num_cu : 1;
-    const int64_t rounds = (nwin * nfb + cu - 1) / cu, full = rounds * cu / nfb;
-    return full > nwin && full * 4 <= nwin * 5 ? full : nwin;
-}
-
-// usl_backward_input's form: windows of as many labels as send about 32 connections into a feature (the registers of a
-// lane hold two such lists), at most WL (the LDS row), a multiple of 4 (16-byte copies), all of equal size.
-static Cut bwi_cut(const usl_ctx* c) {
-    const int64_t by_lists = (int64_t)32 * c->d / c->k, cap = (by_lists < WL ? by_lists : WL) / 4 * 4;
-    Cut cut;
-    cut.S = 1;
-    cut.vd = c->d;
-    cut.nfb = (c->d + NF - 1) / NF;
-    cut.fpb = NF;
-    cut.nwin = (int)full_rounds(c, (c->m + cap - 1) / cap, cut.nfb);
-    cut.run = cut.wl = (int)(((c->m + cut.nwin - 1) / cut.nwin + 3) / 4 * 4);
-    return cut;
-}
-
-// Instances that a pass of the kernel for both products takes together: four where windows that send 11 connections into
-// a feature fit LDS four rows at a time, else two.  A pass is a chain of waits, so the fewer the better; with shorter lists
-// there are too many windows (backward, m = 100k, d = 20k, k = 48 (lists of 11), b = 64: 167 us with four, 195 with two;
-// m = 300k, d = 14k, k = 32 (10.7): 362 and 365; m = 670k, d = 16k, k = 32 (9.1): 472 and 414).
-static int both_q(const usl_ctx* c) {
-    return c->d <= NT || (int64_t)11 * c->d / c->k <= (int64_t)BothLayout<4>::zero_label ? 4 : 2;
-}
-// The form for both products: lists of 16 connections (half the registers go to the weight-gradient sums; with four
-// instances a lane has 32 slots instead of 36, hence 14), longer where the features do not fill the lanes twice over;
-// blocks of equal size; S runs where the layer is narrower than half a block.
-static Cut both_cut(const usl_ctx* c) {
-    Cut cut;
-    cut.S = c->d <= NT ? NF / c->d : 1;
-    cut.vd = cut.S * c->d;
-    cut.nfb = (cut.vd + NF - 1) / NF;
-    cut.fpb = ((cut.vd + cut.nfb - 1) / cut.nfb + 31) / 32 * 32;
-    const int64_t mean = both_q(c) == 4 ? 14 : 16, longest = both_q(c) == 4 ? 21 : 24;
-    const int64_t lists = mean * NF / cut.fpb < longest ? mean * NF / cut.fpb : longest;
-    const int64_t most = (int64_t)(both_q(c) == 4 ? BothLayout<4>::zero_label : BothLayout<2>::zero_label) / cut.S;
-    int64_t run = lists * c->d / c->k;
-    run = run < most ? run : most;
-    run = run >= 4 ? run / 4 * 4 : 4;
-    if (cut.S == 1) {
-        cut.nwin = (int)full_rounds(c, (c->m + run - 1) / run, cut.nfb);
-        cut.run = cut.wl = (int)(((c->m + cut.nwin - 1) / cut.nwin + 3) / 4 * 4);
-    } else {
-        cut.run = (int)run;
-        cut.wl = cut.run * cut.S;
-        cut.nwin = (int)((c->m + cut.wl - 1) / cut.wl);
-    }
-    return cut;
-}
+static Cut bwi_cut(const usl_ctx* c) { return bwi_cut(c->m, c->d, c->k, c->num_cu); }
+static Cut both_cut(const usl_ctx* c) { return both_cut(c->m, c->d, c->k, c->num_cu); }
+static int both_q(const usl_ctx* c) { return both_q(c->d, c->k); }
 
 // The most that the partial sums of a pass over the batch may take: 16 GiB on a device with 128 GiB or more (every
 // pass loads lists and weights anew: at m = 3M, d = 65536, b = 1024 the two products take 74 ms with passes of 4 GiB,

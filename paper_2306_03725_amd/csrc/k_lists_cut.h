@@ -1,0 +1,88 @@
+// How a layer is cut up for the kernels that keep the connections of a window of labels in registers
+// (k_backward_input_lds.hip).  Plain arithmetic on the layer's sizes: no GPU is needed to check it.
+#pragma once
+#include <stdint.h>
+
+namespace usl_lists {
+
+constexpr int WL = 32768;      // most labels a window has: one float32 row of 128 KiB in LDS.  A layer's windows are of equal
+                               // size wl <= WL (a multiple of 4): no short last window whose workgroups idle
+constexpr int NF = 2048;       // features per workgroup (two per lane)
+constexpr int NT = 1024;
+constexpr int BOTH2_LABELS = 15968, BOTH4_LABELS = 4672;   // most labels of a window whose rows LDS holds two, four at a time
+
+// A workgroup owns a window of wl labels and a block of NF features.  Where the layer is narrower
+// than a block, the window consists of S runs of `run` labels, and the features count S times over, once for every run
+// ("virtual" features run * d + c, vd = S * d of them): the lists stay of the length that the registers are made for.
+// The sums of the runs are added up on their way out of the workgroup.
+// fpb: features of a block, a multiple of 32 (whole lines of x), at most NF.
+// Every window has labels: (nwin - 1) * wl < m <= nwin * wl.
+struct Cut {
+    int run, S, wl, nwin, vd, nfb, fpb;
+    __host__ __device__ __forceinline__ uint32_t vfeat(uint32_t col, uint32_t label_in_window, int d) const {
+        return S == 1 ? col : col + label_in_window / (uint32_t)run * (uint32_t)d;
+    }
+};
+
+// (window, feature block) workgroups run in rounds of one per compute unit: a last round that is not full takes as
+// long as a full one, so the windows are made a little shorter until the rounds are full (up to a quarter more
+// windows: more than that and the extra partial sums cost what the shorter lists save).
+inline int64_t full_rounds(int64_t num_cu, int64_t nwin, int64_t nfb) {
+    const int64_t cu = num_cu > 0 ? num_cu : 1;
+    const int64_t rounds = (nwin * nfb + cu - 1) / cu, full = rounds * cu / nfb;
+    return full > nwin && full * 4 <= nwin * 5 ? full : nwin;
+}
+
+// Windows of equal size for m labels, about nwin of them: rounding the size up to a multiple of 4 can leave fewer.
+inline void equal_windows(Cut* cut, int64_t m, int64_t nwin) {
+    const int64_t wl = ((m + nwin - 1) / nwin + 3) / 4 * 4;
+    cut->run = cut->wl = (int)wl;
+    cut->nwin = (int)((m + wl - 1) / wl);
+}
+
+// usl_backward_input's form: windows of as many labels as send about 32 connections into a feature (the registers of a
+// lane hold two such lists), at most WL (the LDS row), a multiple of 4 (16-byte copies), all of equal size.
+inline Cut bwi_cut(int64_t m, int d, int k, int num_cu) {
+    const int64_t by_lists = (int64_t)32 * d / k, cap = (by_lists < WL ? by_lists : WL) / 4 * 4;
+    Cut cut;
+    cut.S = 1;
+    cut.vd = d;
+    cut.nfb = (d + NF - 1) / NF;
+    cut.fpb = NF;
+    equal_windows(&cut, m, full_rounds(num_cu, (m + cap - 1) / cap, cut.nfb));
+    return cut;
+}
+
+// Instances that a pass of the kernel for both products takes together: four where windows that send 11 connections into
+// a feature fit LDS four rows at a time, else two.  A pass is a chain of waits, so the fewer the better; with shorter lists
+// there are too many windows (backward, m = 100k, d = 20k, k = 48 (lists of 11), b = 64: 167 us with four, 195 with two;
+// m = 300k, d = 14k, k = 32 (10.7): 362 and 365; m = 670k, d = 16k, k = 32 (9.1): 472 and 414).
+inline int both_q(int d, int k) { return d <= NT || (int64_t)11 * d / k <= (int64_t)BOTH4_LABELS ? 4 : 2; }
+
+// The form for both products: lists of 16 connections (half the registers go to the weight-gradient sums; with four
+// instances a lane has 32 slots instead of 36, hence 14), longer where the features do not fill the lanes twice over;
+// blocks of equal size; S runs where the layer is narrower than half a block.
+inline Cut both_cut(int64_t m, int d, int k, int num_cu) {
+    Cut cut;
+    const bool four = both_q(d, k) == 4;
+    cut.S = d <= NT ? NF / d : 1;
+    cut.vd = cut.S * d;
+    cut.nfb = (cut.vd + NF - 1) / NF;
+    cut.fpb = ((cut.vd + cut.nfb - 1) / cut.nfb + 31) / 32 * 32;
+    const int64_t mean = four ? 14 : 16, longest = four ? 21 : 24;
+    const int64_t lists = mean * NF / cut.fpb < longest ? mean * NF / cut.fpb : longest;
+    const int64_t most = (int64_t)(four ? BOTH4_LABELS : BOTH2_LABELS) / cut.S;
+    int64_t run = lists * d / k;
+    run = run < most ? run : most;
+    run = run >= 4 ? run / 4 * 4 : 4;
+    if (cut.S == 1) {
+        equal_windows(&cut, m, full_rounds(num_cu, (m + run - 1) / run, cut.nfb));
+    } else {
+        cut.run = (int)run;
+        cut.wl = cut.run * cut.S;
+        cut.nwin = (int)((m + cut.wl - 1) / cut.wl);
+    }
+    return cut;
+}
+
+}  // namespace usl_lists

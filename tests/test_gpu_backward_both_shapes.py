@@ -37,3 +37,20 @@ def test_one_pass_backward_shapes(orc, m, d, k, b, storage, parts, monkeypatch):
     L = usl.Layer(m, d, k, b, storage)
     run_and_compare(orc, L, gu, cfg, idx, W, x, g, b, max(1, b // 2))
     L.close()
+
+
+# layers of many short windows, as the layer is cut by itself: sizes at which rounding the window to a multiple of four
+# labels leaves fewer windows than were aimed at
+MANY_WINDOWS = [(76296, 1133, 64, 5, "f32"), (300000, 1100, 32, 6, "bf16"), (500000, 1500, 64, 2, "f32"), (670000, 2048, 32, 3, "f32")]
+
+
+@pytest.mark.parametrize("m,d,k,b,storage", MANY_WINDOWS)
+def test_one_pass_backward_of_many_windows(orc, m, d, k, b, storage):
+    import gpu_util as gu
+    from paper_2306_03725_amd import usl
+    cfg = wl.custom(m, d, k, b, storage=storage, positives=3, index=720)
+    print("backward", m, d, k, b, storage, flush=True)
+    idx, W, x, g = wl.gen_idx(cfg), wl.gen_W(cfg), wl.gen_x(cfg), wl.gen_g(cfg)
+    L = usl.Layer(m, d, k, b, storage)
+    run_and_compare(orc, L, gu, cfg, idx, W, x, g, b, max(1, b // 2))
+    L.close()
