@@ -65,13 +65,15 @@ inline int both_q(int d, int k) { return d <= NT || (int64_t)11 * d / k <= (int6
 inline Cut both_cut(int64_t m, int d, int k, int num_cu) {
     Cut cut;
     const bool four = both_q(d, k) == 4;
+    const int labels = four ? BOTH4_LABELS : BOTH2_LABELS;
     cut.S = d <= NT ? NF / d : 1;
+    if (cut.S > labels / 4) cut.S = labels / 4;   // a run has at least four labels, and the window has to fit LDS (d = 1)
     cut.vd = cut.S * d;
     cut.nfb = (cut.vd + NF - 1) / NF;
     cut.fpb = ((cut.vd + cut.nfb - 1) / cut.nfb + 31) / 32 * 32;
     const int64_t mean = four ? 14 : 16, longest = four ? 21 : 24;
     const int64_t lists = mean * NF / cut.fpb < longest ? mean * NF / cut.fpb : longest;
-    const int64_t most = (int64_t)(four ? BOTH4_LABELS : BOTH2_LABELS) / cut.S;
+    const int64_t most = labels / cut.S;
     int64_t run = lists * d / k;
     run = run < most ? run : most;
     run = run >= 4 ? run / 4 * 4 : 4;

@@ -11,6 +11,7 @@ pytestmark = pytest.mark.gpu
 # (m, d, k, b, storage, parts of the batch)
 SHAPES = [
     (900, 3, 3, 5, "f32", 1),           # 682 runs of 4 labels
+    (20011, 1, 1, 9, "f32", 1),         # one feature: as many runs of 4 labels as LDS holds
     (1024, 64, 8, 16, "bf16", 3),       # 32 runs, parts of 8, 8 and no instances
     (3000, 700, 5, 9, "f32", 2),        # two runs of a ragged number of features
     (5001, 1024, 32, 6, "f32", 1),      # two runs that fill the block

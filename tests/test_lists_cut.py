@@ -28,7 +28,7 @@ int main() {
     auto next = [&]() { r ^= r << 13; r ^= r >> 7; r ^= r << 17; return r; };
     const int ks[] = {1, 3, 5, 8, 16, 17, 32, 33, 48, 64};
     for (int n = 0; n < 400000; ++n) {
-        const int d = 2 + (int)(next() % (1u << (1 + next() % 16)));
+        const int d = 1 + (int)(next() % (1u << (1 + next() % 16)));
         const long long m = 1 + (long long)(next() % (1ull << (1 + next() % 23)));
         int k = ks[next() % 10];
         if (k > d) k = d;
