@@ -3,18 +3,20 @@
 
 namespace usl_products {
 
+enum ProductKind { FORWARD, FORWARD_LOSS, WEIGHT_GRADIENT };   // FORWARD_LOSS: the scores become the gradient of the loss
+
 struct ProductKernel {
     const void* fn;        // nullptr: no such kernel
     int K, LPT, NT;        // padded fan-in, labels per lane, lanes
     int transpose_bytes;   // LDS its prologue and epilogue need
 };
 
-ProductKernel kernel_f32_q4(bool backward, int K, int shape);
-ProductKernel kernel_f32_q2(bool backward, int K, int shape);
-ProductKernel kernel_f32_q1(bool backward, int K, int shape);
-ProductKernel kernel_f32_halves(bool backward, int K, int shape);
-ProductKernel kernel_bf16_q4(bool backward, int K, int shape);
-ProductKernel kernel_bf16_q2(bool backward, int K, int shape);
-ProductKernel kernel_bf16_q1(bool backward, int K, int shape);
+ProductKernel kernel_f32_q4(ProductKind kind, int K, int shape);
+ProductKernel kernel_f32_q2(ProductKind kind, int K, int shape);
+ProductKernel kernel_f32_q1(ProductKind kind, int K, int shape);
+ProductKernel kernel_f32_halves(ProductKind kind, int K, int shape);
+ProductKernel kernel_bf16_q4(ProductKind kind, int K, int shape);
+ProductKernel kernel_bf16_q2(ProductKind kind, int K, int shape);
+ProductKernel kernel_bf16_q1(ProductKind kind, int K, int shape);
 
 }  // namespace usl_products

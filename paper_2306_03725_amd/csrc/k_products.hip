@@ -123,12 +123,39 @@ __global__ void k_fill_zero(float* __restrict__ p, size_t n) {
     for (; i < n; i += s) p[i] = 0.f;
 }
 
+// Sets the bits of the targets (usl_ctx::tgt_bits).  Wavefront q of n takes instances q, q + n, ...
+struct TargetMarks {
+    const int64_t* off;    // nullptr: nothing to mark
+    const int32_t* lab;
+    uint32_t* bits;
+    int64_t m;
+    int b;
+    int row0;              // in k_interleave: the first row of blocks that does this
+};
+constexpr int MARK_WAVES = 4;   // of a block of 256 lanes
+__device__ __forceinline__ void mark_targets(const TargetMarks& t, int q, int n) {
+    for (int i = q; i < t.b; i += n) {
+        const int64_t p1 = t.off[i + 1];
+        for (int64_t p = t.off[i] + (threadIdx.x & 63); p < p1; p += 64) {
+            const int64_t j = t.lab[p];
+            if (j >= 0 && j < t.m) atomicOr(t.bits + (size_t)(i >> 5) * t.m + j, 1u << (i & 31));
+        }
+    }
+}
+__global__ void __launch_bounds__(256)
+k_mark_targets(TargetMarks t) { mark_targets(t, (int)(blockIdx.x * MARK_WAVES + (threadIdx.x >> 6)), (int)gridDim.x * MARK_WAVES); }
+
 // xi[group][column][Q instances] from x[b][d]; columns past d and instances past b are zeros.
-// grid (blocks of 256 columns, groups)
+// grid (blocks of 256 columns, groups); with targets to mark some rows of blocks more, which do that (a launch of its own
+// takes 5 us)
 template <typename TS, int Q>
 __global__ void __launch_bounds__(256)
-k_interleave(const TS* __restrict__ x, TS* __restrict__ xi, int b, int d, int cols) {
+k_interleave(const TS* __restrict__ x, TS* __restrict__ xi, int b, int d, int cols, TargetMarks marks) {
     const int c = blockIdx.x * 256 + threadIdx.x, g = blockIdx.y;
+    if (marks.off && g >= marks.row0) {
+        mark_targets(marks, (int)(((g - marks.row0) * gridDim.x + blockIdx.x) * MARK_WAVES + (threadIdx.x >> 6)), (int)((gridDim.y - marks.row0) * gridDim.x) * MARK_WAVES);
+        return;
+    }
     if (c >= cols) return;
     TS v[Q];
 #pragma unroll
@@ -363,11 +390,11 @@ Layout layout_of(const usl_ctx* c, int b, const void* x) {
     return L;
 }
 
-ProductKernel kernel_for(const usl_ctx* c, const Layout& L, bool backward, int shape) {
+ProductKernel kernel_for(const usl_ctx* c, const Layout& L, ProductKind kind, int shape) {
     if (c->storage == USL_F32)
-        return L.halves ? kernel_f32_halves(backward, L.K, shape) : L.Q == 4 ? kernel_f32_q4(backward, L.K, shape)
-             : L.Q == 2 ? kernel_f32_q2(backward, L.K, shape) : kernel_f32_q1(backward, L.K, shape);
-    return L.Q == 4 ? kernel_bf16_q4(backward, L.K, shape) : L.Q == 2 ? kernel_bf16_q2(backward, L.K, shape) : kernel_bf16_q1(backward, L.K, shape);
+        return L.halves ? kernel_f32_halves(kind, L.K, shape) : L.Q == 4 ? kernel_f32_q4(kind, L.K, shape)
+             : L.Q == 2 ? kernel_f32_q2(kind, L.K, shape) : kernel_f32_q1(kind, L.K, shape);
+    return L.Q == 4 ? kernel_bf16_q4(kind, L.K, shape) : L.Q == 2 ? kernel_bf16_q2(kind, L.K, shape) : kernel_bf16_q1(kind, L.K, shape);
 }
 
 struct Launch {
@@ -384,7 +411,8 @@ struct Launch {
 // per clock with every unit at it).  What a workgroup waits for alone: its prologue, a barrier and copy latency per
 // tile, and, with few wavefronts, the latency of a batch of reads (200 clocks).  The weight gradient of a split batch
 // is written and read once more per part.  Within 25 % of 40 measured launches, and the best or within 10 % of it there.
-Launch choose(const usl_ctx* c, const Layout& L, int b, bool backward) {
+Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind) {
+    const bool backward = kind == WEIGHT_GRADIENT;
     const int es = c->storage == USL_F32 ? 4 : 2, unit = L.Q * es;
     const int groups = (b + L.Q - 1) / L.Q;
     const double reads_per_clk = unit == 16 ? 8.0 : unit == 8 ? 12.0 : 14.0;
@@ -394,8 +422,8 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, bool backward) {
     double best_t = 0.0;
     const int shape_force = tune_shape(), split_force = tune_split();
     for (int shape = 0; shape < 3; ++shape) {
-        if (shape_force >= 0 && shape != shape_force && kernel_for(c, L, backward, shape_force).fn) continue;
-        const ProductKernel kern = kernel_for(c, L, backward, shape);
+        if (shape_force >= 0 && shape != shape_force && kernel_for(c, L, kind, shape_force).fn) continue;
+        const ProductKernel kern = kernel_for(c, L, kind, shape);
         if (!kern.fn) continue;
         const int64_t per_block = (int64_t)kern.NT * kern.LPT, nblk = (c->m + per_block - 1) / per_block;
         // tiles of about 16 KB, two of them where they fit beside each other
@@ -405,6 +433,7 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, bool backward) {
         tg.groups = groups;
         tg.tile_rows = L.halves || L.Q == 1 || L.row_bytes > 16384 ? 1 : 16384 / L.row_bytes;
         if (tg.tile_rows > groups) tg.tile_rows = groups;
+        if (kind == FORWARD_LOSS && tg.tile_rows > 32 / L.Q) tg.tile_rows = 32 / L.Q;   // a tile's instances lie in one window of targets
         const size_t tile = L.halves ? (size_t)HALF_COLS * 4 : (size_t)tg.tile_rows * L.row_bytes;
         tg.nbuf = L.Q > 1 && 2 * tile <= (size_t)ROW_LDS_MAX ? 2 : 1;
         tg.buf_bytes = (int)tile;
@@ -461,13 +490,15 @@ usl_status launch(usl_ctx* c, const Launch& p, void** args, const char* what) {
     return usl_check_launch(c, what);
 }
 
-usl_status interleave(usl_ctx* c, const void* x, int b, int Q, int row_bytes, void** to, size_t* cap) {
+usl_status interleave(usl_ctx* c, const void* x, int b, int Q, int row_bytes, void** to, size_t* cap, TargetMarks marks = TargetMarks{}) {
     const int es = c->storage == USL_F32 ? 4 : 2, groups = (b + Q - 1) / Q, cols = row_bytes / (Q * es);
     const int qmax = 4;   // sized once, for the largest batch any later call can bring
     const size_t need = (size_t)((c->max_b + qmax - 1) / qmax) * qmax * ((size_t)c->d + 16) * es;
     USL_TRY(usl_reserve(c, to, cap, max_sz(need, (size_t)groups * row_bytes)));
-    const dim3 grid((unsigned)((cols + 255) / 256), (unsigned)groups);
-#define USL_IL(TS, QQ) hipLaunchKernelGGL((k_interleave<TS, QQ>), grid, dim3(256), 0, c->stream, (const TS*)x, (TS*)*to, b, c->d, cols)
+    const int blocks = (cols + 255) / 256, per_row = blocks * MARK_WAVES, mark_rows = marks.off ? (b + per_row - 1) / per_row : 0;
+    marks.row0 = groups;
+    const dim3 grid((unsigned)blocks, (unsigned)(groups + mark_rows < 65535 ? groups + mark_rows : 65535));
+#define USL_IL(TS, QQ) hipLaunchKernelGGL((k_interleave<TS, QQ>), grid, dim3(256), 0, c->stream, (const TS*)x, (TS*)*to, b, c->d, cols, marks)
     if (es == 4) { if (Q == 4) USL_IL(float, 4); else if (Q == 2) USL_IL(float, 2); else USL_IL(float, 1); }
     else { if (Q == 4) USL_IL(uint16_t, 4); else if (Q == 2) USL_IL(uint16_t, 2); else USL_IL(uint16_t, 1); }
 #undef USL_IL
@@ -475,11 +506,15 @@ usl_status interleave(usl_ctx* c, const void* x, int b, int Q, int row_bytes, vo
 }
 
 // The interleaved activations of this call, in scratch of the context (or x itself, if it is laid out that way).
-// Inside usl_train_step the copy that forward made serves the backward products too.
-usl_status activations(usl_ctx* c, const Layout& L, const void* x, int b, const void** xi) {
+// Inside usl_train_step the copy that forward made serves the backward products too.  marks: targets to mark on the way.
+usl_status activations(usl_ctx* c, const Layout& L, const void* x, int b, const void** xi, const TargetMarks& marks = TargetMarks{}) {
     *xi = x;
+    const bool copies = L.copy && (c->xi_of != x || c->xi_q != L.Q || c->xi_row_bytes != L.row_bytes);
+    const bool along = copies && (b + L.Q - 1) / L.Q < 65535;   // (k_interleave's grid has room for a row of blocks more)
+    if (marks.off && !along)
+        hipLaunchKernelGGL(k_mark_targets, dim3((unsigned)((b + MARK_WAVES - 1) / MARK_WAVES)), dim3(256), 0, c->stream, marks);
     if (!L.copy) return USL_OK;
-    if (c->xi_of != x || c->xi_q != L.Q || c->xi_row_bytes != L.row_bytes) USL_TRY(interleave(c, x, b, L.Q, L.row_bytes, &c->xi, &c->xi_cap));
+    if (copies) USL_TRY(interleave(c, x, b, L.Q, L.row_bytes, &c->xi, &c->xi_cap, along ? marks : TargetMarks{}));
     *xi = c->xi;
     c->xi_of = c->xi_keep ? x : nullptr;
     c->xi_q = L.Q;
@@ -556,16 +591,15 @@ namespace {
 
 // What k_forward's loss leaves to do: the gradient and the loss of the targets, a few per instance.  Their scores are taken
 // once more, in k_forward's order of additions (the same bits): 16 lanes bring the slots of a target, in the order of
-// their steps, and one of them adds up.  A label listed twice for an instance counts once: the exchange shows who came
-// second, for the gradient of a target is never what it is without one.  Block i of the first b: instance i, its change
-// of the loss goes to partials[i].  Block b, if there is one, compares the fingerprint of idx for the backward product
+// their steps, and one of them adds up.  A label listed twice for an instance counts once: whoever takes its bit back
+// first.  Block i of the first b: instance i, its targets' part of the loss goes to partials[i].  Block b, if there is one, compares the fingerprint of idx for the backward product
 // (a launch of its own took 4 to 8 us).
 template <typename TS>
 __global__ void __launch_bounds__(1024)
 k_loss_positives(const TS* __restrict__ x, const int32_t* __restrict__ idx, const TS* __restrict__ W, float* __restrict__ g, int64_t m,
                  int d, int k, int K, bool halves, const uint8_t* __restrict__ perm, int b, const int64_t* __restrict__ tgt_off,
-                 const int32_t* __restrict__ tgt_lab, int kind, float scale, double* __restrict__ partials, size_t n_words,
-                 uint64_t* __restrict__ print) {
+                 const int32_t* __restrict__ tgt_lab, uint32_t* __restrict__ bits, int kind, float scale, double* __restrict__ partials,
+                 size_t n_words, uint64_t* __restrict__ print) {
     constexpr int PER = 64;   // targets at a time
     __shared__ float2 slots[PER][65];        // {weight, activation} of a slot; zeros behind the last one
     __shared__ uint8_t upper[PER][64];       // whether its column is in the second half of a row in two halves
@@ -580,7 +614,7 @@ k_loss_positives(const TS* __restrict__ x, const int32_t* __restrict__ idx, cons
     const TS* row = x + (size_t)i * d;
     const int q16 = threadIdx.x >> 4;
     const float2* mine = slots[q16];
-    double delta = 0.0;
+    double lost = 0.0;
     for (int64_t p = tgt_off[i] + (threadIdx.x >> 4); p < p1; p += PER) {   // the lanes of a target are of one wavefront
         const int64_t j = tgt_lab[p];
         if (j < 0 || j >= m) continue;
@@ -613,14 +647,17 @@ k_loss_positives(const TS* __restrict__ x, const int32_t* __restrict__ idx, cons
                     z = dot2(__float_as_uint(u.y) >> 16 | __float_as_uint(v.y), __float_as_uint(u.x) >> 16 | __float_as_uint(v.x), z);
                 }
             }
-            const usl_loss_of without = usl_loss_one(kind, z, 0.f, scale), with = usl_loss_one(kind, z, 1.f, scale);
-            const float before = atomicExch(g + (size_t)i * m + j, with.g);
-            if (__float_as_uint(before) != __float_as_uint(with.g)) delta += (double)with.l - (double)without.l;
+            const uint32_t bit = 1u << (i & 31);
+            if (atomicAnd(bits + (size_t)(i >> 5) * m + j, ~bit) & bit) {
+                const usl_loss_of r = usl_loss_one(kind, z, 1.f, scale);
+                g[(size_t)i * m + j] = r.g;
+                lost += (double)r.l;
+            }
         }
         wave_sync();
     }
-    for (int o = 32; o > 0; o >>= 1) delta += __shfl_down(delta, o);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = delta;
+    for (int o = 32; o > 0; o >>= 1) lost += __shfl_down(lost, o);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = lost;
     __syncthreads();
     if (threadIdx.x == 0) {
         double t = 0.0;
@@ -629,14 +666,24 @@ k_loss_positives(const TS* __restrict__ x, const int32_t* __restrict__ idx, cons
     }
 }
 
-// the forward kernel over the whole batch, with or without the loss
+// the forward kernel over the whole batch, with or without the loss (then marks says what the targets are; the bits are set
+// here and taken back by k_loss_positives)
 usl_status run_forward(usl_ctx* c, const Layout& L, const void* x, const int32_t* idx, const void* W, float* out, int32_t b, LossArgs loss,
-                       size_t* blocks) {
-    const Launch p = choose(c, L, b, false);
+                       size_t* blocks, TargetMarks marks = TargetMarks{}) {
+    const Launch p = choose(c, L, b, loss.kind >= 0 ? FORWARD_LOSS : FORWARD);
     const uint8_t* perm = nullptr;
     const void* xi = nullptr;
     USL_TRY(slot_order(c, idx, &perm));
-    USL_TRY(activations(c, L, x, b, &xi));
+    if (loss.kind >= 0) {
+        const size_t words = (size_t)((c->max_b + 31) / 32) * c->m, had = c->tgt_bits_cap;
+        USL_TRY(usl_reserve(c, (void**)&c->tgt_bits, &c->tgt_bits_cap, words * 4));
+        if (had != c->tgt_bits_cap || c->tgt_bits_set)   // new, or a call before failed half way
+            hipLaunchKernelGGL(k_fill_zero, dim3(c->num_cu * 4), dim3(256), 0, c->stream, reinterpret_cast<float*>(c->tgt_bits), words);
+        c->tgt_bits_set = true;
+        marks.bits = c->tgt_bits;
+        loss.targets = c->tgt_bits;
+    }
+    USL_TRY(activations(c, L, x, b, &xi, marks));
     int64_t m = c->m;
     int k = c->k, bb = b;
     Geom tg = p.geom;
@@ -659,7 +706,7 @@ usl_status usl_launch_forward(usl_ctx* c, const void* x, const int32_t* idx, con
         return c->storage == USL_F32 ? run_forward_generic<float>(c, x, idx, W, out, b) : run_forward_generic<uint16_t>(c, x, idx, W, out, b);
     const Layout L = layout_of(c, b, x);
     if (streams(c, L, b)) return run_forward_few(c, L, x, idx, W, out, b);
-    return run_forward(c, L, x, idx, W, out, b, LossArgs{-1, 0.f, nullptr}, nullptr);
+    return run_forward(c, L, x, idx, W, out, b, LossArgs{-1, 0.f, nullptr, nullptr}, nullptr);
 }
 
 bool usl_forward_loss_applies(const usl_ctx* c, const void* x, const int32_t* idx, const void* W, int32_t b) {
@@ -670,18 +717,20 @@ usl_status usl_launch_forward_loss(usl_ctx* c, const void* x, const int32_t* idx
                                    const int64_t* tgt_off, const int32_t* tgt_lab, float scale, float* loss, usl_loss_sum* sum) {
     size_t blocks = 0;
     const Layout L = layout_of(c, b, x);
-    USL_TRY(run_forward(c, L, x, idx, W, g, b, LossArgs{loss_kind, scale, nullptr}, &blocks));
+    USL_TRY(run_forward(c, L, x, idx, W, g, b, LossArgs{loss_kind, scale, nullptr, nullptr}, &blocks, TargetMarks{tgt_off, tgt_lab, nullptr, c->m, b, 0}));
     const bool check = c->lf[1].built_for == idx;   // lists that the backward product will use
     const dim3 grid((unsigned)(b + (check ? 1 : 0)));
 #define USL_POS(TS)                                                                                                              \
     hipLaunchKernelGGL(k_loss_positives<TS>, grid, dim3(1024), 0, c->stream, (const TS*)x, idx, (const TS*)W, g, c->m, c->d, c->k, L.K,   \
-                       L.halves, c->no_order ? nullptr : c->slot_order, b, tgt_off, tgt_lab, loss_kind, scale, c->bce_partials + blocks, \
+                       L.halves, c->no_order ? nullptr : c->slot_order, b, tgt_off, tgt_lab, c->tgt_bits, loss_kind, scale, c->bce_partials + blocks, \
                        (size_t)c->m * c->k, c->idx_print)
     if (c->storage == USL_F32) USL_POS(float); else USL_POS(uint16_t);
 #undef USL_POS
+    USL_TRY(usl_check_launch(c, "loss of the targets"));
+    c->tgt_bits_set = false;
     c->print_done = check;
     *sum = usl_loss_sum{c->bce_partials, blocks + (size_t)b, scale, loss};
-    return usl_check_launch(c, "loss of the targets");
+    return USL_OK;
 }
 
 usl_status usl_activation_rows(usl_ctx* c, const void* x, int32_t b, int Q, const void** rows, size_t* stride) {
@@ -708,7 +757,7 @@ usl_status usl_launch_backward_weight(usl_ctx* c, const float* g, const void* x,
         return c->storage == USL_F32 ? run_backward_weight_generic<float>(c, g, x, idx, grad_W, b)
                                      : run_backward_weight_generic<uint16_t>(c, g, x, idx, grad_W, b);
     const Layout L = layout_of(c, b, x);
-    const Launch p = choose(c, L, b, true);
+    const Launch p = choose(c, L, b, WEIGHT_GRADIENT);
     const uint8_t* perm = nullptr;
     const void* xi = nullptr;
     USL_TRY(slot_order(c, idx, &perm));
@@ -727,7 +776,7 @@ usl_status usl_launch_backward_weight(usl_ctx* c, const float* g, const void* x,
     if (p.G > 1) {   // G partial gradients in scratch, summed afterwards in a fixed order (no atomics, reproducible)
         stride = (N + 3) / 4 * 4;
         size_t parts = (size_t)p.G;   // sized once, for the batch of max_b instances too: never grown by a later call
-        if (b < c->max_b) parts = max_sz(parts, (size_t)choose(c, layout_of(c, c->max_b, x), c->max_b, true).G);
+        if (b < c->max_b) parts = max_sz(parts, (size_t)choose(c, layout_of(c, c->max_b, x), c->max_b, WEIGHT_GRADIENT).G);
         USL_TRY(usl_reserve(c, (void**)&c->gw_part, &c->gw_part_cap, parts * stride * 4));
         dst = c->gw_part;
     }

@@ -1,6 +1,6 @@
 // Forward and weight-gradient kernels: bfloat16 activations, 1 instance per group.
 #include "k_products_inst.h"
 
-usl_products::ProductKernel usl_products::kernel_bf16_q1(bool backward, int K, int shape) {
-    return pick_k<uint16_t, 1, false>(backward, K, shape);
+usl_products::ProductKernel usl_products::kernel_bf16_q1(ProductKind kind, int K, int shape) {
+    return pick_k<uint16_t, 1, false>(kind, K, shape);
 }

@@ -1,6 +1,6 @@
 // Forward and weight-gradient kernels: bfloat16 activations, 4 instances per group.
 #include "k_products_inst.h"
 
-usl_products::ProductKernel usl_products::kernel_bf16_q4(bool backward, int K, int shape) {
-    return pick_k<uint16_t, 4, false>(backward, K, shape);
+usl_products::ProductKernel usl_products::kernel_bf16_q4(ProductKind kind, int K, int shape) {
+    return pick_k<uint16_t, 4, false>(kind, K, shape);
 }

@@ -578,10 +578,11 @@ __device__ __forceinline__ void label_outer(const uint32_t (&pk)[K / 2], const f
 
 // --------------------------------------------------------------------------------------------- the walk over the batch
 // Calls body(group, first LDS byte of its row, part) for every instance group of this blockIdx.y, with the rows staged
-// tile by tile; late(first group of the tile, groups in it, lane) right after a tile has arrived.
+// tile by tile; late(first group of the tile, groups in it, lane) right after a tile has arrived, early(first group,
+// groups) right before the wait for it: what is loaded there can be waited for at no cost.
 // MULTI = false: one row fills the buffer (tiles of one row, one buffer); HALVES: part 0 / 1 of every row.
-template <int NT, bool MULTI, bool HALVES, typename BODY, typename LATE>
-__device__ __forceinline__ void walk(const char* __restrict__ xi, uint32_t lds0, const Geom& tg, int g0, int g1, BODY body, LATE late) {
+template <int NT, bool MULTI, bool HALVES, typename BODY, typename LATE, typename EARLY>
+__device__ __forceinline__ void walk(const char* __restrict__ xi, uint32_t lds0, const Geom& tg, int g0, int g1, BODY body, LATE late, EARLY early) {
     const uint32_t dummy = lds0 + (uint32_t)tg.dummy;
     const WarmShare ws(tg.share);
     if (!MULTI) {
@@ -599,6 +600,7 @@ __device__ __forceinline__ void walk(const char* __restrict__ xi, uint32_t lds0,
                 __syncthreads();
                 if (HALVES) stage_async(row + (part ? HB : 0), lds0, part ? tg.row_bytes - HB : HB, tid, NT);
                 else stage_async(row, lds0, tg.row_bytes, tid, NT);
+                if (part == 0) early(g, 1);
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 __syncthreads();
                 if ((!HALVES || part == 1) && g + 1 < g1) warm_slice<NT>(row + tg.row_bytes, tg.row_bytes, per, ws.slice, dummy, tid);
@@ -623,6 +625,7 @@ __device__ __forceinline__ void walk(const char* __restrict__ xi, uint32_t lds0,
             __syncthreads();   // the buffer is no longer read
             stage_async(xi + (size_t)t * tg.row_bytes, base, rows * tg.row_bytes, tid, NT);
         }
+        early(t, rows);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this tile has landed
         __syncthreads();                                   // (two buffers: and the other one is no longer read)
         if (two && next < g1)
@@ -646,15 +649,19 @@ __device__ __forceinline__ uint32_t lds_base(const void* p) {
 
 // ------------------------------------------------------------------------------------------------ forward
 // out[i][j] = sum_t W[j][t] x[i][idx[j][t]].  grid (label blocks, groups of the batch).
-// With a loss (training): out receives the gradient of the loss by the score, for a target of 0 (k_loss_positives puts the
-// few others right), and the workgroup's part of the loss goes to partials[block].  The scores then never go to memory:
-// the separate pass over them took 24 us at m = 200k, b = 64 and 170 us at m = 500k, b = 256.
+// With a loss (training): out receives the gradient of the loss by the score, for a target of 0 (k_loss_positives writes that
+// of the few others), and the workgroup's part of the loss, targets left out, goes to partials[block].  The scores then
+// never go to memory: the separate pass over them took 24 us at m = 200k, b = 64 and 170 us at m = 500k, b = 256.
+// Which labels are targets comes as one bit per score; a lane reads a word for 32 instances at a time.  (Added up with
+// the others and subtracted afterwards, a target far on the right side of its margin would leave rounding errors of a
+// loss that it does not have, and NaN where that loss overflows.)
 struct LossArgs {
-    int kind;           // 0, 1: usl_loss_one's; -1: none, out receives the scores
+    int kind;           // usl_loss_one's
     float scale;
     double* partials;
+    const uint32_t* targets;   // [b / 32][m], see usl_ctx::tgt_bits
 };
-template <int K, int LPT, int NT, typename TS, int Q, bool HALVES>
+template <int K, int LPT, int NT, typename TS, int Q, bool HALVES, bool LOSS>
 __global__ void __launch_bounds__(NT)
 k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS* __restrict__ W, float* __restrict__ out,
           int64_t m, int k, int b, Geom tg, const uint8_t* __restrict__ perm, LossArgs loss) {
@@ -687,13 +694,39 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
     }
     const int g0 = blockIdx.y * tg.groups_per_block, g1 = min(tg.groups, g0 + tg.groups_per_block);
     const int nlab = (int)min((int64_t)NT * LPT, m - j0);
-    // Q <= 2: the scores of a group are written while the next group is gathered, between two labels' gathers (a store
+    // Q <= 2: the scores of a group are written while the next group is gathered, before the last label's gathers (a store
     // right before the next copy would make that copy's wait include it; four stores in a row would hold the wavefront
-    // at the memory pipeline).  Q = 4 has no registers left for that, and a quarter of the waits.
+    // at the memory pipeline).  Q = 4 has no registers left for that, and a quarter of the waits.  All labels' losses
+    // in one place, and the gathers before everything else (setprio): 805 us at m = 500k, d = 32k, k = 32, b = 256, where
+    // a label's loss in front of its own gathers took 866, and 852 with the priority.
     constexpr bool DELAY = Q <= 2;
     float prev[DELAY ? LPT : 1][Q] = {};
     double lost = 0.0;
-    auto put = [&](int g, int l, const float (&v)[Q]) {
+    // Bit i % 32 of others[l]: instance i has another target than the label.  Good for 32 instances, before `until`; loaded
+    // with the tile that leaves them and waited for together with that tile: a load still under way when the losses are
+    // added up would be waited for there, with the stores and the warm-up loads behind it (50 of 825 us at m = 500k, b = 256).
+    uint32_t others[LPT];
+    int until = -1;
+    auto load_targets = [&](int first, int last) {   // for the instances first .. last, at most 32 of them
+        if (!LOSS || last < until) return;
+        until = first + 32;
+        uint32_t behind[LPT];
+#pragma unroll
+        for (int l = 0; l < LPT; ++l) {
+            int jl = (int)threadIdx.x + l * NT;
+            asm volatile("" : "+v"(jl));
+            const uint32_t* p = loss.targets + (size_t)(first >> 5) * m + j0;
+            others[l] = jl < nlab ? p[(uint32_t)jl] : 0u;
+            behind[l] = jl < nlab && (first & 31) != 0 && (first | 31) + 1 < b ? p[m + jl] : 0u;
+        }
+        const uint32_t later = (1u << (first & 31)) - 1u;   // the bits of the second word
+#pragma unroll
+        for (int l = 0; l < LPT; ++l) {
+            others[l] = ~((behind[l] & later) | (others[l] & ~later));
+            asm volatile("" : "+v"(others[l]));
+        }
+    };
+    auto put = [&](int g, int l, const float (&z)[Q]) {
         int jl = (int)threadIdx.x + l * NT;   // rebuilt here: kept, every label's offset would be a register across the gathers
         asm volatile("" : "+v"(jl));
         if (jl < nlab) {
@@ -701,11 +734,11 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
 #pragma unroll
             for (int q = 0; q < Q; ++q)
                 if (g * Q + q < b) {
-                    float o = v[q];
-                    if (loss.kind >= 0) {
+                    float o = z[q];
+                    if (LOSS) {
                         const usl_loss_of r = usl_loss_one(loss.kind, o, 0.f, loss.scale);
                         o = r.g;
-                        sum += r.l;
+                        sum += __uint_as_float(__float_as_uint(r.l) & (uint32_t)__builtin_amdgcn_sbfe((int)others[l], (uint32_t)(g * Q + q) & 31u, 1u));
                     }
                     (out + ((size_t)(g * Q + q) * m + j0))[(uint32_t)jl] = o;
                 }
@@ -714,14 +747,25 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
     };
     walk<NT, (Q > 1), HALVES>(xi, lds0, tg, g0, g1,
         [&](int g, uint32_t base, int part) {
+            float before[DELAY ? LPT : 1][Q];
+#pragma unroll
+            for (int l = 0; l < (DELAY ? LPT : 0); ++l) {
+#pragma unroll
+                for (int q = 0; q < Q; ++q) before[l][q] = prev[l][q];
+            }
 #pragma unroll
             for (int l = 0; l < LPT; ++l) {
-                if (DELAY && part == 0 && g > g0) put(g - 1, l, prev[DELAY ? l : 0]);
+                if (DELAY && l == LPT - 1 && part == 0 && g > g0) {
+#pragma unroll
+                    for (int l2 = 0; l2 < LPT; ++l2) put(g - 1, l2, before[DELAY ? l2 : 0]);
+                }
                 float acc[Q];
 #pragma unroll
                 for (int q = 0; q < Q; ++q) acc[q] = HALVES && part ? prev[DELAY ? l : 0][q] : 0.f;   // the first half's sums
                 keep_packed(pk[l]);
+                __builtin_amdgcn_s_setprio(1);
                 label_dot<K, Q, HALVES>(pk[l], w[l].v, base, zbyte, acc);
+                __builtin_amdgcn_s_setprio(0);
                 // finish the sums here; left alone the compiler sinks the multiply-adds into the guarded store
                 // and keeps every gathered value alive until then
 #pragma unroll
@@ -734,12 +778,17 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
                 }
             }
         },
-        [&](int, int, int) {});
+        [&](int, int, int) {},
+        [&](int t, int rows) {   // (the groups that are put while this tile is gathered)
+            const int first = (DELAY && t > g0 ? t - 1 : t) * Q;
+            load_targets(first, first + rows * Q - 1);
+        });
     if (DELAY && g1 > g0) {
+        load_targets((g1 - 1) * Q, g1 * Q - 1);
 #pragma unroll
         for (int l = 0; l < LPT; ++l) put(g1 - 1, l, prev[DELAY ? l : 0]);
     }
-    if (loss.kind >= 0) {   // the workgroup's share, added up in a fixed order
+    if (LOSS) {   // the workgroup's share, added up in a fixed order
         for (int o = 32; o > 0; o >>= 1) lost += __shfl_down(lost, o);
         double* red = reinterpret_cast<double*>(lds_raw);
         __syncthreads();
@@ -837,7 +886,8 @@ k_backward_weight(const float* __restrict__ g, const char* __restrict__ xi, cons
                         touch_lines<NT>(reinterpret_cast<const char*>(g + i * m + j0), 0, nlab * 4 / 128, lds0 + (uint32_t)tg.dummy, tid);
                 }
             }
-        });
+        },
+        [](int, int) {});
 #pragma unroll
     for (int l = 0; l < LPT; ++l) {
         const int64_t row0 = j0 + (int64_t)l * NT;

@@ -13,16 +13,17 @@ namespace usl_products {
 constexpr int labels_per_lane(int K, int slots) { return slots / K < 1 ? 1 : slots / K > 8 ? 8 : slots / K; }
 
 template <int K, typename TS, int Q, bool HALVES>
-ProductKernel pick(bool backward, int shape) {
+ProductKernel pick(ProductKind kind, int shape) {
     constexpr int L = K == 8 ? 4 : labels_per_lane(K, 64), L2 = labels_per_lane(K, 128);
 #define USL_PICK(LPT, NT)                                                                                      \
-    ProductKernel{backward ? (const void*)k_backward_weight<K, LPT, NT, TS, Q, HALVES>                          \
-                           : (const void*)k_forward<K, LPT, NT, TS, Q, HALVES>, K, LPT, NT, transpose_bytes<K, NT>()}
+    ProductKernel{kind == WEIGHT_GRADIENT ? (const void*)k_backward_weight<K, LPT, NT, TS, Q, HALVES>           \
+                  : kind == FORWARD_LOSS  ? (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, true>             \
+                                          : (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, false>, K, LPT, NT, transpose_bytes<K, NT>()}
     if constexpr (Q > 1) {
         if (shape == 0) return USL_PICK(1, 256);
         if (shape == 1) return USL_PICK(L, 512);
         if constexpr (K == 64) {
-            if (shape == 2 && !backward) return USL_PICK(L2, 512);
+            if (shape == 2 && kind != WEIGHT_GRADIENT) return USL_PICK(L2, 512);
         }
         if (shape == 2) return USL_PICK(L, 1024);
     } else if constexpr (K < 64) {
@@ -37,14 +38,14 @@ ProductKernel pick(bool backward, int shape) {
 }
 
 template <typename TS, int Q, bool HALVES>
-ProductKernel pick_k(bool backward, int K, int shape) {
+ProductKernel pick_k(ProductKind kind, int K, int shape) {
     switch (K) {
-        case 8: return pick<8, TS, Q, HALVES>(backward, shape);
-        case 16: return pick<16, TS, Q, HALVES>(backward, shape);
-        case 24: return pick<24, TS, Q, HALVES>(backward, shape);
-        case 32: return pick<32, TS, Q, HALVES>(backward, shape);
-        case 48: return pick<48, TS, Q, HALVES>(backward, shape);
-        case 64: return pick<64, TS, Q, HALVES>(backward, shape);
+        case 8: return pick<8, TS, Q, HALVES>(kind, shape);
+        case 16: return pick<16, TS, Q, HALVES>(kind, shape);
+        case 24: return pick<24, TS, Q, HALVES>(kind, shape);
+        case 32: return pick<32, TS, Q, HALVES>(kind, shape);
+        case 48: return pick<48, TS, Q, HALVES>(kind, shape);
+        case 64: return pick<64, TS, Q, HALVES>(kind, shape);
         default: return ProductKernel{nullptr, 0, 0, 0, 0};
     }
 }

@@ -46,6 +46,8 @@ struct usl_ctx {
     bool xi_keep;                  // inside usl_train_step: the copy that forward makes serves the weight gradient
     const void* xi_of;             // x that xi holds (only set inside usl_train_step), else NULL
     int xi_q, xi_row_bytes;        // ... its instances per group and bytes per row
+    uint32_t* tgt_bits;       size_t tgt_bits_cap;   // [max_b / 32][m] bit i % 32 of word [i / 32][j]: j is a target of instance i.  All zero between calls
+    bool tgt_bits_set;             // a call has set bits and not come to the kernel that takes them back
     void* xr;                 size_t xr_cap;   // activations in the layout of the backward kernel, where that is another one
     float* gT;                size_t gT_cap;   // [tiles][m][32] upstream gradient, one 128-byte piece per (tile of 32 instances, label)
     uint8_t* nz_flags;        size_t nz_flags_cap;   // [tiles][m] 1 = that 32-instance piece of gT is not all zero

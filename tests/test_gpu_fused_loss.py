@@ -41,3 +41,42 @@ def test_fused_loss(orc, m, d, k, b, storage, loss_kind):
         assert_close(gu.host(loss), gu.host(ref_loss), 1e-5, "loss")
         assert_close(gu.host(gW), orc.backward_weight(gu.host(g), x, idx), 1e-5, "grad_W")
     L.close()
+
+
+@pytest.mark.parametrize("size", [1.0, 1e24])
+@pytest.mark.parametrize("loss_kind", [0, 1])
+@pytest.mark.parametrize("m,d,k,b,storage", [(5000, 300, 16, 70, "f32"), (5000, 300, 12, 37, "bf16"), (5000, 12000, 32, 34, "f32"), (2050, 24000, 32, 65, "f32")])
+def test_targets_that_are_learned(orc, m, d, k, b, storage, loss_kind, size):
+    """Every target far on its side of the margin, every other score far on the other: the squared hinge is exactly 0,
+    also where the square of a score exceeds float32 (a target's loss must not be taken as if it were none, and then
+    taken back), and the binary cross-entropy is what the separate calls give.  The batch ends off a word of 32
+    instances.  Twice, the second time with other targets: what marks them does not outlive the call."""
+    import gpu_util as gu
+    from paper_2306_03725_amd import usl
+    print("learned targets", m, d, k, b, storage, loss_kind, size, flush=True)
+    cfg = wl.custom(m, d, k, b, storage=storage, positives=3, index=830)
+    idx = wl.gen_idx(cfg)
+    x = wl.store(1.0 + np.abs(wl.as_f32(wl.gen_x(cfg))), storage)
+    scale = 1.0 / b
+    L = usl.Layer(m, d, k, b, storage)
+    d_x, d_idx = gu.dev(x), gu.dev(idx)
+    rng = np.random.default_rng(7)
+    for turn in range(2):
+        targets = rng.choice(m, size=19, replace=False).astype(np.int32)
+        W = -np.abs(rng.normal(1.0, 0.2, size=(m, k))).astype(np.float32) * np.float32(3.0 if loss_kind == 0 else 1.0)
+        W[targets] = np.abs(W[targets]) * np.float32(size)
+        W = wl.store(W, storage)
+        off, lab = np.arange(b + 1, dtype=np.int64) * 19, np.tile(targets, b)
+        d_W, d_off, d_lab = gu.dev(W), gu.dev(off), gu.dev(lab)
+        ref, ref_loss = gu.empty((b, m)), gu.empty((1,))
+        L.forward(d_x, d_idx, d_W, ref, b)
+        (L.bce_loss_grad if loss_kind == 0 else L.sqh_loss_grad)(ref, d_off, d_lab, scale, ref, ref_loss, b)
+        m1, m2 = gu.empty((m, k)).fill_(0.0), gu.empty((m, k)).fill_(0.0)
+        g, gW, loss = gu.empty((b, m)), gu.empty((m, k)), gu.empty((1,)).fill_(float("nan"))
+        L.train_step(d_x, d_idx, d_W, m1, m2, d_off, d_lab, loss_kind, scale, 1, 1e-3, 0.9, 0.999, 1e-8, g, gW, None, loss, b)
+        np.testing.assert_array_equal(gu.host(g), gu.host(ref))
+        # both are float32 sums of at most 16 losses, added up in float64
+        assert abs(gu.host(loss)[0] - gu.host(ref_loss)[0]) <= 1e-6 * abs(gu.host(ref_loss)[0])
+        if loss_kind == 1:
+            assert gu.host(loss)[0] == 0.0
+    L.close()
