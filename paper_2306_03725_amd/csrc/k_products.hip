@@ -188,12 +188,16 @@ k_forward_few(const char* __restrict__ xi, const int32_t* __restrict__ idx, cons
     const int64_t waves = (int64_t)gridDim.x * nw;
     const int64_t w0 = (int64_t)blockIdx.x * nw + (threadIdx.x >> 6);
     struct Piece { uint32_t c[4]; uint32_t w[sizeof(TS) == 4 ? 4 : 2]; };
-    // the four slots of this lane in round r of the wavefront's 64 labels (columns 0 and weights 0 where there are none)
+    // What a slot that does not exist reads: a unit of zeros behind the row.  (Weight 0 times a real activation would turn
+    // an infinity into NaN for labels that have no connection to it.)
+    const uint32_t nowhere = (uint32_t)row_bytes / (uint32_t)sizeof(U);
+    if (threadIdx.x < 4) reinterpret_cast<uint32_t*>(lds_raw)[(uint32_t)row_bytes / 4 + threadIdx.x] = 0u;
+    // the four slots of this lane in round r of the wavefront's 64 labels
     auto fetch = [&](int64_t j0, int r, Piece& p) {
         const int64_t j = j0 + r * (64 / LPL) + lane / LPL;
         const bool in = j < m && t < k;
         if (VEC) {
-            uint4 c = make_uint4(0, 0, 0, 0);
+            uint4 c = make_uint4(nowhere, nowhere, nowhere, nowhere);
             if (in) c = *reinterpret_cast<const uint4*>(idx + j * k + t);
             p.c[0] = c.x; p.c[1] = c.y; p.c[2] = c.z; p.c[3] = c.w;
             if constexpr (sizeof(TS) == 4) {
@@ -209,7 +213,7 @@ k_forward_few(const char* __restrict__ xi, const int32_t* __restrict__ idx, cons
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const bool inq = j < m && t + q < k;
-                p.c[q] = inq ? (uint32_t)idx[j * k + t + q] : 0u;
+                p.c[q] = inq ? (uint32_t)idx[j * k + t + q] : nowhere;
                 if constexpr (sizeof(TS) == 4) p.w[q] = inq ? __float_as_uint(W[j * k + t + q]) : 0u;
                 else if (q & 1) p.w[q / 2] |= inq ? (uint32_t)W[j * k + t + q] << 16 : 0u;
                 else p.w[q / 2] = inq ? (uint32_t)W[j * k + t + q] : 0u;
@@ -282,6 +286,27 @@ k_forward_few(const char* __restrict__ xi, const int32_t* __restrict__ idx, cons
 #pragma unroll
             for (int i = 0; i < Q; ++i)
                 if (i < b) out[(size_t)i * m + j] = sum[i];
+        }
+    }
+}
+
+// out[i][:] once more, slot by slot, for the instances whose activation 0 is not finite (see pads_with_column_0): nearly
+// always none, and a block that finds none leaves.  A lane per label.
+template <typename TS>
+__global__ void __launch_bounds__(256)
+k_forward_again(const TS* __restrict__ x, const int32_t* __restrict__ idx, const TS* __restrict__ W, float* __restrict__ out, int64_t m, int d,
+                int k, int b) {
+    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    for (int i0 = 0; i0 < b; i0 += 64) {
+        const float v = i0 + lane < b ? usl_load_f32<TS>(x, (size_t)(i0 + lane) * d) : 0.f;
+        uint64_t todo = __ballot((__float_as_uint(v) & 0x7F800000u) == 0x7F800000u);
+        for (; todo; todo &= todo - 1) {
+            const int i = i0 + __ffsll((unsigned long long)todo) - 1;
+            if (j >= m) continue;
+            float acc = 0.f;
+            for (int t = 0; t < k; ++t) acc = fmaf(usl_load_f32<TS>(W, (size_t)j * k + t), usl_load_f32<TS>(x, (size_t)i * d + idx[j * k + t]), acc);
+            out[(size_t)i * m + j] = acc;
         }
     }
 }
@@ -380,15 +405,19 @@ Layout layout_of(const usl_ctx* c, int b, const void* x) {
         L.zero_col = L.K > c->k ? c->d : 0;
         if (L.row_bytes <= ROW_LDS_MAX && cols <= 65536) return L;
     }
-    // a float32 row in two halves (or the widest bfloat16 row with padded fan-in, whose zero column would be number
-    // 65536): padding slots read column 0, with weight 0
+    // a float32 row in two halves, or the widest bfloat16 row with padded fan-in
+    const bool zeros = L.K > c->k && c->d < 65536;
     L.Q = 1;
-    L.zero_col = 0;
-    L.copy = (size_t)c->d * es % 16 != 0 || (uintptr_t)x % 16 != 0;
-    L.row_bytes = (c->d * es + 15) / 16 * 16;
+    L.zero_col = zeros ? c->d : 0;
+    L.copy = zeros || (size_t)c->d * es % 16 != 0 || (uintptr_t)x % 16 != 0;
+    L.row_bytes = ((c->d + (zeros ? 1 : 0)) * es + 15) / 16 * 16;
     L.halves = L.row_bytes > ROW_LDS_MAX;
     return L;
 }
+
+// At d = 65536 a column of zeros would be number 65536, which does not fit the 16 bits of a packed index: padding slots read
+// column 0 there, with weight 0, and instances whose activation 0 is not finite are done again (k_forward_again).
+bool pads_with_column_0(const usl_ctx* c, const Layout& L) { return L.K > c->k && c->d == 65536; }
 
 ProductKernel kernel_for(const usl_ctx* c, const Layout& L, ProductKind kind, int shape) {
     if (c->storage == USL_F32)
@@ -552,8 +581,8 @@ usl_status run_forward_few(usl_ctx* c, const Layout& L, const void* x, const int
     const int64_t waves = wavefronts();
     const int nw = waves >= (int64_t)c->num_cu * 16 ? 16 : waves >= (int64_t)c->num_cu * 8 ? 8 : 4;
     const int64_t blocks = (waves + nw - 1) / nw;
-    const size_t lds = (size_t)L.row_bytes;
-    const int by_lds = (int)((size_t)(160 * 1024) / (lds ? lds : 1)), resident = by_lds < 32 / nw ? (by_lds < 1 ? 1 : by_lds) : 32 / nw;
+    const size_t lds = (size_t)L.row_bytes + 16;
+    const int by_lds = (int)((size_t)(160 * 1024) / lds), resident = by_lds < 32 / nw ? (by_lds < 1 ? 1 : by_lds) : 32 / nw;
     const unsigned grid = (unsigned)(blocks < (int64_t)c->num_cu * resident ? blocks : (int64_t)c->num_cu * resident);
     const bool vec = c->k % 4 == 0;
 #define USL_FEW(LPL, TS, Q, VEC)                                                                                    \
@@ -706,11 +735,19 @@ usl_status usl_launch_forward(usl_ctx* c, const void* x, const int32_t* idx, con
         return c->storage == USL_F32 ? run_forward_generic<float>(c, x, idx, W, out, b) : run_forward_generic<uint16_t>(c, x, idx, W, out, b);
     const Layout L = layout_of(c, b, x);
     if (streams(c, L, b)) return run_forward_few(c, L, x, idx, W, out, b);
-    return run_forward(c, L, x, idx, W, out, b, LossArgs{-1, 0.f, nullptr, nullptr}, nullptr);
+    USL_TRY(run_forward(c, L, x, idx, W, out, b, LossArgs{-1, 0.f, nullptr, nullptr}, nullptr));
+    if (!pads_with_column_0(c, L)) return USL_OK;
+    const dim3 grid((unsigned)((c->m + 255) / 256));
+    if (c->storage == USL_F32)
+        hipLaunchKernelGGL(k_forward_again<float>, grid, dim3(256), 0, c->stream, (const float*)x, idx, (const float*)W, out, c->m, c->d, c->k, b);
+    else
+        hipLaunchKernelGGL(k_forward_again<uint16_t>, grid, dim3(256), 0, c->stream, (const uint16_t*)x, idx, (const uint16_t*)W, out, c->m, c->d, c->k, b);
+    return usl_check_launch(c, "forward (activations that are not finite)");
 }
 
 bool usl_forward_loss_applies(const usl_ctx* c, const void* x, const int32_t* idx, const void* W, int32_t b) {
-    return fast_path_ok(c, idx, W) && !streams(c, layout_of(c, b, x), b);
+    const Layout L = layout_of(c, b, x);
+    return fast_path_ok(c, idx, W) && !streams(c, L, b) && !pads_with_column_0(c, L);   // (scores are done again, their losses not)
 }
 
 usl_status usl_launch_forward_loss(usl_ctx* c, const void* x, const int32_t* idx, const void* W, float* g, int32_t b, int loss_kind,

@@ -15,7 +15,8 @@
 // column of zeros) costs one pass over b * d values; it also takes the alignment of d out of the row copies.  Q = 1
 // needs no copy when rows of x are 16-byte aligned already.
 //
-// Fan-ins are padded to K, the next multiple of 8 up to 64; padding slots have weight 0 and read the column of zeros.
+// Fan-ins are padded to K, the next multiple of 8 up to 32, 48 or 64; padding slots have weight 0 and read the column of
+// zeros (a real column times weight 0 would make NaN of an infinity that the label has no connection to).
 #pragma once
 #include "usl_internal.h"
 
