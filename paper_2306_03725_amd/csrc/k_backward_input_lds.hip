@@ -1400,31 +1400,6 @@ usl_status usl_bwi_lds_run(usl_ctx* c, const float* g, const int32_t* idx, const
     return usl_check_launch(c, "backward_input (LDS form)");
 }
 
-// Parts of the batch in k_both_lds: more than one where the (window, feature block) workgroups leave compute
-// units idle.  A workgroup loads its lists and weights and hands out its sums in about 20 us, a pass of its loop takes
-// about 4.4 (m = 31k, d = 1k, k = 32, b = 128: 187 us with 1 part, 117 with 2, 83 with 4, 75 with 6, 100 with 8, which are
-// two rounds); every part writes a weight gradient of its own, which the reader adds up.
-static int both_parts(const usl_ctx* c, const Cut& cut, int rows, int Q) {
-    const int64_t wgs = (int64_t)cut.nwin * cut.nfb, passes = (rows + Q - 1) / Q, cu = c->num_cu;
-    if (const char* e = getenv("USL_TUNE_BOTH_PARTS")) return atoi(e) > 0 ? (atoi(e) < passes ? atoi(e) : (int)passes) : 1;
-    int best = 1;
-    double best_t = 0.0;
-    for (int P = 1; P <= 32 && P <= passes; ++P) {
-        if ((size_t)P * c->m * c->k * 4 > ((size_t)1 << 28) && P > 1) break;
-        const double rounds = (double)((wgs * P + cu - 1) / cu);
-        const double t = rounds * (20.0 + 4.4 * (double)((passes + P - 1) / P)) + (double)P * c->m * c->k * 8 / 4e6;
-        if (P == 1 || t < best_t) { best = P; best_t = t; }
-    }
-    return best;
-}
-
-// Chains of windows in k_both_lds: as many as the compute units have room for, where there are more windows than that.
-static int both_chains(const usl_ctx* c, const Cut& cut) {
-    const int at_once = c->num_cu > cut.nfb ? c->num_cu / cut.nfb : 1;
-    const int rounds = (cut.nwin + at_once - 1) / at_once;
-    return (cut.nwin + rounds - 1) / rounds;
-}
-
 // grad_x[b][d] and the weight gradient from g[b][m] and x[b][d].  The weight gradient is left in the order of the lists:
 // slot f's is the sum over p < *parts of (*stage)[p * *part_stride + (*pos)[f]] (usl_launch_adam_staged takes it from
 // there); both arrays belong to the context and hold until the next call or a change of idx.  A stale idx (see usl_check)
@@ -1437,15 +1412,19 @@ usl_status usl_both_lds_run(usl_ctx* c, const float* g, const void* x, const int
     const size_t N = (size_t)c->m * c->k, nbins = (size_t)cut.nwin * cut.vd, rkn = (size_t)cut.nwin * cut.nfb * (Q == 4 ? KT_BOTH4 : KT_BOTH) * NT;
     if (Q == 4) USL_TRY(lf_ready<KT_BOTH4>(c, idx, 1, cut));
     else USL_TRY(lf_ready<KT_BOTH>(c, idx, 1, cut));
-    const int chains_of_all = both_chains(c, cut);
-    const int G = pass_rows(c, chains_of_all, Q);
-    const int parts = b <= G ? both_parts(c, cut, b, Q) : 1;
-    const int most = c->max_b <= G ? both_parts(c, cut, c->max_b, Q) : 1;   // scratch for the largest batch too
-    const int chains = parts > 1 ? cut.nwin : chains_of_all;
-    USL_TRY(usl_reserve(c, (void**)&L.partial, &L.partial_cap, (size_t)(most > 1 ? cut.nwin : chains_of_all) * G * dp * 4));
-    if (chains > chains_of_all) USL_TRY(usl_reserve(c, (void**)&L.partial, &L.partial_cap, (size_t)chains * b * dp * 4));
+    int forced = 0;   // parts of the batch (tests)
+    if (const char* e = getenv("USL_TUNE_BOTH_PARTS")) forced = atoi(e) > 0 ? atoi(e) : 1;
+    const int G = pass_rows(c, both_chains(cut, c->num_cu), Q);
+    const BothPlan plan = both_plan(cut, c->m, c->k, c->num_cu, b, G, Q, forced);
+    if (!L.most_parts || forced) {   // scratch for every batch that a later call can bring
+        const BothMost most = both_most(cut, c->m, c->k, c->num_cu, c->max_b, G, Q, forced);
+        L.most_parts = most.parts;
+        L.most_rows = most.rows;
+    }
+    const int parts = plan.parts, chains = plan.sets;
+    USL_TRY(usl_reserve(c, (void**)&L.partial, &L.partial_cap, L.most_rows * dp * 4));
     // per part: stage [N], the sums of the overflow entries beyond LDS [N + nbins]
-    const size_t keep = (size_t)(parts > most ? parts : most);
+    const size_t keep = (size_t)L.most_parts;
     USL_TRY(usl_reserve(c, (void**)&L.stage, &L.stage_cap, keep * (N + N + nbins) * 4));
     float* ovgw = L.stage + keep * N;
     const void* xs = nullptr;

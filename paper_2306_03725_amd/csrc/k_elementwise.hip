@@ -366,12 +366,12 @@ k_adam_staged(TS* __restrict__ W, const float* __restrict__ stage, const uint32_
 
 }  // namespace
 
-// Per-block loss sums of either loss kernel, sized once for max_b instances: a later, larger batch never
-// has to grow the buffer (growing frees and allocates, which waits for the stream).
-static usl_status usl_reserve_loss_partials(usl_ctx* c) {
+usl_status usl_reserve_loss_partials(usl_ctx* c) {
     const size_t rows = (size_t)((c->m + BCE_CHUNK - 1) / BCE_CHUNK) * (size_t)c->max_b;
     const size_t tiles = (size_t)((c->m + LT_TL - 1) / LT_TL) * (size_t)((c->max_b + 31) / 32);
-    return usl_reserve(c, (void**)&c->bce_partials, &c->bce_partials_cap, (rows > tiles ? rows : tiles) * sizeof(double));
+    const size_t forward = usl_forward_blocks(c) + (size_t)c->max_b;   // and one for every instance's targets
+    const size_t most = rows > tiles ? rows : tiles;
+    return usl_reserve(c, (void**)&c->bce_partials, &c->bce_partials_cap, (most > forward ? most : forward) * sizeof(double));
 }
 
 usl_status usl_launch_loss(usl_ctx* c, int loss_kind, const float* out, const int64_t* tgt_off,

@@ -1,6 +1,7 @@
 // How a layer is cut up for the kernels that keep the connections of a window of labels in registers
 // (k_backward_input_lds.hip).  Plain arithmetic on the layer's sizes: no GPU is needed to check it.
 #pragma once
+#include <stddef.h>
 #include <stdint.h>
 
 namespace usl_lists {
@@ -85,6 +86,54 @@ inline Cut both_cut(int64_t m, int d, int k, int num_cu) {
         cut.nwin = (int)((m + cut.wl - 1) / cut.wl);
     }
     return cut;
+}
+
+// Parts of the batch in the kernel for both products: more than one where the (window, feature block) workgroups leave
+// compute units idle.  A workgroup loads its lists and weights and hands out its sums in about 20 us, a pass of its loop
+// takes about 4.4 (m = 31k, d = 1k, k = 32, b = 128: 187 us with 1 part, 117 with 2, 83 with 4, 75 with 6, 100 with 8, which
+// are two rounds); every part writes a weight gradient of its own, which the reader adds up.  forced > 0: that many, if
+// the batch has them.
+inline int both_parts(const Cut& cut, int64_t m, int k, int num_cu, int rows, int Q, int forced) {
+    const int64_t wgs = (int64_t)cut.nwin * cut.nfb, passes = (rows + Q - 1) / Q, cu = num_cu;
+    if (forced > 0) return (int)(forced < passes ? forced : passes);
+    int best = 1;
+    double best_t = 0.0;
+    for (int P = 1; P <= 32 && P <= passes; ++P) {
+        if ((size_t)P * m * k * 4 > ((size_t)1 << 28) && P > 1) break;
+        const double rounds = (double)((wgs * P + cu - 1) / cu);
+        const double t = rounds * (20.0 + 4.4 * (double)((passes + P - 1) / P)) + (double)P * m * k * 8 / 4e6;
+        if (P == 1 || t < best_t) { best = P; best_t = t; }
+    }
+    return best;
+}
+
+// Chains of windows: as many as the compute units have room for, where there are more windows than that.
+inline int both_chains(const Cut& cut, int num_cu) {
+    const int at_once = num_cu > cut.nfb ? num_cu / cut.nfb : 1;
+    const int rounds = (cut.nwin + at_once - 1) / at_once;
+    return (cut.nwin + rounds - 1) / rounds;
+}
+
+// How a batch of `rows` instances goes through: in passes of at most G, one part each, or at once in several parts.
+// sets: sums of the input gradient that are kept beside each other.
+struct BothPlan { int parts, sets; };
+inline BothPlan both_plan(const Cut& cut, int64_t m, int k, int num_cu, int rows, int G, int Q, int forced) {
+    BothPlan p;
+    p.parts = rows <= G ? both_parts(cut, m, k, num_cu, rows, Q, forced) : 1;
+    p.sets = p.parts > 1 ? cut.nwin : both_chains(cut, num_cu);
+    return p;
+}
+// The most that any batch of up to max_b instances takes, of parts and of rows of input-gradient sums (sets times
+// instances): neither grows with the batch (m = 13 330, d = 5000, k = 32: 12 parts at 96 instances, 11 at 128).
+struct BothMost { int parts; size_t rows; };
+inline BothMost both_most(const Cut& cut, int64_t m, int k, int num_cu, int max_b, int G, int Q, int forced) {
+    BothMost most = {1, (size_t)both_chains(cut, num_cu) * (size_t)(G < max_b ? G : max_b)};
+    for (int b = max_b < G ? max_b : G; b >= 1; b = (b - 1) / Q * Q) {   // the largest batch of every number of passes
+        const BothPlan p = both_plan(cut, m, k, num_cu, b, G, Q, forced);
+        if (p.parts > most.parts) most.parts = p.parts;
+        if ((size_t)p.sets * (size_t)b > most.rows) most.rows = (size_t)p.sets * (size_t)b;
+    }
+    return most;
 }
 
 }  // namespace usl_lists

@@ -440,7 +440,7 @@ struct Launch {
 // per clock with every unit at it).  What a workgroup waits for alone: its prologue, a barrier and copy latency per
 // tile, and, with few wavefronts, the latency of a batch of reads (200 clocks).  The weight gradient of a split batch
 // is written and read once more per part.  Within 25 % of 40 measured launches, and the best or within 10 % of it there.
-Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind) {
+Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int most_parts = 65535) {
     const bool backward = kind == WEIGHT_GRADIENT;
     const int es = c->storage == USL_F32 ? 4 : 2, unit = L.Q * es;
     const int groups = (b + L.Q - 1) / L.Q;
@@ -480,9 +480,10 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind) {
             if (split_force > 0 && G > 1) break;
             const int split = split_force > 0 ? split_force : G, gpb = (groups + split - 1) / split;
             const int64_t parts = (groups + gpb - 1) / gpb;   // those that have work
-            if (parts > 65535) break;
+            if (parts > most_parts && parts > 1) break;
             if (backward && parts > 1 && (size_t)parts * c->m * c->k * 4 > ((size_t)1 << 29)) break;
             const int64_t wgs = nblk * parts;
+            if (kind == FORWARD_LOSS && parts > 1 && (size_t)wgs > usl_forward_blocks(c)) break;
             const double most = (double)((wgs + cus - 1) / cus);      // workgroups the busiest compute unit runs
             const double per_cu = wgs > cus ? 0.75 * most + 0.25 * wgs / cus : most;
             const double rounds = (double)((wgs + (int64_t)cus * res - 1) / ((int64_t)cus * res));
@@ -716,10 +717,9 @@ usl_status run_forward(usl_ctx* c, const Layout& L, const void* x, const int32_t
     int64_t m = c->m;
     int k = c->k, bb = b;
     Geom tg = p.geom;
-    if (loss.kind >= 0) {   // sized once for max_b: a part of the batch to every block, or parts until the chip is full several times
-        const size_t most = (size_t)((c->m + 255) / 256) + (size_t)c->num_cu * 32 + (size_t)c->max_b;
+    if (loss.kind >= 0) {
         *blocks = (size_t)p.nblk * (size_t)p.G;
-        USL_TRY(usl_reserve(c, (void**)&c->bce_partials, &c->bce_partials_cap, max_sz(most, *blocks + (size_t)b) * sizeof(double)));
+        USL_TRY(usl_reserve_loss_partials(c));
         loss.partials = c->bce_partials;
     }
     void* args[] = {&xi, &idx, &W, &out, &m, &k, &bb, &tg, &perm, &loss};
@@ -789,12 +789,28 @@ usl_status usl_activation_rows(usl_ctx* c, const void* x, int32_t b, int Q, cons
     return USL_OK;
 }
 
+// Parts of the batch that the weight gradient's scratch has room for: the most that the largest batch or a half, a quarter
+// or an eighth of it would take.  A batch in between makes do with them.
+static int weight_gradient_parts(usl_ctx* c, const void* x) {
+    if (tune_split() > 0) return 65535;
+    if (!c->gw_parts_most) {
+        int most = 1;
+        for (int b = c->max_b, q = 0; b >= 1 && q < 4; b /= 2, ++q) {
+            const int G = choose(c, layout_of(c, b, x), b, WEIGHT_GRADIENT).G;
+            if (G > most) most = G;
+        }
+        c->gw_parts_most = most;
+    }
+    return c->gw_parts_most;
+}
+
 usl_status usl_launch_backward_weight(usl_ctx* c, const float* g, const void* x, const int32_t* idx, float* grad_W, int32_t b, bool dense) {
     if (!fast_path_ok(c, idx, nullptr) || (uintptr_t)grad_W % 16 != 0)
         return c->storage == USL_F32 ? run_backward_weight_generic<float>(c, g, x, idx, grad_W, b)
                                      : run_backward_weight_generic<uint16_t>(c, g, x, idx, grad_W, b);
     const Layout L = layout_of(c, b, x);
-    const Launch p = choose(c, L, b, WEIGHT_GRADIENT);
+    const int most_parts = weight_gradient_parts(c, x);
+    const Launch p = choose(c, L, b, WEIGHT_GRADIENT, most_parts);
     const uint8_t* perm = nullptr;
     const void* xi = nullptr;
     USL_TRY(slot_order(c, idx, &perm));
@@ -808,15 +824,13 @@ usl_status usl_launch_backward_weight(usl_ctx* c, const float* g, const void* x,
     }
     USL_TRY(activations(c, L, x, b, &xi));
     const size_t N = (size_t)c->m * c->k;
-    size_t stride = 0;
+    // a batch in several parts: partial gradients in scratch, summed afterwards in a fixed order (no atomics, reproducible)
+    size_t stride = (N + 3) / 4 * 4;
     float* dst = grad_W;
-    if (p.G > 1) {   // G partial gradients in scratch, summed afterwards in a fixed order (no atomics, reproducible)
-        stride = (N + 3) / 4 * 4;
-        size_t parts = (size_t)p.G;   // sized once, for the batch of max_b instances too: never grown by a later call
-        if (b < c->max_b) parts = max_sz(parts, (size_t)choose(c, layout_of(c, c->max_b, x), c->max_b, WEIGHT_GRADIENT).G);
-        USL_TRY(usl_reserve(c, (void**)&c->gw_part, &c->gw_part_cap, parts * stride * 4));
-        dst = c->gw_part;
-    }
+    const size_t parts = (size_t)(most_parts < 65535 ? most_parts : p.G);
+    if (parts > 1) USL_TRY(usl_reserve(c, (void**)&c->gw_part, &c->gw_part_cap, parts * stride * 4));   // also for a batch in one part: never in a later call
+    if (p.G > 1) dst = c->gw_part;
+    else stride = 0;
     int64_t m = c->m;
     int k = c->k, bb = b;
     Geom tg = p.geom;

@@ -58,6 +58,7 @@ struct usl_ctx {
     float* predict_out;       size_t predict_out_cap;   // [chunk][m] scores of usl_predict, one chunk of instances at a time
     uint64_t* topk_cand;      size_t topk_cand_cap;  // [b][segments][kk] packed (score, label) keys
     float* gw_part;           size_t gw_part_cap;   // [groups][m*k] partial weight gradients of a split batch
+    int gw_parts_most;             // groups that it has room for (0: not known yet)
     float* gxT;               size_t gxT_cap;  // [tiles][d][32] input gradient in the same layout
     // per-instance lists of the nonzero entries of g (k_sparse_grad.hip)
     uint32_t* nz_state;       size_t nz_state_cap;   // [0] = 1: gradient is dense, lists abandoned; [16+i] = entries of instance i
@@ -88,7 +89,8 @@ struct usl_ctx {
         void* ov;                                  // overflow entries
         float* stage;         size_t stage_cap;    // [1] only: the weight gradient in list order, [wg][slots][1024], then one per overflow entry
         uint32_t* pos;                             // [1] only: [m*k] where a slot's weight gradient is in stage
-        float* partial;       size_t partial_cap;  // [nwin][rows of a pass][d]
+        float* partial;       size_t partial_cap;  // [nwin or chains of windows][rows of a pass][d]
+        int most_parts;       size_t most_rows;    // [1] only: what the largest need of any batch is (0: not known yet)
         const int32_t* built_for;                  // idx pointer the lists were built from (NULL = stale)
     } lf[2];
 };
@@ -116,6 +118,10 @@ struct usl_ctx {
 usl_status usl_prepare_device(usl_ctx* ctx);
 // Grows *buf to at least `bytes` (old contents are dropped).
 usl_status usl_reserve(usl_ctx* ctx, void** buf, size_t* cap, size_t bytes);
+// The per-block loss sums of every loss kernel, for max_b instances: no later call has to grow them (growing frees and
+// allocates, which waits for the stream).  usl_forward_blocks: workgroups that forward may have when it sums the loss.
+usl_status usl_reserve_loss_partials(usl_ctx* ctx);
+static inline size_t usl_forward_blocks(const usl_ctx* c) { return (size_t)((c->m + 255) / 256) + (size_t)c->num_cu * 32; }
 usl_status usl_check_launch(usl_ctx* ctx, const char* what);
 
 // K = padded fan-in, unit = bytes per column of the rows that will be gathered (4, 8 or 16; 2: single bfloat16)

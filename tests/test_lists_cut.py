@@ -55,3 +55,41 @@ def run_host_check(tmp_path, text, *more):
 def test_every_window_has_labels(tmp_path):
     r = run_host_check(tmp_path, CHECK)
     assert r.returncode == 0, r.stdout
+
+
+MOST = r"""
+#include <stdio.h>
+#include "k_lists_cut.h"
+using namespace usl_lists;
+int main() {
+    long bad = 0, drops = 0;
+    unsigned long long r = 88172645463325252ull;
+    auto next = [&]() { r ^= r << 13; r ^= r >> 7; r ^= r << 17; return r; };
+    for (int n = 0; n < 3000; ++n) {
+        long long m = n == 0 ? 13330 : 1 + (long long)(next() % (1ull << (4 + next() % 18)));
+        const int d = n == 0 ? 5000 : 1 + (int)(next() % (1u << (1 + next() % 16)));
+        int k = n == 0 ? 32 : 1 + (int)(next() % 64);
+        if (k > d) k = d;
+        const int max_b = n == 0 ? 128 : 1 + (int)(next() % 700), Q = both_q(d, k), forced = n % 5 == 4 ? 1 + (int)(next() % 8) : 0;
+        const int G = n == 0 || n % 3 ? max_b : 1 + (int)(next() % max_b);
+        const Cut cut = both_cut(m, d, k, 256);
+        const BothMost most = both_most(cut, m, k, 256, max_b, G, Q, forced);
+        int last = 0;
+        for (int b = 1; b <= max_b; ++b) {
+            const BothPlan p = both_plan(cut, m, k, 256, b, G, Q, forced);
+            const long long rows = (long long)p.sets * (b < G ? b : G);
+            if (p.parts > most.parts || rows > (long long)most.rows) ++bad;
+            if (p.parts < last) ++drops;
+            last = p.parts;
+        }
+    }
+    printf("%ld bad, %ld larger batches with fewer parts\n", bad, drops);
+    return bad != 0 || drops == 0;
+}
+"""
+
+
+def test_scratch_of_the_largest_need_covers_every_batch(tmp_path):
+    """The parts of a batch do not grow with it; what is reserved once is what the neediest batch takes."""
+    r = run_host_check(tmp_path, MOST)
+    assert r.returncode == 0, r.stdout
