@@ -36,8 +36,8 @@ __global__ void k_zero_u32(uint32_t* p, size_t n) {
 }
 
 __global__ void __launch_bounds__(1024)
-k_idx_fingerprint(const uint32_t* __restrict__ idx, size_t n_words, uint64_t* __restrict__ print, int store) {
-    usl_idx_fingerprint_block(idx, n_words, print, store);
+k_idx_fingerprint(const uint32_t* __restrict__ idx, size_t n_words, uint64_t* __restrict__ print, int which, int store) {
+    usl_idx_fingerprint_block(idx, n_words, print, which, store);
 }
 
 // Lists are grouped by (label window, feature).  A workgroup takes one of `splits` equal shares of
@@ -208,7 +208,7 @@ k_gather_w(const TS* __restrict__ W, const uint32_t* __restrict__ slot, const ui
            const uint32_t* __restrict__ idx_check /* or NULL */, size_t n_words, uint64_t* __restrict__ print) {
     if (gate && *gate == 0) return;   // the sparse kernels do this call's work
     // the first workgroup also checks that idx still holds what the lists were built from (see usl_idx_fingerprint_block)
-    if (idx_check && blockIdx.x == 0) usl_idx_fingerprint_block(idx_check, n_words, print, 0);
+    if (idx_check && blockIdx.x == 0) usl_idx_fingerprint_block(idx_check, n_words, print, USL_PRINT_COLUMNS, 0);
     int w, local;
     if (nwin >= 8) {
         const int xcd = blockIdx.x & 7;
@@ -491,23 +491,22 @@ usl_status build_csc(usl_ctx* c, const int32_t* idx) {
     hipLaunchKernelGGL(k_zero_u32, dim3(c->num_cu), dim3(256), 0, c->stream, c->csc_cursor, nbins);
     hipLaunchKernelGGL(k_csc_fill, cgrid, dim3(CSC_NT), clds, c->stream, idx, c->m, c->k, c->d, wl,
                        splits, c->csc_ptr, rank_of, c->csc_cursor, c->csc_slot);
-    USL_TRY(usl_idx_fingerprint(c, idx, 1));
+    USL_TRY(usl_idx_fingerprint(c, idx, USL_PRINT_COLUMNS, 1));
     USL_TRY(usl_check_launch(c, "column lists"));
     c->csc_built_for = idx;
-    c->lf[0].built_for = c->lf[1].built_for = nullptr;   // one fingerprint: it belongs to the lists built last
     return USL_OK;
 }
 
 }  // namespace
 
-usl_status usl_idx_fingerprint(usl_ctx* c, const int32_t* idx, int store) {
+usl_status usl_idx_fingerprint(usl_ctx* c, const int32_t* idx, int which, int store) {
     if (!c->idx_print) {
         size_t cap = 0;
         USL_TRY(usl_reserve(c, (void**)&c->idx_print, &cap, 64));
         hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, c->stream, reinterpret_cast<uint32_t*>(c->idx_print), (size_t)16);
     }
     hipLaunchKernelGGL(k_idx_fingerprint, dim3(1), dim3(1024), 0, c->stream, reinterpret_cast<const uint32_t*>(idx),
-                       (size_t)c->m * c->k, c->idx_print, store);
+                       (size_t)c->m * c->k, c->idx_print, which, store);
     return USL_OK;
 }
 
@@ -591,7 +590,7 @@ usl_status usl_bwd_input_group(usl_ctx* c, float* grad_x_rows, int32_t rows, uin
     {
         dim3 grid2((unsigned)((c->d + 31) / 32), (unsigned)ntile);
         hipLaunchKernelGGL(k_untile, grid2, dim3(256), 0, c->stream, c->gxT, grad_x_rows, (int64_t)rows, (int64_t)c->d, gate,
-                           reinterpret_cast<const uint32_t*>(c->idx_print) + 4);
+                           usl_stale_word(c));
     }
     return usl_check_launch(c, "backward_input");
 }

@@ -1317,11 +1317,8 @@ static usl_status lf_build_t(usl_ctx* c, const int32_t* idx, int set, const Cut&
     if (Q == 4) USL_LF_SCHED(16);
     else USL_LF_SCHED(32);
 #undef USL_LF_SCHED
-    USL_TRY(usl_idx_fingerprint(c, idx, 1));
+    USL_TRY(usl_idx_fingerprint(c, idx, set == 1 ? USL_PRINT_BOTH_PRODUCTS : USL_PRINT_ONE_PRODUCT, 1));
     USL_TRY(usl_check_launch(c, "register lists of the input gradient"));
-    // one fingerprint: it belongs to the lists built last
-    c->csc_built_for = nullptr;
-    c->lf[0].built_for = c->lf[1].built_for = nullptr;
     L.built_for = idx;
     return USL_OK;
 }
@@ -1331,7 +1328,7 @@ static usl_status lf_build_t(usl_ctx* c, const int32_t* idx, int set, const Cut&
 template <int KT>
 static usl_status lf_ready(usl_ctx* c, const int32_t* idx, int set, const Cut& cut) {
     if (c->lf[set].built_for != idx) return lf_build_t<KT>(c, idx, set, cut);
-    return set == 1 && c->print_done ? USL_OK : usl_idx_fingerprint(c, idx, 0);
+    return set == 1 && c->print_done ? USL_OK : usl_idx_fingerprint(c, idx, set == 1 ? USL_PRINT_BOTH_PRODUCTS : USL_PRINT_ONE_PRODUCT, 0);
 }
 
 // Instances per pass over the batch: every pass loads the lists and the weights anew, and its partial sums are sets * G * d
@@ -1350,7 +1347,7 @@ static void lf_reduce(usl_ctx* c, const float* partial, int sets, int rows, bool
     const int dp = padded_d(c);
     const size_t n4 = (size_t)rows * dp / 4;
     const bool vec = dp == c->d && (uintptr_t)grad_x % 16 == 0;
-    const uint32_t* stale = reinterpret_cast<const uint32_t*>(c->idx_print) + 4;
+    const uint32_t* stale = usl_stale_word(c);
     size_t blocks = (n4 + 255) / 256;
     if (blocks > (size_t)c->num_cu * 8) blocks = (size_t)c->num_cu * 8;
     if (both)
@@ -1430,7 +1427,7 @@ usl_status usl_both_lds_run(usl_ctx* c, const float* g, const void* x, const int
     const void* xs = nullptr;
     size_t x_stride = 0;
     USL_TRY(usl_activation_rows(c, x, b, Q == 4 ? 4 : 1, &xs, &x_stride));
-    out->stale = reinterpret_cast<const uint32_t*>(c->idx_print) + 4;
+    out->stale = usl_stale_word(c);
     const bool direct = chains == 1 && dp == c->d && (uintptr_t)grad_x % 16 == 0;   // nothing to add up
     static bool checked[4] = {false, false, false, false};
     for (int i0 = 0; i0 < b; i0 += G) {

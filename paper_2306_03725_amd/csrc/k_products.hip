@@ -637,7 +637,7 @@ k_loss_positives(const TS* __restrict__ x, const int32_t* __restrict__ idx, cons
     __shared__ double red[16];
     const int i = blockIdx.x;
     if (i == b) {
-        usl_idx_fingerprint_block(reinterpret_cast<const uint32_t*>(idx), n_words, print, 0);
+        usl_idx_fingerprint_block(reinterpret_cast<const uint32_t*>(idx), n_words, print, USL_PRINT_BOTH_PRODUCTS, 0);
         return;
     }
     const int64_t p1 = tgt_off[i + 1];

@@ -496,14 +496,14 @@ extern "C" usl_status usl_check(usl_ctx* c) {
     USL_HIP(c, hipStreamSynchronize(c->stream));
     if (c->idx_print) {
         uint32_t stale = 0;
-        USL_HIP(c, hipMemcpy(&stale, reinterpret_cast<uint32_t*>(c->idx_print) + 4, 4, hipMemcpyDeviceToHost));
+        USL_HIP(c, hipMemcpy(&stale, usl_stale_word(c), 4, hipMemcpyDeviceToHost));
         if (stale) {
-            USL_HIP(c, hipMemset(reinterpret_cast<uint32_t*>(c->idx_print) + 4, 0, 4));
+            USL_HIP(c, hipMemset(usl_stale_word(c), 0, 4));
             c->csc_built_for = nullptr;
             c->lf[0].built_for = c->lf[1].built_for = nullptr;
             c->slot_order_for = nullptr;
-            USL_FAIL(c, USL_ESTALE, "idx changed without usl_invalidate: a usl_backward_input call since the last "
-                                    "check ran on column lists of the old contents and filled grad_x with NaN");
+            USL_FAIL(c, USL_ESTALE, "idx changed without usl_invalidate: a backward call since the last check ran on "
+                                    "lists of the old contents and filled its gradients with NaN");
         }
     }
     return USL_OK;

@@ -33,7 +33,8 @@ struct usl_ctx {
     uint32_t* csc_slot;       // [m*k] flat slot j*k+t, grouped by (label window, feature)
     float* csc_w;             // [m*k] W of that slot (refreshed by every backward_input)
     bool print_done;          // inside usl_train_step: the fingerprint of idx has been compared
-    uint64_t* idx_print;      // [0] fingerprint of idx when the lists were built; word [2] (32 bits): 1 = a later call found idx changed
+    uint64_t* idx_print;      // fingerprints of idx when each of the three kinds of lists was built (USL_PRINT_*), and the stale word:
+                              // 1 = a later call found idx changed
     const int32_t* idx_to_check;  // idx whose fingerprint the next weight gather compares (NULL right after a build)
     int csc_win_labels;       // labels per window the lists were built with
     const int32_t* csc_built_for;  // idx pointer the lists were built from (NULL = stale)
@@ -189,9 +190,12 @@ usl_status usl_activation_rows(usl_ctx* ctx, const void* x, int32_t b, int Q, co
 usl_status usl_launch_unstage(usl_ctx* ctx, const usl_staged& st, const uint32_t* gate, float* grad_W);
 usl_status usl_launch_adam_staged(usl_ctx* ctx, void* W, const usl_staged& st, const uint32_t* gate, float* grad_W, float* m1, float* m2,
                                   float lr, float beta1, float beta2, float eps, float inv_c1, float inv_c2, const usl_loss_sum& sum);
-// Records (store = 1) the fingerprint of idx in ctx->idx_print, or compares with the recorded one (store = 0) and
-// raises the stale word (32-bit word 4 of idx_print) on a difference.
-usl_status usl_idx_fingerprint(usl_ctx* ctx, const int32_t* idx, int store);
+// Places in ctx->idx_print: a fingerprint for each kind of lists (they are built and kept side by side), the stale word.
+enum { USL_PRINT_COLUMNS = 0, USL_PRINT_ONE_PRODUCT = 1, USL_PRINT_BOTH_PRODUCTS = 2, USL_PRINT_STALE = 4 };
+static inline uint32_t* usl_stale_word(usl_ctx* c) { return reinterpret_cast<uint32_t*>(c->idx_print + USL_PRINT_STALE); }
+// Records (store = 1) the fingerprint of idx for lists of the kind `which`, or compares with the recorded one (store = 0)
+// and raises the stale word on a difference.
+usl_status usl_idx_fingerprint(usl_ctx* ctx, const int32_t* idx, int which, int store);
 static inline uint32_t* usl_nz_cells(usl_ctx* c) { return reinterpret_cast<uint32_t*>(c->counter64) + 4; }
 // Loss and gradient in place on zg[b][m], which also leaves the gradient in c->gT (tile-major) with
 // its piece flags and sampled nonzero count (usl_bwd_input_prepare must have run); *sampled_labels
@@ -269,11 +273,11 @@ template <> __device__ __forceinline__ float usl_load_f32<uint16_t>(const uint16
 }
 // Fingerprint of idx: a sum of mixed 16-byte groups at up to 4096 evenly spaced places (64 KiB read by one
 // workgroup, every load in flight at once: a few microseconds).  store = 1 records it when the column lists
-// are built; store = 0 compares on a later call and raises print[2] (as a 32-bit word) when the contents are
+// are built; store = 0 compares on a later call and raises the stale word when the contents are
 // no longer those the lists were built from: a new tensor at a recycled address, a checkpoint copied in, ...
 // A single edited entry can slip through the sample; wholesale replacement cannot.
 __device__ __forceinline__ void usl_idx_fingerprint_block(const uint32_t* __restrict__ idx, size_t n_words,
-                                                      uint64_t* __restrict__ print, int store) {   // 1024 lanes
+                                                      uint64_t* __restrict__ print, int which, int store) {   // 1024 lanes
     __shared__ uint64_t red[16];
     const size_t groups = n_words / 4;
     const size_t samples = groups < 4096 ? groups : 4096;
@@ -303,8 +307,8 @@ __device__ __forceinline__ void usl_idx_fingerprint_block(const uint32_t* __rest
     if (threadIdx.x == 0) {
         uint64_t t = 0;
         for (int q = 0; q < 16; ++q) t += red[q];
-        if (store) { print[0] = t; }
-        else if (print[0] != t) reinterpret_cast<uint32_t*>(print)[4] = 1u;
+        if (store) print[which] = t;
+        else if (print[which] != t) *reinterpret_cast<uint32_t*>(print + USL_PRINT_STALE) = 1u;
     }
 }
 // The lanes whose reads meet in one pass of the LDS: 32 consecutive lanes (ds_read_b32, ds_read_b64), or, for
