@@ -499,12 +499,17 @@ usl_status build_csc(usl_ctx* c, const int32_t* idx) {
 
 }  // namespace
 
-usl_status usl_idx_fingerprint(usl_ctx* c, const int32_t* idx, int which, int store) {
+usl_status usl_idx_print_ready(usl_ctx* c) {
     if (!c->idx_print) {
         size_t cap = 0;
         USL_TRY(usl_reserve(c, (void**)&c->idx_print, &cap, 64));
         hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, c->stream, reinterpret_cast<uint32_t*>(c->idx_print), (size_t)16);
     }
+    return USL_OK;
+}
+
+usl_status usl_idx_fingerprint(usl_ctx* c, const int32_t* idx, int which, int store) {
+    USL_TRY(usl_idx_print_ready(c));
     hipLaunchKernelGGL(k_idx_fingerprint, dim3(1), dim3(1024), 0, c->stream, reinterpret_cast<const uint32_t*>(idx),
                        (size_t)c->m * c->k, c->idx_print, which, store);
     return USL_OK;

@@ -152,9 +152,22 @@ k_lf_plan(const uint32_t* __restrict__ count, int vd, int nfb, int fpb, uint32_t
         atomicAdd(&start[min(n[q], 255u)], 1u);
     }
     __syncthreads();
-    if (threadIdx.x == 0) {   // ranks of the buckets, longest lists first
-        uint32_t run = 0;
-        for (int q = 255; q >= 0; --q) { const uint32_t t = start[q]; start[q] = run; run += t; }
+    {   // ranks of the buckets, longest lists first: how many lists the buckets above hold, four buckets a lane
+        // (one lane going through all of them took 9 of this kernel's 16 us on a small layer)
+        uint32_t mine[4], above = 0;
+        if (threadIdx.x < 64) {
+            uint32_t sum = 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) sum += mine[u] = start[255 - 4 * threadIdx.x - u];
+            above = sum;
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t t = __shfl_up(above, o);
+                if ((int)threadIdx.x >= o) above += t;
+            }
+            above -= sum;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { start[255 - 4 * threadIdx.x - u] = above; above += mine[u]; }
+        }
     }
     __syncthreads();
     uint32_t lane_of[2], zone_of[2];
@@ -237,10 +250,18 @@ k_lf_plan(const uint32_t* __restrict__ count, int vd, int nfb, int fpb, uint32_t
     }
 }
 
-// ov_base[wg] = sum of ov_count over the workgroups before wg; ov_base[nwg] = all of them (one block).
+// base[wg] = sum of count over the workgroups before wg, base[nwg] = all of them: of the overflow entries (block 0) and of
+// all entries (block 1).  Block 2 records the fingerprint of idx.
+struct LfScan { const uint32_t* count[2]; uint32_t* base[2]; };
 __global__ void __launch_bounds__(1024)
-k_lf_scan(const uint32_t* __restrict__ ov_count, int nwg, uint32_t* __restrict__ ov_base) {
+k_lf_scan(LfScan what, int nwg, const uint32_t* __restrict__ idx, size_t n_words, uint64_t* __restrict__ print, int which) {
     __shared__ uint32_t part[1024];
+    if (blockIdx.x == 2) {
+        usl_idx_fingerprint_block(idx, n_words, print, which, 1);
+        return;
+    }
+    const uint32_t* ov_count = what.count[blockIdx.x];
+    uint32_t* ov_base = what.base[blockIdx.x];
     const int per = (nwg + 1023) / 1024;
     const int a = min(nwg, (int)threadIdx.x * per), e = min(nwg, a + per);
     uint32_t s = 0;
@@ -1277,8 +1298,7 @@ static usl_status lf_build_t(usl_ctx* c, const int32_t* idx, int set, const Cut&
             if (turn == 0) USL_TRY(usl_reserve(c, &L.mem, &L.mem_cap, total));
         }
     }
-    int rounds = 3;                // of proposals per step of the bank-aware order; 0 = lists stay as filled
-    if (const char* e = getenv("USL_TUNE_ROUNDS")) rounds = atoi(e);
+    const int rounds = usl_order_rounds(c);
     uint32_t* ov_base = L.ov_base;                   // [nwg + 1]
     uint32_t* n_ov = ov_base + nwg + 1;              // [nwg]
     uint32_t* ent_base = n_ov + nwg;                 // [nwg + 1]
@@ -1295,8 +1315,9 @@ static usl_status lf_build_t(usl_ctx* c, const int32_t* idx, int set, const Cut&
     hipLaunchKernelGGL(k_lf_count, grid, dim3(NT), lds, c->stream, idx, c->m, c->k, c->d, cut, splits, L.count);
     hipLaunchKernelGGL(k_lf_plan<KT>, dim3((unsigned)nwg), dim3(NT), 0, c->stream, L.count, cut.vd, nfb, cut.fpb, L.where, L.ovoff,
                        L.feat, L.caps, n_ent, n_ov, L.ovr);
-    hipLaunchKernelGGL(k_lf_scan, dim3(1), dim3(1024), 0, c->stream, n_ov, nwg, ov_base);
-    hipLaunchKernelGGL(k_lf_scan, dim3(1), dim3(1024), 0, c->stream, n_ent, nwg, ent_base);
+    USL_TRY(usl_idx_print_ready(c));
+    hipLaunchKernelGGL(k_lf_scan, dim3(3), dim3(1024), 0, c->stream, LfScan{{n_ov, n_ent}, {ov_base, ent_base}}, nwg,
+                       reinterpret_cast<const uint32_t*>(idx), N, c->idx_print, set == 1 ? USL_PRINT_BOTH_PRODUCTS : USL_PRINT_ONE_PRODUCT);
     hipLaunchKernelGGL(k_lf_fill, grid, dim3(NT), lds, c->stream, idx, c->m, c->k, c->d, cut, splits, L.where, L.taken,
                        ent_base, L.ent);
     if (set == 1) {   // where the weight gradients go (before the order of the lists, which hands the places on)
@@ -1317,7 +1338,6 @@ static usl_status lf_build_t(usl_ctx* c, const int32_t* idx, int set, const Cut&
     if (Q == 4) USL_LF_SCHED(16);
     else USL_LF_SCHED(32);
 #undef USL_LF_SCHED
-    USL_TRY(usl_idx_fingerprint(c, idx, set == 1 ? USL_PRINT_BOTH_PRODUCTS : USL_PRINT_ONE_PRODUCT, 1));
     USL_TRY(usl_check_launch(c, "register lists of the input gradient"));
     L.built_for = idx;
     return USL_OK;

@@ -70,8 +70,7 @@ __global__ void k_identity_order(int64_t n, int K, uint8_t* __restrict__ perm) {
 usl_status usl_build_slot_order(usl_ctx* c, const int32_t* idx, int K, int unit) {
     USL_TRY(usl_reserve(c, (void**)&c->slot_order, &c->slot_order_cap, (size_t)c->m * K));
     const int shift = unit == 2 ? 1 : 0;  // two single bfloat16 columns share a bank word
-    int rounds = 3;
-    if (const char* e = getenv("USL_TUNE_ROUNDS")) rounds = atoi(e);   // 0 = slots in stored order
+    const int rounds = usl_order_rounds(c);
     const unsigned grid = (unsigned)((c->m + SCHED_NT - 1) / SCHED_NT);
     if (rounds <= 0) {
         hipLaunchKernelGGL(k_identity_order, dim3(c->num_cu * 4), dim3(256), 0, c->stream, c->m * K, K, c->slot_order);

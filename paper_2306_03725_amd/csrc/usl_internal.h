@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stdio.h>
+#include <stdlib.h>
 #include <string.h>
 
 #include "../../include/usl.h"
@@ -125,6 +126,16 @@ usl_status usl_reserve_loss_partials(usl_ctx* ctx);
 static inline size_t usl_forward_blocks(const usl_ctx* c) { return (size_t)((c->m + 255) / 256) + (size_t)c->num_cu * 32; }
 usl_status usl_check_launch(usl_ctx* ctx, const char* what);
 
+// Proposal rounds of a bank-aware order (k_matching.h), of forward's slots and of the register lists; 0 = stored order.
+// None for a layer whose steps gather so little that the order cannot pay for its making, a chain of waits of 40 to 90 us
+// whatever the size: at m = 1024, d = 64, k = 8, b = 16 a step on new connectivity takes 107 us instead of 160, a later one
+// 33.6 instead of 33.4; at m = 1024, b = 128 there is no difference between later steps; at m = 4096, d = 256, k = 16,
+// b = 32 (the line) it is 45.0 and 44.3, at m = 31k, d = 1024, k = 32, b = 128 already 109 and 102.
+static inline int usl_order_rounds(const usl_ctx* c) {
+    if (const char* e = getenv("USL_TUNE_ROUNDS")) return atoi(e);
+    return (double)c->m * c->k * c->max_b < (double)(1 << 21) ? 0 : 3;
+}
+
 // K = padded fan-in, unit = bytes per column of the rows that will be gathered (4, 8 or 16; 2: single bfloat16)
 usl_status usl_build_slot_order(usl_ctx* ctx, const int32_t* idx, int K, int unit);
 
@@ -196,6 +207,7 @@ static inline uint32_t* usl_stale_word(usl_ctx* c) { return reinterpret_cast<uin
 // Records (store = 1) the fingerprint of idx for lists of the kind `which`, or compares with the recorded one (store = 0)
 // and raises the stale word on a difference.
 usl_status usl_idx_fingerprint(usl_ctx* ctx, const int32_t* idx, int which, int store);
+usl_status usl_idx_print_ready(usl_ctx* ctx);   // allocates ctx->idx_print, for kernels that record a fingerprint themselves
 static inline uint32_t* usl_nz_cells(usl_ctx* c) { return reinterpret_cast<uint32_t*>(c->counter64) + 4; }
 // Loss and gradient in place on zg[b][m], which also leaves the gradient in c->gT (tile-major) with
 // its piece flags and sampled nonzero count (usl_bwd_input_prepare must have run); *sampled_labels

@@ -55,3 +55,10 @@ def test_one_pass_backward_of_many_windows(orc, m, d, k, b, storage):
     L = usl.Layer(m, d, k, b, storage)
     run_and_compare(orc, L, gu, cfg, idx, W, x, g, b, max(1, b // 2))
     L.close()
+
+
+@pytest.mark.parametrize("m,d,k,b,storage,parts", SHAPES)
+def test_one_pass_backward_shapes_in_bank_order(orc, m, d, k, b, storage, parts, monkeypatch):
+    """Layers this small keep their lists in stored order by themselves; the bank-aware order has to be right for them too."""
+    monkeypatch.setenv("USL_TUNE_ROUNDS", "3")
+    test_one_pass_backward_shapes(orc, m, d, k, b, storage, parts, monkeypatch)

@@ -45,3 +45,10 @@ def test_products_in_every_launch_shape(orc, shape, split, monkeypatch):
     for q, (m, d, k, b, storage) in enumerate([(2500, 4096, 32, 13, "f32"), (2500, 15000, 20, 13, "bf16"), (2500, 40000, 64, 5, "f32")]):
         print("products", m, d, k, b, storage, shape, split, flush=True)
         compare(orc, gu, wl.custom(m, d, k, b, storage=storage, positives=3, index=790 + q), m, d, k, b, storage)
+
+
+@pytest.mark.parametrize("m,d,k,b,storage", [s for s in SHAPES if s[0] * s[2] * s[3] < 1 << 21])
+def test_products_at_their_edges_in_bank_order(orc, m, d, k, b, storage, monkeypatch):
+    """Layers this small keep their slots in stored order by themselves; the bank-aware order has to be right for them too."""
+    monkeypatch.setenv("USL_TUNE_ROUNDS", "3")
+    test_products_at_their_edges(orc, m, d, k, b, storage)
