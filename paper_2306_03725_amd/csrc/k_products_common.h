@@ -42,6 +42,9 @@ static constexpr int HALF_COLS = 32768;                 // columns per half of a
 // moves 1 KiB per instruction, no registers are used, all of it is in flight together.  In the last instruction the
 // lanes past the end are masked off.  The caller waits (vmcnt) before its barrier.  Inline assembly: behind the builtin
 // the compiler waits for the copy before the next LDS read of any address, so nothing would overlap it.
+// M0 is written here without being listed as clobbered: the compiler holds it in reserve and takes no clobber of it, and
+// sets it itself only where it emits an instruction that reads it.  No kernel of these files does (no LDS-DMA builtin, no
+// register index known at run time only); tests/test_listing_m0.py looks at what the compiler made.
 __device__ __forceinline__ void stage_async(const char* __restrict__ src, uint32_t lds, int nbytes, int tid, int nt) {
     for (int v = (tid >> 6) * 1024; v < nbytes; v += (nt / 64) * 1024) {
         const uint32_t off = (uint32_t)(v + (tid & 63) * 16);
