@@ -34,40 +34,53 @@ __global__ void k_stream_write(float4* __restrict__ b, size_t n) {
 }
 
 // ---- LDS gathers: one workgroup of 1024 lanes per compute unit, 32 resident addresses per lane,
-// WIDTH bytes per read.  PATTERN 0: random addresses.  PATTERN 1: the 32 lanes of a half-wavefront
-// read 32 different banks (WIDTH 4: lane l reads bank l of a random row of 32 words; wider reads:
-// consecutive lanes read consecutive elements) -- what a perfect bank-aware slot order would reach.
+// WIDTH bytes per read, eight reads in flight per wavefront and nothing else: written out in assembly, because the
+// compiler, given the wider reads, waits for one before it issues the next.  PATTERN 0: random addresses.  PATTERN 1: the
+// lanes that a read serves together (32 neighbours; with 16 bytes per lane the 16 lanes 0-3, 12-15, 20-27 of a
+// half-wavefront, and the other 16) read different banks -- what a perfect bank-aware slot order would reach.
 constexpr int LDS_WORDS = 32768;   // 128 KiB, the size of one float32 activation row of 32768 columns
+typedef float lds_v2 __attribute__((ext_vector_type(2)));
+typedef float lds_v4 __attribute__((ext_vector_type(4)));
+template <int WIDTH> struct LdsUnit;
+template <> struct LdsUnit<4> { typedef float T; };
+template <> struct LdsUnit<8> { typedef lds_v2 T; };
+template <> struct LdsUnit<16> { typedef lds_v4 T; };
+#define USL_EIGHT_READS(OP)                                                                                              \
+    asm volatile(OP " %0, %8\n\t" OP " %1, %9\n\t" OP " %2, %10\n\t" OP " %3, %11\n\t" OP " %4, %12\n\t" OP " %5, %13\n\t" \
+                 OP " %6, %14\n\t" OP " %7, %15\n\ts_waitcnt lgkmcnt(0)"                                                 \
+                 : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7]) \
+                 : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7]) : "memory")
+template <int WIDTH>
+__device__ __forceinline__ void eight_reads(const uint32_t* a, typename LdsUnit<WIDTH>::T (&v)[8]) {
+    if constexpr (WIDTH == 4) USL_EIGHT_READS("ds_read_b32");
+    else if constexpr (WIDTH == 8) USL_EIGHT_READS("ds_read_b64");
+    else USL_EIGHT_READS("ds_read_b128");
+}
+#undef USL_EIGHT_READS
 template <int WIDTH, int PATTERN>
 __global__ void __launch_bounds__(1024) k_lds_gather(float* sink, int reps) {
     extern __shared__ float lds[];
     for (int i = threadIdx.x; i < LDS_WORDS; i += 1024) lds[i] = (float)(i & 1023) * 1e-3f;
     __syncthreads();
-    constexpr int EW = WIDTH / 4;                 // words per element
-    constexpr uint32_t NE = LDS_WORDS / EW;       // elements in LDS
+    constexpr uint32_t GS = WIDTH == 16 ? 16 : 32, NE = LDS_WORDS * 4 / WIDTH;   // lanes served together, elements in LDS
+    const uint32_t base = (uint32_t)(uintptr_t)((const __attribute__((address_space(3))) void*)lds);
+    const uint32_t l = threadIdx.x & 31u;
+    const uint32_t pos = WIDTH != 16 ? l : l < 4 ? l : l < 12 ? l - 4 : l < 16 ? l - 8 : l < 20 ? l - 8 : l < 28 ? l - 12 : l - 16;
     uint32_t at[32];
     uint32_t seed = mix32(blockIdx.x * 1024u + threadIdx.x + 1u);
 #pragma unroll
     for (int t = 0; t < 32; ++t) {
         seed = mix32(seed + t);
-        uint32_t e = seed % NE;
-        if (PATTERN == 1) {
-            if (WIDTH == 4) e = (threadIdx.x & 31u) + 32u * (seed % (NE / 32u));
-            else e = (threadIdx.x + 64u * (uint32_t)t * 7u) % NE;
-        }
-        at[t] = e * EW;
+        at[t] = base + (PATTERN == 1 ? pos + GS * (seed % (NE / GS)) : seed % NE) * WIDTH;
     }
-    float acc = 0.f;
+    typename LdsUnit<WIDTH>::T v[8];
     for (int r = 0; r < reps; ++r) {
 #pragma unroll
-        for (int t = 0; t < 32; ++t) {
-            if (WIDTH == 4) acc += lds[at[t]];
-            else if (WIDTH == 8) { const float2 v = *reinterpret_cast<const float2*>(&lds[at[t]]); acc += v.x + v.y; }
-            else { const float4 v = *reinterpret_cast<const float4*>(&lds[at[t]]); acc += (v.x + v.y) + (v.z + v.w); }
-        }
-#pragma unroll
-        for (int t = 0; t < 32; ++t) at[t] = (acc == -1.0f) ? 0u : at[t];   // keeps the reads inside the loop
+        for (int t = 0; t < 32; t += 8) eight_reads<WIDTH>(at + t, v);
     }
+    float acc;
+    if constexpr (WIDTH == 4) acc = v[0] + v[7];
+    else acc = v[0][0] + v[7][1];
     if (acc == 123.456f) sink[0] = acc;
 }
 

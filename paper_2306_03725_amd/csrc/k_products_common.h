@@ -5,8 +5,8 @@
 // for its whole life; the activations stream through LDS, and every gather is an LDS read.
 //
 // What bounds it is the number of LDS reads, not their width: a ds_read_b64 of 64 random addresses takes as long as a
-// ds_read_b32 (7.8 against 7.9 lanes per clock and compute unit; 15.7 against 21 when no two lanes of a pass meet in a
-// bank), a ds_read_b128 little longer (5.0 and 13.4).  So the activations are interleaved: Q instances form a group,
+// ds_read_b32 (8.7 lanes per clock and compute unit both; 25 both when no two lanes of a pass meet in a bank), a
+// ds_read_b128 little longer (5.1 and 14.7; all measured by csrc/ceilings.hip).  So the activations are interleaved: Q instances form a group,
 // and the group's row holds x[i0][c], x[i0+1][c], ... side by side, one unit of 4, 8 or 16 bytes per column, which one
 // read brings to a lane.  A row of units has to fit LDS (160 KB):
 //     float32   Q = 4 up to d = 10 200,  Q = 2 up to 20 400,  Q = 1 up to 40 800,  beyond that the row in two halves
