@@ -29,17 +29,17 @@ MEASURED_TRAFFIC_BYTES = {
     "stress": {"backward": 178784619724, "backward_input": 203820315443, "forward": 26037190656, "backward_weight": 26132296499},
 }
 KERNELS_OF_CALL = {
-    "forward": "k_forward (1 launch)",
+    "forward": "k_interleave where one LDS read serves several instances, k_forward",
     "bce": "k_bce + k_bce_finish",
-    "backward_weight": "k_backward_weight (1 launch)",
+    "backward_weight": "a look at a sample of g, k_interleave as for forward, k_backward_weight",
     "backward_input": "a look at a sample of g, k_gather_w, then per group of 256 instances k_transpose_g + one "
                       "k_bwd_input_window per window of 24576 labels + k_untile",
     "backward_input_register_lists": "a look at a sample of g, k_idx_fingerprint, then per pass over the batch "
                                      "k_bwi_lds (lists in registers, rows of g through LDS) + k_lf_reduce",
     "backward": "usl_backward_weight's and usl_backward_input's kernels, one call after the other",
     "backward_one_pass": "a look at a sample of g, k_idx_fingerprint, k_both_lds (both products from one pass over g: "
-                         "lists in registers with a weight-gradient sum per connection, two rows of g through LDS at a "
-                         "time) + k_lf_reduce + k_unstage (the weight gradient into slot order)",
+                         "lists in registers with a weight-gradient sum per connection, two or four rows of g "
+                         "interleaved in LDS) + k_lf_reduce + k_unstage (the weight gradient into slot order)",
     "adam": "k_adam (1 launch)",
 }
 
@@ -66,6 +66,17 @@ def algorithmic_bytes(cfg):
 PARTIAL_SUM_BYTES = 16 << 30   # what the library lets the partial sums of a pass over the batch take on this device
 
 
+def full_rounds(nwin, nfb, cus):
+    full = -(-nwin * nfb // cus) * cus // nfb
+    return full if nwin < full <= nwin * 5 // 4 else nwin
+
+
+def equal_windows(m, nwin):
+    """(labels per window, windows) of about nwin windows of equal size, a multiple of 4."""
+    wl = -(-(-(-m // nwin)) // 4) * 4
+    return wl, -(-m // wl)
+
+
 def register_list_windows(cfg, cus=256):
     """Label windows of usl_backward_input's register-list form for this shape, or 0 where the library keeps the other
     form (its rule: windows of 16384 to 32768 labels that send about 32 connections into a feature, whole blocks of
@@ -73,41 +84,53 @@ def register_list_windows(cfg, cus=256):
     lists32 = 32 * cfg.d // cfg.k
     if not (cfg.d % 2048 == 0 and cfg.d <= 65536 and cfg.m % 4 == 0 and 16384 <= lists32 <= 32768):
         return 0
-    cap = min(lists32, 32768) // 4 * 4
-    nwin, nfb = -(-cfg.m // cap), cfg.d // 2048
-    if nwin * nfb * 4 < cus * 3:
-        return 0
-    full = -(-nwin * nfb // cus) * cus // nfb
-    return full if nwin < full <= nwin * 5 // 4 else nwin
+    nfb = cfg.d // 2048
+    nwin = equal_windows(cfg.m, full_rounds(-(-cfg.m // (min(lists32, 32768) // 4 * 4)), nfb, cus))[1]
+    return nwin if nwin * nfb * 4 >= cus * 3 else 0
 
 
-def register_list_form(cfg):
-    return register_list_windows(cfg) > 0
+def one_pass_cut(cfg, cus=256):
+    """How usl_backward's one-pass form cuts this layer up (the library's rules, csrc/k_lists_cut.h): instances a pass
+    takes, label windows, feature blocks, chains of windows, passes over the batch.  None where the library runs the two
+    separate products."""
+    q = 4 if cfg.d <= 1024 or 11 * cfg.d // cfg.k <= 4672 else 2
+    runs = 2048 // cfg.d if cfg.d <= 1024 else 1
+    nfb = -(-runs * cfg.d // 2048)
+    fpb = -(-(-(-runs * cfg.d // nfb)) // 32) * 32
+    lists = min((14 if q == 4 else 16) * 2048 // fpb, 21 if q == 4 else 24)
+    run = max(4, min(lists * cfg.d // cfg.k, (4672 if q == 4 else 15968) // runs) // 4 * 4)
+    if runs == 1:
+        nwin = equal_windows(cfg.m, full_rounds(-(-cfg.m // run), nfb, cus))[1]
+    else:
+        nwin = -(-cfg.m // (run * runs))
+    row = -(-cfg.d // 4) * 16   # bytes of an instance's sums
+    if cfg.d > 65536 or nwin * 64 * row > PARTIAL_SUM_BYTES:
+        return None
+    at_once = max(1, cus // nfb)
+    chains = -(-nwin // -(-nwin // at_once))
+    rows = min(cfg.b, max(64, PARTIAL_SUM_BYTES // (chains * row)))
+    return {"q": q, "nwin": nwin, "nfb": nfb, "chains": chains, "passes": -(-cfg.b // rows)}
 
 
-def one_pass_windows(cfg, cus=256):
-    """Label windows of usl_backward's one-pass form (both products from one pass over g), or 0 where the library runs
-    the two separate products (its rule: windows of 8192 to 15968 labels that send 16 connections or fewer into a
-    feature, whole blocks of 2048 features, enough workgroups to fill the chip)."""
-    lists16 = 16 * cfg.d // cfg.k
-    if not (cfg.d % 2048 == 0 and cfg.d <= 65536 and cfg.m % 4 == 0 and 8192 <= lists16 <= 32768):
-        return 0
-    cap = min(lists16, 15968) // 4 * 4
-    nwin, nfb = -(-cfg.m // cap), cfg.d // 2048
-    full = -(-nwin * nfb // cus) * cus // nfb
-    nwin = full if nwin < full <= nwin * 5 // 4 else nwin
-    if nwin * nfb * 4 < cus * 3 or nwin * 64 * cfg.d * 4 > PARTIAL_SUM_BYTES:
-        return 0
-    return nwin
+def forward_unit(cfg):
+    """(instances that one LDS read of forward serves, reads per connection): a row of that many instances has to fit LDS."""
+    es = 2 if cfg.storage == "bf16" else 4
+    for q in (4, 2, 1):
+        if cfg.d * q * es <= 160 * 1024 - 512:
+            return q, 1
+    return 1, 2   # a row in two halves, every connection visited in both
 
 
 def launches_in_call(cfg, call):
     """Kernel launches behind one call (the HIP-event time of the call covers all of them)."""
+    look = 2 if cfg.m >= 65536 else 0    # the sample of g
+    es = 2 if cfg.storage == "bf16" else 4
+    if call in ("forward", "backward_weight"):
+        return 1 + (1 if forward_unit(cfg)[0] > 1 else 0) + (look if call == "backward_weight" else 0)
     if call == "backward":
-        nwin = one_pass_windows(cfg)
-        if nwin:
-            rows = max(64, min(cfg.b, PARTIAL_SUM_BYTES // (nwin * cfg.d * 4))) & ~1
-            return 3 + 2 * -(-cfg.b // rows) + 1
+        cut = one_pass_cut(cfg)
+        if cut:   # fingerprint of idx, activations in the kernel's layout, k_both_lds and k_lf_reduce, k_unstage
+            return look + 1 + (1 if cut["q"] == 4 or cfg.d * es % 16 else 0) + 2 * cut["passes"] + 1
         return launches_in_call(cfg, "backward_weight") + launches_in_call(cfg, "backward_input")
     if call != "backward_input":
         return 2 if call == "bce" else 1
@@ -115,10 +138,10 @@ def launches_in_call(cfg, call):
     nwin = register_list_windows(cfg)
     if nwin:
         passes = -(-cfg.b // max(64, min(cfg.b, PARTIAL_SUM_BYTES // (nwin * cfg.d * 4))))
-        return 3 + passes * 2
+        return look + 1 + passes * 2
     win = int((24576.0 * ((cfg.d / 32768.0) * (32.0 / cfg.k)) ** 0.5 + 2048.0) / 4096.0) * 4096   # labels per window,
     win = min(max(win, 16384), 49152)                                                              # as the library picks them
-    return 3 + groups * (1 + -(-cfg.m // win) + 1 + 1)
+    return look + 1 + groups * (1 + 1 + -(-cfg.m // win) + 1)
 
 
 def cpu_baseline(cfg, budget_s=12.0, max_reps=5):
@@ -366,7 +389,7 @@ def main():
     traffic = MEASURED_TRAFFIC_BYTES.get(cfg.name, {}).get(dom)
     if args.traffic_kib is not None:
         traffic = args.traffic_kib * 1024
-    dom_kernels = KERNELS_OF_CALL["backward_one_pass" if dom == "backward" and one_pass_windows(cfg) else dom]
+    dom_kernels = KERNELS_OF_CALL["backward_one_pass" if dom == "backward" and one_pass_cut(cfg) else dom]
     roof = {"bound": "hbm", "kernel": "usl_%s: %s" % (dom, dom_kernels),
             "achieved": round(dom_gbps, 1), "peak": HBM_PEAK_GBPS,
             "unit": "GB/s", "frac": round(dom_gbps / HBM_PEAK_GBPS, 4),
@@ -406,25 +429,34 @@ def main():
             from paper_2306_03725_amd import ceilings
             c = ceilings.run()
             cu, ghz = c["compute_units"], c["clock_GHz"]
-            # one LDS gather per (instance, connection) and product; the two backward products share theirs where
-            # usl_backward takes its one-pass form
-            products = 2.0 if one_pass_windows(cfg) else 3.0
-            gathers = products * b * m * k
-            gather_rate = c["lds_gather_b32_conflict_free_lanes_per_clk_cu"] * cu * ghz * 1e9
+            # LDS reads per step, by width: a read of forward serves the instances that lie side by side in its rows,
+            # a read of the one-pass backward both products of q instances
             es = 2 if cfg.storage == "bf16" else 4
-            # every product stages its rows into the LDS of every workgroup: per product, label (or feature)
-            # blocks of 2048 x batch rows x row bytes
-            copy_bytes = products * (-(-m // 2048)) * b * d * es
-            t_gather = gathers / gather_rate * 1e3
-            t_copy = copy_bytes / (c["l2_to_lds_row_copy_aggregate_GBps"] * 1e9) * 1e3
+            rate = {4: c["lds_gather_b32_conflict_free_lanes_per_clk_cu"], 8: c["lds_gather_b64_conflict_free_lanes_per_clk_cu"],
+                    16: c["lds_gather_b128_conflict_free_lanes_per_clk_cu"]}
+            fq, visits = forward_unit(cfg)
+            cut = one_pass_cut(cfg)
+            connections = b * m * k
+            reads = [(visits * connections / fq, max(4, fq * es))]
+            # rows staged: every block of about 2048 labels copies the activations of the batch; every feature block of a
+            # window copies its slice of g (or, by separate products, blocks of 2048 labels and of 2048 features)
+            copies = -(-m // 2048) * b * d * es
+            if cut:
+                reads.append((connections / cut["q"], 4 * cut["q"]))
+                copies += cut["nfb"] * b * m * 4
+            else:
+                reads += [reads[0], (connections, 4)]
+                copies += copies + -(-d // 2048) * b * m * 4
+            t_gather = sum(n / rate[w] for n, w in reads) / (cu * ghz * 1e9) * 1e3
+            t_copy = copies / (c["l2_to_lds_row_copy_aggregate_GBps"] * 1e9) * 1e3
             t_hbm = ab["step"] / (c["hbm_copy_GBps_read_plus_write"] * 1e9) * 1e3
             res["ceilings"] = {k_: round(v, 3) for k_, v in c.items()}
             roof["gather_frac"] = round(t_gather / ms_per_step, 4)
-            roof["gather_note"] = ("%d*b*m*k LDS gathers per step at the measured conflict-free ds_read_b32 rate "
+            roof["gather_note"] = ("the step's LDS gathers (%s) at the measured conflict-free rates of their widths "
                                    "would take %.3f ms; staging the rows those gathers read, at the measured L2 to "
                                    "LDS copy rate, %.3f ms; the step's algorithmic HBM bytes at the measured copy "
                                    "rate, %.3f ms; these three do not overlap inside a product kernel"
-                                   % (int(products), t_gather, t_copy, t_hbm))
+                                   % (", ".join("%.3g of %d bytes" % r for r in reads), t_gather, t_copy, t_hbm))
             roof["measured_ceilings_frac"] = round((t_gather + t_copy + t_hbm) / ms_per_step, 4)
         except Exception as exc:   # the headline line must survive a failure of an appended leg
             res["ceilings"] = {"error": repr(exc)}
