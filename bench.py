@@ -24,9 +24,9 @@ HBM_PEAK_GBPS = 8000.0   # MI355X published peak
 # They are measured offline (a counter run serialises the kernels) and go stale when a kernel changes: the
 # profile files carry the date of truth, these constants only repeat their per-call totals.
 MEASURED_TRAFFIC_BYTES = {
-    "large": {"backward": 3903848448, "backward_input": 2844157542, "forward": 924948889, "backward_weight": 940782387},
-    "large_wide": {"backward": 17392939827, "backward_input": 8593394892, "forward": 2478204518, "backward_weight": 2651114700},
-    "stress": {"backward": 178784619724, "backward_input": 203820315443, "forward": 26037190656, "backward_weight": 26132296499},
+    "large": {"backward": 3944660070, "backward_input": 2845542092, "forward": 988964454, "backward_weight": 983684505},
+    "large_wide": {"backward": 17964965478, "backward_input": 8598012928, "forward": 3800982016, "backward_weight": 3052722073},
+    "stress": {"backward": 172239572070, "backward_input": 203855339520, "forward": 37601100492, "backward_weight": 26393168179},
 }
 KERNELS_OF_CALL = {
     "forward": "k_interleave where one LDS read serves several instances, k_forward",

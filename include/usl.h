@@ -64,9 +64,9 @@ usl_status usl_create(usl_ctx** ctx, int64_t m, int32_t d, int32_t k, int32_t ma
                       usl_dtype storage, void* hip_stream);
 usl_status usl_destroy(usl_ctx* ctx); /* frees the context and its device scratch; NULL is OK */
 usl_status usl_set_stream(usl_ctx* ctx, void* hip_stream);
-/* The library keeps private views of the connectivity (a column-major copy for usl_backward_input,
- * a per-label visiting order of the slots for the two other products), keyed by the idx pointer and
- * rebuilt after usl_init_indices / usl_redistribute / usl_redistribute_rows.  A caller that rewrites
+/* The library keeps private views of the connectivity (column-major lists for usl_backward_input, others for
+ * usl_backward and usl_train_step, a per-label visiting order of the slots for the two other products), keyed by
+ * the idx pointer and rebuilt after usl_init_indices / usl_redistribute / usl_redistribute_rows.  A caller that rewrites
  * the contents of idx by any other means must call this before the next product call: a stale
  * column-major copy gives wrong input gradients (a stale visiting order only costs speed). */
 usl_status usl_invalidate(usl_ctx* ctx);
@@ -197,9 +197,10 @@ usl_status usl_adam_step(usl_ctx* ctx, void* W, const float* grad_W, float* m1, 
 /* One training step of the layer in one call: usl_forward, the loss (loss_kind 0 = binary
  * cross-entropy, 1 = squared hinge), usl_backward_weight, usl_backward_input and usl_adam_step, in that
  * order (Sections 3.2-3.3, 4.1), with the same arguments and the same results as the separate calls
- * (the loss value up to the order of its additions).  Fused inside: the loss writes the gradient in the
- * two layouts the backward products read, so no separate transposition pass runs.
- *   g      [b][m] float32  work and result: the scores, then the upstream gradient
+ * (the loss value up to the order of its additions).  Fused inside: the loss is part of the forward kernel (or
+ * writes the gradient in the two layouts that the separate backward products read), both backward products come
+ * from one pass over the gradient, and Adam reads the weight gradient where that pass left it.
+ *   g      [b][m] float32  work and result: the upstream gradient
  *   grad_W [m][k] float32  result: the gradient Adam consumed
  *   grad_x [b][d] float32  result, or NULL to skip the input gradient
  * W, m1, m2 are updated in place; grad_x is computed from W as it was before the update. */

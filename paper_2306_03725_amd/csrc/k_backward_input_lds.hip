@@ -670,17 +670,18 @@ k_bwi_lds(const float* __restrict__ g, const TS* __restrict__ W, int64_t m, int 
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// Both backward products from one pass of gathers (usl_train_step).  Every gathered g[i][j] serves twice: times the
-// connection's weight it goes into the feature's sum (Algorithm 2), times the feature's activation x[i][c] into a sum
-// that the lane keeps per slot over the whole batch (Algorithm 3) and stores at the end -- every slot of the layer
+// Both backward products from one pass of gathers (usl_train_step, usl_backward).  Every gathered g[i][j] serves twice:
+// times the connection's weight it goes into the feature's sum (Algorithm 2), times the feature's activation x[i][c] into a
+// sum that the lane keeps per slot over the whole batch (Algorithm 3) and stores at the end -- every slot of the layer
 // belongs to exactly one list of one workgroup, so every weight gradient is written once, without atomics.  The third
 // register per slot halves the slots (KT_BOTH = 36) and with them the windows; the row buffer then has room for the
 // slices of two instances, and a pass of the loop does two instances.  They lie interleaved, so a slot costs one address,
 // one ds_read_b64 and four multiply-adds: 64 random 8-byte reads take LDS no longer than 64 random 4-byte ones (before,
 // with the slices one behind the other and two ds_read_b32, usl_backward took 1408 us at m = 500k, d = 32k, k = 32,
-// b = 256 and 6662 us at m = 670k, k = 64, b = 512; now 1319 and 6068).  What bounds it now: a pass of 3.3 us is about
-// 1.4 us of row copies at the L2 -> LDS rate, 1.3 of gathers, the rest barriers and the sums on their way out, one after the
-// other; with neither copies nor gathers 1.7 us remain, the trip to memory of the warm-up loads.
+// b = 256 and 6662 us at m = 670k, k = 64, b = 512; now 1310 and 5350 to 5590).  What bounds it at the first of these
+// (1052 us, two windows of 128 passes per workgroup, the lists of a window 20 us): LDS is busy for half of the time, nearly
+// half of that with bank conflicts (profiles/products_large_f32_lds_bank_conflicts.txt), the row copies take a third of a
+// pass at the L2 -> LDS rate, and copy, gathers and sums of a pass follow one another, with barriers between them.
 // The sums of overflow entries live in LDS (ov_sum) or, beyond the NEAR2 that LDS holds, in memory (ovgw).
 __device__ __forceinline__ void gather4_two(float& acc0, float& acc1, float& s0, float& s1, float& s2, float& s3,
                                             uint32_t p0, uint32_t p1, float w0, float w1, float w2, float w3, float x0, float x1) {

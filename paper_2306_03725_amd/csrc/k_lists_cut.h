@@ -56,8 +56,10 @@ inline Cut bwi_cut(int64_t m, int d, int k, int num_cu) {
 
 // Instances that a pass of the kernel for both products takes together: four where windows that send 11 connections into
 // a feature fit LDS four rows at a time, else two.  A pass is a chain of waits, so the fewer the better; with shorter lists
-// there are too many windows (backward, m = 100k, d = 20k, k = 48 (lists of 11), b = 64: 167 us with four, 195 with two;
-// m = 300k, d = 14k, k = 32 (10.7): 362 and 365; m = 670k, d = 16k, k = 32 (9.1): 472 and 414).
+// there are too many windows (backward, m = 100k, d = 20k, k = 48 (lists of 11.2), b = 64: 168 us with four, 184 with two;
+// m = 300k, d = 14k, k = 32 (10.7): 347 and 334; m = 670k, d = 16k, k = 32, b = 32 (9.1): 413 and 356).  Of 16 layers
+// measured (profiles/rules_measured.txt) it takes the faster in 11 and is within 4 % in three; where the other number leaves
+// a last round of workgroups nearly empty it can be wrong by more (m = 200k, d = 12k, k = 32: 252 us, 185 with two).
 inline int both_q(int d, int k) { return d <= NT || (int64_t)11 * d / k <= (int64_t)BOTH4_LABELS ? 4 : 2; }
 
 // The form for both products: lists of 16 connections (half the registers go to the weight-gradient sums; with four
@@ -90,9 +92,9 @@ inline Cut both_cut(int64_t m, int d, int k, int num_cu) {
 
 // Parts of the batch in the kernel for both products: more than one where the (window, feature block) workgroups leave
 // compute units idle.  A workgroup loads its lists and weights and hands out its sums in about 20 us, a pass of its loop
-// takes about 4.4 (m = 31k, d = 1k, k = 32, b = 128: 187 us with 1 part, 117 with 2, 83 with 4, 75 with 6, 100 with 8, which
-// are two rounds); every part writes a weight gradient of its own, which the reader adds up.  forced > 0: that many, if
-// the batch has them.
+// takes about 4.4 (m = 31k, d = 1k, k = 32, b = 128: 179 us with 1 part, 116 with 2, 83 with 4, 77 with 6, 103 with 8, which
+// are two rounds); every part writes a weight gradient of its own, which the reader adds up.  Of 16 layers measured
+// (profiles/rules_measured.txt) the best number or within 4 % of it.  forced > 0: that many, if the batch has them.
 inline int both_parts(const Cut& cut, int64_t m, int k, int num_cu, int rows, int Q, int forced) {
     const int64_t wgs = (int64_t)cut.nwin * cut.nfb, passes = (rows + Q - 1) / Q, cu = num_cu;
     if (forced > 0) return (int)(forced < passes ? forced : passes);

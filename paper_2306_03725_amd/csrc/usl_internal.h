@@ -72,9 +72,9 @@ struct usl_ctx {
     uint32_t* hint_dev;       // the same words as the device addresses them
     uint32_t hint_seen, probe_serial;
     int sparse_streak;        // looks in a row that found the sample sparse
-    // the register-list form of the input gradient (k_backward_input_lds.hip): [0] lists of 68 slots per lane from
-    // windows of up to 32768 labels, for usl_backward_input; [1] lists of 36 slots from windows of half that length, for
-    // the kernel of usl_train_step that computes the weight gradient from the same gathers
+    // the register-list forms (k_backward_input_lds.hip): [0] lists of 68 slots per lane from windows of up to 32768
+    // labels, for usl_backward_input; [1] lists of 36 or 32 slots from shorter windows, for the kernel of usl_train_step
+    // and usl_backward that computes both gradients from the same gathers
     struct usl_lf {
         void* mem;            size_t mem_cap;      // holds count .. pos
         uint32_t* count;                           // [nwin*d] list lengths
@@ -89,7 +89,8 @@ struct usl_ctx {
         uint32_t* ent;                             // [m*k] flat slots grouped by (workgroup, feature), before the bank-aware order
         uint32_t* ovoff;                           // [nwin*d] where a list's overflow starts in its workgroup's
         void* ov;                                  // overflow entries
-        float* stage;         size_t stage_cap;    // [1] only: the weight gradient in list order, [wg][slots][1024], then one per overflow entry
+        float* stage;         size_t stage_cap;    // [1] only: per part of the batch the weight gradient by place, [m*k]; behind them per part
+                                                   // the sums of the overflow entries that LDS does not hold
         uint32_t* pos;                             // [1] only: [m*k] where a slot's weight gradient is in stage
         float* partial;       size_t partial_cap;  // [nwin or chains of windows][rows of a pass][d]
         int most_parts;       size_t most_rows;    // [1] only: what the largest need of any batch is (0: not known yet)
@@ -181,7 +182,8 @@ bool usl_bwi_lds_applies(const usl_ctx* ctx);
 usl_status usl_bwi_lds_run(usl_ctx* ctx, const float* g, const int32_t* idx, const void* W, float* grad_x, int32_t b,
                            const uint32_t* gate);
 // Both backward products from one pass of gathers through register lists of half the length (k_backward_input_lds.hip):
-// grad_W[m][k] and grad_x[b][d] from g[b][m] and x[b][d]; for layers with k / d <= 1/1024, one pass over the batch.
+// grad_W[m][k] and grad_x[b][d] from g[b][m] and x[b][d]; for every layer of up to 65536 features whose partial sums of 64
+// instances fit the allowance.
 bool usl_both_lds_applies(const usl_ctx* ctx);
 // Where k_both_lds left the weight gradient: slot f's is the sum over p < parts of stage[p * part_stride + pos[f]].
 // stale: device word, not 0 = the lists were built from other contents of idx.
@@ -263,7 +265,8 @@ __device__ __forceinline__ usl_loss_of usl_loss_one(int kind, float z, float y, 
     usl_loss_of o;
     if (kind == 0) {
         const float e = __expf(-fabsf(z)), p = 1.f + e;   // p in [1, 2]
-        // 1 / p: the hardware's estimate (1 ulp) and a Newton step, within a hair of half an ulp
+        // 1 / p: the hardware's estimate and a Newton step; the bits of the correctly rounded division for each of the
+        // 2^23 + 1 values of p (compared on the device)
         const float r0 = __builtin_amdgcn_rcpf(p), r = fmaf(r0, fmaf(-p, r0, 1.f), r0);
         const float sig = z >= 0.f ? r : e * r;
         o.g = scale * (sig - y);

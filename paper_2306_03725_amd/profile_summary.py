@@ -23,7 +23,7 @@ COPY_KIB = 1048576.0                        # it moves 2^30 bytes each way
 
 
 def short(name, width=70):
-    name = re.sub(r"\(anonymous namespace\)::", "", name)
+    name = re.sub(r"\(anonymous namespace\)::|usl_products::|usl_lists::", "", name)
     return re.sub(r"\(.*", "", name)[:width]
 
 
