@@ -622,10 +622,14 @@ usl_status run_forward_few(usl_ctx* c, const Layout& L, const void* x, const int
 namespace {
 
 // What k_forward's loss leaves to do: the gradient and the loss of the targets, a few per instance.  Their scores are taken
-// once more, in k_forward's order of additions (the same bits): 16 lanes bring the slots of a target, in the order of
-// their steps, and one of them adds up.  A label listed twice for an instance counts once: whoever takes its bit back
-// first.  Block i of the first b: instance i, its targets' part of the loss goes to partials[i].  Block b, if there is one, compares the fingerprint of idx for the backward product
-// (a launch of its own took 4 to 8 us).
+// once more, in k_forward's order of additions (the same bits): 16 lanes bring the slots of a target, and one of them adds
+// up in the order of the steps, eight steps' reads of LDS together (one by one the chain took 17 us instead of 13 at
+// m = 1987, k = 64, b = 259, 36 targets).  A label listed twice for an instance counts once: the exchange shows who came
+// second, for the gradient of a target has other bits than without one, unless the scale is 0 or the loss NaN.  (Taking the
+// label's bit back atomically would tell too, but the words of the labels that many instances have are fought over: 6.3 us
+// instead of 4.6 at m = 5505, k = 8, b = 220.)  Block i of the first b: instance i, its targets' part of the loss goes to
+// partials[i].  Block b, if there is one, compares the fingerprint of idx for the backward product (a launch of its own took
+// 4 to 8 us).
 template <typename TS>
 __global__ void __launch_bounds__(1024)
 k_loss_positives(const TS* __restrict__ x, const int32_t* __restrict__ idx, const TS* __restrict__ W, float* __restrict__ g, int64_t m,
@@ -635,7 +639,7 @@ k_loss_positives(const TS* __restrict__ x, const int32_t* __restrict__ idx, cons
     constexpr int PER = 64;   // targets at a time
     __shared__ float2 slots[PER][65];        // {weight, activation} of a slot; zeros behind the last one
     __shared__ uint8_t upper[PER][64];       // whether its column is in the second half of a row in two halves
-    __shared__ uint8_t order[PER][64];       // slot of a step
+    __shared__ __align__(8) uint8_t order[PER][64];   // slot of a step
     __shared__ double red[16];
     const int i = blockIdx.x;
     if (i == b) {
@@ -667,24 +671,33 @@ k_loss_positives(const TS* __restrict__ x, const int32_t* __restrict__ idx, cons
         wave_sync();
         if ((threadIdx.x & 15) == 0) {
             float z = 0.f;
-            if (sizeof(TS) == 4) {
-                for (int part = 0; part < (halves ? 2 : 1); ++part)
-                    for (int s = 0; s < K; ++s) {
-                        const int t = order[q16][s];
-                        if (!halves || upper[q16][t] == part) z = fmaf(mine[t].x, mine[t].y, z);
+            for (int part = 0; part < (halves ? 2 : 1); ++part) {
+#pragma unroll 1
+                for (int s0 = 0; s0 < K; s0 += 8) {   // eight steps' reads together (K is a multiple of 8)
+                    const uint2 eight = *reinterpret_cast<const uint2*>(order[q16] + s0);
+                    float2 v[8];
+                    bool on[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const uint32_t t = ((u < 4 ? eight.x : eight.y) >> (8 * (u & 3))) & 0xFFu;
+                        v[u] = mine[t];
+                        on[u] = !halves || upper[q16][t] == part;
                     }
-            } else {
-                for (int s = 0; s < K; s += 2) {
-                    const float2 u = mine[order[q16][s]], v = mine[order[q16][s + 1]];
-                    z = dot2(__float_as_uint(u.y) >> 16 | __float_as_uint(v.y), __float_as_uint(u.x) >> 16 | __float_as_uint(v.x), z);
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        if constexpr (sizeof(TS) == 4) {
+                            if (on[u]) z = fmaf(v[u].x, v[u].y, z);
+                        } else if (u & 1) {
+                            z = dot2(__float_as_uint(v[u - 1].y) >> 16 | __float_as_uint(v[u].y), __float_as_uint(v[u - 1].x) >> 16 | __float_as_uint(v[u].x), z);
+                        }
+                    }
                 }
             }
-            const uint32_t bit = 1u << (i & 31);
-            if (atomicAnd(bits + (size_t)(i >> 5) * m + j, ~bit) & bit) {
-                const usl_loss_of r = usl_loss_one(kind, z, 1.f, scale);
-                g[(size_t)i * m + j] = r.g;
-                lost += (double)r.l;
-            }
+            const usl_loss_of r = usl_loss_one(kind, z, 1.f, scale);
+            const float before = atomicExch(g + (size_t)i * m + j, r.g);
+            const bool first = __float_as_uint(before) != __float_as_uint(r.g) || r.l != r.l;
+            if (first) lost += (double)r.l;
+            if (first || scale == 0.f) bits[(size_t)(i >> 5) * m + j] = 0u;   // all bits of the word go in this launch; nobody reads them
         }
         wave_sync();
     }
