@@ -80,3 +80,24 @@ def test_targets_that_are_learned(orc, m, d, k, b, storage, loss_kind, size):
         if loss_kind == 1:
             assert gu.host(loss)[0] == 0.0
     L.close()
+
+
+def test_marks_of_a_step_without_gradient_do_not_stay(orc):
+    """At scale 0 a target's gradient has the same bits as without the target; what marked it is cleared all the same."""
+    import gpu_util as gu
+    from paper_2306_03725_amd import usl
+    m, d, k, b = 3000, 300, 16, 40
+    cfg = wl.custom(m, d, k, b, positives=3, index=835)
+    d_idx, d_W, d_x = gu.dev(wl.gen_idx(cfg)), gu.dev(wl.gen_W(cfg)), gu.dev(wl.gen_x(cfg))
+    rng = np.random.default_rng(9)
+    L = usl.Layer(m, d, k, b)
+    m1, m2, g, gW, loss, ref, ref_loss = (gu.empty(s).fill_(0.0) for s in [(m, k), (m, k), (b, m), (m, k), (1,), (b, m), (1,)])
+    for scale in (0.0, 1.0 / b):
+        off, lab = gu.dev(np.arange(b + 1, dtype=np.int64) * 7), gu.dev(rng.integers(0, m, size=7 * b).astype(np.int32))
+        for loss_kind in (0, 1):
+            L.forward(d_x, d_idx, d_W, ref, b)
+            (L.bce_loss_grad if loss_kind == 0 else L.sqh_loss_grad)(ref, off, lab, scale, ref, ref_loss, b)
+            L.train_step(d_x, d_idx, d_W, m1, m2, off, lab, loss_kind, scale, 1, 0.0, 0.9, 0.999, 1e-8, g, gW, None, loss, b)
+            np.testing.assert_array_equal(gu.host(g), gu.host(ref))
+            assert_close(gu.host(loss), gu.host(ref_loss), 1e-6, "loss")
+    L.close()
