@@ -1434,12 +1434,13 @@ usl_status usl_both_lds_run(usl_ctx* c, const float* g, const void* x, const int
     if (const char* e = getenv("USL_TUNE_BOTH_PARTS")) forced = atoi(e) > 0 ? atoi(e) : 1;
     const int G = pass_rows(c, both_chains(cut, c->num_cu), Q);
     const BothPlan plan = both_plan(cut, c->m, c->k, c->num_cu, b, G, Q, forced);
-    if (!L.most_parts || forced) {   // scratch for every batch that a later call can bring
-        const BothMost most = both_most(cut, c->m, c->k, c->num_cu, c->max_b, G, Q, forced);
-        L.most_parts = most.parts;
-        L.most_rows = most.rows;
-    }
     const int parts = plan.parts, chains = plan.sets;
+    const size_t sum_rows = (size_t)chains * (size_t)(b < G ? b : G);
+    if (parts > L.most_parts || sum_rows > L.most_rows) {   // the first call (or another setting of a tuning aid): scratch for every batch that a later call can bring
+        const BothMost most = both_most(cut, c->m, c->k, c->num_cu, c->max_b, G, Q, forced);
+        if (most.parts > L.most_parts) L.most_parts = most.parts;
+        if (most.rows > L.most_rows) L.most_rows = most.rows;
+    }
     USL_TRY(usl_reserve(c, (void**)&L.partial, &L.partial_cap, L.most_rows * dp * 4));
     // per part: stage [N], the sums of the overflow entries beyond LDS [N + nbins]
     const size_t keep = (size_t)L.most_parts;

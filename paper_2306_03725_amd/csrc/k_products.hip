@@ -485,7 +485,7 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
             if (parts > most_parts && parts > 1) break;
             if (backward && parts > 1 && (size_t)parts * c->m * c->k * 4 > ((size_t)1 << 29)) break;
             const int64_t wgs = nblk * parts;
-            if (kind == FORWARD_LOSS && parts > 1 && (size_t)wgs > usl_forward_blocks(c)) break;
+            if (kind == FORWARD_LOSS && parts > 1 && (size_t)wgs > usl_forward_blocks(c) && split_force <= 0) break;
             const double most = (double)((wgs + cus - 1) / cus);      // workgroups the busiest compute unit runs
             const double per_cu = wgs > cus ? 0.75 * most + 0.25 * wgs / cus : most;
             const double rounds = (double)((wgs + (int64_t)cus * res - 1) / ((int64_t)cus * res));
@@ -735,6 +735,7 @@ usl_status run_forward(usl_ctx* c, const Layout& L, const void* x, const int32_t
     if (loss.kind >= 0) {
         *blocks = (size_t)p.nblk * (size_t)p.G;
         USL_TRY(usl_reserve_loss_partials(c));
+        USL_TRY(usl_reserve(c, (void**)&c->bce_partials, &c->bce_partials_cap, (*blocks + (size_t)b) * sizeof(double)));   // more only with parts asked for by hand
         loss.partials = c->bce_partials;
     }
     void* args[] = {&xi, &idx, &W, &out, &m, &k, &bb, &tg, &perm, &loss};

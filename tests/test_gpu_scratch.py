@@ -42,3 +42,26 @@ def test_no_later_batch_grows_the_scratch(m, d, k, max_b, first):
     for b in batches:
         assert calls(L, b) == free, "a batch of %d after one of %d" % (b, first)
     L.close()
+
+
+def test_parts_asked_for_by_hand_between_calls(orc, monkeypatch):
+    """The tuning aids are read on every call: scratch that was sized under one setting has to serve the next."""
+    import gpu_util as gu
+    from helpers import assert_close
+    from paper_2306_03725_amd import usl
+    m, d, k, b = 13330, 5000, 32, 96
+    cfg = wl.custom(m, d, k, b, positives=3, index=865)
+    h_idx, h_W, h_x, h_g = wl.gen_idx(cfg), wl.gen_W(cfg), wl.gen_x(cfg), wl.gen_g(cfg)
+    idx, W, x, g = gu.dev(h_idx), gu.dev(h_W), gu.dev(h_x), gu.dev(h_g)
+    gW, gx = gu.empty((m, k)), gu.empty((b, d))
+    L = usl.Layer(m, d, k, b)
+    for parts in ("1", None, "3", "24", None):
+        if parts:
+            monkeypatch.setenv("USL_TUNE_BOTH_PARTS", parts)
+        else:
+            monkeypatch.delenv("USL_TUNE_BOTH_PARTS", raising=False)
+        gW.fill_(7.0); gx.fill_(7.0)
+        L.backward(g, x, idx, W, gW, gx, b)
+        assert_close(gu.host(gW), orc.backward_weight(h_g, h_x, h_idx), 1e-5, "grad_W")
+        assert_close(gu.host(gx), orc.backward_input(h_g, h_idx, h_W, d), 1e-4, "grad_x")
+    L.close()
