@@ -711,6 +711,8 @@ k_loss_positives(const TS* __restrict__ x, const int32_t* __restrict__ idx, cons
     }
 }
 
+size_t target_words(const usl_ctx* c) { return (size_t)((c->max_b + 31) / 32) * (size_t)c->m; }
+
 // the forward kernel over the whole batch, with or without the loss (then marks says what the targets are; the bits are set
 // here and taken back by k_loss_positives)
 usl_status run_forward(usl_ctx* c, const Layout& L, const void* x, const int32_t* idx, const void* W, float* out, int32_t b, LossArgs loss,
@@ -720,7 +722,7 @@ usl_status run_forward(usl_ctx* c, const Layout& L, const void* x, const int32_t
     const void* xi = nullptr;
     USL_TRY(slot_order(c, idx, &perm));
     if (loss.kind >= 0) {
-        const size_t words = (size_t)((c->max_b + 31) / 32) * c->m, had = c->tgt_bits_cap;
+        const size_t words = target_words(c), had = c->tgt_bits_cap;
         USL_TRY(usl_reserve(c, (void**)&c->tgt_bits, &c->tgt_bits_cap, words * 4));
         if (had != c->tgt_bits_cap || c->tgt_bits_set)   // new, or a call before failed half way
             hipLaunchKernelGGL(k_fill_zero, dim3(c->num_cu * 4), dim3(256), 0, c->stream, reinterpret_cast<float*>(c->tgt_bits), words);
@@ -763,7 +765,9 @@ usl_status usl_launch_forward(usl_ctx* c, const void* x, const int32_t* idx, con
 
 bool usl_forward_loss_applies(const usl_ctx* c, const void* x, const int32_t* idx, const void* W, int32_t b) {
     const Layout L = layout_of(c, b, x);
-    return fast_path_ok(c, idx, W) && !streams(c, L, b) && !pads_with_column_0(c, L);   // (scores are done again, their losses not)
+    // (at most 1 GiB of target bits, m * max_b of 8.6e9: a context made for far larger batches than it sees pays in time, not memory)
+    return fast_path_ok(c, idx, W) && !streams(c, L, b) && !pads_with_column_0(c, L) /* scores are done again, their losses not */ &&
+           target_words(c) * 4 <= (size_t)1 << 30;
 }
 
 usl_status usl_launch_forward_loss(usl_ctx* c, const void* x, const int32_t* idx, const void* W, float* g, int32_t b, int loss_kind,

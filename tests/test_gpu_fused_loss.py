@@ -101,3 +101,23 @@ def test_marks_of_a_step_without_gradient_do_not_stay(orc):
             np.testing.assert_array_equal(gu.host(g), gu.host(ref))
             assert_close(gu.host(loss), gu.host(ref_loss), 1e-6, "loss")
     L.close()
+
+
+def test_a_context_for_far_larger_batches(orc):
+    """The bits that mark targets are held to 1 GiB; beyond, the loss is a pass of its own and the step gives the same."""
+    import gpu_util as gu
+    from paper_2306_03725_amd import usl
+    m, d, k, b = 140000, 64, 8, 5
+    cfg = wl.custom(m, d, k, b, positives=3, index=836)
+    idx, W, x = wl.gen_idx(cfg), wl.gen_W(cfg), wl.gen_x(cfg)
+    off, lab = wl.gen_targets(cfg)
+    d_idx, d_W, d_x, d_off, d_lab = gu.dev(idx), gu.dev(W), gu.dev(x), gu.dev(off), gu.dev(lab)
+    m1, m2, g, gW, gx, loss = (gu.empty(s).fill_(0.0) for s in [(m, k), (m, k), (b, m), (m, k), (b, d), (1,)])
+    L = usl.Layer(m, d, k, 65535)
+    L.train_step(d_x, d_idx, d_W, m1, m2, d_off, d_lab, 0, 0.2, 1, 0.0, 0.9, 0.999, 1e-8, g, gW, gx, loss, b)
+    ref_loss, ref_g = orc.bce_loss_grad(orc.forward(x, idx, W), off, lab, 0.2)
+    assert_close(gu.host(g), ref_g, 1e-5, "g")
+    assert abs(gu.host(loss)[0] - ref_loss) <= 1e-5 * abs(ref_loss)
+    assert_close(gu.host(gW), orc.backward_weight(ref_g, x, idx), 1e-5, "grad_W")
+    assert_close(gu.host(gx), orc.backward_input(ref_g, idx, W, d), 1e-4, "grad_x")
+    L.close()
