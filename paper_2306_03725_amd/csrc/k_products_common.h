@@ -672,6 +672,9 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const uint32_t lds0 = lds_base(lds_raw);
     const int64_t j0 = (int64_t)blockIdx.x * (NT * LPT);
+    if (LOSS)   // the first words of target bits come to the L2 while the labels' rows are brought in (1 % of the step at m = 500k, b = 256)
+        touch_lines<NT>(reinterpret_cast<const char*>(loss.targets + (size_t)((int)blockIdx.y * tg.groups_per_block * Q >> 5) * m + j0), 0,
+                        ((int)min((int64_t)NT * LPT, m - j0) * 4 + 127) / 128, lds0 + (uint32_t)tg.dummy, (int)threadIdx.x);
     uint32_t pk[LPT][K / 2];
     WReg<TS, K> w[LPT];
 #pragma unroll
