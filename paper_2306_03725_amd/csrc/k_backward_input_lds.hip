@@ -52,17 +52,39 @@ static_assert(ZERO_LABEL % 32 == 0 && ZERO_LABEL + 31 < 65536 && LDS_BYTES <= 16
 // "label": a window has at most that many labels).  Then Q * NF floats for the sums of the instances, for Q = 4 the
 // activations of the block's features (for Q = 2 they lie in the place of the sums until those are ready: there is no room
 // for both beside windows of 16k labels), NT words (features; for Q = 4 another NT: their places among the activations),
-// NEAR2 overflow entries of 8 bytes, 2 * NT words (each lane's share of them), NEAR2 floats (their weight-gradient sums).
+// NEAR2 overflow entries of 8 bytes, 2 * NT words (each lane's share of them), NEAR2 floats (their weight-gradient sums), and a
+// word for what an empty place of a list brings or leaves.
 constexpr int NEAR2 = 512;
 template <int Q> struct BothLayout;
 template <> struct BothLayout<2> { static constexpr uint32_t zero_label = BOTH2_LABELS, row_bytes = (zero_label + 32) * 8, x_bytes = 0, feat_words = 1024; };
 template <> struct BothLayout<4> { static constexpr uint32_t zero_label = BOTH4_LABELS, row_bytes = (zero_label + 32) * 16, x_bytes = 4 * 2048 * 4, feat_words = 2048; };
 template <int Q> constexpr size_t both_lds_bytes() {
     return (size_t)BothLayout<Q>::row_bytes + (size_t)Q * 2048 * 4 + BothLayout<Q>::x_bytes + (size_t)BothLayout<Q>::feat_words * 4 +
-           (size_t)NEAR2 * 8 + (size_t)2 * 1024 * 4 + (size_t)NEAR2 * 4;
+           (size_t)NEAR2 * 8 + (size_t)2 * 1024 * 4 + (size_t)NEAR2 * 4 + 16;
 }
+// places that LDS holds at a time below the sums of the overflow entries; a workgroup with no more has 16-bit places
+template <int Q> constexpr uint32_t both_places() { return (uint32_t)((both_lds_bytes<Q>() - 16 - (size_t)NEAR2 * 4) / 4); }
+template <int Q> constexpr uint32_t no_place() { return (uint32_t)((both_lds_bytes<Q>() - 16) / 4); }
+static_assert(both_places<2>() >= KT_BOTH * NT && both_places<4>() >= KT_BOTH4 * NT && both_lds_bytes<2>() >= (both_places<2>() + 63) * 4 && both_lds_bytes<4>() >= (both_places<4>() + 63) * 4, "a lane's slots have places of their own");
+static_assert(no_place<2>() < 65535 && no_place<4>() < 65535, "16 bits, and one value for no place");
 static_assert(BothLayout<2>::zero_label % 32 == 0 && BothLayout<4>::zero_label % 32 == 0, "zero units on the banks of their number");
 static_assert(both_lds_bytes<2>() <= 160 * 1024 && both_lds_bytes<4>() <= 160 * 1024, "inside LDS");
+// The labels (and, in the kernel for both products, the places) of a lane's slots lie in 16-bit halves of words, four words to a
+// 16-byte piece, a piece of all lanes behind the other: what bounds bringing them in is the number of loads.  Index in 16-bit units of slot t of lane l.
+template <int KT> constexpr int pieces_of() { return (KT / 2 + 3) / 4; }
+template <int KT> __device__ __forceinline__ size_t half_at(size_t wg, int t, int l) { return ((wg * pieces_of<KT>() + t / 8) * NT + l) * 8 + t % 8; }
+// all of a lane's words
+template <int KT>
+__device__ __forceinline__ void load_words(const void* base, uint32_t lane, uint32_t (&w)[KT / 2]) {
+#pragma unroll
+    for (int q = 0; q < pieces_of<KT>(); ++q) {
+        const uint4 v = (reinterpret_cast<const uint4*>(base) + (size_t)q * NT)[lane];
+        w[4 * q] = v.x;
+        if (4 * q + 1 < KT / 2) w[4 * q + 1 < KT / 2 ? 4 * q + 1 : 0] = v.y;
+        if (4 * q + 2 < KT / 2) w[4 * q + 2 < KT / 2 ? 4 * q + 2 : 0] = v.z;
+        if (4 * q + 3 < KT / 2) w[4 * q + 3 < KT / 2 ? 4 * q + 3 : 0] = v.w;
+    }
+}
 template <int KT> struct ListLayout;   // what depends on which kernel the lists are for
 template <> struct ListLayout<68> { static constexpr uint32_t near = 1024; };
 template <> struct ListLayout<36> { static constexpr uint32_t near = NEAR2; };
@@ -324,7 +346,8 @@ k_lf_fill(const int32_t* __restrict__ idx, int64_t m, int k, int d, Cut cut, int
 // which goes through the slots in order, then reads 16 or so neighbouring places from each of the window's nfb
 // workgroups per wavefront -- whole lines; in the order of the lists it would fetch a line per value.
 // slot_at[place] is the way back: the kernel reads the weights in the order of the places, for the same reason.
-// Three kernels: the counts of every run per feature block, their running sums, the places.
+// Three kernels: the counts of every run per feature block, their running sums, the places.  Where a window has one block
+// only, the places are the flat slots themselves, and slot_at is not needed.
 constexpr int SEG = 256;   // slots of a run: one wavefront, four per lane
 __device__ __forceinline__ bool seg_of_wave(int64_t m, int k, const Cut& cut, int nseg, int64_t total, int* w, int* seg, size_t* s0, size_t* s1) {
     const int64_t gs = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -377,9 +400,11 @@ k_lf_seg_place(const int32_t* __restrict__ idx, int64_t m, int k, Cut cut, int n
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     int w, seg; size_t s0, s1;
     const bool on = seg_of_wave(m, k, cut, nseg, total, &w, &seg, &s0, &s1);
-    if (on && lane < cut.nfb) h[wave][lane] = segbase[((size_t)w * cut.nfb + lane) * nseg + seg];
+    if (on && cut.nfb > 1 && lane < cut.nfb) h[wave][lane] = segbase[((size_t)w * cut.nfb + lane) * nseg + seg];
     __syncthreads();
-    if (on)
+    if (on && cut.nfb == 1) {
+        for (size_t e = s0 + lane; e < s1; e += 64) pos[e] = (uint32_t)e;
+    } else if (on)
         for (size_t e = s0 + lane; e < s1; e += 64) {
             const uint32_t p = atomicAdd(&h[wave][cut.S > 1 ? 0u : min((uint32_t)idx[e] / (uint32_t)cut.fpb, 31u)], 1u);
             pos[e] = p;
@@ -400,7 +425,8 @@ k_lf_seg_place(const int32_t* __restrict__ idx, int64_t m, int k, Cut cut, int n
 // registers from (lab / slot: [workgroup][slot][lane]) and what exceeds the allowance into the overflow list.  Any
 // outcome is a valid order: it changes speed, never results.  rounds = 0: the lists stay in the order of ent.
 // pos (if given, see k_lf_seg_place): every entry's place among its workgroup's weight gradients goes along, into rk
-// (beside lab / slot) or ovrk (beside ov); an empty place gets PAD_SLOT.
+// (beside lab / slot) or ovrk (beside ov); an empty place gets PAD_SLOT.  A workgroup of at most small_wg entries, as all are
+// unless the connectivity is skewed, has places of 16 bits in rk, laid out like lab, at the beginning of its part.
 // GS = lanes and banks of a group: 32, or 16 where the gathers are 16 bytes wide (the lanes of a half-wavefront that such a
 // read serves together: 0-3, 12-15, 20-27 and the other 16).
 constexpr int SG_NT = 256;   // lanes per workgroup
@@ -410,7 +436,7 @@ k_lf_schedule(const uint32_t* __restrict__ ent, const uint32_t* __restrict__ ent
               const uint32_t* __restrict__ count, const uint16_t* __restrict__ feat, const uint32_t* __restrict__ caps,
               const uint32_t* __restrict__ ov_base, const uint32_t* __restrict__ ov_off, int k, Cut cut,
               uint32_t zero_label, int rounds, uint16_t* __restrict__ lab, uint32_t* __restrict__ slot, OvEntry* __restrict__ ov,
-              const uint32_t* __restrict__ pos, uint32_t* __restrict__ rk, uint32_t* __restrict__ ovrk) {
+              const uint32_t* __restrict__ pos, uint32_t small_wg, uint32_t* __restrict__ rk, uint32_t* __restrict__ ovrk) {
     constexpr int SG = SG_NT / GS;
     typedef usl_bank_lists<GS, KTOT> Lists;
     __shared__ typename Lists::Lane lists[SG][GS];
@@ -428,6 +454,29 @@ k_lf_schedule(const uint32_t* __restrict__ ent, const uint32_t* __restrict__ ent
     const int cap = zone ? (int)(cw >> 8) : (int)(cw & 0xFFu);
     const int w = (int)(wg / cut.nfb), fb = (int)(wg % cut.nfb);
     auto at = [&](int p) -> size_t { return (wg * KTOT + (zone ? KTOT - 1 - p : p)) * NT + mypos; };
+    const bool small = pos && ent_base[wg + 1] - ent_base[wg] <= small_wg;
+    // four steps' labels, flat slots (PAD_SLOT: none) and places at once: neighbours in the lane's record (caps are multiples of 4)
+    auto leave = [&](int s, const uint32_t (&l)[4], const uint32_t (&e)[4]) {
+        const int t = zone ? KTOT - 4 - s : s;
+        auto two = [&](uint32_t lo, uint32_t hi) { return zone ? hi & 0xFFFFu | lo << 16 : lo & 0xFFFFu | hi << 16; };
+        auto four = [&](const uint32_t (&v)[4]) { return zone ? make_uint2(two(v[2], v[3]), two(v[0], v[1])) : make_uint2(two(v[0], v[1]), two(v[2], v[3])); };
+        *reinterpret_cast<uint2*>(lab + half_at<KTOT>(wg, t, mypos)) = four(l);
+        if (slot) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) slot[at(s + u)] = e[u];
+        }
+        if (pos) {
+            uint32_t place[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) place[u] = e[u] != PAD_SLOT ? pos[e[u]] - ent_base[wg] : PAD_SLOT;
+            if (small) {
+                *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(rk + wg * KTOT * NT) + half_at<KTOT>(0, t, mypos)) = four(place);
+            } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) rk[at(s + u)] = place[u];
+            }
+        }
+    };
     // my list: feature, length, where its entries are; label of an entry = its flat slot / k, counted from the window's first
     const uint32_t f = feat[(wg * 2 + zone) * NT + mypos];
     const bool exists = (int)f < min(cut.fpb, cut.vd - fb * cut.fpb);
@@ -454,10 +503,14 @@ k_lf_schedule(const uint32_t* __restrict__ ent, const uint32_t* __restrict__ ent
         if (pos) ovrk[(size_t)ov_base[wg] + ov_off[bin] + (len - (uint32_t)cap)] = PAD_SLOT;
     }
     if (rounds <= 0) {
-        for (int s = 0; s < cap; ++s) {
-            lab[at(s)] = s < n ? (uint16_t)label_of(my[s]) : (uint16_t)zero_label;
-            if (slot) slot[at(s)] = s < n ? my[s] : PAD_SLOT;
-            if (pos) rk[at(s)] = s < n ? pos[my[s]] - ent_base[wg] : PAD_SLOT;
+        for (int s = 0; s < cap; s += 4) {
+            uint32_t l[4], e[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                e[u] = s + u < n ? my[s + u] : PAD_SLOT;
+                l[u] = s + u < n ? label_of(e[u]) : zero_label;
+            }
+            leave(s, l, e);
         }
         return;   // the whole wavefront: rounds is the same for all
     }
@@ -491,14 +544,16 @@ k_lf_schedule(const uint32_t* __restrict__ ent, const uint32_t* __restrict__ ent
         }
     }
     // out, several places' loads in flight together
-#pragma unroll 4
-    for (int s = 0; s < cap; ++s) {
-        const int pick = ord[gl][lane][s];
-        const bool real = pick < 128;
-        const uint32_t e = real ? my[pick] : 0u;
-        lab[at(s)] = real ? (uint16_t)label_of(e) : (uint16_t)(zero_label + (uint32_t)(pick - 128));
-        if (slot) slot[at(s)] = real ? e : PAD_SLOT;
-        if (pos) rk[at(s)] = real ? pos[e] - ent_base[wg] : PAD_SLOT;
+#pragma unroll 2
+    for (int s = 0; s < cap; s += 4) {
+        uint32_t l[4], e[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int pick = ord[gl][lane][s + u];
+            e[u] = pick < 128 ? my[pick] : PAD_SLOT;
+            l[u] = pick < 128 ? label_of(e[u]) : zero_label + (uint32_t)(pick - 128);
+        }
+        leave(s, l, e);
     }
 }
 
@@ -552,22 +607,19 @@ k_bwi_lds(const float* __restrict__ g, const TS* __restrict__ W, int64_t m, int 
     uint32_t pk[KT_BWI / 2];
     float wt[KT_BWI];
     const uint32_t last_slot = (uint32_t)(m * k - 1);
+    load_words<KT_BWI>(reinterpret_cast<const uint4*>(lab) + wg * pieces_of<KT_BWI>() * NT, threadIdx.x, pk);
 #pragma unroll
     for (int q = 0; q < KT_BWI / 4; ++q) {
         const bool used = q * 4 < acap || q * 4 >= KT_BWI - bcap;   // the same for the whole wavefront
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int t = q * 4 + u;
-            uint32_t l16 = 0;
             float wv = 0.f;
             if (used) {
-                const size_t at = (wg * KT_BWI + t) * NT + threadIdx.x;
-                l16 = lab[at];
-                const uint32_t s = slot[at];
+                const uint32_t s = slot[(wg * KT_BWI + t) * NT + threadIdx.x];
                 wv = usl_load_f32<TS>(W, (size_t)min(s, last_slot));   // an empty place reads some weight and drops it
                 wv = s != PAD_SLOT ? wv : 0.f;
             }
-            if (t & 1) pk[t >> 1] |= l16 << 16; else pk[t >> 1] = l16;
             wt[t] = wv;
         }
     }
@@ -830,58 +882,98 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
     uint32_t lane = threadIdx.x;   // taken afresh for each window: nothing computed from it lives through the passes
     asm volatile("" : "+v"(lane));
     const size_t wg = (size_t)__builtin_amdgcn_readfirstlane(w * nfb + fb);
-    const uint32_t cw = caps[wg * (NT / 64) + (lane >> 6)];
-    const int acap = __builtin_amdgcn_readfirstlane((int)(cw & 0xFFu)), bcap = __builtin_amdgcn_readfirstlane((int)(cw >> 8));
     uint32_t pk[KT / 2];
     float wt[KT], gw[KT];
     // The weights come in the order of the places (slot_at; rk: see the end of the kernel) and are picked up from LDS: in the
     // order of the lists every value was a 128-byte line of its own (96 of 1320 us at m = 500k, d = 32k, k = 32, 25 of 210 at
-    // m = 200k, d = 8k, b = 64).  All loads are in flight together, those of slots that the wavefront does not visit included
-    // (their places hold anything): in batches, or behind branches, they would wait out a memory latency each.
-    constexpr uint32_t CH = (uint32_t)((both_lds_bytes<Q>() - (size_t)NEAR2 * 4) / 4);   // places LDS holds at a time
+    // m = 200k, d = 8k, b = 64).  What bounds a window's beginning is the number of loads and the waits for them: the lane's
+    // labels and places come 16 bytes at a time, the places of all weights in one go, the weights by LDS-DMA without a register.
+    // With loads of 4 bytes and a wait for every eight places a window began in 44 us at m = 500k and ended in 10 (clock
+    // counters), now 23 and 8; the step 33.3 -> 31.6 us at m = 1024, d = 64, k = 8, b = 16, 258 -> 251 at m = 200k, d = 8k,
+    // k = 32, b = 64 (bfloat16), 2034 -> 1999 at m = 500k, d = 32k, k = 32, b = 256.
+    constexpr uint32_t CH = both_places<Q>();   // places LDS holds at a time
     float* perm = reinterpret_cast<float*>(lds_raw);
     const uint32_t e0 = ent_base[wg], n_ent = ent_base[wg + 1] - e0;
+    const uint32_t ov0 = ov_base[wg], ov_n = ov_base[wg + 1] - ov0;
+    uint32_t tid4 = threadIdx.x * 4u;
+    asm volatile("" : "+v"(tid4));
+    const uint32_t first_slot = (uint32_t)w * (uint32_t)cut.wl * (uint32_t)k;   // of the window: 32-bit offsets from there
+    const TS* W_window = W + first_slot;
+    const bool one_go = n_ent <= CH;   // (unless the connectivity is skewed)
+    const uint32_t cw = caps[wg * (NT / 64) + (lane >> 6)];
+    uint32_t r[KT / 2];
+    load_words<KT>(rk + wg * KT * NT, lane, r);
+    load_words<KT>(reinterpret_cast<const uint4*>(lab) + wg * pieces_of<KT>() * NT, lane, pk);
+    const uint32_t fa = feat[(wg * 2 + 0) * NT + lane], fbb = feat[(wg * 2 + 1) * NT + lane];
+    const uint32_t ovra = ovr[(wg * 2 + 0) * NT + lane], ovrb = ovr[(wg * 2 + 1) * NT + lane];
+    OvEntry o = {0, 0, PAD_SLOT};
+    if (lane < min((uint32_t)NEAR2, ov_n)) o = ov[(size_t)ov0 + lane];
+    __builtin_amdgcn_sched_barrier(0);
+    // the weights of the first N * NT places: float32 ones by LDS-DMA, a lane's own address each and no registers
+    auto bring = [&](auto N_) {
+        constexpr int N = decltype(N_)::value;
+        const uint32_t n_bytes = min(n_ent, CH) * 4;
+        uint32_t at = threadIdx.x * 4u, sl[N];   // (a lane past the end reads the last place again)
+        asm volatile("" : "+v"(at));
+        const uint32_t wave_at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+        if (nfb > 1) {
 #pragma unroll
-    for (int t = 0; t < KT; ++t) wt[t] = 0.f;
-    for (uint32_t c0 = 0; c0 < n_ent; c0 += CH) {
-        const uint32_t n = min(CH, n_ent - c0);
-        __syncthreads();
-        for (uint32_t r0 = lane; r0 < n; r0 += 8 * NT) {
-            uint32_t sl[8];
-            float v[8];
+            for (int u = 0; u < N; ++u) sl[u] = at_byte(slot_at + e0, min(at + (uint32_t)(u * NT * 4), n_bytes - 4));
+        } else {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) sl[u] = (slot_at + e0 + c0)[min(r0 + u * NT, n - 1)];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = usl_load_f32<TS>(W, (size_t)sl[u]);
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (r0 + u * NT < n) perm[r0 + u * NT] = v[u];
-        }
-        __syncthreads();
-        uint32_t tid4 = threadIdx.x * 4u;   // taken afresh: addresses are rebuilt from it, not kept (and spilled)
-        asm volatile("" : "+v"(tid4));
-        uint32_t r[KT];
-#pragma unroll
-        for (int t = 0; t < KT; ++t) r[t] = at_byte(rk + (wg * KT + t) * NT, tid4) - c0;   // an empty place: far beyond
-#pragma unroll
-        for (int t = 0; t < KT; ++t) {
-            const bool used = t / 4 * 4 < acap || t / 4 * 4 >= KT - bcap;   // the same for the whole wavefront
-            if (used && r[t] < n) wt[t] = perm[r[t]];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    {
-        uint32_t lb[KT];
-#pragma unroll
-        for (int t = 0; t < KT; ++t) lb[t] = (lab + wg * KT * NT)[(uint32_t)t * NT + lane];
-#pragma unroll
-        for (int t = 0; t < KT; ++t) {
-            const bool used = t / 4 * 4 < acap || t / 4 * 4 >= KT - bcap;
-            const uint32_t l16 = used ? lb[t] : 0u;
-            if (t & 1) pk[t >> 1] |= l16 << 16; else pk[t >> 1] = l16;
+            for (int u = 0; u < N; ++u) sl[u] = e0 + min(at + (uint32_t)(u * NT * 4), n_bytes - 4) / 4;
         }
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (sizeof(TS) == 4) {
+#pragma unroll
+            for (int u = 0; u < N; ++u)
+                if (wave_at + (uint32_t)(u * NT * 4) < n_bytes)   // (whole wavefronts: at most 63 places behind the last one are written too)
+                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(W_window + (sl[u] - first_slot)),
+                                                     (__attribute__((address_space(3))) void*)(lds_raw + wave_at + (size_t)(u * NT * 4)), 4, 0, 0);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        } else {
+            constexpr int B = N < 10 ? N : (N + 3) / 4;
+#pragma unroll
+            for (int u0 = 0; u0 < N; u0 += B) {
+                TS v[B];
+#pragma unroll
+                for (int u = 0; u < B; ++u)
+                    if (u0 + u < N) v[u] = at_byte(W_window, (sl[u0 + u] - first_slot) * (uint32_t)sizeof(TS));
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < B; ++u)
+                    if (u0 + u < N && wave_at + (uint32_t)((u0 + u) * NT * 4) < n_bytes)
+                        *reinterpret_cast<float*>(lds_raw + at + (uint32_t)((u0 + u) * NT * 4)) = usl_to_f32(v[u]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+    __syncthreads();   // LDS is free
+    if (one_go && n_ent > 8 * NT) bring(std::integral_constant<int, ((int)CH + NT - 1) / NT>{});
+    else if (one_go && n_ent > 0) bring(std::integral_constant<int, 8>{});
+    const float ov_weight = o.slot != PAD_SLOT ? usl_to_f32(W_window[o.slot - first_slot]) : 0.f;
+    const int acap = __builtin_amdgcn_readfirstlane((int)(cw & 0xFFu)), bcap = __builtin_amdgcn_readfirstlane((int)(cw >> 8));
+    // (a skewed connectivity: one by one, and the places are just the lane's slots)
+    auto own_places = [&](uint32_t (&places)[KT / 2]) {
+#pragma unroll
+        for (int t = 0; t < KT / 2; ++t) places[t] = (uint32_t)(2 * t * NT) + tid4 / 4 | ((uint32_t)((2 * t + 1) * NT) + tid4 / 4) << 16;
+    };
+    auto used = [&](int t) { return t / 4 * 4 < acap || t / 4 * 4 >= KT - bcap; };   // the same for the whole wavefront
+    constexpr uint32_t NOWHERE = no_place<Q>();
+    auto place_of = [&](const uint32_t (&places)[KT / 2], int t) { return min(t & 1 ? places[t / 2] >> 16 : places[t / 2] & 0xFFFFu, NOWHERE); };
+    if (threadIdx.x == 0) perm[NOWHERE] = 0.f;
+    if (!one_go) {
+#pragma unroll 1
+        for (int t = 0; t < KT; ++t) {
+            const uint32_t place = used(t) ? (rk + (wg * KT + t) * NT)[threadIdx.x] : PAD_SLOT;
+            perm[t * NT + threadIdx.x] = place != PAD_SLOT ? usl_load_f32<TS>(W, (size_t)(nfb > 1 ? (slot_at + e0)[place] : e0 + place)) : 0.f;
+        }
+        own_places(r);
     }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < KT; ++t) wt[t] = perm[place_of(r, t)];   // (of slots that nobody visits: anything)
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < KT; ++t) {   // (written here, not by the compiler at the top: there the registers are needed)
         float zero = 0.f;
@@ -889,7 +981,6 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
         gw[t] = zero;
     }
     __syncthreads();   // LDS is free
-    const uint32_t ov0 = ov_base[wg], ov_n = ov_base[wg + 1] - ov0;
     const float* row = reinterpret_cast<const float*>(lds_raw);           // row[Q * label + q]: instance q of a pass
     float* outbuf = reinterpret_cast<float*>(lds_raw + BothLayout<Q>::row_bytes);   // [Q][NF]
     TS* xbuf = reinterpret_cast<TS*>(outbuf + (BothLayout<Q>::x_bytes ? Q * NF : 0));   // Q = 4: [NF][4]; Q = 2: [2][NF], in the place of the sums
@@ -898,23 +989,18 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
     uint32_t* ovr_a = reinterpret_cast<uint32_t*>(ov_near + NEAR2);       // [NT] start | n << 16
     uint32_t* ovr_b = ovr_a + NT;
     float* ov_sum = reinterpret_cast<float*>(ovr_b + NT);                 // [NEAR2]
-    {
-        const uint32_t fa = feat[(wg * 2 + 0) * NT + lane], fbb = feat[(wg * 2 + 1) * NT + lane];
-        feat_of[lane] = fa | fbb << 16;
-        // Q = 4: where the features' activations are (a list of a feature that does not exist reads some place, and is empty)
-        if (Q == 4) feat_of[NT + lane] = cut.S == 1 ? fa | fbb << 16 : fa % (uint32_t)d | fbb % (uint32_t)d << 16;
-    }
+    lane = threadIdx.x;
+    asm volatile("" : "+v"(lane));
+    const uint32_t feat2 = fa | fbb << 16;
+    feat_of[lane] = feat2;
+    // Q = 4: where the features' activations are (a list of a feature that does not exist reads some place, and is empty)
+    if (Q == 4) feat_of[NT + lane] = cut.S == 1 ? feat2 : (feat2 & 0xFFFFu) % (uint32_t)d | (feat2 >> 16) % (uint32_t)d << 16;
     if (lane < NEAR2) {
-        uint2 e = make_uint2(ZL * U, 0u);
-        if (lane < ov_n) {
-            const OvEntry o = ov[(size_t)ov0 + lane];
-            e = make_uint2((uint32_t)o.label * U, o.slot == PAD_SLOT ? 0u : __float_as_uint(usl_load_f32<TS>(W, (size_t)o.slot)));
-        }
-        ov_near[lane] = e;
+        ov_near[lane] = make_uint2(o.slot != PAD_SLOT ? (uint32_t)o.label * U : ZL * U, __float_as_uint(ov_weight));   // an empty place: the unit of zeros, no weight
         ov_sum[lane] = 0.f;
     }
-    ovr_a[lane] = ovr[(wg * 2 + 0) * NT + lane];
-    ovr_b[lane] = ovr[(wg * 2 + 1) * NT + lane];
+    ovr_a[lane] = ovra;
+    ovr_b[lane] = ovrb;
     if (lane < 32 * Q) reinterpret_cast<uint32_t*>(lds_raw)[ZL * Q + lane] = 0u;   // what empty places read
     for (uint32_t q = NEAR2 + lane; q < ov_n; q += NT) ovgw[(size_t)ov0 + q] = 0.f;   // entry q is lane q % NT's
     const int nl = (int)max((int64_t)0, min((int64_t)cut.wl, m - (int64_t)w * cut.wl));   // labels of this window (the last one may be short)
@@ -1119,7 +1205,9 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
                 float u[Q];
                 unit_of(row + (size_t)o.label * Q, u);
                 float t = ovgw[(size_t)ov0 + q];
-                const size_t xf = cut.S > 1 ? o.feature % (uint32_t)d : o.feature;
+                uint32_t dd = (uint32_t)d;
+                asm volatile("" : "+s"(dd));   // (its reciprocal is taken here, not kept in a register)
+                const size_t xf = cut.S > 1 ? o.feature % dd : o.feature;
 #pragma unroll
                 for (int j = 0; j < Q; ++j) {
                     unsafeAtomicAdd(&outbuf[j * NF + o.feature], wv * u[j]);
@@ -1157,25 +1245,45 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
     // they would be 4 bytes each into lines that 16 workgroups share (0.29 ms at m = 500k, a fifth of this kernel); the
     // Adam kernel picks them up through pos instead, and finds neighbours there.  As many places at a time as LDS
     // holds below ov_sum (all of them, unless the connectivity is skewed).
-    for (uint32_t c0 = 0; c0 < n_ent; c0 += CH) {
-        __syncthreads();   // the last pass's reads of LDS, the owners' last additions to ov_sum; the copy before
-        uint32_t tid4 = threadIdx.x * 4u;   // taken afresh: addresses are rebuilt from it, not kept (and spilled)
-        asm volatile("" : "+v"(tid4));
-        uint32_t r[KT];
+    tid4 = threadIdx.x * 4u;   // taken afresh: addresses are rebuilt from it, not kept (and spilled)
+    asm volatile("" : "+v"(tid4));
+    float* to = stage + e0;   // (a later pass over the batch adds to the earlier ones)
+    uint32_t places[KT / 2];
+    if (one_go) load_words<KT>(rk + wg * KT * NT, tid4 / 4, places);
+    else own_places(places);
+    const uint32_t mine = threadIdx.x < ov_n ? (ovrk + (size_t)ov0)[threadIdx.x] : PAD_SLOT;
+    __syncthreads();   // the last pass's reads of LDS, the owners' last additions to ov_sum
 #pragma unroll
-        for (int t = 0; t < KT; ++t) r[t] = at_byte(rk + (wg * KT + t) * NT, tid4) - c0;   // an empty place: far beyond
+    for (int q = 0; q < KT / 4; ++q) {
+        if (!used(4 * q)) continue;
 #pragma unroll
-        for (int t = 0; t < KT; ++t) {
-            const bool used = t / 4 * 4 < acap || t / 4 * 4 >= KT - bcap;
-            if (used && r[t] < CH) perm[r[t]] = gw[t];
-        }
-        for (uint32_t q = threadIdx.x; q < ov_n; q += NT) {
-            const uint32_t r = ovrk[(size_t)ov0 + q] - c0;
-            if (r < CH) perm[r] = q < (uint32_t)NEAR2 ? ov_sum[q] : ovgw[(size_t)ov0 + q];
+        for (int t = 4 * q; t < 4 * q + 4; ++t) perm[place_of(places, t)] = gw[t];
+    }
+    const float near_sum = threadIdx.x < min((uint32_t)NEAR2, ov_n) ? ov_sum[threadIdx.x] : 0.f;
+    if (one_go) {
+        if (mine != PAD_SLOT) perm[mine] = threadIdx.x < (uint32_t)NEAR2 ? near_sum : ovgw[(size_t)ov0 + threadIdx.x];
+        for (uint32_t q = NT + threadIdx.x; q < ov_n; q += NT) {
+            const uint32_t place = (ovrk + (size_t)ov0)[q];
+            if (place != PAD_SLOT) perm[place] = ovgw[(size_t)ov0 + q];
         }
         __syncthreads();
-        for (uint32_t r = threadIdx.x; r < min(CH, n_ent - c0); r += NT)   // a later pass over the batch adds to the earlier ones
-            stage[(size_t)e0 + c0 + r] = accumulate ? stage[(size_t)e0 + c0 + r] + perm[r] : perm[r];
+        for (uint32_t q = threadIdx.x * 4; q < n_ent; q += NT * 4) {
+            const float4 v = *reinterpret_cast<const float4*>(perm + q);
+            const f32x4_any sum = {v.x, v.y, v.z, v.w};
+            if (q + 4 <= n_ent) {
+                f32x4_any* at = reinterpret_cast<f32x4_any*>(to + q);
+                *at = accumulate ? *at + sum : sum;
+            } else {
+                for (uint32_t u = 0; q + u < n_ent; ++u) to[q + u] = accumulate ? to[q + u] + sum[u] : sum[u];
+            }
+        }
+    } else {
+        auto leave = [&](uint32_t place, float sum) { if (place != PAD_SLOT) to[place] = accumulate ? to[place] + sum : sum; };
+#pragma unroll 1
+        for (int t = 0; t < KT; ++t)
+            if (used(t)) leave((rk + (wg * KT + t) * NT)[threadIdx.x], perm[t * NT + threadIdx.x]);
+        leave(mine, threadIdx.x < (uint32_t)NEAR2 ? near_sum : mine != PAD_SLOT ? ovgw[(size_t)ov0 + threadIdx.x] : 0.f);
+        for (uint32_t q = NT + threadIdx.x; q < ov_n; q += NT) leave((ovrk + (size_t)ov0)[q], ovgw[(size_t)ov0 + q]);
     }
     }
 }
@@ -1232,6 +1340,8 @@ static size_t lf_partial_bytes() {
     return cached;
 }
 
+// where rk begins behind pos: 16-byte pieces
+static size_t rk_at(size_t N) { return (N + 3) / 4 * 4; }
 // runs of SEG slots in a window of the lists for both products
 static int lf_runs(const usl_ctx* c, const Cut& cut) { return (int)(((int64_t)cut.wl * c->k + SEG - 1) / SEG); }
 
@@ -1290,12 +1400,12 @@ static usl_status lf_build_t(usl_ctx* c, const int32_t* idx, int set, const Cut&
             share(&L.caps, (size_t)nwg * (NT / 64) * 4);
             share(&L.ov_base, ((size_t)nwg * 4 + 2) * 4);
             share(&L.ovr, (size_t)nwg * 2 * NT * 4);
-            share(&L.lab, (size_t)nwg * KT * NT * 2);
+            share(&L.lab, (size_t)nwg * pieces_of<KT>() * NT * 16);
             share(&L.slot, (set == 1 ? N : (size_t)nwg * KT * NT) * 4);   // by place, or by list
             share(&L.ent, N * 4);
             share(&L.ov, (N + nbins) * sizeof(OvEntry));   // worst case, + an empty place per list
-            if (set == 1)   // pos [N], rk [nwg][KT][NT], ovrk [N + nbins], the counts of the runs [nwg][nseg]
-                share(&L.pos, (N + (size_t)nwg * KT * NT + N + nbins + (size_t)nwg * lf_runs(c, cut)) * 4);
+            if (set == 1)   // pos [N] (and up to a multiple of 4), rk [nwg][KT][NT], ovrk [N + nbins], the counts of the runs [nwg][nseg]
+                share(&L.pos, (rk_at(N) + (size_t)nwg * KT * NT + N + nbins + (size_t)nwg * lf_runs(c, cut)) * 4);
             if (turn == 0) USL_TRY(usl_reserve(c, &L.mem, &L.mem_cap, total));
         }
     }
@@ -1324,18 +1434,20 @@ static usl_status lf_build_t(usl_ctx* c, const int32_t* idx, int set, const Cut&
     if (set == 1) {   // where the weight gradients go (before the order of the lists, which hands the places on)
         const int nseg = lf_runs(c, cut);
         const int64_t total = (int64_t)nwin * nseg;
-        uint32_t* segcnt = L.pos + N + (size_t)nwg * KT * NT + N + nbins;
+        uint32_t* segcnt = L.pos + rk_at(N) + (size_t)nwg * KT * NT + N + nbins;
         const dim3 sg((unsigned)((total + 3) / 4));
-        hipLaunchKernelGGL(k_lf_seg_count, sg, dim3(256), 0, c->stream, idx, c->m, c->k, cut, nseg, total, segcnt);
-        hipLaunchKernelGGL(k_lf_seg_scan, dim3((unsigned)nwg), dim3(256), 0, c->stream, segcnt, nseg, ent_base);
+        if (nfb > 1) {   // (one block: the places are the flat slots)
+            hipLaunchKernelGGL(k_lf_seg_count, sg, dim3(256), 0, c->stream, idx, c->m, c->k, cut, nseg, total, segcnt);
+            hipLaunchKernelGGL(k_lf_seg_scan, dim3((unsigned)nwg), dim3(256), 0, c->stream, segcnt, nseg, ent_base);
+        }
         hipLaunchKernelGGL(k_lf_seg_place, sg, dim3(256), 0, c->stream, idx, c->m, c->k, cut, nseg, total, segcnt, L.pos, L.slot);
     }
     const uint32_t zero_label = set == 0 ? ZERO_LABEL : Q == 4 ? BothLayout<4>::zero_label : BothLayout<2>::zero_label;
 #define USL_LF_SCHED(GS)                                                                                                    \
     hipLaunchKernelGGL((k_lf_schedule<KT, GS>), dim3((unsigned)(nwg * 64 / (SG_NT / 32))), dim3(SG_NT), 0, c->stream, L.ent, \
                        ent_base, L.where, L.count, L.feat, L.caps, ov_base, L.ovoff, c->k, cut, zero_label, rounds,          \
-                       L.lab, set == 1 ? nullptr : L.slot, reinterpret_cast<OvEntry*>(L.ov), set == 1 ? L.pos : nullptr,      \
-                       set == 1 ? L.pos + N : nullptr, set == 1 ? L.pos + N + (size_t)nwg * KT * NT : nullptr)
+                       L.lab, set == 1 ? nullptr : L.slot, reinterpret_cast<OvEntry*>(L.ov), set == 1 ? L.pos : nullptr, Q == 4 ? both_places<4>() : both_places<2>(),      \
+                       set == 1 ? L.pos + rk_at(N) : nullptr, set == 1 ? L.pos + rk_at(N) + (size_t)nwg * KT * NT : nullptr)
     if (Q == 4) USL_LF_SCHED(16);
     else USL_LF_SCHED(32);
 #undef USL_LF_SCHED
@@ -1465,7 +1577,7 @@ usl_status usl_both_lds_run(usl_ctx* c, const float* g, const void* x, const int
             hipLaunchKernelGGL((k_both_lds<TS, QQ>), grid, dim3(NT), both_lds_bytes<QQ>(), c->stream, g + (size_t)i0 * c->m, \
                                (const TS*)W, (const TS*)xs + (size_t)(QQ == 4 ? i0 / 4 : i0) * x_stride, x_stride, c->m, c->k, rows, c->d, \
                                dp, cut, L.lab, L.slot, L.feat, L.caps, L.ov_base, reinterpret_cast<const OvEntry*>(L.ov), L.ovr, \
-                               direct ? grad_x + (size_t)i0 * c->d : L.partial, L.pos + N, L.pos + N + rkn, L.ov_base + 2 * ((size_t)cut.nwin * cut.nfb) + 1, L.stage, \
+                               direct ? grad_x + (size_t)i0 * c->d : L.partial, L.pos + rk_at(N), L.pos + rk_at(N) + rkn, L.ov_base + 2 * ((size_t)cut.nwin * cut.nfb) + 1, L.stage, \
                                ovgw, chains, parts, per_part, N, N + nbins, gate, i0 > 0 ? 1 : 0, direct ? out->stale : nullptr);                                         \
         } while (0)
         if (c->storage == USL_F32) { if (Q == 4) USL_BOTH(float, 4, 0); else USL_BOTH(float, 2, 1); }

@@ -84,7 +84,7 @@ struct usl_ctx {
         uint32_t* caps;                            // [wg][16] slots the wavefronts visit
         uint32_t* ov_base;                         // [wg+1] start of a workgroup's overflow entries, [wg] their number; the same two for all its entries
         uint32_t* ovr;                             // [wg][2][1024] a lane's lists' share of the overflow entries held in LDS
-        uint16_t* lab;                             // [wg][slots][1024] label within the window
+        uint16_t* lab;                             // [wg][slots / 8][1024][8] label within the window
         uint32_t* slot;                            // flat slot j*k+t (where the weight lives): [0] [wg][slots][1024]; [1] [m*k], by place
         uint32_t* ent;                             // [m*k] flat slots grouped by (workgroup, feature), before the bank-aware order
         uint32_t* ovoff;                           // [nwin*d] where a list's overflow starts in its workgroup's
@@ -279,6 +279,8 @@ __device__ __forceinline__ usl_loss_of usl_loss_one(int kind, float z, float y, 
     }
     return o;
 }
+__device__ __forceinline__ float usl_to_f32(float v) { return v; }
+__device__ __forceinline__ float usl_to_f32(uint16_t v) { return usl_bf16_to_f32(v); }
 template <typename TS> __device__ __forceinline__ float usl_load_f32(const TS* p, size_t i);
 template <> __device__ __forceinline__ float usl_load_f32<float>(const float* p, size_t i) {
     return p[i];
