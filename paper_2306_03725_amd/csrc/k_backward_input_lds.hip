@@ -50,25 +50,29 @@ static_assert(ZERO_LABEL % 32 == 0 && ZERO_LABEL + 31 < 65536 && LDS_BYTES <= 16
 // LDS of the kernel for both backward products.  It stages the slices of Q instances interleaved: label l's Q values are the
 // 4 Q bytes at 4 Q l (one ds_read_b64 or ds_read_b128 brings them), behind them 32 units of zeros (zero_label is their
 // "label": a window has at most that many labels).  Then Q * NF floats for the sums of the instances, for Q = 4 the
-// activations of the block's features (for Q = 2 they lie in the place of the sums until those are ready: there is no room
-// for both beside windows of 16k labels), NT words (features; for Q = 4 another NT: their places among the activations),
-// NEAR2 overflow entries of 8 bytes, 2 * NT words (each lane's share of them), NEAR2 floats (their weight-gradient sums), and a
-// word for what an empty place of a list brings or leaves.
-constexpr int NEAR2 = 512;
-template <int Q> struct BothLayout;
-template <> struct BothLayout<2> { static constexpr uint32_t zero_label = BOTH2_LABELS, row_bytes = (zero_label + 32) * 8, x_bytes = 0, feat_words = 1024; };
-template <> struct BothLayout<4> { static constexpr uint32_t zero_label = BOTH4_LABELS, row_bytes = (zero_label + 32) * 16, x_bytes = 4 * 2048 * 4, feat_words = 2048; };
-template <int Q> constexpr size_t both_lds_bytes() {
-    return (size_t)BothLayout<Q>::row_bytes + (size_t)Q * 2048 * 4 + BothLayout<Q>::x_bytes + (size_t)BothLayout<Q>::feat_words * 4 +
-           (size_t)NEAR2 * 8 + (size_t)2 * 1024 * 4 + (size_t)NEAR2 * 4 + 16;
+// activations of the block's features where there is room for them (OWN; else they lie in the place of the sums until those are
+// ready), NT words (features; with OWN another NT: their places among the activations), NEAR2 overflow entries of 8 bytes, NT
+// words (each lane's share of them), NEAR2 floats (their weight-gradient sums), and a word for what an empty place of a list
+// brings or leaves.
+constexpr int NEAR2 = 510;   // even, and counted in pairs by 8 bits
+template <int Q, bool OWN> struct BothLayout {
+    static constexpr uint32_t zero_label = Q == 2 ? BOTH2_LABELS : OWN ? BOTH4_OWN_LABELS : BOTH4_LABELS;
+    static constexpr uint32_t row_bytes = (zero_label + 32) * 4 * Q, x_bytes = OWN ? 4 * 2048 * 4 : 0, feat_words = OWN ? 2048 : 1024;
+};
+template <int Q, bool OWN> constexpr size_t both_lds_bytes() {
+    typedef BothLayout<Q, OWN> L;
+    return (size_t)L::row_bytes + (size_t)Q * 2048 * 4 + L::x_bytes + (size_t)L::feat_words * 4 + (size_t)NEAR2 * 8 + (size_t)1024 * 4 + (size_t)NEAR2 * 4 + 16;
 }
 // places that LDS holds at a time below the sums of the overflow entries; a workgroup with no more has 16-bit places
-template <int Q> constexpr uint32_t both_places() { return (uint32_t)((both_lds_bytes<Q>() - 16 - (size_t)NEAR2 * 4) / 4); }
-template <int Q> constexpr uint32_t no_place() { return (uint32_t)((both_lds_bytes<Q>() - 16) / 4); }
-static_assert(both_places<2>() >= KT_BOTH * NT && both_places<4>() >= KT_BOTH4 * NT && both_lds_bytes<2>() >= (both_places<2>() + 63) * 4 && both_lds_bytes<4>() >= (both_places<4>() + 63) * 4, "a lane's slots have places of their own");
-static_assert(no_place<2>() < 65535 && no_place<4>() < 65535, "16 bits, and one value for no place");
-static_assert(BothLayout<2>::zero_label % 32 == 0 && BothLayout<4>::zero_label % 32 == 0, "zero units on the banks of their number");
-static_assert(both_lds_bytes<2>() <= 160 * 1024 && both_lds_bytes<4>() <= 160 * 1024, "inside LDS");
+template <int Q, bool OWN> constexpr uint32_t both_places() { return (uint32_t)((both_lds_bytes<Q, OWN>() - 16 - (size_t)NEAR2 * 4) / 4); }
+template <int Q, bool OWN> constexpr uint32_t no_place() { return (uint32_t)((both_lds_bytes<Q, OWN>() - 16) / 4); }
+template <int Q, bool OWN> constexpr bool both_layout_ok() {
+    return both_places<Q, OWN>() >= (Q == 4 ? KT_BOTH4 : KT_BOTH) * NT          // a lane's slots have places of their own
+           && both_lds_bytes<Q, OWN>() >= (both_places<Q, OWN>() + 63) * 4 && no_place<Q, OWN>() < 65535   // 16 bits, and one value for no place
+           && BothLayout<Q, OWN>::zero_label % 32 == 0                          // zero units on the banks of their number
+           && both_lds_bytes<Q, OWN>() <= 160 * 1024;
+}
+static_assert(both_layout_ok<2, false>() && both_layout_ok<4, true>() && both_layout_ok<4, false>(), "LDS of k_both_lds");
 // The labels (and, in the kernel for both products, the places) of a lane's slots lie in 16-bit halves of words, four words to a
 // 16-byte piece, a piece of all lanes behind the other: what bounds bringing them in is the number of loads.  Index in 16-bit units of slot t of lane l.
 template <int KT> constexpr int pieces_of() { return (KT / 2 + 3) / 4; }
@@ -84,6 +88,14 @@ __device__ __forceinline__ void load_words(const void* base, uint32_t lane, uint
         if (4 * q + 2 < KT / 2) w[4 * q + 2 < KT / 2 ? 4 * q + 2 : 0] = v.z;
         if (4 * q + 3 < KT / 2) w[4 * q + 3 < KT / 2 ? 4 * q + 3 : 0] = v.w;
     }
+}
+// Where label l of a window of wl lies in the rows of k_both_lds, in units of Q values.  A lane brings four neighbouring labels
+// of every instance: four writes of 16 bytes with four instances, and with the labels in order a wavefront's would be 64
+// bytes apart, four to a bank.  So each of the four goes into a quarter of the row of its own, next to those of the other
+// lanes; the lists hold these numbers instead of the labels', which costs nothing.  (Two instances, two writes 32 bytes apart:
+// in order; by halves it measured the same.)
+template <int Q> __host__ __device__ __forceinline__ uint32_t unit_of_label(uint32_t l, uint32_t wl) {
+    return Q == 4 ? (l & 3u) * (wl / 4u) + (l >> 2) : l;
 }
 template <int KT> struct ListLayout;   // what depends on which kernel the lists are for
 template <> struct ListLayout<68> { static constexpr uint32_t near = 1024; };
@@ -487,7 +499,8 @@ k_lf_schedule(const uint32_t* __restrict__ ent, const uint32_t* __restrict__ ent
     auto label_of = [&](uint32_t e) -> uint32_t {   // e / k, at most one too low at first
         uint32_t q = __umulhi(e, inv_k);
         if (e - q * (uint32_t)k >= (uint32_t)k) ++q;
-        return q - (uint32_t)w * (uint32_t)cut.wl;
+        q -= (uint32_t)w * (uint32_t)cut.wl;
+        return KTOT == KT_BOTH4 ? unit_of_label<4>(q, (uint32_t)cut.wl) : q;
     };
     const int n = (int)min(len, (uint32_t)cap);     // entries that get a register slot
     for (uint32_t p = (uint32_t)cap; p < len; ++p) {   // the others: to the list's part of the overflow list
@@ -846,10 +859,10 @@ template <typename T>
 __device__ __forceinline__ T at_byte(const T* base, uint32_t byte) { return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + byte); }
 
 // Q = 2: windows of up to 15 968 labels (wide layers), x as rows of x_stride elements, 16-byte aligned.
-// Q = 4: windows of up to 4 672 labels, x interleaved by fours (x_stride = elements from group to group, k_interleave).
+// Q = 4: windows of up to 7 232 labels (4 672 where OWN), x interleaved by fours (x_stride = elements from group to group, k_interleave).
 // grid: at least windows * parts of the batch * feature blocks, a multiple of 8.  A part of the batch (rows_per_part
 // instances, a multiple of Q) leaves its weight gradient at stage + part * part_stride.
-template <typename TS, int Q>
+template <typename TS, int Q, bool OWN>
 __global__ void __launch_bounds__(NT)
 k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __restrict__ x, size_t x_stride, int64_t m, int k, int rows, int d,
            int dp, Cut cut, const uint16_t* __restrict__ lab, const uint32_t* __restrict__ slot_at,
@@ -859,7 +872,7 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
            float* __restrict__ stage, float* __restrict__ ovgw, int chains, int parts, int rows_per_part, size_t part_stride, size_t ov_stride,
            const uint32_t* __restrict__ gate, int accumulate, const uint32_t* __restrict__ stale) {
     constexpr int KT = Q == 4 ? KT_BOTH4 : KT_BOTH;   // (with four instances 36 slots spill)
-    constexpr uint32_t ZL = BothLayout<Q>::zero_label, U = 4 * Q;   // U: bytes of a unit
+    constexpr uint32_t ZL = BothLayout<Q, OWN>::zero_label, U = 4 * Q;   // U: bytes of a unit
     extern __shared__ __align__(16) unsigned char lds_raw[];
     if (gate && *gate == 0) return;   // the kernels over the nonzero gradients do this call's work
     const int nfb = cut.nfb;
@@ -891,7 +904,7 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
     // With loads of 4 bytes and a wait for every eight places a window began in 44 us at m = 500k and ended in 10 (clock
     // counters), now 23 and 8; the step 33.3 -> 31.6 us at m = 1024, d = 64, k = 8, b = 16, 258 -> 251 at m = 200k, d = 8k,
     // k = 32, b = 64 (bfloat16), 2034 -> 1999 at m = 500k, d = 32k, k = 32, b = 256.
-    constexpr uint32_t CH = both_places<Q>();   // places LDS holds at a time
+    constexpr uint32_t CH = both_places<Q, OWN>();   // places LDS holds at a time
     float* perm = reinterpret_cast<float*>(lds_raw);
     const uint32_t e0 = ent_base[wg], n_ent = ent_base[wg + 1] - e0;
     const uint32_t ov0 = ov_base[wg], ov_n = ov_base[wg + 1] - ov0;
@@ -959,7 +972,7 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
         for (int t = 0; t < KT / 2; ++t) places[t] = (uint32_t)(2 * t * NT) + tid4 / 4 | ((uint32_t)((2 * t + 1) * NT) + tid4 / 4) << 16;
     };
     auto used = [&](int t) { return t / 4 * 4 < acap || t / 4 * 4 >= KT - bcap; };   // the same for the whole wavefront
-    constexpr uint32_t NOWHERE = no_place<Q>();
+    constexpr uint32_t NOWHERE = no_place<Q, OWN>();
     auto place_of = [&](const uint32_t (&places)[KT / 2], int t) { return min(t & 1 ? places[t / 2] >> 16 : places[t / 2] & 0xFFFFu, NOWHERE); };
     if (threadIdx.x == 0) perm[NOWHERE] = 0.f;
     if (!one_go) {
@@ -981,40 +994,38 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
         gw[t] = zero;
     }
     __syncthreads();   // LDS is free
-    const float* row = reinterpret_cast<const float*>(lds_raw);           // row[Q * label + q]: instance q of a pass
-    float* outbuf = reinterpret_cast<float*>(lds_raw + BothLayout<Q>::row_bytes);   // [Q][NF]
-    TS* xbuf = reinterpret_cast<TS*>(outbuf + (BothLayout<Q>::x_bytes ? Q * NF : 0));   // Q = 4: [NF][4]; Q = 2: [2][NF], in the place of the sums
-    uint32_t* feat_of = reinterpret_cast<uint32_t*>(reinterpret_cast<unsigned char*>(outbuf + Q * NF) + BothLayout<Q>::x_bytes);   // [NT]
-    uint2* ov_near = reinterpret_cast<uint2*>(feat_of + BothLayout<Q>::feat_words);   // [NEAR2] {address of the label in the row, weight}
-    uint32_t* ovr_a = reinterpret_cast<uint32_t*>(ov_near + NEAR2);       // [NT] start | n << 16
-    uint32_t* ovr_b = ovr_a + NT;
-    float* ov_sum = reinterpret_cast<float*>(ovr_b + NT);                 // [NEAR2]
+    const float* row = reinterpret_cast<const float*>(lds_raw);           // row[Q * unit + q]: instance q of a pass
+    float* outbuf = reinterpret_cast<float*>(lds_raw + BothLayout<Q, OWN>::row_bytes);   // [Q][NF]
+    TS* xbuf = reinterpret_cast<TS*>(outbuf + (OWN ? Q * NF : 0));   // Q = 4: [NF][4]; Q = 2: [2][NF]
+    uint32_t* feat_of = reinterpret_cast<uint32_t*>(reinterpret_cast<unsigned char*>(outbuf + Q * NF) + BothLayout<Q, OWN>::x_bytes);   // [NT]
+    uint2* ov_near = reinterpret_cast<uint2*>(feat_of + BothLayout<Q, OWN>::feat_words);   // [NEAR2] {address of the label in the row, weight}
+    uint32_t* ov_share = reinterpret_cast<uint32_t*>(ov_near + NEAR2);    // [NT] of the lane's two lists, in pairs of entries: start | n << 8, << 16
+    float* ov_sum = reinterpret_cast<float*>(ov_share + NT);              // [NEAR2]
     lane = threadIdx.x;
     asm volatile("" : "+v"(lane));
     const uint32_t feat2 = fa | fbb << 16;
     feat_of[lane] = feat2;
-    // Q = 4: where the features' activations are (a list of a feature that does not exist reads some place, and is empty)
-    if (Q == 4) feat_of[NT + lane] = cut.S == 1 ? feat2 : (feat2 & 0xFFFFu) % (uint32_t)d | (feat2 >> 16) % (uint32_t)d << 16;
+    // OWN: where the features' activations are (a list of a feature that does not exist reads some place, and is empty)
+    if (OWN) feat_of[NT + lane] = cut.S == 1 ? feat2 : (feat2 & 0xFFFFu) % (uint32_t)d | (feat2 >> 16) % (uint32_t)d << 16;
     if (lane < NEAR2) {
         ov_near[lane] = make_uint2(o.slot != PAD_SLOT ? (uint32_t)o.label * U : ZL * U, __float_as_uint(ov_weight));   // an empty place: the unit of zeros, no weight
         ov_sum[lane] = 0.f;
     }
-    ovr_a[lane] = ovra;
-    ovr_b[lane] = ovrb;
+    ov_share[lane] = (ovra & 0xFFFFu) / 2 | ovra >> 17 << 8 | (ovrb & 0xFFFFu) / 2 << 16 | ovrb >> 17 << 24;
     if (lane < 32 * Q) reinterpret_cast<uint32_t*>(lds_raw)[ZL * Q + lane] = 0u;   // what empty places read
     for (uint32_t q = NEAR2 + lane; q < ov_n; q += NT) ovgw[(size_t)ov0 + q] = 0.f;   // entry q is lane q % NT's
     const int nl = (int)max((int64_t)0, min((int64_t)cut.wl, m - (int64_t)w * cut.wl));   // labels of this window (the last one may be short)
-    const int nv = nl / 4;                                               // whole 16-byte pieces of a row slice
+    const int nv = nl / 4, quarter = cut.wl / 4;                         // whole 16-byte pieces of a row slice; see unit_of_label
     const int nf = min(cut.fpb, cut.vd - fb * cut.fpb);                            // features of this block that exist
     const int nx = cut.S > 1 ? d : nf;                                   // ... and activations
     const int lines = (nl * 4 + 127) / 128, per = (lines + nfb - 1) / nfb;   // 128-byte lines; this workgroup's share of the warm-up
     const int plines = w >= chains && cut.S == 1 ? (nf * 4 + 127) / 128 : 0;   // ... and of its earlier sums (per instance)
     const int xlines = ((Q == 4 ? Q : 1) * nx * (int)sizeof(TS) + 127) / 128;    // 128-byte lines of the block's activations (per row of x)
-    // the rest of a list (r = start | n << 16 in ov_near, n even), two entries in flight at a time
+    // the rest of a list (r = start | n << 8 in pairs of entries of ov_near), two entries in flight at a time
     auto more = [&](float (&acc)[Q], uint32_t r, const float (&xv)[Q]) {
         constexpr int AT_ONCE = Q == 2 ? 2 : 1;   // (four instances leave no registers for two)
 #pragma unroll 1
-        for (uint32_t q = r & 0xFFFFu, e = q + (r >> 16); q < e; q += AT_ONCE) {
+        for (uint32_t q = (r & 0xFFu) * 2, e = q + (r >> 8 & 0xFFu) * 2; q < e; q += AT_ONCE) {
             uint2 o[AT_ONCE];
             float u[AT_ONCE][Q], t[AT_ONCE];
 #pragma unroll
@@ -1054,7 +1065,8 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
             if (wv < have * PR && piece < nx * (int)sizeof(TS))
                 __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(reinterpret_cast<const char*>(xrow + (size_t)(wv / PR) * x_stride) + piece),
                                                  (__attribute__((address_space(3))) void*)(reinterpret_cast<unsigned char*>(outbuf) + (size_t)(wv / PR) * NF * sizeof(TS) + (size_t)(wv % PR) * 1024), 16, 0, 0);
-        } else {
+        } else {   // ... of the four in one run, into a place of their own or that of the sums (there, too, a wavefront overwrites
+            // only what it alone read: kibibytes v and v + 16)
             const int bytes = nx * Q * (int)sizeof(TS);
             for (int v = (int)(tid >> 6) * 1024; v < bytes; v += NT * 16)
                 if (v + (int)(tid & 63u) * 16 < bytes)
@@ -1062,37 +1074,35 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
                                                      (__attribute__((address_space(3))) void*)(reinterpret_cast<unsigned char*>(xbuf) + v), 16, 0, 0);
         }
         {   // The slices of the instances side by side, through registers: 16 bytes of each, interleaved, Q writes of 16
-            // bytes.  As fast as LDS-DMA of the slices one after the other (37.6 against 38.2 bytes per clock), which
-            // cannot interleave them (by single words: 13.8), and for rows of any alignment.
+            // bytes.  (LDS-DMA cannot interleave them but by single words, 13.8 bytes per clock.  Loads of 4 bytes, a label
+            // per lane, held the memory pipe for as long as loads of 16.)  For rows of any alignment.
             const size_t rb = (size_t)m * 4;
-            if constexpr (Q == 2) {
-                const char* grow1 = grow + (have > 1 ? rb : 0);
+            const char* r[Q];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) r[q] = grow + (q < have ? q * rb : 0);
 #pragma unroll 1
-                for (uint32_t o = tid * 16u; o < (uint32_t)nv * 16u; o += NT * 16u) {
-                    const f32x4_any a = *reinterpret_cast<const f32x4_any*>(grow + o);
-                    f32x4_any c = *reinterpret_cast<const f32x4_any*>(grow1 + o);
-                    if (have < 2) c = (f32x4_any){0.f, 0.f, 0.f, 0.f};
+            for (uint32_t o = tid * 16u; o < (uint32_t)nv * 16u; o += NT * 16u) {
+                f32x4_any v[Q];
+#pragma unroll
+                for (int q = 0; q < Q; ++q) v[q] = *reinterpret_cast<const f32x4_any*>(r[q] + o);
+#pragma unroll
+                for (int q = 1; q < Q; ++q)
+                    if (have <= q) v[q] = (f32x4_any){0.f, 0.f, 0.f, 0.f};
+                if constexpr (Q == 2) {
                     float4* to = reinterpret_cast<float4*>(lds_raw + 2u * o);
-                    to[0] = make_float4(a.x, c.x, a.y, c.y);
-                    to[1] = make_float4(a.z, c.z, a.w, c.w);
-                }
-            } else {
-                // (a label per lane: its unit is one 16-byte write, next to its neighbours'; 16 bytes of a row per lane would
-                // put the writes of a pass 64 bytes apart, four to a bank)
-                const char *grow1 = grow + (have > 1 ? rb : 0), *grow2 = grow + (have > 2 ? 2 * rb : 0), *grow3 = grow + (have > 3 ? 3 * rb : 0);
-#pragma unroll 2
-                for (uint32_t o = tid * 4u; o < (uint32_t)nl * 4u; o += NT * 4u) {
-                    float4 v = make_float4(*reinterpret_cast<const float*>(grow + o), *reinterpret_cast<const float*>(grow1 + o),
-                                           *reinterpret_cast<const float*>(grow2 + o), *reinterpret_cast<const float*>(grow3 + o));
-                    if (have < 2) v.y = 0.f;
-                    if (have < 3) v.z = 0.f;
-                    if (have < 4) v.w = 0.f;
-                    *reinterpret_cast<float4*>(lds_raw + 4u * o) = v;
+                    to[0] = make_float4(v[0].x, v[1].x, v[0].y, v[1].y);
+                    to[1] = make_float4(v[0].z, v[1].z, v[0].w, v[1].w);
+                } else {
+                    float4* to = reinterpret_cast<float4*>(lds_raw + o);
+                    to[0] = make_float4(v[0].x, v[1].x, v[2].x, v[3].x);
+                    to[quarter] = make_float4(v[0].y, v[1].y, v[2].y, v[3].y);
+                    to[2 * quarter] = make_float4(v[0].z, v[1].z, v[2].z, v[3].z);
+                    to[3 * quarter] = make_float4(v[0].w, v[1].w, v[2].w, v[3].w);
                 }
             }
-            if (Q == 2 && (int)tid < (nl & 3) * Q) {   // the last labels of a slice that is no multiple of four
-                const int l = nv * 4 + (int)tid / Q, q = (int)tid % Q;
-                reinterpret_cast<float*>(lds_raw)[l * Q + q] = q < have ? *reinterpret_cast<const float*>(grow + (size_t)q * rb + (size_t)l * 4) : 0.f;
+            if ((int)tid < (nl & 3) * Q) {   // the last labels of a slice that is no multiple of four
+                const uint32_t l = (uint32_t)nv * 4 + tid / Q, q = tid % Q;
+                reinterpret_cast<float*>(lds_raw)[unit_of_label<Q>(l, (uint32_t)cut.wl) * Q + q] = (int)q < have ? *reinterpret_cast<const float*>(grow + (size_t)q * rb + (size_t)l * 4) : 0.f;
             }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             asm volatile("" : "+v"(token));
@@ -1135,41 +1145,43 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
             const int items = i + Q < i_end ? Q * per + XR * xlines + Q * plines : 0;
             if (__builtin_amdgcn_readfirstlane((int)tid) < items && (int)tid < items) line = item((int)tid);
             // (the last lines of more than NT, possible where one block is the whole layer, stay cold)
-        if (w >= chains) {
-            if (Q == 2 || cut.S == 1) {
+            if (w >= chains) {
+                if (Q == 2 || cut.S == 1) {
 #pragma unroll
-                for (int u = 0; u < Q / 2; ++u) {
-                    const int v = (int)tid + u * NT;
-                    if (v < have * (NF / 4) && v % (NF / 4) * 4 < nf)
-                        prior[u] = reinterpret_cast<const float4*>(dst + (size_t)(v / (NF / 4)) * dp)[v % (NF / 4)];
+                    for (int u = 0; u < Q / 2; ++u) {
+                        const int v = (int)tid + u * NT;
+                        if (v < have * (NF / 4) && v % (NF / 4) * 4 < nf)
+                            prior[u] = reinterpret_cast<const float4*>(dst + (size_t)(v / (NF / 4)) * dp)[v % (NF / 4)];
+                    }
+                } else if ((int)tid < d) {
+                    float* p = &prior[0].x;
+#pragma unroll
+                    for (int j = 0; j < Q; ++j)
+                        if (j < have) p[j] = dst[(size_t)j * dp + tid];
                 }
-            } else if ((int)tid < d) {
-                float* p = &prior[0].x;
-#pragma unroll
-                for (int j = 0; j < Q; ++j)
-                    if (j < have) p[j] = dst[(size_t)j * dp + tid];
             }
-        }
             token = *reinterpret_cast<const uint32_t*>(line);
         }
         float acc_a[Q] = {}, acc_b[Q] = {};
         int ac = acap, bc = bcap;   // compared afresh in every pass, see k_bwi_lds
         asm volatile("" : "+s"(ac), "+s"(bc));
-        if constexpr (Q == 4) unit_of(xbuf + (size_t)(feat_of[NT + tid] & 0xFFFFu) * 4, xa);
+        if constexpr (Q == 4) unit_of(xbuf + (size_t)(feat_of[(OWN ? NT : 0) + tid] & 0xFFFFu) * 4, xa);
 #pragma unroll
         for (int q = 0; q < KT / 4; ++q) {
             if (q * 4 < ac)
                 gather_group<Q>(acc_a, gw[q * 4], gw[q * 4 + 1], gw[q * 4 + 2], gw[q * 4 + 3], pk[q * 2], pk[q * 2 + 1],
                                 wt[q * 4], wt[q * 4 + 1], wt[q * 4 + 2], wt[q * 4 + 3], xa);
         }
-        if constexpr (Q == 4) {   // the first list's sums leave before the second list begins: their registers are needed
+        if constexpr (Q == 4) {   // OWN: the first list's sums leave before the second list begins
             tid = threadIdx.x;
             asm volatile("" : "+v"(tid));
-            if (ov_n) more(acc_a, ovr_a[tid], xa);
-            const uint32_t f = feat_of[tid] & 0xFFFFu;
+            if (ov_n) more(acc_a, ov_share[tid], xa);
+            if constexpr (OWN) {
+                const uint32_t f = feat_of[tid] & 0xFFFFu;
 #pragma unroll
-            for (int j = 0; j < Q; ++j) outbuf[j * NF + f] = acc_a[j];
-            unit_of(xbuf + (size_t)(feat_of[NT + tid] >> 16) * 4, xb);
+                for (int j = 0; j < Q; ++j) outbuf[j * NF + f] = acc_a[j];
+            }
+            unit_of(xbuf + (size_t)(feat_of[(OWN ? NT : 0) + tid] >> 16) * 4, xb);
         }
 #pragma unroll
         for (int q = 0; q < KT / 4; ++q) {
@@ -1181,8 +1193,8 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
         asm volatile("" : "+v"(tid));
         if constexpr (Q == 2) {
             if (ov_n) {   // the same for the whole workgroup: the few lanes whose lists did not fit go on through LDS
-                more(acc_a, ovr_a[tid], xa);
-                more(acc_b, ovr_b[tid], xb);
+                more(acc_a, ov_share[tid], xa);
+                more(acc_b, ov_share[tid] >> 16, xb);
             }
             __syncthreads();   // every lane has taken its activations from the place of the sums
             const uint32_t f = feat_of[tid];
@@ -1191,10 +1203,14 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
             outbuf[f >> 16] = acc_b[0];
             outbuf[NF + (f >> 16)] = acc_b[1];
         } else {
-            if (ov_n) more(acc_b, ovr_b[tid], xb);
-            const uint32_t f = feat_of[tid] >> 16;
+            if (ov_n) more(acc_b, ov_share[tid] >> 16, xb);
+            if constexpr (!OWN) __syncthreads();   // every lane has taken its activations from the place of the sums
+            const uint32_t f = feat_of[tid];
 #pragma unroll
-            for (int j = 0; j < Q; ++j) outbuf[j * NF + f] = acc_b[j];
+            for (int j = 0; j < Q; ++j) {
+                if (!OWN) outbuf[j * NF + (f & 0xFFFFu)] = acc_a[j];
+                outbuf[j * NF + (f >> 16)] = acc_b[j];
+            }
         }
         if (ov_n > (uint32_t)NEAR2) {   // only a skewed connectivity gets here: what LDS does not hold, by atomics
             __syncthreads();
@@ -1442,11 +1458,12 @@ static usl_status lf_build_t(usl_ctx* c, const int32_t* idx, int set, const Cut&
         }
         hipLaunchKernelGGL(k_lf_seg_place, sg, dim3(256), 0, c->stream, idx, c->m, c->k, cut, nseg, total, segcnt, L.pos, L.slot);
     }
-    const uint32_t zero_label = set == 0 ? ZERO_LABEL : Q == 4 ? BothLayout<4>::zero_label : BothLayout<2>::zero_label;
+    const bool own = set == 1 && both_own(Q, cut);
+    const uint32_t zero_label = set == 0 ? ZERO_LABEL : Q == 2 ? BothLayout<2, false>::zero_label : own ? BothLayout<4, true>::zero_label : BothLayout<4, false>::zero_label;
 #define USL_LF_SCHED(GS)                                                                                                    \
     hipLaunchKernelGGL((k_lf_schedule<KT, GS>), dim3((unsigned)(nwg * 64 / (SG_NT / 32))), dim3(SG_NT), 0, c->stream, L.ent, \
                        ent_base, L.where, L.count, L.feat, L.caps, ov_base, L.ovoff, c->k, cut, zero_label, rounds,          \
-                       L.lab, set == 1 ? nullptr : L.slot, reinterpret_cast<OvEntry*>(L.ov), set == 1 ? L.pos : nullptr, Q == 4 ? both_places<4>() : both_places<2>(),      \
+                       L.lab, set == 1 ? nullptr : L.slot, reinterpret_cast<OvEntry*>(L.ov), set == 1 ? L.pos : nullptr, Q == 2 ? both_places<2, false>() : own ? both_places<4, true>() : both_places<4, false>(),      \
                        set == 1 ? L.pos + rk_at(N) : nullptr, set == 1 ? L.pos + rk_at(N) + (size_t)nwg * KT * NT : nullptr)
     if (Q == 4) USL_LF_SCHED(16);
     else USL_LF_SCHED(32);
@@ -1563,25 +1580,26 @@ usl_status usl_both_lds_run(usl_ctx* c, const float* g, const void* x, const int
     USL_TRY(usl_activation_rows(c, x, b, Q == 4 ? 4 : 1, &xs, &x_stride));
     out->stale = usl_stale_word(c);
     const bool direct = chains == 1 && dp == c->d && (uintptr_t)grad_x % 16 == 0;   // nothing to add up
-    static bool checked[4] = {false, false, false, false};
+    static bool checked[6] = {false, false, false, false, false, false};
+    const bool own = both_own(Q, cut);
     for (int i0 = 0; i0 < b; i0 += G) {
         const int rows = b - i0 < G ? b - i0 : G;
         const int per_part = ((rows + parts - 1) / parts + Q - 1) / Q * Q;
         // whole windows to an XCD where that leaves no XCD more rounds (of 32 compute units) than even shares
         const int64_t even = ((int64_t)chains * parts * cut.nfb + 7) / 8, whole = ((int64_t)chains * parts + 7) / 8 * cut.nfb;
         const dim3 grid((unsigned)(8 * ((whole + 31) / 32 == (even + 31) / 32 ? whole : even)));
-#define USL_BOTH(TS, QQ, WHICH)                                                                                             \
+#define USL_BOTH(TS, QQ, OWN, WHICH)                                                                                             \
         do {                                                                                                                \
-            if (!checked[WHICH]) USL_TRY(lf_kernel_ready(c, k_both_lds<TS, QQ>, both_lds_bytes<QQ>()));                      \
+            if (!checked[WHICH]) USL_TRY(lf_kernel_ready(c, k_both_lds<TS, QQ, OWN>, both_lds_bytes<QQ, OWN>()));                      \
             checked[WHICH] = true;                                                                                          \
-            hipLaunchKernelGGL((k_both_lds<TS, QQ>), grid, dim3(NT), both_lds_bytes<QQ>(), c->stream, g + (size_t)i0 * c->m, \
+            hipLaunchKernelGGL((k_both_lds<TS, QQ, OWN>), grid, dim3(NT), (both_lds_bytes<QQ, OWN>()), c->stream, g + (size_t)i0 * c->m, \
                                (const TS*)W, (const TS*)xs + (size_t)(QQ == 4 ? i0 / 4 : i0) * x_stride, x_stride, c->m, c->k, rows, c->d, \
                                dp, cut, L.lab, L.slot, L.feat, L.caps, L.ov_base, reinterpret_cast<const OvEntry*>(L.ov), L.ovr, \
                                direct ? grad_x + (size_t)i0 * c->d : L.partial, L.pos + rk_at(N), L.pos + rk_at(N) + rkn, L.ov_base + 2 * ((size_t)cut.nwin * cut.nfb) + 1, L.stage, \
                                ovgw, chains, parts, per_part, N, N + nbins, gate, i0 > 0 ? 1 : 0, direct ? out->stale : nullptr);                                         \
         } while (0)
-        if (c->storage == USL_F32) { if (Q == 4) USL_BOTH(float, 4, 0); else USL_BOTH(float, 2, 1); }
-        else { if (Q == 4) USL_BOTH(uint16_t, 4, 2); else USL_BOTH(uint16_t, 2, 3); }
+        if (c->storage == USL_F32) { if (Q == 2) USL_BOTH(float, 2, false, 0); else if (own) USL_BOTH(float, 4, true, 1); else USL_BOTH(float, 4, false, 2); }
+        else { if (Q == 2) USL_BOTH(uint16_t, 2, false, 3); else if (own) USL_BOTH(uint16_t, 4, true, 4); else USL_BOTH(uint16_t, 4, false, 5); }
 #undef USL_BOTH
         if (!direct) lf_reduce(c, L.partial, chains, rows, true, grad_x + (size_t)i0 * c->d, gate);
     }

@@ -10,7 +10,8 @@ constexpr int WL = 32768;      // most labels a window has: one float32 row of 1
                                // size wl <= WL (a multiple of 4): no short last window whose workgroups idle
 constexpr int NF = 2048;       // features per workgroup (two per lane)
 constexpr int NT = 1024;
-constexpr int BOTH2_LABELS = 15968, BOTH4_LABELS = 4672;   // most labels of a window whose rows LDS holds two, four at a time
+// most labels of a window whose rows LDS holds two at a time; four; four, and the activations in a place of their own
+constexpr int BOTH2_LABELS = 15968, BOTH4_LABELS = 7232, BOTH4_OWN_LABELS = 4672;
 
 // A workgroup owns a window of wl labels and a block of NF features.  Where the layer is narrower
 // than a block, the window consists of S runs of `run` labels, and the features count S times over, once for every run
@@ -54,13 +55,17 @@ inline Cut bwi_cut(int64_t m, int d, int k, int num_cu) {
     return cut;
 }
 
-// Instances that a pass of the kernel for both products takes together: four where windows that send 11 connections into
+// Instances that a pass of the kernel for both products takes together: four where windows that send 15 connections into
 // a feature fit LDS four rows at a time, else two.  A pass is a chain of waits, so the fewer the better; with shorter lists
-// there are too many windows (backward, m = 100k, d = 20k, k = 48 (lists of 11.2), b = 64: 168 us with four, 184 with two;
-// m = 300k, d = 14k, k = 32 (10.7): 347 and 334; m = 670k, d = 16k, k = 32, b = 32 (9.1): 413 and 356).  Of 16 layers
-// measured (profiles/rules_measured.txt) it takes the faster in 11 and is within 4 % in three; where the other number leaves
-// a last round of workgroups nearly empty it can be wrong by more (m = 200k, d = 12k, k = 32: 252 us, 185 with two).
-inline int both_q(int d, int k) { return d <= NT || (int64_t)11 * d / k <= (int64_t)BOTH4_LABELS ? 4 : 2; }
+// there are too many windows.  usl_backward with four and two, float32 unless said: m = 200k, d = 12k, k = 32, b = 64 (d / k = 375):
+// 169 and 250 us; m = 300k, d = 14k, k = 32, b = 128 (438): 462 and 509; m = 400k, d = 15k, k = 32, b = 128, bfloat16 (469): 457 and
+// 522; m = 300k, d = 24k, k = 48, b = 100 (500): 545 and 486; m = 670k, d = 32k, k = 64, b = 256, bfloat16 (512): 2987 and 2670.
+// Where the other number leaves a last round of workgroups nearly empty it can be wrong (m = 130k, d = 15k, k = 32, b = 64
+// (480): 141 and 129; m = 1M, d = 17.6k, k = 32, b = 64 (550): 747 and 823).
+inline int both_q(int d, int k) { return d <= NT || (int64_t)15 * d / k <= (int64_t)BOTH4_LABELS ? 4 : 2; }
+// Do the activations of the block have a place of their own, beside that of the sums (a barrier less per pass)?  Where a row
+// leaves room for it, and where runs share activations (the places of the sums are then other ones).
+inline bool both_own(int Q, const Cut& cut) { return Q == 4 && (cut.wl <= BOTH4_OWN_LABELS || cut.S > 1); }
 
 // The form for both products: lists of 16 connections (half the registers go to the weight-gradient sums; with four
 // instances a lane has 32 slots instead of 36, hence 14), longer where the features do not fill the lanes twice over;
@@ -68,7 +73,7 @@ inline int both_q(int d, int k) { return d <= NT || (int64_t)11 * d / k <= (int6
 inline Cut both_cut(int64_t m, int d, int k, int num_cu) {
     Cut cut;
     const bool four = both_q(d, k) == 4;
-    const int labels = four ? BOTH4_LABELS : BOTH2_LABELS;
+    const int labels = !four ? BOTH2_LABELS : d <= NT ? BOTH4_OWN_LABELS : BOTH4_LABELS;
     cut.S = d <= NT ? NF / d : 1;
     if (cut.S > labels / 4) cut.S = labels / 4;   // a run has at least four labels, and the window has to fit LDS (d = 1)
     cut.vd = cut.S * d;
