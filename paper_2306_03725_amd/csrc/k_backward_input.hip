@@ -40,10 +40,20 @@ k_idx_fingerprint(const uint32_t* __restrict__ idx, size_t n_words, uint64_t* __
     usl_idx_fingerprint_block(idx, n_words, print, which, store);
 }
 
-// Lists are grouped by (label window, feature).  A workgroup takes one of `splits` equal shares of
-// a window's slots (contiguous in idx) and a chunk of up to 32768 features, and counts its share in
-// an LDS histogram; global memory sees one coalesced atomic per (workgroup, feature), not one per slot.
-constexpr int CSC_NT = 1024, CSC_CHUNK = 32768;
+// Lists are grouped by (label window, feature).  Three launches build them.  A workgroup of the first and the last has one of
+// `splits` equal shares of a window's slots (contiguous in idx) and a chunk of PER * 1024 features; it counts its share in LDS,
+// and later hands out the places in the lists from cursors in LDS: global memory sees no atomics.  In between, a workgroup
+// per (window, chunk) puts the chunk's features into the order of falling list length and turns the counts into cursors.  A
+// wavefront of the gather kernel walks 8 lists in lockstep and pays for the longest of them; with this order the 8 are of
+// (nearly) one length, and neighbours in the kernel are neighbours in memory.
+//   part[window * splits + share][feature]: count, then cursor.    total[window][chunk][share]: sum of the counts.
+// What bounds this is latency: PER = 1, hence d / 1024 workgroups per share, where with four times the features there would
+// not be one for every two compute units.  For 16 000 labels of 32 connections to 32 768 features it takes 29 us, where
+// chunks of 32 768 features, one workgroup that orders them all, scans in launches of their own and places reserved by atomics
+// took 147.
+// The order of a list's entries is not fixed; the sums that walk it do not fix theirs either.
+constexpr int CSC_NT = 1024;
+typedef int i32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
 __device__ __forceinline__ void csc_share(int64_t m, int k, int win_labels, int splits, size_t* e0, size_t* e1) {
     const int w = blockIdx.x / splits, s = blockIdx.x % splits;
@@ -54,145 +64,151 @@ __device__ __forceinline__ void csc_share(int64_t m, int k, int win_labels, int 
     *e1 = min(*e0 + per, w1);
 }
 
-__device__ __forceinline__ void csc_histogram(const int32_t* __restrict__ idx, size_t e0, size_t e1, int c0, int nc,
-                                              uint32_t* hist) {
-    for (int q = threadIdx.x; q < nc; q += CSC_NT) hist[q] = 0;
-    __syncthreads();
-    for (size_t e = e0 + threadIdx.x; e < e1; e += CSC_NT) {
-        const uint32_t c = (uint32_t)(idx[e] - c0);
-        if (c < (uint32_t)nc) atomicAdd(&hist[c], 1u);
-    }
-    __syncthreads();
-}
-
-// count (zeroed by the caller) += this workgroup's histogram
-__global__ void __launch_bounds__(CSC_NT)
-k_csc_count(const int32_t* __restrict__ idx, int64_t m, int k, int d, int win_labels, int splits,
-            uint32_t* __restrict__ count) {
-    extern __shared__ uint32_t hist[];
-    const int c0 = blockIdx.y * CSC_CHUNK, nc = min(CSC_CHUNK, d - c0);
-    size_t e0, e1;
-    csc_share(m, k, win_labels, splits, &e0, &e1);
-    csc_histogram(idx, e0, e1, c0, nc, hist);
-    uint32_t* dst = count + (size_t)(blockIdx.x / splits) * d + c0;
-    for (int q = threadIdx.x; q < nc; q += CSC_NT)
-        if (hist[q]) atomicAdd(&dst[q], hist[q]);
-}
-
-// Exclusive scan of count[n] into ptr[n+1] (and cursor[c] = ptr[c]) in three launches: per-chunk
-// sums, a one-block scan of those, and a per-chunk rescan with the chunk's offset.
-constexpr int SCAN_NT = 1024, SCAN_PER = 8, SCAN_CHUNK = SCAN_NT * SCAN_PER;
-
-__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* sh, uint32_t* total) {
-    // sh: SCAN_NT words.  Returns the sum of v over lower thread ids; *total = sum over the block.
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int o = 1; o < SCAN_NT; o <<= 1) {
-        const uint32_t t = threadIdx.x >= (unsigned)o ? sh[threadIdx.x - o] : 0u;
-        __syncthreads();
-        sh[threadIdx.x] += t;
-        __syncthreads();
-    }
-    *total = sh[SCAN_NT - 1];
-    return sh[threadIdx.x] - v;
-}
-
-__global__ void __launch_bounds__(SCAN_NT)
-k_scan_sums(const uint32_t* __restrict__ count, size_t n, uint32_t* __restrict__ sums) {
-    __shared__ uint32_t sh[SCAN_NT];
-    const size_t f0 = (size_t)blockIdx.x * SCAN_CHUNK + (size_t)threadIdx.x * SCAN_PER;
-    uint32_t s = 0;
-    for (int q = 0; q < SCAN_PER; ++q)
-        if (f0 + q < n) s += count[f0 + q];
-    uint32_t total;
-    block_exclusive_scan(s, sh, &total);
-    if (threadIdx.x == 0) sums[blockIdx.x] = total;
-}
-
-__global__ void __launch_bounds__(SCAN_NT)
-k_scan_top(uint32_t* __restrict__ sums, size_t nchunks, uint32_t* __restrict__ ptr_end) {
-    __shared__ uint32_t sh[SCAN_NT];
-    const size_t per = (nchunks + SCAN_NT - 1) / SCAN_NT;
-    const size_t a = min(nchunks, threadIdx.x * per), e = min(nchunks, a + per);
-    uint32_t s = 0;
-    for (size_t q = a; q < e; ++q) s += sums[q];
-    uint32_t total;
-    uint32_t run = block_exclusive_scan(s, sh, &total);
-    for (size_t q = a; q < e; ++q) { const uint32_t v = sums[q]; sums[q] = run; run += v; }
-    if (threadIdx.x == 0) *ptr_end = total;
-}
-
-__global__ void __launch_bounds__(SCAN_NT)
-k_scan_apply(uint32_t* __restrict__ cursor /* in: counts */, const uint32_t* __restrict__ sums,
-             size_t n, uint32_t* __restrict__ ptr) {
-    __shared__ uint32_t sh[SCAN_NT];
-    const size_t f0 = (size_t)blockIdx.x * SCAN_CHUNK + (size_t)threadIdx.x * SCAN_PER;
-    uint32_t v[SCAN_PER];
-    uint32_t s = 0;
+// use(entry, feature - c0) for the entries of the share whose feature is in the chunk: 16 bytes a load, four loads in flight
+template <typename F>
+__device__ __forceinline__ void csc_entries(const int32_t* __restrict__ idx, size_t e0, size_t e1, int c0, int nc, F use) {
+    const size_t n4 = (e1 - e0) / 4;
+    for (size_t q = threadIdx.x; q < n4; q += 4 * CSC_NT) {
+        i32x4_any v[4];
 #pragma unroll
-    for (int q = 0; q < SCAN_PER; ++q) { v[q] = f0 + q < n ? cursor[f0 + q] : 0u; s += v[q]; }
-    uint32_t total;
-    uint32_t run = sums[blockIdx.x] + block_exclusive_scan(s, sh, &total);
+        for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const i32x4_any*>(idx + e0 + min(q + u * CSC_NT, n4 - 1) * 4);
 #pragma unroll
-    for (int q = 0; q < SCAN_PER; ++q) {
-        if (f0 + q < n) { ptr[f0 + q] = run; cursor[f0 + q] = run; }
-        run += v[q];
-    }
-}
-
-// Same decomposition.  The workgroup counts its share again, reserves that many places in every
-// list with one atomic on `taken` (zeroed by the caller), and hands the places out from LDS cursors.
-// The order of a list's entries is therefore not fixed; the sums that walk it do not fix theirs either.
-__global__ void __launch_bounds__(CSC_NT)
-k_csc_fill(const int32_t* __restrict__ idx, int64_t m, int k, int d, int win_labels, int splits,
-           const uint32_t* __restrict__ ptr /* by rank */, const uint32_t* __restrict__ rank_of,
-           uint32_t* __restrict__ taken, uint32_t* __restrict__ slot) {
-    extern __shared__ uint32_t cur[];
-    const int c0 = blockIdx.y * CSC_CHUNK, nc = min(CSC_CHUNK, d - c0);
-    size_t e0, e1;
-    csc_share(m, k, win_labels, splits, &e0, &e1);
-    csc_histogram(idx, e0, e1, c0, nc, cur);
-    const size_t bin0 = (size_t)(blockIdx.x / splits) * d + c0;
-    for (int q = threadIdx.x; q < nc; q += CSC_NT) {
-        const uint32_t n = cur[q];
-        if (n) cur[q] = ptr[bin0 - c0 + rank_of[bin0 + q]] + atomicAdd(&taken[bin0 + q], n);
-    }
-    __syncthreads();
-    for (size_t e = e0 + threadIdx.x; e < e1; e += CSC_NT) {
-        const uint32_t c = (uint32_t)(idx[e] - c0);
-        if (c < (uint32_t)nc) {
-            const uint32_t pos = atomicAdd(&cur[c], 1u);
-            slot[pos] = (uint32_t)e;
+        for (int u = 0; u < 4; ++u) {
+            if (q + u * CSC_NT >= n4) continue;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t c = (uint32_t)(v[u][j] - c0);
+                if (c < (uint32_t)nc) use(e0 + (q + u * CSC_NT) * 4 + j, c);
+            }
         }
     }
+    const size_t e = e0 + n4 * 4 + threadIdx.x;
+    if (e < e1) {
+        const uint32_t c = (uint32_t)(idx[e] - c0);
+        if (c < (uint32_t)nc) use(e, c);
+    }
 }
 
-// Features of one window in the order of falling list length (one workgroup per window).  A wavefront
-// of the gather kernel walks 8 lists in lockstep and pays for the longest of them; with this order the 8
-// are of (nearly) one length.  The lists themselves are laid out in this order too, so neighbours in the
-// kernel are neighbours in memory.  order[rank] = feature, rank_of[feature] = rank, by_rank[rank] = its
-// list length.  Lists of 1023 entries or more share the first bucket.
-__global__ void __launch_bounds__(1024)
-k_csc_order(const uint32_t* __restrict__ count, int d, uint32_t* __restrict__ order,
-            uint32_t* __restrict__ rank_of, uint32_t* __restrict__ by_rank) {
-    __shared__ uint32_t start[1024];
-    const size_t w0 = (size_t)blockIdx.x * d;
-    start[threadIdx.x] = 0;
-    __syncthreads();
-    for (int c = threadIdx.x; c < d; c += 1024) atomicAdd(&start[min(count[w0 + c], 1023u)], 1u);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t run = 0;
-        for (int q = 1023; q >= 0; --q) { const uint32_t n = start[q]; start[q] = run; run += n; }
+// Sum of v over the lanes below; *total = over all.  sh: 16 words that no other use of them is still reading.
+__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* sh, uint32_t* total) {
+    uint32_t run = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t t = __shfl_up(run, o);
+        if ((int)(threadIdx.x & 63) >= o) run += t;
     }
+    if ((threadIdx.x & 63) == 63) sh[threadIdx.x >> 6] = run;
     __syncthreads();
-    for (int c = threadIdx.x; c < d; c += 1024) {
-        const uint32_t n = count[w0 + c];
-        const uint32_t r = atomicAdd(&start[min(n, 1023u)], 1u);
-        order[w0 + r] = (uint32_t)c;
-        rank_of[w0 + c] = r;
-        by_rank[w0 + r] = n;
+    uint32_t below = 0, all = 0;
+#pragma unroll
+    for (int q = 0; q < CSC_NT / 64; ++q) {
+        const uint32_t t = sh[q];
+        below += q < (int)(threadIdx.x >> 6) ? t : 0u;
+        all += t;
     }
+    *total = all;
+    return below + run - v;
+}
+
+template <int PER>
+__global__ void __launch_bounds__(CSC_NT)
+k_csc_count(const int32_t* __restrict__ idx, int64_t m, int k, int d, int win_labels, int splits,
+            uint32_t* __restrict__ part, uint32_t* __restrict__ total) {
+    __shared__ uint32_t hist[PER * CSC_NT], sh[CSC_NT / 64];
+    const int c0 = blockIdx.y * (PER * CSC_NT), nc = min(PER * CSC_NT, d - c0);
+    size_t e0, e1;
+    csc_share(m, k, win_labels, splits, &e0, &e1);
+#pragma unroll
+    for (int q = 0; q < PER; ++q) hist[q * CSC_NT + threadIdx.x] = 0;
+    __syncthreads();
+    uint32_t mine = 0, all;
+    csc_entries(idx, e0, e1, c0, nc, [&](size_t, uint32_t c) { atomicAdd(&hist[c], 1u); ++mine; });
+    block_exclusive_scan(mine, sh, &all);   // (its barrier stands behind the counts, too)
+    uint32_t* dst = part + (size_t)blockIdx.x * d + c0;
+    for (int q = threadIdx.x; q < nc; q += CSC_NT) dst[q] = hist[q];
+    if (threadIdx.x == 0) total[((size_t)(blockIdx.x / splits) * gridDim.y + blockIdx.y) * splits + blockIdx.x % splits] = all;
+}
+
+// order[rank] = feature, ptr[rank] = start of its list.  Lists of 1023 entries or more share the first bucket.
+template <int PER>
+__global__ void __launch_bounds__(CSC_NT)
+k_csc_order(uint32_t* __restrict__ part, const uint32_t* __restrict__ total, int d, int splits,
+            uint32_t* __restrict__ order, uint32_t* __restrict__ ptr) {
+    __shared__ uint32_t bucket[1024], sh[3][CSC_NT / 64], at[PER * CSC_NT];
+    const int c0 = blockIdx.y * (PER * CSC_NT), nc = min(PER * CSC_NT, d - c0), lane = threadIdx.x;
+    const size_t w0 = (size_t)blockIdx.x * d + c0, before = ((size_t)blockIdx.x * gridDim.y + blockIdx.y) * splits;
+    uint32_t sum = 0, base, all;
+    for (size_t q = lane; q < before; q += CSC_NT) sum += total[q];   // the lists of earlier windows and chunks
+    uint32_t* const mine = part + (size_t)blockIdx.x * splits * d + c0;
+    uint32_t n[PER] = {};
+    for (int s = 0; s < splits; ++s)
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            if (q * CSC_NT + lane < nc) n[q] += mine[(size_t)s * d + q * CSC_NT + lane];
+    bucket[lane] = 0;
+    block_exclusive_scan(sum, sh[0], &base);
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        if (q * CSC_NT + lane < nc) atomicAdd(&bucket[min(n[q], 1023u)], 1u);
+    __syncthreads();
+    bucket[1023 - lane] = block_exclusive_scan(bucket[1023 - lane], sh[1], &all);
+    __syncthreads();
+    uint32_t rank[PER] = {};
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        if (q * CSC_NT + lane < nc) {
+            rank[q] = atomicAdd(&bucket[min(n[q], 1023u)], 1u);
+            at[rank[q]] = n[q];
+            order[w0 + rank[q]] = (uint32_t)(c0 + q * CSC_NT + lane);
+        }
+    __syncthreads();
+    uint32_t len[PER], lens = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        len[q] = lane * PER + q < nc ? at[lane * PER + q] : 0u;
+        lens += len[q];
+    }
+    uint32_t run = base + block_exclusive_scan(lens, sh[2], &all);
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        if (lane * PER + q < nc) {
+            at[lane * PER + q] = run;
+            ptr[w0 + lane * PER + q] = run;
+        }
+        run += len[q];
+    }
+    if (blockIdx.x == gridDim.x - 1 && blockIdx.y == gridDim.y - 1 && lane == 0) ptr[w0 + nc] = base + all;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        if (q * CSC_NT + lane < nc) {
+            uint32_t cursor = at[rank[q]];
+            for (int s = 0; s < splits; ++s) {
+                uint32_t* p = &mine[(size_t)s * d + q * CSC_NT + lane];
+                const uint32_t t = *p;
+                *p = cursor;
+                cursor += t;
+            }
+        }
+}
+
+// Same decomposition as the counts, and one workgroup more that takes the fingerprint of idx.
+template <int PER>
+__global__ void __launch_bounds__(CSC_NT)
+k_csc_fill(const int32_t* __restrict__ idx, int64_t m, int k, int d, int win_labels, int splits,
+           const uint32_t* __restrict__ part, uint32_t* __restrict__ slot, uint64_t* __restrict__ print) {
+    __shared__ uint32_t cur[PER * CSC_NT];
+    if (blockIdx.x == gridDim.x - 1) {
+        if (blockIdx.y == 0) usl_idx_fingerprint_block(reinterpret_cast<const uint32_t*>(idx), (size_t)m * k, print, USL_PRINT_COLUMNS, 1);
+        return;
+    }
+    const int c0 = blockIdx.y * (PER * CSC_NT), nc = min(PER * CSC_NT, d - c0);
+    size_t e0, e1;
+    csc_share(m, k, win_labels, splits, &e0, &e1);
+    const uint32_t* src = part + (size_t)blockIdx.x * d + c0;
+    for (int q = threadIdx.x; q < nc; q += CSC_NT) cur[q] = src[q];
+    __syncthreads();
+    csc_entries(idx, e0, e1, c0, nc, [&](size_t e, uint32_t c) { slot[atomicAdd(&cur[c], 1u)] = (uint32_t)e; });
 }
 
 // Weights in list order, as float32 (refreshed on every call: W changes with every Adam step).  The lists of
@@ -440,17 +456,36 @@ int window_labels(const usl_ctx* c) {
     return win;
 }
 
+template <int PER>
+void launch_csc(usl_ctx* c, const int32_t* idx, size_t nwin, int splits, uint32_t* total) {
+    const unsigned chunks = (unsigned)(((size_t)c->d + PER * CSC_NT - 1) / (PER * CSC_NT));
+    hipLaunchKernelGGL((k_csc_count<PER>), dim3((unsigned)(nwin * splits), chunks), dim3(CSC_NT), 0, c->stream, idx, c->m, c->k, c->d,
+                       c->csc_win_labels, splits, c->csc_cursor, total);
+    hipLaunchKernelGGL((k_csc_order<PER>), dim3((unsigned)nwin, chunks), dim3(CSC_NT), 0, c->stream, c->csc_cursor, total, c->d, splits,
+                       c->csc_order, c->csc_ptr);
+    hipLaunchKernelGGL((k_csc_fill<PER>), dim3((unsigned)(nwin * splits) + 1, chunks), dim3(CSC_NT), 0, c->stream, idx, c->m, c->k, c->d,
+                       c->csc_win_labels, splits, c->csc_cursor, c->csc_slot, c->idx_print);
+}
+
 usl_status build_csc(usl_ctx* c, const int32_t* idx) {
     const size_t N = (size_t)c->m * c->k;
     const int wl = window_labels(c);
     const size_t nwin = ((size_t)c->m + wl - 1) / wl;
     const size_t nbins = nwin * (size_t)c->d;
     if (nbins + 1 > (size_t)0xFFFFFFF0u) USL_FAIL(c, USL_ESHAPE, "too many (window, feature) lists");
+    const size_t cu = (size_t)c->num_cu, wide = ((size_t)c->d + 4 * CSC_NT - 1) / (4 * CSC_NT);
+    const bool narrow = 2 * nwin * wide < cu;
+    const size_t chunks = narrow ? ((size_t)c->d + CSC_NT - 1) / CSC_NT : wide;
+    // a workgroup fills half a compute unit (1024 lanes): as many shares as give one workgroup to each, of 4096 slots or more
+    const size_t share = ((size_t)wl < (size_t)c->m ? (size_t)wl : (size_t)c->m) * c->k / 4096;
+    size_t splits = cu / (nwin * chunks);
+    splits = splits < share ? splits : share;
+    splits = splits < 1 ? 1 : splits > 16 ? 16 : splits;
     if (!c->csc_ptr || c->csc_win_labels != wl) {
         size_t cap = c->csc_ptr_cap;
         USL_TRY(usl_reserve(c, (void**)&c->csc_ptr, &cap, (nbins + 1) * 4));
         c->csc_ptr_cap = cap; cap = c->csc_cursor_cap;
-        USL_TRY(usl_reserve(c, (void**)&c->csc_cursor, &cap, nbins * 4));
+        USL_TRY(usl_reserve(c, (void**)&c->csc_cursor, &cap, (nbins + nwin * chunks) * splits * 4));
         c->csc_cursor_cap = cap;
         if (!c->csc_slot) {
             cap = 0; USL_TRY(usl_reserve(c, (void**)&c->csc_slot, &cap, N * 4));
@@ -458,40 +493,11 @@ usl_status build_csc(usl_ctx* c, const int32_t* idx) {
         }
         c->csc_win_labels = wl;
     }
-    const unsigned cchunks = (unsigned)((c->d + CSC_CHUNK - 1) / CSC_CHUNK);
-    // a workgroup fills a compute unit (1024 lanes, up to 128 KiB of LDS): as many shares as give one full round
-    int splits = (int)((size_t)c->num_cu / (nwin * cchunks));
-    splits = splits < 1 ? 1 : splits > 16 ? 16 : splits;
-    const dim3 cgrid((unsigned)(nwin * splits), cchunks);
-    const size_t clds = (size_t)(c->d < CSC_CHUNK ? c->d : CSC_CHUNK) * 4;
-    USL_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(k_csc_count),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)clds));
-    USL_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(k_csc_fill),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)clds));
-    hipLaunchKernelGGL(k_zero_u32, dim3(c->num_cu), dim3(256), 0, c->stream, c->csc_cursor, nbins);
-    hipLaunchKernelGGL(k_csc_count, cgrid, dim3(CSC_NT), clds, c->stream, idx, c->m, c->k, c->d, wl,
-                       splits, c->csc_cursor);
-    const size_t nchunks = (nbins + SCAN_CHUNK - 1) / SCAN_CHUNK;
-    {
-        size_t cap = c->tie_counts_cap;  // the redistribution's block-count buffer doubles as scan scratch
-        USL_TRY(usl_reserve(c, (void**)&c->tie_counts, &cap, nchunks * 4));
-        c->tie_counts_cap = cap;
-    }
-    USL_TRY(usl_reserve(c, (void**)&c->csc_order, &c->csc_order_cap, 3 * nbins * 4));
-    uint32_t* rank_of = c->csc_order + nbins;
-    uint32_t* by_rank = c->csc_order + 2 * nbins;
-    hipLaunchKernelGGL(k_csc_order, dim3((unsigned)nwin), dim3(1024), 0, c->stream, c->csc_cursor, c->d,
-                       c->csc_order, rank_of, by_rank);
-    hipLaunchKernelGGL(k_scan_sums, dim3((unsigned)nchunks), dim3(SCAN_NT), 0, c->stream, by_rank,
-                       nbins, c->tie_counts);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(SCAN_NT), 0, c->stream, c->tie_counts, nchunks,
-                       c->csc_ptr + nbins);
-    hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nchunks), dim3(SCAN_NT), 0, c->stream, by_rank,
-                       c->tie_counts, nbins, c->csc_ptr);
-    hipLaunchKernelGGL(k_zero_u32, dim3(c->num_cu), dim3(256), 0, c->stream, c->csc_cursor, nbins);
-    hipLaunchKernelGGL(k_csc_fill, cgrid, dim3(CSC_NT), clds, c->stream, idx, c->m, c->k, c->d, wl,
-                       splits, c->csc_ptr, rank_of, c->csc_cursor, c->csc_slot);
-    USL_TRY(usl_idx_fingerprint(c, idx, USL_PRINT_COLUMNS, 1));
+    USL_TRY(usl_reserve(c, (void**)&c->csc_order, &c->csc_order_cap, nbins * 4));
+    USL_TRY(usl_idx_print_ready(c));
+    uint32_t* total = c->csc_cursor + nbins * splits;
+    if (narrow) launch_csc<1>(c, idx, nwin, (int)splits, total);
+    else launch_csc<4>(c, idx, nwin, (int)splits, total);
     USL_TRY(usl_check_launch(c, "column lists"));
     c->csc_built_for = idx;
     return USL_OK;
