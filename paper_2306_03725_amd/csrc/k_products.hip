@@ -504,7 +504,14 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
                 best_t = t;
                 best.kern = kern;
                 tg.groups_per_block = gpb;
-                tg.share = res * (cus / 8 > 0 ? cus / 8 : 1);
+                // Workgroups go round-robin to the 8 XCDs.  With the blocks of labels first, an XCD reads an eighth of the
+                // labels' rows and all of x; with the parts of the batch first (a multiple of 8 of them) the other way round.
+                // m = 16k, d = 32k, k = 32, b = 256 (x 33 MB, labels 4): forward 52 and 49 us, weight gradient 73 and 60; m = 4k,
+                // d = 65k: 76 and 31, 94 and 51; m = 30k, d = 16k, b = 128 (8.4 and 7.7): 43 and 47, 52 and 51.
+                tg.parts_first = parts % 8 == 0 && nblk <= 65535 &&
+                                 (int64_t)groups * L.row_bytes > 2 * c->m * c->k * (backward ? 4 : 4 + es);
+                const int64_t same = tg.parts_first ? nblk : nblk / 8, resident = (int64_t)res * (cus / 8 > 0 ? cus / 8 : 1);
+                tg.share = (int)(same < 1 ? 1 : same < resident ? same : resident);
                 best.geom = tg;
                 best.nblk = nblk;
                 best.G = (int)parts;
@@ -518,7 +525,8 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
 usl_status launch(usl_ctx* c, const Launch& p, void** args, const char* what) {
     if (p.lds > 65536)
         USL_HIP(c, hipFuncSetAttribute(p.kern.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds));
-    USL_HIP(c, hipLaunchKernel(p.kern.fn, dim3((unsigned)p.nblk, (unsigned)p.G), dim3((unsigned)p.kern.NT), args, p.lds, c->stream));
+    const dim3 grid = p.geom.parts_first ? dim3((unsigned)p.G, (unsigned)p.nblk) : dim3((unsigned)p.nblk, (unsigned)p.G);
+    USL_HIP(c, hipLaunchKernel(p.kern.fn, grid, dim3((unsigned)p.kern.NT), args, p.lds, c->stream));
     return usl_check_launch(c, what);
 }
 

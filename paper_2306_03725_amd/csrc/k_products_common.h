@@ -28,9 +28,10 @@ struct Geom {
     int nbuf;              // 2: the next tile is copied in while this one is gathered
     int buf_bytes;         // LDS bytes from one buffer to the next
     int groups;            // instance groups of the batch
-    int groups_per_block;  // ... that one blockIdx.y walks
-    int share;             // workgroups resident together on one XCD: they split the warm-up of the next row
+    int groups_per_block;  // ... that one workgroup walks
+    int share;             // workgroups resident together on one XCD that walk the same rows: they split the warm-up of the next row
     int zero_col;          // column that padding slots read (a unit of zeros)
+    int parts_first;       // blockIdx.x is the part of the batch and blockIdx.y the block of labels, not the other way round
     int dummy;             // 256 bytes of LDS that the warm-up loads are thrown into
 };
 
@@ -65,13 +66,13 @@ __device__ __forceinline__ void touch_lines(const char* __restrict__ row, int fi
 
 // Warms the L2 of this workgroup's XCD with a share of the next tile.  All workgroups walk the batch in step, so without
 // this every row is first touched by all of them at once and the whole chip waits out an HBM round trip per row.
-// Workgroups are dealt to the 8 XCDs round robin; those of one XCD that are resident together (consecutive in
-// blockIdx.x) split the row between them, one load per 128-byte line.
+// Workgroups are dealt to the 8 XCDs round robin; those of one XCD that walk the same rows and are resident together
+// split the row between them, one load per 128-byte line.
 struct WarmShare {
     int slice, slices;
-    __device__ __forceinline__ explicit WarmShare(int share) {
-        slices = max(1, min((int)(gridDim.x >> 3), share));
-        slice = (int)(blockIdx.x >> 3) % slices;
+    __device__ __forceinline__ explicit WarmShare(const Geom& tg) {
+        slices = tg.share;
+        slice = (int)(tg.parts_first ? blockIdx.y : blockIdx.x >> 3) % slices;
     }
     // first and number of this workgroup's lines of a tile of nbytes
     __device__ __forceinline__ int per(int nbytes) const { return ((nbytes + 127) / 128 + slices - 1) / slices; }
@@ -581,14 +582,14 @@ __device__ __forceinline__ void label_outer(const uint32_t (&pk)[K / 2], const f
 }
 
 // --------------------------------------------------------------------------------------------- the walk over the batch
-// Calls body(group, first LDS byte of its row, part) for every instance group of this blockIdx.y, with the rows staged
+// Calls body(group, first LDS byte of its row, part) for every instance group of this part of the batch, with the rows staged
 // tile by tile; late(first group of the tile, groups in it, lane) right after a tile has arrived, early(first group,
 // groups) right before the wait for it: what is loaded there can be waited for at no cost.
 // MULTI = false: one row fills the buffer (tiles of one row, one buffer); HALVES: part 0 / 1 of every row.
 template <int NT, bool MULTI, bool HALVES, typename BODY, typename LATE, typename EARLY>
 __device__ __forceinline__ void walk(const char* __restrict__ xi, uint32_t lds0, const Geom& tg, int g0, int g1, BODY body, LATE late, EARLY early) {
     const uint32_t dummy = lds0 + (uint32_t)tg.dummy;
-    const WarmShare ws(tg.share);
+    const WarmShare ws(tg);
     if (!MULTI) {
         const int per = ws.per(tg.row_bytes);
         constexpr int HB = HALF_COLS * 4;
@@ -652,7 +653,7 @@ __device__ __forceinline__ uint32_t lds_base(const void* p) {
 }
 
 // ------------------------------------------------------------------------------------------------ forward
-// out[i][j] = sum_t W[j][t] x[i][idx[j][t]].  grid (label blocks, groups of the batch).
+// out[i][j] = sum_t W[j][t] x[i][idx[j][t]].  grid (label blocks, parts of the batch), or the other way round.
 // With a loss (training): out receives the gradient of the loss by the score, for a target of 0 (k_loss_positives writes that
 // of the few others), and the workgroup's part of the loss, targets left out, goes to partials[block].  The scores then
 // never go to memory: the separate pass over them took 24 us at m = 200k, b = 64 and 170 us at m = 500k, b = 256.
@@ -671,9 +672,10 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
           int64_t m, int k, int b, Geom tg, const uint8_t* __restrict__ perm, LossArgs loss) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const uint32_t lds0 = lds_base(lds_raw);
-    const int64_t j0 = (int64_t)blockIdx.x * (NT * LPT);
+    const uint32_t part = tg.parts_first ? blockIdx.x : blockIdx.y;
+    const int64_t j0 = (int64_t)(tg.parts_first ? blockIdx.y : blockIdx.x) * (NT * LPT);
     if (LOSS)   // the first words of target bits come to the L2 while the labels' rows are brought in (1 % of the step at m = 500k, b = 256)
-        touch_lines<NT>(reinterpret_cast<const char*>(loss.targets + (size_t)((int)blockIdx.y * tg.groups_per_block * Q >> 5) * m + j0), 0,
+        touch_lines<NT>(reinterpret_cast<const char*>(loss.targets + (size_t)((int)part * tg.groups_per_block * Q >> 5) * m + j0), 0,
                         ((int)min((int64_t)NT * LPT, m - j0) * 4 + 127) / 128, lds0 + (uint32_t)tg.dummy, (int)threadIdx.x);
     uint32_t pk[LPT][K / 2];
     WReg<TS, K> w[LPT];
@@ -699,7 +701,7 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
         __syncthreads();
         if (threadIdx.x < 4) reinterpret_cast<uint32_t*>(lds_raw)[HALF_COLS + threadIdx.x] = 0u;
     }
-    const int g0 = blockIdx.y * tg.groups_per_block, g1 = min(tg.groups, g0 + tg.groups_per_block);
+    const int g0 = (int)part * tg.groups_per_block, g1 = min(tg.groups, g0 + tg.groups_per_block);
     const int nlab = (int)min((int64_t)NT * LPT, m - j0);
     // Q <= 2: the scores of a group are written while the next group is gathered, before the last label's gathers (a store
     // right before the next copy would make that copy's wait include it; four stores in a row would hold the wavefront
@@ -810,7 +812,7 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
 }
 
 // ------------------------------------------------------------------------------------------------ weight gradient
-// grad_W[j][t] = sum_i g[i][j] x[i][idx[j][t]].  With the batch split over blockIdx.y every part of it leaves a partial
+// grad_W[j][t] = sum_i g[i][j] x[i][idx[j][t]].  With the batch split every part of it leaves a partial
 // gradient (part_stride elements apart) that a later kernel adds up in a fixed order.  A label whose gradients of a
 // group are zero in all 64 lanes skips its gathers (Algorithm 3 skips zero entries).
 template <int K, int LPT, int NT, typename TS, int Q, bool HALVES>
@@ -820,7 +822,8 @@ k_backward_weight(const float* __restrict__ g, const char* __restrict__ xi, cons
     extern __shared__ __align__(16) unsigned char lds_raw[];
     if (gate && *gate == 0) return;   // the gradient is almost all zeros: the kernels over its nonzeros do the work
     const uint32_t lds0 = lds_base(lds_raw);
-    const int64_t j0 = (int64_t)blockIdx.x * (NT * LPT);
+    const uint32_t part = tg.parts_first ? blockIdx.x : blockIdx.y;
+    const int64_t j0 = (int64_t)(tg.parts_first ? blockIdx.y : blockIdx.x) * (NT * LPT);
     uint32_t pk[LPT][K / 2];
     float acc[LPT][K];
 #pragma unroll
@@ -843,7 +846,7 @@ k_backward_weight(const float* __restrict__ g, const char* __restrict__ xi, cons
         __syncthreads();
         if (threadIdx.x < 4) reinterpret_cast<uint32_t*>(lds_raw)[HALF_COLS + threadIdx.x] = 0u;
     }
-    const int g0 = blockIdx.y * tg.groups_per_block, g1 = min(tg.groups, g0 + tg.groups_per_block);
+    const int g0 = (int)part * tg.groups_per_block, g1 = min(tg.groups, g0 + tg.groups_per_block);
     const int nlab = (int)min((int64_t)NT * LPT, m - j0);
     // The gradients of the next group come from HBM and are requested one group ahead, right after this group's row
     // copy: before it, the copy's wait would wait for them too.  (Q = 4 on wide blocks has no registers for that: their
@@ -900,7 +903,7 @@ k_backward_weight(const float* __restrict__ g, const char* __restrict__ xi, cons
         const int64_t row0 = j0 + (int64_t)l * NT;
         SlotOrder<K> so;
         so.load(perm, row0 + threadIdx.x, row0 + threadIdx.x < m);
-        store_rows<K, NT>(acc[l], grad_W + (size_t)blockIdx.y * part_stride, row0, m, k, reinterpret_cast<uint32_t*>(lds_raw), so);
+        store_rows<K, NT>(acc[l], grad_W + (size_t)part * part_stride, row0, m, k, reinterpret_cast<uint32_t*>(lds_raw), so);
     }
 }
 

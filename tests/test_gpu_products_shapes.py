@@ -52,3 +52,13 @@ def test_products_at_their_edges_in_bank_order(orc, m, d, k, b, storage, monkeyp
     """Layers this small keep their slots in stored order by themselves; the bank-aware order has to be right for them too."""
     monkeypatch.setenv("USL_TUNE_ROUNDS", "3")
     test_products_at_their_edges(orc, m, d, k, b, storage)
+
+
+@pytest.mark.parametrize("m,d,k,b,storage,split", [(700, 9000, 5, 93, "f32", 8), (1, 2000, 8, 61, "bf16", 8), (2100, 40000, 9, 31, "f32", 16),
+                                                   (600, 65536, 6, 8, "f32", 8), (4100, 65536, 8, 95, "bf16", 24)])
+def test_products_with_the_parts_of_the_batch_first(orc, m, d, k, b, storage, split, monkeypatch):
+    """A multiple of 8 parts, and far more activations than connections: the grid's first dimension is the part."""
+    import gpu_util as gu
+    monkeypatch.setenv("USL_TUNE_SPLIT", str(split))
+    print("products", m, d, k, b, storage, split, flush=True)
+    compare(orc, gu, wl.custom(m, d, k, b, storage=storage, positives=1, index=810 + split), m, d, k, b, storage)
