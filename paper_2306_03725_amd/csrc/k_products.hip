@@ -429,8 +429,10 @@ ProductKernel kernel_for(const usl_ctx* c, const Layout& L, ProductKind kind, in
 struct Launch {
     ProductKernel kern;
     Geom geom;
+    Tail tail;
     int64_t nblk;
-    int G;              // parts of the batch (blockIdx.y)
+    int G;              // parts of the batch
+    int64_t extra;      // workgroups beyond nblk, of a tail that takes the batch in parts of its own
     size_t lds;
 };
 
@@ -478,14 +480,8 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
         const int by_regs = (512 / regs > 8 ? 8 : 512 / regs) * 4 / (kern.NT / 64);
         if (res > by_regs) res = by_regs;
         if (res < 1) res = 1;
-        for (int G = 1; G <= groups; G = G < 8 ? G + 1 : G + (G + 3) / 4) {
-            if (split_force > 0 && G > 1) break;
-            const int split = split_force > 0 ? split_force : G, gpb = (groups + split - 1) / split;
-            const int64_t parts = (groups + gpb - 1) / gpb;   // those that have work
-            if (parts > most_parts && parts > 1) break;
-            if (backward && parts > 1 && (size_t)parts * c->m * c->k * 4 > ((size_t)1 << 29)) break;
-            const int64_t wgs = nblk * parts;
-            if (kind == FORWARD_LOSS && parts > 1 && (size_t)wgs > usl_forward_blocks(c) && split_force <= 0) break;
+        // clocks of wgs workgroups with gpb groups each
+        auto clocks = [&](int64_t wgs, int gpb) {
             const double most = (double)((wgs + cus - 1) / cus);      // workgroups the busiest compute unit runs
             const double per_cu = wgs > cus ? 0.75 * most + 0.25 * wgs / cus : most;
             const double rounds = (double)((wgs + (int64_t)cus * res - 1) / ((int64_t)cus * res));
@@ -498,20 +494,50 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
             const double latency = (double)gpb * kern.LPT * kern.K * (L.halves ? 2 : 1) / (unit == 16 ? 4 : 8) * 200.0;
             double busy = per_cu * (more + (tg.nbuf == 2 || together > 1.5 ? 0.5 : 1.0) * less);
             if (busy < rounds * latency) busy = rounds * latency;
-            double t = busy + per_cu * load + rounds * (6000.0 + tiles * (tg.nbuf == 2 ? 600.0 : 1500.0) / (together > 1.0 ? together : 1.0));
+            return busy + per_cu * load + rounds * (6000.0 + tiles * (tg.nbuf == 2 ? 600.0 : 1500.0) / (together > 1.0 ? together : 1.0));
+        };
+        const int64_t resident = (int64_t)res * (cus / 8 > 0 ? cus / 8 : 1);   // workgroups on an XCD; they go round-robin to the 8
+        auto shared_by = [&](int64_t same) { return (int)(same < 1 ? 1 : same < resident ? same : resident); };
+        for (int G = 1; G <= groups; G = G < 8 ? G + 1 : G + (G + 3) / 4) {
+            if (split_force > 0 && G > 1) break;
+            const int split = split_force > 0 ? split_force : G, gpb = (groups + split - 1) / split;
+            const int64_t parts = (groups + gpb - 1) / gpb;   // those that have work
+            if (parts > most_parts && parts > 1) break;
+            if (backward && parts > 1 && (size_t)parts * c->m * c->k * 4 > ((size_t)1 << 29)) break;
+            const int64_t wgs = nblk * parts;
+            if (kind == FORWARD_LOSS && parts > 1 && (size_t)wgs > usl_forward_blocks(c) && split_force <= 0) break;
+            double t = clocks(wgs, gpb);
             if (backward && parts > 1) t += 6000.0 + (double)(parts + 1) * c->m * c->k * 4 / 4000.0;
+            // A last round of workgroups that leaves most of the chip idle: its blocks take the batch in parts, so that there are
+            // more and shorter workgroups of them (the scores need no adding up).  m = 670k, d = 16k, k = 32, b = 32 (328 blocks
+            // of 2048 labels, 72 in three parts): 187 and 162 us; m = 600k, d = 20k, k = 32, b = 128: 452 and 330; m = 670k, d = 32k,
+            // k = 64, b = 256, bfloat16: 1450 and 1305.
+            const int64_t slots = (int64_t)cus * res, tail = parts == 1 && !backward && nblk > slots ? nblk % slots : 0;
+            int tail_gpb = 0;
+            for (int T = 2; tail > 0 && T <= groups && T <= 16; ++T) {
+                const int per = (groups + T - 1) / T;
+                const int64_t items = tail * ((groups + per - 1) / per);
+                if (kind == FORWARD_LOSS && (size_t)(nblk - tail + items) > usl_forward_blocks(c)) break;
+                const double with = clocks(nblk - tail, gpb) + clocks(items, per);
+                if (with < t) { t = with; tail_gpb = per; }
+            }
             if (!best.kern.fn || t < best_t) {
                 best_t = t;
                 best.kern = kern;
                 tg.groups_per_block = gpb;
-                // Workgroups go round-robin to the 8 XCDs.  With the blocks of labels first, an XCD reads an eighth of the
-                // labels' rows and all of x; with the parts of the batch first (a multiple of 8 of them) the other way round.
+                // With the blocks of labels first, an XCD reads an eighth of the labels' rows and all of x; with the parts of the
+                // batch first (a multiple of 8 of them) the other way round.
                 // m = 16k, d = 32k, k = 32, b = 256 (x 33 MB, labels 4): forward 52 and 49 us, weight gradient 73 and 60; m = 4k,
                 // d = 65k: 76 and 31, 94 and 51; m = 30k, d = 16k, b = 128 (8.4 and 7.7): 43 and 47, 52 and 51.
                 tg.parts_first = parts % 8 == 0 && nblk <= 65535 &&
                                  (int64_t)groups * L.row_bytes > 2 * c->m * c->k * (backward ? 4 : 4 + es);
-                const int64_t same = tg.parts_first ? nblk : nblk / 8, resident = (int64_t)res * (cus / 8 > 0 ? cus / 8 : 1);
-                tg.share = (int)(same < 1 ? 1 : same < resident ? same : resident);
+                tg.share = shared_by(tg.parts_first ? nblk : nblk / 8);
+                best.tail = Tail{0x7FFFFFFF, 1, 1, 1};
+                best.extra = 0;
+                if (tail_gpb) {
+                    best.tail = Tail{(int)(nblk - tail), (int)tail, tail_gpb, shared_by(tail / 8)};
+                    best.extra = tail * ((groups + tail_gpb - 1) / tail_gpb) - tail;
+                }
                 best.geom = tg;
                 best.nblk = nblk;
                 best.G = (int)parts;
@@ -525,7 +551,7 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
 usl_status launch(usl_ctx* c, const Launch& p, void** args, const char* what) {
     if (p.lds > 65536)
         USL_HIP(c, hipFuncSetAttribute(p.kern.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds));
-    const dim3 grid = p.geom.parts_first ? dim3((unsigned)p.G, (unsigned)p.nblk) : dim3((unsigned)p.nblk, (unsigned)p.G);
+    const dim3 grid = p.geom.parts_first ? dim3((unsigned)p.G, (unsigned)p.nblk) : dim3((unsigned)(p.nblk + p.extra), (unsigned)p.G);
     USL_HIP(c, hipLaunchKernel(p.kern.fn, grid, dim3((unsigned)p.kern.NT), args, p.lds, c->stream));
     return usl_check_launch(c, what);
 }
@@ -743,12 +769,13 @@ usl_status run_forward(usl_ctx* c, const Layout& L, const void* x, const int32_t
     int k = c->k, bb = b;
     Geom tg = p.geom;
     if (loss.kind >= 0) {
-        *blocks = (size_t)p.nblk * (size_t)p.G;
+        *blocks = (size_t)p.nblk * (size_t)p.G + (size_t)p.extra;
         USL_TRY(usl_reserve_loss_partials(c));
         USL_TRY(usl_reserve(c, (void**)&c->bce_partials, &c->bce_partials_cap, (*blocks + (size_t)b) * sizeof(double)));   // more only with parts asked for by hand
         loss.partials = c->bce_partials;
     }
-    void* args[] = {&xi, &idx, &W, &out, &m, &k, &bb, &tg, &perm, &loss};
+    Tail tail = p.tail;
+    void* args[] = {&xi, &idx, &W, &out, &m, &k, &bb, &tg, &perm, &loss, &tail};
     return launch(c, p, args, "forward");
 }
 

@@ -34,6 +34,10 @@ struct Geom {
     int parts_first;       // blockIdx.x is the part of the batch and blockIdx.y the block of labels, not the other way round
     int dummy;             // 256 bytes of LDS that the warm-up loads are thrown into
 };
+// The blocks of labels from `first` on (INT_MAX: none), `blocks` of them, take the batch in parts of `groups` groups: blockIdx.x
+// runs over them part by part, behind the others.  (Forward's alone: as part of Geom it made the compiler's weight gradient
+// 3 % slower at m = 500k, d = 32k.)
+struct Tail { int first, blocks, groups, share; };
 
 static constexpr int ROW_LDS_MAX = 160 * 1024 - 512;    // largest tile
 static constexpr int HALF_COLS = 32768;                 // columns per half of a row in two halves
@@ -70,12 +74,36 @@ __device__ __forceinline__ void touch_lines(const char* __restrict__ row, int fi
 // split the row between them, one load per 128-byte line.
 struct WarmShare {
     int slice, slices;
-    __device__ __forceinline__ explicit WarmShare(const Geom& tg) {
-        slices = tg.share;
-        slice = (int)(tg.parts_first ? blockIdx.y : blockIdx.x >> 3) % slices;
-    }
+    __device__ __forceinline__ WarmShare(uint32_t at, int share) : slice((int)at % share), slices(share) {}
+    __device__ __forceinline__ explicit WarmShare(const Geom& tg)   // no tail
+        : WarmShare(tg.parts_first ? blockIdx.y : blockIdx.x >> 3, tg.share) {}
     // first and number of this workgroup's lines of a tile of nbytes
     __device__ __forceinline__ int per(int nbytes) const { return ((nbytes + 127) / 128 + slices - 1) / slices; }
+};
+// A workgroup of forward: its block of labels, and its groups g0 .. g1 - 1 of the batch.  (The weight gradient has no tail: its
+// parts would have to be added up.)
+struct Turn {
+    uint32_t block;
+    int g0, g1;
+    uint32_t warm_at;   // number among the workgroups that share the warm-up
+    int warm_share;
+    __device__ __forceinline__ Turn(const Geom& tg, const Tail& tail) {
+        block = tg.parts_first ? blockIdx.y : blockIdx.x;
+        uint32_t part = tg.parts_first ? blockIdx.x : blockIdx.y, at = block;
+        int groups = tg.groups_per_block;
+        warm_share = tg.share;
+        if (__builtin_expect(block >= (uint32_t)tail.first, 0)) {
+            at -= (uint32_t)tail.first;
+            part = at / (uint32_t)tail.blocks;   // (with a loop of subtractions the step at m = 500k, b = 256 took 1 % longer)
+            at %= (uint32_t)tail.blocks;
+            block = (uint32_t)tail.first + at;
+            groups = tail.groups;
+            warm_share = tail.share;
+        }
+        warm_at = tg.parts_first ? at : at >> 3;
+        g0 = (int)part * groups;
+        g1 = min(tg.groups, g0 + groups);
+    }
 };
 template <int NT>
 __device__ __forceinline__ void warm_slice(const char* __restrict__ row, int nbytes, int per, int slice, uint32_t dummy, int tid) {
@@ -587,9 +615,8 @@ __device__ __forceinline__ void label_outer(const uint32_t (&pk)[K / 2], const f
 // groups) right before the wait for it: what is loaded there can be waited for at no cost.
 // MULTI = false: one row fills the buffer (tiles of one row, one buffer); HALVES: part 0 / 1 of every row.
 template <int NT, bool MULTI, bool HALVES, typename BODY, typename LATE, typename EARLY>
-__device__ __forceinline__ void walk(const char* __restrict__ xi, uint32_t lds0, const Geom& tg, int g0, int g1, BODY body, LATE late, EARLY early) {
+__device__ __forceinline__ void walk(const char* __restrict__ xi, uint32_t lds0, const Geom& tg, const WarmShare& ws, int g0, int g1, BODY body, LATE late, EARLY early) {
     const uint32_t dummy = lds0 + (uint32_t)tg.dummy;
-    const WarmShare ws(tg);
     if (!MULTI) {
         const int per = ws.per(tg.row_bytes);
         constexpr int HB = HALF_COLS * 4;
@@ -669,13 +696,13 @@ struct LossArgs {
 template <int K, int LPT, int NT, typename TS, int Q, bool HALVES, bool LOSS>
 __global__ void __launch_bounds__(NT)
 k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS* __restrict__ W, float* __restrict__ out,
-          int64_t m, int k, int b, Geom tg, const uint8_t* __restrict__ perm, LossArgs loss) {
+          int64_t m, int k, int b, Geom tg, const uint8_t* __restrict__ perm, LossArgs loss, Tail tail) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const uint32_t lds0 = lds_base(lds_raw);
-    const uint32_t part = tg.parts_first ? blockIdx.x : blockIdx.y;
-    const int64_t j0 = (int64_t)(tg.parts_first ? blockIdx.y : blockIdx.x) * (NT * LPT);
+    const Turn turn(tg, tail);
+    const int64_t j0 = (int64_t)turn.block * (NT * LPT);
     if (LOSS)   // the first words of target bits come to the L2 while the labels' rows are brought in (1 % of the step at m = 500k, b = 256)
-        touch_lines<NT>(reinterpret_cast<const char*>(loss.targets + (size_t)((int)part * tg.groups_per_block * Q >> 5) * m + j0), 0,
+        touch_lines<NT>(reinterpret_cast<const char*>(loss.targets + (size_t)(turn.g0 * Q >> 5) * m + j0), 0,
                         ((int)min((int64_t)NT * LPT, m - j0) * 4 + 127) / 128, lds0 + (uint32_t)tg.dummy, (int)threadIdx.x);
     uint32_t pk[LPT][K / 2];
     WReg<TS, K> w[LPT];
@@ -701,7 +728,7 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
         __syncthreads();
         if (threadIdx.x < 4) reinterpret_cast<uint32_t*>(lds_raw)[HALF_COLS + threadIdx.x] = 0u;
     }
-    const int g0 = (int)part * tg.groups_per_block, g1 = min(tg.groups, g0 + tg.groups_per_block);
+    const int g0 = turn.g0, g1 = turn.g1;
     const int nlab = (int)min((int64_t)NT * LPT, m - j0);
     // Q <= 2: the scores of a group are written while the next group is gathered, before the last label's gathers (a store
     // right before the next copy would make that copy's wait include it; four stores in a row would hold the wavefront
@@ -754,7 +781,7 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
             lost += (double)sum;
         }
     };
-    walk<NT, (Q > 1), HALVES>(xi, lds0, tg, g0, g1,
+    walk<NT, (Q > 1), HALVES>(xi, lds0, tg, WarmShare(turn.warm_at, turn.warm_share), g0, g1,
         [&](int g, uint32_t base, int part) {
             float before[DELAY ? LPT : 1][Q];
 #pragma unroll
@@ -863,7 +890,7 @@ k_backward_weight(const float* __restrict__ g, const char* __restrict__ xi, cons
 #pragma unroll
         for (int l = 0; l < LPT; ++l) load_g(g0, l, gnext[AHEAD ? l : 0]);
     }
-    walk<NT, (Q > 1), HALVES>(xi, lds0, tg, g0, g1,
+    walk<NT, (Q > 1), HALVES>(xi, lds0, tg, WarmShare(tg), g0, g1,
         [&](int grp, uint32_t base, int part) {
             if (part == 0) {
                 if (AHEAD) {

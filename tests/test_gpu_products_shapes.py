@@ -62,3 +62,24 @@ def test_products_with_the_parts_of_the_batch_first(orc, m, d, k, b, storage, sp
     monkeypatch.setenv("USL_TUNE_SPLIT", str(split))
     print("products", m, d, k, b, storage, split, flush=True)
     compare(orc, gu, wl.custom(m, d, k, b, storage=storage, positives=1, index=810 + split), m, d, k, b, storage)
+
+
+# more blocks of labels than workgroups fit at once: those of the last round take the batch in parts
+LAST_ROUND = [(263000, 30000, 3, 9, "f32"), (300001, 36000, 2, 35, "bf16"), (262145, 40000, 1, 4, "f32"), (600011, 20000, 3, 13, "f32"),
+              (270000, 65536, 2, 5, "f32"), (530000, 10000, 5, 37, "f32")]
+
+
+@pytest.mark.parametrize("m,d,k,b,storage", LAST_ROUND)
+def test_scores_of_the_blocks_of_a_last_round(orc, m, d, k, b, storage):
+    import gpu_util as gu
+    print("products", m, d, k, b, storage, flush=True)
+    compare(orc, gu, wl.custom(m, d, k, b, storage=storage, positives=1, index=830), m, d, k, b, storage)
+
+
+@pytest.mark.parametrize("m,d,k,b,storage", [s for s in LAST_ROUND if s[1] < 65536])
+def test_losses_of_the_blocks_of_a_last_round(orc, m, d, k, b, storage, monkeypatch):
+    """The sum over all workgroups, and the target bits of parts that begin within a word of 32 instances."""
+    import test_gpu_train_step as steps
+    case = (m, d, k, b, storage, 0, False, False)
+    monkeypatch.setattr(steps, "CASES", [case])
+    steps.test_train_step(orc, *case, monkeypatch)
