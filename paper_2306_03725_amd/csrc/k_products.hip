@@ -377,7 +377,7 @@ usl_status run_backward_weight_generic(usl_ctx* c, const float* g, const void* x
 
 // ---- the register-resident kernels ---------------------------------------------------------------------------
 
-// tuning and test aids: workgroup shape (0, 1, 2) and parts of the batch instead of the estimate's choice
+// tuning and test aids: workgroup shape (0 .. 3) and parts of the batch instead of the estimate's choice
 int tune_shape() { const char* e = getenv("USL_TUNE_SHAPE"); return e && *e ? atoi(e) : -1; }
 int tune_split() { const char* e = getenv("USL_TUNE_SPLIT"); return e && *e ? atoi(e) : 0; }
 
@@ -454,7 +454,7 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
     best.kern.fn = nullptr;
     double best_t = 0.0;
     const int shape_force = tune_shape(), split_force = tune_split();
-    for (int shape = 0; shape < 3; ++shape) {
+    for (int shape = 0; shape < 4; ++shape) {
         if (shape_force >= 0 && shape != shape_force && kernel_for(c, L, kind, shape_force).fn) continue;
         const ProductKernel kern = kernel_for(c, L, kind, shape);
         if (!kern.fn) continue;
@@ -487,7 +487,11 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
             const double rounds = (double)((wgs + (int64_t)cus * res - 1) / ((int64_t)cus * res));
             const double together = most / rounds;
             const double copy = (double)gpb * L.row_bytes / 42.0;
-            const double gather = (double)gpb * kern.NT * kern.LPT * kern.K * (L.halves ? 2 : 1) / reads_per_clk;
+            // At most two wavefronts on a SIMD: they wait for their reads.  The factors are from workgroups of 512 lanes with two
+            // labels each and of 1024 with one: m = 100k, d = 4k, k = 32, b = 128: forward 63 and 54 us, weight gradient 89 and 76;
+            // m = 200k, d = 8k, b = 64, bfloat16: 60.4 and 57.3, 83 and 70.
+            const bool thin = kern.NT / 64 * res <= 8;
+            const double gather = (double)gpb * kern.NT * kern.LPT * kern.K * (L.halves ? 2 : 1) / reads_per_clk * (!thin ? 1.0 : backward ? 1.3 : 1.1);
             const double more = copy > gather ? copy : gather, less = copy > gather ? gather : copy;
             const double load = (double)kern.NT * kern.LPT * c->k * (4.0 + (backward ? 4.0 : es)) / 7.0;
             const double tiles = (double)((gpb + tg.tile_rows - 1) / tg.tile_rows) * (L.halves ? 2 : 1);

@@ -26,6 +26,9 @@ ProductKernel pick(ProductKind kind, int shape) {
             if (shape == 2 && kind != WEIGHT_GRADIENT) return USL_PICK(L2, 512);
         }
         if (shape == 2) return USL_PICK(L, 1024);
+        if constexpr (L > 1 && K >= 16) {
+            if (shape == 3) return USL_PICK(1, 1024);
+        }
     } else if constexpr (K < 64) {
         if (shape == 1) return USL_PICK(1, 1024);
         if (shape == 2 && L > 1) return USL_PICK(L, 1024);

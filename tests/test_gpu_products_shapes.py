@@ -83,3 +83,13 @@ def test_losses_of_the_blocks_of_a_last_round(orc, m, d, k, b, storage, monkeypa
     case = (m, d, k, b, storage, 0, False, False)
     monkeypatch.setattr(steps, "CASES", [case])
     steps.test_train_step(orc, *case, monkeypatch)
+
+
+@pytest.mark.parametrize("split", [1, 3])
+@pytest.mark.parametrize("m,d,k,b,storage", [(2500, 4096, 32, 13, "f32"), (2049, 15000, 20, 13, "bf16"), (1023, 10000, 16, 30, "f32"), (1025, 20000, 32, 7, "f32")])
+def test_products_with_one_label_a_lane_in_wide_workgroups(orc, m, d, k, b, storage, split, monkeypatch):
+    import gpu_util as gu
+    monkeypatch.setenv("USL_TUNE_SHAPE", "3")
+    monkeypatch.setenv("USL_TUNE_SPLIT", str(split))
+    print("products", m, d, k, b, storage, split, flush=True)
+    compare(orc, gu, wl.custom(m, d, k, b, storage=storage, positives=1, index=840 + split), m, d, k, b, storage)
