@@ -101,88 +101,120 @@ template <int KT> struct ListLayout;   // what depends on which kernel the lists
 template <> struct ListLayout<68> { static constexpr uint32_t near = 1024; };
 template <> struct ListLayout<36> { static constexpr uint32_t near = NEAR2; };
 template <> struct ListLayout<32> { static constexpr uint32_t near = NEAR2; };
-constexpr int CHUNK = 32768;   // features per LDS histogram
-
-__global__ void k_fill_u32(uint32_t* p, size_t n, uint32_t v) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = v;
+// label of flat slot e within its window (w0: the window's first label), as the lists hold it.  inv_k: inverse_of(k)
+__device__ __forceinline__ uint32_t inverse_of(int k) { return k > 1 ? (uint32_t)(0x100000000ull / (uint32_t)k) : 0xFFFFFFFFu; }
+template <int KTOT>
+__device__ __forceinline__ uint32_t label_of_slot(uint32_t e, int k, uint32_t inv_k, uint32_t w0, const Cut& cut) {
+    uint32_t q = __umulhi(e, inv_k);   // e / k, at most one too low
+    if (e - q * (uint32_t)k >= (uint32_t)k) ++q;
+    q -= w0;
+    return KTOT == KT_BOTH4 ? unit_of_label<4>(q, (uint32_t)cut.wl) : q;
 }
-
-// The slots of one window's labels, cut into `splits` contiguous shares.  Returns the window.  An XCD (blockIdx.x % 8) takes
-// an eighth of the shares in order: the shares of a window write into the same lines, through one L2.
-__device__ __forceinline__ int share_of(int64_t m, int k, int wl, int splits, size_t* e0, size_t* e1) {
-    const int t = (int)(blockIdx.x & 7) * ((int)gridDim.x / 8) + (int)(blockIdx.x >> 3);
-    const int w = t / splits, s = t % splits;
-    const size_t w0 = (size_t)min((int64_t)w * wl, m) * k;   // (a window behind the last one: no slots)
-    const size_t w1 = (size_t)min((int64_t)(w + 1) * wl, m) * k;
-    const size_t per = (w1 - w0 + splits - 1) / splits;
-    *e0 = min(w0 + per * s, w1);
-    *e1 = min(*e0 + per, w1);
-    return w;
-}
-
-// f(slot, its virtual feature counted from c0) for the slots [e0, e1) of a share: eight of a lane's loads in flight together
-// (one at a time, the latency of memory was most of the time of these kernels)
-template <typename F>
-__device__ __forceinline__ void for_share(const int32_t* __restrict__ idx, size_t e0, size_t e1, int k, int d, const Cut& cut, uint32_t j0, int c0, F f) {
-    for (size_t e = e0 + threadIdx.x; e < e1; e += 8 * NT) {
-        uint32_t col[8];
+// Sum of v over the lanes up to this one; *total = over all.  sh: NT / 64 words that no other use of them is still reading.
+__device__ __forceinline__ uint32_t block_inclusive_scan(uint32_t v, uint32_t* sh, uint32_t* total) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) col[u] = e + u * NT < e1 ? (uint32_t)idx[e + u * NT] : 0u;
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (e + u * NT < e1) f(e + u * NT, cut.S == 1 ? col[u] - (uint32_t)c0 : cut.vfeat(col[u], (uint32_t)(e + u * NT) / (uint32_t)k - j0, d) - (uint32_t)c0);
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t t = __shfl_up(v, o);
+        if ((int)(threadIdx.x & 63) >= o) v += t;
     }
+    if ((threadIdx.x & 63) == 63) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    uint32_t below = 0, all = 0;
+#pragma unroll
+    for (int q = 0; q < NT / 64; ++q) {
+        const uint32_t t = sh[q];
+        below += q < (int)(threadIdx.x >> 6) ? t : 0u;
+        all += t;
+    }
+    *total = all;
+    return below + v;
 }
 
-// count[w][c] += connections of this workgroup's share that lead into feature c (LDS histogram, then one global
-// atomic per feature that occurs).  grid (nwin * splits, feature chunks).
-__global__ void __launch_bounds__(NT)
-k_lf_count(const int32_t* __restrict__ idx, int64_t m, int k, int d, Cut cut, int splits, uint32_t* __restrict__ count) {
-    extern __shared__ uint32_t hist[];
-    const int c0 = blockIdx.y * CHUNK, nc = min(CHUNK, cut.vd - c0);
-    size_t e0, e1;
-    const int w = share_of(m, k, cut.wl, splits, &e0, &e1);
-    if (w >= cut.nwin) return;
-    const uint32_t j0 = (uint32_t)w * (uint32_t)cut.wl;
-    for (int q = threadIdx.x; q < nc; q += NT) hist[q] = 0;
-    __syncthreads();
-    for_share(idx, e0, e1, k, d, cut, j0, c0, [&](size_t, uint32_t c) {
-        if (c < (uint32_t)nc) atomicAdd(&hist[c], 1u);
-    });
-    __syncthreads();
-    uint32_t* dst = count + (size_t)w * cut.vd + c0;
-    for (int q = threadIdx.x; q < nc; q += NT)
-        if (hist[q]) atomicAdd(&dst[q], hist[q]);
-}
-
-// One workgroup per (window, feature block): ranks the block's NF features by list length, pairs them, fixes the
-// slot ranges of every wavefront and counts what will not fit.
+// The connections of a workgroup of the gather kernel, by place (k_lf_seg_place): their flat slots and features.  Where a
+// window has one block of features only, the places are the flat slots, and idx has the features.
+constexpr size_t LF_STAGED = 36864 + 512;
+struct LfPlaces {
+    const int32_t* idx;
+    const uint32_t* slot_at;   // [m*k] by place
+    const uint16_t* feat_at;   // [m*k] by place: feature within the block
+    uint32_t* pos;             // one block only: place of every flat slot, written here (or NULL)
+    uint32_t small_wg;         // workgroups with no more connections have entries of label and place in one word (0: none)
+    int staged;                // entries that LDS holds
+};
+// One workgroup per (window, feature block): counts the connections of the block's NF features, ranks these by list length, pairs
+// them, fixes the slot ranges of every wavefront, counts what will not fit, and groups the connections by feature:
+// ent[ent_base[wg] + where[w][c] + p] = the p-th connection from window w into feature c (p by a cursor: the order inside a list
+// is not fixed): its flat slot j*k+t, or, for the kernel of both products unless the connectivity is skewed, its label within
+// the window and its place, 16 bits each.  The groups are put together in LDS and leave it in whole lines (beyond what LDS holds
+// each entry goes where it belongs by itself).
+// Reading every connection once from its place, a workgroup counts and groups without a global atomic; with shares of a window's
+// slots that counted all features and reserved their places in every list by atomics, counting, ranking and grouping took
+// 414 us at m = 500k, d = 32k, k = 32, with the places 462, now 189.
+//   count[w][c]       = length of a list
 //   feat[wg][z][lane] = feature (within the block) whose list lane holds in zone z
 //   caps[wg][wave]    = acap | bcap << 8
-//   where[w][c]       = where the list of feature c starts among the workgroup's entries (k_lf_fill puts them there)
-//   n_ent[wg]         = entries of the workgroup
+//   where[w][c]       = where the list of feature c starts among the workgroup's entries
 //   ov_off[w][c]      = where what does not fit of that list starts in the workgroup's overflow list
 //   n_ov[wg]          = entries beyond the allowances
 //   ovr[wg][z][lane]  = start | n << 16: the part of that list's overflow among the first NT (NEAR2) entries (those the
 //                       gather kernel keeps in LDS and the list's own lane adds up)
 template <int KTOT>
 __global__ void __launch_bounds__(NT)
-k_lf_plan(const uint32_t* __restrict__ count, int vd, int nfb, int fpb, uint32_t* __restrict__ where, uint32_t* __restrict__ ov_off,
-          uint16_t* __restrict__ feat, uint32_t* __restrict__ caps, uint32_t* __restrict__ n_ent,
-          uint32_t* __restrict__ n_ov, uint32_t* __restrict__ ovr) {
+k_lf_plan(LfPlaces in, int64_t m, int k, int d, Cut cut, uint32_t* __restrict__ ent_base, uint32_t* __restrict__ count,
+          uint32_t* __restrict__ where, uint32_t* __restrict__ ov_off, uint16_t* __restrict__ feat, uint32_t* __restrict__ caps,
+          uint32_t* __restrict__ n_ov, uint32_t* __restrict__ ovr, uint32_t* __restrict__ ent) {
+    extern __shared__ uint32_t staged[];
     __shared__ uint32_t start[256];
-    __shared__ uint32_t scan[NT];
+    __shared__ uint32_t cur[NF];            // lengths of the lists, then where their next entries go
+    __shared__ uint32_t sh[2][NT / 64];
     __shared__ uint16_t len_of[2][NT];
     __shared__ uint32_t cap_of[NT / 64];
+    const int nfb = cut.nfb, fpb = cut.fpb, vd = cut.vd;
     const int wg = blockIdx.x, w = wg / nfb, fb = wg % nfb;
-    const uint32_t* cnt = count + (size_t)w * vd + (size_t)fb * fpb;
+    const uint32_t w0 = (uint32_t)((size_t)w * cut.wl * k);
+    if (nfb == 1 && threadIdx.x == 0) {   // (the launch order makes it known to the kernels that follow)
+        ent_base[wg] = w0;
+        if (wg == cut.nwin - 1) ent_base[wg + 1] = (uint32_t)(m * k);
+    }
+    const uint32_t e0 = nfb == 1 ? w0 : ent_base[wg];
+    const uint32_t n_ent = nfb == 1 ? (uint32_t)(min((int64_t)(w + 1) * cut.wl, m) * k) - w0 : ent_base[wg + 1] - e0;
+    // use(place, feature within the block) for the workgroup's connections, eight of a lane's loads in flight together
+    auto connections = [&](auto use) {
+        for (uint32_t p = threadIdx.x; p < n_ent; p += 8 * NT) {
+            uint32_t f[8];
+            if (nfb == 1) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) f[u] = (uint32_t)in.idx[e0 + min(p + u * NT, n_ent - 1)];
+                if (cut.S > 1) {
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) f[u] = f[u] < (uint32_t)d ? cut.vfeat(f[u], (p + u * NT) / (uint32_t)k, d) : (uint32_t)NF;
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) f[u] = in.feat_at[e0 + min(p + u * NT, n_ent - 1)];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (p + u * NT >= n_ent) f[u] = NF;   // none
+            use(p, f);
+        }
+    };
     const int nf = min(fpb, vd - fb * fpb);   // features of the block that exist; the others have empty lists
     if (threadIdx.x < 256) start[threadIdx.x] = 0;
+    cur[threadIdx.x] = cur[threadIdx.x + NT] = 0;
     __syncthreads();
+    connections([&](uint32_t, const uint32_t (&f)[8]) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (f[u] < (uint32_t)nf) atomicAdd(&cur[f[u]], 1u);
+    });
+    __syncthreads();
+    const size_t bin = (size_t)w * vd + (size_t)fb * fpb + threadIdx.x;
     uint32_t n[2];
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-        n[q] = (int)threadIdx.x + q * NT < nf ? cnt[threadIdx.x + q * NT] : 0u;
+        n[q] = cur[threadIdx.x + q * NT];
+        if ((int)threadIdx.x + q * NT < nf) count[bin + q * NT] = n[q];
         atomicAdd(&start[min(n[q], 255u)], 1u);
     }
     __syncthreads();
@@ -251,28 +283,17 @@ k_lf_plan(const uint32_t* __restrict__ count, int vd, int nfb, int fpb, uint32_t
         ov[q] = n[q] > cap ? n[q] - cap : 0u;
         ov[q] = (ov[q] + 1u) & ~1u;   // an even number of places: the list's lane walks them two at a time
     }
-    auto block_scan = [&](uint32_t mine) -> uint32_t {   // inclusive, over the lanes of the workgroup
-        __syncthreads();
-        scan[threadIdx.x] = mine;
-        __syncthreads();
-        for (int o = 1; o < NT; o <<= 1) {
-            const uint32_t t = threadIdx.x >= (unsigned)o ? scan[threadIdx.x - o] : 0u;
-            __syncthreads();
-            scan[threadIdx.x] += t;
-            __syncthreads();
-        }
-        return scan[threadIdx.x];
-    };
-    const size_t bin = (size_t)w * vd + (size_t)fb * fpb + threadIdx.x;
     {
-        const uint32_t incl = block_scan(n[0] + n[1]);
-        if ((int)threadIdx.x < nf) where[bin] = incl - n[0] - n[1];
-        if ((int)threadIdx.x + NT < nf) where[bin + NT] = incl - n[1];
-        if (threadIdx.x == NT - 1) n_ent[wg] = incl;
+        uint32_t all, at = block_inclusive_scan(n[0] + n[1], sh[0], &all) - n[0] - n[1];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            if ((int)threadIdx.x + q * NT < nf) where[bin + q * NT] = at;
+            cur[threadIdx.x + q * NT] = at;   // (read as a length by this lane alone)
+            at += n[q];
+        }
     }
     {
-        const uint32_t incl = block_scan(ov[0] + ov[1]);
-        uint32_t at = incl - ov[0] - ov[1];
+        uint32_t all, at = block_inclusive_scan(ov[0] + ov[1], sh[1], &all) - ov[0] - ov[1];
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             if ((int)threadIdx.x + q * NT < nf) ov_off[bin + q * NT] = at;
@@ -280,26 +301,44 @@ k_lf_plan(const uint32_t* __restrict__ count, int vd, int nfb, int fpb, uint32_t
             ovr[((size_t)wg * 2 + zone_of[q]) * NT + lane_of[q]] = first | (min(ov[q], ListLayout<KTOT>::near - first) << 16);
             at += ov[q];
         }
-        if (threadIdx.x == NT - 1) n_ov[wg] = incl;
+        if (threadIdx.x == 0) n_ov[wg] = all;
     }
+    // (the second scan's barrier stands between the cursors and their use)
+    const bool small = n_ent <= in.small_wg, stage = n_ent <= (uint32_t)in.staged;
+    const uint32_t inv_k = inverse_of(k), first_label = (uint32_t)w * (uint32_t)cut.wl;
+    uint32_t* to = stage ? staged : ent + e0;
+    connections([&](uint32_t p, const uint32_t (&f)[8]) {
+        uint32_t e[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const uint32_t place = min(p + u * NT, n_ent - 1);
+            e[u] = nfb == 1 ? e0 + place : in.slot_at[e0 + place];
+            if (nfb == 1 && in.pos) in.pos[e[u]] = e[u];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (f[u] < (uint32_t)nf)
+                to[atomicAdd(&cur[f[u]], 1u)] = small ? label_of_slot<KTOT>(e[u], k, inv_k, first_label, cut) | (p + u * NT) << 16 : e[u];
+    });
+    if (!stage) return;
+    __syncthreads();
+    for (uint32_t q = threadIdx.x; q < n_ent; q += NT) ent[e0 + q] = staged[q];
 }
 
-// base[wg] = sum of count over the workgroups before wg, base[nwg] = all of them: of the overflow entries (block 0) and of
-// all entries (block 1).  Block 2 records the fingerprint of idx.
-struct LfScan { const uint32_t* count[2]; uint32_t* base[2]; };
+// base[wg] = sum of count over the workgroups before wg, base[nwg] = all of them.  Block 1, if there is one, records the
+// fingerprint of idx.
 __global__ void __launch_bounds__(1024)
-k_lf_scan(LfScan what, int nwg, const uint32_t* __restrict__ idx, size_t n_words, uint64_t* __restrict__ print, int which) {
+k_lf_scan(const uint32_t* __restrict__ count, uint32_t* __restrict__ base, int nwg, const uint32_t* __restrict__ idx, size_t n_words,
+          uint64_t* __restrict__ print, int which) {
     __shared__ uint32_t part[1024];
-    if (blockIdx.x == 2) {
+    if (blockIdx.x == 1) {
         usl_idx_fingerprint_block(idx, n_words, print, which, 1);
         return;
     }
-    const uint32_t* ov_count = what.count[blockIdx.x];
-    uint32_t* ov_base = what.base[blockIdx.x];
     const int per = (nwg + 1023) / 1024;
     const int a = min(nwg, (int)threadIdx.x * per), e = min(nwg, a + per);
     uint32_t s = 0;
-    for (int q = a; q < e; ++q) s += ov_count[q];
+    for (int q = a; q < e; ++q) s += count[q];
     part[threadIdx.x] = s;
     __syncthreads();
     for (int o = 1; o < 1024; o <<= 1) {
@@ -309,86 +348,76 @@ k_lf_scan(LfScan what, int nwg, const uint32_t* __restrict__ idx, size_t n_words
         __syncthreads();
     }
     uint32_t run = part[threadIdx.x] - s;
-    for (int q = a; q < e; ++q) { ov_base[q] = run; run += ov_count[q]; }
-    if (threadIdx.x == 1023) ov_base[nwg] = part[1023];
+    for (int q = a; q < e; ++q) { base[q] = run; run += count[q]; }
+    if (threadIdx.x == 1023) base[nwg] = part[1023];
 }
 
-// Groups the connections by (workgroup of the gather kernel, feature): ent[ent_base[wg] + where[w][c] + p] = flat
-// slot j*k+t of the p-th connection from window w into feature c (p by a cursor: the order inside a list is not
-// fixed).  Same decomposition as k_lf_count: a share's positions in every list are reserved with one global atomic
-// per feature, then handed out from LDS cursors.
 struct OvEntry { uint16_t feature; uint16_t label; uint32_t slot; };
-__global__ void __launch_bounds__(NT)
-k_lf_fill(const int32_t* __restrict__ idx, int64_t m, int k, int d, Cut cut, int splits, const uint32_t* __restrict__ where,
-          uint32_t* __restrict__ taken, const uint32_t* __restrict__ ent_base, uint32_t* __restrict__ ent) {
-    extern __shared__ uint32_t cur[];
-    const int c0 = blockIdx.y * CHUNK, nc = min(CHUNK, cut.vd - c0);
-    size_t e0, e1;
-    const int w = share_of(m, k, cut.wl, splits, &e0, &e1);
-    if (w >= cut.nwin) return;
-    const uint32_t j0 = (uint32_t)w * (uint32_t)cut.wl;
-    for (int q = threadIdx.x; q < nc; q += NT) cur[q] = 0;
-    __syncthreads();
-    for_share(idx, e0, e1, k, d, cut, j0, c0, [&](size_t, uint32_t c) {
-        if (c < (uint32_t)nc) atomicAdd(&cur[c], 1u);
-    });
-    __syncthreads();
-    const size_t bin0 = (size_t)w * cut.vd + c0;
-    for (int q0 = threadIdx.x; q0 < nc; q0 += 8 * NT) {   // from here cur[q] = where this share's part of the list starts
-        uint32_t at[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int q = q0 + u * NT;
-            const uint32_t n = q < nc ? cur[q] : 0u;
-            at[u] = n ? atomicAdd(&taken[bin0 + q], n) + where[bin0 + q] + ent_base[(size_t)w * cut.nfb + (c0 + q) / cut.fpb] : 0u;
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (q0 + u * NT < nc) cur[q0 + u * NT] = at[u];
-    }
-    __syncthreads();
-    for_share(idx, e0, e1, k, d, cut, j0, c0, [&](size_t e, uint32_t c) {
-        if (c < (uint32_t)nc) ent[atomicAdd(&cur[c], 1u)] = (uint32_t)e;
-    });
-}
-
-// Where the kernel for both products leaves the weight gradient of every connection (pos[flat slot], a place in an
-// array of m * k floats): the connections of a (window, feature block) workgroup together (from ent_base[wg], as in
-// ent), and within it in the order of their flat slots, up to the order inside a run of SEG slots.  The Adam kernel,
-// which goes through the slots in order, then reads 16 or so neighbouring places from each of the window's nfb
+// The place of every connection, out of m * k: those of a (window, feature block) workgroup together (from ent_base[wg], as in
+// ent), and within it in the order of their flat slots, up to the order inside a run of SEG slots.  k_lf_plan goes through a
+// workgroup's connections by place, and the kernel for both products leaves the weight gradients there (pos[flat slot]): the
+// Adam kernel, which goes through the slots in order, then reads 16 or so neighbouring places from each of the window's nfb
 // workgroups per wavefront -- whole lines; in the order of the lists it would fetch a line per value.
 // slot_at[place] is the way back: the kernel reads the weights in the order of the places, for the same reason.
-// Three kernels: the counts of every run per feature block, their running sums, the places.  Where a window has one block
-// only, the places are the flat slots themselves, and slot_at is not needed.
+// Three kernels (and the sums of the workgroups in between): the counts of every run per feature block, their running sums, the
+// places.  Where a window has one block only, the places are the flat slots themselves, and none of this is needed.
 constexpr int SEG = 256;   // slots of a run: one wavefront, four per lane
-__device__ __forceinline__ bool seg_of_wave(int64_t m, int k, const Cut& cut, int nseg, int64_t total, int* w, int* seg, size_t* s0, size_t* s1) {
-    const int64_t gs = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (gs >= total) return false;
-    *w = (int)(gs / nseg); *seg = (int)(gs % nseg);
-    const size_t w0 = (size_t)*w * cut.wl * k, w1 = (size_t)min((int64_t)(*w + 1) * cut.wl, m) * k;
-    *s0 = min(w0 + (size_t)*seg * SEG, w1);
-    *s1 = min(*s0 + SEG, w1);
-    return true;
-}
+struct LfRun {
+    int w, seg;
+    bool on;
+    size_t e;       // the lane's first slot
+    int n;          // how many it has, up to four
+    uint32_t col[4], block[4];   // feature, block of features (nfb: a feature that the layer does not have)
+    // An XCD (blockIdx.x % 8) takes an eighth of the runs in order: neighbours write into the same lines, through one L2.
+    __device__ __forceinline__ LfRun(const int32_t* __restrict__ idx, int64_t m, int k, const Cut& cut, int nseg, int64_t total) {
+        typedef int i32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+        const int64_t gs = ((int64_t)(blockIdx.x & 7) * (gridDim.x / 8) + (blockIdx.x >> 3)) * 4 + (threadIdx.x >> 6);
+        on = gs < total;
+        w = seg = n = 0;
+        e = 0;
+        if (!on) return;
+        w = (int)(gs / nseg);
+        seg = (int)(gs % nseg);
+        const size_t w0 = (size_t)w * cut.wl * k, w1 = (size_t)min((int64_t)(w + 1) * cut.wl, m) * k;
+        const size_t s0 = min(w0 + (size_t)seg * SEG, w1), s1 = min(s0 + SEG, w1);
+        e = s0 + (threadIdx.x & 63) * 4;
+        n = e < s1 ? (int)min(s1 - e, (size_t)4) : 0;
+        if (n == 4) {
+            const i32x4_any v = *reinterpret_cast<const i32x4_any*>(idx + e);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) col[u] = (uint32_t)v[u];
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) col[u] = u < n ? (uint32_t)idx[e + u] : 0u;
+        }
+        const uint32_t inv = inverse_of(cut.fpb);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            block[u] = __umulhi(col[u], inv);   // at most one too low
+            if (col[u] - block[u] * (uint32_t)cut.fpb >= (uint32_t)cut.fpb) ++block[u];
+            block[u] = min(block[u], (uint32_t)cut.nfb);
+        }
+    }
+};
 __global__ void __launch_bounds__(256)
 k_lf_seg_count(const int32_t* __restrict__ idx, int64_t m, int k, Cut cut, int nseg, int64_t total, uint32_t* __restrict__ segcnt) {
-    __shared__ uint32_t h[4][32];
+    __shared__ uint32_t h[4][33];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (lane < 32) h[wave][lane] = 0;
+    if (lane < 33) h[wave][lane] = 0;
     __syncthreads();
-    int w, seg; size_t s0, s1;
-    const bool on = seg_of_wave(m, k, cut, nseg, total, &w, &seg, &s0, &s1);
-    if (on)
-        for (size_t e = s0 + lane; e < s1; e += 64) atomicAdd(&h[wave][cut.S > 1 ? 0u : min((uint32_t)idx[e] / (uint32_t)cut.fpb, 31u)], 1u);
+    const LfRun run(idx, m, k, cut, nseg, total);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (u < run.n) atomicAdd(&h[wave][run.block[u]], 1u);
     __syncthreads();
-    if (on && lane < cut.nfb) segcnt[((size_t)w * cut.nfb + lane) * nseg + seg] = h[wave][lane];
+    if (run.on && lane < cut.nfb) segcnt[((size_t)run.w * cut.nfb + lane) * nseg + run.seg] = h[wave][lane];
 }
-// segcnt[wg][seg] -> ent_base[wg] + the counts of the runs before seg (in place).  One block per workgroup wg.
+// segcnt[wg][seg] -> the counts of the runs before seg (in place); n_ent[wg] = all of them.  One block per workgroup wg.
 __global__ void __launch_bounds__(256)
-k_lf_seg_scan(uint32_t* __restrict__ segcnt, int nseg, const uint32_t* __restrict__ ent_base) {
+k_lf_seg_scan(uint32_t* __restrict__ segcnt, int nseg, uint32_t* __restrict__ n_ent) {
     __shared__ uint32_t part[256];
     uint32_t* c = segcnt + (size_t)blockIdx.x * nseg;
-    uint32_t carry = ent_base[blockIdx.x];
+    uint32_t carry = 0;
     for (int q0 = 0; q0 < nseg; q0 += 256) {
         const int q = q0 + (int)threadIdx.x;
         const uint32_t mine = q < nseg ? c[q] : 0u;
@@ -404,24 +433,68 @@ k_lf_seg_scan(uint32_t* __restrict__ segcnt, int nseg, const uint32_t* __restric
         carry += part[255];
         __syncthreads();
     }
+    if (threadIdx.x == 0) n_ent[blockIdx.x] = carry;
 }
 __global__ void __launch_bounds__(256)
-k_lf_seg_place(const int32_t* __restrict__ idx, int64_t m, int k, Cut cut, int nseg, int64_t total,
-               const uint32_t* __restrict__ segbase, uint32_t* __restrict__ pos, uint32_t* __restrict__ slot_at) {
-    __shared__ uint32_t h[4][32];
+k_lf_seg_place(const int32_t* __restrict__ idx, int64_t m, int k, Cut cut, int nseg, int64_t total, const uint32_t* __restrict__ segbase,
+               const uint32_t* __restrict__ ent_base, uint32_t* __restrict__ pos /* or NULL */, uint32_t* __restrict__ slot_at,
+               uint16_t* __restrict__ feat_at) {
+    // A run's connections are put into the order of their places in LDS, so that a store writes a few stretches of consecutive
+    // places; each lane storing its own four, what bounded this was the number of lines per store (80 us at m = 500k, d = 32k,
+    // k = 32, now 69).
+    __shared__ uint32_t h[4][33], base[4][33];   // per block: connections; first place, less what lies before it in the run
+    __shared__ uint32_t sorted[4][SEG];          // slot within the run | feature within the block << 8 | block << 19
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    int w, seg; size_t s0, s1;
-    const bool on = seg_of_wave(m, k, cut, nseg, total, &w, &seg, &s0, &s1);
-    if (on && cut.nfb > 1 && lane < cut.nfb) h[wave][lane] = segbase[((size_t)w * cut.nfb + lane) * nseg + seg];
+    if (lane < 33) h[wave][lane] = 0;
     __syncthreads();
-    if (on && cut.nfb == 1) {
-        for (size_t e = s0 + lane; e < s1; e += 64) pos[e] = (uint32_t)e;
-    } else if (on)
-        for (size_t e = s0 + lane; e < s1; e += 64) {
-            const uint32_t p = atomicAdd(&h[wave][cut.S > 1 ? 0u : min((uint32_t)idx[e] / (uint32_t)cut.fpb, 31u)], 1u);
-            pos[e] = p;
-            slot_at[p] = (uint32_t)e;
+    const LfRun run(idx, m, k, cut, nseg, total);
+    uint32_t r[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) r[u] = u < run.n ? atomicAdd(&h[wave][run.block[u]], 1u) : 0u;
+    __syncthreads();
+    {
+        const uint32_t n = lane < cut.nfb ? h[wave][lane] : 0u;   // (features that the layer does not have get no place)
+        uint32_t before = n;
+        for (int o = 1; o < 32; o <<= 1) {
+            const uint32_t t = __shfl_up(before, o);
+            if (lane >= o) before += t;
         }
+        before -= n;
+        if (run.on && lane < cut.nfb) {
+            h[wave][lane] = before;
+            base[wave][lane] = ent_base[run.w * cut.nfb + lane] + segbase[((size_t)run.w * cut.nfb + lane) * nseg + run.seg] - before;
+        }
+        if (lane == cut.nfb - 1) h[wave][32] = before + n;   // all that have a place
+    }
+    __syncthreads();
+    const int have = run.on ? (int)h[wave][32] : 0;
+    uint32_t place[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const uint32_t b = run.block[u];
+        place[u] = PAD_SLOT;
+        if (u < run.n && b < (uint32_t)cut.nfb) {
+            const uint32_t at = h[wave][b] + r[u];
+            place[u] = base[wave][b] + at;
+            sorted[wave][at] = (uint32_t)(lane * 4 + u) | (run.col[u] - b * (uint32_t)cut.fpb) << 8 | b << 19;
+        }
+    }
+    if (pos) {
+        typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+        if (run.n == 4) *reinterpret_cast<u32x4_any*>(pos + run.e) = (u32x4_any){place[0], place[1], place[2], place[3]};
+        else
+            for (int u = 0; u < run.n; ++u) pos[run.e + u] = place[u];
+    }
+    __syncthreads();
+    const uint32_t first = (uint32_t)(run.e - (size_t)lane * 4);
+#pragma unroll
+    for (int u = 0; u < SEG / 64; ++u) {
+        const int i = u * 64 + lane;
+        if (i >= have) break;
+        const uint32_t v = sorted[wave][i], p = base[wave][v >> 19] + (uint32_t)i;
+        slot_at[p] = first + (v & 255u);
+        feat_at[p] = (uint16_t)(v >> 8 & 2047u);
+    }
 }
 
 // Bank-aware order of the entries in every lane's lists.  At step t of the gathers the 32 lanes of a half-wavefront
@@ -433,12 +506,13 @@ k_lf_seg_place(const int32_t* __restrict__ idx, int64_t m, int k, Cut cut, int n
 // empty places, which may go to any step and read any bank.  A lane that finds no bank among its entries spends an
 // empty place (it then reads the zero word of a free bank, see ZERO_LABEL) while it has one.
 // One half-wavefront per (workgroup of the gather kernel, zone, 32 lanes); lane i is list i and also bank i.
-// Reads the lists as k_lf_fill grouped them (ent), writes them ordered into the places the gather kernel loads its
+// Reads the lists as k_lf_plan grouped them (ent), writes them ordered into the places the gather kernel loads its
 // registers from (lab / slot: [workgroup][slot][lane]) and what exceeds the allowance into the overflow list.  Any
 // outcome is a valid order: it changes speed, never results.  rounds = 0: the lists stay in the order of ent.
 // pos (if given, see k_lf_seg_place): every entry's place among its workgroup's weight gradients goes along, into rk
 // (beside lab / slot) or ovrk (beside ov); an empty place gets PAD_SLOT.  A workgroup of at most small_wg entries, as all are
-// unless the connectivity is skewed, has places of 16 bits in rk, laid out like lab, at the beginning of its part.
+// unless the connectivity is skewed, has labels and places in ent, and places of 16 bits in rk, laid out like lab, at the
+// beginning of its part; slot_at (NULL: one block of features) has its flat slots by place.
 // GS = lanes and banks of a group: 32, or 16 where the gathers are 16 bytes wide (the lanes of a half-wavefront that such a
 // read serves together: 0-3, 12-15, 20-27 and the other 16).
 constexpr int SG_NT = 256;   // lanes per workgroup
@@ -448,7 +522,8 @@ k_lf_schedule(const uint32_t* __restrict__ ent, const uint32_t* __restrict__ ent
               const uint32_t* __restrict__ count, const uint16_t* __restrict__ feat, const uint32_t* __restrict__ caps,
               const uint32_t* __restrict__ ov_base, const uint32_t* __restrict__ ov_off, int k, Cut cut,
               uint32_t zero_label, int rounds, uint16_t* __restrict__ lab, uint32_t* __restrict__ slot, OvEntry* __restrict__ ov,
-              const uint32_t* __restrict__ pos, uint32_t small_wg, uint32_t* __restrict__ rk, uint32_t* __restrict__ ovrk) {
+              const uint32_t* __restrict__ pos, const uint32_t* __restrict__ slot_at, uint32_t small_wg, uint32_t* __restrict__ rk,
+              uint32_t* __restrict__ ovrk) {
     constexpr int SG = SG_NT / GS;
     typedef usl_bank_lists<GS, KTOT> Lists;
     __shared__ typename Lists::Lane lists[SG][GS];
@@ -467,7 +542,10 @@ k_lf_schedule(const uint32_t* __restrict__ ent, const uint32_t* __restrict__ ent
     const int w = (int)(wg / cut.nfb), fb = (int)(wg % cut.nfb);
     auto at = [&](int p) -> size_t { return (wg * KTOT + (zone ? KTOT - 1 - p : p)) * NT + mypos; };
     const bool small = pos && ent_base[wg + 1] - ent_base[wg] <= small_wg;
-    // four steps' labels, flat slots (PAD_SLOT: none) and places at once: neighbours in the lane's record (caps are multiples of 4)
+    const uint32_t inv_k = inverse_of(k);   // the same for all lanes
+    auto label_of = [&](uint32_t e) { return small ? e & 0xFFFFu : label_of_slot<KTOT>(e, k, inv_k, (uint32_t)w * (uint32_t)cut.wl, cut); };
+    auto place_of = [&](uint32_t e) { return small ? e >> 16 : pos[e] - ent_base[wg]; };
+    // four steps' labels, entries (PAD_SLOT: none; no entry is that: a place is below 65535) and places at once: neighbours in the lane's record (caps are multiples of 4)
     auto leave = [&](int s, const uint32_t (&l)[4], const uint32_t (&e)[4]) {
         const int t = zone ? KTOT - 4 - s : s;
         auto two = [&](uint32_t lo, uint32_t hi) { return zone ? hi & 0xFFFFu | lo << 16 : lo & 0xFFFFu | hi << 16; };
@@ -480,7 +558,7 @@ k_lf_schedule(const uint32_t* __restrict__ ent, const uint32_t* __restrict__ ent
         if (pos) {
             uint32_t place[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) place[u] = e[u] != PAD_SLOT ? pos[e[u]] - ent_base[wg] : PAD_SLOT;
+            for (int u = 0; u < 4; ++u) place[u] = e[u] != PAD_SLOT ? place_of(e[u]) : PAD_SLOT;
             if (small) {
                 *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(rk + wg * KTOT * NT) + half_at<KTOT>(0, t, mypos)) = four(place);
             } else {
@@ -489,25 +567,20 @@ k_lf_schedule(const uint32_t* __restrict__ ent, const uint32_t* __restrict__ ent
             }
         }
     };
-    // my list: feature, length, where its entries are; label of an entry = its flat slot / k, counted from the window's first
+    // my list: feature, length, where its entries are
     const uint32_t f = feat[(wg * 2 + zone) * NT + mypos];
     const bool exists = (int)f < min(cut.fpb, cut.vd - fb * cut.fpb);
     const size_t bin = exists ? (size_t)w * cut.vd + (size_t)fb * cut.fpb + f : 0;
     const uint32_t len = exists ? count[bin] : 0u;
     const uint32_t* my = ent + ent_base[wg] + (exists ? where[bin] : 0u);
-    const uint32_t inv_k = k > 1 ? (uint32_t)(0x100000000ull / (uint32_t)k) : 0xFFFFFFFFu;   // the same for all lanes
-    auto label_of = [&](uint32_t e) -> uint32_t {   // e / k, at most one too low at first
-        uint32_t q = __umulhi(e, inv_k);
-        if (e - q * (uint32_t)k >= (uint32_t)k) ++q;
-        q -= (uint32_t)w * (uint32_t)cut.wl;
-        return KTOT == KT_BOTH4 ? unit_of_label<4>(q, (uint32_t)cut.wl) : q;
-    };
     const int n = (int)min(len, (uint32_t)cap);     // entries that get a register slot
     for (uint32_t p = (uint32_t)cap; p < len; ++p) {   // the others: to the list's part of the overflow list
         OvEntry o;
-        o.feature = (uint16_t)f; o.label = (uint16_t)label_of(my[p]); o.slot = my[p];
+        const uint32_t e = my[p];
+        o.feature = (uint16_t)f; o.label = (uint16_t)label_of(e);
+        o.slot = !small ? e : slot_at ? slot_at[ent_base[wg] + place_of(e)] : ent_base[wg] + place_of(e);
         ov[(size_t)ov_base[wg] + ov_off[bin] + (p - (uint32_t)cap)] = o;
-        if (pos) ovrk[(size_t)ov_base[wg] + ov_off[bin] + (p - (uint32_t)cap)] = pos[my[p]] - ent_base[wg];
+        if (pos) ovrk[(size_t)ov_base[wg] + ov_off[bin] + (p - (uint32_t)cap)] = place_of(e);
     }
     if (len > (uint32_t)cap && ((len - (uint32_t)cap) & 1u)) {   // an odd number: one empty place behind them
         OvEntry o;
@@ -1409,7 +1482,6 @@ static usl_status lf_build_t(usl_ctx* c, const int32_t* idx, int set, const Cut&
         for (int turn = 0; turn < 2; ++turn) {
             total = 0;
             share(&L.count, nbins * 4);
-            share(&L.taken, nbins * 4);
             share(&L.where, nbins * 4);
             share(&L.ovoff, nbins * 4);
             share(&L.feat, (size_t)nwg * 2 * NT * 2);
@@ -1425,45 +1497,53 @@ static usl_status lf_build_t(usl_ctx* c, const int32_t* idx, int set, const Cut&
             if (turn == 0) USL_TRY(usl_reserve(c, &L.mem, &L.mem_cap, total));
         }
     }
+    const bool own = set == 1 && both_own(Q, cut);
+    const uint32_t small_wg = Q == 2 ? both_places<2, false>() : own ? both_places<4, true>() : both_places<4, false>();
     const int rounds = usl_order_rounds(c);
     uint32_t* ov_base = L.ov_base;                   // [nwg + 1]
     uint32_t* n_ov = ov_base + nwg + 1;              // [nwg]
     uint32_t* ent_base = n_ov + nwg;                 // [nwg + 1]
     uint32_t* n_ent = ent_base + nwg + 1;            // [nwg]
-    const unsigned chunks = (unsigned)((cut.vd + CHUNK - 1) / CHUNK);
-    int splits = (int)((size_t)2 * c->num_cu / ((size_t)nwin * chunks));
-    splits = splits < 1 ? 1 : splits > 16 ? 16 : splits;
-    const dim3 grid((unsigned)((nwin * splits + 7) / 8 * 8), chunks);
-    const size_t lds = (size_t)(cut.vd < CHUNK ? cut.vd : CHUNK) * 4;
-    USL_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(k_lf_count), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    USL_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(k_lf_fill), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    const dim3 fillg(c->num_cu * 4), fillb(256);
-    hipLaunchKernelGGL(k_fill_u32, fillg, fillb, 0, c->stream, L.count, (size_t)(L.taken - L.count) + nbins, 0u);   // both: neighbours
-    hipLaunchKernelGGL(k_lf_count, grid, dim3(NT), lds, c->stream, idx, c->m, c->k, c->d, cut, splits, L.count);
-    hipLaunchKernelGGL(k_lf_plan<KT>, dim3((unsigned)nwg), dim3(NT), 0, c->stream, L.count, cut.vd, nfb, cut.fpb, L.where, L.ovoff,
-                       L.feat, L.caps, n_ent, n_ov, L.ovr);
-    USL_TRY(usl_idx_print_ready(c));
-    hipLaunchKernelGGL(k_lf_scan, dim3(3), dim3(1024), 0, c->stream, LfScan{{n_ov, n_ent}, {ov_base, ent_base}}, nwg,
-                       reinterpret_cast<const uint32_t*>(idx), N, c->idx_print, set == 1 ? USL_PRINT_BOTH_PRODUCTS : USL_PRINT_ONE_PRODUCT);
-    hipLaunchKernelGGL(k_lf_fill, grid, dim3(NT), lds, c->stream, idx, c->m, c->k, c->d, cut, splits, L.where, L.taken,
-                       ent_base, L.ent);
-    if (set == 1) {   // where the weight gradients go (before the order of the lists, which hands the places on)
-        const int nseg = lf_runs(c, cut);
-        const int64_t total = (int64_t)nwin * nseg;
-        uint32_t* segcnt = L.pos + rk_at(N) + (size_t)nwg * KT * NT + N + nbins;
-        const dim3 sg((unsigned)((total + 3) / 4));
-        if (nfb > 1) {   // (one block: the places are the flat slots)
-            hipLaunchKernelGGL(k_lf_seg_count, sg, dim3(256), 0, c->stream, idx, c->m, c->k, cut, nseg, total, segcnt);
-            hipLaunchKernelGGL(k_lf_seg_scan, dim3((unsigned)nwg), dim3(256), 0, c->stream, segcnt, nseg, ent_base);
-        }
-        hipLaunchKernelGGL(k_lf_seg_place, sg, dim3(256), 0, c->stream, idx, c->m, c->k, cut, nseg, total, segcnt, L.pos, L.slot);
+    const int nseg = lf_runs(c, cut);
+    const int64_t total = (int64_t)nwin * nseg;
+    // What only the building needs lies where the overflow entries come last: 8 bytes for every connection.
+    uint32_t* slot_at = L.slot;
+    uint16_t* feat_at = reinterpret_cast<uint16_t*>(L.ov);
+    uint32_t* segcnt = set == 1 ? L.pos + rk_at(N) + (size_t)nwg * KT * NT + N + nbins : nullptr;
+    if (set == 0) {
+        slot_at = reinterpret_cast<uint32_t*>(feat_at + (N + 1) / 2 * 2);
+        segcnt = slot_at + N;   // nwg * nseg words: fewer than N / 2 + nbins
     }
-    const bool own = set == 1 && both_own(Q, cut);
+    USL_TRY(usl_idx_print_ready(c));
+    const int print = set == 1 ? USL_PRINT_BOTH_PRODUCTS : USL_PRINT_ONE_PRODUCT;
+    if (nfb > 1) {
+        const dim3 sg((unsigned)((total + 31) / 32 * 8));
+        hipLaunchKernelGGL(k_lf_seg_count, sg, dim3(256), 0, c->stream, idx, c->m, c->k, cut, nseg, total, segcnt);
+        hipLaunchKernelGGL(k_lf_seg_scan, dim3((unsigned)nwg), dim3(256), 0, c->stream, segcnt, nseg, n_ent);
+        hipLaunchKernelGGL(k_lf_scan, dim3(1), dim3(1024), 0, c->stream, n_ent, ent_base, nwg, nullptr, (size_t)0, nullptr, 0);
+        hipLaunchKernelGGL(k_lf_seg_place, sg, dim3(256), 0, c->stream, idx, c->m, c->k, cut, nseg, total, segcnt, ent_base,
+                           set == 1 ? L.pos : nullptr, slot_at, feat_at);
+    }
+    LfPlaces places;
+    places.idx = idx;
+    places.slot_at = slot_at;
+    places.feat_at = feat_at;
+    places.pos = set == 1 ? L.pos : nullptr;
+    places.small_wg = set == 1 ? small_wg : 0;
+    // LDS for a quarter more connections than a workgroup has on average, as far as there is room (beside 14 KiB of other things)
+    const size_t mean = (size_t)cut.wl * c->k / nfb, want = mean + mean / 4 + 1024;
+    places.staged = (int)(want < LF_STAGED ? want : LF_STAGED);
+    const size_t lds = (size_t)places.staged * 4;
+    USL_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(k_lf_plan<KT>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL(k_lf_plan<KT>, dim3((unsigned)nwg), dim3(NT), lds, c->stream, places, c->m, c->k, c->d, cut, ent_base, L.count,
+                       L.where, L.ovoff, L.feat, L.caps, n_ov, L.ovr, L.ent);
+    hipLaunchKernelGGL(k_lf_scan, dim3(2), dim3(1024), 0, c->stream, n_ov, ov_base, nwg, reinterpret_cast<const uint32_t*>(idx), N,
+                       c->idx_print, print);
     const uint32_t zero_label = set == 0 ? ZERO_LABEL : Q == 2 ? BothLayout<2, false>::zero_label : own ? BothLayout<4, true>::zero_label : BothLayout<4, false>::zero_label;
 #define USL_LF_SCHED(GS)                                                                                                    \
     hipLaunchKernelGGL((k_lf_schedule<KT, GS>), dim3((unsigned)(nwg * 64 / (SG_NT / 32))), dim3(SG_NT), 0, c->stream, L.ent, \
                        ent_base, L.where, L.count, L.feat, L.caps, ov_base, L.ovoff, c->k, cut, zero_label, rounds,          \
-                       L.lab, set == 1 ? nullptr : L.slot, reinterpret_cast<OvEntry*>(L.ov), set == 1 ? L.pos : nullptr, Q == 2 ? both_places<2, false>() : own ? both_places<4, true>() : both_places<4, false>(),      \
+                       L.lab, set == 1 ? nullptr : L.slot, reinterpret_cast<OvEntry*>(L.ov), set == 1 ? L.pos : nullptr, nfb > 1 ? L.slot : nullptr, small_wg,                                 \
                        set == 1 ? L.pos + rk_at(N) : nullptr, set == 1 ? L.pos + rk_at(N) + (size_t)nwg * KT * NT : nullptr)
     if (Q == 4) USL_LF_SCHED(16);
     else USL_LF_SCHED(32);

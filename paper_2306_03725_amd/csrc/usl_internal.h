@@ -78,7 +78,6 @@ struct usl_ctx {
     struct usl_lf {
         void* mem;            size_t mem_cap;      // holds count .. pos
         uint32_t* count;                           // [nwin*d] list lengths
-        uint32_t* taken;                           // [nwin*d] positions handed out while filling
         uint32_t* where;                           // [nwin*d] where a feature's list starts among its workgroup's entries
         uint16_t* feat;                            // [wg][2][1024] feature of a lane's list
         uint32_t* caps;                            // [wg][16] slots the wavefronts visit
@@ -86,7 +85,7 @@ struct usl_ctx {
         uint32_t* ovr;                             // [wg][2][1024] a lane's lists' share of the overflow entries held in LDS
         uint16_t* lab;                             // [wg][slots / 8][1024][8] label within the window
         uint32_t* slot;                            // flat slot j*k+t (where the weight lives): [0] [wg][slots][1024]; [1] [m*k], by place
-        uint32_t* ent;                             // [m*k] flat slots grouped by (workgroup, feature), before the bank-aware order
+        uint32_t* ent;                             // [m*k] entries grouped by (workgroup, feature), before the bank-aware order (k_lf_plan)
         uint32_t* ovoff;                           // [nwin*d] where a list's overflow starts in its workgroup's
         void* ov;                                  // overflow entries
         float* stage;         size_t stage_cap;    // [1] only: per part of the batch the weight gradient by place, [m*k]; behind them per part
