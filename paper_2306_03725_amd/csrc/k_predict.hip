@@ -21,21 +21,42 @@ __device__ __forceinline__ uint64_t score_key(float z, uint32_t label) {
     return ((uint64_t)u << 32) | (uint64_t)(uint32_t)~label;
 }
 
-// Largest v of the workgroup, returned to every lane.  Two barriers: red may be reused right away.
-__device__ __forceinline__ uint64_t block_max(uint64_t v, uint64_t* red) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const uint64_t t = __shfl_xor((unsigned long long)v, o);
-        v = t > v ? t : v;
-    }
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    uint64_t r = red[0];
-#pragma unroll
-    for (int w = 1; w < TK_NT / 64; ++w) r = red[w] > r ? red[w] : r;
-    return r;
+// Largest v of the wavefront, the same register for all lanes.  What bounds these kernels is the chain of 2 kk such maxima; lane
+// shifts within the vector unit (rows of 16 lanes, then the last lane of a row into the next ones) do not wait for LDS as
+// shuffles do (one row of 500k scores, 5 labels: segments 7.5 and 6.3 us, merge 6.2 and 4.5).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t max_with(uint64_t v) {   // a lane without a source keeps its own
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)v, (int)(uint32_t)v, CTRL, ROWS, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(v >> 32), (int)(v >> 32), CTRL, ROWS, 0xF, false);
+    const uint64_t t = (uint64_t)hi << 32 | lo;
+    return t > v ? t : v;
 }
+__device__ __forceinline__ uint64_t wave_max(uint64_t v) {
+    v = max_with<0x111, 0xF>(v);   // row_shr:1, 2, 4, 8: lane 15 of a row has the row's largest
+    v = max_with<0x112, 0xF>(v);
+    v = max_with<0x114, 0xF>(v);
+    v = max_with<0x118, 0xF>(v);
+    v = max_with<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3, row_bcast:31 into rows 2 and 3
+    v = max_with<0x143, 0xC>(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63), hi = (uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), 63);
+    return (uint64_t)hi << 32 | lo;
+}
+// Largest v of the workgroup, returned to every lane.  red: two sets used in turn, so one barrier is enough.
+struct BlockMax {
+    uint64_t (*red)[TK_NT / 64];
+    int turn;
+    __device__ __forceinline__ uint64_t operator()(uint64_t v) {
+        v = wave_max(v);
+        uint64_t* set = red[turn];
+        turn ^= 1;
+        if ((threadIdx.x & 63) == 0) set[threadIdx.x >> 6] = v;
+        __syncthreads();
+        uint64_t r = set[0];
+#pragma unroll
+        for (int w = 1; w < TK_NT / 64; ++w) r = set[w] > r ? set[w] : r;
+        return r;
+    }
+};
 
 // The kk best keys of one segment of 256 * TK_EPT labels of one row, best first, into cand[row][segment][kk]
 // (0 where the segment has fewer than kk labels).
@@ -48,7 +69,8 @@ __device__ __forceinline__ uint64_t block_max(uint64_t v, uint64_t* red) {
 template <bool VEC, int TK_EPT>
 __global__ void __launch_bounds__(TK_NT)
 k_topk_segments(const float* __restrict__ out, int64_t m, int kk, int nseg, uint64_t* __restrict__ cand) {
-    __shared__ uint64_t red[TK_NT / 64];
+    __shared__ uint64_t red[2][TK_NT / 64];
+    BlockMax block_max = {red, 0};
     __shared__ uint64_t list[TK_MAX * TK_EPT];
     __shared__ uint32_t count;
     constexpr int TK_SEG = TK_NT * TK_EPT;   // labels per workgroup
@@ -87,7 +109,7 @@ k_topk_segments(const float* __restrict__ out, int64_t m, int kk, int nseg, uint
     }
     const uint64_t mine = top_j >= 0 ? score_key(top, (uint32_t)(seg0 + top_j)) : 0ull;
     uint64_t tau = ~0ull;
-    for (int r = 0; r < kk && tau != 0; ++r) tau = block_max(mine < tau ? mine : 0ull, red);
+    for (int r = 0; r < kk && tau != 0; ++r) tau = block_max(mine < tau ? mine : 0ull);
     if (threadIdx.x == 0) count = 0;
     __syncthreads();
     // keys are built only for scores that reach tau's score (a cheap float test first)
@@ -111,19 +133,20 @@ k_topk_segments(const float* __restrict__ out, int64_t m, int kk, int nseg, uint
             const uint64_t key = list[q];
             if (key < prev && key > best) best = key;
         }
-        prev = block_max(best, red);
+        prev = block_max(best);
         if (threadIdx.x == 0) dst[r] = prev;
     }
 }
 
 // One workgroup per row: the best kk of the row's nseg*kk candidate keys, unpacked.  The score is read
 // back from out so that it keeps its own bits (a -0 stays -0).  A launch of its own: merged by the workgroup
-// that finishes a row's last segment, one row of 500k scores took 14.6 us instead of 7.5 + 5.2 (the
+// that finishes a row's last segment, one row of 500k scores took 14.6 us when the two launches took 7.5 + 5.2 (the
 // candidates then have to be made visible across the L2s by every workgroup).
 __global__ void __launch_bounds__(TK_NT)
 k_topk_merge(const uint64_t* __restrict__ cand, int n, int kk, const float* __restrict__ out, int64_t m,
              int32_t* __restrict__ top_lab, float* __restrict__ top_val) {
-    __shared__ uint64_t red[TK_NT / 64];
+    __shared__ uint64_t red[2][TK_NT / 64];
+    BlockMax block_max = {red, 0};
     const uint64_t* c = cand + (size_t)blockIdx.x * n;
     constexpr int HELD = 8;   // candidates a lane keeps in registers; only very wide rows have more
     uint64_t mine[HELD];
@@ -139,7 +162,7 @@ k_topk_merge(const uint64_t* __restrict__ cand, int n, int kk, const float* __re
             const uint64_t key = c[q];
             if (key < prev && key > best) best = key;
         }
-        prev = block_max(best, red);
+        prev = block_max(best);
         if ((int)threadIdx.x == r) {   // a lane per rank: the reads of the scores do not wait for each other
             const uint32_t label = ~(uint32_t)prev;
             top_lab[(size_t)blockIdx.x * kk + r] = (int32_t)label;
