@@ -167,6 +167,10 @@ k_interleave(const TS* __restrict__ x, TS* __restrict__ xi, int b, int d, int co
     *reinterpret_cast<U*>(to) = u;
 }
 
+// v of another lane: a permutation within 16 lanes by the vector unit
+template <int CTRL>
+__device__ __forceinline__ float moved(float v) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true)); }
+
 // ---- forward of one group of instances (b <= Q) ----------------------------------------------------------------
 // With one row of activations nothing is reused, and bringing idx and W into registers label by label only delays them:
 // here they stream.  A lane takes four neighbouring slots (16 bytes of idx, 16 or 8 of W, coalesced), gathers their
@@ -175,7 +179,9 @@ k_interleave(const TS* __restrict__ x, TS* __restrict__ xi, int b, int d, int co
 // and W: m = 500k, k = 32, b = 1: 128 MB in 21.6 us, 5.9 TB/s (29.6 us label by label).  Not for rows that exceed LDS (gathers
 // from L2 instead took 498 us at m = 3M, d = 65536, where the two halves of the label-by-label form take about 300).
 // VEC: k is a multiple of 4.
-template <int LPL, typename TS, int Q, bool VEC>
+// AHEAD: rounds in flight, a divisor of `rounds`.  Four where there is one instance (four spill where there are four): with two,
+// and the sums of a label's lanes through LDS, the scores of m = 500k took 0.8 us longer.
+template <int LPL, typename TS, int Q, bool VEC, int AHEAD>
 __global__ void __launch_bounds__(1024)
 k_forward_few(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS* __restrict__ W, float* __restrict__ out,
               int64_t m, int k, int b, int row_bytes, int rounds) {
@@ -251,7 +257,6 @@ k_forward_few(const char* __restrict__ xi, const int32_t* __restrict__ idx, cons
             }
         }
     };
-    constexpr int AHEAD = 2;   // rounds in flight (four spill where Q = 4)
     Piece p[AHEAD];
     const int per = rounds * (64 / LPL);   // labels of a wavefront's turn
     if (w0 * per < m) {
@@ -273,9 +278,11 @@ k_forward_few(const char* __restrict__ xi, const int32_t* __restrict__ idx, cons
                 if (r + AHEAD < rounds) fetch(j0, r + AHEAD, p[a]);
                 else fetch(jn, a, p[a]);
 #pragma unroll
-                for (int o = 1; o < LPL; o <<= 1) {
-#pragma unroll
-                    for (int i = 0; i < Q; ++i) acc[i] += __shfl_xor(acc[i], o);
+                for (int i = 0; i < Q; ++i) {   // (lanes that have been added up are alike: a mirror reaches the others as well)
+                    if (LPL > 1) acc[i] += moved<0xB1>(acc[i]);    // quads 1 0 3 2
+                    if (LPL > 2) acc[i] += moved<0x4E>(acc[i]);    // quads 2 3 0 1
+                    if (LPL > 4) acc[i] += moved<0x141>(acc[i]);   // 8 lanes, mirrored
+                    if (LPL > 8) acc[i] += moved<0x140>(acc[i]);   // 16
                 }
 #pragma unroll
                 for (int i = 0; i < Q; ++i) sum[i] = sub == r ? acc[i] : sum[i];
@@ -626,11 +633,16 @@ usl_status run_forward_few(usl_ctx* c, const Layout& L, const void* x, const int
     const int by_lds = (int)((size_t)(160 * 1024) / lds), resident = by_lds < 32 / nw ? (by_lds < 1 ? 1 : by_lds) : 32 / nw;
     const unsigned grid = (unsigned)(blocks < (int64_t)c->num_cu * resident ? blocks : (int64_t)c->num_cu * resident);
     const bool vec = c->k % 4 == 0;
+#define USL_FEW_A(LPL, TS, Q, VEC, AHEAD)                                                                           \
+    do {                                                                                                                \
+        USL_TRY(allow_lds(c, k_forward_few<LPL, TS, Q, VEC, AHEAD>, lds));                                          \
+        hipLaunchKernelGGL((k_forward_few<LPL, TS, Q, VEC, AHEAD>), dim3(grid), dim3((unsigned)nw * 64), lds, c->stream,              \
+                           (const char*)xi, idx, (const TS*)W, out, c->m, c->k, b, L.row_bytes, rounds);                \
+    } while (0)
 #define USL_FEW(LPL, TS, Q, VEC)                                                                                    \
     do {                                                                                                                \
-        USL_TRY(allow_lds(c, k_forward_few<LPL, TS, Q, VEC>, lds));                                                 \
-        hipLaunchKernelGGL((k_forward_few<LPL, TS, Q, VEC>), dim3(grid), dim3((unsigned)nw * 64), lds, c->stream,              \
-                           (const char*)xi, idx, (const TS*)W, out, c->m, c->k, b, L.row_bytes, rounds);                \
+        if (Q == 1 && LPL >= 4 && rounds >= 4) USL_FEW_A(LPL, TS, Q, VEC, (Q == 1 && LPL >= 4 ? 4 : 2));            \
+        else USL_FEW_A(LPL, TS, Q, VEC, 2);                                                                         \
     } while (0)
 #define USL_FEW_V(LPL, TS, Q) do { if (vec) USL_FEW(LPL, TS, Q, true); else USL_FEW(LPL, TS, Q, false); } while (0)
 #define USL_FEW_L(TS, Q)                                                                                            \
@@ -652,6 +664,7 @@ usl_status run_forward_few(usl_ctx* c, const Layout& L, const void* x, const int
 #undef USL_FEW_L
 #undef USL_FEW_V
 #undef USL_FEW
+#undef USL_FEW_A
     return usl_check_launch(c, "forward (one group)");
 }
 

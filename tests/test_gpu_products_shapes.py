@@ -93,3 +93,12 @@ def test_products_with_one_label_a_lane_in_wide_workgroups(orc, m, d, k, b, stor
     monkeypatch.setenv("USL_TUNE_SPLIT", str(split))
     print("products", m, d, k, b, storage, split, flush=True)
     compare(orc, gu, wl.custom(m, d, k, b, storage=storage, positives=1, index=840 + split), m, d, k, b, storage)
+
+
+@pytest.mark.parametrize("m,d,k,b,storage", [(262145, 300, 12, 1, "f32"), (262144, 40000, 13, 1, "bf16"), (140000, 1000, 30, 1, "f32"), (131073, 30000, 64, 1, "bf16"),
+                                             (70001, 500, 49, 1, "f32")])
+def test_scores_of_one_instance_over_many_labels(orc, m, d, k, b, storage):
+    """Enough labels for four rounds in flight, 4 to 16 lanes to a label."""
+    import gpu_util as gu
+    print("products", m, d, k, b, storage, flush=True)
+    compare(orc, gu, wl.custom(m, d, k, b, storage=storage, positives=1, index=850), m, d, k, b, storage)
