@@ -1380,16 +1380,19 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
 // grad_x[i][c] = sum over the windows (chains of them, in the kernel for both products) of partial[w][i][c], i < rows; a row of partial is dp floats (d rounded up to a
 // multiple of 4).  BOTH only names the kernel after the one whose sums it adds, so that a profile tells the two apart.
 // vec: rows of grad_x are 16-byte aligned too.
+// Bound by the stream of the partial sums, so eight windows' loads go out together (one after the other, and the rows from the
+// first: 11.0 us at m = 31k, d = 1k, b = 128, now 5.6; m = 200k, d = 8k, b = 64: 28.5 and 23.3; m = 500k, d = 32k, b = 256, 537 MB: 120 and 116).
 template <bool BOTH>
 __global__ void __launch_bounds__(256)
 k_lf_reduce(const float4* __restrict__ partial, int nwin, size_t n4, int d, int dp, bool vec, float* __restrict__ out,
             const uint32_t* __restrict__ gate, const uint32_t* __restrict__ stale) {
     if (gate && *gate == 0) return;
     const bool poison = *stale != 0;   // the lists were built from other contents of idx: no number is better than a wrong one
-    size_t v = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const size_t step = (size_t)gridDim.x * blockDim.x;
-    for (; v < n4; v += step) {
+    for (size_t u = (size_t)blockIdx.x * blockDim.x + threadIdx.x; u < n4; u += step) {
+        const size_t v = n4 - 1 - u;   // the last rows first: they were written last, and may still be in a cache
         float4 a = partial[v];
+#pragma unroll 8
         for (int q = 1; q < nwin; ++q) {
             const float4 t = partial[(size_t)q * n4 + v];
             a.x += t.x; a.y += t.y; a.z += t.z; a.w += t.w;
