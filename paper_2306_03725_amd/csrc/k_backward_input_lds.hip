@@ -995,7 +995,9 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
     OvEntry o = {0, 0, PAD_SLOT};
     if (lane < min((uint32_t)NEAR2, ov_n)) o = ov[(size_t)ov0 + lane];
     __builtin_amdgcn_sched_barrier(0);
-    // the weights of the first N * NT places: float32 ones by LDS-DMA, a lane's own address each and no registers
+    // The weights of the first N * NT places: float32 ones by LDS-DMA, a lane's own address each and no registers.  The weight of
+    // the lane's overflow entry goes out with them: behind them it was another trip to memory.
+    TS ov_raw = (TS)0;
     auto bring = [&](auto N_) {
         constexpr int N = decltype(N_)::value;
         const uint32_t n_bytes = min(n_ent, CH) * 4;
@@ -1009,6 +1011,8 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
 #pragma unroll
             for (int u = 0; u < N; ++u) sl[u] = e0 + min(at + (uint32_t)(u * NT * 4), n_bytes - 4) / 4;
         }
+        __builtin_amdgcn_sched_barrier(0);
+        if (ov_n) ov_raw = W_window[o.slot != PAD_SLOT ? o.slot - first_slot : 0u];
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (sizeof(TS) == 4) {
 #pragma unroll
@@ -1037,7 +1041,8 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
     __syncthreads();   // LDS is free
     if (one_go && n_ent > 8 * NT) bring(std::integral_constant<int, ((int)CH + NT - 1) / NT>{});
     else if (one_go && n_ent > 0) bring(std::integral_constant<int, 8>{});
-    const float ov_weight = o.slot != PAD_SLOT ? usl_to_f32(W_window[o.slot - first_slot]) : 0.f;
+    else if (ov_n) ov_raw = W_window[o.slot != PAD_SLOT ? o.slot - first_slot : 0u];
+    const float ov_weight = o.slot != PAD_SLOT ? usl_to_f32(ov_raw) : 0.f;
     const int acap = __builtin_amdgcn_readfirstlane((int)(cw & 0xFFu)), bcap = __builtin_amdgcn_readfirstlane((int)(cw >> 8));
     // (a skewed connectivity: one by one, and the places are just the lane's slots)
     auto own_places = [&](uint32_t (&places)[KT / 2]) {
