@@ -40,17 +40,23 @@ __global__ void k_philox(const uint32_t* __restrict__ ctr, uint32_t k0, uint32_t
 }
 
 // ---- radix select ---------------------------------------------------------------------------
-constexpr int SEL_BINS = 2048;
-// device state: [0..SEL_BINS) histogram, then: prefix, remaining count, (unused), tie total
+constexpr int SEL_BINS = 2048, SEL_NT = 1024;
+// device state: [0..SEL_BINS) histogram, then: prefix, remaining count, (unused), keys in the bin picked last
 enum { ST_PREFIX = SEL_BINS, ST_REMAIN = SEL_BINS + 1, ST_TIES = SEL_BINS + 3, ST_WORDS = SEL_BINS + 4 };
 
-template <typename TS> __device__ __forceinline__ uint32_t mag_key(const TS* W, size_t f);
-template <> __device__ __forceinline__ uint32_t mag_key<float>(const float* W, size_t f) {
-    return __float_as_uint(W[f]) & 0x7FFFFFFFu;
+__device__ __forceinline__ uint32_t mag_of(float v) { return __float_as_uint(v) & 0x7FFFFFFFu; }
+__device__ __forceinline__ uint32_t mag_of(uint16_t v) { return (uint32_t)v & 0x7FFFu; }
+template <typename TS> __device__ __forceinline__ uint32_t mag_key(const TS* W, size_t f) { return mag_of(W[f]); }
+// 16 bytes of W, at any element
+template <typename TS> struct Piece {
+    static constexpr int N = 16 / sizeof(TS);
+    typedef TS T __attribute__((ext_vector_type(N), aligned(sizeof(TS))));
+};
+template <typename TS> __device__ __forceinline__ typename Piece<TS>::T piece_at(const TS* W, size_t f) {
+    return *reinterpret_cast<const typename Piece<TS>::T*>(W + f);
 }
-template <> __device__ __forceinline__ uint32_t mag_key<uint16_t>(const uint16_t* W, size_t f) {
-    return (uint32_t)W[f] & 0x7FFFu;
-}
+// Do all keys equal to the threshold go?  (float32: nearly always, there is one.)  Nobody has to count them in order then.
+__device__ __forceinline__ bool all_ties_go(const uint32_t* st) { return st[ST_TIES] == st[ST_REMAIN]; }
 
 __global__ void k_sel_init(uint32_t* st, uint32_t n) {
     for (int i = threadIdx.x; i < ST_WORDS; i += blockDim.x) st[i] = 0;
@@ -60,20 +66,35 @@ __global__ void k_sel_init(uint32_t* st, uint32_t n) {
 
 // histogram of digit (key >> shift) & (2^bits - 1) over the keys whose higher bits equal the prefix
 template <typename TS>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(SEL_NT)
 k_sel_hist(const TS* __restrict__ W, size_t N, uint32_t* st, int shift, int bits, int first) {
     __shared__ uint32_t h[SEL_BINS];
-    for (int i = threadIdx.x; i < SEL_BINS; i += 256) h[i] = 0;
+    for (int i = threadIdx.x; i < SEL_BINS; i += SEL_NT) h[i] = 0;
     __syncthreads();
     const uint32_t prefix = st[ST_PREFIX];
     const uint32_t mask = (1u << bits) - 1u;
-    const size_t stride = (size_t)gridDim.x * 256;
-    for (size_t f = (size_t)blockIdx.x * 256 + threadIdx.x; f < N; f += stride) {
-        const uint32_t key = mag_key<TS>(W, f);
+    constexpr int V = Piece<TS>::N;
+    auto one = [&](TS v) {
+        const uint32_t key = mag_of(v);
         if (first || (key >> (shift + bits)) == prefix) atomicAdd(&h[(key >> shift) & mask], 1u);
+    };
+    // 16 bytes a load, four of a lane's in flight (one value a load and 2048 workgroups of 256 lanes, see the launch: 56, 35 and 35 us for the three
+    // digits of 16 million float32 weights, now 21, 14 and 14)
+    const size_t stride = (size_t)gridDim.x * SEL_NT, pieces = N / V;
+    for (size_t q = (size_t)blockIdx.x * SEL_NT + threadIdx.x; q < pieces; q += 4 * stride) {
+        typename Piece<TS>::T v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = piece_at(W, min(q + u * stride, pieces - 1) * V);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (q + u * stride >= pieces) continue;
+#pragma unroll
+            for (int e = 0; e < V; ++e) one(v[u][e]);
+        }
     }
+    if (blockIdx.x == 0 && threadIdx.x < N - pieces * V) one(W[pieces * V + threadIdx.x]);
     __syncthreads();
-    for (int i = threadIdx.x; i < SEL_BINS; i += 256)
+    for (int i = threadIdx.x; i < SEL_BINS; i += SEL_NT)
         if (h[i]) atomicAdd(&st[i], h[i]);
 }
 
@@ -103,11 +124,13 @@ __global__ void __launch_bounds__(256) k_sel_pick(uint32_t* st, int bits) {
     if (before < remain && before + mine >= remain) {
         uint32_t cum = before;
         int bin = first;
+        uint32_t hcount = 0;
         for (int q = 0; q < per; ++q) {
-            const uint32_t hcount = st[first + q];
+            hcount = st[first + q];
             if (cum + hcount >= remain) { bin = first + q; break; }
             cum += hcount;
         }
+        st[ST_TIES] = hcount;
         st[ST_PREFIX] = (prefix << bits) | (uint32_t)bin;
         st[ST_REMAIN] = remain - cum;  // = how many keys equal to the final prefix must go
     } else if (threadIdx.x == 0 && total < remain) {   // cannot happen for a consistent histogram
@@ -118,20 +141,44 @@ __global__ void __launch_bounds__(256) k_sel_pick(uint32_t* st, int bits) {
     for (int i = threadIdx.x; i < SEL_BINS; i += blockDim.x) st[i] = 0;
 }
 
+// A workgroup of the two kernels below has MARK_CHUNK values: pieces of 16 bytes, lane by lane, MARK_PIECES<TS> of them a lane.
 constexpr int MARK_NT = 256;
-constexpr int MARK_PER = 16;
-constexpr int MARK_CHUNK = MARK_NT * MARK_PER;
+constexpr int MARK_CHUNK = 4096;
+template <typename TS> constexpr int MARK_PIECES = MARK_CHUNK / MARK_NT / Piece<TS>::N;
+
+// the lane's keys; 0xFFFFFFFF behind the last one
+template <typename TS>
+__device__ __forceinline__ void mark_keys(const TS* __restrict__ W, size_t N, uint32_t (&keys)[MARK_PIECES<TS>][Piece<TS>::N]) {
+    constexpr int V = Piece<TS>::N;
+    const size_t f0 = (size_t)blockIdx.x * MARK_CHUNK + (size_t)threadIdx.x * V;
+    typename Piece<TS>::T v[MARK_PIECES<TS>];
+#pragma unroll
+    for (int u = 0; u < MARK_PIECES<TS>; ++u) {
+        const size_t f = f0 + (size_t)u * MARK_NT * V;
+        if (f + V <= N) v[u] = piece_at(W, f);
+        else
+#pragma unroll
+            for (int e = 0; e < V; ++e) v[u][e] = f + e < N ? W[f + e] : (TS)0;
+    }
+#pragma unroll
+    for (int u = 0; u < MARK_PIECES<TS>; ++u)
+#pragma unroll
+        for (int e = 0; e < V; ++e) keys[u][e] = f0 + (size_t)u * MARK_NT * V + e < N ? mag_of((TS)v[u][e]) : 0xFFFFFFFFu;
+}
 
 template <typename TS>
 __global__ void __launch_bounds__(MARK_NT)
 k_tie_count(const TS* __restrict__ W, size_t N, const uint32_t* __restrict__ st,
             uint32_t* __restrict__ tie_counts) {
     __shared__ uint32_t red[MARK_NT / 64];
+    if (all_ties_go(st)) return;
     const uint32_t T = st[ST_PREFIX];
-    const size_t f0 = (size_t)blockIdx.x * MARK_CHUNK + (size_t)threadIdx.x * MARK_PER;
-    uint32_t cnt = 0;
-    for (int q = 0; q < MARK_PER; ++q)
-        if (f0 + q < N && mag_key<TS>(W, f0 + q) == T) ++cnt;
+    uint32_t keys[MARK_PIECES<TS>][Piece<TS>::N], cnt = 0;
+    mark_keys(W, N, keys);
+#pragma unroll
+    for (int u = 0; u < MARK_PIECES<TS>; ++u)
+#pragma unroll
+        for (int e = 0; e < Piece<TS>::N; ++e) cnt += keys[u][e] == T;
     for (int o = 32; o > 0; o >>= 1) cnt += __shfl_down(cnt, o);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = cnt;
     __syncthreads();
@@ -143,8 +190,9 @@ k_tie_count(const TS* __restrict__ W, size_t N, const uint32_t* __restrict__ st,
 }
 
 // exclusive scan of the per-block tie counts, in place (one block)
-__global__ void __launch_bounds__(1024) k_tie_scan(uint32_t* tie_counts, size_t nblk) {
+__global__ void __launch_bounds__(1024) k_tie_scan(uint32_t* tie_counts, size_t nblk, const uint32_t* __restrict__ st) {
     __shared__ uint32_t part[1024];
+    if (all_ties_go(st)) return;
     const size_t per = (nblk + 1023) / 1024;
     const size_t a = threadIdx.x * per, e = min(nblk, a + per);
     uint32_t s = 0;
@@ -160,41 +208,67 @@ __global__ void __launch_bounds__(1024) k_tie_scan(uint32_t* tie_counts, size_t 
     for (size_t q = a; q < e; ++q) { const uint32_t v = tie_counts[q]; tie_counts[q] = run; run += v; }
 }
 
-// flags every removed slot and resets its value and moments
+// Flags every removed slot and resets its value and moments.  Bound by the lines of the values that it resets.  (Sixteen
+// neighbouring values to a lane, a load each, and the ties counted whatever their number took 77 us behind 52 for the counts at
+// m = 500k, k = 32, 5 %; now 41 behind 9.)
 template <typename TS>
 __global__ void __launch_bounds__(MARK_NT)
 k_mark(TS* __restrict__ W, float* __restrict__ m1, float* __restrict__ m2, size_t N,
        const uint32_t* __restrict__ st, const uint32_t* __restrict__ tie_off,
        uint8_t* __restrict__ flags) {
-    __shared__ uint32_t scan[MARK_NT];
+    constexpr int V = Piece<TS>::N, P = MARK_PIECES<TS>;
+    __shared__ uint32_t ties[P][MARK_NT / 64];
     const uint32_t T = st[ST_PREFIX], q_take = st[ST_REMAIN];
-    const size_t f0 = (size_t)blockIdx.x * MARK_CHUNK + (size_t)threadIdx.x * MARK_PER;
-    uint32_t keys[MARK_PER];
-    uint32_t mine = 0;
+    const bool all = all_ties_go(st);
+    const size_t f0 = (size_t)blockIdx.x * MARK_CHUNK + (size_t)threadIdx.x * V;
+    uint32_t keys[P][V];
+    mark_keys<TS>(W, N, keys);
+    uint32_t rank[P] = {};   // of the first tie of the lane's piece, in flat order
+    if (!all) {
 #pragma unroll
-    for (int q = 0; q < MARK_PER; ++q) {
-        keys[q] = f0 + q < N ? mag_key<TS>(W, f0 + q) : 0xFFFFFFFFu;
-        mine += keys[q] == T;
-    }
-    scan[threadIdx.x] = mine;
-    __syncthreads();
-    for (int o = 1; o < MARK_NT; o <<= 1) {  // inclusive scan of the per-lane tie counts
-        const uint32_t v = threadIdx.x >= (unsigned)o ? scan[threadIdx.x - o] : 0u;
-        __syncthreads();
-        scan[threadIdx.x] += v;
-        __syncthreads();
-    }
-    uint32_t rank = tie_off[blockIdx.x] + scan[threadIdx.x] - mine;
+        for (int u = 0; u < P; ++u) {
+            uint32_t mine = 0;
 #pragma unroll
-    for (int q = 0; q < MARK_PER; ++q) {
-        if (f0 + q >= N) break;
-        bool gone = keys[q] < T;
-        if (keys[q] == T) { gone = rank < q_take; ++rank; }
-        flags[f0 + q] = gone ? 1 : 0;
-        if (gone) {
-            W[f0 + q] = (TS)0;
-            m1[f0 + q] = 0.f;
-            m2[f0 + q] = 0.f;
+            for (int e = 0; e < V; ++e) mine += keys[u][e] == T;
+            uint32_t upto = mine;
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t t = __shfl_up(upto, o);
+                if ((int)(threadIdx.x & 63) >= o) upto += t;
+            }
+            if ((threadIdx.x & 63) == 63) ties[u][threadIdx.x >> 6] = upto;
+            rank[u] = upto - mine;
+        }
+        __syncthreads();
+        uint32_t before = tie_off[blockIdx.x];
+#pragma unroll
+        for (int u = 0; u < P; ++u)
+#pragma unroll
+            for (int w = 0; w < MARK_NT / 64; ++w) {
+                if (w == (int)(threadIdx.x >> 6)) rank[u] += before;
+                before += ties[u][w];
+            }
+    }
+#pragma unroll
+    for (int u = 0; u < P; ++u) {
+        const size_t f = f0 + (size_t)u * MARK_NT * V;
+        uint32_t gone[V / 4] = {};   // a byte per value
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            bool g = keys[u][e] < T;
+            if (keys[u][e] == T) { g = all || rank[u] < q_take; ++rank[u]; }
+            gone[e / 4] |= (g ? 1u : 0u) << (8 * (e % 4));
+            if (g && f + e < N) {
+                W[f + e] = (TS)0;
+                m1[f + e] = 0.f;
+                m2[f + e] = 0.f;
+            }
+        }
+        if (f + V <= N) {
+#pragma unroll
+            for (int q = 0; q < V / 4; ++q) *reinterpret_cast<uint32_t*>(flags + f + 4 * q) = gone[q];   // (flags is this library's own, f a multiple of 4)
+        } else {
+            for (int e = 0; e < V; ++e)
+                if (f + e < N) flags[f + e] = (uint8_t)(gone[e / 4] >> (8 * (e % 4)));
         }
     }
 }
@@ -250,39 +324,89 @@ k_mark_rows_serial(TS* __restrict__ W, float* __restrict__ m1, float* __restrict
 // ---- regrow ---------------------------------------------------------------------------------
 // GS lanes own one row (GS = power of two >= k, <= 64); lane t of the group holds slot t.
 // flags == nullptr means every slot is empty (initial connectivity).
+// What bounds this is the vector unit.  The first candidates of all empty slots are drawn together, by as many lanes as there are
+// such slots in RG_TURNS turns of a wavefront's rows, and compared in one short loop; where two columns of a row clash, which is
+// rare, the turn goes slot by slot, drawing on.  Slot by slot from the beginning, each candidate drawn by the whole group, took
+// 118 us at m = 500k, k = 32, 5 % empty; now 67.
+constexpr int RG_TURNS = 8;
+template <int GS> struct RowMask { typedef uint32_t T; };   // a bit per slot
+template <> struct RowMask<64> { typedef uint64_t T; };
 template <int GS>
 __global__ void __launch_bounds__(256)
 k_regrow(int32_t* __restrict__ idx, const uint8_t* __restrict__ flags, int64_t m, uint32_t d, int k,
          uint32_t k0, uint32_t k1, uint32_t epoch_lo) {
-    const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t row = gid / GS;
-    const int t = (int)(gid % GS);
-    const int lane = threadIdx.x & 63;
+    __shared__ uint32_t list[4][RG_TURNS * 64];   // turn * 64 + lane of the empty slots, then their first candidates
+    const int lane = threadIdx.x & 63, t = lane & (GS - 1);
+    uint32_t* const mine_of = list[threadIdx.x >> 6];
     const int gshift = lane & ~(GS - 1);
-    const uint64_t gmask = GS == 64 ? ~0ull : ((1ull << GS) - 1ull);
-    const bool active = row < m && t < k;
-    const size_t f = (size_t)row * k + t;
-    bool empty = active && (flags ? flags[f] != 0 : true);
-    bool occupied = active && !empty;
-    int32_t mine = occupied ? idx[f] : -1;
-    const bool was_empty = empty;
-    uint64_t todo = (__ballot(empty) >> gshift) & gmask;  // empty slots of my row, bit = slot
-    uint32_t attempt = 0;
-    while (__any(todo != 0)) {
-        const int ts = todo ? __ffsll((unsigned long long)todo) - 1 : 0;
-        const int32_t c = todo ? draw_column(k0, k1, epoch_lo, (uint32_t)row, (uint32_t)ts, attempt, d) : -2;
-        const uint64_t clash = (__ballot(todo != 0 && occupied && mine == c) >> gshift) & gmask;
-        if (todo) {
-            if (clash == 0) {
-                if (t == ts) { mine = c; occupied = true; }
-                todo &= todo - 1;
-                attempt = 0;
-            } else {
-                ++attempt;
+    typedef typename RowMask<GS>::T Mask;
+    const Mask gmask = GS >= 32 ? (Mask)~(Mask)0 : (Mask)((1u << (GS & 31)) - 1u);
+    const uint64_t below = (1ull << lane) - 1ull;
+    auto of_row = [&](uint64_t ballot) { return (Mask)(ballot >> gshift) & gmask; };
+    auto lowest = [&](Mask v) { return GS == 64 ? __ffsll((unsigned long long)v) - 1 : __ffs((int)v) - 1; };   // -1: none
+    const int64_t row0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * (RG_TURNS * 64 / GS);   // the wavefront's first
+    auto row_of = [&](int turn, int l) { return row0 + turn * (64 / GS) + l / GS; };
+    uint64_t empty[RG_TURNS];    // of the turn's lanes
+    int32_t mine[RG_TURNS];
+    uint32_t first[RG_TURNS], n = 0;
+    bool is[RG_TURNS];
+#pragma unroll
+    for (int r = 0; r < RG_TURNS; ++r) is[r] = row_of(r, lane) < m && t < k && (flags ? flags[(size_t)row_of(r, lane) * k + t] != 0 : true);
+#pragma unroll
+    for (int r = 0; r < RG_TURNS; ++r) {
+        empty[r] = __ballot(is[r]);
+        first[r] = n;
+        if (is[r]) mine_of[n + (uint32_t)__popcll(empty[r] & below)] = (uint32_t)(r * 64 + lane);
+        n += (uint32_t)__popcll(empty[r]);
+        mine[r] = -1;   // (nobody asks for the columns of a full row)
+        if (!is[r] && row_of(r, lane) < m && t < k && of_row(empty[r]) != 0) mine[r] = idx[(size_t)row_of(r, lane) * k + t];
+    }
+    __syncthreads();
+    for (uint32_t q = (uint32_t)lane; q < n; q += 64) {
+        const uint32_t e = mine_of[q];
+        mine_of[q] = (uint32_t)draw_column(k0, k1, epoch_lo, (uint32_t)row_of((int)(e / 64), (int)(e % 64)), e % GS, 0u, d);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < RG_TURNS; ++r) {
+        const int64_t row = row_of(r, lane);
+        const int32_t own = is[r] ? (int32_t)mine_of[first[r] + (uint32_t)__popcll(empty[r] & below)] : 0;
+        Mask todo = of_row(empty[r]);   // empty slots of my row, bit = slot
+        {
+            const int32_t have = is[r] ? own : mine[r];
+            bool clash = false;
+            for (Mask rest = todo; __any(rest != 0); rest &= rest - 1) {
+                const int ts = lowest(rest);
+                const int32_t c = __shfl(own, gshift + (ts & (GS - 1)));
+                clash = clash || (rest != 0 && have == c && t != ts);
+            }
+            if (!__any(clash)) {
+                if (is[r]) idx[(size_t)row * k + t] = own;
+                continue;
             }
         }
+        bool occupied = mine[r] >= 0;
+        uint32_t attempt = 0;
+        while (__any(todo != 0)) {
+            const int ts = todo ? lowest(todo) : 0;
+            int32_t c = __shfl(own, gshift + ts);
+            if (__any(attempt != 0)) {
+                const int32_t next = draw_column(k0, k1, epoch_lo, (uint32_t)row, (uint32_t)ts, attempt, d);
+                if (attempt != 0) c = next;
+            }
+            const Mask clash = of_row(__ballot(todo != 0 && occupied && mine[r] == c));
+            if (todo) {
+                if (clash == 0) {
+                    if (t == ts) { mine[r] = c; occupied = true; }
+                    todo &= todo - 1;
+                    attempt = 0;
+                } else {
+                    ++attempt;
+                }
+            }
+        }
+        if (is[r]) idx[(size_t)row * k + t] = mine[r];
     }
-    if (was_empty) idx[f] = mine;
 }
 
 // any k: one thread per row, row kept in global memory
@@ -343,7 +467,7 @@ usl_status regrow(usl_ctx* c, int32_t* idx, uint8_t* flags, bool all_empty, uint
     while (gs < k) gs <<= 1;
     const uint8_t* fl = all_empty ? nullptr : flags;
     const int64_t lanes = c->m * gs;
-    const unsigned grid = (unsigned)((lanes + 255) / 256);
+    const unsigned grid = (unsigned)((lanes + 256 * RG_TURNS - 1) / (256 * RG_TURNS));
 #define USL_RG(GS)                                                                             \
     hipLaunchKernelGGL(k_regrow<GS>, dim3(grid), dim3(256), 0, c->stream, idx, fl, c->m,       \
                        (uint32_t)c->d, k, k0, k1, elo)
@@ -386,17 +510,19 @@ usl_status redistribute_t(usl_ctx* c, int32_t* idx, TS* W, float* m1, float* m2,
     const int npass = sizeof(TS) == 4 ? 3 : 2;
     const int* bits = sizeof(TS) == 4 ? f32_bits : bf_bits;
     int shift = sizeof(TS) == 4 ? 31 : 15;
-    size_t hblocks = (N + 256 * 16 - 1) / (256 * 16);
-    if (hblocks > (size_t)c->num_cu * 8) hblocks = (size_t)c->num_cu * 8;
+    // few and large workgroups: each of them adds its bins to the same few words (four times as many of a quarter of the lanes:
+    // 49, 31 and 31 us for the three digits of 16 million float32 weights, against 21, 14 and 14)
+    size_t hblocks = (N + SEL_NT * 16 - 1) / (SEL_NT * 16);
+    if (hblocks > (size_t)c->num_cu * 2) hblocks = (size_t)c->num_cu * 2;
     for (int p = 0; p < npass; ++p) {
         shift -= bits[p];
-        hipLaunchKernelGGL(k_sel_hist<TS>, dim3((unsigned)hblocks), dim3(256), 0, c->stream, W, N, st,
+        hipLaunchKernelGGL(k_sel_hist<TS>, dim3((unsigned)hblocks), dim3(SEL_NT), 0, c->stream, W, N, st,
                            shift, bits[p], p == 0 ? 1 : 0);
         hipLaunchKernelGGL(k_sel_pick, dim3(1), dim3(256), 0, c->stream, st, bits[p]);
     }
     hipLaunchKernelGGL(k_tie_count<TS>, dim3((unsigned)nmark), dim3(MARK_NT), 0, c->stream, W, N, st,
                        c->tie_counts);
-    hipLaunchKernelGGL(k_tie_scan, dim3(1), dim3(1024), 0, c->stream, c->tie_counts, nmark);
+    hipLaunchKernelGGL(k_tie_scan, dim3(1), dim3(1024), 0, c->stream, c->tie_counts, nmark, st);
     hipLaunchKernelGGL(k_mark<TS>, dim3((unsigned)nmark), dim3(MARK_NT), 0, c->stream, W, m1, m2, N, st,
                        c->tie_counts, c->prune_flags);
     USL_TRY(usl_check_launch(c, "prune"));
