@@ -325,17 +325,17 @@ k_mark_rows_serial(TS* __restrict__ W, float* __restrict__ m1, float* __restrict
 // GS lanes own one row (GS = power of two >= k, <= 64); lane t of the group holds slot t.
 // flags == nullptr means every slot is empty (initial connectivity).
 // What bounds this is the vector unit.  The first candidates of all empty slots are drawn together, by as many lanes as there are
-// such slots in RG_TURNS turns of a wavefront's rows, and compared in one short loop; where two columns of a row clash, which is
+// such slots in TURNS turns of a wavefront's rows, and compared in one short loop; where two columns of a row clash, which is
 // rare, the turn goes slot by slot, drawing on.  Slot by slot from the beginning, each candidate drawn by the whole group, took
 // 118 us at m = 500k, k = 32, 5 % empty; now 67.
-constexpr int RG_TURNS = 8;
+// TURNS: 8, or 1 where that would leave compute units without 16 wavefronts.
 template <int GS> struct RowMask { typedef uint32_t T; };   // a bit per slot
 template <> struct RowMask<64> { typedef uint64_t T; };
-template <int GS>
+template <int GS, int TURNS>
 __global__ void __launch_bounds__(256)
 k_regrow(int32_t* __restrict__ idx, const uint8_t* __restrict__ flags, int64_t m, uint32_t d, int k,
          uint32_t k0, uint32_t k1, uint32_t epoch_lo) {
-    __shared__ uint32_t list[4][RG_TURNS * 64];   // turn * 64 + lane of the empty slots, then their first candidates
+    __shared__ uint32_t list[4][TURNS * 64];   // turn * 64 + lane of the empty slots, then their first candidates
     const int lane = threadIdx.x & 63, t = lane & (GS - 1);
     uint32_t* const mine_of = list[threadIdx.x >> 6];
     const int gshift = lane & ~(GS - 1);
@@ -344,16 +344,16 @@ k_regrow(int32_t* __restrict__ idx, const uint8_t* __restrict__ flags, int64_t m
     const uint64_t below = (1ull << lane) - 1ull;
     auto of_row = [&](uint64_t ballot) { return (Mask)(ballot >> gshift) & gmask; };
     auto lowest = [&](Mask v) { return GS == 64 ? __ffsll((unsigned long long)v) - 1 : __ffs((int)v) - 1; };   // -1: none
-    const int64_t row0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * (RG_TURNS * 64 / GS);   // the wavefront's first
+    const int64_t row0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * (TURNS * 64 / GS);   // the wavefront's first
     auto row_of = [&](int turn, int l) { return row0 + turn * (64 / GS) + l / GS; };
-    uint64_t empty[RG_TURNS];    // of the turn's lanes
-    int32_t mine[RG_TURNS];
-    uint32_t first[RG_TURNS], n = 0;
-    bool is[RG_TURNS];
+    uint64_t empty[TURNS];    // of the turn's lanes
+    int32_t mine[TURNS];
+    uint32_t first[TURNS], n = 0;
+    bool is[TURNS];
 #pragma unroll
-    for (int r = 0; r < RG_TURNS; ++r) is[r] = row_of(r, lane) < m && t < k && (flags ? flags[(size_t)row_of(r, lane) * k + t] != 0 : true);
+    for (int r = 0; r < TURNS; ++r) is[r] = row_of(r, lane) < m && t < k && (flags ? flags[(size_t)row_of(r, lane) * k + t] != 0 : true);
 #pragma unroll
-    for (int r = 0; r < RG_TURNS; ++r) {
+    for (int r = 0; r < TURNS; ++r) {
         empty[r] = __ballot(is[r]);
         first[r] = n;
         if (is[r]) mine_of[n + (uint32_t)__popcll(empty[r] & below)] = (uint32_t)(r * 64 + lane);
@@ -368,7 +368,7 @@ k_regrow(int32_t* __restrict__ idx, const uint8_t* __restrict__ flags, int64_t m
     }
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < RG_TURNS; ++r) {
+    for (int r = 0; r < TURNS; ++r) {
         const int64_t row = row_of(r, lane);
         const int32_t own = is[r] ? (int32_t)mine_of[first[r] + (uint32_t)__popcll(empty[r] & below)] : 0;
         Mask todo = of_row(empty[r]);   // empty slots of my row, bit = slot
@@ -467,10 +467,13 @@ usl_status regrow(usl_ctx* c, int32_t* idx, uint8_t* flags, bool all_empty, uint
     while (gs < k) gs <<= 1;
     const uint8_t* fl = all_empty ? nullptr : flags;
     const int64_t lanes = c->m * gs;
-    const unsigned grid = (unsigned)((lanes + 256 * RG_TURNS - 1) / (256 * RG_TURNS));
-#define USL_RG(GS)                                                                             \
-    hipLaunchKernelGGL(k_regrow<GS>, dim3(grid), dim3(256), 0, c->stream, idx, fl, c->m,       \
+    const bool many = lanes >= (int64_t)8 * 64 * 16 * c->num_cu;
+    const int64_t per = many ? 256 * 8 : 256;
+    const unsigned grid = (unsigned)((lanes + per - 1) / per);
+#define USL_RG_T(GS, TURNS)                                                                    \
+    hipLaunchKernelGGL((k_regrow<GS, TURNS>), dim3(grid), dim3(256), 0, c->stream, idx, fl, c->m, \
                        (uint32_t)c->d, k, k0, k1, elo)
+#define USL_RG(GS) do { if (many) USL_RG_T(GS, 8); else USL_RG_T(GS, 1); } while (0)
     switch (gs) {
         case 1: USL_RG(1); break;
         case 2: USL_RG(2); break;
@@ -481,6 +484,7 @@ usl_status regrow(usl_ctx* c, int32_t* idx, uint8_t* flags, bool all_empty, uint
         default: USL_RG(64); break;
     }
 #undef USL_RG
+#undef USL_RG_T
     return usl_check_launch(c, "regrow");
 }
 

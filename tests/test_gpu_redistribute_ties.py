@@ -10,7 +10,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("m,d,k,storage,frac,few", [(3001, 400, 5, "f32", 0.37, 0.02), (3001, 400, 5, "bf16", 0.37, 0.02), (4096, 64, 3, "f32", 0.5, 0.0),
-                                                    (4099, 64, 3, "bf16", 0.9, 0.3), (1021, 40, 33, "f32", 0.25, 0.1), (2000, 70, 64, "bf16", 0.3, 0.1)])
+                                                    (4099, 64, 3, "bf16", 0.9, 0.3), (1021, 40, 33, "f32", 0.25, 0.1), (2000, 70, 64, "bf16", 0.3, 0.1),
+                                                    (70001, 40, 31, "f32", 0.1, 0.5)])   # enough rows for eight turns of a wavefront
 def test_ties_over_many_workgroups(orc, m, d, k, storage, frac, few):
     import gpu_util as gu
     from paper_2306_03725_amd import usl
