@@ -8,7 +8,7 @@
 // is free and that it has a slot for; the number that stays there has the bank.  A move round lets lists that have a
 // bank that a list without one could use move on to a free one, so that the next proposal round finds theirs free: an
 // augmenting path of length three, for all lists at once.  Exact augmenting paths, one bank at a time, and doubling up on
-// the exactly fullest bank took 360 us for the slots of m = 500k, k = 32 (now 225) and 200 for m = 200k (now 125), for
+// the exactly fullest bank took 360 us for the slots of m = 500k, k = 32 (then 225) and 200 for m = 200k (then 125), for
 // gathers that were 2 % faster.
 #pragma once
 #include "usl_internal.h"
@@ -95,53 +95,56 @@ struct usl_matching {
     }
 };
 
-// A list's entries sorted by bank, one list per lane: N entries at most, everything in the lane's own bytes of LDS.  Counts
-// and ends of the banks are bytes, four to a word: updates are atomics on words that nobody waits for (a chain of reads
+// A list's entries sorted by bank, one list per lane: N entries at most (128), everything in the lane's own bytes of LDS.  Where
+// the banks' entries end are bytes, four to a word: updates are atomics on words that nobody waits for (a chain of reads
 // and writes of single bytes took most of the time of these kernels), and the running sums of four bytes are one product.
+// The entries of a bank are taken from the end; the first one carries a mark (FIRST), so there is no count beside the end: a
+// fifth workgroup fits a compute unit (m = 500k, d = 32k, k = 32: slots of the labels 213 and 187 us, register lists 285 and 266).
 template <int GS, int N>
 struct usl_bank_lists {
     static constexpr int Q = GS / 4;
-    struct Lane {
-        uint32_t cnt[Q + 1], end[Q + 1];   // entries left per bank; where bank b's entries end in `sorted`  (odd strides)
-        uint8_t sorted[N + 4];
+    static constexpr uint32_t FIRST = 0x80u;
+    static constexpr int WORDS = Q + (N + 3) / 4;
+    struct Lane {              // an odd number of words: neighbours' are in different LDS banks
+        uint32_t end[Q];       // where bank b's entries end in `sorted`
+        uint8_t sorted[(N + 3) / 4 * 4 + (WORDS % 2 ? 0 : 4)];
     };
     // bank[p] (bytes of LDS too) for p < n; returns the banks that occur.  degree: counts of the group.
     template <typename BANK>
     static __device__ __forceinline__ uint32_t build(Lane& me, uint8_t* bank, int n, int* degree, BANK bank_of) {
 #pragma unroll
-        for (int q = 0; q < Q; ++q) me.cnt[q] = 0u;
+        for (int q = 0; q < Q; ++q) me.end[q] = 0u;
 #pragma unroll 4
         for (int p = 0; p < n; ++p) {
-            const int b = bank_of(p);
-            bank[p] = (uint8_t)b;
-            atomicAdd(&me.cnt[b >> 2], 1u << (8 * (b & 3)));
+            const int b = bank_of(p), sh = 8 * (b & 3);
+            const uint32_t old = atomicAdd(&me.end[b >> 2], 1u << sh);
+            bank[p] = (uint8_t)((uint32_t)b | (((old >> sh) & 0xFFu) ? 0u : FIRST));
             atomicAdd(&degree[b], 1);
         }
-        uint32_t avail = 0, run = 0, ends[Q];
+        uint32_t avail = 0, run = 0;
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
-            const uint32_t w = me.cnt[q];
-            ends[q] = (w + run) * 0x01010101u;   // run: in the lowest byte
-            run = ends[q] >> 24;
-            me.end[q] = ends[q];
+            const uint32_t w = me.end[q], ends = (w + run) * 0x01010101u;   // run: in the lowest byte
+            run = ends >> 24;
+            me.end[q] = ends - w;   // where they begin: moves to the end as they are filled in
 #pragma unroll
             for (int u = 0; u < 4; ++u) avail |= ((w >> (8 * u)) & 0xFFu) ? 1u << (4 * q + u) : 0u;
         }
 #pragma unroll 4
         for (int p = 0; p < n; ++p) {
-            const int b = bank[p], sh = 8 * (b & 3);
-            const uint32_t old = atomicSub(&me.end[b >> 2], 1u << sh);
-            me.sorted[((old >> sh) & 0xFFu) - 1u] = (uint8_t)p;
+            const uint32_t b = bank[p], sh = 8 * (b & 3u);
+            const uint32_t old = atomicAdd(&me.end[(b & ~FIRST) >> 2], 1u << sh);
+            me.sorted[(old >> sh) & 0xFFu] = (uint8_t)((uint32_t)p | (b & FIRST));
         }
-#pragma unroll
-        for (int q = 0; q < Q; ++q) me.end[q] = ends[q];
         return avail;
     }
     // takes an entry of a bank that has one left
     static __device__ __forceinline__ int take(Lane& me, int b, uint32_t& avail) {
-        const int left = reinterpret_cast<uint8_t*>(me.cnt)[b], pick = me.sorted[reinterpret_cast<uint8_t*>(me.end)[b] - left];
-        reinterpret_cast<uint8_t*>(me.cnt)[b] = (uint8_t)(left - 1);
-        if (left == 1) avail &= ~(1u << b);
-        return pick;
+        uint8_t& end = reinterpret_cast<uint8_t*>(me.end)[b];
+        const int at = end - 1;
+        const uint32_t e = me.sorted[at];
+        end = (uint8_t)at;
+        if (e & FIRST) avail &= ~(1u << b);
+        return (int)(e & ~FIRST);
     }
 };
