@@ -221,8 +221,10 @@ template <typename TS>
 __global__ void __launch_bounds__(GW_NT)
 k_gather_w(const TS* __restrict__ W, const uint32_t* __restrict__ slot, const uint32_t* __restrict__ ptr,
            int d, int nwin, float* __restrict__ wl, int bpw, const uint32_t* __restrict__ gate,
-           const uint32_t* __restrict__ idx_check /* or NULL */, size_t n_words, uint64_t* __restrict__ print) {
+           const uint32_t* __restrict__ idx_check /* or NULL */, size_t n_words, uint64_t* __restrict__ print,
+           uint32_t* __restrict__ clear /* or NULL */) {
     if (gate && *gate == 0) return;   // the sparse kernels do this call's work
+    if (clear && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0;
     // the first workgroup also checks that idx still holds what the lists were built from (see usl_idx_fingerprint_block)
     if (idx_check && blockIdx.x == 0) usl_idx_fingerprint_block(idx_check, n_words, print, USL_PRINT_COLUMNS, 0);
     int w, local;
@@ -546,8 +548,10 @@ usl_status usl_bwd_input_prepare(usl_ctx* c, const int32_t* idx, int32_t b) {
     return USL_OK;
 }
 
-// Weights in list order, once per call (every group of instances uses them).
-usl_status usl_bwd_input_gather_w(usl_ctx* c, const void* W, const uint32_t* gate) {
+// Weights in list order, once per call (every group of instances uses them).  begin: also what usl_bwd_input_begin_group does for
+// the first group (a launch of its own is 4.6 us).
+usl_status usl_bwd_input_gather_w(usl_ctx* c, const void* W, const uint32_t* gate, bool begin) {
+    uint32_t* clear = begin ? usl_nz_cells(c) : nullptr;
     const int wl = c->csc_win_labels;
     const int nwin = (int)((c->m + wl - 1) / wl);
     const int bpw = nwin >= 8 ? 32 : 128;
@@ -555,11 +559,11 @@ usl_status usl_bwd_input_gather_w(usl_ctx* c, const void* W, const uint32_t* gat
     if (c->storage == USL_F32)
         hipLaunchKernelGGL(k_gather_w<float>, dim3(blocks), dim3(GW_NT), 0, c->stream, (const float*)W,
                            c->csc_slot, c->csc_ptr, c->d, nwin, c->csc_w, bpw, gate,
-                           reinterpret_cast<const uint32_t*>(c->idx_to_check), (size_t)c->m * c->k, c->idx_print);
+                           reinterpret_cast<const uint32_t*>(c->idx_to_check), (size_t)c->m * c->k, c->idx_print, clear);
     else
         hipLaunchKernelGGL(k_gather_w<uint16_t>, dim3(blocks), dim3(GW_NT), 0, c->stream, (const uint16_t*)W,
                            c->csc_slot, c->csc_ptr, c->d, nwin, c->csc_w, bpw, gate,
-                           reinterpret_cast<const uint32_t*>(c->idx_to_check), (size_t)c->m * c->k, c->idx_print);
+                           reinterpret_cast<const uint32_t*>(c->idx_to_check), (size_t)c->m * c->k, c->idx_print, clear);
     return usl_check_launch(c, "backward_input weights");
 }
 
@@ -620,11 +624,11 @@ usl_status usl_launch_backward_input(usl_ctx* c, const float* g, const int32_t* 
         if (gate) USL_TRY(usl_sparse_backward_input(c, idx, W, grad_x, b));
     }
     if (lds_form) return usl_bwi_lds_run(c, g, idx, W, grad_x, b, gate);
-    USL_TRY(usl_bwd_input_gather_w(c, W, gate));
+    USL_TRY(usl_bwd_input_gather_w(c, W, gate, true));
     const int G = usl_bwd_input_group_rows();
     for (int i0 = 0; i0 < b; i0 += G) {
         const int rows = b - i0 < G ? b - i0 : G;
-        USL_TRY(usl_bwd_input_begin_group(c));
+        if (i0) USL_TRY(usl_bwd_input_begin_group(c));
         {   // gT = the group's rows of g transposed tile by tile, with the zero flags of every (label, tile) piece
             dim3 grid((unsigned)((c->m + 31) / 32), (unsigned)((rows + 31) / 32));
             hipLaunchKernelGGL(k_transpose_g, grid, dim3(256), 0, c->stream, g + (size_t)i0 * c->m, c->gT, (int64_t)rows,

@@ -430,7 +430,7 @@ extern "C" usl_status usl_train_step(usl_ctx* c, const void* x, const int32_t* i
             USL_TRY(usl_bwd_input_prepare(c, idx, b));
             const uint32_t* gate = nullptr;
             uint64_t sampled = 0;
-            if (!lists) USL_TRY(usl_bwd_input_gather_w(c, W, nullptr));
+            if (!lists) USL_TRY(usl_bwd_input_gather_w(c, W, nullptr, false));
             for (int i0 = 0; i0 < b; i0 += G) {
                 const int rows = b - i0 < G ? b - i0 : G;
                 USL_TRY(usl_bwd_input_begin_group(c));
@@ -440,7 +440,7 @@ extern "C" usl_status usl_train_step(usl_ctx* c, const void* x, const int32_t* i
                     c->nz_lists_of = g;             // backward-weight below does not look a second time
                     c->nz_lists_tried = gate != nullptr;
                     if (gate) USL_TRY(usl_sparse_backward_input(c, idx, W, grad_x, b));
-                    USL_TRY(usl_bwd_input_gather_w(c, W, gate));
+                    USL_TRY(usl_bwd_input_gather_w(c, W, gate, false));
                 }
                 USL_TRY(usl_bwd_input_group(c, grad_x + (size_t)i0 * c->d, rows, sampled, gate));
             }

@@ -171,7 +171,7 @@ usl_status usl_sparse_backward_input(usl_ctx* ctx, const int32_t* idx, const voi
 // at most usl_bwd_input_group_rows() instances at a time
 int usl_bwd_input_group_rows(void);
 usl_status usl_bwd_input_prepare(usl_ctx* ctx, const int32_t* idx, int32_t b);
-usl_status usl_bwd_input_gather_w(usl_ctx* ctx, const void* W, const uint32_t* gate);
+usl_status usl_bwd_input_gather_w(usl_ctx* ctx, const void* W, const uint32_t* gate, bool begin);
 usl_status usl_bwd_input_begin_group(usl_ctx* ctx);
 usl_status usl_bwd_input_group(usl_ctx* ctx, float* grad_x_rows, int32_t rows, uint64_t sampled_labels,
                                const uint32_t* gate);
