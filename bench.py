@@ -24,9 +24,9 @@ HBM_PEAK_GBPS = 8000.0   # MI355X published peak
 # They are measured offline (a counter run serialises the kernels) and go stale when a kernel changes: the
 # profile files carry the date of truth, these constants only repeat their per-call totals.
 MEASURED_TRAFFIC_BYTES = {
-    "large": {"backward": 3944660070, "backward_input": 2845542092, "forward": 988964454, "backward_weight": 983684505},
-    "large_wide": {"backward": 17964965478, "backward_input": 8598012928, "forward": 3800982016, "backward_weight": 3052722073},
-    "stress": {"backward": 172239572070, "backward_input": 203855339520, "forward": 37601100492, "backward_weight": 26393168179},
+    "large": {"backward": 3882038067, "backward_input": 2809659392, "forward": 988912026, "backward_weight": 983564288},
+    "large_wide": {"backward": 17548338790, "backward_input": 8440931942, "forward": 3191445914, "backward_weight": 3052090163},
+    "stress": {"backward": 172082960794, "backward_input": 206994145280, "forward": 29374283776, "backward_weight": 26389407334},
 }
 KERNELS_OF_CALL = {
     "forward": "k_interleave where one LDS read serves several instances, k_forward",
@@ -93,12 +93,12 @@ def one_pass_cut(cfg, cus=256):
     """How usl_backward's one-pass form cuts this layer up (the library's rules, csrc/k_lists_cut.h): instances a pass
     takes, label windows, feature blocks, chains of windows, passes over the batch.  None where the library runs the two
     separate products."""
-    q = 4 if cfg.d <= 1024 or 11 * cfg.d // cfg.k <= 4672 else 2
+    q = 4 if cfg.d <= 1024 or 15 * cfg.d // cfg.k <= 7232 else 2
     runs = 2048 // cfg.d if cfg.d <= 1024 else 1
     nfb = -(-runs * cfg.d // 2048)
     fpb = -(-(-(-runs * cfg.d // nfb)) // 32) * 32
     lists = min((14 if q == 4 else 16) * 2048 // fpb, 21 if q == 4 else 24)
-    run = max(4, min(lists * cfg.d // cfg.k, (4672 if q == 4 else 15968) // runs) // 4 * 4)
+    run = max(4, min(lists * cfg.d // cfg.k, (15968 if q == 2 else 4672 if cfg.d <= 1024 else 7232) // runs) // 4 * 4)
     if runs == 1:
         nwin = equal_windows(cfg.m, full_rounds(-(-cfg.m // run), nfb, cus))[1]
     else:
@@ -141,7 +141,7 @@ def launches_in_call(cfg, call):
         return look + 1 + passes * 2
     win = int((24576.0 * ((cfg.d / 32768.0) * (32.0 / cfg.k)) ** 0.5 + 2048.0) / 4096.0) * 4096   # labels per window,
     win = min(max(win, 16384), 49152)                                                              # as the library picks them
-    return look + 1 + groups * (1 + 1 + -(-cfg.m // win) + 1)
+    return look + 1 + groups * (1 + 1 + -(-cfg.m // win) + 1) - 1   # (the first group's count is cleared by the weights' kernel)
 
 
 def cpu_baseline(cfg, budget_s=12.0, max_reps=5):
