@@ -93,20 +93,28 @@ def one_pass_cut(cfg, cus=256):
     """How usl_backward's one-pass form cuts this layer up (the library's rules, csrc/k_lists_cut.h): instances a pass
     takes, label windows, feature blocks, chains of windows, passes over the batch.  None where the library runs the two
     separate products."""
-    q = 4 if cfg.d <= 1024 or 15 * cfg.d // cfg.k <= 7232 else 2
     runs = 2048 // cfg.d if cfg.d <= 1024 else 1
     nfb = -(-runs * cfg.d // 2048)
     fpb = -(-(-(-runs * cfg.d // nfb)) // 32) * 32
-    lists = min((14 if q == 4 else 16) * 2048 // fpb, 21 if q == 4 else 24)
-    run = max(4, min(lists * cfg.d // cfg.k, (15968 if q == 2 else 4672 if cfg.d <= 1024 else 7232) // runs) // 4 * 4)
-    if runs == 1:
-        nwin = equal_windows(cfg.m, full_rounds(-(-cfg.m // run), nfb, cus))[1]
+    at_once = max(1, cus // nfb)
+
+    def windows(q):
+        lists = min((14 if q == 4 else 16) * 2048 // fpb, 21 if q == 4 else 24)
+        run = max(4, min(lists * cfg.d // cfg.k, (15968 if q == 2 else 4672 if cfg.d <= 1024 else 7232) // runs) // 4 * 4)
+        return equal_windows(cfg.m, full_rounds(-(-cfg.m // run), nfb, cus))[1] if runs == 1 else -(-cfg.m // (run * runs))
+
+    def rounds(q):
+        chains = -(-windows(q) // -(-windows(q) // at_once))
+        return -(-windows(q) // chains)
+
+    if cfg.d <= 1024 or 11 * cfg.d // cfg.k <= 4672:
+        q = 4
     else:
-        nwin = -(-cfg.m // (run * runs))
+        q = 4 if 14 * cfg.d // cfg.k <= 7232 and windows(4) * nfb > cus and rounds(4) <= min(rounds(2), 5) else 2
+    nwin = windows(q)
     row = -(-cfg.d // 4) * 16   # bytes of an instance's sums
     if cfg.d > 65536 or nwin * 64 * row > PARTIAL_SUM_BYTES:
         return None
-    at_once = max(1, cus // nfb)
     chains = -(-nwin // -(-nwin // at_once))
     rows = min(cfg.b, max(64, PARTIAL_SUM_BYTES // (chains * row)))
     return {"q": q, "nwin": nwin, "nfb": nfb, "chains": chains, "passes": -(-cfg.b // rows)}

@@ -1421,8 +1421,8 @@ k_lf_reduce(const float4* __restrict__ partial, int nwin, size_t n4, int d, int 
 // ---- how a layer is cut up for either form --------------------------------------------------------------------
 
 static Cut bwi_cut(const usl_ctx* c) { return bwi_cut(c->m, c->d, c->k, c->num_cu); }
-static Cut both_cut(const usl_ctx* c) { return both_cut(c->m, c->d, c->k, c->num_cu); }
-static int both_q(const usl_ctx* c) { return both_q(c->d, c->k); }
+static int both_q(const usl_ctx* c) { return both_q(c->m, c->d, c->k, c->num_cu); }
+static Cut both_cut(const usl_ctx* c) { return both_cut(c->m, c->d, c->k, c->num_cu, both_q(c)); }
 
 // The most that the partial sums of a pass over the batch may take: 16 GiB on a device with 128 GiB or more (every
 // pass loads lists and weights anew: at m = 3M, d = 65536, b = 1024 the two products take 74 ms with passes of 4 GiB,

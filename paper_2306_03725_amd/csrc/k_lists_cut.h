@@ -71,9 +71,10 @@ inline bool both_own(int Q, const Cut& cut) { return Q == 4 && (cut.wl <= BOTH4_
 // The form for both products: lists of 16 connections (half the registers go to the weight-gradient sums; with four
 // instances a lane has 32 slots instead of 36, hence 14), longer where the features do not fill the lanes twice over;
 // blocks of equal size; S runs where the layer is narrower than half a block.
-inline Cut both_cut(int64_t m, int d, int k, int num_cu) {
+// Q: instances of a pass, 2 or 4 (0: both_q's).
+inline Cut both_cut(int64_t m, int d, int k, int num_cu, int Q = 0) {
     Cut cut;
-    const bool four = both_q(d, k) == 4;
+    const bool four = (Q ? Q : both_q(d, k)) == 4;
     const int labels = !four ? BOTH2_LABELS : d <= NT ? BOTH4_OWN_LABELS : BOTH4_LABELS;
     cut.S = d <= NT ? NF / d : 1;
     if (cut.S > labels / 4) cut.S = labels / 4;   // a run has at least four labels, and the window has to fit LDS (d = 1)
@@ -120,6 +121,20 @@ inline int both_chains(const Cut& cut, int num_cu) {
     const int at_once = num_cu > cut.nfb ? num_cu / cut.nfb : 1;
     const int rounds = (cut.nwin + at_once - 1) / at_once;
     return (cut.nwin + rounds - 1) / rounds;
+}
+
+// The instances that the library takes for a layer: both_q's, but where that leaves little between the two (windows of 4672 labels
+// send fewer than 11 connections into a feature, those of 7232 at least 14) only what the rounds of workgroups say, one after the
+// other on a compute unit: four where there are more workgroups than compute units, in no more rounds than two
+// and in five at most.  With six the chains' sums come from memory in every pass (m = 670k, d = 30k, k = 64, bfloat16, b = 512: 5557
+// us with two, 6388 with four; b = 64: 984 and 922).  m = 670k, d = 16k, k = 32, b = 32, three rounds each: 355 and 331; m = 300k,
+// d = 24k, k = 48, b = 64, two and three rounds: 368 and 418; m = 130k, d = 15k, k = 32, b = 128, less than one: 200 and 237.
+inline int both_q(int64_t m, int d, int k, int num_cu) {
+    if (d <= NT || (int64_t)11 * d / k <= (int64_t)BOTH4_OWN_LABELS) return 4;
+    if ((int64_t)14 * d / k > (int64_t)BOTH4_LABELS) return 2;
+    auto rounds = [&](const Cut& cut) { const int chains = both_chains(cut, num_cu); return (cut.nwin + chains - 1) / chains; };
+    const Cut two = both_cut(m, d, k, num_cu, 2), four = both_cut(m, d, k, num_cu, 4);
+    return (int64_t)four.nwin * four.nfb > num_cu && rounds(four) <= rounds(two) && rounds(four) <= 5 ? 4 : 2;
 }
 
 // How a batch of `rows` instances goes through: in passes of at most G, one part each, or at once in several parts.
