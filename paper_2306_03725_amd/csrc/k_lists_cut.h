@@ -55,14 +55,14 @@ inline Cut bwi_cut(int64_t m, int d, int k, int num_cu) {
     return cut;
 }
 
-// Instances that a pass of the kernel for both products takes together: four where windows that send 15 connections into
+// Instances that a pass of the kernel for both products takes together, by the width alone (what both_cut assumes unless told;
+// the library asks both_q of the whole layer, below): four where windows that send 15 connections into
 // a feature fit LDS four rows at a time, else two.  A pass is a chain of waits, so the fewer the better; with shorter lists
 // there are too many windows.  usl_backward with four and two, float32 unless said: m = 200k, d = 12k, k = 32, b = 64 (d / k = 375):
 // 169 and 250 us; m = 300k, d = 14k, k = 32, b = 128 (438): 462 and 509; m = 400k, d = 15k, k = 32, b = 128, bfloat16 (469): 457 and
 // 522; m = 300k, d = 24k, k = 48, b = 100 (500): 545 and 486; m = 670k, d = 32k, k = 64, b = 256, bfloat16 (512): 2987 and 2670.
-// Where the other number leaves a last round of workgroups nearly empty, or the batch is small, it can be wrong (m = 130k,
-// d = 15k, k = 32, b = 64 (480): 141 and 129; m = 670k, d = 16k, k = 32, b = 32 (512): 329 and 353); of 16 layers it takes the faster
-// in 13 and is within 9 % in the others (profiles/rules_measured.txt).
+// Close to the line the rounds of workgroups decide (m = 130k, d = 15k, k = 32, b = 64 (480): 141 and 129; m = 670k, d = 16k,
+// k = 32, b = 32 (512): 329 and 353).
 inline int both_q(int d, int k) { return d <= NT || (int64_t)15 * d / k <= (int64_t)BOTH4_LABELS ? 4 : 2; }
 // Do the activations of the block have a place of their own, beside that of the sums (a barrier less per pass)?  Where a row
 // leaves room for it, and where runs share activations (the places of the sums are then other ones).
