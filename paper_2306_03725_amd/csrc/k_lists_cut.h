@@ -101,7 +101,7 @@ inline Cut both_cut(int64_t m, int d, int k, int num_cu, int Q = 0) {
 // compute units idle.  A workgroup loads its lists and weights and hands out its sums in about 20 us, a pass of its loop
 // takes about 4.4 (m = 31k, d = 1k, k = 32, b = 128: 179 us with 1 part, 116 with 2, 83 with 4, 77 with 6, 103 with 8, which
 // are two rounds); every part writes a weight gradient of its own, which the reader adds up.  Of 16 layers measured
-// (profiles/rules_measured.txt) the best number or within 4 % of it.  forced > 0: that many, if the batch has them.
+// (profiles/rules_measured.txt) the best number or within 5 % of it.  forced > 0: that many, if the batch has them.
 inline int both_parts(const Cut& cut, int64_t m, int k, int num_cu, int rows, int Q, int forced) {
     const int64_t wgs = (int64_t)cut.nwin * cut.nfb, passes = (rows + Q - 1) / Q, cu = num_cu;
     if (forced > 0) return (int)(forced < passes ? forced : passes);

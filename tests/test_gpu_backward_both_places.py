@@ -19,13 +19,17 @@ CASES = [
     (513, 2048, 16, 5, "f32", "all"),             # fewer than eight connections to a lane
     (521, 2048, 16, 5, "f32", "all"),             # ... just more
     (40001, 2047, 3, 4, "bf16", "all"),           # one block: places are flat slots
-    # four at a time with the activations in the place of the sums: windows of 4 676 to 7 232 labels
+    # around four at a time with the activations in the place of the sums (windows of 4 676 to 7 232 labels)
     (120000, 27000, 64, 5, "f32", "all"),         # more windows than chains: earlier sums
     (9001, 4099, 9, 7, "bf16", "all"),            # a last pass of three, a last window of some labels
     (15003, 2048, 5, 6, "f32", "all"),            # one block
     (4700, 3343, 10, 9, "f32", "all"),            # just above the other form's longest window
-    (14465, 9643, 20, 4, "bf16", "all"),          # the longest windows
-    (7003, 9000, 20, 301, "f32", "one block"),    # three passes over the batch, some 30000 entries beside the lists
+    (14465, 9643, 20, 4, "bf16", "all"),          # too few workgroups: two
+    (7003, 9000, 20, 301, "f32", "one block"),    # the same; three passes over the batch, some 30000 entries beside the lists
+    (300001, 14100, 30, 3, "f32", "all"),         # two rounds either way: four
+    (150001, 30000, 60, 5, "bf16", "all"),
+    (230001, 20640, 40, 4, "f32", "all"),         # the longest windows
+    (300001, 14100, 30, 2, "bf16", "one block"),  # ... a block with all connections, beyond LDS
 ]
 
 
