@@ -35,23 +35,24 @@ k_schedule(const int32_t* __restrict__ idx, int64_t m, int k, int shift, int rou
     __shared__ int deg0[G][GS];                             // slots of the group that read a bank and are not used yet
     __shared__ uint32_t win[G][GS];
     const int gl = threadIdx.x / GS, lane = threadIdx.x & (GS - 1);
-    const int label = (int)(threadIdx.x & ~31u) + usl_lane_of_position<GS>(threadIdx.x & 31);   // of the workgroup's
+    const int label = usl_order_label<GS>((int)threadIdx.x);   // of the workgroup's
     const int64_t j0 = (int64_t)blockIdx.x * SCHED_NT, j = j0 + label;
     const bool valid = j < m;
     deg0[gl][lane] = 0;
-    // The banks of all the workgroup's slots, in the order of memory (a lane reading its own row fetched every line several
-    // times: 651 MB instead of 64 at m = 500k, k = 32), at the place of their label; below, a wavefront's lanes read the bank at a place of the
-    // label before any of them writes to that place of its own row.
-    uint8_t(*of_label)[K + 4] = &ord[0][0];
+    // The banks of all the workgroup's slots, in the order of memory (a lane reading its own row of idx fetched every line several
+    // times: 651 MB instead of 64 at m = 500k, k = 32), each into the row of the lane that has its label: behind the barrier a
+    // lane reads and writes its own row only, whatever the order in which the lanes of a wavefront run.
+    uint8_t(*row)[K + 4] = &ord[0][0];
     const uint32_t n = (uint32_t)(min((int64_t)SCHED_NT, m - j0) * k), inv = k > 1 ? 0xFFFFFFFFu / (uint32_t)k + 1u : 0u;   // exact: n < 2^15
 #pragma unroll 8
     for (uint32_t q = threadIdx.x; q < n; q += SCHED_NT) {
-        const uint32_t r = k > 1 ? __umulhi(q, inv) : q;
-        of_label[r][q - r * (uint32_t)k] = (uint8_t)((idx[j0 * k + q] >> shift) & (GS - 1));
+        const uint32_t r = k > 1 ? __umulhi(q, inv) : q;   // label of the workgroup's
+        row[usl_order_row<GS>((int)r)][q - r * (uint32_t)k] = (uint8_t)((idx[j0 * k + q] >> shift) & (GS - 1));
     }
     __syncthreads();
     uint32_t avail = Lists::build(lists[gl][lane], ord[gl][lane], k, deg0[gl],
-                                  [&](int t) { return valid ? (int)of_label[label][t] : ((lane + t) & (GS - 1)); });
+                                  [&](int t) { return valid ? (int)ord[gl][lane][t] : ((lane + t) & (GS - 1)); });
+    __syncthreads();
     __syncthreads();
     usl_matching<GS> match(win[gl], lane);
     for (int s = 0; s < k; ++s) {
