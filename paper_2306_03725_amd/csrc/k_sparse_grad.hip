@@ -21,9 +21,16 @@ namespace {
 
 constexpr int CG_NT = 256, CG_PER = 32, CG_CHUNK = CG_NT * CG_PER;   // labels per block, as 8 x float4 per lane
 
+// The words of nz_state: [0] 1 once the gradient counts as dense, [1], [2] the looks (k_probe_density), and the number of
+// entries listed for instance i, each in a 128-byte line of its own.  Side by side, 32 instances' counts shared a line with
+// one another, and the first of them with the word that every block reads first: what a block waits for is its turn at
+// that line (k_compact_g, m = 500k, b = 256, usl_backward_weight on 0.5 % nonzeros 293 us with the first rows first, 312 with the
+// last, now 272 with either; on 0.1 % 190, 198 and 166; the squared-hinge step 1029, 1010 and 990).
+constexpr size_t STATE_LINE = 32;
+__host__ __device__ constexpr size_t count_at(size_t i) { return (i + 1) * STATE_LINE; }
+
 // A look at a sample of g (four labels in 1024 of every row) before the full pass: a dense gradient, the
 // common case after binary cross-entropy, is recognised here and the full pass leaves at its first instruction.
-// state[0] = 1 once the gradient counts as dense; state[16 + i] = entries listed for instance i.
 __global__ void __launch_bounds__(256)
 k_probe_density(const float* __restrict__ g, int64_t m, uint32_t* __restrict__ state,
                 uint32_t* __restrict__ hint /* pinned host memory: [0] serial of the last finished look, [1] its verdict */,
@@ -61,7 +68,7 @@ k_compact_g(const float* __restrict__ g, int64_t m, uint32_t cap, uint32_t* __re
     __shared__ uint32_t wave_total[CG_NT / 64];
     __shared__ uint32_t block_base;
     if (*reinterpret_cast<volatile uint32_t*>(state) != 0) return;   // the sample, or an earlier block, found g dense
-    const int i = (int)(gridDim.y - 1 - blockIdx.y);   // the last rows first: they were written last, and may still be in a cache (m = 500k, b = 256: 134 and 116 us)
+    const int i = (int)(gridDim.y - 1 - blockIdx.y);   // the last rows first: behind a loss they were written last, and may still be in a cache (m = 500k, b = 256, squared-hinge step 1004 and 990 us)
     const int64_t j0 = (int64_t)blockIdx.x * CG_CHUNK;
     const float* row = g + (size_t)i * m;
     const bool vec = (m % 4 == 0) && ((uintptr_t)g % 16 == 0);
@@ -97,7 +104,7 @@ k_compact_g(const float* __restrict__ g, int64_t m, uint32_t cap, uint32_t* __re
         total += t;
     }
     if (total == 0) return;   // the same for every lane of the block
-    if (threadIdx.x == 0) block_base = atomicAdd(&state[16 + i], total);
+    if (threadIdx.x == 0) block_base = atomicAdd(&state[count_at(i)], total);
     __syncthreads();
     const uint32_t base = block_base;
     if (base + total > cap) {
@@ -117,8 +124,9 @@ k_compact_g(const float* __restrict__ g, int64_t m, uint32_t cap, uint32_t* __re
     }
 }
 
-__global__ void k_zero_state(uint32_t* p, size_t n) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0;
+__global__ void k_zero_state(uint32_t* state, int b) {
+    if (threadIdx.x < STATE_LINE) state[threadIdx.x] = 0;
+    for (int i = threadIdx.x; i < b; i += blockDim.x) state[count_at(i)] = 0;
 }
 
 // clears p[0..n) when the lists stand (state[0] == 0)
@@ -140,7 +148,7 @@ k_bww_sparse(const TS* __restrict__ x, const int32_t* __restrict__ idx, const ui
              float* __restrict__ grad_W, int d, int k) {
     if (state[0] != 0) return;
     const int i = blockIdx.y;
-    const uint64_t items = (uint64_t)state[16 + i] * (uint32_t)k;
+    const uint64_t items = (uint64_t)state[count_at(i)] * (uint32_t)k;
     const int32_t* lab = nz_lab + (size_t)i * cap;
     const float* val = nz_val + (size_t)i * cap;
     const TS* row = x + (size_t)i * d;
@@ -169,7 +177,7 @@ k_bwi_sparse(const int32_t* __restrict__ idx, const TS* __restrict__ W, const ui
     const int nc = min(XS_COLS, d - c0);
     for (int c = threadIdx.x; c < nc; c += XS_NT) acc[c] = 0.f;
     __syncthreads();
-    const uint64_t items = (uint64_t)state[16 + i] * (uint32_t)k;
+    const uint64_t items = (uint64_t)state[count_at(i)] * (uint32_t)k;
     const int32_t* lab = nz_lab + (size_t)i * cap;
     const float* val = nz_val + (size_t)i * cap;
     for (uint64_t e = threadIdx.x; e < items; e += XS_NT) {
@@ -233,9 +241,9 @@ usl_status usl_sparse_compact(usl_ctx* c, const float* g, int32_t b, const uint3
         c->hint_host[0] = 0; c->hint_host[1] = 1;
         USL_HIP(c, hipHostGetDevicePointer((void**)&c->hint_dev, c->hint_host, 0));
     }
-    USL_TRY(usl_reserve(c, (void**)&c->nz_state, &c->nz_state_cap, ((size_t)c->max_b + 16) * 4));
+    USL_TRY(usl_reserve(c, (void**)&c->nz_state, &c->nz_state_cap, count_at(c->max_b) * 4));
     const bool try_lists = usl_sparse_expected(c);
-    hipLaunchKernelGGL(k_zero_state, dim3(1), dim3(256), 0, c->stream, c->nz_state, (size_t)b + 16);
+    hipLaunchKernelGGL(k_zero_state, dim3(1), dim3(256), 0, c->stream, c->nz_state, b);
     hipLaunchKernelGGL(k_probe_density, dim3((unsigned)b), dim3(256), 0, c->stream, g, c->m, c->nz_state, c->hint_dev,
                        ++c->probe_serial);
     if (!try_lists) return usl_check_launch(c, "gradient sample");

@@ -64,7 +64,7 @@ struct usl_ctx {
     int gw_parts_most;             // groups that it has room for (0: not known yet)
     float* gxT;               size_t gxT_cap;  // [tiles][d][32] input gradient in the same layout
     // per-instance lists of the nonzero entries of g (k_sparse_grad.hip)
-    uint32_t* nz_state;       size_t nz_state_cap;   // [0] = 1: gradient is dense, lists abandoned; [16+i] = entries of instance i
+    uint32_t* nz_state;       size_t nz_state_cap;   // [0] = 1: gradient is dense, lists abandoned; entries of every instance, a line each (k_sparse_grad.hip)
     int32_t* nz_lab;          size_t nz_lab_cap;     // [max_b][m/32] label of an entry
     float* nz_val;            size_t nz_val_cap;     // [max_b][m/32] its gradient
     const float* nz_lists_of; // g that has just been looked at (only set inside usl_train_step), else NULL
