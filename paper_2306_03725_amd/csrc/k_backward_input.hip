@@ -26,6 +26,7 @@
 #include <stdlib.h>
 
 #include "usl_internal.h"
+#include "k_lists_cut.h"
 
 namespace {
 
@@ -331,12 +332,13 @@ k_bwd_input_window(const float* __restrict__ gT, const float* __restrict__ wl,
                    const uint32_t* __restrict__ ptr /* this window's d+1 offsets, by rank */,
                    const uint32_t* __restrict__ order /* this window's features by falling list length */,
                    const uint32_t* __restrict__ slot, int k, int kshift /* log2 k, or -1 */,
-                   float* __restrict__ gxT, int d, int tile0,
+                   float* __restrict__ gxT, int d, usl_lists::ChunkTurns turns, int tile0,
                    int accumulate, const uint8_t* __restrict__ nzf /* this tile row is nzf + tile*m */,
                    int64_t m, const uint32_t* __restrict__ nz_cells, uint32_t sparse_below,
                    const uint32_t* __restrict__ gate) {
     if (gate && *gate == 0) return;
-    const int rank = SPLIT == 1 ? blockIdx.y * 32 + (threadIdx.x >> 3) : blockIdx.y * 4 + (threadIdx.x >> 6);
+    const int turn = turns((int)blockIdx.y);
+    const int rank = SPLIT == 1 ? turn * 32 + (int)(threadIdx.x >> 3) : turn * 4 + (int)(threadIdx.x >> 6);
     if (rank >= d) return;   // SPLIT = 8: the whole wavefront leaves
     const int c = (int)order[rank];
     auto label_of = [&](uint32_t e) -> int32_t { return (int32_t)(kshift >= 0 ? e >> kshift : e / (uint32_t)k); };
@@ -498,6 +500,7 @@ usl_status build_csc(usl_ctx* c, const int32_t* idx) {
     USL_TRY(usl_reserve(c, (void**)&c->csc_order, &c->csc_order_cap, nbins * 4));
     USL_TRY(usl_idx_print_ready(c));
     uint32_t* total = c->csc_cursor + nbins * splits;
+    c->csc_chunk = (narrow ? 1 : 4) * CSC_NT;
     if (narrow) launch_csc<1>(c, idx, nwin, (int)splits, total);
     else launch_csc<4>(c, idx, nwin, (int)splits, total);
     USL_TRY(usl_check_launch(c, "column lists"));
@@ -590,16 +593,17 @@ usl_status usl_bwd_input_group(usl_ctx* c, float* grad_x_rows, int32_t rows, uin
     bool split = (int64_t)ntile * ((c->d + 31) / 32) < 2 * (int64_t)c->num_cu;
     if ((c->d + 3) / 4 > 65535) split = false;   // the grid's second dimension
     dim3 grid((unsigned)ntile, (unsigned)(split ? (c->d + 3) / 4 : (c->d + 31) / 32));
+    const usl_lists::ChunkTurns turns = usl_lists::chunk_turns(c->d, c->csc_chunk, split ? 4 : 32);
     for (int w = 0; w < nwin; ++w) {
         if (split)
             hipLaunchKernelGGL(k_bwd_input_window<8>, grid, dim3(256), 0, c->stream, c->gT, c->csc_w,
                                c->csc_ptr + (size_t)w * c->d, c->csc_order + (size_t)w * c->d, c->csc_slot,
-                               c->k, kshift, c->gxT, c->d, 0,
+                               c->k, kshift, c->gxT, c->d, turns, 0,
                                w > 0 ? 1 : 0, c->nz_flags, c->m, usl_nz_cells(c), sparse_below, gate);
         else
             hipLaunchKernelGGL(k_bwd_input_window<1>, grid, dim3(256), 0, c->stream, c->gT, c->csc_w,
                                c->csc_ptr + (size_t)w * c->d, c->csc_order + (size_t)w * c->d, c->csc_slot,
-                               c->k, kshift, c->gxT, c->d, 0,
+                               c->k, kshift, c->gxT, c->d, turns, 0,
                                w > 0 ? 1 : 0, c->nz_flags, c->m, usl_nz_cells(c), sparse_below, gate);
     }
     {

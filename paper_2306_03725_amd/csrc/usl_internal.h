@@ -39,6 +39,7 @@ struct usl_ctx {
                               // 1 = a later call found idx changed
     const int32_t* idx_to_check;  // idx whose fingerprint the next weight gather compares (NULL right after a build)
     int csc_win_labels;       // labels per window the lists were built with
+    int csc_chunk;            // features that were put into the order of their lists' lengths together
     const int32_t* csc_built_for;  // idx pointer the lists were built from (NULL = stale)
     // bank-aware order in which a label's slots are visited by the LDS gathers (performance only)
     uint8_t* slot_order;      size_t slot_order_cap;   // [m][padded k] slot read at step s
