@@ -1385,9 +1385,12 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
 // grad_x[i][c] = sum over the windows (chains of them, in the kernel for both products) of partial[w][i][c], i < rows; a row of partial is dp floats (d rounded up to a
 // multiple of 4).  BOTH only names the kernel after the one whose sums it adds, so that a profile tells the two apart.
 // vec: rows of grad_x are 16-byte aligned too.
-// Bound by the stream of the partial sums, so eight windows' loads go out together (one after the other, and the rows from the
-// first: 11.0 us at m = 31k, d = 1k, b = 128, now 5.6; m = 200k, d = 8k, b = 64: 28.5 and 23.3; m = 500k, d = 32k, b = 256, 537 MB: 120 and 116).
-template <bool BOTH>
+// Bound by the stream of the partial sums.  Where lanes are few the loads of eight or four windows go out together (AT_ONCE): one
+// after the other a lane waits out every window.  Where they are many, one: they cover for one another, and their rows stay
+// close together.  In a step, with eight, four, one: m = 31k, d = 1k, b = 128 (128 workgroups): 5.8, 6.4, 11.0 us; m = 200k, d = 8k, b = 64
+// (512): 24, 22, 31; m = 60k, d = 8k, b = 128 (1000): 15.1, 13.9, 12.6; m = 130k, d = 32k, b = 64 (2048): 17.8, 16.4, 15.6; m = 500k,
+// d = 32k, b = 256, 537 MB: 116, 119, 109 (120 with the rows from the first).
+template <bool BOTH, int AT_ONCE>
 __global__ void __launch_bounds__(256)
 k_lf_reduce(const float4* __restrict__ partial, int nwin, size_t n4, int d, int dp, bool vec, float* __restrict__ out,
             const uint32_t* __restrict__ gate, const uint32_t* __restrict__ stale) {
@@ -1397,7 +1400,7 @@ k_lf_reduce(const float4* __restrict__ partial, int nwin, size_t n4, int d, int 
     for (size_t u = (size_t)blockIdx.x * blockDim.x + threadIdx.x; u < n4; u += step) {
         const size_t v = n4 - 1 - u;   // the last rows first: they were written last, and may still be in a cache
         float4 a = partial[v];
-#pragma unroll 8
+#pragma unroll AT_ONCE
         for (int q = 1; q < nwin; ++q) {
             const float4 t = partial[(size_t)q * n4 + v];
             a.x += t.x; a.y += t.y; a.z += t.z; a.w += t.w;
@@ -1588,12 +1591,18 @@ static void lf_reduce(usl_ctx* c, const float* partial, int sets, int rows, bool
     const uint32_t* stale = usl_stale_word(c);
     size_t blocks = (n4 + 255) / 256;
     if (blocks > (size_t)c->num_cu * 8) blocks = (size_t)c->num_cu * 8;
-    if (both)
-        hipLaunchKernelGGL(k_lf_reduce<true>, dim3((unsigned)blocks), dim3(256), 0, c->stream,
-                           reinterpret_cast<const float4*>(partial), sets, n4, c->d, dp, vec, grad_x, gate, stale);
-    else
-        hipLaunchKernelGGL(k_lf_reduce<false>, dim3((unsigned)blocks), dim3(256), 0, c->stream,
-                           reinterpret_cast<const float4*>(partial), sets, n4, c->d, dp, vec, grad_x, gate, stale);
+#define USL_REDUCE(BOTH, AT_ONCE)                                                                                            \
+    hipLaunchKernelGGL((k_lf_reduce<BOTH, AT_ONCE>), dim3((unsigned)blocks), dim3(256), 0, c->stream,                         \
+                       reinterpret_cast<const float4*>(partial), sets, n4, c->d, dp, vec, grad_x, gate, stale)
+#define USL_REDUCE_B(BOTH)                                                                                                  \
+    do {                                                                                                                    \
+        if (blocks <= (size_t)c->num_cu) USL_REDUCE(BOTH, 8);                                                               \
+        else if (blocks <= (size_t)c->num_cu * 2) USL_REDUCE(BOTH, 4);                                                      \
+        else USL_REDUCE(BOTH, 1);                                                                                           \
+    } while (0)
+    if (both) USL_REDUCE_B(true); else USL_REDUCE_B(false);   // see the kernel for the lines
+#undef USL_REDUCE_B
+#undef USL_REDUCE
 }
 
 // The one-product form needs its row buffer at LDS address 0 (a label's byte offset is the address); all need the LDS.
