@@ -1004,9 +1004,14 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
         uint32_t at = threadIdx.x * 4u, sl[N];   // (a lane past the end reads the last place again)
         asm volatile("" : "+v"(at));
         const uint32_t wave_at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+        // Does the wavefront fetch a weight for its lanes' u-th places?  bfloat16 ones always: sl[u] has to hold a slot then.  Float32 ones
+        // up to the last place, and a window of few places asks for no more slots than that (a step at m = 31k, d = 1k, k = 32, b = 128:
+        // 100.4 and 95.7 us; usl_backward at m = 130k, d = 15k, k = 32, b = 64: 172 and 168; m = 10k, d = 39k, b = 54: 51.0 and 49.4).
+        auto fetches = [&](int u) { return sizeof(TS) != 4 || wave_at + (uint32_t)(u * NT * 4) < n_bytes; };
         if (nfb > 1) {
 #pragma unroll
-            for (int u = 0; u < N; ++u) sl[u] = at_byte(slot_at + e0, min(at + (uint32_t)(u * NT * 4), n_bytes - 4));
+            for (int u = 0; u < N; ++u)
+                if (u < 8 || fetches(u)) sl[u] = at_byte(slot_at + e0, min(at + (uint32_t)(u * NT * 4), n_bytes - 4));
         } else {
 #pragma unroll
             for (int u = 0; u < N; ++u) sl[u] = e0 + min(at + (uint32_t)(u * NT * 4), n_bytes - 4) / 4;
@@ -1017,7 +1022,7 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
         if constexpr (sizeof(TS) == 4) {
 #pragma unroll
             for (int u = 0; u < N; ++u)
-                if (wave_at + (uint32_t)(u * NT * 4) < n_bytes)   // (whole wavefronts: at most 63 places behind the last one are written too)
+                if (fetches(u))   // (whole wavefronts: at most 63 places behind the last one are written too)
                     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(W_window + (sl[u] - first_slot)),
                                                      (__attribute__((address_space(3))) void*)(lds_raw + wave_at + (size_t)(u * NT * 4)), 4, 0, 0);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
