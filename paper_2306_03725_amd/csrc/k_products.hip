@@ -384,9 +384,11 @@ usl_status run_backward_weight_generic(usl_ctx* c, const float* g, const void* x
 
 // ---- the register-resident kernels ---------------------------------------------------------------------------
 
-// tuning and test aids: workgroup shape (0 .. 3) and parts of the batch instead of the estimate's choice
+// tuning and test aids: workgroup shape (0 .. 3) and parts of the batch instead of the estimate's choice; parts of the batch (up to
+// as many as it has groups) for the last half of forward's blocks of labels, whatever the rounds
 int tune_shape() { const char* e = getenv("USL_TUNE_SHAPE"); return e && *e ? atoi(e) : -1; }
 int tune_split() { const char* e = getenv("USL_TUNE_SPLIT"); return e && *e ? atoi(e) : 0; }
+int tune_tail() { const char* e = getenv("USL_TUNE_TAIL"); return e && *e ? atoi(e) : 0; }
 
 // How the activations of this layer are laid out for the kernels (k_products_common.h): instances per group, bytes
 // from row to row, whether x itself is that layout.
@@ -460,7 +462,7 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
     Launch best;
     best.kern.fn = nullptr;
     double best_t = 0.0;
-    const int shape_force = tune_shape(), split_force = tune_split();
+    const int shape_force = tune_shape(), split_force = tune_split(), tail_force = backward ? 0 : tune_tail();
     for (int shape = 0; shape < 4; ++shape) {
         if (shape_force >= 0 && shape != shape_force && kernel_for(c, L, kind, shape_force).fn) continue;
         const ProductKernel kern = kernel_for(c, L, kind, shape);
@@ -510,7 +512,7 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
         const int64_t resident = (int64_t)res * (cus / 8 > 0 ? cus / 8 : 1);   // workgroups on an XCD; they go round-robin to the 8
         auto shared_by = [&](int64_t same) { return (int)(same < 1 ? 1 : same < resident ? same : resident); };
         for (int G = 1; G <= groups; G = G < 8 ? G + 1 : G + (G + 3) / 4) {
-            if (split_force > 0 && G > 1) break;
+            if ((split_force > 0 || tail_force > 0) && G > 1) break;
             const int split = split_force > 0 ? split_force : G, gpb = (groups + split - 1) / split;
             const int64_t parts = (groups + gpb - 1) / gpb;   // those that have work
             if (parts > most_parts && parts > 1) break;
@@ -523,14 +525,16 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
             // more and shorter workgroups of them (the scores need no adding up).  m = 670k, d = 16k, k = 32, b = 32 (328 blocks
             // of 2048 labels, 72 in three parts): 187 and 162 us; m = 600k, d = 20k, k = 32, b = 128: 452 and 330; m = 670k, d = 32k,
             // k = 64, b = 256, bfloat16: 1450 and 1305.
-            const int64_t slots = (int64_t)cus * res, tail = parts == 1 && !backward && nblk > slots ? nblk % slots : 0;
+            const int64_t slots = (int64_t)cus * res, last = tail_force > 0 ? (nblk + 1) / 2 : nblk > slots ? nblk % slots : 0;
+            const int64_t tail = parts == 1 && !backward ? last : 0;
             int tail_gpb = 0;
-            for (int T = 2; tail > 0 && T <= groups && T <= 16; ++T) {
+            for (int T = tail_force > 0 ? tail_force : 2; tail > 0 && T <= groups && (T <= 16 || T == tail_force); ++T) {
                 const int per = (groups + T - 1) / T;
                 const int64_t items = tail * ((groups + per - 1) / per);
-                if (kind == FORWARD_LOSS && (size_t)(nblk - tail + items) > usl_forward_blocks(c)) break;
+                if (kind == FORWARD_LOSS && (size_t)(nblk - tail + items) > usl_forward_blocks(c) && tail_force <= 0) break;
                 const double with = clocks(nblk - tail, gpb) + clocks(items, per);
-                if (with < t) { t = with; tail_gpb = per; }
+                if (with < t || tail_force > 0) { t = with; tail_gpb = per; }
+                if (tail_force > 0) break;
             }
             if (!best.kern.fn || t < best_t) {
                 best_t = t;

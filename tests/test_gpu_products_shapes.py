@@ -64,7 +64,8 @@ def test_products_with_the_parts_of_the_batch_first(orc, m, d, k, b, storage, sp
     compare(orc, gu, wl.custom(m, d, k, b, storage=storage, positives=1, index=810 + split), m, d, k, b, storage)
 
 
-# more blocks of labels than workgroups fit at once: those of the last round take the batch in parts
+# Far more labels than the other tests have.  Only the last layer has more blocks of labels than workgroups fit at once (256
+# compute units), so that the blocks of its last round take the batch in parts; most others take it in parts altogether.
 LAST_ROUND = [(263000, 30000, 3, 9, "f32"), (300001, 36000, 2, 35, "bf16"), (262145, 40000, 1, 4, "f32"), (600011, 20000, 3, 13, "f32"),
               (270000, 65536, 2, 5, "f32"), (530000, 10000, 5, 37, "f32")]
 
@@ -80,6 +81,30 @@ def test_scores_of_the_blocks_of_a_last_round(orc, m, d, k, b, storage):
 def test_losses_of_the_blocks_of_a_last_round(orc, m, d, k, b, storage, monkeypatch):
     """The sum over all workgroups, and the target bits of parts that begin within a word of 32 instances."""
     import test_gpu_train_step as steps
+    case = (m, d, k, b, storage, 0, False, False)
+    monkeypatch.setattr(steps, "CASES", [case])
+    steps.test_train_step(orc, *case, monkeypatch)
+
+
+# (parts of the batch): groups of 4, 2, 1 instances and rows in two halves; parts that begin within a word of 32 instances, parts
+# of unequal size, one of a single group; one block of labels, which is then the last half, and several
+IN_PARTS = [(9001, 9000, 5, 37, "f32", 3), (9001, 15000, 9, 37, "f32", 3), (9001, 15000, 9, 64, "f32", 16), (9001, 30000, 12, 37, "f32", 4),
+            (9001, 65536, 8, 35, "f32", 3), (9001, 20000, 24, 70, "bf16", 5), (9001, 30001, 33, 37, "bf16", 3), (9001, 65536, 16, 37, "bf16", 37),
+            (700, 9000, 20, 10, "f32", 3), (5000, 30000, 64, 5, "f32", 2), (5000, 12000, 50, 9, "bf16", 2)]
+
+
+@pytest.mark.parametrize("m,d,k,b,storage,parts", IN_PARTS)
+def test_scores_of_blocks_that_take_the_batch_in_parts(orc, m, d, k, b, storage, parts, monkeypatch):
+    import gpu_util as gu
+    monkeypatch.setenv("USL_TUNE_TAIL", str(parts))
+    print("products", m, d, k, b, storage, parts, flush=True)
+    compare(orc, gu, wl.custom(m, d, k, b, storage=storage, positives=1, index=832), m, d, k, b, storage)
+
+
+@pytest.mark.parametrize("m,d,k,b,storage,parts", IN_PARTS)
+def test_losses_of_blocks_that_take_the_batch_in_parts(orc, m, d, k, b, storage, parts, monkeypatch):
+    import test_gpu_train_step as steps
+    monkeypatch.setenv("USL_TUNE_TAIL", str(parts))
     case = (m, d, k, b, storage, 0, False, False)
     monkeypatch.setattr(steps, "CASES", [case])
     steps.test_train_step(orc, *case, monkeypatch)
