@@ -55,15 +55,6 @@ inline Cut bwi_cut(int64_t m, int d, int k, int num_cu) {
     return cut;
 }
 
-// Instances that a pass of the kernel for both products takes together, by the width alone (what both_cut assumes unless told;
-// the library asks both_q of the whole layer, below): four where windows that send 15 connections into
-// a feature fit LDS four rows at a time, else two.  A pass is a chain of waits, so the fewer the better; with shorter lists
-// there are too many windows.  usl_backward with four and two, float32 unless said: m = 200k, d = 12k, k = 32, b = 64 (d / k = 375):
-// 169 and 250 us; m = 300k, d = 14k, k = 32, b = 128 (438): 462 and 509; m = 400k, d = 15k, k = 32, b = 128, bfloat16 (469): 457 and
-// 522; m = 300k, d = 24k, k = 48, b = 100 (500): 545 and 486; m = 670k, d = 32k, k = 64, b = 256, bfloat16 (512): 2987 and 2670.
-// Close to the line the rounds of workgroups decide (m = 130k, d = 15k, k = 32, b = 64 (480): 141 and 129; m = 670k, d = 16k,
-// k = 32, b = 32 (512): 329 and 353).
-inline int both_q(int d, int k) { return d <= NT || (int64_t)15 * d / k <= (int64_t)BOTH4_LABELS ? 4 : 2; }
 // Do the activations of the block have a place of their own, beside that of the sums (a barrier less per pass)?  Where a row
 // leaves room for it, and where runs share activations (the places of the sums are then other ones).
 inline bool both_own(int Q, const Cut& cut) { return Q == 4 && (cut.wl <= BOTH4_OWN_LABELS || cut.S > 1); }
@@ -71,10 +62,10 @@ inline bool both_own(int Q, const Cut& cut) { return Q == 4 && (cut.wl <= BOTH4_
 // The form for both products: lists of 16 connections (half the registers go to the weight-gradient sums; with four
 // instances a lane has 32 slots instead of 36, hence 14), longer where the features do not fill the lanes twice over;
 // blocks of equal size; S runs where the layer is narrower than half a block.
-// Q: instances of a pass, 2 or 4 (0: both_q's).
-inline Cut both_cut(int64_t m, int d, int k, int num_cu, int Q = 0) {
+// Q: instances of a pass, 2 or 4 (both_q, below).
+inline Cut both_cut(int64_t m, int d, int k, int num_cu, int Q) {
     Cut cut;
-    const bool four = (Q ? Q : both_q(d, k)) == 4;
+    const bool four = Q == 4;
     const int labels = !four ? BOTH2_LABELS : d <= NT ? BOTH4_OWN_LABELS : BOTH4_LABELS;
     cut.S = d <= NT ? NF / d : 1;
     if (cut.S > labels / 4) cut.S = labels / 4;   // a run has at least four labels, and the window has to fit LDS (d = 1)
@@ -123,12 +114,17 @@ inline int both_chains(const Cut& cut, int num_cu) {
     return (cut.nwin + rounds - 1) / rounds;
 }
 
-// The instances that the library takes for a layer: both_q's, but where that leaves little between the two (windows of 4672 labels
-// send fewer than 11 connections into a feature, those of 7232 at least 14) only what the rounds of workgroups say, one after the
-// other on a compute unit: four where there are more workgroups than compute units, in no more rounds than two
-// and in five at most.  With six the chains' sums come from memory in every pass (m = 670k, d = 30k, k = 64, bfloat16, b = 512: 5557
-// us with two, 6388 with four; b = 64: 984 and 922).  m = 670k, d = 16k, k = 32, b = 32, three rounds each: 355 and 331; m = 300k,
-// d = 24k, k = 48, b = 64, two and three rounds: 368 and 418; m = 130k, d = 15k, k = 32, b = 128, less than one: 200 and 237.
+// Instances that a pass of the kernel for both products takes together.  A pass is a chain of waits, so the fewer the better:
+// four, where windows that send 11 connections into a feature leave four rows room in LDS beside the activations (usl_backward with
+// four and two, float32: m = 200k, d = 12k, k = 32, b = 64: 174 and 188 us; m = 400k, d = 27k, k = 64, b = 64: 626 and 699); two, where even
+// windows of 7232 labels send fewer than 14 (too many windows; m = 670k, d = 32k, k = 64, b = 256, bfloat16: 3533 and 2830).
+// In between the rounds of workgroups decide, one after the other on a compute unit: four where there are more workgroups than compute
+// units, in no more rounds than two and in five at most.  With six the chains' sums come from memory in every pass (m = 670k, d = 30k,
+// k = 64, bfloat16, b = 512: 5557 us with two, 6388 with four).  m = 670k, d = 16k, k = 32, b = 32, three rounds each: 355 and
+// 331; m = 300k, d = 24k, k = 48, b = 64, two and three rounds: 368 and 418; m = 130k, d = 15 360, k = 32, b = 128, less than one round of
+// windows: 200 (in two parts of the batch that fit a round) and 237.
+// The rule does not see the batch, which can decide it the other way: the six rounds above at b = 64 take 984 and 922, and
+// m = 130k, d = 15 000, where two parts of the windows of two do not fit a round, 168 and 140 at b = 64.
 inline int both_q(int64_t m, int d, int k, int num_cu) {
     if (d <= NT || (int64_t)11 * d / k <= (int64_t)BOTH4_OWN_LABELS) return 4;
     if ((int64_t)14 * d / k > (int64_t)BOTH4_LABELS) return 2;

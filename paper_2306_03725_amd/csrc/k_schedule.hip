@@ -53,7 +53,6 @@ k_schedule(const int32_t* __restrict__ idx, int64_t m, int k, int shift, int rou
     uint32_t avail = Lists::build(lists[gl][lane], ord[gl][lane], k, deg0[gl],
                                   [&](int t) { return valid ? (int)ord[gl][lane][t] : ((lane + t) & (GS - 1)); });
     __syncthreads();
-    __syncthreads();
     usl_matching<GS> match(win[gl], lane);
     for (int s = 0; s < k; ++s) {
         match.run(avail, rounds);
