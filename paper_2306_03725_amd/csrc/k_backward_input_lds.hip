@@ -507,10 +507,10 @@ k_lf_seg_place(const int32_t* __restrict__ idx, int64_t m, int k, Cut cut, int n
 // empty place (it then reads the zero word of a free bank, see ZERO_LABEL) while it has one.
 // One half-wavefront per (workgroup of the gather kernel, zone, 32 lanes); lane i is list i and also bank i.
 // Reads the lists as k_lf_plan grouped them (ent), writes them ordered into the places the gather kernel loads its
-// registers from (lab / slot: [workgroup][slot][lane]) and what exceeds the allowance into the overflow list.  Any
-// outcome is a valid order: it changes speed, never results.  rounds = 0: the lists stay in the order of ent.
+// registers from (lab: [workgroup][slot / 8][lane][slot % 8], see half_at; slot: [workgroup][slot][lane]) and what exceeds the
+// allowance into the overflow list.  Any outcome is a valid order: it changes speed, never results.  rounds = 0: the lists stay in the order of ent.
 // pos (if given, see k_lf_seg_place): every entry's place among its workgroup's weight gradients goes along, into rk
-// (beside lab / slot) or ovrk (beside ov); an empty place gets PAD_SLOT.  A workgroup of at most small_wg entries, as all are
+// (laid out like slot) or ovrk (beside ov); an empty place gets PAD_SLOT.  A workgroup of at most small_wg entries, as all are
 // unless the connectivity is skewed, has labels and places in ent, and places of 16 bits in rk, laid out like lab, at the
 // beginning of its part; slot_at (NULL: one block of features) has its flat slots by place.
 // GS = lanes and banks of a group: 32, or 16 where the gathers are 16 bytes wide (the lanes of a half-wavefront that such a
@@ -1096,7 +1096,7 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
     }
     ov_share[lane] = (ovra & 0xFFFFu) / 2 | ovra >> 17 << 8 | (ovrb & 0xFFFFu) / 2 << 16 | ovrb >> 17 << 24;
     if (lane < 32 * Q) reinterpret_cast<uint32_t*>(lds_raw)[ZL * Q + lane] = 0u;   // what empty places read
-    for (uint32_t q = NEAR2 + lane; q < ov_n; q += NT) ovgw[(size_t)ov0 + q] = 0.f;   // entry q is lane q % NT's
+    for (uint32_t q = NEAR2 + lane; q < ov_n; q += NT) ovgw[(size_t)ov0 + q] = 0.f;   // in the passes entry q is lane (q - NEAR2) % NT's
     const int nl = (int)max((int64_t)0, min((int64_t)cut.wl, m - (int64_t)w * cut.wl));   // labels of this window (the last one may be short)
     const int nv = nl / 4, quarter = cut.wl / 4;                         // whole 16-byte pieces of a row slice; see unit_of_label
     const int nf = min(cut.fpb, cut.vd - fb * cut.fpb);                            // features of this block that exist
@@ -1351,7 +1351,9 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
     if (one_go) load_words<KT>(rk + wg * KT * NT, tid4 / 4, places);
     else own_places(places);
     const uint32_t mine = threadIdx.x < ov_n ? (ovrk + (size_t)ov0)[threadIdx.x] : PAD_SLOT;
-    __syncthreads();   // the last pass's reads of LDS, the owners' last additions to ov_sum
+    // Behind it: the last pass's reads of LDS, the owners' last additions to ov_sum, and (the wait above) those to ovgw, whose
+    // entries are handed out below by other lanes than theirs.
+    __syncthreads();
 #pragma unroll
     for (int q = 0; q < KT / 4; ++q) {
         if (!used(4 * q)) continue;
