@@ -502,10 +502,15 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
             const bool thin = kern.NT / 64 * res <= 8;
             const double gather = (double)gpb * kern.NT * kern.LPT * kern.K * (L.halves ? 2 : 1) / reads_per_clk * (!thin ? 1.0 : backward ? 1.3 : 1.1);
             const double more = copy > gather ? copy : gather, less = copy > gather ? gather : copy;
+            // With four labels of eight slots a lane stores as much as half of what it reads: 11 bytes a clock beside the gathers of two
+            // wavefronts on a SIMD, 45 beside those of four (m = 524k, d = 3k, k = 8, b = 128: a pass takes 42 of 98 us longer than its
+            // copies and gathers with 512 lanes, 20 of 109 with 1024).  Without the stores, 512 lanes with the last blocks in parts were
+            // taken for m = 645k, d = 3k, k = 8, b = 125: 133 us, where 1024 lanes in three parts of the batch take 110.
+            const double stores = !backward && kern.K == 8 && kern.LPT >= 4 ? (double)gpb * L.Q * kern.NT * kern.LPT * 4.0 / (thin ? 11.0 : 45.0) : 0.0;
             const double load = (double)kern.NT * kern.LPT * c->k * (4.0 + (backward ? 4.0 : es)) / 7.0;
             const double tiles = (double)((gpb + tg.tile_rows - 1) / tg.tile_rows) * (L.halves ? 2 : 1);
             const double latency = (double)gpb * kern.LPT * kern.K * (L.halves ? 2 : 1) / (unit == 16 ? 4 : 8) * 200.0;
-            double busy = per_cu * (more + (tg.nbuf == 2 || together > 1.5 ? 0.5 : 1.0) * less);
+            double busy = per_cu * (more + (tg.nbuf == 2 || together > 1.5 ? 0.5 : 1.0) * less + stores);
             if (busy < rounds * latency) busy = rounds * latency;
             return busy + per_cu * load + rounds * (6000.0 + tiles * (tg.nbuf == 2 ? 600.0 : 1500.0) / (together > 1.0 ? together : 1.0));
         };
