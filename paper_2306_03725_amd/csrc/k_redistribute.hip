@@ -335,7 +335,7 @@ template <int GS, int TURNS>
 __global__ void __launch_bounds__(256)
 k_regrow(int32_t* __restrict__ idx, const uint8_t* __restrict__ flags, int64_t m, uint32_t d, int k,
          uint32_t k0, uint32_t k1, uint32_t epoch_lo) {
-    __shared__ uint32_t list[4][TURNS * 64];   // turn * 64 + lane of the empty slots, then their first candidates
+    __shared__ uint32_t list[4][TURNS > 1 ? TURNS * 64 : 1];   // turn * 64 + lane of the empty slots, then their first candidates
     const int lane = threadIdx.x & 63, t = lane & (GS - 1);
     uint32_t* const mine_of = list[threadIdx.x >> 6];
     const int gshift = lane & ~(GS - 1);
@@ -356,21 +356,25 @@ k_regrow(int32_t* __restrict__ idx, const uint8_t* __restrict__ flags, int64_t m
     for (int r = 0; r < TURNS; ++r) {
         empty[r] = __ballot(is[r]);
         first[r] = n;
-        if (is[r]) mine_of[n + (uint32_t)__popcll(empty[r] & below)] = (uint32_t)(r * 64 + lane);
+        if (TURNS > 1 && is[r]) mine_of[n + (uint32_t)__popcll(empty[r] & below)] = (uint32_t)(r * 64 + lane);
         n += (uint32_t)__popcll(empty[r]);
         mine[r] = -1;   // (nobody asks for the columns of a full row)
         if (!is[r] && row_of(r, lane) < m && t < k && of_row(empty[r]) != 0) mine[r] = idx[(size_t)row_of(r, lane) * k + t];
     }
-    __syncthreads();
-    for (uint32_t q = (uint32_t)lane; q < n; q += 64) {
-        const uint32_t e = mine_of[q];
-        mine_of[q] = (uint32_t)draw_column(k0, k1, epoch_lo, (uint32_t)row_of((int)(e / 64), (int)(e % 64)), e % GS, 0u, d);
+    if constexpr (TURNS > 1) {
+        __syncthreads();
+        for (uint32_t q = (uint32_t)lane; q < n; q += 64) {
+            const uint32_t e = mine_of[q];
+            mine_of[q] = (uint32_t)draw_column(k0, k1, epoch_lo, (uint32_t)row_of((int)(e / 64), (int)(e % 64)), e % GS, 0u, d);
+        }
+        __syncthreads();
     }
-    __syncthreads();
 #pragma unroll
     for (int r = 0; r < TURNS; ++r) {
         const int64_t row = row_of(r, lane);
-        const int32_t own = is[r] ? (int32_t)mine_of[first[r] + (uint32_t)__popcll(empty[r] & below)] : 0;
+        int32_t own = 0;
+        if (TURNS > 1) own = is[r] ? (int32_t)mine_of[first[r] + (uint32_t)__popcll(empty[r] & below)] : 0;
+        else if (is[r]) own = draw_column(k0, k1, epoch_lo, (uint32_t)row, (uint32_t)t, 0u, d);   // one turn: no lane to pass a slot on to
         Mask todo = of_row(empty[r]);   // empty slots of my row, bit = slot
         {
             const int32_t have = is[r] ? own : mine[r];
