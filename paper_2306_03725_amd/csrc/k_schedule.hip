@@ -44,10 +44,20 @@ k_schedule(const int32_t* __restrict__ idx, int64_t m, int k, int shift, int rou
     // lane reads and writes its own row only, whatever the order in which the lanes of a wavefront run.
     uint8_t(*row)[K + 4] = &ord[0][0];
     const uint32_t n = (uint32_t)(min((int64_t)SCHED_NT, m - j0) * k), inv = k > 1 ? 0xFFFFFFFFu / (uint32_t)k + 1u : 0u;   // exact: n < 2^15
-#pragma unroll 8
-    for (uint32_t q = threadIdx.x; q < n; q += SCHED_NT) {
-        const uint32_t r = k > 1 ? __umulhi(q, inv) : q;   // label of the workgroup's
-        row[usl_order_row<GS>((int)r)][q - r * (uint32_t)k] = (uint8_t)((idx[j0 * k + q] >> shift) & (GS - 1));
+    // Loads of a lane in flight: with 8 and a check behind every one a small layer waited longer than for its own rows (m = 61k, d = 63k,
+    // k = 32, b = 29, slots and forward: 132 us, now 127; k = 64, m = 670k: 1085 and 1010); 32 take a workgroup off the compute unit
+    // (m = 200k, d = 8k, k = 32, b = 64: 187 and 143).
+    constexpr int AT_ONCE = K % 16 == 0 ? 16 : 8;
+#pragma unroll 1
+    for (uint32_t q0 = threadIdx.x; q0 < n; q0 += AT_ONCE * SCHED_NT) {
+        int32_t col[AT_ONCE];
+#pragma unroll
+        for (int u = 0; u < AT_ONCE; ++u) col[u] = idx[j0 * k + min(q0 + u * SCHED_NT, n - 1)];
+#pragma unroll
+        for (int u = 0; u < AT_ONCE; ++u) {
+            const uint32_t q = q0 + u * SCHED_NT, r = k > 1 ? __umulhi(q, inv) : q;   // label of the workgroup's
+            if (q < n) row[usl_order_row<GS>((int)r)][q - r * (uint32_t)k] = (uint8_t)((col[u] >> shift) & (GS - 1));
+        }
     }
     __syncthreads();
     uint32_t avail = Lists::build(lists[gl][lane], ord[gl][lane], k, deg0[gl],
