@@ -98,20 +98,25 @@ def one_pass_cut(cfg, cus=256):
     fpb = -(-(-(-runs * cfg.d // nfb)) // 32) * 32
     at_once = max(1, cus // nfb)
 
-    def windows(q):
+    def windows(q, labels):
         lists = min((14 if q == 4 else 16) * 2048 // fpb, 21 if q == 4 else 24)
-        run = max(4, min(lists * cfg.d // cfg.k, (15968 if q == 2 else 4672 if cfg.d <= 1024 else 7232) // runs) // 4 * 4)
+        run = max(4, min(lists * cfg.d // cfg.k, labels // runs) // 4 * 4)
         return equal_windows(cfg.m, full_rounds(-(-cfg.m // run), nfb, cus))[1] if runs == 1 else -(-cfg.m // (run * runs))
 
-    def rounds(q):
-        chains = -(-windows(q) // -(-windows(q) // at_once))
-        return -(-windows(q) // chains)
+    def rounds(nwin):
+        chains = -(-nwin // -(-nwin // at_once))
+        return -(-nwin // chains)
 
+    two, own = windows(2, 15968), windows(4, 4672)
+    four = own
+    if cfg.d > 1024:
+        wide = windows(4, 7232)
+        four = own if 11 * cfg.d // cfg.k <= 4672 and rounds(own) <= rounds(wide) else wide
     if cfg.d <= 1024 or 11 * cfg.d // cfg.k <= 4672:
         q = 4
     else:
-        q = 4 if 14 * cfg.d // cfg.k <= 7232 and windows(4) * nfb > cus and rounds(4) <= min(rounds(2), 5) else 2
-    nwin = windows(q)
+        q = 4 if 14 * cfg.d // cfg.k <= 7232 and four * nfb > cus and rounds(four) <= min(rounds(two), 5) else 2
+    nwin = four if q == 4 else two
     row = -(-cfg.d // 4) * 16   # bytes of an instance's sums
     if cfg.d > 65536 or nwin * 64 * row > PARTIAL_SUM_BYTES:
         return None

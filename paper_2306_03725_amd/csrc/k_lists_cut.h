@@ -59,33 +59,52 @@ inline Cut bwi_cut(int64_t m, int d, int k, int num_cu) {
 // leaves room for it, and where runs share activations (the places of the sums are then other ones).
 inline bool both_own(int Q, const Cut& cut) { return Q == 4 && (cut.wl <= BOTH4_OWN_LABELS || cut.S > 1); }
 
+// Chains of windows: as many as the compute units have room for, where there are more windows than that.
+inline int both_chains(const Cut& cut, int num_cu) {
+    const int at_once = num_cu > cut.nfb ? num_cu / cut.nfb : 1;
+    const int rounds = (cut.nwin + at_once - 1) / at_once;
+    return (cut.nwin + rounds - 1) / rounds;
+}
+
+// ... and the rounds of workgroups that they go through, one after the other on a compute unit
+inline int both_rounds(const Cut& cut, int num_cu) { const int chains = both_chains(cut, num_cu); return (cut.nwin + chains - 1) / chains; }
+
 // The form for both products: lists of 16 connections (half the registers go to the weight-gradient sums; with four
 // instances a lane has 32 slots instead of 36, hence 14), longer where the features do not fill the lanes twice over;
 // blocks of equal size; S runs where the layer is narrower than half a block.
 // Q: instances of a pass, 2 or 4 (both_q, below).
 inline Cut both_cut(int64_t m, int d, int k, int num_cu, int Q) {
-    Cut cut;
-    const bool four = Q == 4;
-    const int labels = !four ? BOTH2_LABELS : d <= NT ? BOTH4_OWN_LABELS : BOTH4_LABELS;
-    cut.S = d <= NT ? NF / d : 1;
-    if (cut.S > labels / 4) cut.S = labels / 4;   // a run has at least four labels, and the window has to fit LDS (d = 1)
-    cut.vd = cut.S * d;
-    cut.nfb = (cut.vd + NF - 1) / NF;
-    cut.fpb = ((cut.vd + cut.nfb - 1) / cut.nfb + 31) / 32 * 32;
-    const int64_t mean = four ? 14 : 16, longest = four ? 21 : 24;
-    const int64_t lists = mean * NF / cut.fpb < longest ? mean * NF / cut.fpb : longest;
-    const int64_t most = labels / cut.S;
-    int64_t run = lists * d / k;
-    run = run < most ? run : most;
-    run = run >= 4 ? run / 4 * 4 : 4;
-    if (cut.S == 1) {
-        equal_windows(&cut, m, full_rounds(num_cu, (m + run - 1) / run, cut.nfb));
-    } else {
-        cut.run = (int)run;
-        cut.wl = cut.run * cut.S;
-        cut.nwin = (int)((m + cut.wl - 1) / cut.wl);
-    }
-    return cut;
+    auto cut_of = [&](int labels) {   // with windows of that many at most
+        Cut cut;
+        cut.S = d <= NT ? NF / d : 1;
+        if (cut.S > labels / 4) cut.S = labels / 4;   // a run has at least four labels, and the window has to fit LDS (d = 1)
+        cut.vd = cut.S * d;
+        cut.nfb = (cut.vd + NF - 1) / NF;
+        cut.fpb = ((cut.vd + cut.nfb - 1) / cut.nfb + 31) / 32 * 32;
+        const int64_t mean = Q == 4 ? 14 : 16, longest = Q == 4 ? 21 : 24;
+        const int64_t lists = mean * NF / cut.fpb < longest ? mean * NF / cut.fpb : longest;
+        const int64_t most = labels / cut.S;
+        int64_t run = lists * d / k;
+        run = run < most ? run : most;
+        run = run >= 4 ? run / 4 * 4 : 4;
+        if (cut.S == 1) {
+            equal_windows(&cut, m, full_rounds(num_cu, (m + run - 1) / run, cut.nfb));
+        } else {
+            cut.run = (int)run;
+            cut.wl = cut.run * cut.S;
+            cut.nwin = (int)((m + cut.wl - 1) / cut.wl);
+        }
+        return cut;
+    };
+    if (Q != 4) return cut_of(BOTH2_LABELS);
+    const Cut own = cut_of(BOTH4_OWN_LABELS);
+    if (d <= NT) return own;
+    // Windows that leave the activations a place of their own, unless their lists would be short (fewer than 11 connections) or they
+    // make more rounds than longer ones.  usl_backward with windows of up to 4672 and of up to 7232 labels: m = 154k, d = 2762, k = 8,
+    // b = 64: 70 and 77 us; m = 6k, d = 3094, k = 8, b = 24: 29 and 33; m = 22k, d = 6747, k = 16, b = 64: 44 and 47; m = 41k, d = 13k,
+    // k = 32, b = 400: 185 and 179; two rounds and one, m = 200k, d = 12k, k = 32, b = 64: 250 and 169.
+    const Cut wide = cut_of(BOTH4_LABELS);
+    return (int64_t)11 * d / k <= (int64_t)BOTH4_OWN_LABELS && both_rounds(own, num_cu) <= both_rounds(wide, num_cu) ? own : wide;
 }
 
 // Parts of the batch in the kernel for both products: more than one where the (window, feature block) workgroups leave
@@ -107,13 +126,6 @@ inline int both_parts(const Cut& cut, int64_t m, int k, int num_cu, int rows, in
     return best;
 }
 
-// Chains of windows: as many as the compute units have room for, where there are more windows than that.
-inline int both_chains(const Cut& cut, int num_cu) {
-    const int at_once = num_cu > cut.nfb ? num_cu / cut.nfb : 1;
-    const int rounds = (cut.nwin + at_once - 1) / at_once;
-    return (cut.nwin + rounds - 1) / rounds;
-}
-
 // Instances that a pass of the kernel for both products takes together.  A pass is a chain of waits, so the fewer the better:
 // four, where windows that send 11 connections into a feature leave four rows room in LDS beside the activations (usl_backward with
 // four and two, float32: m = 200k, d = 12k, k = 32, b = 64: 174 and 188 us; m = 400k, d = 27k, k = 64, b = 64: 626 and 699); two, where even
@@ -128,9 +140,9 @@ inline int both_chains(const Cut& cut, int num_cu) {
 inline int both_q(int64_t m, int d, int k, int num_cu) {
     if (d <= NT || (int64_t)11 * d / k <= (int64_t)BOTH4_OWN_LABELS) return 4;
     if ((int64_t)14 * d / k > (int64_t)BOTH4_LABELS) return 2;
-    auto rounds = [&](const Cut& cut) { const int chains = both_chains(cut, num_cu); return (cut.nwin + chains - 1) / chains; };
     const Cut two = both_cut(m, d, k, num_cu, 2), four = both_cut(m, d, k, num_cu, 4);
-    return (int64_t)four.nwin * four.nfb > num_cu && rounds(four) <= rounds(two) && rounds(four) <= 5 ? 4 : 2;
+    const int rounds = both_rounds(four, num_cu);
+    return (int64_t)four.nwin * four.nfb > num_cu && rounds <= both_rounds(two, num_cu) && rounds <= 5 ? 4 : 2;
 }
 
 // How a batch of `rows` instances goes through: in passes of at most G, one part each, or at once in several parts.
