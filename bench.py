@@ -24,9 +24,9 @@ HBM_PEAK_GBPS = 8000.0   # MI355X published peak
 # They are measured offline (a counter run serialises the kernels) and go stale when a kernel changes: the
 # profile files carry the date of truth, these constants only repeat their per-call totals.
 MEASURED_TRAFFIC_BYTES = {
-    "large": {"backward": 3882038067, "backward_input": 2809659392, "forward": 988912026, "backward_weight": 983564288},
-    "large_wide": {"backward": 17548338790, "backward_input": 8440931942, "forward": 3191445914, "backward_weight": 3052090163},
-    "stress": {"backward": 172082960794, "backward_input": 206994145280, "forward": 29374283776, "backward_weight": 26389407334},
+    "large": {"backward": 3884554649, "backward_input": 2784703283, "forward": 989226598, "backward_weight": 983564288},
+    "large_wide": {"backward": 17481439641, "backward_input": 8376339660, "forward": 3186203033, "backward_weight": 3052299878},
+    "stress": {"backward": 171694568243, "backward_input": 204216152883, "forward": 29409096499, "backward_weight": 26389302476},
 }
 KERNELS_OF_CALL = {
     "forward": "k_interleave where one LDS read serves several instances, k_forward",

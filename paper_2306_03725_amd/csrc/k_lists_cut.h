@@ -111,7 +111,7 @@ inline Cut both_cut(int64_t m, int d, int k, int num_cu, int Q) {
 // compute units idle.  A workgroup loads its lists and weights and hands out its sums in about 20 us, a pass of its loop
 // takes about 4.4 (m = 31k, d = 1k, k = 32, b = 128: 179 us with 1 part, 116 with 2, 83 with 4, 77 with 6, 103 with 8, which
 // are two rounds); every part writes a weight gradient of its own, which the reader adds up.  Of 16 layers measured
-// (profiles/rules_measured.txt) the best number or within 5 % of it.  forced > 0: that many, if the batch has them.
+// (profiles/rules_measured.txt) the best number or within 6 % of it.  forced > 0: that many, if the batch has them.
 inline int both_parts(const Cut& cut, int64_t m, int k, int num_cu, int rows, int Q, int forced) {
     const int64_t wgs = (int64_t)cut.nwin * cut.nfb, passes = (rows + Q - 1) / Q, cu = num_cu;
     if (forced > 0) return (int)(forced < passes ? forced : passes);
@@ -128,15 +128,15 @@ inline int both_parts(const Cut& cut, int64_t m, int k, int num_cu, int rows, in
 
 // Instances that a pass of the kernel for both products takes together.  A pass is a chain of waits, so the fewer the better:
 // four, where windows that send 11 connections into a feature leave four rows room in LDS beside the activations (usl_backward with
-// four and two, float32: m = 200k, d = 12k, k = 32, b = 64: 174 and 188 us; m = 400k, d = 27k, k = 64, b = 64: 626 and 699); two, where even
-// windows of 7232 labels send fewer than 14 (too many windows; m = 670k, d = 32k, k = 64, b = 256, bfloat16: 3533 and 2830).
+// four and two, float32: m = 200k, d = 12k, k = 32, b = 64: 171 and 187 us; m = 400k, d = 27k, k = 64, b = 64: 617 and 698); two, where even
+// windows of 7232 labels send fewer than 14 (too many windows; m = 700k, d = 32k, k = 64, b = 256: 3312 and 2800).
 // In between the rounds of workgroups decide, one after the other on a compute unit: four where there are more workgroups than compute
 // units, in no more rounds than two and in five at most.  With six the chains' sums come from memory in every pass (m = 670k, d = 30k,
-// k = 64, bfloat16, b = 512: 5557 us with two, 6388 with four).  m = 670k, d = 16k, k = 32, b = 32, three rounds each: 355 and
-// 331; m = 300k, d = 24k, k = 48, b = 64, two and three rounds: 368 and 418; m = 130k, d = 15 360, k = 32, b = 128, less than one round of
-// windows: 200 (in two parts of the batch that fit a round) and 237.
-// The rule does not see the batch, which can decide it the other way: the six rounds above at b = 64 take 984 and 922, and
-// m = 130k, d = 15 000, where two parts of the windows of two do not fit a round, 168 and 140 at b = 64.
+// k = 64, bfloat16, b = 512: 5419 us with two, 5985 with four).  m = 670k, d = 16k, k = 32, b = 32, three rounds each: 348 and
+// 322; m = 300k, d = 24k, k = 48, b = 64, two and three rounds: 362 and 409; m = 130k, d = 15 360, k = 32, b = 128, less than one round of
+// windows: 202 (in two parts of the batch that fit a round) and 225.
+// The rule does not see the batch, which can decide it the other way: the six rounds above at b = 64 take 938 and 887, and
+// m = 130k, d = 15 000, where two parts of the windows of two do not fit a round, 169 and 141 at b = 64.
 inline int both_q(int64_t m, int d, int k, int num_cu) {
     if (d <= NT || (int64_t)11 * d / k <= (int64_t)BOTH4_OWN_LABELS) return 4;
     if ((int64_t)14 * d / k > (int64_t)BOTH4_LABELS) return 2;
