@@ -468,7 +468,7 @@ def main():
             roof["gather_note"] = ("the step's LDS gathers (%s) at the measured conflict-free rates of their widths "
                                    "would take %.3f ms; staging the rows those gathers read, at the measured L2 to "
                                    "LDS copy rate, %.3f ms; the step's algorithmic HBM bytes at the measured copy "
-                                   "rate, %.3f ms; these three do not overlap inside a product kernel"
+                                   "rate, %.3f ms; the product kernels run their copies and gathers in turn"
                                    % (", ".join("%.3g of %d bytes" % r for r in reads), t_gather, t_copy, t_hbm))
             roof["measured_ceilings_frac"] = round((t_gather + t_copy + t_hbm) / ms_per_step, 4)
         except Exception as exc:   # the headline line must survive a failure of an appended leg
