@@ -498,19 +498,16 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
             const double copy = (double)gpb * L.row_bytes / 42.0;
             // At most two wavefronts on a SIMD: they wait for their reads.  The factors are from workgroups of 512 lanes with two
             // labels each and of 1024 with one: m = 100k, d = 4k, k = 32, b = 128: forward 63 and 54 us, weight gradient 89 and 76;
-            // m = 200k, d = 8k, b = 64, bfloat16: 60.4 and 57.3, 83 and 70.
+            // m = 200k, d = 8k, b = 64, bfloat16: 60.4 and 57.3, 83 and 70.  (512 lanes with one label each lose nothing to 1024 in the
+            // weight gradient: m = 646k, d = 2k, k = 64, b = 31: 223 and 253.)
             const bool thin = kern.NT / 64 * res <= 8;
-            const double gather = (double)gpb * kern.NT * kern.LPT * kern.K * (L.halves ? 2 : 1) / reads_per_clk * (!thin ? 1.0 : backward ? 1.3 : 1.1);
+            const double waits = !thin ? 1.0 : !backward ? 1.1 : kern.LPT > 1 ? 1.3 : 1.0;
+            const double gather = (double)gpb * kern.NT * kern.LPT * kern.K * (L.halves ? 2 : 1) / reads_per_clk * waits;
             const double more = copy > gather ? copy : gather, less = copy > gather ? gather : copy;
-            // With four labels of eight slots a lane stores as much as half of what it reads: 11 bytes a clock beside the gathers of two
-            // wavefronts on a SIMD, 45 beside those of four (m = 524k, d = 3k, k = 8, b = 128: a pass takes 42 of 98 us longer than its
-            // copies and gathers with 512 lanes, 20 of 109 with 1024).  Without the stores, 512 lanes with the last blocks in parts were
-            // taken for m = 645k, d = 3k, k = 8, b = 125: 133 us, where 1024 lanes in three parts of the batch take 110.
-            const double stores = !backward && kern.K == 8 && kern.LPT >= 4 ? (double)gpb * L.Q * kern.NT * kern.LPT * 4.0 / (thin ? 11.0 : 45.0) : 0.0;
             const double load = (double)kern.NT * kern.LPT * c->k * (4.0 + (backward ? 4.0 : es)) / 7.0;
             const double tiles = (double)((gpb + tg.tile_rows - 1) / tg.tile_rows) * (L.halves ? 2 : 1);
             const double latency = (double)gpb * kern.LPT * kern.K * (L.halves ? 2 : 1) / (unit == 16 ? 4 : 8) * 200.0;
-            double busy = per_cu * (more + (tg.nbuf == 2 || together > 1.5 ? 0.5 : 1.0) * less + stores);
+            double busy = per_cu * (more + (tg.nbuf == 2 || together > 1.5 ? 0.5 : 1.0) * less);
             if (busy < rounds * latency) busy = rounds * latency;
             return busy + per_cu * load + rounds * (6000.0 + tiles * (tg.nbuf == 2 ? 600.0 : 1500.0) / (together > 1.0 ? together : 1.0));
         };
@@ -533,6 +530,7 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
             const int64_t slots = (int64_t)cus * res, last = tail_force > 0 ? (nblk + 1) / 2 : nblk > slots ? nblk % slots : 0;
             const int64_t tail = parts == 1 && !backward ? last : 0;
             int tail_gpb = 0;
+            const double whole = t;
             for (int T = tail_force > 0 ? tail_force : 2; tail > 0 && T <= groups && (T <= 16 || T == tail_force); ++T) {
                 const int per = (groups + T - 1) / T;
                 const int64_t items = tail * ((groups + per - 1) / per);
@@ -541,6 +539,10 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
                 if (with < t || tail_force > 0) { t = with; tail_gpb = per; }
                 if (tail_force > 0) break;
             }
+            // ... but labels of eight slots with two wavefronts on a SIMD have to win against another shape or split by 8 %: they wait for
+            // the stores of the scores, half as many as their reads, which the estimate leaves out (m = 645k, d = 3k, k = 8, b = 125:
+            // 512 lanes and a tail 78 us by the estimate, 123 measured; 1024 lanes in three parts 83 and 98).
+            if (tail_gpb && kern.K == 8 && kern.NT / 64 * res <= 8) t = t * 1.08 < whole ? t * 1.08 : whole;
             if (!best.kern.fn || t < best_t) {
                 best_t = t;
                 best.kern = kern;
