@@ -324,60 +324,51 @@ k_mark_rows_serial(TS* __restrict__ W, float* __restrict__ m1, float* __restrict
 // ---- regrow ---------------------------------------------------------------------------------
 // GS lanes own one row (GS = power of two >= k, <= 64); lane t of the group holds slot t.
 // flags == nullptr means every slot is empty (initial connectivity).
-// What bounds this is the vector unit.  The first candidates of all empty slots are drawn together, by as many lanes as there are
-// such slots in TURNS turns of a wavefront's rows, and compared in one short loop; where two columns of a row clash, which is
-// rare, the turn goes slot by slot, drawing on.  Slot by slot from the beginning, each candidate drawn by the whole group, took
-// 118 us at m = 500k, k = 32, 5 % empty; now 67.
-// TURNS: 8, or 1 where that would leave compute units without 16 wavefronts.
+// What bounds this is the vector unit.  The first candidates of a wavefront's empty slots are drawn together, every lane its own,
+// and compared in one short loop; where two columns of a row clash, which is rare but in narrow layers, the wavefront goes slot
+// by slot, drawing on.  (Slot by slot from the beginning, each candidate drawn by the whole group, took 118 us at m = 500k, d = 32k, k = 32,
+// 5 % empty, now 56.  A list of eight turns' empty slots, drawn by as few lanes as could, took 58 there, and longer where slots clash or
+// most are empty: m = 50k, d = 64, k = 64, one slot of ten 1425 us, now 1016; all slots of m = 500k, d = 32k, k = 32 268 and 201.)
+// TURNS of rows to a wavefront: 8 in the largest layers, whose workgroups it saves (a redistribution of 5 % with one and eight:
+// m = 3M, k = 32 1037 and 989 us; m = 670k, k = 64 483 and 442; m = 500k, k = 32 153 and 155; all slots of m = 100k, k = 32 64 and 96), unless
+// the layer is narrow and its slots clash (m = 50k, d = 64, k = 64: 803 and 1004).
 template <int GS> struct RowMask { typedef uint32_t T; };   // a bit per slot
 template <> struct RowMask<64> { typedef uint64_t T; };
 template <int GS, int TURNS>
 __global__ void __launch_bounds__(256)
 k_regrow(int32_t* __restrict__ idx, const uint8_t* __restrict__ flags, int64_t m, uint32_t d, int k,
          uint32_t k0, uint32_t k1, uint32_t epoch_lo) {
-    __shared__ uint32_t list[4][TURNS > 1 ? TURNS * 64 : 1];   // turn * 64 + lane of the empty slots, then their first candidates
-    const int lane = threadIdx.x & 63, t = lane & (GS - 1);
-    uint32_t* const mine_of = list[threadIdx.x >> 6];
-    const int gshift = lane & ~(GS - 1);
     typedef typename RowMask<GS>::T Mask;
     const Mask gmask = GS >= 32 ? (Mask)~(Mask)0 : (Mask)((1u << (GS & 31)) - 1u);
-    const uint64_t below = (1ull << lane) - 1ull;
+    const int lane = threadIdx.x & 63, t = lane & (GS - 1), gshift = lane & ~(GS - 1);
+    const int64_t row0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * (TURNS * 64 / GS) + lane / GS;
     auto of_row = [&](uint64_t ballot) { return (Mask)(ballot >> gshift) & gmask; };
     auto lowest = [&](Mask v) { return GS == 64 ? __ffsll((unsigned long long)v) - 1 : __ffs((int)v) - 1; };   // -1: none
-    const int64_t row0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * (TURNS * 64 / GS);   // the wavefront's first
-    auto row_of = [&](int turn, int l) { return row0 + turn * (64 / GS) + l / GS; };
-    uint64_t empty[TURNS];    // of the turn's lanes
-    int32_t mine[TURNS];
-    uint32_t first[TURNS], n = 0;
-    bool is[TURNS];
-#pragma unroll
-    for (int r = 0; r < TURNS; ++r) is[r] = row_of(r, lane) < m && t < k && (flags ? flags[(size_t)row_of(r, lane) * k + t] != 0 : true);
+    bool is[TURNS];   // my slot of the turn is empty
 #pragma unroll
     for (int r = 0; r < TURNS; ++r) {
-        empty[r] = __ballot(is[r]);
-        first[r] = n;
-        if (TURNS > 1 && is[r]) mine_of[n + (uint32_t)__popcll(empty[r] & below)] = (uint32_t)(r * 64 + lane);
-        n += (uint32_t)__popcll(empty[r]);
-        mine[r] = -1;   // (nobody asks for the columns of a full row)
-        if (!is[r] && row_of(r, lane) < m && t < k && of_row(empty[r]) != 0) mine[r] = idx[(size_t)row_of(r, lane) * k + t];
+        const int64_t row = row0 + r * (64 / GS);
+        is[r] = row < m && t < k && (flags ? flags[(size_t)row * k + t] != 0 : true);
     }
-    if constexpr (TURNS > 1) {
-        __syncthreads();
-        for (uint32_t q = (uint32_t)lane; q < n; q += 64) {
-            const uint32_t e = mine_of[q];
-            mine_of[q] = (uint32_t)draw_column(k0, k1, epoch_lo, (uint32_t)row_of((int)(e / 64), (int)(e % 64)), e % GS, 0u, d);
-        }
-        __syncthreads();
+    int32_t columns[TURNS];   // of the full slots, or -1 (nobody asks for the columns of a full row)
+#pragma unroll
+    for (int r = 0; r < TURNS; ++r) {
+        const int64_t row = row0 + r * (64 / GS);
+        const Mask empty = of_row(__ballot(is[r]));   // (of all lanes: not behind a condition)
+        columns[r] = -1;
+        if (row < m && t < k && !is[r] && empty != 0) columns[r] = idx[(size_t)row * k + t];
     }
 #pragma unroll
     for (int r = 0; r < TURNS; ++r) {
-        const int64_t row = row_of(r, lane);
-        int32_t own = 0;
-        if (TURNS > 1) own = is[r] ? (int32_t)mine_of[first[r] + (uint32_t)__popcll(empty[r] & below)] : 0;
-        else if (is[r]) own = draw_column(k0, k1, epoch_lo, (uint32_t)row, (uint32_t)t, 0u, d);   // one turn: no lane to pass a slot on to
-        Mask todo = of_row(empty[r]);   // empty slots of my row, bit = slot
+        const int64_t row = row0 + r * (64 / GS);
+        const bool empty = is[r];
+        Mask todo = of_row(__ballot(empty));   // empty slots of my row, bit = slot
+        if (!__any(empty)) continue;
+        int32_t mine = columns[r];
+        const int32_t own = draw_column(k0, k1, epoch_lo, (uint32_t)row, (uint32_t)t, 0u, d);   // (full slots' are not asked for; a branch per lane took 5 % longer)
+        int32_t* const at = idx + (size_t)row * k + t;
         {
-            const int32_t have = is[r] ? own : mine[r];
+            const int32_t have = empty ? own : mine;
             bool clash = false;
             for (Mask rest = todo; __any(rest != 0); rest &= rest - 1) {
                 const int ts = lowest(rest);
@@ -385,11 +376,11 @@ k_regrow(int32_t* __restrict__ idx, const uint8_t* __restrict__ flags, int64_t m
                 clash = clash || (rest != 0 && have == c && t != ts);
             }
             if (!__any(clash)) {
-                if (is[r]) idx[(size_t)row * k + t] = own;
+                if (empty) *at = own;
                 continue;
             }
         }
-        bool occupied = mine[r] >= 0;
+        bool occupied = mine >= 0;
         uint32_t attempt = 0;
         while (__any(todo != 0)) {
             const int ts = todo ? lowest(todo) : 0;
@@ -398,10 +389,10 @@ k_regrow(int32_t* __restrict__ idx, const uint8_t* __restrict__ flags, int64_t m
                 const int32_t next = draw_column(k0, k1, epoch_lo, (uint32_t)row, (uint32_t)ts, attempt, d);
                 if (attempt != 0) c = next;
             }
-            const Mask clash = of_row(__ballot(todo != 0 && occupied && mine[r] == c));
+            const Mask clash = of_row(__ballot(todo != 0 && occupied && mine == c));
             if (todo) {
                 if (clash == 0) {
-                    if (t == ts) { mine[r] = c; occupied = true; }
+                    if (t == ts) { mine = c; occupied = true; }
                     todo &= todo - 1;
                     attempt = 0;
                 } else {
@@ -409,7 +400,7 @@ k_regrow(int32_t* __restrict__ idx, const uint8_t* __restrict__ flags, int64_t m
                 }
             }
         }
-        if (is[r]) idx[(size_t)row * k + t] = mine[r];
+        if (empty) *at = mine;
     }
 }
 
@@ -471,7 +462,7 @@ usl_status regrow(usl_ctx* c, int32_t* idx, uint8_t* flags, bool all_empty, uint
     while (gs < k) gs <<= 1;
     const uint8_t* fl = all_empty ? nullptr : flags;
     const int64_t lanes = c->m * gs;
-    const bool many = lanes >= (int64_t)8 * 64 * 16 * c->num_cu;
+    const bool many = lanes >= (int64_t)8 * 64 * 256 * c->num_cu && c->d >= 16 * k;   // see the kernel
     const int64_t per = many ? 256 * 8 : 256;
     const unsigned grid = (unsigned)((lanes + per - 1) / per);
 #define USL_RG_T(GS, TURNS)                                                                    \
