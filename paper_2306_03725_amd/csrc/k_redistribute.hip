@@ -326,10 +326,11 @@ k_mark_rows_serial(TS* __restrict__ W, float* __restrict__ m1, float* __restrict
 // flags == nullptr means every slot is empty (initial connectivity).
 // What bounds this is the vector unit.  The first candidates of a wavefront's empty slots are drawn together, every lane its own,
 // and compared in one short loop; where two columns of a row clash, which is rare but in narrow layers, the wavefront goes slot
-// by slot, drawing on.  (Slot by slot from the beginning, each candidate drawn by the whole group, took 118 us at m = 500k, d = 32k, k = 32,
-// 5 % empty, now 56.  A list of eight turns' empty slots, drawn by as few lanes as could, took 58 there, and longer where slots clash or
-// most are empty: m = 50k, d = 64, k = 64, one slot of ten 1425 us, now 1016; all slots of m = 500k, d = 32k, k = 32 268 and 201.)
-// TURNS of rows to a wavefront: 8 in the largest layers, whose workgroups it saves (a redistribution of 5 % with one and eight:
+// by slot, drawing on.  (Slot by slot from the beginning, each candidate drawn by the whole group, took 109 us at m = 500k, d = 32k, k = 32,
+// 5 % empty, between other kernels, now 69.  A list of eight turns' empty slots, drawn by as few lanes as could, took 62 there, but longer
+// where slots clash or most are empty: m = 50k, d = 64, k = 64, one slot of ten 1425 us the call, now 1016; all slots of m = 500k, d = 32k,
+// k = 32 268 and 201.)
+// TURNS of rows to a wavefront: 8 in the largest layers, whose workgroups it saves (calls that redistribute 5 %, with one and eight:
 // m = 3M, k = 32 1037 and 989 us; m = 670k, k = 64 483 and 442; m = 500k, k = 32 153 and 155; all slots of m = 100k, k = 32 64 and 96), unless
 // the layer is narrow and its slots clash (m = 50k, d = 64, k = 64: 803 and 1004).
 template <int GS> struct RowMask { typedef uint32_t T; };   // a bit per slot

@@ -1,6 +1,6 @@
 """The oracle's pins once more against a build of the same C source with AddressSanitizer and
 UndefinedBehaviorSanitizer: an out-of-bounds access, a use of uninitialised stack, a signed overflow or a
-misaligned load in the checker would make its agreement with the pins worth less.  Runs in a child process
+misaligned load in the oracle would make its agreement with the pins worth less.  Runs in a child process
 (the sanitizer runtime has to be loaded before anything else).  No GPU."""
 import os
 import subprocess
