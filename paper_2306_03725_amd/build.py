@@ -10,7 +10,7 @@ LIB = os.path.join(HERE, "libusl.so")
 LIB_CEILINGS = os.path.join(HERE, "libusl_ceilings.so")   # measurement kernels, not part of the training path
 SOURCES = ["k_products_f32_q4.hip", "k_products_f32_q2.hip", "k_products_f32_q1.hip", "k_products_f32_halves.hip",
            "k_products_bf16_q4.hip", "k_products_bf16_q2.hip", "k_products_bf16_q1.hip", "usl_api.hip", "k_products.hip", "k_elementwise.hip", "k_backward_input.hip",
-           "k_redistribute.hip", "k_schedule.hip", "k_predict.hip", "k_sparse_grad.hip", "k_backward_input_lds.hip"]
+           "k_redistribute.hip", "k_schedule.hip", "k_predict.hip", "k_sparse_grad.hip", "k_step_small.hip", "k_backward_input_lds.hip"]
 # -packed-fp32-ops: packed FP32 VALU instructions are switched off (they have produced wrong
 # results on the test machines); -munsafe-fp-atomics: hardware float atomic add, no CAS loop.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-munsafe-fp-atomics",
@@ -127,7 +127,7 @@ def build(force=True, verbose=False):
     objs = []
     procs = []
     os.makedirs(os.path.join(HERE, "_build"), exist_ok=True)
-    deps = [os.path.join(CSRC, "usl_internal.h"), os.path.join(CSRC, "k_lists_cut.h"), os.path.join(CSRC, "k_matching.h"), os.path.join(CSRC, "k_lanes.h"), os.path.join(CSRC, "k_products_common.h"), os.path.join(CSRC, "k_products_inst.h"),
+    deps = [os.path.join(CSRC, "usl_internal.h"), os.path.join(CSRC, "k_lists_cut.h"), os.path.join(CSRC, "k_matching.h"), os.path.join(CSRC, "k_lanes.h"), os.path.join(CSRC, "k_adam.h"), os.path.join(CSRC, "k_products_common.h"), os.path.join(CSRC, "k_products_inst.h"),
             os.path.join(CSRC, "k_products.h"), os.path.join(HERE, "..", "include", "usl.h")]
     newest_dep = max(os.path.getmtime(p) for p in deps)
     for src in SOURCES:

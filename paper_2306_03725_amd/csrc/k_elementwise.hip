@@ -1,7 +1,7 @@
 // Sparse-target one-vs-all losses (binary cross-entropy, squared hinge: loss + gradient in one pass
 // over the scores) and Adam.
 // Both are pure HBM streams: one read and one write of every element, 16 bytes per lane.
-#include "usl_internal.h"
+#include "k_adam.h"
 
 namespace {
 
@@ -170,40 +170,8 @@ k_loss_tiles(float* zg, const int64_t* __restrict__ tgt_off, const int32_t* __re
     }
 }
 
-// One block adds the per-block sums in a fixed order: the loss is reproducible run to run.
-template <int NT_>
-__device__ __forceinline__ void sum_loss(const usl_loss_sum& sum) {
-    __shared__ double red[NT_ / 64];
-    double s = 0.0;
-    for (size_t q = threadIdx.x; q < sum.n; q += NT_) s += sum.partials[q];
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int q = 0; q < NT_ / 64; ++q) t += red[q];
-        *sum.loss = (float)((double)sum.scale * t);
-    }
-}
 __global__ void __launch_bounds__(1024)
 k_bce_finish(usl_loss_sum sum) { sum_loss<1024>(sum); }
-
-template <typename TS> struct WIo;
-template <> struct WIo<float> {
-    static __device__ __forceinline__ float get(const float* W, size_t f) { return W[f]; }
-    static __device__ __forceinline__ void put(float* W, size_t f, float v) { W[f] = v; }
-};
-template <> struct WIo<uint16_t> {
-    static __device__ __forceinline__ float get(const uint16_t* W, size_t f) { return usl_bf16_to_f32(W[f]); }
-    static __device__ __forceinline__ void put(uint16_t* W, size_t f, float v) { W[f] = usl_f32_to_bf16(v); }
-};
-
-__device__ __forceinline__ float adam_one(float w, float gw, float& a, float& v, float lr, float b1,
-                                          float b2, float eps, float ic1, float ic2) {
-    a = fmaf(b1, a, (1.f - b1) * gw);
-    v = fmaf(b2, v, (1.f - b2) * gw * gw);
-    return w - lr * (a * ic1) / (sqrtf(v * ic2) + eps);
-}
 
 template <typename TS>
 __global__ void __launch_bounds__(256)

@@ -91,7 +91,9 @@ __global__ void k_identity_order(int64_t n, int K, uint8_t* __restrict__ perm) {
 usl_status usl_build_slot_order(usl_ctx* c, const int32_t* idx, int K, int unit) {
     USL_TRY(usl_reserve(c, (void**)&c->slot_order, &c->slot_order_cap, (size_t)c->m * K));
     const int shift = unit == 2 ? 1 : 0;  // two single bfloat16 columns share a bank word
-    const int rounds = usl_order_rounds(c);
+    // A layer whose step is k_step_small's gathers too little for an order to pay: over 22 such layers of m * k * max_b >= 2^21 forward and weight gradient
+    // take as long with it as without, and a forward on new connectivity 10 to 14 us instead of 26 to 79.  (And the scores have the step's bits.)
+    const int rounds = usl_step_small_applies(c) && !getenv("USL_TUNE_ROUNDS") ? 0 : usl_order_rounds(c);
     const unsigned grid = (unsigned)((c->m + SCHED_NT - 1) / SCHED_NT);
     if (rounds <= 0) {
         hipLaunchKernelGGL(k_identity_order, dim3(c->num_cu * 4), dim3(256), 0, c->stream, c->m * K, K, c->slot_order);

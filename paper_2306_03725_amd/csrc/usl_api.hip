@@ -33,7 +33,7 @@ extern "C" usl_status usl_destroy(usl_ctx* c) {
         void* bufs[] = {c->bce_partials, c->sel_hist, c->prune_flags, c->tie_counts, c->counter64,
                         c->csc_ptr, c->csc_cursor, c->csc_order, c->csc_slot, c->csc_w, c->gT, c->gxT, c->nz_flags,
                         c->slot_order, c->topk_cand, c->sub_idx, c->sub_W, c->predict_out, c->gw_part,
-                        c->nz_state, c->nz_lab, c->nz_val, c->idx_print, c->xi, c->xr, c->tgt_bits};
+                        c->nz_state, c->nz_lab, c->nz_val, c->idx_print, c->xi, c->xr, c->tgt_bits, c->small_sums, c->small_order};
         (void)hipStreamSynchronize(c->stream);
         for (void* p : bufs)
             if (p) (void)hipFree(p);
@@ -387,6 +387,11 @@ extern "C" usl_status usl_train_step(usl_ctx* c, const void* x, const int32_t* i
     if (!(eps >= 0.f) || !(lr == lr)) USL_FAIL(c, USL_EINVAL, "eps < 0 or lr is NaN");
     USL_TRY(check_batch(c, b));
     USL_TRY(usl_prepare_device(c));
+    if (usl_step_small_applies(c)) {
+        const double c1 = 1.0 - pow((double)beta1, (double)t), c2 = 1.0 - pow((double)beta2, (double)t);
+        return usl_launch_step_small(c, x, idx, W, m1, m2, tgt_off, tgt_lab, loss_kind, scale, lr, beta1, beta2, eps, (float)(1.0 / c1),
+                                     (float)(1.0 / c2), g, grad_W, grad_x, loss, b);
+    }
     // the interleaved copy of x that forward makes serves the weight gradient of this call too
     struct KeepX {
         usl_ctx* c;

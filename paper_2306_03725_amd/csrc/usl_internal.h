@@ -44,6 +44,9 @@ struct usl_ctx {
     // bank-aware order in which a label's slots are visited by the LDS gathers (performance only)
     uint8_t* slot_order;      size_t slot_order_cap;   // [m][padded k] slot read at step s
     const int32_t* slot_order_for; // idx pointer it was computed from (NULL = stale)
+    // the step of a small layer (k_step_small.hip)
+    float* small_sums;        size_t small_sums_cap;   // [workgroups][b][d] of the input gradient
+    uint16_t* small_order;    size_t small_order_cap;  // [m*k] a workgroup's connections in the order of their columns; looked at before use
     bool part_of_batch;            // usl_predict's chunks: the sums are taken in the order of a whole batch's, however short the chunk
     bool no_order;                 // label-subset context: idx is new on every call, an order would not pay
     void* xi;                 size_t xi_cap;   // activations interleaved for the LDS gathers (k_products.hip)
@@ -227,6 +230,11 @@ usl_status usl_launch_loss(usl_ctx* ctx, int loss_kind, const float* out, const 
 usl_status usl_noalloc_setup(usl_ctx* ctx);
 usl_status usl_launch_loss_noalloc(usl_ctx* ctx, int loss_kind, const float* out, const int64_t* tgt_off,
                                    const int32_t* tgt_lab, float scale, float* g, float* loss, int32_t b);
+// The whole training step of a small layer in two launches (k_step_small.hip).
+bool usl_step_small_applies(const usl_ctx* ctx);
+usl_status usl_launch_step_small(usl_ctx* ctx, const void* x, const int32_t* idx, void* W, float* m1, float* m2, const int64_t* tgt_off,
+                                 const int32_t* tgt_lab, int loss_kind, float scale, float lr, float beta1, float beta2, float eps, float inv_c1,
+                                 float inv_c2, float* g, float* grad_W, float* grad_x, float* loss, int32_t b);
 usl_status usl_launch_adam(usl_ctx* ctx, void* W, const float* grad_W, float* m1, float* m2,
                            float lr, float beta1, float beta2, float eps, float inv_c1,
                            float inv_c2, const usl_loss_sum& sum);
