@@ -776,7 +776,9 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
                         o = r.g;
                         sum += __uint_as_float(__float_as_uint(r.l) & (uint32_t)__builtin_amdgcn_sbfe((int)others[l], (uint32_t)(g * Q + q) & 31u, 1u));
                     }
-                    (out + ((size_t)(g * Q + q) * m + j0))[(uint32_t)jl] = o;
+                    // past the caches: as ordinary stores they push rows of x out of the L2 (forward of m = 1M, d = 2000, k = 8, b = 32: 42.1 and 39.0 us;
+                    // m = 600k, d = 20k, k = 32, b = 128: 331 and 320; m = 500k, d = 32k, b = 256: 761 and 751)
+                    __builtin_nontemporal_store(o, out + ((size_t)(g * Q + q) * m + j0) + (uint32_t)jl);
                 }
             lost += (double)sum;
         }
