@@ -7,6 +7,7 @@ enum ProductKind { FORWARD, FORWARD_LOSS, WEIGHT_GRADIENT };   // FORWARD_LOSS: 
 
 struct ProductKernel {
     const void* fn;        // nullptr: no such kernel
+    const void* even;      // the same for blocks of fewer labels than its lanes take
     int K, LPT, NT;        // padded fan-in, labels per lane, lanes
     int transpose_bytes;   // LDS its prologue and epilogue need
 };

@@ -37,7 +37,10 @@ struct Geom {
 // The blocks of labels from `first` on (INT_MAX: none), `blocks` of them, take the batch in parts of `groups` groups: blockIdx.x
 // runs over them part by part, behind the others.  (Forward's alone: as part of Geom it made the compiler's weight gradient
 // 3 % slower at m = 500k, d = 32k.)
-struct Tail { int first, blocks, groups, share; };
+struct Tail {
+    int first, blocks, groups, share;
+    int labels;            // of any block: at most its lanes times the labels of a lane, a multiple of 32
+};
 
 static constexpr int ROW_LDS_MAX = 160 * 1024 - 512;    // largest tile
 static constexpr int HALF_COLS = 32768;                 // columns per half of a row in two halves
@@ -693,17 +696,19 @@ struct LossArgs {
     double* partials;
     const uint32_t* targets;   // [b / 32][m], see usl_ctx::tgt_bits
 };
-template <int K, int LPT, int NT, typename TS, int Q, bool HALVES, bool LOSS>
+// EVEN: blocks of tail.labels labels, not of as many as the lanes take.  (An instance of its own: with the number known only at run time the others'
+// prologues came out otherwise and they were up to 4 % slower.)
+template <int K, int LPT, int NT, typename TS, int Q, bool HALVES, bool LOSS, bool EVEN>
 __global__ void __launch_bounds__(NT)
 k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS* __restrict__ W, float* __restrict__ out,
           int64_t m, int k, int b, Geom tg, const uint8_t* __restrict__ perm, LossArgs loss, Tail tail) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const uint32_t lds0 = lds_base(lds_raw);
     const Turn turn(tg, tail);
-    const int64_t j0 = (int64_t)turn.block * (NT * LPT);
+    const int64_t j0 = (int64_t)turn.block * (EVEN ? tail.labels : NT * LPT), end = EVEN ? min(m, j0 + tail.labels) : m;
     if (LOSS)   // the first words of target bits come to the L2 while the labels' rows are brought in (1 % of the step at m = 500k, b = 256)
         touch_lines<NT>(reinterpret_cast<const char*>(loss.targets + (size_t)(turn.g0 * Q >> 5) * m + j0), 0,
-                        ((int)min((int64_t)NT * LPT, m - j0) * 4 + 127) / 128, lds0 + (uint32_t)tg.dummy, (int)threadIdx.x);
+                        ((int)min((int64_t)NT * LPT, end - j0) * 4 + 127) / 128, lds0 + (uint32_t)tg.dummy, (int)threadIdx.x);
     uint32_t pk[LPT][K / 2];
     WReg<TS, K> w[LPT];
 #pragma unroll
@@ -711,16 +716,16 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
         const int64_t row0 = j0 + (int64_t)l * NT;
         if constexpr (raw_rows<TS, K, NT>()) {
             RawRows<TS, K> raw;
-            raw.load_idx(perm, idx, row0, m, k, (uint32_t)tg.zero_col);
-            raw.load_w(W, row0, m, k);
+            raw.load_idx(perm, idx, row0, end, k, (uint32_t)tg.zero_col);
+            raw.load_w(W, row0, end, k);
             unpack_idx<K, TS>(raw, k, reinterpret_cast<uint32_t*>(lds_raw), pk[l]);
             unpack_w<K, NT>(raw, k, reinterpret_cast<uint32_t*>(lds_raw), w[l].v);
         } else {
             SlotOrder<K> so;
-            so.load(perm, row0 + threadIdx.x, row0 + threadIdx.x < m);
+            so.load(perm, row0 + threadIdx.x, row0 + threadIdx.x < end);
             if (l) __syncthreads();
-            fetch_idx<K>(idx, row0, m, k, (uint32_t)tg.zero_col, reinterpret_cast<uint32_t*>(lds_raw), so, pk[l]);
-            fetch_w<K, NT>(W, row0, m, k, reinterpret_cast<uint32_t*>(lds_raw), so, w[l].v);
+            fetch_idx<K>(idx, row0, end, k, (uint32_t)tg.zero_col, reinterpret_cast<uint32_t*>(lds_raw), so, pk[l]);
+            fetch_w<K, NT>(W, row0, end, k, reinterpret_cast<uint32_t*>(lds_raw), so, w[l].v);
         }
     }
     const uint32_t zbyte = lds0 + HALF_COLS * 4u;
@@ -729,7 +734,8 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
         if (threadIdx.x < 4) reinterpret_cast<uint32_t*>(lds_raw)[HALF_COLS + threadIdx.x] = 0u;
     }
     const int g0 = turn.g0, g1 = turn.g1;
-    const int nlab = (int)min((int64_t)NT * LPT, m - j0);
+    const int nlab = (int)min((int64_t)NT * LPT, end - j0);
+    const int wave0 = EVEN ? __builtin_amdgcn_readfirstlane((int)threadIdx.x & ~63) : 0;   // a wavefront without labels gathers nothing
     // Q <= 2: the scores of a group are written while the next group is gathered, before the last label's gathers (a store
     // right before the next copy would make that copy's wait include it; four stores in a row would hold the wavefront
     // at the memory pipeline).  Q = 4 has no registers left for that, and a quarter of the waits.  All labels' losses
@@ -802,7 +808,7 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
                 for (int q = 0; q < Q; ++q) acc[q] = HALVES && part ? prev[DELAY ? l : 0][q] : 0.f;   // the first half's sums
                 keep_packed(pk[l]);
                 __builtin_amdgcn_s_setprio(1);
-                label_dot<K, Q, HALVES>(pk[l], w[l].v, base, zbyte, acc);
+                if (!EVEN || wave0 + l * NT < nlab) label_dot<K, Q, HALVES>(pk[l], w[l].v, base, zbyte, acc);
                 __builtin_amdgcn_s_setprio(0);
                 // finish the sums here; left alone the compiler sinks the multiply-adds into the guarded store
                 // and keeps every gathered value alive until then
@@ -844,15 +850,15 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
 // grad_W[j][t] = sum_i g[i][j] x[i][idx[j][t]].  With the batch split every part of it leaves a partial
 // gradient (part_stride elements apart) that a later kernel adds up in a fixed order.  A label whose gradients of a
 // group are zero in all 64 lanes skips its gathers (Algorithm 3 skips zero entries).
-template <int K, int LPT, int NT, typename TS, int Q, bool HALVES>
+template <int K, int LPT, int NT, typename TS, int Q, bool HALVES, bool EVEN>
 __global__ void __launch_bounds__(NT)
 k_backward_weight(const float* __restrict__ g, const char* __restrict__ xi, const int32_t* __restrict__ idx, float* __restrict__ grad_W,
-                  int64_t m, int k, int b, Geom tg, const uint8_t* __restrict__ perm, size_t part_stride, const uint32_t* __restrict__ gate) {
+                  int64_t m, int k, int b, Geom tg, const uint8_t* __restrict__ perm, size_t part_stride, const uint32_t* __restrict__ gate, int labels) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     if (gate && *gate == 0) return;   // the gradient is almost all zeros: the kernels over its nonzeros do the work
     const uint32_t lds0 = lds_base(lds_raw);
     const uint32_t part = tg.parts_first ? blockIdx.x : blockIdx.y;
-    const int64_t j0 = (int64_t)(tg.parts_first ? blockIdx.y : blockIdx.x) * (NT * LPT);
+    const int64_t j0 = (int64_t)(tg.parts_first ? blockIdx.y : blockIdx.x) * (EVEN ? labels : NT * LPT), end = EVEN ? min(m, j0 + labels) : m;
     uint32_t pk[LPT][K / 2];
     float acc[LPT][K];
 #pragma unroll
@@ -860,12 +866,12 @@ k_backward_weight(const float* __restrict__ g, const char* __restrict__ xi, cons
         const int64_t row0 = j0 + (int64_t)l * NT;
         if constexpr (raw_rows<float, K, NT>()) {
             RawRows<TS, K> raw;
-            raw.load_idx(perm, idx, row0, m, k, (uint32_t)tg.zero_col);
+            raw.load_idx(perm, idx, row0, end, k, (uint32_t)tg.zero_col);
             unpack_idx<K, TS>(raw, k, reinterpret_cast<uint32_t*>(lds_raw), pk[l]);
         } else {
             SlotOrder<K> so;
-            so.load(perm, row0 + threadIdx.x, row0 + threadIdx.x < m);
-            fetch_idx<K>(idx, row0, m, k, (uint32_t)tg.zero_col, reinterpret_cast<uint32_t*>(lds_raw), so, pk[l]);
+            so.load(perm, row0 + threadIdx.x, row0 + threadIdx.x < end);
+            fetch_idx<K>(idx, row0, end, k, (uint32_t)tg.zero_col, reinterpret_cast<uint32_t*>(lds_raw), so, pk[l]);
         }
 #pragma unroll
         for (int t = 0; t < K; ++t) acc[l][t] = 0.f;
@@ -876,7 +882,7 @@ k_backward_weight(const float* __restrict__ g, const char* __restrict__ xi, cons
         if (threadIdx.x < 4) reinterpret_cast<uint32_t*>(lds_raw)[HALF_COLS + threadIdx.x] = 0u;
     }
     const int g0 = (int)part * tg.groups_per_block, g1 = min(tg.groups, g0 + tg.groups_per_block);
-    const int nlab = (int)min((int64_t)NT * LPT, m - j0);
+    const int nlab = (int)min((int64_t)NT * LPT, end - j0);
     // The gradients of the next group come from HBM and are requested one group ahead, right after this group's row
     // copy: before it, the copy's wait would wait for them too.  (Q = 4 on wide blocks has no registers for that: their
     // lines are brought to the L2 one group ahead instead and read behind the copy.)
@@ -931,8 +937,8 @@ k_backward_weight(const float* __restrict__ g, const char* __restrict__ xi, cons
     for (int l = 0; l < LPT; ++l) {
         const int64_t row0 = j0 + (int64_t)l * NT;
         SlotOrder<K> so;
-        so.load(perm, row0 + threadIdx.x, row0 + threadIdx.x < m);
-        store_rows<K, NT>(acc[l], grad_W + (size_t)part * part_stride, row0, m, k, reinterpret_cast<uint32_t*>(lds_raw), so);
+        so.load(perm, row0 + threadIdx.x, row0 + threadIdx.x < end);
+        store_rows<K, NT>(acc[l], grad_W + (size_t)part * part_stride, row0, end, k, reinterpret_cast<uint32_t*>(lds_raw), so);
     }
 }
 

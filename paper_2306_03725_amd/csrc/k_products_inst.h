@@ -15,10 +15,12 @@ constexpr int labels_per_lane(int K, int slots) { return slots / K < 1 ? 1 : slo
 template <int K, typename TS, int Q, bool HALVES>
 ProductKernel pick(ProductKind kind, int shape) {
     constexpr int L = K == 8 ? 4 : labels_per_lane(K, 64), L2 = labels_per_lane(K, 128);
+#define USL_KIND(LPT, NT, EVEN)                                                                                \
+    (kind == WEIGHT_GRADIENT ? (const void*)k_backward_weight<K, LPT, NT, TS, Q, HALVES, EVEN>                  \
+     : kind == FORWARD_LOSS  ? (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, true, EVEN>                    \
+                             : (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, false, EVEN>)
 #define USL_PICK(LPT, NT)                                                                                      \
-    ProductKernel{kind == WEIGHT_GRADIENT ? (const void*)k_backward_weight<K, LPT, NT, TS, Q, HALVES>           \
-                  : kind == FORWARD_LOSS  ? (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, true>             \
-                                          : (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, false>, K, LPT, NT, transpose_bytes<K, NT>()}
+    ProductKernel{USL_KIND(LPT, NT, false), USL_KIND(LPT, NT, true), K, LPT, NT, transpose_bytes<K, NT>()}
     if constexpr (Q > 1) {
         if (shape == 0) return USL_PICK(1, 256);
         if (shape == 1) return USL_PICK(L, 512);
@@ -37,7 +39,8 @@ ProductKernel pick(ProductKind kind, int shape) {
         if (shape == 2) return USL_PICK(L2, 512);
     }
 #undef USL_PICK
-    return ProductKernel{nullptr, 0, 0, 0, 0};
+#undef USL_KIND
+    return ProductKernel{nullptr, nullptr, 0, 0, 0, 0};
 }
 
 template <typename TS, int Q, bool HALVES>
@@ -49,7 +52,7 @@ ProductKernel pick_k(ProductKind kind, int K, int shape) {
         case 32: return pick<32, TS, Q, HALVES>(kind, shape);
         case 48: return pick<48, TS, Q, HALVES>(kind, shape);
         case 64: return pick<64, TS, Q, HALVES>(kind, shape);
-        default: return ProductKernel{nullptr, 0, 0, 0, 0};
+        default: return ProductKernel{nullptr, nullptr, 0, 0, 0, 0};
     }
 }
 
