@@ -18,6 +18,24 @@ __device__ __forceinline__ void sum_loss(const usl_loss_sum& sum) {
     }
 }
 
+// The first `lead` blocks (of 256 lanes) of the kernel that ends a step whose loss forward computed: the first of them adds up the loss, the
+// others take the targets' bits back, four instances to a wavefront.  In front of the others, which are at work by the time these
+// wait for the target lists.
+static inline unsigned step_end_blocks(const usl_loss_sum& sum) { return sum.partials ? (unsigned)((1 + (sum.targets.b + 15) / 16 + 7) / 8 * 8) : 0u; }   // (a multiple of 8: the others keep their XCDs)
+__device__ __forceinline__ void step_end(const usl_loss_sum& sum, unsigned lead) {
+    if (blockIdx.x == 0) { sum_loss<256>(sum); return; }
+    const usl_targets& t = sum.targets;
+    if (!t.off) return;
+    const int n = ((int)lead - 1) * 4;
+    for (int i = (int)(blockIdx.x - 1) * 4 + (int)(threadIdx.x >> 6); i < t.b; i += n) {
+        const int64_t p1 = t.off[i + 1];
+        for (int64_t p = t.off[i] + (threadIdx.x & 63); p < p1; p += 64) {
+            const int64_t j = t.lab[p];
+            if (j >= 0 && j < t.m) t.bits[(size_t)(i >> 5) * t.m + j] = 0u;   // all bits of the word go in this launch; nobody reads them
+        }
+    }
+}
+
 template <typename TS> struct WIo;
 template <> struct WIo<float> {
     static __device__ __forceinline__ float get(const float* W, size_t f) { return W[f]; }

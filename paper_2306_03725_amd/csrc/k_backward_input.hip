@@ -513,8 +513,8 @@ usl_status build_csc(usl_ctx* c, const int32_t* idx) {
 usl_status usl_idx_print_ready(usl_ctx* c) {
     if (!c->idx_print) {
         size_t cap = 0;
-        USL_TRY(usl_reserve(c, (void**)&c->idx_print, &cap, 64));
-        hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, c->stream, reinterpret_cast<uint32_t*>(c->idx_print), (size_t)16);
+        USL_TRY(usl_reserve(c, (void**)&c->idx_print, &cap, USL_PRINT_WORDS * 8));
+        hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, c->stream, reinterpret_cast<uint32_t*>(c->idx_print), (size_t)USL_PRINT_WORDS * 2);
     }
     return USL_OK;
 }
@@ -546,7 +546,7 @@ usl_status usl_bwd_input_prepare(usl_ctx* c, const int32_t* idx, int32_t b) {
     USL_TRY(usl_reserve(c, (void**)&c->nz_flags, &c->nz_flags_cap, (size_t)ntile * c->m));
     if (!c->counter64) {
         size_t cap = 0;
-        USL_TRY(usl_reserve(c, (void**)&c->counter64, &cap, 64));
+        USL_TRY(usl_reserve(c, (void**)&c->counter64, &cap, USL_PRINT_WORDS * 8));
     }
     return USL_OK;
 }

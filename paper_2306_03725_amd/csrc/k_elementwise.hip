@@ -177,10 +177,10 @@ template <typename TS>
 __global__ void __launch_bounds__(256)
 k_adam(TS* __restrict__ W, const float* __restrict__ gW, float* __restrict__ m1,
        float* __restrict__ m2, size_t n, float lr, float b1, float b2, float eps, float ic1,
-       float ic2, usl_loss_sum sum) {
-    if (sum.partials && blockIdx.x == gridDim.x - 1) sum_loss<256>(sum);
-    const size_t stride = (size_t)gridDim.x * 256 * 4;
-    for (size_t f = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4; f < n; f += stride) {
+       float ic2, usl_loss_sum sum, unsigned lead) {
+    if (blockIdx.x < lead) { step_end(sum, lead); return; }
+    const size_t stride = (size_t)(gridDim.x - lead) * 256 * 4;
+    for (size_t f = ((size_t)(blockIdx.x - lead) * 256 + threadIdx.x) * 4; f < n; f += stride) {
         if (f + 4 <= n) {
             const float4 g4 = *reinterpret_cast<const float4*>(gW + f);
             float4 a4 = *reinterpret_cast<const float4*>(m1 + f);
@@ -270,16 +270,17 @@ __global__ void __launch_bounds__(256)
 k_adam_staged(TS* __restrict__ W, const float* __restrict__ stage, const uint32_t* __restrict__ pos, int parts, size_t part_stride,
               const uint32_t* __restrict__ gate, const uint32_t* __restrict__ stale, float* __restrict__ gW,
               float* __restrict__ m1, float* __restrict__ m2, size_t n, float lr, float b1, float b2, float eps, float ic1,
-              float ic2, usl_loss_sum sum) {
-    if (sum.partials && blockIdx.x == gridDim.x - 1) sum_loss<256>(sum);
+              float ic2, usl_loss_sum sum, unsigned lead) {
+    if (blockIdx.x < lead) { step_end(sum, lead); return; }
+    const unsigned block = blockIdx.x - lead;
     const bool listed = gate && *gate == 0;
     const bool poison = !listed && *stale != 0;
     const float nan = __uint_as_float(0x7FC00000u);
     const size_t n4 = n / 4;
-    const size_t per_xcd = (n4 + 7) / 8, first = (size_t)(blockIdx.x & 7) * per_xcd;
+    const size_t per_xcd = (n4 + 7) / 8, first = (size_t)(block & 7) * per_xcd;
     const size_t last = first + per_xcd < n4 ? first + per_xcd : n4;
-    const size_t stride = (size_t)(gridDim.x / 8) * 256;
-    if (blockIdx.x == 0 && threadIdx.x < (n & 3)) {   // the ragged end
+    const size_t stride = (size_t)((gridDim.x - lead) / 8) * 256;
+    if (block == 0 && threadIdx.x < (n & 3)) {   // the ragged end
         const size_t f = n4 * 4 + threadIdx.x;
         if (poison) {
             gW[f] = nan;
@@ -291,7 +292,7 @@ k_adam_staged(TS* __restrict__ W, const float* __restrict__ stage, const uint32_
             WIo<TS>::put(W, f, w);
         }
     }
-    for (size_t v = first + (size_t)(blockIdx.x >> 3) * 256 + threadIdx.x; v < last; v += stride) {
+    for (size_t v = first + (size_t)(block >> 3) * 256 + threadIdx.x; v < last; v += stride) {
         const size_t f = v * 4;
         float4 g4;
         if (listed) {
@@ -337,7 +338,7 @@ k_adam_staged(TS* __restrict__ W, const float* __restrict__ stage, const uint32_
 usl_status usl_reserve_loss_partials(usl_ctx* c) {
     const size_t rows = (size_t)((c->m + BCE_CHUNK - 1) / BCE_CHUNK) * (size_t)c->max_b;
     const size_t tiles = (size_t)((c->m + LT_TL - 1) / LT_TL) * (size_t)((c->max_b + 31) / 32);
-    const size_t forward = usl_forward_blocks(c) + (size_t)c->max_b;   // and one for every instance's targets
+    const size_t forward = usl_forward_blocks(c);
     const size_t most = rows > tiles ? rows : tiles;
     return usl_reserve(c, (void**)&c->bce_partials, &c->bce_partials_cap, (most > forward ? most : forward) * sizeof(double));
 }
@@ -356,7 +357,7 @@ usl_status usl_launch_loss(usl_ctx* c, int loss_kind, const float* out, const in
     else                       { if (vec) USL_LOSS(true, LOSS_SQH); else USL_LOSS(false, LOSS_SQH); }
 #undef USL_LOSS
     USL_TRY(usl_check_launch(c, "loss"));
-    hipLaunchKernelGGL(k_bce_finish, dim3(1), dim3(1024), 0, c->stream, usl_loss_sum{c->bce_partials, nblk, scale, loss});
+    hipLaunchKernelGGL(k_bce_finish, dim3(1), dim3(1024), 0, c->stream, usl_loss_sum{c->bce_partials, nblk, scale, loss, {}});
     return usl_check_launch(c, "loss_finish");
 }
 
@@ -397,7 +398,7 @@ usl_status usl_launch_loss_noalloc(usl_ctx* c, int loss_kind, const float* out, 
     else                       { if (vec) USL_LOSS(true, LOSS_SQH); else USL_LOSS(false, LOSS_SQH); }
 #undef USL_LOSS
     USL_TRY(usl_check_launch(c, "loss (static scratch)"));
-    hipLaunchKernelGGL(k_bce_finish, dim3(1), dim3(1024), 0, c->stream, usl_loss_sum{partials, nblk, scale, loss});
+    hipLaunchKernelGGL(k_bce_finish, dim3(1), dim3(1024), 0, c->stream, usl_loss_sum{partials, nblk, scale, loss, {}});
     return usl_check_launch(c, "loss_finish (static scratch)");
 }
 
@@ -420,7 +421,7 @@ usl_status usl_launch_loss_tiles(usl_ctx* c, int loss_kind, float* zg, const int
     *sampled_labels = (uint64_t)((nlb + LT_SAMPLE - 1) / LT_SAMPLE) * LT_TL;
     if (b_end >= b) {   // the last group: every tile of the batch has left its sums
         const size_t nblk = (size_t)nlb * (size_t)((b + 31) / 32);
-        hipLaunchKernelGGL(k_bce_finish, dim3(1), dim3(1024), 0, c->stream, usl_loss_sum{c->bce_partials, nblk, scale, loss});
+        hipLaunchKernelGGL(k_bce_finish, dim3(1), dim3(1024), 0, c->stream, usl_loss_sum{c->bce_partials, nblk, scale, loss, {}});
     }
     return usl_check_launch(c, "loss_finish");
 }
@@ -436,12 +437,14 @@ usl_status usl_launch_adam(usl_ctx* c, void* W, const float* grad_W, float* m1, 
     const bool aligned = ((uintptr_t)W % 16 == 0) && ((uintptr_t)grad_W % 16 == 0) &&
                          ((uintptr_t)m1 % 16 == 0) && ((uintptr_t)m2 % 16 == 0);
     if (!aligned) USL_FAIL(c, USL_EINVAL, "W, grad_W, m1, m2 must be 16-byte aligned");
+    const unsigned lead = step_end_blocks(sum);
     if (c->storage == USL_F32)
-        hipLaunchKernelGGL(k_adam<float>, dim3((unsigned)blocks), dim3(256), 0, c->stream, (float*)W,
-                           grad_W, m1, m2, n, lr, beta1, beta2, eps, inv_c1, inv_c2, sum);
+        hipLaunchKernelGGL(k_adam<float>, dim3((unsigned)blocks + lead), dim3(256), 0, c->stream, (float*)W,
+                           grad_W, m1, m2, n, lr, beta1, beta2, eps, inv_c1, inv_c2, sum, lead);
     else
-        hipLaunchKernelGGL(k_adam<uint16_t>, dim3((unsigned)blocks), dim3(256), 0, c->stream,
-                           (uint16_t*)W, grad_W, m1, m2, n, lr, beta1, beta2, eps, inv_c1, inv_c2, sum);
+        hipLaunchKernelGGL(k_adam<uint16_t>, dim3((unsigned)blocks + lead), dim3(256), 0, c->stream,
+                           (uint16_t*)W, grad_W, m1, m2, n, lr, beta1, beta2, eps, inv_c1, inv_c2, sum, lead);
+    if (sum.targets.off) c->tgt_bits_set = false;
     return usl_check_launch(c, "adam");
 }
 
@@ -467,13 +470,14 @@ usl_status usl_launch_adam_staged(usl_ctx* c, void* W, const usl_staged& st, con
     const bool aligned = ((uintptr_t)W % 16 == 0) && ((uintptr_t)grad_W % 16 == 0) &&
                          ((uintptr_t)m1 % 16 == 0) && ((uintptr_t)m2 % 16 == 0);
     if (!aligned) USL_FAIL(c, USL_EINVAL, "W, grad_W, m1, m2 must be 16-byte aligned");
-    const unsigned blocks = staged_blocks(c, n);
+    const unsigned blocks = staged_blocks(c, n), lead = step_end_blocks(sum);
     if (c->storage == USL_F32)
-        hipLaunchKernelGGL(k_adam_staged<float>, dim3(blocks), dim3(256), 0, c->stream, (float*)W, st.stage, st.pos, st.parts, st.part_stride,
-                           gate, st.stale, grad_W, m1, m2, n, lr, beta1, beta2, eps, inv_c1, inv_c2, sum);
+        hipLaunchKernelGGL(k_adam_staged<float>, dim3(blocks + lead), dim3(256), 0, c->stream, (float*)W, st.stage, st.pos, st.parts, st.part_stride,
+                           gate, st.stale, grad_W, m1, m2, n, lr, beta1, beta2, eps, inv_c1, inv_c2, sum, lead);
     else
-        hipLaunchKernelGGL(k_adam_staged<uint16_t>, dim3(blocks), dim3(256), 0, c->stream, (uint16_t*)W, st.stage, st.pos, st.parts,
-                           st.part_stride, gate, st.stale, grad_W, m1, m2, n, lr, beta1, beta2, eps, inv_c1, inv_c2, sum);
+        hipLaunchKernelGGL(k_adam_staged<uint16_t>, dim3(blocks + lead), dim3(256), 0, c->stream, (uint16_t*)W, st.stage, st.pos, st.parts,
+                           st.part_stride, gate, st.stale, grad_W, m1, m2, n, lr, beta1, beta2, eps, inv_c1, inv_c2, sum, lead);
+    if (sum.targets.off) c->tgt_bits_set = false;
     return usl_check_launch(c, "adam (staged gradient)");
 }
 

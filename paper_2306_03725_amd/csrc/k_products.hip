@@ -123,17 +123,10 @@ __global__ void k_fill_zero(float* __restrict__ p, size_t n) {
     for (; i < n; i += s) p[i] = 0.f;
 }
 
-// Sets the bits of the targets (usl_ctx::tgt_bits).  Wavefront q of n takes instances q, q + n, ...
-struct TargetMarks {
-    const int64_t* off;    // nullptr: nothing to mark
-    const int32_t* lab;
-    uint32_t* bits;
-    int64_t m;
-    int b;
-    int row0;              // in k_interleave: the first row of blocks that does this
-};
+// Sets the bits of the targets (usl_ctx::tgt_bits).  Wavefront q of n takes instances q, q + n, ...  The kernel that ends the step
+// takes them back (step_end).
 constexpr int MARK_WAVES = 4;   // of a block of 256 lanes
-__device__ __forceinline__ void mark_targets(const TargetMarks& t, int q, int n) {
+__device__ __forceinline__ void mark_targets(const usl_targets& t, int q, int n) {
     for (int i = q; i < t.b; i += n) {
         const int64_t p1 = t.off[i + 1];
         for (int64_t p = t.off[i] + (threadIdx.x & 63); p < p1; p += 64) {
@@ -142,18 +135,33 @@ __device__ __forceinline__ void mark_targets(const TargetMarks& t, int q, int n)
         }
     }
 }
+// What a step needs before forward: the targets marked, and the fingerprint of idx compared for the backward product where lists stand
+// (a launch of its own takes 4 to 8 us).  Done by block `at` of n blocks of 256 lanes.
+struct Before {
+    usl_targets targets;      // off = nullptr: nothing to do
+    const uint32_t* idx;      // nullptr: nothing to compare
+    size_t n_words;
+    uint64_t* print;
+    __host__ __device__ int print_blocks() const { return idx ? USL_PRINT_SUMS / MARK_WAVES : 0; }
+    int blocks() const { return print_blocks() + (targets.b + MARK_WAVES - 1) / MARK_WAVES; }
+};
+__device__ __forceinline__ void before_forward(const Before& w, int at, int n) {
+    const int first = w.print_blocks(), wave = (int)(threadIdx.x >> 6);
+    if (at < first) usl_idx_fingerprint_sums<1>(w.idx, w.n_words, w.print, USL_PRINT_BOTH_PRODUCTS, 0, at * MARK_WAVES + wave, 0);
+    else mark_targets(w.targets, (at - first) * MARK_WAVES + wave, (n - first) * MARK_WAVES);
+}
 __global__ void __launch_bounds__(256)
-k_mark_targets(TargetMarks t) { mark_targets(t, (int)(blockIdx.x * MARK_WAVES + (threadIdx.x >> 6)), (int)gridDim.x * MARK_WAVES); }
+k_before_forward(Before w) { before_forward(w, (int)blockIdx.x, (int)gridDim.x); }
 
 // xi[group][column][Q instances] from x[b][d]; columns past d and instances past b are zeros.
-// grid (blocks of 256 columns, groups); with targets to mark some rows of blocks more, which do that (a launch of its own
-// takes 5 us)
+// grid (blocks of 256 columns, groups); in a training step some rows of blocks more, which mark the targets and compare the
+// fingerprint (a launch of its own takes 5 us): from row `row0` on
 template <typename TS, int Q>
 __global__ void __launch_bounds__(256)
-k_interleave(const TS* __restrict__ x, TS* __restrict__ xi, int b, int d, int cols, TargetMarks marks) {
+k_interleave(const TS* __restrict__ x, TS* __restrict__ xi, int b, int d, int cols, Before before, int row0) {
     const int c = blockIdx.x * 256 + threadIdx.x, g = blockIdx.y;
-    if (marks.off && g >= marks.row0) {
-        mark_targets(marks, (int)(((g - marks.row0) * gridDim.x + blockIdx.x) * MARK_WAVES + (threadIdx.x >> 6)), (int)((gridDim.y - marks.row0) * gridDim.x) * MARK_WAVES);
+    if (before.targets.off && g >= row0) {
+        before_forward(before, (int)((g - row0) * gridDim.x + blockIdx.x), (int)((gridDim.y - row0) * gridDim.x));
         return;
     }
     if (c >= cols) return;
@@ -602,15 +610,14 @@ usl_status launch(usl_ctx* c, const Launch& p, void** args, const char* what) {
     return usl_check_launch(c, what);
 }
 
-usl_status interleave(usl_ctx* c, const void* x, int b, int Q, int row_bytes, void** to, size_t* cap, TargetMarks marks = TargetMarks{}) {
+usl_status interleave(usl_ctx* c, const void* x, int b, int Q, int row_bytes, void** to, size_t* cap, const Before& before = Before{}) {
     const int es = c->storage == USL_F32 ? 4 : 2, groups = (b + Q - 1) / Q, cols = row_bytes / (Q * es);
     const int qmax = 4;   // sized once, for the largest batch any later call can bring
     const size_t need = (size_t)((c->max_b + qmax - 1) / qmax) * qmax * ((size_t)c->d + 16) * es;
     USL_TRY(usl_reserve(c, to, cap, max_sz(need, (size_t)groups * row_bytes)));
-    const int blocks = (cols + 255) / 256, per_row = blocks * MARK_WAVES, mark_rows = marks.off ? (b + per_row - 1) / per_row : 0;
-    marks.row0 = groups;
-    const dim3 grid((unsigned)blocks, (unsigned)(groups + mark_rows < 65535 ? groups + mark_rows : 65535));
-#define USL_IL(TS, QQ) hipLaunchKernelGGL((k_interleave<TS, QQ>), grid, dim3(256), 0, c->stream, (const TS*)x, (TS*)*to, b, c->d, cols, marks)
+    const int blocks = (cols + 255) / 256, more_rows = before.targets.off ? (before.blocks() + blocks - 1) / blocks : 0;
+    const dim3 grid((unsigned)blocks, (unsigned)(groups + more_rows < 65535 ? groups + more_rows : 65535));
+#define USL_IL(TS, QQ) hipLaunchKernelGGL((k_interleave<TS, QQ>), grid, dim3(256), 0, c->stream, (const TS*)x, (TS*)*to, b, c->d, cols, before, groups)
     if (es == 4) { if (Q == 4) USL_IL(float, 4); else if (Q == 2) USL_IL(float, 2); else USL_IL(float, 1); }
     else { if (Q == 4) USL_IL(uint16_t, 4); else if (Q == 2) USL_IL(uint16_t, 2); else USL_IL(uint16_t, 1); }
 #undef USL_IL
@@ -618,15 +625,14 @@ usl_status interleave(usl_ctx* c, const void* x, int b, int Q, int row_bytes, vo
 }
 
 // The interleaved activations of this call, in scratch of the context (or x itself, if it is laid out that way).
-// Inside usl_train_step the copy that forward made serves the backward products too.  marks: targets to mark on the way.
-usl_status activations(usl_ctx* c, const Layout& L, const void* x, int b, const void** xi, const TargetMarks& marks = TargetMarks{}) {
+// Inside usl_train_step the copy that forward made serves the backward products too.  before: what else is to be done on the way.
+usl_status activations(usl_ctx* c, const Layout& L, const void* x, int b, const void** xi, const Before& before = Before{}) {
     *xi = x;
     const bool copies = L.copy && (c->xi_of != x || c->xi_q != L.Q || c->xi_row_bytes != L.row_bytes);
-    const bool along = copies && (b + L.Q - 1) / L.Q < 65535;   // (k_interleave's grid has room for a row of blocks more)
-    if (marks.off && !along)
-        hipLaunchKernelGGL(k_mark_targets, dim3((unsigned)((b + MARK_WAVES - 1) / MARK_WAVES)), dim3(256), 0, c->stream, marks);
+    const bool along = copies && (b + L.Q - 1) / L.Q < 65535 - 32;   // k_interleave's grid has room for the fingerprint's blocks and more, a row each at worst
+    if (before.targets.off && !along) hipLaunchKernelGGL(k_before_forward, dim3((unsigned)before.blocks()), dim3(256), 0, c->stream, before);
     if (!L.copy) return USL_OK;
-    if (copies) USL_TRY(interleave(c, x, b, L.Q, L.row_bytes, &c->xi, &c->xi_cap, along ? marks : TargetMarks{}));
+    if (copies) USL_TRY(interleave(c, x, b, L.Q, L.row_bytes, &c->xi, &c->xi_cap, along ? before : Before{}));
     *xi = c->xi;
     c->xi_of = c->xi_keep ? x : nullptr;
     c->xi_q = L.Q;
@@ -707,102 +713,12 @@ usl_status run_forward_few(usl_ctx* c, const Layout& L, const void* x, const int
 
 namespace {
 
-// What k_forward's loss leaves to do: the gradient and the loss of the targets, a few per instance.  Their scores are taken
-// once more, in k_forward's order of additions (the same bits): 16 lanes bring the slots of a target, and one of them adds
-// up in the order of the steps, eight steps' reads of LDS together (one by one the chain took 17 us instead of 13 at
-// m = 1987, k = 64, b = 259, 36 targets).  A label listed twice for an instance counts once: the exchange shows who came
-// second, for the gradient of a target has other bits than without one, unless the scale is 0 or the loss NaN.  (Taking the
-// label's bit back atomically would tell too, but the words of the labels that many instances have are fought over: 6.3 us
-// instead of 4.6 at m = 5505, k = 8, b = 220.)  Block i of the first b: instance i, its targets' part of the loss goes to
-// partials[i].  Block b, if there is one, compares the fingerprint of idx for the backward product (a launch of its own took
-// 4 to 8 us).
-template <typename TS>
-__global__ void __launch_bounds__(1024)
-k_loss_positives(const TS* __restrict__ x, const int32_t* __restrict__ idx, const TS* __restrict__ W, float* __restrict__ g, int64_t m,
-                 int d, int k, int K, bool halves, const uint8_t* __restrict__ perm, int b, const int64_t* __restrict__ tgt_off,
-                 const int32_t* __restrict__ tgt_lab, uint32_t* __restrict__ bits, int kind, float scale, double* __restrict__ partials,
-                 size_t n_words, uint64_t* __restrict__ print) {
-    constexpr int PER = 64;   // targets at a time
-    __shared__ float2 slots[PER][65];        // {weight, activation} of a slot; zeros behind the last one
-    __shared__ uint8_t upper[PER][64];       // whether its column is in the second half of a row in two halves
-    __shared__ __align__(8) uint8_t order[PER][64];   // slot of a step
-    __shared__ double red[16];
-    const int i = blockIdx.x;
-    if (i == b) {
-        usl_idx_fingerprint_block(reinterpret_cast<const uint32_t*>(idx), n_words, print, USL_PRINT_BOTH_PRODUCTS, 0);
-        return;
-    }
-    const int64_t p1 = tgt_off[i + 1];
-    const TS* row = x + (size_t)i * d;
-    const int q16 = threadIdx.x >> 4;
-    const float2* mine = slots[q16];
-    double lost = 0.0;
-    for (int64_t p = tgt_off[i] + (threadIdx.x >> 4); p < p1; p += PER) {   // the lanes of a target are of one wavefront
-        const int64_t j = tgt_lab[p];
-        if (j < 0 || j >= m) continue;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {   // (order, indices and weights are under way together)
-            const int s = q * 16 + (int)(threadIdx.x & 15);
-            if (s >= K) continue;
-            order[q16][s] = perm ? perm[j * K + s] : (uint8_t)s;
-            float2 v = make_float2(0.f, 0.f);
-            int col = 0;
-            if (s < k) {
-                col = idx[j * k + s];
-                v = make_float2(usl_load_f32<TS>(W, (size_t)j * k + s), usl_load_f32<TS>(row, (size_t)col));
-            }
-            slots[q16][s] = v;
-            upper[q16][s] = col >= HALF_COLS ? 1 : 0;
-        }
-        wave_sync();
-        if ((threadIdx.x & 15) == 0) {
-            float z = 0.f;
-            for (int part = 0; part < (halves ? 2 : 1); ++part) {
-#pragma unroll 1
-                for (int s0 = 0; s0 < K; s0 += 8) {   // eight steps' reads together (K is a multiple of 8)
-                    const uint2 eight = *reinterpret_cast<const uint2*>(order[q16] + s0);
-                    float2 v[8];
-                    bool on[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const uint32_t t = ((u < 4 ? eight.x : eight.y) >> (8 * (u & 3))) & 0xFFu;
-                        v[u] = mine[t];
-                        on[u] = !halves || upper[q16][t] == part;
-                    }
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        if constexpr (sizeof(TS) == 4) {
-                            if (on[u]) z = fmaf(v[u].x, v[u].y, z);
-                        } else if (u & 1) {
-                            z = dot2(__float_as_uint(v[u - 1].y) >> 16 | __float_as_uint(v[u].y), __float_as_uint(v[u - 1].x) >> 16 | __float_as_uint(v[u].x), z);
-                        }
-                    }
-                }
-            }
-            const usl_loss_of r = usl_loss_one(kind, z, 1.f, scale);
-            const float before = atomicExch(g + (size_t)i * m + j, r.g);
-            const bool first = __float_as_uint(before) != __float_as_uint(r.g) || r.l != r.l;
-            if (first) lost += (double)r.l;
-            if (first || scale == 0.f) bits[(size_t)(i >> 5) * m + j] = 0u;   // all bits of the word go in this launch; nobody reads them
-        }
-        wave_sync();
-    }
-    for (int o = 32; o > 0; o >>= 1) lost += __shfl_down(lost, o);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = lost;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int q = 0; q < 16; ++q) t += red[q];
-        partials[i] = t;
-    }
-}
-
 size_t target_words(const usl_ctx* c) { return (size_t)((c->max_b + 31) / 32) * (size_t)c->m; }
 
-// the forward kernel over the whole batch, with or without the loss (then marks says what the targets are; the bits are set
-// here and taken back by k_loss_positives)
+// the forward kernel over the whole batch, with or without the loss (then `before` says what the targets are; their bits are set
+// here and taken back by the kernel that ends the step)
 usl_status run_forward(usl_ctx* c, const Layout& L, const void* x, const int32_t* idx, const void* W, float* out, int32_t b, LossArgs loss,
-                       size_t* blocks, TargetMarks marks = TargetMarks{}) {
+                       size_t* blocks, Before before = Before{}) {
     const Launch p = choose(c, L, b, loss.kind >= 0 ? FORWARD_LOSS : FORWARD);
     const uint8_t* perm = nullptr;
     const void* xi = nullptr;
@@ -813,17 +729,17 @@ usl_status run_forward(usl_ctx* c, const Layout& L, const void* x, const int32_t
         if (had != c->tgt_bits_cap || c->tgt_bits_set)   // new, or a call before failed half way
             hipLaunchKernelGGL(k_fill_zero, dim3(c->num_cu * 4), dim3(256), 0, c->stream, reinterpret_cast<float*>(c->tgt_bits), words);
         c->tgt_bits_set = true;
-        marks.bits = c->tgt_bits;
+        before.targets.bits = c->tgt_bits;
         loss.targets = c->tgt_bits;
     }
-    USL_TRY(activations(c, L, x, b, &xi, marks));
+    USL_TRY(activations(c, L, x, b, &xi, before));
     int64_t m = c->m;
     int k = c->k, bb = b;
     Geom tg = p.geom;
     if (loss.kind >= 0) {
         *blocks = (size_t)p.nblk * (size_t)p.G + (size_t)p.extra;
         USL_TRY(usl_reserve_loss_partials(c));
-        USL_TRY(usl_reserve(c, (void**)&c->bce_partials, &c->bce_partials_cap, (*blocks + (size_t)b) * sizeof(double)));   // more only with parts asked for by hand
+        USL_TRY(usl_reserve(c, (void**)&c->bce_partials, &c->bce_partials_cap, *blocks * sizeof(double)));   // more only with parts asked for by hand
         loss.partials = c->bce_partials;
     }
     Tail tail = p.tail;
@@ -861,19 +777,13 @@ usl_status usl_launch_forward_loss(usl_ctx* c, const void* x, const int32_t* idx
                                    const int64_t* tgt_off, const int32_t* tgt_lab, float scale, float* loss, usl_loss_sum* sum) {
     size_t blocks = 0;
     const Layout L = layout_of(c, b, x);
-    USL_TRY(run_forward(c, L, x, idx, W, g, b, LossArgs{loss_kind, scale, nullptr, nullptr}, &blocks, TargetMarks{tgt_off, tgt_lab, nullptr, c->m, b, 0}));
+    usl_targets targets = {tgt_off, tgt_lab, nullptr, c->m, b};
     const bool check = c->lf[1].built_for == idx;   // lists that the backward product will use
-    const dim3 grid((unsigned)(b + (check ? 1 : 0)));
-#define USL_POS(TS)                                                                                                              \
-    hipLaunchKernelGGL(k_loss_positives<TS>, grid, dim3(1024), 0, c->stream, (const TS*)x, idx, (const TS*)W, g, c->m, c->d, c->k, L.K,   \
-                       L.halves, c->no_order ? nullptr : c->slot_order, b, tgt_off, tgt_lab, c->tgt_bits, loss_kind, scale, c->bce_partials + blocks, \
-                       (size_t)c->m * c->k, c->idx_print)
-    if (c->storage == USL_F32) USL_POS(float); else USL_POS(uint16_t);
-#undef USL_POS
-    USL_TRY(usl_check_launch(c, "loss of the targets"));
-    c->tgt_bits_set = false;
+    USL_TRY(run_forward(c, L, x, idx, W, g, b, LossArgs{loss_kind, scale, nullptr, nullptr}, &blocks,
+                        Before{targets, check ? reinterpret_cast<const uint32_t*>(idx) : nullptr, (size_t)c->m * c->k, c->idx_print}));
     c->print_done = check;
-    *sum = usl_loss_sum{c->bce_partials, blocks + (size_t)b, scale, loss};
+    targets.bits = c->tgt_bits;
+    *sum = usl_loss_sum{c->bce_partials, blocks, scale, loss, targets};
     return USL_OK;
 }
 

@@ -18,6 +18,8 @@
 // Fan-ins are padded to K, the next multiple of 8 up to 32, 48 or 64; padding slots have weight 0 and read the column of
 // zeros (a real column times weight 0 would make NaN of an infinity that the label has no connection to).
 #pragma once
+#include <type_traits>
+
 #include "usl_internal.h"
 
 namespace usl_products {
@@ -684,12 +686,9 @@ __device__ __forceinline__ uint32_t lds_base(const void* p) {
 
 // ------------------------------------------------------------------------------------------------ forward
 // out[i][j] = sum_t W[j][t] x[i][idx[j][t]].  grid (label blocks, parts of the batch), or the other way round.
-// With a loss (training): out receives the gradient of the loss by the score, for a target of 0 (k_loss_positives writes that
-// of the few others), and the workgroup's part of the loss, targets left out, goes to partials[block].  The scores then
-// never go to memory: the separate pass over them took 24 us at m = 200k, b = 64 and 170 us at m = 500k, b = 256.
-// Which labels are targets comes as one bit per score; a lane reads a word for 32 instances at a time.  (Added up with
-// the others and subtracted afterwards, a target far on the right side of its margin would leave rounding errors of a
-// loss that it does not have, and NaN where that loss overflows.)
+// With a loss (training): out receives the gradient of the loss by the score, and the workgroup's part of the loss goes to
+// partials[block].  The scores then never go to memory: the separate pass over them took 24 us at m = 200k, b = 64 and 170 us at
+// m = 500k, b = 256.  Which labels are targets comes as one bit per score; a lane reads a word for 32 instances at a time.
 struct LossArgs {
     int kind;           // usl_loss_one's
     float scale;
@@ -744,10 +743,10 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
     constexpr bool DELAY = Q <= 2;
     float prev[DELAY ? LPT : 1][Q] = {};
     double lost = 0.0;
-    // Bit i % 32 of others[l]: instance i has another target than the label.  Good for 32 instances, before `until`; loaded
+    // Bit i % 32 of marks[l]: the label is a target of instance i.  Good for 32 instances, before `until`; loaded
     // with the tile that leaves them and waited for together with that tile: a load still under way when the losses are
     // added up would be waited for there, with the stores and the warm-up loads behind it (50 of 825 us at m = 500k, b = 256).
-    uint32_t others[LPT];
+    uint32_t marks[LPT];
     int until = -1;
     auto load_targets = [&](int first, int last) {   // for the instances first .. last, at most 32 of them
         if (!LOSS || last < until) return;
@@ -758,14 +757,14 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
             int jl = (int)threadIdx.x + l * NT;
             asm volatile("" : "+v"(jl));
             const uint32_t* p = loss.targets + (size_t)(first >> 5) * m + j0;
-            others[l] = jl < nlab ? p[(uint32_t)jl] : 0u;
+            marks[l] = jl < nlab ? p[(uint32_t)jl] : 0u;
             behind[l] = jl < nlab && (first & 31) != 0 && (first | 31) + 1 < b ? p[m + jl] : 0u;
         }
         const uint32_t later = (1u << (first & 31)) - 1u;   // the bits of the second word
 #pragma unroll
         for (int l = 0; l < LPT; ++l) {
-            others[l] = ~((behind[l] & later) | (others[l] & ~later));
-            asm volatile("" : "+v"(others[l]));
+            marks[l] = (behind[l] & later) | (marks[l] & ~later);
+            asm volatile("" : "+v"(marks[l]));
         }
     };
     auto put = [&](int g, int l, const float (&z)[Q]) {
@@ -773,19 +772,27 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
         asm volatile("" : "+v"(jl));
         if (jl < nlab) {
             float sum = 0.f;
+            // Targets are few: a wavefront without one among these scores takes the short form of the loss (a step at m = 670k, d = 16k, b = 32:
+            // 584 us with the general form for all, 571 with both).  A kernel of its own for the targets, which took their scores once more, cost
+            // 8 us a step at m = 31k, d = 1k, b = 128 and at m = 200k, d = 8k, b = 64, 13 at m = 500k, b = 256.
+            const uint32_t hits = LOSS ? __builtin_amdgcn_ubfe(marks[l], (uint32_t)(g * Q) & 31u, (uint32_t)Q) : 0u;
+            auto finish = [&](auto any_target) {
 #pragma unroll
-            for (int q = 0; q < Q; ++q)
-                if (g * Q + q < b) {
-                    float o = z[q];
-                    if (LOSS) {
-                        const usl_loss_of r = usl_loss_one(loss.kind, o, 0.f, loss.scale);
-                        o = r.g;
-                        sum += __uint_as_float(__float_as_uint(r.l) & (uint32_t)__builtin_amdgcn_sbfe((int)others[l], (uint32_t)(g * Q + q) & 31u, 1u));
+                for (int q = 0; q < Q; ++q)
+                    if (g * Q + q < b) {
+                        float o = z[q];
+                        if (LOSS) {
+                            const usl_loss_of r = usl_loss_one(loss.kind, o, any_target.value && (hits >> q & 1u) ? 1.f : 0.f, loss.scale);
+                            o = r.g;
+                            sum += r.l;
+                        }
+                        // past the caches: as ordinary stores they push rows of x out of the L2 (forward of m = 1M, d = 2000, k = 8, b = 32: 42.1 and 39.0 us;
+                        // m = 600k, d = 20k, k = 32, b = 128: 331 and 320; m = 500k, d = 32k, b = 256: 761 and 751)
+                        __builtin_nontemporal_store(o, out + ((size_t)(g * Q + q) * m + j0) + (uint32_t)jl);
                     }
-                    // past the caches: as ordinary stores they push rows of x out of the L2 (forward of m = 1M, d = 2000, k = 8, b = 32: 42.1 and 39.0 us;
-                    // m = 600k, d = 20k, k = 32, b = 128: 331 and 320; m = 500k, d = 32k, b = 256: 761 and 751)
-                    __builtin_nontemporal_store(o, out + ((size_t)(g * Q + q) * m + j0) + (uint32_t)jl);
-                }
+            };
+            if (LOSS && __builtin_expect(__any(hits != 0u), 0)) finish(std::true_type());
+            else finish(std::false_type());
             lost += (double)sum;
         }
     };

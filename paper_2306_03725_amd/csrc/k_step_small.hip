@@ -413,6 +413,6 @@ usl_status usl_launch_step_small(usl_ctx* c, const void* x, const int32_t* idx, 
     USL_TRY(usl_check_launch(c, "training step of a small layer"));
     const size_t n = grad_x ? (size_t)b * c->d : 0;
     hipLaunchKernelGGL(k_step_small_sums, dim3((unsigned)((n + 63) / 64 + 1)), dim3(SUMS_NT), 0, c->stream, c->small_sums, wgs, n, grad_x,
-                       usl_loss_sum{c->bce_partials, (size_t)wgs, scale, loss});
+                       usl_loss_sum{c->bce_partials, (size_t)wgs, scale, loss, {}});
     return usl_check_launch(c, "sums of a small layer's step");
 }

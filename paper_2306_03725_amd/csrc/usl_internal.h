@@ -148,13 +148,22 @@ usl_status usl_build_slot_order(usl_ctx* ctx, const int32_t* idx, int K, int uni
 usl_status usl_launch_forward(usl_ctx* ctx, const void* x, const int32_t* idx, const void* W,
                               float* out, int32_t b);
 // forward and loss in one: out receives the gradient of the loss by the scores.  A later kernel of the same step has to
-// turn *sum into the loss (usl_launch_adam and usl_launch_adam_staged do).  Also compares the fingerprint of idx if lists
-// for it stand (ctx->print_done says so).  usl_forward_loss_applies: else forward and loss are called one after the other.
+// turn *sum into the loss and take the targets' bits back (usl_launch_adam and usl_launch_adam_staged do).  Also compares the
+// fingerprint of idx if lists for it stand (ctx->print_done says so).  usl_forward_loss_applies: else forward and loss are called one
+// after the other.
+struct usl_targets {
+    const int64_t* off;    // nullptr: none
+    const int32_t* lab;
+    uint32_t* bits;        // usl_ctx::tgt_bits
+    int64_t m;
+    int b;
+};
 struct usl_loss_sum {
     const double* partials;   // the loss = scale * the sum of n partial sums; nullptr: nothing left to add up
     size_t n;
     float scale;
     float* loss;
+    usl_targets targets;      // whose bits have to go
 };
 bool usl_forward_loss_applies(const usl_ctx* ctx, const void* x, const int32_t* idx, const void* W, int32_t b);
 usl_status usl_launch_forward_loss(usl_ctx* ctx, const void* x, const int32_t* idx, const void* W, float* g, int32_t b, int loss_kind,
@@ -207,8 +216,8 @@ usl_status usl_activation_rows(usl_ctx* ctx, const void* x, int32_t b, int Q, co
 usl_status usl_launch_unstage(usl_ctx* ctx, const usl_staged& st, const uint32_t* gate, float* grad_W);
 usl_status usl_launch_adam_staged(usl_ctx* ctx, void* W, const usl_staged& st, const uint32_t* gate, float* grad_W, float* m1, float* m2,
                                   float lr, float beta1, float beta2, float eps, float inv_c1, float inv_c2, const usl_loss_sum& sum);
-// Places in ctx->idx_print: a fingerprint for each kind of lists (they are built and kept side by side), the stale word.
-enum { USL_PRINT_COLUMNS = 0, USL_PRINT_ONE_PRODUCT = 1, USL_PRINT_BOTH_PRODUCTS = 2, USL_PRINT_STALE = 4 };
+// In ctx->idx_print: the sums of a fingerprint for each kind of lists (they are built and kept side by side), then the stale word.
+enum { USL_PRINT_COLUMNS = 0, USL_PRINT_ONE_PRODUCT = 1, USL_PRINT_BOTH_PRODUCTS = 2, USL_PRINT_STALE = 3 * 64, USL_PRINT_WORDS = USL_PRINT_STALE + 8 };
 static inline uint32_t* usl_stale_word(usl_ctx* c) { return reinterpret_cast<uint32_t*>(c->idx_print + USL_PRINT_STALE); }
 // Records (store = 1) the fingerprint of idx for lists of the kind `which`, or compares with the recorded one (store = 0)
 // and raises the stale word on a difference.
@@ -297,43 +306,45 @@ template <> __device__ __forceinline__ float usl_load_f32<float>(const float* p,
 template <> __device__ __forceinline__ float usl_load_f32<uint16_t>(const uint16_t* p, size_t i) {
     return usl_bf16_to_f32(p[i]);
 }
-// Fingerprint of idx: a sum of mixed 16-byte groups at up to 4096 evenly spaced places (64 KiB read by one
-// workgroup, every load in flight at once: a few microseconds).  store = 1 records it when the column lists
-// are built; store = 0 compares on a later call and raises the stale word when the contents are
-// no longer those the lists were built from: a new tensor at a recycled address, a checkpoint copied in, ...
-// A single edited entry can slip through the sample; wholesale replacement cannot.
-__device__ __forceinline__ void usl_idx_fingerprint_block(const uint32_t* __restrict__ idx, size_t n_words,
-                                                      uint64_t* __restrict__ print, int which, int store) {   // 1024 lanes
-    __shared__ uint64_t red[16];
+// Fingerprint of idx: mixed 16-byte groups at up to 4096 evenly spaced places, 64 consecutive ones to a sum (64 KiB read, every load in
+// flight at once).  store = 1 records the sums when lists are built; store = 0 compares on a later call and raises the stale
+// word when the contents are no longer those the lists were built from: a new tensor at a recycled address, a checkpoint copied
+// in, ...  A single edited entry can slip through the sample; wholesale replacement cannot.
+// A sum for each wavefront, so that a check can be spread: one workgroup takes 10 us for the 4096 lines of a large idx, sixteen hide
+// beside the activations (usl_train_step at m = 200k, k = 32: 15.1 and 5.5 us with them).
+static constexpr int USL_PRINT_SUMS = 64;
+template <int N>   // sums first, first + step, ... (N of them) by one wavefront
+__device__ __forceinline__ void usl_idx_fingerprint_sums(const uint32_t* __restrict__ idx, size_t n_words, uint64_t* __restrict__ print, int which,
+                                                         int store, int first, int step) {
     const size_t groups = n_words / 4;
     const size_t samples = groups < 4096 ? groups : 4096;
     const size_t stride = samples ? groups / samples : 1;   // >= 1
-    uint4 v[4];
-    size_t at[4];
+    const int lane = threadIdx.x & 63;
+    uint4 v[N];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const size_t s = (size_t)q * 1024 + threadIdx.x;
-        at[q] = s < samples ? s * stride : 0;
-        v[q] = s < samples ? reinterpret_cast<const uint4*>(idx)[at[q]] : make_uint4(0, 0, 0, 0);
+    for (int q = 0; q < N; ++q) {
+        const size_t s = (size_t)(first + q * step) * 64 + lane;
+        v[q] = s < samples ? reinterpret_cast<const uint4*>(idx)[s * stride] : make_uint4(0, 0, 0, 0);
     }
-    uint64_t h = 0;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        if ((size_t)q * 1024 + threadIdx.x >= samples) continue;
-        uint64_t a = ((uint64_t)v[q].x << 32 | v[q].y) ^ (at[q] * 0x9E3779B97F4A7C15ull);
-        uint64_t b2 = ((uint64_t)v[q].z << 32 | v[q].w) + (at[q] << 7);
+    for (int q = 0; q < N; ++q) {
+        const size_t s = (size_t)(first + q * step) * 64 + lane, at = s * stride;
+        uint64_t a = ((uint64_t)v[q].x << 32 | v[q].y) ^ (at * 0x9E3779B97F4A7C15ull);
+        uint64_t b2 = ((uint64_t)v[q].z << 32 | v[q].w) + (at << 7);
         a ^= a >> 31; a *= 0xD6E8FEB86659FD93ull; a ^= a >> 29;
         b2 ^= b2 >> 33; b2 *= 0xC2B2AE3D27D4EB4Full; b2 ^= b2 >> 30;
-        h += a + (b2 << 1 | b2 >> 63);
+        uint64_t h = s < samples ? a + (b2 << 1 | b2 >> 63) : 0;
+        if (first + q * step == 0)   // the ragged tail
+            for (size_t w = groups * 4 + lane; w < n_words; w += 64) h += (uint64_t)idx[w] * 0xFF51AFD7ED558CCDull;
+        for (int o = 32; o > 0; o >>= 1) h += __shfl_down(h, o);
+        if (lane == 0) {
+            uint64_t* at_sum = print + which * USL_PRINT_SUMS + first + q * step;
+            if (store) *at_sum = h;
+            else if (*at_sum != h) *reinterpret_cast<uint32_t*>(print + USL_PRINT_STALE) = 1u;
+        }
     }
-    for (size_t w = groups * 4 + threadIdx.x; w < n_words; w += 1024) h += (uint64_t)idx[w] * 0xFF51AFD7ED558CCDull;   // ragged tail
-    for (int o = 32; o > 0; o >>= 1) h += __shfl_down(h, o);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = h;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint64_t t = 0;
-        for (int q = 0; q < 16; ++q) t += red[q];
-        if (store) print[which] = t;
-        else if (print[which] != t) *reinterpret_cast<uint32_t*>(print + USL_PRINT_STALE) = 1u;
-    }
+}
+__device__ __forceinline__ void usl_idx_fingerprint_block(const uint32_t* __restrict__ idx, size_t n_words,
+                                                      uint64_t* __restrict__ print, int which, int store) {   // 1024 lanes
+    usl_idx_fingerprint_sums<USL_PRINT_SUMS / 16>(idx, n_words, print, which, store, (int)(threadIdx.x >> 6), 16);
 }
