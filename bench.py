@@ -39,7 +39,7 @@ KERNELS_OF_CALL = {
     "backward": "usl_backward_weight's and usl_backward_input's kernels, one call after the other",
     "backward_one_pass": "a look at a sample of g, k_idx_fingerprint, k_both_lds (both products from one pass over g: "
                          "lists in registers with a weight-gradient sum per connection, two or four rows of g "
-                         "interleaved in LDS) + k_lf_reduce + k_unstage (the weight gradient into slot order)",
+                         "interleaved in LDS) + k_unstage (the weight gradient into slot order, the sums of grad_x added up)",
     "adam": "k_adam (1 launch)",
 }
 
@@ -142,8 +142,8 @@ def launches_in_call(cfg, call):
         return 1 + (1 if forward_unit(cfg)[0] > 1 else 0) + (look if call == "backward_weight" else 0)
     if call == "backward":
         cut = one_pass_cut(cfg)
-        if cut:   # fingerprint of idx, activations in the kernel's layout, k_both_lds and k_lf_reduce, k_unstage
-            return look + 1 + (1 if cut["q"] == 4 or cfg.d * es % 16 else 0) + 2 * cut["passes"] + 1
+        if cut:   # fingerprint of idx, activations in the kernel's layout, k_both_lds, k_lf_reduce between two passes, k_unstage
+            return look + 1 + (1 if cut["q"] == 4 or cfg.d * es % 16 else 0) + 2 * cut["passes"]
         return launches_in_call(cfg, "backward_weight") + launches_in_call(cfg, "backward_input")
     if call != "backward_input":
         return 2 if call == "bce" else 1

@@ -30,6 +30,7 @@
 #include "usl_internal.h"
 
 #include "k_lists_cut.h"
+#include "k_sums.h"
 #include "k_matching.h"
 
 using namespace usl_lists;
@@ -1389,41 +1390,13 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
     }
 }
 
-// grad_x[i][c] = sum over the windows (chains of them, in the kernel for both products) of partial[w][i][c], i < rows; a row of partial is dp floats (d rounded up to a
-// multiple of 4).  BOTH only names the kernel after the one whose sums it adds, so that a profile tells the two apart.
-// vec: rows of grad_x are 16-byte aligned too.
-// Bound by the stream of the partial sums.  Where lanes are few the loads of eight or four windows go out together (AT_ONCE): one
-// after the other a lane waits out every window.  Where they are many, one: they cover for one another, and their rows stay
-// close together.  In a step, with eight, four, one: m = 31k, d = 1k, b = 128 (128 workgroups): 5.8, 6.4, 11.0 us; m = 200k, d = 8k, b = 64
-// (512): 24, 22, 31; m = 60k, d = 8k, b = 128 (1000): 15.1, 13.9, 12.6; m = 130k, d = 32k, b = 64 (2048): 17.8, 16.4, 15.6; m = 500k,
-// d = 32k, b = 256, 537 MB: 116, 119, 109 (120 with the rows from the first).
+// BOTH only names the kernel after the one whose sums it adds, so that a profile tells the two apart.
 template <bool BOTH, int AT_ONCE>
 __global__ void __launch_bounds__(256)
-k_lf_reduce(const float4* __restrict__ partial, int nwin, size_t n4, int d, int dp, bool vec, float* __restrict__ out,
-            const uint32_t* __restrict__ gate, const uint32_t* __restrict__ stale) {
+k_lf_reduce(usl_window_sums sums, const uint32_t* __restrict__ gate, const uint32_t* __restrict__ stale) {
     if (gate && *gate == 0) return;
-    const bool poison = *stale != 0;   // the lists were built from other contents of idx: no number is better than a wrong one
-    const size_t step = (size_t)gridDim.x * blockDim.x;
-    for (size_t u = (size_t)blockIdx.x * blockDim.x + threadIdx.x; u < n4; u += step) {
-        const size_t v = n4 - 1 - u;   // the last rows first: they were written last, and may still be in a cache
-        float4 a = partial[v];
-#pragma unroll AT_ONCE
-        for (int q = 1; q < nwin; ++q) {
-            const float4 t = partial[(size_t)q * n4 + v];
-            a.x += t.x; a.y += t.y; a.z += t.z; a.w += t.w;
-        }
-        if (poison) a.x = a.y = a.z = a.w = __uint_as_float(0x7FC00000u);
-        if (vec) {
-            reinterpret_cast<float4*>(out)[v] = a;
-        } else {
-            const uint32_t row4 = (uint32_t)dp / 4, i = (uint32_t)(v / row4), c = (uint32_t)(v % row4) * 4;
-            float* to = out + (size_t)i * d + c;
-            const float r[4] = {a.x, a.y, a.z, a.w};
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if ((int)c + q < d) to[q] = r[q];
-        }
-    }
+    usl_add_up_windows<AT_ONCE>(sums, *stale != 0 /* the lists were built from other contents of idx: no number is better than a wrong one */,
+                                blockIdx.x, gridDim.x);
 }
 
 }  // namespace
@@ -1591,23 +1564,24 @@ static int pass_rows(const usl_ctx* c, int sets, int step) {
     return G < c->max_b && G > step ? G / step * step : G;
 }
 
-static void lf_reduce(usl_ctx* c, const float* partial, int sets, int rows, bool both, float* grad_x, const uint32_t* gate) {
+// How the sums of `rows` instances are added up: see usl_add_up_windows for the lines.
+static usl_window_sums window_sums(const usl_ctx* c, const float* partial, int sets, int rows, float* grad_x) {
     const int dp = padded_d(c);
-    const size_t n4 = (size_t)rows * dp / 4;
-    const bool vec = dp == c->d && (uintptr_t)grad_x % 16 == 0;
-    const uint32_t* stale = usl_stale_word(c);
-    size_t blocks = (n4 + 255) / 256;
-    if (blocks > (size_t)c->num_cu * 8) blocks = (size_t)c->num_cu * 8;
-#define USL_REDUCE(BOTH, AT_ONCE)                                                                                            \
-    hipLaunchKernelGGL((k_lf_reduce<BOTH, AT_ONCE>), dim3((unsigned)blocks), dim3(256), 0, c->stream,                         \
-                       reinterpret_cast<const float4*>(partial), sets, n4, c->d, dp, vec, grad_x, gate, stale)
+    const size_t n4 = (size_t)rows * dp / 4, want = (n4 + 255) / 256, most = (size_t)c->num_cu * 8, blocks = want < most ? want : most;
+    return {reinterpret_cast<const float4*>(partial), sets, n4, c->d, dp, dp == c->d && (uintptr_t)grad_x % 16 == 0, grad_x,
+            (unsigned)((blocks + 7) / 8 * 8), blocks <= (size_t)c->num_cu ? 8 : blocks <= (size_t)c->num_cu * 2 ? 4 : 1};
+}
+
+static void lf_reduce(usl_ctx* c, const usl_window_sums& sums, bool both, const uint32_t* gate) {
+#define USL_REDUCE(BOTH, AT_ONCE) \
+    hipLaunchKernelGGL((k_lf_reduce<BOTH, AT_ONCE>), dim3(sums.blocks), dim3(256), 0, c->stream, sums, gate, usl_stale_word(c))
 #define USL_REDUCE_B(BOTH)                                                                                                  \
     do {                                                                                                                    \
-        if (blocks <= (size_t)c->num_cu) USL_REDUCE(BOTH, 8);                                                               \
-        else if (blocks <= (size_t)c->num_cu * 2) USL_REDUCE(BOTH, 4);                                                      \
+        if (sums.at_once == 8) USL_REDUCE(BOTH, 8);                                                                         \
+        else if (sums.at_once == 4) USL_REDUCE(BOTH, 4);                                                                    \
         else USL_REDUCE(BOTH, 1);                                                                                           \
     } while (0)
-    if (both) USL_REDUCE_B(true); else USL_REDUCE_B(false);   // see the kernel for the lines
+    if (both) USL_REDUCE_B(true); else USL_REDUCE_B(false);
 #undef USL_REDUCE_B
 #undef USL_REDUCE
 }
@@ -1646,15 +1620,16 @@ usl_status usl_bwi_lds_run(usl_ctx* c, const float* g, const int32_t* idx, const
         if (c->storage == USL_F32) USL_BWI(float, 0);
         else USL_BWI(uint16_t, 1);
 #undef USL_BWI
-        lf_reduce(c, L.partial, cut.nwin, rows, false, grad_x + (size_t)i0 * c->d, gate);
+        lf_reduce(c, window_sums(c, L.partial, cut.nwin, rows, grad_x + (size_t)i0 * c->d), false, gate);
     }
     return usl_check_launch(c, "backward_input (LDS form)");
 }
 
 // grad_x[b][d] and the weight gradient from g[b][m] and x[b][d].  The weight gradient is left in the order of the lists:
 // slot f's is the sum over p < *parts of (*stage)[p * *part_stride + (*pos)[f]] (usl_launch_adam_staged takes it from
-// there); both arrays belong to the context and hold until the next call or a change of idx.  A stale idx (see usl_check)
-// poisons grad_x here; *stale is the device word that says so, for whoever picks up the weight gradient.
+// there); both arrays belong to the context and hold until the next call or a change of idx.  The last pass's sums of the input
+// gradient are handed over in out->sums: added up beside the weight gradient, not by a launch of their own before it.  A stale idx (see
+// usl_check) poisons grad_x; *stale is the device word that says so, for whoever picks up the weight gradient.
 usl_status usl_both_lds_run(usl_ctx* c, const float* g, const void* x, const int32_t* idx, const void* W, float* grad_x,
                             int32_t b, const uint32_t* gate, usl_staged* out) {
     auto& L = c->lf[1];
@@ -1683,6 +1658,7 @@ usl_status usl_both_lds_run(usl_ctx* c, const float* g, const void* x, const int
     size_t x_stride = 0;
     USL_TRY(usl_activation_rows(c, x, b, Q == 4 ? 4 : 1, &xs, &x_stride));
     out->stale = usl_stale_word(c);
+    out->sums.blocks = 0;
     const bool direct = chains == 1 && dp == c->d && (uintptr_t)grad_x % 16 == 0;   // nothing to add up
     static bool checked[6] = {false, false, false, false, false, false};
     const bool own = both_own(Q, cut);
@@ -1705,7 +1681,10 @@ usl_status usl_both_lds_run(usl_ctx* c, const float* g, const void* x, const int
         if (c->storage == USL_F32) { if (Q == 2) USL_BOTH(float, 2, false, 0); else if (own) USL_BOTH(float, 4, true, 1); else USL_BOTH(float, 4, false, 2); }
         else { if (Q == 2) USL_BOTH(uint16_t, 2, false, 3); else if (own) USL_BOTH(uint16_t, 4, true, 4); else USL_BOTH(uint16_t, 4, false, 5); }
 #undef USL_BOTH
-        if (!direct) lf_reduce(c, L.partial, chains, rows, true, grad_x + (size_t)i0 * c->d, gate);
+        if (direct) continue;
+        const usl_window_sums sums = window_sums(c, L.partial, chains, rows, grad_x + (size_t)i0 * c->d);
+        if (i0 + G < b) lf_reduce(c, sums, true, gate);   // the next pass takes the place of these
+        else out->sums = sums;
     }
     out->stage = L.stage;
     out->pos = L.pos;

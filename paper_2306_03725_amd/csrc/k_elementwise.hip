@@ -2,6 +2,7 @@
 // over the scores) and Adam.
 // Both are pure HBM streams: one read and one write of every element, 16 bytes per lane.
 #include "k_adam.h"
+#include "k_sums.h"
 
 namespace {
 
@@ -237,21 +238,24 @@ __device__ __forceinline__ float staged1(const float* __restrict__ stage, uint32
 
 // grad_W[f] = stage[pos[f]]: the weight gradient of k_both_lds brought into the order of the slots (for callers of
 // usl_backward; usl_train_step lets Adam do it in passing).  Blocks and XCDs as in k_adam_staged.
+template <int AT_ONCE>
 __global__ void __launch_bounds__(256)
 k_unstage(const float* __restrict__ stage, const uint32_t* __restrict__ pos, int parts, size_t part_stride, const uint32_t* __restrict__ gate,
-          const uint32_t* __restrict__ stale, float* __restrict__ gW, size_t n) {
+          const uint32_t* __restrict__ stale, float* __restrict__ gW, size_t n, usl_window_sums sums) {
     if (gate && *gate == 0) return;
     const bool poison = *stale != 0;   // the lists were built from other contents of idx: no number is better than a wrong one
+    if (blockIdx.x < sums.blocks) { usl_add_up_windows<AT_ONCE>(sums, poison, blockIdx.x, sums.blocks); return; }
+    const unsigned block = blockIdx.x - sums.blocks;
     const float nan = __uint_as_float(0x7FC00000u);
     const size_t n4 = n / 4;
-    const size_t per_xcd = (n4 + 7) / 8, first = (size_t)(blockIdx.x & 7) * per_xcd;
+    const size_t per_xcd = (n4 + 7) / 8, first = (size_t)(block & 7) * per_xcd;
     const size_t last = first + per_xcd < n4 ? first + per_xcd : n4;
-    const size_t stride = (size_t)(gridDim.x / 8) * 256;
-    for (size_t v = first + (size_t)(blockIdx.x >> 3) * 256 + threadIdx.x; v < last; v += stride) {
+    const size_t stride = (size_t)((gridDim.x - sums.blocks) / 8) * 256;
+    for (size_t v = first + (size_t)(block >> 3) * 256 + threadIdx.x; v < last; v += stride) {
         const uint4 p4 = reinterpret_cast<const uint4*>(pos)[v];
         reinterpret_cast<float4*>(gW)[v] = poison ? make_float4(nan, nan, nan, nan) : staged4(stage, p4, parts, part_stride);
     }
-    if (blockIdx.x == 0 && threadIdx.x < (n & 3)) {   // the ragged end
+    if (block == 0 && threadIdx.x < (n & 3)) {   // the ragged end
         const size_t f = n4 * 4 + threadIdx.x;
         gW[f] = poison ? nan : staged1(stage, pos[f], parts, part_stride);
     }
@@ -265,21 +269,26 @@ k_unstage(const float* __restrict__ stage, const uint32_t* __restrict__ pos, int
 // gate (may be null): zero means the kernels over the listed nonzero gradients wrote grad_W themselves; read it.
 // stale: nonzero means the lists were built from other contents of idx (see usl_check); grad_W then becomes NaN and W,
 // m1, m2 stay as they are -- a step from a wrong gradient could not be taken back.
-template <typename TS>
+// The sums of the input gradient's windows are added up by blocks in front of Adam's (lead: step_end's, before those).
+template <typename TS, int AT_ONCE>
 __global__ void __launch_bounds__(256)
 k_adam_staged(TS* __restrict__ W, const float* __restrict__ stage, const uint32_t* __restrict__ pos, int parts, size_t part_stride,
               const uint32_t* __restrict__ gate, const uint32_t* __restrict__ stale, float* __restrict__ gW,
               float* __restrict__ m1, float* __restrict__ m2, size_t n, float lr, float b1, float b2, float eps, float ic1,
-              float ic2, usl_loss_sum sum, unsigned lead) {
+              float ic2, usl_loss_sum sum, unsigned lead, usl_window_sums sums) {
     if (blockIdx.x < lead) { step_end(sum, lead); return; }
-    const unsigned block = blockIdx.x - lead;
     const bool listed = gate && *gate == 0;
     const bool poison = !listed && *stale != 0;
+    if (blockIdx.x < lead + sums.blocks) {
+        if (!listed) usl_add_up_windows<AT_ONCE>(sums, poison, blockIdx.x - lead, sums.blocks);
+        return;
+    }
+    const unsigned others = lead + sums.blocks, block = blockIdx.x - others;
     const float nan = __uint_as_float(0x7FC00000u);
     const size_t n4 = n / 4;
     const size_t per_xcd = (n4 + 7) / 8, first = (size_t)(block & 7) * per_xcd;
     const size_t last = first + per_xcd < n4 ? first + per_xcd : n4;
-    const size_t stride = (size_t)((gridDim.x - lead) / 8) * 256;
+    const size_t stride = (size_t)((gridDim.x - others) / 8) * 256;
     if (block == 0 && threadIdx.x < (n & 3)) {   // the ragged end
         const size_t f = n4 * 4 + threadIdx.x;
         if (poison) {
@@ -457,8 +466,11 @@ static unsigned staged_blocks(const usl_ctx* c, size_t n) {
 usl_status usl_launch_unstage(usl_ctx* c, const usl_staged& st, const uint32_t* gate, float* grad_W) {
     const size_t n = (size_t)c->m * c->k;
     if ((uintptr_t)grad_W % 16) USL_FAIL(c, USL_EINVAL, "grad_W must be 16-byte aligned");
-    hipLaunchKernelGGL(k_unstage, dim3(staged_blocks(c, n)), dim3(256), 0, c->stream, st.stage, st.pos, st.parts, st.part_stride, gate,
-                       st.stale, grad_W, n);
+#define USL_UNSTAGE(AT_ONCE)                                                                                                     \
+    hipLaunchKernelGGL(k_unstage<AT_ONCE>, dim3(st.sums.blocks + staged_blocks(c, n)), dim3(256), 0, c->stream, st.stage, st.pos, st.parts, \
+                       st.part_stride, gate, st.stale, grad_W, n, st.sums)
+    if (st.sums.at_once == 8) USL_UNSTAGE(8); else if (st.sums.at_once == 4) USL_UNSTAGE(4); else USL_UNSTAGE(1);
+#undef USL_UNSTAGE
     return usl_check_launch(c, "weight gradient into slot order");
 }
 
@@ -471,12 +483,13 @@ usl_status usl_launch_adam_staged(usl_ctx* c, void* W, const usl_staged& st, con
                          ((uintptr_t)m1 % 16 == 0) && ((uintptr_t)m2 % 16 == 0);
     if (!aligned) USL_FAIL(c, USL_EINVAL, "W, grad_W, m1, m2 must be 16-byte aligned");
     const unsigned blocks = staged_blocks(c, n), lead = step_end_blocks(sum);
-    if (c->storage == USL_F32)
-        hipLaunchKernelGGL(k_adam_staged<float>, dim3(blocks + lead), dim3(256), 0, c->stream, (float*)W, st.stage, st.pos, st.parts, st.part_stride,
-                           gate, st.stale, grad_W, m1, m2, n, lr, beta1, beta2, eps, inv_c1, inv_c2, sum, lead);
-    else
-        hipLaunchKernelGGL(k_adam_staged<uint16_t>, dim3(blocks + lead), dim3(256), 0, c->stream, (uint16_t*)W, st.stage, st.pos, st.parts,
-                           st.part_stride, gate, st.stale, grad_W, m1, m2, n, lr, beta1, beta2, eps, inv_c1, inv_c2, sum, lead);
+#define USL_STAGED(TS, AT_ONCE)                                                                                                  \
+    hipLaunchKernelGGL((k_adam_staged<TS, AT_ONCE>), dim3(lead + st.sums.blocks + blocks), dim3(256), 0, c->stream, (TS*)W, st.stage, st.pos, \
+                       st.parts, st.part_stride, gate, st.stale, grad_W, m1, m2, n, lr, beta1, beta2, eps, inv_c1, inv_c2, sum, lead, st.sums)
+#define USL_STAGED_A(TS) do { if (st.sums.at_once == 8) USL_STAGED(TS, 8); else if (st.sums.at_once == 4) USL_STAGED(TS, 4); else USL_STAGED(TS, 1); } while (0)
+    if (c->storage == USL_F32) USL_STAGED_A(float); else USL_STAGED_A(uint16_t);
+#undef USL_STAGED_A
+#undef USL_STAGED
     if (sum.targets.off) c->tgt_bits_set = false;
     return usl_check_launch(c, "adam (staged gradient)");
 }

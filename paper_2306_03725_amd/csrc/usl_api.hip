@@ -314,7 +314,7 @@ extern "C" usl_status usl_backward(usl_ctx* c, const float* g, const void* x, co
     USL_TRY(check_batch(c, b));
     USL_TRY(usl_prepare_device(c));
     const uint32_t* gate = nullptr;
-    usl_staged staged;
+    usl_staged staged = {};
     USL_TRY(backward_both(c, g, x, idx, W, grad_W, grad_x, b, usl_sparse_supported(c), false, &gate, &staged));
     if (staged.stage) USL_TRY(usl_launch_unstage(c, staged, gate, grad_W));
     return USL_OK;
@@ -423,7 +423,7 @@ extern "C" usl_status usl_train_step(usl_ctx* c, const void* x, const int32_t* i
             // listed once, and both backward products use the lists (the dense kernels stand by behind the gate)
             // (the same order of calls where the input gradient reads g row-major: its register-list form)
             const uint32_t* gate = nullptr;
-            usl_staged staged;
+            usl_staged staged = {};
             USL_TRY(backward_both(c, g, x, idx, W, grad_W, grad_x, b, lists, loss_kind == 0, &gate, &staged));
             if (staged.stage) {   // the weight gradient is in the order of the lists: Adam picks it up there and writes grad_W
                 const double c1 = 1.0 - pow((double)beta1, (double)t);

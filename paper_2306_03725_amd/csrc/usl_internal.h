@@ -198,6 +198,18 @@ usl_status usl_bwi_lds_run(usl_ctx* ctx, const float* g, const int32_t* idx, con
 // grad_W[m][k] and grad_x[b][d] from g[b][m] and x[b][d]; for every layer of up to 65536 features whose partial sums of 64
 // instances fit the allowance.
 bool usl_both_lds_applies(const usl_ctx* ctx);
+// Sums of the input gradient that are still to be added up: out[i][c] = sum over the sets of partial[set][i][c], n4 groups of four values a
+// set, rows of dp values (d rounded up to a multiple of 4).  vec: rows of out are 16-byte aligned and dp = d.
+struct usl_window_sums {
+    const float4* partial;
+    int sets;
+    size_t n4;
+    int d, dp;
+    bool vec;
+    float* out;
+    unsigned blocks;   // of 256 lanes, a multiple of 8; 0: nothing to do
+    int at_once;       // windows whose loads of a lane go out together
+};
 // Where k_both_lds left the weight gradient: slot f's is the sum over p < parts of stage[p * part_stride + pos[f]].
 // stale: device word, not 0 = the lists were built from other contents of idx.
 struct usl_staged {
@@ -206,6 +218,7 @@ struct usl_staged {
     const uint32_t* stale;
     int parts;
     size_t part_stride;
+    usl_window_sums sums;   // the kernel that picks up the weight gradient adds these up beside it
 };
 usl_status usl_both_lds_run(usl_ctx* ctx, const float* g, const void* x, const int32_t* idx, const void* W, float* grad_x,
                             int32_t b, const uint32_t* gate, usl_staged* out);
