@@ -3,7 +3,8 @@
 
 namespace usl_products {
 
-enum ProductKind { FORWARD, FORWARD_LOSS, WEIGHT_GRADIENT };   // FORWARD_LOSS: the scores become the gradient of the loss
+// FORWARD_LOSS: the scores become the gradient of the loss; FORWARD_MARKS: of the squared hinge, and its nonzeros are marked
+enum ProductKind { FORWARD, FORWARD_LOSS, FORWARD_MARKS, WEIGHT_GRADIENT };
 
 struct ProductKernel {
     const void* fn;        // nullptr: no such kernel

@@ -142,13 +142,15 @@ struct Before {
     const uint32_t* idx;      // nullptr: nothing to compare
     size_t n_words;
     uint64_t* print;
+    uint32_t* nz_state;       // nullptr: none.  Else its first three words are cleared
     __host__ __device__ int print_blocks() const { return idx ? USL_PRINT_SUMS / MARK_WAVES : 0; }
     int blocks() const { return print_blocks() + (targets.b + MARK_WAVES - 1) / MARK_WAVES; }
 };
 __device__ __forceinline__ void before_forward(const Before& w, int at, int n) {
     const int first = w.print_blocks(), wave = (int)(threadIdx.x >> 6);
     if (at < first) usl_idx_fingerprint_sums<1>(w.idx, w.n_words, w.print, USL_PRINT_BOTH_PRODUCTS, 0, at * MARK_WAVES + wave, 0);
-    else mark_targets(w.targets, (at - first) * MARK_WAVES + wave, (n - first) * MARK_WAVES);
+    if (w.nz_state && at == first && threadIdx.x < 3) w.nz_state[threadIdx.x] = 0u;
+    if (at >= first) mark_targets(w.targets, (at - first) * MARK_WAVES + wave, (n - first) * MARK_WAVES);
 }
 __global__ void __launch_bounds__(256)
 k_before_forward(Before w) { before_forward(w, (int)blockIdx.x, (int)gridDim.x); }
@@ -464,7 +466,7 @@ struct Launch {
 // is within 10 % of the best shape and split found by hand in 35, the median 2 %; furthest off is the weight
 // gradient of a small layer with a large batch (m = 1024, d = 64, k = 8, b = 512: 25.5 us, with 16 parts 15).
 Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int most_parts = 65535) {
-    const bool backward = kind == WEIGHT_GRADIENT;
+    const bool backward = kind == WEIGHT_GRADIENT, with_loss = kind == FORWARD_LOSS || kind == FORWARD_MARKS;
     const int es = c->storage == USL_F32 ? 4 : 2, unit = L.Q * es;
     const int groups = (b + L.Q - 1) / L.Q;
     const double reads_per_clk = unit == 16 ? 8.0 : unit == 8 ? 12.0 : 14.0;
@@ -485,7 +487,7 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
         tg.groups = groups;
         tg.tile_rows = L.halves || L.Q == 1 || L.row_bytes > 16384 ? 1 : 16384 / L.row_bytes;
         if (tg.tile_rows > groups) tg.tile_rows = groups;
-        if (kind == FORWARD_LOSS && tg.tile_rows > 32 / L.Q) tg.tile_rows = 32 / L.Q;   // a tile's instances lie in one window of targets
+        if (with_loss && tg.tile_rows > 32 / L.Q) tg.tile_rows = 32 / L.Q;   // a tile's instances lie in one window of targets
         const size_t tile = L.halves ? (size_t)HALF_COLS * 4 : (size_t)tg.tile_rows * L.row_bytes;
         tg.nbuf = L.Q > 1 && 2 * tile <= (size_t)ROW_LDS_MAX ? 2 : 1;
         tg.buf_bytes = (int)tile;
@@ -530,7 +532,7 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
             const int64_t parts = (groups + gpb - 1) / gpb;   // those that have work
             if (parts > most_parts && parts > 1) break;
             if (backward && parts > 1 && (size_t)parts * c->m * c->k * 4 > ((size_t)1 << 29)) break;
-            if (kind == FORWARD_LOSS && parts > 1 && (size_t)(nblk * parts) > usl_forward_blocks(c) && split_force <= 0) break;
+            if (with_loss && parts > 1 && (size_t)(nblk * parts) > usl_forward_blocks(c) && split_force <= 0) break;
             const int64_t slots = (int64_t)cus * res;
             // Blocks of as many labels as the lanes take, or, with the same shape and split, of so many fewer that the rounds of workgroups are full: a
             // round that leaves compute units idle takes as long as a full one.  m = 200k, d = 8k, k = 32, b = 64, bfloat16 (196 blocks of 1024 labels or
@@ -545,7 +547,7 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
                     if (labels_force > 0) labels = (labels_force + 31) / 32 * 32;
                     if (labels >= (int)per_block || tail_force > 0) break;
                     n = (c->m + labels - 1) / labels;
-                    if (kind == FORWARD_LOSS && (size_t)(n * parts) > usl_forward_blocks(c) && labels_force <= 0) break;
+                    if (with_loss && (size_t)(n * parts) > usl_forward_blocks(c) && labels_force <= 0) break;
                 }
                 double t = clocks(n * parts, gpb, labels);
                 if (backward && parts > 1) t += 6000.0 + (double)(parts + 1) * c->m * c->k * 4 / 4000.0;
@@ -561,7 +563,7 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
                 for (int T = tail_force > 0 ? tail_force : 2; tail > 0 && T <= groups && (T <= 16 || T == tail_force); ++T) {
                     const int per = (groups + T - 1) / T;
                     const int64_t items = tail * ((groups + per - 1) / per);
-                    if (kind == FORWARD_LOSS && (size_t)(n - tail + items) > usl_forward_blocks(c) && tail_force <= 0) break;
+                    if (with_loss && (size_t)(n - tail + items) > usl_forward_blocks(c) && tail_force <= 0) break;
                     const double with = clocks(n - tail, gpb, labels) + clocks(items, per, labels);
                     if (with < t || tail_force > 0) { t = with; tail_gpb = per; }
                     if (tail_force > 0) break;
@@ -719,7 +721,7 @@ size_t target_words(const usl_ctx* c) { return (size_t)((c->max_b + 31) / 32) * 
 // here and taken back by the kernel that ends the step)
 usl_status run_forward(usl_ctx* c, const Layout& L, const void* x, const int32_t* idx, const void* W, float* out, int32_t b, LossArgs loss,
                        size_t* blocks, Before before = Before{}) {
-    const Launch p = choose(c, L, b, loss.kind >= 0 ? FORWARD_LOSS : FORWARD);
+    const Launch p = choose(c, L, b, loss.nonzeros ? FORWARD_MARKS : loss.kind >= 0 ? FORWARD_LOSS : FORWARD);
     const uint8_t* perm = nullptr;
     const void* xi = nullptr;
     USL_TRY(slot_order(c, idx, &perm));
@@ -756,7 +758,7 @@ usl_status usl_launch_forward(usl_ctx* c, const void* x, const int32_t* idx, con
         return c->storage == USL_F32 ? run_forward_generic<float>(c, x, idx, W, out, b) : run_forward_generic<uint16_t>(c, x, idx, W, out, b);
     const Layout L = layout_of(c, b, x);
     if (streams(c, L, b)) return run_forward_few(c, L, x, idx, W, out, b);
-    USL_TRY(run_forward(c, L, x, idx, W, out, b, LossArgs{-1, 0.f, nullptr, nullptr}, nullptr));
+    USL_TRY(run_forward(c, L, x, idx, W, out, b, LossArgs{-1, 0.f, nullptr, nullptr, nullptr, 0, nullptr}, nullptr));
     if (!pads_with_column_0(c, L)) return USL_OK;
     const dim3 grid((unsigned)((c->m + 255) / 256));
     if (c->storage == USL_F32)
@@ -774,13 +776,15 @@ bool usl_forward_loss_applies(const usl_ctx* c, const void* x, const int32_t* id
 }
 
 usl_status usl_launch_forward_loss(usl_ctx* c, const void* x, const int32_t* idx, const void* W, float* g, int32_t b, int loss_kind,
-                                   const int64_t* tgt_off, const int32_t* tgt_lab, float scale, float* loss, usl_loss_sum* sum) {
+                                   const int64_t* tgt_off, const int32_t* tgt_lab, float scale, float* loss, usl_loss_sum* sum, float* marks_clear) {
     size_t blocks = 0;
     const Layout L = layout_of(c, b, x);
     usl_targets targets = {tgt_off, tgt_lab, nullptr, c->m, b};
     const bool check = c->lf[1].built_for == idx;   // lists that the backward product will use
-    USL_TRY(run_forward(c, L, x, idx, W, g, b, LossArgs{loss_kind, scale, nullptr, nullptr}, &blocks,
-                        Before{targets, check ? reinterpret_cast<const uint32_t*>(idx) : nullptr, (size_t)c->m * c->k, c->idx_print}));
+    if (marks_clear) USL_TRY(usl_sparse_marks_ready(c));
+    USL_TRY(run_forward(c, L, x, idx, W, g, b, LossArgs{loss_kind, scale, nullptr, nullptr, marks_clear ? c->nz_bits : nullptr, (int64_t)usl_sparse_mark_words(c), marks_clear},
+                        &blocks, Before{targets, check ? reinterpret_cast<const uint32_t*>(idx) : nullptr, (size_t)c->m * c->k, c->idx_print,
+                                        marks_clear ? c->nz_state : nullptr}));
     c->print_done = check;
     targets.bits = c->tgt_bits;
     *sum = usl_loss_sum{c->bce_partials, blocks, scale, loss, targets};

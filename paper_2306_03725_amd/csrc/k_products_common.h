@@ -694,10 +694,16 @@ struct LossArgs {
     float scale;
     double* partials;
     const uint32_t* targets;   // [b / 32][m], see usl_ctx::tgt_bits
+    uint32_t* nonzeros;        // LOSS = 2: usl_ctx::nz_bits
+    int64_t words;             // ... of an instance
+    float* clear;              // ... [m][k], which the kernels over the lists of the nonzeros add into (16-byte aligned)
 };
 // EVEN: blocks of tail.labels labels, not of as many as the lanes take.  (An instance of its own: with the number known only at run time the others'
 // prologues came out otherwise and they were up to 4 % slower.)
-template <int K, int LPT, int NT, typename TS, int Q, bool HALVES, bool LOSS, bool EVEN>
+// LOSS: 0 the scores, 1 either loss, 2 the squared hinge with its nonzeros marked, one bit per score, where few of them are expected: the
+// pass over g that listed them took 105 us at m = 500k, b = 256, and clearing the weight gradient, which goes out here while the chip waits
+// for LDS anyway, 11.  (Instances of their own: with a test at run time the step of the binary cross-entropy there took 1 % longer.)
+template <int K, int LPT, int NT, typename TS, int Q, bool HALVES, int LOSS, bool EVEN>
 __global__ void __launch_bounds__(NT)
 k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS* __restrict__ W, float* __restrict__ out,
           int64_t m, int k, int b, Geom tg, const uint8_t* __restrict__ perm, LossArgs loss, Tail tail) {
@@ -708,6 +714,13 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
     if (LOSS)   // the first words of target bits come to the L2 while the labels' rows are brought in (1 % of the step at m = 500k, b = 256)
         touch_lines<NT>(reinterpret_cast<const char*>(loss.targets + (size_t)(turn.g0 * Q >> 5) * m + j0), 0,
                         ((int)min((int64_t)NT * LPT, end - j0) * 4 + 127) / 128, lds0 + (uint32_t)tg.dummy, (int)threadIdx.x);
+    if (LOSS == 2 && turn.g0 == 0) {
+        const size_t n = (size_t)min((int64_t)NT * LPT, end - j0) * k;
+        float* to = loss.clear + (size_t)j0 * k;   // j0 is a multiple of 32
+        const f32x4 zeros = {0.f, 0.f, 0.f, 0.f};
+        for (size_t v = threadIdx.x; v < n / 4; v += NT) __builtin_nontemporal_store(zeros, reinterpret_cast<f32x4*>(to) + v);
+        if (threadIdx.x < (n & 3)) to[(n & ~(size_t)3) + threadIdx.x] = 0.f;
+    }
     uint32_t pk[LPT][K / 2];
     WReg<TS, K> w[LPT];
 #pragma unroll
@@ -782,16 +795,22 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
                     if (g * Q + q < b) {
                         float o = z[q];
                         if (LOSS) {
-                            const usl_loss_of r = usl_loss_one(loss.kind, o, any_target.value && (hits >> q & 1u) ? 1.f : 0.f, loss.scale);
+                            const usl_loss_of r = usl_loss_one(LOSS == 2 ? 1 : loss.kind, o, any_target.value && (hits >> q & 1u) ? 1.f : 0.f, loss.scale);
                             o = r.g;
                             sum += r.l;
                         }
                         // past the caches: as ordinary stores they push rows of x out of the L2 (forward of m = 1M, d = 2000, k = 8, b = 32: 42.1 and 39.0 us;
                         // m = 600k, d = 20k, k = 32, b = 128: 331 and 320; m = 500k, d = 32k, b = 256: 761 and 751)
                         __builtin_nontemporal_store(o, out + ((size_t)(g * Q + q) * m + j0) + (uint32_t)jl);
+                        if constexpr (LOSS == 2) {   // lane 0's word and, where the wavefront has more than 32 labels, lane 1's
+                            const uint64_t set = __ballot(o != 0.f);
+                            const int first = __builtin_amdgcn_readfirstlane(jl), lane = jl & 63;   // (blocks of labels begin at a multiple of 32)
+                            uint32_t* words = loss.nonzeros + ((int64_t)(g * Q + q) * loss.words + ((j0 + first) >> 5));
+                            if (lane < 2 && first + lane * 32 < nlab) words[lane] = lane ? (uint32_t)(set >> 32) : (uint32_t)set;
+                        }
                     }
             };
-            if (LOSS && __builtin_expect(__any(hits != 0u), 0)) finish(std::true_type());
+            if (LOSS == 2 || (LOSS && __builtin_expect(__any(hits != 0u), 0))) finish(std::true_type());
             else finish(std::false_type());
             lost += (double)sum;
         }

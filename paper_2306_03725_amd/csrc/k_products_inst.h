@@ -17,8 +17,9 @@ ProductKernel pick(ProductKind kind, int shape) {
     constexpr int L = K == 8 ? 4 : labels_per_lane(K, 64), L2 = labels_per_lane(K, 128);
 #define USL_KIND(LPT, NT, EVEN)                                                                                \
     (kind == WEIGHT_GRADIENT ? (const void*)k_backward_weight<K, LPT, NT, TS, Q, HALVES, EVEN>                  \
-     : kind == FORWARD_LOSS  ? (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, true, EVEN>                    \
-                             : (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, false, EVEN>)
+     : kind == FORWARD_MARKS ? (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, 2, EVEN>                       \
+     : kind == FORWARD_LOSS  ? (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, 1, EVEN>                       \
+                             : (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, 0, EVEN>)
 #define USL_PICK(LPT, NT)                                                                                      \
     ProductKernel{USL_KIND(LPT, NT, false), USL_KIND(LPT, NT, true), K, LPT, NT, transpose_bytes<K, NT>()}
     if constexpr (Q > 1) {

@@ -33,7 +33,7 @@ extern "C" usl_status usl_destroy(usl_ctx* c) {
         void* bufs[] = {c->bce_partials, c->sel_hist, c->prune_flags, c->tie_counts, c->counter64,
                         c->csc_ptr, c->csc_cursor, c->csc_order, c->csc_slot, c->csc_w, c->gT, c->gxT, c->nz_flags,
                         c->slot_order, c->topk_cand, c->sub_idx, c->sub_W, c->predict_out, c->gw_part,
-                        c->nz_state, c->nz_lab, c->nz_val, c->idx_print, c->xi, c->xr, c->tgt_bits, c->small_sums, c->small_order};
+                        c->nz_state, c->nz_bits, c->nz_lab, c->nz_val, c->idx_print, c->xi, c->xr, c->tgt_bits, c->small_sums, c->small_order};
         (void)hipStreamSynchronize(c->stream);
         for (void* p : bufs)
             if (p) (void)hipFree(p);
@@ -282,12 +282,13 @@ static usl_status subset_context(usl_ctx* c, int64_t n, const int32_t* idx, cons
     } while (0)
 
 // Both backward products of one g.  The nonzeros of g are listed once where the context expects few (as in
-// usl_train_step); the kernels over the lists and the dense ones stand on either side of the gate.
+// usl_train_step); the kernels over the lists and the dense ones stand on either side of the gate.  marked: forward marked them.
 static usl_status backward_both(usl_ctx* c, const float* g, const void* x, const int32_t* idx, const void* W, float* grad_W,
-                                float* grad_x, int32_t b, bool lists, bool dense, const uint32_t** gate_out,
+                                float* grad_x, int32_t b, bool lists, bool marked, bool dense, const uint32_t** gate_out,
                                 usl_staged* staged) {
     const uint32_t* gate = nullptr;
-    if (lists) USL_TRY(usl_sparse_compact(c, g, b, &gate));
+    if (marked) USL_TRY(usl_sparse_lists(c, g, b, &gate));
+    else if (lists) USL_TRY(usl_sparse_compact(c, g, b, &gate));
     c->nz_lists_of = g;
     c->nz_lists_tried = gate != nullptr;
     usl_status s = USL_OK;
@@ -295,7 +296,7 @@ static usl_status backward_both(usl_ctx* c, const float* g, const void* x, const
     if (usl_both_lds_applies(c) && (uintptr_t)grad_W % 16 == 0) {
         // both products from one pass of gathers over the rows of g (k_backward_input_lds.hip); behind the gate like
         // the two dense kernels it stands for.  The weight gradient is left in the order of the lists.
-        if (gate) s = usl_sparse_backward_weight(c, x, idx, grad_W, b);
+        if (gate) s = usl_sparse_backward_weight(c, x, idx, grad_W, b, marked);
         if (gate && s == USL_OK) s = usl_sparse_backward_input(c, idx, W, grad_x, b);
         if (s == USL_OK) s = usl_both_lds_run(c, g, x, idx, W, grad_x, b, gate, staged);
     } else {
@@ -315,7 +316,7 @@ extern "C" usl_status usl_backward(usl_ctx* c, const float* g, const void* x, co
     USL_TRY(usl_prepare_device(c));
     const uint32_t* gate = nullptr;
     usl_staged staged = {};
-    USL_TRY(backward_both(c, g, x, idx, W, grad_W, grad_x, b, usl_sparse_supported(c), false, &gate, &staged));
+    USL_TRY(backward_both(c, g, x, idx, W, grad_W, grad_x, b, usl_sparse_supported(c), false, false, &gate, &staged));
     if (staged.stage) USL_TRY(usl_launch_unstage(c, staged, gate, grad_W));
     return USL_OK;
 }
@@ -405,8 +406,10 @@ extern "C" usl_status usl_train_step(usl_ctx* c, const void* x, const int32_t* i
     const bool by_rows = !grad_x || usl_bwi_lds_applies(c) || usl_both_lds_applies(c) ||
                          (lists && (b > usl_bwd_input_group_rows() || usl_sparse_expected(c)));
     const bool fused = by_rows && usl_forward_loss_applies(c, x, idx, W, b);
+    // where few nonzeros are expected forward marks them in passing, one bit per score, and no pass over g has to look for them
+    const bool marked = fused && lists && grad_x && (uintptr_t)grad_W % 16 == 0 && usl_sparse_expected(c);
     if (fused) {
-        USL_TRY(usl_launch_forward_loss(c, x, idx, W, g, b, loss_kind, tgt_off, tgt_lab, scale, loss, &sum));
+        USL_TRY(usl_launch_forward_loss(c, x, idx, W, g, b, loss_kind, tgt_off, tgt_lab, scale, loss, &sum, marked ? grad_W : nullptr));
     } else {
         USL_TRY(usl_launch_forward(c, x, idx, W, g, b));
         if (by_rows) USL_TRY(usl_launch_loss(c, loss_kind, g, tgt_off, tgt_lab, scale, g, loss, b));
@@ -424,7 +427,7 @@ extern "C" usl_status usl_train_step(usl_ctx* c, const void* x, const int32_t* i
             // (the same order of calls where the input gradient reads g row-major: its register-list form)
             const uint32_t* gate = nullptr;
             usl_staged staged = {};
-            USL_TRY(backward_both(c, g, x, idx, W, grad_W, grad_x, b, lists, loss_kind == 0, &gate, &staged));
+            USL_TRY(backward_both(c, g, x, idx, W, grad_W, grad_x, b, lists, marked, loss_kind == 0, &gate, &staged));
             if (staged.stage) {   // the weight gradient is in the order of the lists: Adam picks it up there and writes grad_W
                 const double c1 = 1.0 - pow((double)beta1, (double)t);
                 const double c2 = 1.0 - pow((double)beta2, (double)t);

@@ -69,6 +69,7 @@ struct usl_ctx {
     float* gxT;               size_t gxT_cap;  // [tiles][d][32] input gradient in the same layout
     // per-instance lists of the nonzero entries of g (k_sparse_grad.hip)
     uint32_t* nz_state;       size_t nz_state_cap;   // [0] = 1: gradient is dense, lists abandoned; entries of every instance, a line each (k_sparse_grad.hip)
+    uint32_t* nz_bits;        size_t nz_bits_cap;    // [max_b][m / 32] bit j % 32 of word j / 32: g of label j is not zero (forward with the squared hinge)
     int32_t* nz_lab;          size_t nz_lab_cap;     // [max_b][m/32] label of an entry
     float* nz_val;            size_t nz_val_cap;     // [max_b][m/32] its gradient
     const float* nz_lists_of; // g that has just been looked at (only set inside usl_train_step), else NULL
@@ -149,7 +150,8 @@ usl_status usl_launch_forward(usl_ctx* ctx, const void* x, const int32_t* idx, c
                               float* out, int32_t b);
 // forward and loss in one: out receives the gradient of the loss by the scores.  A later kernel of the same step has to
 // turn *sum into the loss and take the targets' bits back (usl_launch_adam and usl_launch_adam_staged do).  Also compares the
-// fingerprint of idx if lists for it stand (ctx->print_done says so).  usl_forward_loss_applies: else forward and loss are called one
+// fingerprint of idx if lists for it stand (ctx->print_done says so).  marks_clear (may be null): the squared hinge's nonzeros are to be
+// marked for usl_sparse_lists, and this [m][k] array, 16-byte aligned, to be cleared.  usl_forward_loss_applies: else forward and loss are called one
 // after the other.
 struct usl_targets {
     const int64_t* off;    // nullptr: none
@@ -167,7 +169,7 @@ struct usl_loss_sum {
 };
 bool usl_forward_loss_applies(const usl_ctx* ctx, const void* x, const int32_t* idx, const void* W, int32_t b);
 usl_status usl_launch_forward_loss(usl_ctx* ctx, const void* x, const int32_t* idx, const void* W, float* g, int32_t b, int loss_kind,
-                                   const int64_t* tgt_off, const int32_t* tgt_lab, float scale, float* loss, usl_loss_sum* sum);
+                                   const int64_t* tgt_off, const int32_t* tgt_lab, float scale, float* loss, usl_loss_sum* sum, float* marks_clear);
 // dense = the caller knows that g holds (almost) no exact zeros: the zero-skipping tests are left out
 usl_status usl_launch_backward_weight(usl_ctx* ctx, const float* g, const void* x,
                                       const int32_t* idx, float* grad_W, int32_t b, bool dense = false);
@@ -179,7 +181,11 @@ usl_status usl_launch_backward_input(usl_ctx* ctx, const float* g, const int32_t
 bool usl_sparse_supported(const usl_ctx* ctx);
 bool usl_sparse_expected(usl_ctx* ctx);
 usl_status usl_sparse_compact(usl_ctx* ctx, const float* g, int32_t b, const uint32_t** gate);
-usl_status usl_sparse_backward_weight(usl_ctx* ctx, const void* x, const int32_t* idx, float* grad_W, int32_t b);
+// The same lists from the marks that forward left (ctx->nz_bits; usl_sparse_marks_ready before it): no look and no pass over g.
+usl_status usl_sparse_marks_ready(usl_ctx* ctx);
+static inline size_t usl_sparse_mark_words(const usl_ctx* c) { return (size_t)((c->m + 31) / 32); }   // of an instance
+usl_status usl_sparse_lists(usl_ctx* ctx, const float* g, int32_t b, const uint32_t** gate);
+usl_status usl_sparse_backward_weight(usl_ctx* ctx, const void* x, const int32_t* idx, float* grad_W, int32_t b, bool cleared = false);
 usl_status usl_sparse_backward_input(usl_ctx* ctx, const int32_t* idx, const void* W, float* grad_x, int32_t b);
 // backward_input in pieces, for callers that produce gT / nz_flags / the nonzero count themselves, one group of
 // at most usl_bwd_input_group_rows() instances at a time
