@@ -5,7 +5,7 @@
 // word is the score's bit pattern made monotone (negative values complemented, the sign bit set on the
 // rest; -0 folded onto +0 first), the lower word is ~label, so equal scores rank the smaller label
 // higher and no two keys of a row are equal.  Key 0 never occurs for a real pair and means "nothing".
-#include "usl_internal.h"
+#include "k_topk.h"
 
 namespace {
 
@@ -14,36 +14,10 @@ constexpr int TK_NT = 256;             // lanes per workgroup
 constexpr int TK_EPT = 64, TK_EPT_FEW = 8;
 constexpr int TK_MAX = 32;             // largest kk
 
-__device__ __forceinline__ uint64_t score_key(float z, uint32_t label) {
-    uint32_t u = __float_as_uint(z);
-    if (u == 0x80000000u) u = 0u;
-    u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-    return ((uint64_t)u << 32) | (uint64_t)(uint32_t)~label;
-}
-
-// Largest v of the wavefront, the same register for all lanes.  What bounds these kernels is the chain of 2 kk such maxima; lane
-// shifts within the vector unit (rows of 16 lanes, then the last lane of a row into the next ones) do not wait for LDS as
-// shuffles do (one row of 500k scores, 5 labels: segments 7.5 and 6.3 us, merge 6.2 and 4.5).
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint64_t max_with(uint64_t v) {   // a lane without a source keeps its own
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)v, (int)(uint32_t)v, CTRL, ROWS, 0xF, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(v >> 32), (int)(v >> 32), CTRL, ROWS, 0xF, false);
-    const uint64_t t = (uint64_t)hi << 32 | lo;
-    return t > v ? t : v;
-}
-__device__ __forceinline__ uint64_t wave_max(uint64_t v) {
-    v = max_with<0x111, 0xF>(v);   // row_shr:1, 2, 4, 8: lane 15 of a row has the row's largest
-    v = max_with<0x112, 0xF>(v);
-    v = max_with<0x114, 0xF>(v);
-    v = max_with<0x118, 0xF>(v);
-    v = max_with<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3, row_bcast:31 into rows 2 and 3
-    v = max_with<0x143, 0xC>(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63), hi = (uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), 63);
-    return (uint64_t)hi << 32 | lo;
-}
 // Largest v of the workgroup, returned to every lane.  red: two sets used in turn, so one barrier is enough.
+template <int NT>
 struct BlockMax {
-    uint64_t (*red)[TK_NT / 64];
+    uint64_t (*red)[NT / 64];
     int turn;
     __device__ __forceinline__ uint64_t operator()(uint64_t v) {
         v = wave_max(v);
@@ -53,7 +27,7 @@ struct BlockMax {
         __syncthreads();
         uint64_t r = set[0];
 #pragma unroll
-        for (int w = 1; w < TK_NT / 64; ++w) r = set[w] > r ? set[w] : r;
+        for (int w = 1; w < NT / 64; ++w) r = set[w] > r ? set[w] : r;
         return r;
     }
 };
@@ -70,7 +44,7 @@ template <bool VEC, int TK_EPT>
 __global__ void __launch_bounds__(TK_NT)
 k_topk_segments(const float* __restrict__ out, int64_t m, int kk, int nseg, uint64_t* __restrict__ cand) {
     __shared__ uint64_t red[2][TK_NT / 64];
-    BlockMax block_max = {red, 0};
+    BlockMax<TK_NT> block_max = {red, 0};
     __shared__ uint64_t list[TK_MAX * TK_EPT];
     __shared__ uint32_t count;
     constexpr int TK_SEG = TK_NT * TK_EPT;   // labels per workgroup
@@ -142,23 +116,24 @@ k_topk_segments(const float* __restrict__ out, int64_t m, int kk, int nseg, uint
 // back from out so that it keeps its own bits (a -0 stays -0).  A launch of its own: merged by the workgroup
 // that finishes a row's last segment, one row of 500k scores took 14.6 us when the two launches took 7.5 + 5.2 (the
 // candidates then have to be made visible across the L2s by every workgroup).
-__global__ void __launch_bounds__(TK_NT)
+template <int NT>
+__global__ void __launch_bounds__(NT)
 k_topk_merge(const uint64_t* __restrict__ cand, int n, int kk, const float* __restrict__ out, int64_t m,
              int32_t* __restrict__ top_lab, float* __restrict__ top_val) {
-    __shared__ uint64_t red[2][TK_NT / 64];
-    BlockMax block_max = {red, 0};
+    __shared__ uint64_t red[2][NT / 64];
+    BlockMax<NT> block_max = {red, 0};
     const uint64_t* c = cand + (size_t)blockIdx.x * n;
     constexpr int HELD = 8;   // candidates a lane keeps in registers; only very wide rows have more
     uint64_t mine[HELD];
 #pragma unroll
-    for (int e = 0; e < HELD; ++e) mine[e] = e * TK_NT + (int)threadIdx.x < n ? c[e * TK_NT + threadIdx.x] : 0ull;
+    for (int e = 0; e < HELD; ++e) mine[e] = e * NT + (int)threadIdx.x < n ? c[e * NT + threadIdx.x] : 0ull;
     uint64_t prev = ~0ull;
     for (int r = 0; r < kk; ++r) {
         uint64_t best = 0;
 #pragma unroll
         for (int e = 0; e < HELD; ++e)
             if (mine[e] < prev && mine[e] > best) best = mine[e];
-        for (int q = HELD * TK_NT + (int)threadIdx.x; q < n; q += TK_NT) {
+        for (int q = HELD * NT + (int)threadIdx.x; q < n; q += NT) {
             const uint64_t key = c[q];
             if (key < prev && key > best) best = key;
         }
@@ -192,16 +167,33 @@ k_precision_hits(const int32_t* __restrict__ top_lab, const int64_t* __restrict_
 
 int usl_topk_max(void) { return TK_MAX; }
 
+static int topk_segments(const usl_ctx* c, int ept) { return (int)((c->m + TK_NT * ept - 1) / (TK_NT * ept)); }
+
+// Sized once for the largest batch and the largest kk, so that no later call has to grow it (growing waits for the stream).
+usl_status usl_reserve_topk(usl_ctx* c) {
+    const size_t most = (size_t)topk_segments(c, TK_EPT) * c->max_b, most_few = (size_t)topk_segments(c, TK_EPT_FEW) * (c->num_cu / topk_segments(c, TK_EPT) + 1);
+    const size_t by_forward = (size_t)usl_forward_few_blocks(c);
+    const size_t two = most > most_few ? most : most_few;
+    return usl_reserve(c, (void**)&c->topk_cand, &c->topk_cand_cap, (two > by_forward ? two : by_forward) * TK_MAX * 8);
+}
+
+// The best kk of every row of out from nseg sets of kk candidates each (usl_ctx::topk_cand).
+usl_status usl_launch_topk_merge(usl_ctx* c, int nseg, const float* out, int32_t b, int32_t kk, int32_t* top_lab, float* top_val) {
+    const int n = nseg * kk;
+    if (n <= 8 * TK_NT)   // what 256 lanes hold in registers
+        hipLaunchKernelGGL(k_topk_merge<TK_NT>, dim3((unsigned)b), dim3(TK_NT), 0, c->stream, c->topk_cand, n, (int)kk, out, c->m, top_lab, top_val);
+    else
+        hipLaunchKernelGGL(k_topk_merge<1024>, dim3((unsigned)b), dim3(1024), 0, c->stream, c->topk_cand, n, (int)kk, out, c->m, top_lab, top_val);
+    return usl_check_launch(c, "topk");
+}
+
 usl_status usl_launch_topk(usl_ctx* c, const float* out, int32_t b, int32_t kk, int32_t* top_lab,
                            float* top_val) {
-    auto segments = [&](int ept) { return (int)((c->m + TK_NT * ept - 1) / (TK_NT * ept)); };
     // short segments where long ones would not give every compute unit a workgroup (one row of 500k scores: 31 of 256
     // busy, 11 us; 7.5 with short ones)
-    const bool few = (int64_t)segments(TK_EPT) * b < c->num_cu;
-    const int nseg = segments(few ? TK_EPT_FEW : TK_EPT);
-    // sized once for the largest batch and the largest kk, so that no later call has to grow it (growing waits for the stream)
-    const size_t most = (size_t)segments(TK_EPT) * c->max_b, most_few = (size_t)segments(TK_EPT_FEW) * (c->num_cu / segments(TK_EPT) + 1);
-    USL_TRY(usl_reserve(c, (void**)&c->topk_cand, &c->topk_cand_cap, (most > most_few ? most : most_few) * TK_MAX * 8));
+    const bool few = (int64_t)topk_segments(c, TK_EPT) * b < c->num_cu;
+    const int nseg = topk_segments(c, few ? TK_EPT_FEW : TK_EPT);
+    USL_TRY(usl_reserve_topk(c));
     const bool vec = c->m % 4 == 0 && (uintptr_t)out % 16 == 0;
 #define USL_TOPK(VEC, EPT)                                                                                                   \
     hipLaunchKernelGGL((k_topk_segments<VEC, EPT>), dim3((unsigned)nseg, (unsigned)b), dim3(TK_NT), 0, c->stream, out, c->m, \
@@ -209,9 +201,7 @@ usl_status usl_launch_topk(usl_ctx* c, const float* out, int32_t b, int32_t kk, 
     if (few) { if (vec) USL_TOPK(true, TK_EPT_FEW); else USL_TOPK(false, TK_EPT_FEW); }
     else { if (vec) USL_TOPK(true, TK_EPT); else USL_TOPK(false, TK_EPT); }
 #undef USL_TOPK
-    hipLaunchKernelGGL(k_topk_merge, dim3((unsigned)b), dim3(TK_NT), 0, c->stream, c->topk_cand, nseg * kk,
-                       (int)kk, out, c->m, top_lab, top_val);
-    return usl_check_launch(c, "topk");
+    return usl_launch_topk_merge(c, nseg, out, b, kk, top_lab, top_val);
 }
 
 usl_status usl_launch_precision_hits(usl_ctx* c, const int32_t* top_lab, const int64_t* tgt_off,

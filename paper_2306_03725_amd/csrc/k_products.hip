@@ -5,6 +5,7 @@
 
 #include "k_products.h"
 #include "k_products_common.h"
+#include "k_topk.h"
 
 using namespace usl_products;
 
@@ -191,10 +192,15 @@ __device__ __forceinline__ float moved(float v) { return __int_as_float(__builti
 // VEC: k is a multiple of 4.
 // AHEAD: rounds in flight, a divisor of `rounds`.  Four where there is one instance (four spill where there are four): with two,
 // and the sums of a label's lanes through LDS, the scores of m = 500k took 0.8 us longer.
+// kk > 0, one instance: the workgroup's kk best labels go to cand[workgroup][kk], best first (0 where there are fewer): each wavefront's
+// from its lanes' scores (read back from where they have just been written, but for the first few), then those of the wavefronts.  m = 500k,
+// 5 labels: the scores gone over by a kernel of their own took 6.2 us and a launch; usl_predict of m = 500k, d = 32k, k = 32 37.5 us, now
+// 34.8; m = 5000, d = 64, k = 8 12.9 and 10.4; m = 1.5M 32.6 and 28.0.  (Several instances one after the other took longer than that
+// kernel: m = 31k, d = 1k, k = 32, b = 4 16.2 and 26.6.)
 template <int LPL, typename TS, int Q, bool VEC, int AHEAD>
 __global__ void __launch_bounds__(1024)
 k_forward_few(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS* __restrict__ W, float* __restrict__ out,
-              int64_t m, int k, int b, int row_bytes, int rounds) {
+              int64_t m, int k, int b, int row_bytes, int rounds, int kk, uint64_t* __restrict__ cand) {
     typedef typename Unit<TS, Q>::T U;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const uint32_t lds0 = lds_base(lds_raw);
@@ -275,7 +281,10 @@ k_forward_few(const char* __restrict__ xi, const int32_t* __restrict__ idx, cons
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    for (int64_t wv = w0; wv * per < m; wv += waves) {
+    constexpr int HELD = 4;   // turns whose scores a lane keeps in registers
+    float kept[Q == 1 ? HELD : 1] = {};
+    int turn = 0;
+    for (int64_t wv = w0; wv * per < m; wv += waves, ++turn) {
         const int64_t j0 = wv * per, jn = (wv + waves) * per;
         float sum[Q] = {};   // of label j0 + (lane % LPL) * (64 / LPL) + lane / LPL
 #pragma unroll 1
@@ -304,6 +313,50 @@ k_forward_few(const char* __restrict__ xi, const int32_t* __restrict__ idx, cons
             for (int i = 0; i < Q; ++i)
                 if (i < b) out[(size_t)i * m + j] = sum[i];
         }
+        if (Q == 1) {
+#pragma unroll
+            for (int q = 0; q < HELD; ++q) kept[Q == 1 ? q : 0] = turn == q ? sum[0] : kept[Q == 1 ? q : 0];
+        }
+    }
+    if (Q > 1 || kk == 0) return;
+    const int64_t step = waves * per, turns = w0 * per < m ? (m - w0 * per + step - 1) / step : 0;
+    uint64_t* list = reinterpret_cast<uint64_t*>(lds_raw);
+    auto label_of = [&](int64_t at) -> int64_t {   // m: none
+        const int64_t j = w0 * per + at * step + sub * (64 / LPL) + lane / LPL;
+        return at < turns && sub < rounds && j < m ? j : m;
+    };
+    uint64_t held[HELD];
+#pragma unroll
+    for (int q = 0; q < HELD; ++q) held[q] = label_of(q) < m ? score_key(kept[Q == 1 ? q : 0], (uint32_t)label_of(q)) : 0ull;
+    __syncthreads();   // the row is no longer read
+    uint64_t prev = ~0ull;
+    for (int r = 0; r < kk; ++r) {
+        uint64_t best = 0;
+#pragma unroll
+        for (int q = 0; q < HELD; ++q)
+            if (held[q] < prev && held[q] > best) best = held[q];
+        for (int64_t at = HELD; at < turns; ++at) {
+            const int64_t j = label_of(at);
+            const uint64_t key = j < m ? score_key(out[j], (uint32_t)j) : 0ull;
+            if (key < prev && key > best) best = key;
+        }
+        prev = wave_max(best);
+        if (lane == 0) list[(threadIdx.x >> 6) * kk + r] = prev;
+    }
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    const int n = nw * kk;   // at most 16 * 32
+    uint64_t mine[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) mine[q] = q * 64 + lane < n ? list[q * 64 + lane] : 0ull;
+    prev = ~0ull;
+    for (int r = 0; r < kk; ++r) {
+        uint64_t best = 0;
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (mine[q] < prev && mine[q] > best) best = mine[q];
+        prev = wave_max(best);
+        if (lane == 0) cand[(size_t)blockIdx.x * kk + r] = prev;
     }
 }
 
@@ -660,8 +713,8 @@ usl_status slot_order(usl_ctx* c, const int32_t* idx, const uint8_t** perm) {
     return USL_OK;
 }
 
-// One group of instances: the streaming kernel.
-usl_status run_forward_few(usl_ctx* c, const Layout& L, const void* x, const int32_t* idx, const void* W, float* out, int b) {
+// One group of instances: the streaming kernel.  kk > 0: with the *blocks workgroups' best labels beside the scores.
+usl_status run_forward_few(usl_ctx* c, const Layout& L, const void* x, const int32_t* idx, const void* W, float* out, int b, int kk = 0, int* nblocks = nullptr) {
     const void* xi = nullptr;
     USL_TRY(activations(c, L, x, b, &xi));
     const int lpl = c->k <= 8 ? 2 : c->k <= 16 ? 4 : c->k <= 32 ? 8 : 16;
@@ -672,15 +725,21 @@ usl_status run_forward_few(usl_ctx* c, const Layout& L, const void* x, const int
     const int64_t waves = wavefronts();
     const int nw = waves >= (int64_t)c->num_cu * 16 ? 16 : waves >= (int64_t)c->num_cu * 8 ? 8 : 4;
     const int64_t blocks = (waves + nw - 1) / nw;
-    const size_t lds = (size_t)L.row_bytes + 16;
+    const size_t lds = max_sz((size_t)L.row_bytes + 16, (size_t)nw * kk * 8);
     const int by_lds = (int)((size_t)(160 * 1024) / lds), resident = by_lds < 32 / nw ? (by_lds < 1 ? 1 : by_lds) : 32 / nw;
-    const unsigned grid = (unsigned)(blocks < (int64_t)c->num_cu * resident ? blocks : (int64_t)c->num_cu * resident);
+    const unsigned grid = (unsigned)(blocks < (int64_t)c->num_cu * resident ? blocks : (int64_t)c->num_cu * resident);   // usl_forward_few_blocks at most: fewer than 16 wavefronts only where there are fewer than that of them
     const bool vec = c->k % 4 == 0;
+    uint64_t* cand = nullptr;
+    if (kk > 0) {
+        USL_TRY(usl_reserve_topk(c));
+        cand = c->topk_cand;
+        *nblocks = (int)grid;
+    }
 #define USL_FEW_A(LPL, TS, Q, VEC, AHEAD)                                                                           \
     do {                                                                                                                \
         USL_TRY(allow_lds(c, k_forward_few<LPL, TS, Q, VEC, AHEAD>, lds));                                          \
         hipLaunchKernelGGL((k_forward_few<LPL, TS, Q, VEC, AHEAD>), dim3(grid), dim3((unsigned)nw * 64), lds, c->stream,              \
-                           (const char*)xi, idx, (const TS*)W, out, c->m, c->k, b, L.row_bytes, rounds);                \
+                           (const char*)xi, idx, (const TS*)W, out, c->m, c->k, b, L.row_bytes, rounds, kk, cand);      \
     } while (0)
 #define USL_FEW(LPL, TS, Q, VEC)                                                                                    \
     do {                                                                                                                \
@@ -766,6 +825,19 @@ usl_status usl_launch_forward(usl_ctx* c, const void* x, const int32_t* idx, con
     else
         hipLaunchKernelGGL(k_forward_again<uint16_t>, grid, dim3(256), 0, c->stream, (const uint16_t*)x, idx, (const uint16_t*)W, out, c->m, c->d, c->k, b);
     return usl_check_launch(c, "forward (activations that are not finite)");
+}
+
+usl_status usl_launch_predict_few(usl_ctx* c, const void* x, const int32_t* idx, const void* W, float* out, int32_t b, int32_t kk,
+                                  int32_t* top_lab, float* top_val, bool* done) {
+    *done = false;
+    if (!fast_path_ok(c, idx, W)) return USL_OK;
+    const Layout L = layout_of(c, b, x);
+    if (b > 1 || !streams(c, L, b)) return USL_OK;
+    int blocks = 0;
+    USL_TRY(run_forward_few(c, L, x, idx, W, out, b, kk, &blocks));
+    USL_TRY(usl_launch_topk_merge(c, blocks, out, b, kk, top_lab, top_val));
+    *done = true;
+    return USL_OK;
 }
 
 bool usl_forward_loss_applies(const usl_ctx* c, const void* x, const int32_t* idx, const void* W, int32_t b) {

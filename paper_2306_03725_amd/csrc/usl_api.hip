@@ -201,6 +201,11 @@ extern "C" usl_status usl_predict(usl_ctx* c, const void* x, const int32_t* idx,
     const int mb = c->max_b;   // the scratch takes the chunk of the largest batch, so that no later call has to grow it
     const int chunk_max = (int)(mb <= 64 || cap_rows >= mb ? mb : (cap_rows < 64 ? 64 : cap_rows));
     USL_TRY(usl_reserve(c, (void**)&c->predict_out, &c->predict_out_cap, (size_t)chunk_max * c->m * 4));
+    if (b <= chunk) {
+        bool done = false;
+        USL_TRY(usl_launch_predict_few(c, x, idx, W, c->predict_out, b, kk, top_lab, top_val, &done));
+        if (done) return USL_OK;
+    }
     const size_t xrow = (size_t)c->d * (c->storage == USL_F32 ? 4 : 2);
     for (int i0 = 0; i0 < b; i0 += chunk) {
         const int n = b - i0 < chunk ? b - i0 : chunk;

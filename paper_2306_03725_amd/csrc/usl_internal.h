@@ -276,6 +276,12 @@ usl_status usl_launch_topk(usl_ctx* ctx, const float* out, int32_t b, int32_t kk
 usl_status usl_launch_precision_hits(usl_ctx* ctx, const int32_t* top_lab, const int64_t* tgt_off,
                                      const int32_t* tgt_lab, int32_t b, int32_t kk, int64_t* hits);
 int usl_topk_max(void);
+usl_status usl_reserve_topk(usl_ctx* ctx);
+usl_status usl_launch_topk_merge(usl_ctx* ctx, int nseg, const float* out, int32_t b, int32_t kk, int32_t* top_lab, float* top_val);
+// usl_predict of one instance: forward leaves its workgroups' best labels beside the scores.  *done = false: not such a call.
+usl_status usl_launch_predict_few(usl_ctx* ctx, const void* x, const int32_t* idx, const void* W, float* out, int32_t b, int32_t kk,
+                                  int32_t* top_lab, float* top_val, bool* done);
+static inline int usl_forward_few_blocks(const usl_ctx* c) { return c->num_cu * 2; }   // workgroups of its forward at most
 // dst_idx[q][:] = idx[rows[q]][:] and (if W) dst_W[q][:] = W[rows[q]][:], q < n; row ids are clamped into [0, m)
 usl_status usl_launch_gather_rows(usl_ctx* ctx, const int32_t* idx, const void* W, const int32_t* rows,
                                   int64_t n, int32_t* dst_idx, void* dst_W);  // largest kk usl_launch_topk takes
