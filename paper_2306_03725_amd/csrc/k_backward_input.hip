@@ -546,7 +546,7 @@ usl_status usl_bwd_input_prepare(usl_ctx* c, const int32_t* idx, int32_t b) {
     USL_TRY(usl_reserve(c, (void**)&c->nz_flags, &c->nz_flags_cap, (size_t)ntile * c->m));
     if (!c->counter64) {
         size_t cap = 0;
-        USL_TRY(usl_reserve(c, (void**)&c->counter64, &cap, USL_PRINT_WORDS * 8));
+        USL_TRY(usl_reserve(c, (void**)&c->counter64, &cap, 64));
     }
     return USL_OK;
 }
