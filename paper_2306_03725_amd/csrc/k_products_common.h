@@ -158,7 +158,7 @@ __device__ __forceinline__ void wave_sync() {
 // The prologue brings the rows of a wavefront's 64 labels in: order, indices and weights are requested together
 // (coalesced; one trip to memory instead of three in a row), then indices and weights go through LDS.
 template <typename TS, int K, int NT> constexpr bool raw_rows() {
-    return (K & (K - 1)) == 0 && (sizeof(TS) == 2 || (K <= 32 && NT < 1024));
+    return (K & (K - 1)) == 0 && (sizeof(TS) == 2 ? K <= 32 || NT < 1024 : K <= 32 && NT < 1024);
 }
 template <typename TS, int K>
 struct RawRows {

@@ -4,6 +4,9 @@
 // the 128 registers a lane of a full compute unit has; twice the slots in 512 lanes of 256 registers was slower
 // everywhere but in the forward product at K = 64).
 // Rows that leave room for one workgroup per compute unit (Q = 1) come in the wide shapes only.
+// bfloat16 with K = 64 in such rows (Q <= 2) also as 1024 lanes with one label each in the forward product: sixteen wavefronts wait for their
+// reads instead of eight (m = 670k, d = 32k, k = 64, b = 512: 512 lanes with two labels 2362 us, this 2310; the step 8006 and 7756).  Not in
+// shorter rows, where smaller workgroups share a compute unit (m = 300k, d = 4k, k = 60, b = 64: 512 lanes with one 121, this 151).
 #pragma once
 #include "k_products_common.h"
 #include "k_products.h"
@@ -15,6 +18,7 @@ constexpr int labels_per_lane(int K, int slots) { return slots / K < 1 ? 1 : slo
 template <int K, typename TS, int Q, bool HALVES>
 ProductKernel pick(ProductKind kind, int shape) {
     constexpr int L = K == 8 ? 4 : labels_per_lane(K, 64), L2 = labels_per_lane(K, 128);
+    constexpr bool WIDE_PAIRS = K == 64 && sizeof(TS) == 2 && Q <= 2;   // 64 packed slots take 64 of the 128 registers
 #define USL_KIND(LPT, NT, EVEN)                                                                                \
     (kind == WEIGHT_GRADIENT ? (const void*)k_backward_weight<K, LPT, NT, TS, Q, HALVES, EVEN>                  \
      : kind == FORWARD_MARKS ? (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, 2, EVEN>                       \
@@ -29,8 +33,8 @@ ProductKernel pick(ProductKind kind, int shape) {
             if (shape == 2 && kind != WEIGHT_GRADIENT) return USL_PICK(L2, 512);
         }
         if (shape == 2) return USL_PICK(L, 1024);
-        if constexpr (L > 1 && K >= 16) {
-            if (shape == 3) return USL_PICK(1, 1024);
+        if constexpr ((L > 1 && K >= 16) || WIDE_PAIRS) {
+            if (shape == 3 && (L > 1 || kind != WEIGHT_GRADIENT)) return USL_PICK(1, 1024);
         }
     } else if constexpr (K < 64) {
         if (shape == 1) return USL_PICK(1, 1024);
@@ -38,6 +42,9 @@ ProductKernel pick(ProductKind kind, int shape) {
     } else {   // 64 slots in 128 registers would spill
         if (shape == 1) return USL_PICK(1, 512);
         if (shape == 2) return USL_PICK(L2, 512);
+        if constexpr (WIDE_PAIRS) {
+            if (shape == 3 && kind != WEIGHT_GRADIENT) return USL_PICK(1, 1024);
+        }
     }
 #undef USL_PICK
 #undef USL_KIND
