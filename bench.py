@@ -136,7 +136,7 @@ def forward_unit(cfg):
 
 def launches_in_call(cfg, call):
     """Kernel launches behind one call (the HIP-event time of the call covers all of them)."""
-    look = 2 if cfg.m >= 65536 else 0    # the sample of g
+    look = 1 if cfg.m >= 65536 else 0    # the sample of g
     es = 2 if cfg.storage == "bf16" else 4
     if call in ("forward", "backward_weight"):
         return 1 + (1 if forward_unit(cfg)[0] > 1 else 0) + (look if call == "backward_weight" else 0)

@@ -143,14 +143,12 @@ struct Before {
     const uint32_t* idx;      // nullptr: nothing to compare
     size_t n_words;
     uint64_t* print;
-    uint32_t* nz_state;       // nullptr: none.  Else its first three words are cleared
     __host__ __device__ int print_blocks() const { return idx ? USL_PRINT_SUMS / MARK_WAVES : 0; }
     int blocks() const { return print_blocks() + (targets.b + MARK_WAVES - 1) / MARK_WAVES; }
 };
 __device__ __forceinline__ void before_forward(const Before& w, int at, int n) {
     const int first = w.print_blocks(), wave = (int)(threadIdx.x >> 6);
     if (at < first) usl_idx_fingerprint_sums<1>(w.idx, w.n_words, w.print, USL_PRINT_BOTH_PRODUCTS, 0, at * MARK_WAVES + wave, 0);
-    if (w.nz_state && at == first && threadIdx.x < 3) w.nz_state[threadIdx.x] = 0u;
     if (at >= first) mark_targets(w.targets, (at - first) * MARK_WAVES + wave, (n - first) * MARK_WAVES);
 }
 __global__ void __launch_bounds__(256)
@@ -855,8 +853,7 @@ usl_status usl_launch_forward_loss(usl_ctx* c, const void* x, const int32_t* idx
     const bool check = c->lf[1].built_for == idx;   // lists that the backward product will use
     if (marks_clear) USL_TRY(usl_sparse_marks_ready(c));
     USL_TRY(run_forward(c, L, x, idx, W, g, b, LossArgs{loss_kind, scale, nullptr, nullptr, marks_clear ? c->nz_bits : nullptr, (int64_t)usl_sparse_mark_words(c), marks_clear},
-                        &blocks, Before{targets, check ? reinterpret_cast<const uint32_t*>(idx) : nullptr, (size_t)c->m * c->k, c->idx_print,
-                                        marks_clear ? c->nz_state : nullptr}));
+                        &blocks, Before{targets, check ? reinterpret_cast<const uint32_t*>(idx) : nullptr, (size_t)c->m * c->k, c->idx_print}));
     c->print_done = check;
     targets.bits = c->tgt_bits;
     *sum = usl_loss_sum{c->bce_partials, blocks, scale, loss, targets};

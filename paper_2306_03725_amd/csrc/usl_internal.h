@@ -74,8 +74,8 @@ struct usl_ctx {
     float* nz_val;            size_t nz_val_cap;     // [max_b][m/32] its gradient
     const float* nz_lists_of; // g that has just been looked at (only set inside usl_train_step), else NULL
     bool nz_lists_tried;      // ... and whether lists were built for it (else only the dense kernels run)
-    uint32_t* hint_host;      // pinned: [0] serial of the last finished look at a gradient sample, [1] 1 = it was dense
-    uint32_t* hint_dev;       // the same words as the device addresses them
+    uint32_t* hint_host;      // pinned: serial of the last finished look at a gradient, above one bit: it was dense
+    uint32_t* hint_dev;       // the same word as the device addresses it
     uint32_t hint_seen, probe_serial;
     int sparse_streak;        // looks in a row that found the sample sparse
     // the register-list forms (k_backward_input_lds.hip): [0] lists of 68 slots per lane from windows of up to 32768
