@@ -780,6 +780,14 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
             asm volatile("" : "+v"(marks[l]));
         }
     };
+    // Scores leave past the caches: as ordinary stores they push rows of x out of the L2 (forward of m = 600k, d = 20k, k = 32, b = 128: 331
+    // and 320 us; m = 500k, d = 32k, b = 256: 761 and 751).  But two wavefronts share a line where a row of scores does not begin with
+    // one, and past the caches its halves reach the memory one by one: labels of few slots, whose stores weigh as much as their
+    // gathers, wait for that (m = 173 019, d = 64, k = 4, b = 438: 124 and, through the caches, 74; k = 12 133 and 89; m = 400 003, d = 300, k = 16,
+    // b = 100 76 and 62), and lose 4 to 8 % through the caches where it does (m = 1M, d = 2000, k = 8, b = 32: 39.0 and 40.6).  A test at run time
+    // cost both (80 and 40.5 us).  Not where the loss is part of it: there is more between the stores (steps at these sizes 2 to 4 %
+    // slower through the caches).
+    constexpr bool past = LOSS || K > 16;
     auto put = [&](int g, int l, const float (&z)[Q]) {
         int jl = (int)threadIdx.x + l * NT;   // rebuilt here: kept, every label's offset would be a register across the gathers
         asm volatile("" : "+v"(jl));
@@ -799,9 +807,8 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
                             o = r.g;
                             sum += r.l;
                         }
-                        // past the caches: as ordinary stores they push rows of x out of the L2 (forward of m = 1M, d = 2000, k = 8, b = 32: 42.1 and 39.0 us;
-                        // m = 600k, d = 20k, k = 32, b = 128: 331 and 320; m = 500k, d = 32k, b = 256: 761 and 751)
-                        __builtin_nontemporal_store(o, out + ((size_t)(g * Q + q) * m + j0) + (uint32_t)jl);
+                        float* to = out + ((size_t)(g * Q + q) * m + j0) + (uint32_t)jl;
+                        if constexpr (past) __builtin_nontemporal_store(o, to); else *to = o;
                         if constexpr (LOSS == 2) {   // lane 0's word and, where the wavefront has more than 32 labels, lane 1's
                             const uint64_t set = __ballot(o != 0.f);
                             const int first = __builtin_amdgcn_readfirstlane(jl), lane = jl & 63;   // (blocks of labels begin at a multiple of 32)
