@@ -505,6 +505,7 @@ struct Launch {
     int64_t nblk;
     int G;              // parts of the batch
     int64_t extra;      // workgroups beyond nblk, of a tail that takes the batch in parts of its own
+    int resident;       // workgroups that a compute unit is taken to hold
     size_t lds;
 };
 
@@ -524,8 +525,69 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
     const int cus = c->num_cu;
     Launch best;
     best.kern.fn = nullptr;
-    double best_t = 0.0, even_t = 0.0;   // even_t: of the chosen shape and split, blocks dealt evenly
+    double best_t = 0.0;
+    // clocks of wgs workgroups with gpb groups and `labels` labels each, `res` workgroups to a compute unit
+    auto clocks = [&](const ProductKernel& kern, const Geom& tg, int res, int64_t wgs, int gpb, int labels) {
+        const int lanes = (labels + 63) / 64 * 64;   // whole wavefronts gather
+        const double most = (double)((wgs + cus - 1) / cus);      // workgroups the busiest compute unit runs
+        const double per_cu = wgs > cus ? 0.75 * most + 0.25 * wgs / cus : most;
+        const double rounds = (double)((wgs + (int64_t)cus * res - 1) / ((int64_t)cus * res));
+        const double together = most / rounds;
+        const double copy = (double)gpb * L.row_bytes / 42.0;
+        // At most two wavefronts on a SIMD: they wait for their reads.  The factors are from workgroups of 512 lanes with two
+        // labels each and of 1024 with one: m = 100k, d = 4k, k = 32, b = 128: forward 63 and 54 us, weight gradient 89 and 76;
+        // m = 200k, d = 8k, b = 64, bfloat16: 60.4 and 57.3, 83 and 70.  (512 lanes with one label each lose nothing to 1024 in the
+        // weight gradient: m = 646k, d = 2k, k = 64, b = 31: 223 and 253.)
+        const bool thin = kern.NT / 64 * res <= 8;
+        const double waits = !thin ? 1.0 : !backward ? 1.1 : kern.LPT > 1 ? 1.3 : 1.0;
+        const double gather = (double)gpb * lanes * kern.K * (L.halves ? 2 : 1) / reads_per_clk * waits;
+        const double more = copy > gather ? copy : gather, less = copy > gather ? gather : copy;
+        const double load = (double)labels * c->k * (4.0 + (backward ? 4.0 : es)) / 7.0;
+        const double tiles = (double)((gpb + tg.tile_rows - 1) / tg.tile_rows) * (L.halves ? 2 : 1);
+        const double latency = (double)gpb * ((labels + kern.NT - 1) / kern.NT) * kern.K * (L.halves ? 2 : 1) / (unit == 16 ? 4 : 8) * 200.0;
+        double busy = per_cu * (more + (tg.nbuf == 2 || together > 1.5 ? 0.5 : 1.0) * less);
+        if (busy < rounds * latency) busy = rounds * latency;
+        return busy + per_cu * load + rounds * (6000.0 + tiles * (tg.nbuf == 2 ? 600.0 : 1500.0) / (together > 1.0 ? together : 1.0));
+    };
+    auto sums_of = [&](int parts) { return backward && parts > 1 ? 6000.0 + (double)(parts + 1) * c->m * c->k * 4 / 4000.0 : 0.0; };
     const int shape_force = tune_shape(), split_force = tune_split(), tail_force = backward ? 0 : tune_tail(), labels_force = tune_labels();
+    auto shared_by = [&](int64_t same) {
+        const int64_t resident = (int64_t)best.resident * (cus / 8 > 0 ? cus / 8 : 1);   // workgroups on an XCD; they go round-robin to the 8
+        return (int)(same < 1 ? 1 : same < resident ? same : resident);
+    };
+    // the labels over n blocks of `labels`
+    auto deal = [&](int64_t n, int labels) {
+        // With the blocks of labels first, an XCD reads an eighth of the labels' rows and all of x; with the parts of the
+        // batch first (a multiple of 8 of them) the other way round.
+        // m = 16k, d = 32k, k = 32, b = 256 (x 33 MB, labels 4): forward 52 and 49 us, weight gradient 73 and 60; m = 4k,
+        // d = 65k: 76 and 31, 94 and 51; m = 30k, d = 16k, b = 128 (8.4 and 7.7): 43 and 47, 52 and 51.
+        best.geom.parts_first = best.G % 8 == 0 && n <= 65535 &&
+                                (int64_t)groups * L.row_bytes > 2 * c->m * c->k * (backward ? 4 : 4 + es);
+        best.geom.share = shared_by(best.geom.parts_first ? n : n / 8);
+        best.tail = Tail{0x7FFFFFFF, 1, 1, 1, labels};
+        best.extra = 0;
+        best.nblk = n;
+    };
+    // Labels of a block of equal size (k_products.h); 0: full blocks.  By the estimate, with the workgroups that registers and LDS really leave
+    // room for (of the 256-lane forms of 32 slots and more a compute unit holds half to three quarters of what the rule below takes them for): of 2212
+    // scores and weight gradients over the range of sizes where it is 10 % ahead the blocks of equal size are 6 % faster on average, 38 are slower by
+    // more than 3 %.  With the loss and one label a lane from 20 % on: of the steps below, more are slower than faster.
+    auto even_labels = [&]() -> int {
+        const ProductKernel& kern = best.kern;
+        const int per_block = kern.NT * kern.LPT, gpb = best.geom.groups_per_block;
+        hipFuncAttributes full, even;
+        if (hipFuncGetAttributes(&full, kern.fn) != hipSuccess || hipFuncGetAttributes(&even, kern.even) != hipSuccess) { (void)hipGetLastError(); return 0; }
+        if (!even_blocks_allowed(best.G, (int64_t)groups * L.row_bytes, full.localSizeBytes, even.localSizeBytes)) return 0;
+        const int res = resident_workgroups(kern.NT, full.numRegs, best.lds);
+        const int labels = even_block_labels(c->m, kern, best.nblk, best.G, cus, res);
+        const int64_t wgs = best.nblk * best.G, n = (c->m + labels - 1) / labels;
+        if (labels >= per_block || (with_loss && (size_t)(n * best.G) > usl_forward_blocks(c))) return 0;
+        const int64_t tail = best.extra ? best.tail.blocks : 0;
+        double t = clocks(kern, best.geom, res, wgs - tail, gpb, per_block) + sums_of(best.G);
+        if (tail) t += clocks(kern, best.geom, res, tail + best.extra, best.tail.groups, per_block);
+        const double t_even = clocks(kern, best.geom, res, n * best.G, gpb, labels) + sums_of(best.G);
+        return t_even * (with_loss && kern.LPT == 1 ? 1.2 : 1.1) < t ? labels : 0;
+    };
     for (int shape = 0; shape < 4; ++shape) {
         if (shape_force >= 0 && shape != shape_force && kernel_for(c, L, kind, shape_force).fn) continue;
         const ProductKernel kern = kernel_for(c, L, kind, shape);
@@ -552,31 +614,7 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
         const int by_regs = (512 / regs > 8 ? 8 : 512 / regs) * 4 / (kern.NT / 64);
         if (res > by_regs) res = by_regs;
         if (res < 1) res = 1;
-        // clocks of wgs workgroups with gpb groups and `labels` labels each
-        auto clocks = [&](int64_t wgs, int gpb, int labels) {
-            const int lanes = (labels + 63) / 64 * 64;   // whole wavefronts gather
-            const double most = (double)((wgs + cus - 1) / cus);      // workgroups the busiest compute unit runs
-            const double per_cu = wgs > cus ? 0.75 * most + 0.25 * wgs / cus : most;
-            const double rounds = (double)((wgs + (int64_t)cus * res - 1) / ((int64_t)cus * res));
-            const double together = most / rounds;
-            const double copy = (double)gpb * L.row_bytes / 42.0;
-            // At most two wavefronts on a SIMD: they wait for their reads.  The factors are from workgroups of 512 lanes with two
-            // labels each and of 1024 with one: m = 100k, d = 4k, k = 32, b = 128: forward 63 and 54 us, weight gradient 89 and 76;
-            // m = 200k, d = 8k, b = 64, bfloat16: 60.4 and 57.3, 83 and 70.  (512 lanes with one label each lose nothing to 1024 in the
-            // weight gradient: m = 646k, d = 2k, k = 64, b = 31: 223 and 253.)
-            const bool thin = kern.NT / 64 * res <= 8;
-            const double waits = !thin ? 1.0 : !backward ? 1.1 : kern.LPT > 1 ? 1.3 : 1.0;
-            const double gather = (double)gpb * lanes * kern.K * (L.halves ? 2 : 1) / reads_per_clk * waits;
-            const double more = copy > gather ? copy : gather, less = copy > gather ? gather : copy;
-            const double load = (double)labels * c->k * (4.0 + (backward ? 4.0 : es)) / 7.0;
-            const double tiles = (double)((gpb + tg.tile_rows - 1) / tg.tile_rows) * (L.halves ? 2 : 1);
-            const double latency = (double)gpb * ((labels + kern.NT - 1) / kern.NT) * kern.K * (L.halves ? 2 : 1) / (unit == 16 ? 4 : 8) * 200.0;
-            double busy = per_cu * (more + (tg.nbuf == 2 || together > 1.5 ? 0.5 : 1.0) * less);
-            if (busy < rounds * latency) busy = rounds * latency;
-            return busy + per_cu * load + rounds * (6000.0 + tiles * (tg.nbuf == 2 ? 600.0 : 1500.0) / (together > 1.0 ? together : 1.0));
-        };
-        const int64_t resident = (int64_t)res * (cus / 8 > 0 ? cus / 8 : 1);   // workgroups on an XCD; they go round-robin to the 8
-        auto shared_by = [&](int64_t same) { return (int)(same < 1 ? 1 : same < resident ? same : resident); };
+        const auto time_of = [&](int64_t wgs, int gpb) { return clocks(kern, tg, res, wgs, gpb, (int)per_block); };
         for (int G = 1; G <= groups; G = G < 8 ? G + 1 : G + (G + 3) / 4) {
             if ((split_force > 0 || tail_force > 0) && G > 1) break;
             const int split = split_force > 0 ? split_force : G, gpb = (groups + split - 1) / split;
@@ -585,72 +623,47 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
             if (backward && parts > 1 && (size_t)parts * c->m * c->k * 4 > ((size_t)1 << 29)) break;
             if (with_loss && parts > 1 && (size_t)(nblk * parts) > usl_forward_blocks(c) && split_force <= 0) break;
             const int64_t slots = (int64_t)cus * res;
-            // Blocks of as many labels as the lanes take, or, with the same shape and split, of so many fewer that the rounds of workgroups are full: a
-            // round that leaves compute units idle takes as long as a full one.  m = 200k, d = 8k, k = 32, b = 64, bfloat16 (196 blocks of 1024 labels or
-            // 250 of 800): forward 58 and 53 us; weight gradient of m = 300k, d = 24k, k = 48, b = 64: 255 and 227; m = 300k, d = 5k, k = 16, b = 64: 90 and 82.
-            bool chosen = false;
-            for (int even = 0; even < (chosen ? 2 : 1); ++even) {
-                int labels = (int)per_block;
-                int64_t n = nblk;
-                if (even) {
-                    const int64_t rounds = (nblk * parts + slots - 1) / slots, most = rounds * slots / parts;
-                    labels = (int)(((c->m + most - 1) / most + 31) / 32 * 32);   // (the slot order goes by 32 labels)
-                    if (labels_force > 0) labels = (labels_force + 31) / 32 * 32;
-                    if (labels >= (int)per_block || tail_force > 0) break;
-                    n = (c->m + labels - 1) / labels;
-                    if (with_loss && (size_t)(n * parts) > usl_forward_blocks(c) && labels_force <= 0) break;
-                }
-                double t = clocks(n * parts, gpb, labels);
-                if (backward && parts > 1) t += 6000.0 + (double)(parts + 1) * c->m * c->k * 4 / 4000.0;
-                if (even && labels_force > 0) t = 0.0;
-                // A last round of workgroups that leaves most of the chip idle: its blocks take the batch in parts, so that there are
-                // more and shorter workgroups of them (the scores need no adding up).  m = 670k, d = 16k, k = 32, b = 32 (328 blocks
-                // of 2048 labels, 72 in three parts): 187 and 162 us; m = 600k, d = 20k, k = 32, b = 128: 452 and 330; m = 670k, d = 32k,
-                // k = 64, b = 256, bfloat16: 1450 and 1305.
-                const int64_t last = tail_force > 0 ? (n + 1) / 2 : n > slots ? n % slots : 0;
-                const int64_t tail = parts == 1 && !backward && !even ? last : 0;
-                int tail_gpb = 0;
-                const double whole = t;
-                for (int T = tail_force > 0 ? tail_force : 2; tail > 0 && T <= groups && (T <= 16 || T == tail_force); ++T) {
-                    const int per = (groups + T - 1) / T;
-                    const int64_t items = tail * ((groups + per - 1) / per);
-                    if (with_loss && (size_t)(n - tail + items) > usl_forward_blocks(c) && tail_force <= 0) break;
-                    const double with = clocks(n - tail, gpb, labels) + clocks(items, per, labels);
-                    if (with < t || tail_force > 0) { t = with; tail_gpb = per; }
-                    if (tail_force > 0) break;
-                }
-                // ... but labels of eight slots with two wavefronts on a SIMD have to win against another shape or split by 8 %: they wait for
-                // the stores of the scores, half as many as their reads, which the estimate leaves out (m = 645k, d = 3k, k = 8, b = 125:
-                // 512 lanes and a tail 78 us by the estimate, 123 measured; 1024 lanes in three parts 83 and 98).
-                if (tail_gpb && kern.K == 8 && kern.NT / 64 * res <= 8) t = t * 1.08 < whole ? t * 1.08 : whole;
-                // (By 10 % of the estimate, which is no better than that: by 2 %, m = 300k, d = 7491, k = 64, b = 47 177 and 193 us, m = 153k, d = 1419,
-                // k = 16, b = 16 25.3 and 26.5, beside gains of 3 to 10 %.)
-                if (best.kern.fn && t * (even ? 1.1 : 1.0) >= (even ? even_t : best_t)) continue;
-                chosen = true;
-                if (even) even_t = t;
-                else best_t = even_t = t;
-                best.kern = kern;
-                if (even) best.kern.fn = kern.even;
-                tg.groups_per_block = gpb;
-                // With the blocks of labels first, an XCD reads an eighth of the labels' rows and all of x; with the parts of the
-                // batch first (a multiple of 8 of them) the other way round.
-                // m = 16k, d = 32k, k = 32, b = 256 (x 33 MB, labels 4): forward 52 and 49 us, weight gradient 73 and 60; m = 4k,
-                // d = 65k: 76 and 31, 94 and 51; m = 30k, d = 16k, b = 128 (8.4 and 7.7): 43 and 47, 52 and 51.
-                tg.parts_first = parts % 8 == 0 && n <= 65535 &&
-                                 (int64_t)groups * L.row_bytes > 2 * c->m * c->k * (backward ? 4 : 4 + es);
-                tg.share = shared_by(tg.parts_first ? n : n / 8);
-                best.tail = Tail{0x7FFFFFFF, 1, 1, 1, labels};
-                best.extra = 0;
-                if (tail_gpb) {
-                    best.tail = Tail{(int)(n - tail), (int)tail, tail_gpb, shared_by(tail / 8), labels};
-                    best.extra = tail * ((groups + tail_gpb - 1) / tail_gpb) - tail;
-                }
-                best.geom = tg;
-                best.nblk = n;
-                best.G = (int)parts;
-                best.lds = lds;
+            double t = time_of(nblk * parts, gpb) + sums_of((int)parts);
+            // A last round of workgroups that leaves most of the chip idle: its blocks take the batch in parts, so that there are
+            // more and shorter workgroups of them (the scores need no adding up).  m = 670k, d = 16k, k = 32, b = 32 (328 blocks
+            // of 2048 labels, 72 in three parts): 187 and 162 us; m = 600k, d = 20k, k = 32, b = 128: 452 and 330; m = 670k, d = 32k,
+            // k = 64, b = 256, bfloat16: 1450 and 1305.
+            const int64_t last = tail_force > 0 ? (nblk + 1) / 2 : nblk > slots ? nblk % slots : 0;
+            const int64_t tail = parts == 1 && !backward ? last : 0;
+            int tail_gpb = 0;
+            const double whole = t;
+            for (int T = tail_force > 0 ? tail_force : 2; tail > 0 && T <= groups && (T <= 16 || T == tail_force); ++T) {
+                const int per = (groups + T - 1) / T;
+                const int64_t items = tail * ((groups + per - 1) / per);
+                if (with_loss && (size_t)(nblk - tail + items) > usl_forward_blocks(c) && tail_force <= 0) break;
+                const double with = time_of(nblk - tail, gpb) + time_of(items, per);
+                if (with < t || tail_force > 0) { t = with; tail_gpb = per; }
+                if (tail_force > 0) break;
+            }
+            // ... but labels of eight slots with two wavefronts on a SIMD have to win against another shape or split by 8 %: they wait for
+            // the stores of the scores, half as many as their reads, which the estimate leaves out (m = 645k, d = 3k, k = 8, b = 125:
+            // 512 lanes and a tail 78 us by the estimate, 123 measured; 1024 lanes in three parts 83 and 98).
+            if (tail_gpb && kern.K == 8 && kern.NT / 64 * res <= 8) t = t * 1.08 < whole ? t * 1.08 : whole;
+            if (best.kern.fn && t >= best_t) continue;
+            best_t = t;
+            best.kern = kern;
+            tg.groups_per_block = gpb;
+            best.geom = tg;
+            best.resident = res;
+            best.lds = lds;
+            best.G = (int)parts;
+            deal(nblk, (int)per_block);
+            if (tail_gpb) {
+                best.tail = Tail{(int)(nblk - tail), (int)tail, tail_gpb, shared_by(tail / 8), (int)per_block};
+                best.extra = tail * ((groups + tail_gpb - 1) / tail_gpb) - tail;
             }
         }
+    }
+    if (!best.kern.fn || tail_force > 0) return best;
+    const int labels = labels_force > 0 ? (labels_force + 31) / 32 * 32 : even_labels();
+    if (labels > 0 && labels < best.kern.NT * best.kern.LPT) {
+        best.kern.fn = best.kern.even;
+        deal((c->m + labels - 1) / labels, labels);
     }
     return best;
 }
