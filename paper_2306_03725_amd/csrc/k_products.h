@@ -6,8 +6,9 @@
 
 namespace usl_products {
 
-// FORWARD_LOSS: the scores become the gradient of the loss; FORWARD_MARKS: of the squared hinge, and its nonzeros are marked
-enum ProductKind { FORWARD, FORWARD_LOSS, FORWARD_MARKS, WEIGHT_GRADIENT };
+// FORWARD_CACHED: the scores go through the caches where FORWARD's go past them (K = 24 and four instances a read; others: FORWARD's kernel); FORWARD_LOSS: the scores become
+// the gradient of the loss; FORWARD_MARKS: of the squared hinge, and its nonzeros are marked
+enum ProductKind { FORWARD, FORWARD_CACHED, FORWARD_LOSS, FORWARD_MARKS, WEIGHT_GRADIENT };
 
 struct ProductKernel {
     const void* fn;        // nullptr: no such kernel

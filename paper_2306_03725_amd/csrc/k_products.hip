@@ -787,11 +787,20 @@ namespace {
 
 size_t target_words(const usl_ctx* c) { return (size_t)((c->max_b + 31) / 32) * (size_t)c->m; }
 
+// Labels of 24 slots: through the caches the scores take 5 to 15 % longer, but where a row of them does not begin with a line (see put in k_forward), there are many
+// of them and rows of x are so short that little else is under way, past the caches up to 50 %: m = 327 357, d = 38, b = 189, bfloat16 132 us and 88;
+// m = 413 191, d = 520, b = 219, bfloat16 169 and 138; m = 400 003, d = 300, b = 100 78 and 74.  Past the caches and through them beside the lines: m = 756 271, d = 525,
+// b = 136 170 and 195; m = 59 655, b = 387 46 and 50; b = 33 69 and 74; 44 MB of scores 27 and 32.  (Of 32 slots and more they are nowhere faster through the caches.)
+bool scores_through_caches(const usl_ctx* c, const Layout& L, const float* out, int32_t b) {
+    return L.K == 24 && (c->m % 32 != 0 || (uintptr_t)out % 128 != 0) && (size_t)c->d * (c->storage == USL_F32 ? 4 : 2) <= 1280 && c->m >= 80000 && b >= 36 &&
+           c->m * b >= (int64_t)1 << 24;
+}
+
 // the forward kernel over the whole batch, with or without the loss (then `before` says what the targets are; their bits are set
 // here and taken back by the kernel that ends the step)
 usl_status run_forward(usl_ctx* c, const Layout& L, const void* x, const int32_t* idx, const void* W, float* out, int32_t b, LossArgs loss,
                        size_t* blocks, Before before = Before{}) {
-    const Launch p = choose(c, L, b, loss.nonzeros ? FORWARD_MARKS : loss.kind >= 0 ? FORWARD_LOSS : FORWARD);
+    const Launch p = choose(c, L, b, loss.nonzeros ? FORWARD_MARKS : loss.kind >= 0 ? FORWARD_LOSS : scores_through_caches(c, L, out, b) ? FORWARD_CACHED : FORWARD);
     const uint8_t* perm = nullptr;
     const void* xi = nullptr;
     USL_TRY(slot_order(c, idx, &perm));

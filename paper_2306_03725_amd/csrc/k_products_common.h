@@ -703,7 +703,7 @@ struct LossArgs {
 // LOSS: 0 the scores, 1 either loss, 2 the squared hinge with its nonzeros marked, one bit per score, where few of them are expected: the
 // pass over g that listed them took 105 us at m = 500k, b = 256, and clearing the weight gradient, which goes out here while the chip waits
 // for LDS anyway, 11.  (Instances of their own: with a test at run time the step of the binary cross-entropy there took 1 % longer.)
-template <int K, int LPT, int NT, typename TS, int Q, bool HALVES, int LOSS, bool EVEN>
+template <int K, int LPT, int NT, typename TS, int Q, bool HALVES, int LOSS, bool EVEN, bool CACHED>
 __global__ void __launch_bounds__(NT)
 k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS* __restrict__ W, float* __restrict__ out,
           int64_t m, int k, int b, Geom tg, const uint8_t* __restrict__ perm, LossArgs loss, Tail tail) {
@@ -785,9 +785,9 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
     // one, and past the caches its halves reach the memory one by one: labels of few slots, whose stores weigh as much as their
     // gathers, wait for that (m = 173 019, d = 64, k = 4, b = 438: 124 and, through the caches, 74; k = 12 133 and 89; m = 400 003, d = 300, k = 16,
     // b = 100 76 and 62), and lose 4 to 8 % through the caches where it does (m = 1M, d = 2000, k = 8, b = 32: 39.0 and 40.6).  A test at run time
-    // cost both (80 and 40.5 us).  Not where the loss is part of it: there is more between the stores (steps at these sizes 2 to 4 %
-    // slower through the caches).
-    constexpr bool past = LOSS || K > 16;
+    // cost both (80 and 40.5 us).  So labels of up to 16 slots go through the caches, of 24 where scores_through_caches says so.  Not where the loss
+    // is part of it: there is more between the stores (steps at these sizes 2 to 4 % slower through the caches).
+    constexpr bool past = LOSS || !CACHED;
     auto put = [&](int g, int l, const float (&z)[Q]) {
         int jl = (int)threadIdx.x + l * NT;   // rebuilt here: kept, every label's offset would be a register across the gathers
         asm volatile("" : "+v"(jl));

@@ -20,10 +20,11 @@ ProductKernel pick(ProductKind kind, int shape) {
     constexpr int L = K == 8 ? 4 : labels_per_lane(K, 64), L2 = labels_per_lane(K, 128);
     constexpr bool WIDE_PAIRS = K == 64 && sizeof(TS) == 2 && Q <= 2;   // 64 packed slots take 64 of the 128 registers
 #define USL_KIND(LPT, NT, EVEN)                                                                                \
-    (kind == WEIGHT_GRADIENT ? (const void*)k_backward_weight<K, LPT, NT, TS, Q, HALVES, EVEN>                  \
-     : kind == FORWARD_MARKS ? (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, 2, EVEN>                       \
-     : kind == FORWARD_LOSS  ? (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, 1, EVEN>                       \
-                             : (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, 0, EVEN>)
+    (kind == WEIGHT_GRADIENT  ? (const void*)k_backward_weight<K, LPT, NT, TS, Q, HALVES, EVEN>                 \
+     : kind == FORWARD_MARKS  ? (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, 2, EVEN, false>               \
+     : kind == FORWARD_LOSS   ? (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, 1, EVEN, false>               \
+     : kind == FORWARD_CACHED ? (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, 0, EVEN, (K <= 16 || (K == 24 && Q == 4))> \
+                              : (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, 0, EVEN, (K <= 16)>)
 #define USL_PICK(LPT, NT)                                                                                      \
     ProductKernel{USL_KIND(LPT, NT, false), USL_KIND(LPT, NT, true), K, LPT, NT, transpose_bytes<K, NT>()}
     if constexpr (Q > 1) {
