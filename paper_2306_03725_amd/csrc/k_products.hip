@@ -136,20 +136,25 @@ __device__ __forceinline__ void mark_targets(const usl_targets& t, int q, int n)
         }
     }
 }
-// What a step needs before forward: the targets marked, and the fingerprint of idx compared for the backward product where lists stand
-// (a launch of its own takes 4 to 8 us).  Done by block `at` of n blocks of 256 lanes.
+// What a step needs before forward: the targets marked, the fingerprint of idx compared for the backward product where lists stand
+// (a launch of its own takes 4 to 8 us), the counts of the nonzeros' lists cleared where forward marks the nonzeros.  Done by block `at` of n blocks of 256 lanes.
 struct Before {
     usl_targets targets;      // off = nullptr: nothing to do
     const uint32_t* idx;      // nullptr: nothing to compare
     size_t n_words;
     uint64_t* print;
+    uint32_t* nz_state;       // nullptr, or whose instances' counts are to be cleared (k_list_nonzeros)
     __host__ __device__ int print_blocks() const { return idx ? USL_PRINT_SUMS / MARK_WAVES : 0; }
     int blocks() const { return print_blocks() + (targets.b + MARK_WAVES - 1) / MARK_WAVES; }
 };
 __device__ __forceinline__ void before_forward(const Before& w, int at, int n) {
     const int first = w.print_blocks(), wave = (int)(threadIdx.x >> 6);
     if (at < first) usl_idx_fingerprint_sums<1>(w.idx, w.n_words, w.print, USL_PRINT_BOTH_PRODUCTS, 0, at * MARK_WAVES + wave, 0);
-    if (at >= first) mark_targets(w.targets, (at - first) * MARK_WAVES + wave, (n - first) * MARK_WAVES);
+    if (at < first) return;
+    const int q = (at - first) * MARK_WAVES + wave, waves = (n - first) * MARK_WAVES;
+    if (w.nz_state && (threadIdx.x & 63) == 0)
+        for (int i = q; i < w.targets.b; i += waves) *reinterpret_cast<uint64_t*>(w.nz_state + usl_nz_count_at(i)) = 0;
+    mark_targets(w.targets, q, waves);
 }
 __global__ void __launch_bounds__(256)
 k_before_forward(Before w) { before_forward(w, (int)blockIdx.x, (int)gridDim.x); }
@@ -875,7 +880,7 @@ usl_status usl_launch_forward_loss(usl_ctx* c, const void* x, const int32_t* idx
     const bool check = c->lf[1].built_for == idx;   // lists that the backward product will use
     if (marks_clear) USL_TRY(usl_sparse_marks_ready(c));
     USL_TRY(run_forward(c, L, x, idx, W, g, b, LossArgs{loss_kind, scale, nullptr, nullptr, marks_clear ? c->nz_bits : nullptr, (int64_t)usl_sparse_mark_words(c), marks_clear},
-                        &blocks, Before{targets, check ? reinterpret_cast<const uint32_t*>(idx) : nullptr, (size_t)c->m * c->k, c->idx_print}));
+                        &blocks, Before{targets, check ? reinterpret_cast<const uint32_t*>(idx) : nullptr, (size_t)c->m * c->k, c->idx_print, marks_clear ? c->nz_state : nullptr}));
     c->print_done = check;
     targets.bits = c->tgt_bits;
     *sum = usl_loss_sum{c->bce_partials, blocks, scale, loss, targets};

@@ -26,15 +26,13 @@ constexpr int CG_NT = 256, CG_PER = 32, CG_CHUNK = CG_NT * CG_PER;   // labels p
 // one another, and the first of them with the word that every block reads first: what a block waits for is its turn at
 // that line (k_compact_g, m = 500k, b = 256, usl_backward_weight on 0.5 % nonzeros 293 us with the first rows first, 312 with the
 // last, now 272 with either; on 0.1 % 190, 198 and 166; the squared-hinge step 1029, 1010 and 990).
-constexpr size_t STATE_LINE = 32;
-__host__ __device__ constexpr size_t count_at(size_t i) { return (i + 1) * STATE_LINE; }
+constexpr size_t STATE_LINE = USL_NZ_STATE_LINE;
 
 // The end of a look at g, by one lane of each of its blocks: `full`, the instance's nonzeros cannot fit a list; `dense`, lists would not be worth
 // trying.  The blocks meet in one 64-bit word, a count of blocks for each verdict beside the count of all, so nothing has to be
 // made visible before it: a fence among the XCDs writes their L2s back, here with a loss's gradients in them.  The block that
-// completes the count decides for all and leaves the word 0 for the next look.  (usl_sparse_supported: a batch has at most 2^18
-// instances.)  The host's word, serial and verdict in one, needs no order of stores either.
-// m = 500k, b = 256: k_probe_density 17.8 us and 4.9 of a launch that cleared the words, now 9.4; k_list_nonzeros 13.8 and 10.7.
+// completes the count decides for all and leaves the word 0 for the next look.  (A batch has at most 65535 instances.)  The host's word, serial and verdict in one, needs no order of stores either.
+// m = 500k, b = 256: k_probe_density 17.8 us and 4.9 of a launch that cleared the words, now 9.4.
 constexpr int LOOK_BITS = 20;
 __device__ __forceinline__ void look_done(uint32_t* state, bool full, bool dense, uint32_t blocks, uint32_t* hint, uint32_t serial) {
     unsigned long long* word = reinterpret_cast<unsigned long long*>(state + 2);
@@ -82,7 +80,7 @@ k_probe_density(const float* __restrict__ g, int64_t m, uint32_t* __restrict__ s
     // the lists hold m/32 entries per instance: a sample twice as dense as that cannot fit
     if (threadIdx.x == 0) {
         // what the host reads before its next call: would lists have been worth trying?  (sample at most 1/64 nonzero)
-        state[count_at(blockIdx.x)] = 0;
+        state[usl_nz_count_at(blockIdx.x)] = 0;
         look_done(state, seen >= 128 && (uint64_t)hit * 16 > seen, (uint64_t)hit * 64 > seen, gridDim.x, hint, serial);
     }
 }
@@ -129,7 +127,7 @@ k_compact_g(const float* __restrict__ g, int64_t m, uint32_t cap, uint32_t* __re
         total += t;
     }
     if (total == 0) return;   // the same for every lane of the block
-    if (threadIdx.x == 0) block_base = atomicAdd(&state[count_at(i)], total);
+    if (threadIdx.x == 0) block_base = atomicAdd(&state[usl_nz_count_at(i)], total);
     __syncthreads();
     const uint32_t base = block_base;
     if (base + total > cap) {
@@ -149,58 +147,75 @@ k_compact_g(const float* __restrict__ g, int64_t m, uint32_t cap, uint32_t* __re
     }
 }
 
-// The lists from the marks that forward left, one workgroup per instance: its words' counts, running sums, the labels, then the gradients
-// of the listed labels (4 to 64 bytes of memory each instead of the whole row: at m = 500k, b = 256 16 MB of marks for 512 MB of g).  The
-// counts are exact, so this is the look as well (k_probe_density).
-// m = 500k, k = 32, b = 256, squared hinge, 0.2 % nonzero: 11 us, in the place of 116 (k_probe_density, k_compact_g).
-constexpr int LN_NT = 1024, LN_PER = 16;   // words a lane has in flight
+// The lists from the marks that forward left: a workgroup has 1024 words of an instance, counts and places them, and brings the gradients
+// of the listed labels (4 to 64 bytes of memory each instead of the whole row: at m = 500k, b = 256 16 MB of marks for 512 MB of g).  One atomic
+// a workgroup, in the instance's own line, reserves the places and counts the workgroups; the instance's last one knows its count, which is
+// exact, so this is the look as well (k_probe_density).  k_before_forward or k_interleave cleared the lines.
+// What bounds it is the chain of four trips to memory (marks, place, labels, gradients), so it is spread over the chip.  With one workgroup for an instance
+// m = 1.5M, k = 16, b = 8, 1.6 % nonzero took 37 us, now 6.7 (the look and the pass over g 27); m = 3M, b = 8 69 and 8.2; m = 500k, k = 32, b = 256, 0.2 % nonzero
+// 11.2 and 9.6 (116).
+constexpr int LN_NT = 256, LN_PER = 4, LN_WORDS = LN_NT * LN_PER;
 __global__ void __launch_bounds__(LN_NT)
 k_list_nonzeros(const uint32_t* __restrict__ bits, int64_t words, const float* __restrict__ g, int64_t m, int b, uint32_t cap,
                 uint32_t* __restrict__ state, int32_t* __restrict__ nz_lab, float* __restrict__ nz_val, uint32_t* __restrict__ hint, uint32_t serial) {
+    typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // an instance's words begin anywhere
     __shared__ uint32_t wave_total[LN_NT / 64];
-    const int i = (int)blockIdx.x, lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+    __shared__ uint32_t block_base;
+    const int i = (int)blockIdx.y, lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
     const uint32_t* row = bits + (size_t)i * words;
-    int32_t* lab = nz_lab + (size_t)i * cap;
-    uint32_t count = 0;   // listed so far
-    for (int64_t w0 = 0; w0 < words; w0 += LN_NT * LN_PER) {
-        uint32_t v[LN_PER], cnt = 0;
+    const int64_t w0 = (int64_t)blockIdx.x * LN_WORDS + (int)threadIdx.x * LN_PER;
+    uint32_t v[LN_PER], cnt = 0;
+    if (w0 + LN_PER <= words) {
+        const u32x4_any t = *reinterpret_cast<const u32x4_any*>(row + w0);
+        v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+    } else {
 #pragma unroll
-        for (int u = 0; u < LN_PER; ++u) {
-            const int64_t w = w0 + u * LN_NT + (int)threadIdx.x;
-            v[u] = w < words ? row[w] : 0u;
-        }
-#pragma unroll
-        for (int u = 0; u < LN_PER; ++u) cnt += (uint32_t)__popc(v[u]);
-        uint32_t incl = cnt;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t t = __shfl_up(incl, o);
-            if (lane >= o) incl += t;
-        }
-        if (lane == 63) wave_total[wave] = incl;
-        __syncthreads();
-        uint32_t before = 0, total = 0;
-#pragma unroll
-        for (int q = 0; q < LN_NT / 64; ++q) {
-            const uint32_t t = wave_total[q];
-            if (q < wave) before += t;
-            total += t;
-        }
-        __syncthreads();   // (before the next turn's totals)
-        uint32_t at = count + before + incl - cnt;
-        count += total;
-        if (count > cap) break;   // the same for all lanes
-#pragma unroll
-        for (int u = 0; u < LN_PER; ++u)
-            for (uint32_t rest = v[u]; rest; rest &= rest - 1)
-                lab[at++] = (int32_t)((w0 + u * LN_NT + (int)threadIdx.x) * 32 + __ffs((int)rest) - 1);
+        for (int u = 0; u < LN_PER; ++u) v[u] = w0 + u < words ? row[w0 + u] : 0u;
     }
+#pragma unroll
+    for (int u = 0; u < LN_PER; ++u) cnt += (uint32_t)__popc(v[u]);
+    uint32_t incl = cnt;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t t = __shfl_up(incl, o);
+        if (lane >= o) incl += t;
+    }
+    if (lane == 63) wave_total[wave] = incl;
+    __syncthreads();
+    uint32_t before = 0, total = 0;
+#pragma unroll
+    for (int q = 0; q < LN_NT / 64; ++q) {
+        const uint32_t t = wave_total[q];
+        if (q < wave) before += t;
+        total += t;
+    }
+    if (threadIdx.x == 0) {   // workgroups above, entries below
+        const unsigned long long had = atomicAdd(reinterpret_cast<unsigned long long*>(state + usl_nz_count_at(i)), 1ull << 32 | total);
+        block_base = (uint32_t)had;
+        const uint32_t count = (uint32_t)had + total;
+        if ((uint32_t)(had >> 32) + 1 == gridDim.x) look_done(state, count > cap, (uint64_t)count * 64 > (uint64_t)m, (uint32_t)b, hint, serial);
+    }
+    __syncthreads();
+    const uint32_t base = block_base;
+    if (base + total > cap) return;   // the same for all lanes; the look finds the count too large
+    int32_t* lab = nz_lab + (size_t)i * cap + base;
+    float* val = nz_val + (size_t)i * cap + base;
+    uint32_t at = before + incl - cnt;
+#pragma unroll
+    for (int u = 0; u < LN_PER; ++u)
+        for (uint32_t rest = v[u]; rest; rest &= rest - 1) lab[at++] = (int32_t)((w0 + u) * 32 + __ffs((int)rest) - 1);
     __syncthreads();   // the labels are written
-    if (count <= cap)
-        for (uint32_t e = threadIdx.x; e < count; e += LN_NT) nz_val[(size_t)i * cap + e] = g[(size_t)i * m + lab[e]];
-    if (threadIdx.x == 0) {
-        state[count_at(i)] = count;
-        look_done(state, count > cap, (uint64_t)count * 64 > (uint64_t)m, (uint32_t)b, hint, serial);
+    constexpr int AT_ONCE = 4;
+    for (uint32_t e0 = threadIdx.x; e0 < total; e0 += LN_NT * AT_ONCE) {
+        int32_t j[AT_ONCE];
+        float z[AT_ONCE];
+#pragma unroll
+        for (int u = 0; u < AT_ONCE; ++u) j[u] = e0 + u * LN_NT < total ? lab[e0 + u * LN_NT] : 0;
+#pragma unroll
+        for (int u = 0; u < AT_ONCE; ++u) z[u] = e0 + u * LN_NT < total ? g[(size_t)i * m + j[u]] : 0.f;
+#pragma unroll
+        for (int u = 0; u < AT_ONCE; ++u)
+            if (e0 + u * LN_NT < total) val[e0 + u * LN_NT] = z[u];
     }
 }
 
@@ -227,7 +242,7 @@ k_bww_sparse(const TS* __restrict__ x, const int32_t* __restrict__ idx, const ui
              float* __restrict__ grad_W, int d, int k) {
     if (state[0] != 0) return;
     const int i = blockIdx.y;
-    const uint64_t items = (uint64_t)state[count_at(i)] * (uint32_t)k;
+    const uint64_t items = (uint64_t)state[usl_nz_count_at(i)] * (uint32_t)k;
     const int32_t* lab = nz_lab + (size_t)i * cap;
     const float* val = nz_val + (size_t)i * cap;
     const TS* row = x + (size_t)i * d;
@@ -256,7 +271,7 @@ k_bwi_sparse(const int32_t* __restrict__ idx, const TS* __restrict__ W, const ui
     const int nc = min(XS_COLS, d - c0);
     for (int c = threadIdx.x; c < nc; c += XS_NT) acc[c] = 0.f;
     __syncthreads();
-    const uint64_t items = (uint64_t)state[count_at(i)] * (uint32_t)k;
+    const uint64_t items = (uint64_t)state[usl_nz_count_at(i)] * (uint32_t)k;
     const int32_t* lab = nz_lab + (size_t)i * cap;
     const float* val = nz_val + (size_t)i * cap;
     for (uint64_t e = threadIdx.x; e < items; e += XS_NT) {
@@ -309,7 +324,7 @@ static usl_status state_ready(usl_ctx* c) {
         USL_HIP(c, hipHostGetDevicePointer((void**)&c->hint_dev, c->hint_host, 0));
     }
     if (c->nz_state) return USL_OK;
-    USL_TRY(usl_reserve(c, (void**)&c->nz_state, &c->nz_state_cap, count_at(c->max_b) * 4));
+    USL_TRY(usl_reserve(c, (void**)&c->nz_state, &c->nz_state_cap, usl_nz_count_at(c->max_b) * 4));
     hipLaunchKernelGGL(k_new_state, dim3(1), dim3(64), 0, c->stream, c->nz_state);
     return usl_check_launch(c, "state of the nonzeros' lists");
 }
@@ -350,7 +365,8 @@ usl_status usl_sparse_marks_ready(usl_ctx* c) {
 
 usl_status usl_sparse_lists(usl_ctx* c, const float* g, int32_t b, const uint32_t** gate) {
     USL_TRY(lists_ready(c));
-    hipLaunchKernelGGL(k_list_nonzeros, dim3((unsigned)b), dim3(LN_NT), 0, c->stream, c->nz_bits, (int64_t)usl_sparse_mark_words(c), g,
+    const int64_t words = (int64_t)usl_sparse_mark_words(c);
+    hipLaunchKernelGGL(k_list_nonzeros, dim3((unsigned)((words + LN_WORDS - 1) / LN_WORDS), (unsigned)b), dim3(LN_NT), 0, c->stream, c->nz_bits, words, g,
                        c->m, (int)b, list_capacity(c), c->nz_state, c->nz_lab, c->nz_val, c->hint_dev, ++c->probe_serial);
     *gate = c->nz_state;
     return usl_check_launch(c, "lists of the marked gradients");

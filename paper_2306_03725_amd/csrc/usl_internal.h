@@ -183,6 +183,8 @@ bool usl_sparse_expected(usl_ctx* ctx);
 usl_status usl_sparse_compact(usl_ctx* ctx, const float* g, int32_t b, const uint32_t** gate);
 // The same lists from the marks that forward left (ctx->nz_bits; usl_sparse_marks_ready before it): no look and no pass over g.
 usl_status usl_sparse_marks_ready(usl_ctx* ctx);
+static constexpr size_t USL_NZ_STATE_LINE = 32;   // words; the number of entries of instance i (below) and what else its line counts (above)
+__host__ __device__ constexpr size_t usl_nz_count_at(size_t i) { return (i + 1) * USL_NZ_STATE_LINE; }
 static inline size_t usl_sparse_mark_words(const usl_ctx* c) { return (size_t)((c->m + 31) / 32); }   // of an instance
 usl_status usl_sparse_lists(usl_ctx* ctx, const float* g, int32_t b, const uint32_t** gate);
 usl_status usl_sparse_backward_weight(usl_ctx* ctx, const void* x, const int32_t* idx, float* grad_W, int32_t b, bool cleared = false);

@@ -53,3 +53,37 @@ def test_gradients_from_marks(orc, m, d, k, b, storage, env, crowded, monkeypatc
         assert_close(gu.host(gW), orc.backward_weight(got_g, x, idx), 1e-5, "grad_W")
         assert_close(gu.host(gx), orc.backward_input(got_g, idx, W, d), 1e-4, "grad_x")
     L.close()
+
+
+@pytest.mark.parametrize("m,b", [(200031, 5), (98304, 3), (65537, 40)])
+def test_lists_of_several_workgroups(orc, m, b, monkeypatch):
+    """A list is written by a workgroup for every 32 768 labels: nearly all of its entries from one of them, thousands of it, up to what the list holds; a last
+    workgroup of one word; instances with none and with a single nonzero in the last label."""
+    import gpu_util as gu
+    from paper_2306_03725_amd import usl
+    monkeypatch.setenv("USL_TUNE_SPARSE", "always")
+    print("lists of several workgroups", m, b, flush=True)
+    d, k = 64, 8
+    cfg = wl.custom(m, d, k, b, positives=3, index=996)
+    idx = wl.gen_idx(cfg)
+    x = np.ones((b, d), np.float32)
+    x[1] *= 1e3
+    W = np.full((m, k), -1.0, np.float32)
+    W[7: 7 + m // 32 - 60] = np.float32(-0.05)     # inside the margin, but for instance 1
+    W[m // 2: m // 2 + 3] = np.float32(-0.01)
+    off, lab = np.arange(b + 1, dtype=np.int64), np.full(b, m - 1, np.int32)
+    L = usl.Layer(m, d, k, b)
+    m1, m2, g, gW, gx, loss = (gu.empty(s).fill_(float("nan")) for s in [(m, k), (m, k), (b, m), (m, k), (b, d), (1,)])
+    for turn in range(3):
+        m1.zero_(), m2.zero_()
+        L.train_step(gu.dev(x), gu.dev(idx), gu.dev(W), m1, m2, gu.dev(off), gu.dev(lab), 1, 1.0, 1, 0.0, 0.9, 0.999, 1e-8, g, gW, gx, loss, b)
+        L.invalidate()
+        ref_loss, ref_g = orc.sqh_loss_grad(orc.forward(x, idx, W), off, lab, 1.0)
+        got_g = gu.host(g)
+        assert_close(got_g, ref_g, 1e-5, "g")
+        count = (got_g != 0).sum(axis=1)
+        assert count[1] == 1 and m // 32 - 60 < count[0] <= m // 32
+        assert abs(float(loss) - ref_loss) <= 1e-5 * abs(ref_loss)
+        assert_close(gu.host(gW), orc.backward_weight(got_g, x, idx), 1e-5, "grad_W")
+        assert_close(gu.host(gx), orc.backward_input(got_g, idx, W, d), 1e-4, "grad_x")
+    L.close()
