@@ -576,7 +576,8 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
     // Labels of a block of equal size (k_products.h); 0: full blocks.  By the estimate, with the workgroups that registers and LDS really leave
     // room for (of the 256-lane forms of 32 slots and more a compute unit holds half to three quarters of what the rule below takes them for): of 2212
     // scores and weight gradients over the range of sizes where it is 10 % ahead the blocks of equal size are 6 % faster on average, 38 are slower by
-    // more than 3 %.  With the loss and one label a lane from 20 % on: of the steps below, more are slower than faster.
+    // more than 3 %.  With the loss 256-lane forms have to win by 20 %: of 96 steps below that 27 are slower by more than 3 %, 5 faster; of 17 with
+    // larger forms none and 3 (m = 200k, d = 8k, k = 32, b = 64, bfloat16: 219.5 and 212.4 with them).
     auto even_labels = [&]() -> int {
         const ProductKernel& kern = best.kern;
         const int per_block = kern.NT * kern.LPT, gpb = best.geom.groups_per_block;
@@ -591,7 +592,7 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
         double t = clocks(kern, best.geom, res, wgs - tail, gpb, per_block) + sums_of(best.G);
         if (tail) t += clocks(kern, best.geom, res, tail + best.extra, best.tail.groups, per_block);
         const double t_even = clocks(kern, best.geom, res, n * best.G, gpb, labels) + sums_of(best.G);
-        return t_even * (with_loss && kern.LPT == 1 ? 1.2 : 1.1) < t ? labels : 0;
+        return t_even * (with_loss && kern.NT == 256 ? 1.2 : 1.1) < t ? labels : 0;
     };
     for (int shape = 0; shape < 4; ++shape) {
         if (shape_force >= 0 && shape != shape_force && kernel_for(c, L, kind, shape_force).fn) continue;
