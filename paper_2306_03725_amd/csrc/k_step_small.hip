@@ -3,8 +3,8 @@
 // What bounds a step that gathers little is the chain of launches and of trips to memory behind one another, whatever the sizes: copy of the
 // activations, forward with the loss, the targets, both backward products, Adam took 30 us at m = 1024, d = 64, k = 8, b = 16, of which
 // k_both_lds, which brings lists, weights, slices of g and sums one after the other, 16.6.  Here a workgroup has 64 labels and the
-// whole batch: their rows, all of x and the targets come in together, and everything else happens in LDS.  Each of its four wavefronts takes all
-// 64 labels (a lane each) for a quarter of the groups of four instances; x lies interleaved by four, so a slot costs one read of 16 bytes.
+// whole batch: their rows and all of x come in, then the targets, and everything else happens in LDS.  Each of its four or eight wavefronts takes all
+// 64 labels (a lane each) for its share of the groups of four instances; x lies interleaved by four, so a slot costs one read of 16 bytes.
 // The input gradient of the workgroup's labels is gathered from its own connections in the order of their columns and left as a partial sum
 // per workgroup, which the second launch adds up in a fixed order.
 //
@@ -12,41 +12,17 @@
 // (column, slot) that rise from entry to entry are all its connections, once each, in order, whatever the scratch held before; anything else is sorted
 // anew.  So nothing here can be stale.
 //
-// Where it is used, and both paths' times: usl_step_small_applies.
+// Where it is used, and both paths' times: small_step_pays.
 #include <stdlib.h>
 #include <string.h>
 
 #include "k_adam.h"
 #include "k_products_common.h"   // dot2
+#include "k_step_small.h"
+
+using namespace usl_small;
 
 namespace {
-
-constexpr int NL = 64;                              // labels of a workgroup
-constexpr int MOST_K = 32, SLOT_BITS = 11;          // NL * MOST_K slots; a key: column above, slot below
-static_assert(NL * MOST_K == 1 << SLOT_BITS, "a slot fits its bits");
-constexpr int LDS_MOST = 144 * 1024;   // (m = 2746, d = 1636, k = 8, b = 19, 144 KB: 33 and 39 us; m = 2065, d = 878, k = 32, b = 26, 143 KB: 42 and 38)
-
-// Byte offsets in LDS
-struct SmallLds {
-    int x, red, g, rows, keys, ent, first, bits, off, bytes;
-};
-__host__ __device__ inline SmallLds small_lds(int d, int k, int b, int waves) {
-    const int G = (b + 3) / 4, x = G * d * 16, red = waves * NL * (k + 1) * 4;
-    SmallLds L;
-    L.x = 0;                                  // [G][d] units of four instances; then
-    L.red = 0;                                // [waves][NL][k + 1] sums of the weight gradient
-    L.g = (x > red ? x : red);                // [G][NL] of the gradient
-    L.rows = L.g + G * NL * 16;               // [NL][k + 1] {byte of the column's unit, weight}
-    L.keys = L.rows + NL * (k + 1) * 8;
-    int n2 = 64;
-    while (n2 < NL * k) n2 *= 2;
-    L.ent = L.keys + (n2 + 1) * 4 / 16 * 16 + 16;   // [NL * k] {byte of the label's unit, weight} in the order of the columns
-    L.first = L.ent + NL * k * 8;             // [d] first entry of a column, and behind it the last one + 1, 16 bits each
-    L.bits = L.first + (d * 4 + 15) / 16 * 16;   // [b] which of the labels are targets
-    L.off = L.bits + b * 8;                   // [b + 1] where the instances' targets begin
-    L.bytes = (L.off + (b + 1) * 4 + 15) / 16 * 16;
-    return L;
-}
 
 struct SmallArgs {
     const void* x;
@@ -63,8 +39,10 @@ struct SmallArgs {
     float scale, lr, b1, b2, eps, ic1, ic2;
 };
 
-// KP: k, or (FULL = false) the power of two above it
-template <typename TS, int KP, bool FULL, int NT>
+// KP: k, or (FULL = false) the power of two above it.  SHARED: wavefronts share the columns of a group of instances (of four
+// wavefronts one or two had long rows to themselves and the others none: m = 2096, d = 5314, k = 2, b = 4 67 and 26 us; m = 1762, d = 6033, k = 6, b = 1 47
+// and 20; rows of up to 128 columns 2 to 5 % slower so, and with three groups and more there is nothing to share).
+template <typename TS, int KP, bool FULL, int NT, bool SHARED>
 __global__ void __launch_bounds__(NT)
 k_step_small(SmallArgs a, TS* __restrict__ W) {
     constexpr int PER = NL * KP / NT, WAVES = NT / 64;   // slots of a lane
@@ -85,8 +63,12 @@ k_step_small(SmallArgs a, TS* __restrict__ W) {
     const size_t f0 = (size_t)j0 * k;
     const uint32_t inv = k > 1 ? 0xFFFFFFFFu / (uint32_t)k + 1u : 0u;   // e / k by a multiplication; exact: e < 2^11
     auto label_of = [&](int e) { return k > 1 ? (int)__umulhi((uint32_t)e, inv) : e; };
+    // of x and its gradient a wavefront has group `group0` and every WAVES-th after it, columns `column0` and every `columns`-th
+    static_assert(!SHARED || WAVES == 4, "one group or two");
+    const int share = !SHARED ? 0 : G == 1 ? wave : wave >> 1, group0 = !SHARED ? wave : G == 1 ? 0 : wave & 1;
+    const int column0 = share * 64 + label, columns = !SHARED ? 64 : G == 1 ? 256 : 128;
 
-    // everything that has to come from memory, at once
+    // what has to come from memory: the rows on their way together, behind them the offsets and x, which go to LDS as they come
     uint32_t col[PER];
     float w[PER], a1[PER], a2[PER];
     uint32_t ord[PER];
@@ -103,8 +85,8 @@ k_step_small(SmallArgs a, TS* __restrict__ W) {
     const int64_t t0 = a.off[0];
     for (int i = tid; i <= b; i += NT) offs[i] = (uint32_t)(a.off[i] - t0);
     const TS* x = reinterpret_cast<const TS*>(a.x);
-    for (int g = wave; g < G; g += WAVES)
-        for (int c = label; c < d; c += 64) {
+    for (int g = group0; g < G; g += WAVES)
+        for (int c = column0; c < d; c += columns) {
             float v[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) v[q] = 4 * g + q < b ? usl_load_f32<TS>(x, (size_t)(4 * g + q) * d + c) : 0.f;
@@ -289,9 +271,9 @@ k_step_small(SmallArgs a, TS* __restrict__ W) {
     for (int o = 32; o > 0; o >>= 1) lost += __shfl_down(lost, o);
     if (label == 0) reinterpret_cast<double*>(lds + L.rows)[wave] = lost;   // (rows have been read)
     if (a.sums) {
-        for (int g = wave; g < G; g += WAVES) {
+        for (int g = group0; g < G; g += WAVES) {
             const unsigned char* gg = reinterpret_cast<const unsigned char*>(gs + (size_t)g * NL);
-            for (int c = label; c < d; c += 64) {
+            for (int c = column0; c < d; c += columns) {
                 float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
                 const uint32_t range = reinterpret_cast<const uint32_t*>(first)[c];
                 uint32_t e = range & 0xFFFFu;
@@ -352,24 +334,14 @@ k_step_small_sums(const float* __restrict__ sums, int wgs, size_t n, float* __re
     if (wave == 0 && v < n) grad_x[v] = ((part[0][threadIdx.x] + part[1][threadIdx.x]) + part[2][threadIdx.x]) + part[3][threadIdx.x];
 }
 
-// Wavefronts of a workgroup: eight where four would have more than two groups of instances each
-int small_waves(int b) { return b > 32 ? 8 : 4; }
-
 }  // namespace
 
-// By max_b, so that every batch of a layer takes the same path and finds its scratch sized.  A workgroup is bound by its own chain, so the
-// path pays where all workgroups are resident at once (a second round costs as much as the first), whatever the sizes otherwise.  Both paths, us:
-// m = 1024, d = 64, k = 8, b = 16: 30.2 and 10.8; m = 4096, d = 256, k = 16, b = 32: 37.9 and 19.8; m = 16 000, d = 64, k = 32, b = 64: 65.6 and 29.1;
-// m = 36 551, d = 140, k = 16, b = 9: 47.2 and 25.0; two rounds: m = 31 147, d = 211, k = 31, b = 43: 70 and 88; m = 31 974, d = 843, k = 16, b = 19: 49 and 74.
 // USL_TUNE_SMALL=on|off: wherever the shape allows it at all, or never.
 bool usl_step_small_applies(const usl_ctx* c) {
     const char* e = getenv("USL_TUNE_SMALL");
     const bool on = e && strcmp(e, "on") == 0;
-    if (c->k > MOST_K || c->d > 65536 || c->max_b > 1024 || (int64_t)(c->max_b + 3) / 4 * 16 * c->d > LDS_MOST) return false;
-    const int bytes = small_lds(c->d, c->k, c->max_b, small_waves(c->max_b)).bytes;
-    const int64_t wgs = (c->m + NL - 1) / NL;
-    if (bytes > LDS_MOST || wgs > 65535 || (e && *e && !on) || (!on && getenv("USL_TUNE_BOTH"))) return false;
-    return on || wgs <= (int64_t)c->num_cu * (160 * 1024 / bytes);
+    if (!small_step_fits(c->m, c->d, c->k, c->max_b) || (e && *e && !on) || (!on && getenv("USL_TUNE_BOTH"))) return false;
+    return on || small_step_pays(c->m, c->d, c->k, c->max_b, c->num_cu);
 }
 
 usl_status usl_launch_step_small(usl_ctx* c, const void* x, const int32_t* idx, void* W, float* m1, float* m2, const int64_t* tgt_off,
@@ -390,13 +362,18 @@ usl_status usl_launch_step_small(usl_ctx* c, const void* x, const int32_t* idx, 
     a.scale = scale; a.lr = lr; a.b1 = beta1; a.b2 = beta2; a.eps = eps; a.ic1 = inv_c1; a.ic2 = inv_c2;
     const int waves = small_waves(b);
     const size_t lds = (size_t)small_lds(c->d, c->k, b, waves).bytes;
-#define USL_SMALL(TS, KP, FULL, NT)                                                                                           \
+#define USL_SMALL(TS, KP, FULL, NT, SHARED)                                                                                   \
     do {                                                                                                                      \
         if (lds > 65536)                                                                                                      \
-            USL_HIP(c, hipFuncSetAttribute((const void*)k_step_small<TS, KP, FULL, NT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)); \
-        hipLaunchKernelGGL((k_step_small<TS, KP, FULL, NT>), dim3((unsigned)wgs), dim3(NT), lds, c->stream, a, (TS*)W);       \
+            USL_HIP(c, hipFuncSetAttribute((const void*)k_step_small<TS, KP, FULL, NT, SHARED>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)); \
+        hipLaunchKernelGGL((k_step_small<TS, KP, FULL, NT, SHARED>), dim3((unsigned)wgs), dim3(NT), lds, c->stream, a, (TS*)W); \
     } while (0)
-#define USL_SMALL_W(TS, KP, FULL) do { if (waves == 8) USL_SMALL(TS, KP, FULL, 512); else USL_SMALL(TS, KP, FULL, 256); } while (0)
+#define USL_SMALL_W(TS, KP, FULL)                                                                                             \
+    do {                                                                                                                      \
+        if (waves == 8) USL_SMALL(TS, KP, FULL, 512, false);                                                                  \
+        else if (b <= 8 && c->d > 128) USL_SMALL(TS, KP, FULL, 256, true);   /* see the kernel */                             \
+        else USL_SMALL(TS, KP, FULL, 256, false);                                                                             \
+    } while (0)
 #define USL_SMALL_K(TS)                                                                                                       \
     do {                                                                                                                      \
         if (c->k == 8) USL_SMALL_W(TS, 8, true);                                                                              \

@@ -1,5 +1,5 @@
 """usl_train_step of small layers (k_step_small.hip: the whole step in two launches) against the oracle, where it can go wrong: a
-last workgroup of few labels, fan-ins beside the kernel's own, batches that are no multiple of four, four and eight wavefronts, features
+last workgroup of few labels, fan-ins beside the kernel's own, batches that are no multiple of four, four and eight wavefronts, long rows of few instances, features
 without a connection, targets listed twice or outside the layer, and an order of the connections that is none (new scratch, and idx
 replaced behind the library's back).  The general path runs on the same inputs."""
 import numpy as np
@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 # (m, d, k, b, storage, loss_kind)
 CASES = [(1, 1, 1, 1, "f32", 0), (63, 40, 7, 3, "f32", 1), (64, 8, 8, 4, "bf16", 0), (65, 33, 9, 5, "f32", 0), (130, 16, 16, 33, "bf16", 1),
          (129, 64, 31, 32, "f32", 0), (1024, 64, 8, 16, "f32", 1), (1000, 700, 32, 18, "f32", 0), (640, 32, 32, 100, "bf16", 0),
-         (2111, 1500, 3, 9, "f32", 1), (300, 50, 17, 201, "f32", 0), (4100, 90, 5, 40, "bf16", 1), (20000, 128, 16, 8, "f32", 0)]
+         (2111, 1500, 3, 9, "f32", 1), (300, 50, 17, 201, "f32", 0), (4100, 90, 5, 40, "bf16", 1), (20000, 128, 16, 8, "f32", 0),
+         (300, 700, 8, 3, "f32", 0), (130, 200, 16, 8, "bf16", 1), (200, 1001, 20, 5, "f32", 1), (70, 129, 3, 1, "f32", 0)]   # columns shared by wavefronts
 
 
 @pytest.mark.parametrize("path", ["small", "general"])
