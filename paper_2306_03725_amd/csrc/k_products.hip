@@ -195,12 +195,11 @@ __device__ __forceinline__ float moved(float v) { return __int_as_float(__builti
 // VEC: k is a multiple of 4.
 // AHEAD: rounds in flight, a divisor of `rounds`.  Four where there is one instance (four spill where there are four): with two,
 // and the sums of a label's lanes through LDS, the scores of m = 500k took 0.8 us longer.
-// kk > 0, one instance: the workgroup's kk best labels go to cand[workgroup][kk], best first (0 where there are fewer): each wavefront's
-// from its lanes' scores (read back from where they have just been written, but for the first few), then those of the wavefronts.  m = 500k,
-// 5 labels: the scores gone over by a kernel of their own took 6.2 us and a launch; usl_predict of m = 500k, d = 32k, k = 32 37.5 us, now
-// 34.8; m = 5000, d = 64, k = 8 12.9 and 10.4; m = 1.5M 32.6 and 28.0.  (Several instances one after the other took longer than that
-// kernel: m = 31k, d = 1k, k = 32, b = 4 16.2 and 26.6.)
-template <int LPL, typename TS, int Q, bool VEC, int AHEAD>
+// BEST, one instance: the workgroup's kk best labels go to cand[workgroup][kk], best first (0 where there are fewer): each wavefront's
+// from its lanes' scores (read back from where they have just been written, but for the first few), then those of the wavefronts.  A kernel of its own:
+// it takes 10 more registers, with which a compute unit holds one workgroup of 1024 lanes in the place of two where k is no multiple of 4.  Where it is used:
+// best_from_forward.  (Several instances one after the other took longer than a kernel over the scores: m = 31k, d = 1k, k = 32, b = 4 16.2 and 26.6.)
+template <int LPL, typename TS, int Q, bool VEC, int AHEAD, bool BEST>
 __global__ void __launch_bounds__(1024)
 k_forward_few(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS* __restrict__ W, float* __restrict__ out,
               int64_t m, int k, int b, int row_bytes, int rounds, int kk, uint64_t* __restrict__ cand) {
@@ -285,7 +284,7 @@ k_forward_few(const char* __restrict__ xi, const int32_t* __restrict__ idx, cons
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     constexpr int HELD = 4;   // turns whose scores a lane keeps in registers
-    float kept[Q == 1 ? HELD : 1] = {};
+    float kept[BEST ? HELD : 1] = {};
     int turn = 0;
     for (int64_t wv = w0; wv * per < m; wv += waves, ++turn) {
         const int64_t j0 = wv * per, jn = (wv + waves) * per;
@@ -316,12 +315,12 @@ k_forward_few(const char* __restrict__ xi, const int32_t* __restrict__ idx, cons
             for (int i = 0; i < Q; ++i)
                 if (i < b) out[(size_t)i * m + j] = sum[i];
         }
-        if (Q == 1) {
+        if constexpr (BEST) {
 #pragma unroll
-            for (int q = 0; q < HELD; ++q) kept[Q == 1 ? q : 0] = turn == q ? sum[0] : kept[Q == 1 ? q : 0];
+            for (int q = 0; q < HELD; ++q) kept[q] = turn == q ? sum[0] : kept[q];
         }
     }
-    if (Q > 1 || kk == 0) return;
+    if constexpr (!BEST) return;
     const int64_t step = waves * per, turns = w0 * per < m ? (m - w0 * per + step - 1) / step : 0;
     uint64_t* list = reinterpret_cast<uint64_t*>(lds_raw);
     auto label_of = [&](int64_t at) -> int64_t {   // m: none
@@ -330,7 +329,7 @@ k_forward_few(const char* __restrict__ xi, const int32_t* __restrict__ idx, cons
     };
     uint64_t held[HELD];
 #pragma unroll
-    for (int q = 0; q < HELD; ++q) held[q] = label_of(q) < m ? score_key(kept[Q == 1 ? q : 0], (uint32_t)label_of(q)) : 0ull;
+    for (int q = 0; q < HELD; ++q) held[q] = label_of(q) < m ? score_key(kept[BEST ? q : 0], (uint32_t)label_of(q)) : 0ull;
     __syncthreads();   // the row is no longer read
     uint64_t prev = ~0ull;
     for (int r = 0; r < kk; ++r) {
@@ -730,21 +729,46 @@ usl_status slot_order(usl_ctx* c, const int32_t* idx, const uint8_t** perm) {
     return USL_OK;
 }
 
+// Shape of the streaming kernel: lanes of a label, rounds of a wavefront's turn, wavefronts of a workgroup, workgroups, turns of a wavefront.
+struct FewShape {
+    int lpl, rounds, nw;
+    unsigned grid;
+    int64_t turns;
+    size_t lds;
+};
+FewShape few_shape(const usl_ctx* c, const Layout& L, int kk) {
+    FewShape f;
+    f.lpl = c->k <= 8 ? 2 : c->k <= 16 ? 4 : c->k <= 32 ? 8 : 16;
+    // fewer labels per wavefront, then workgroups of 4 or 8 wavefronts, so that a small layer still reaches every compute unit
+    f.rounds = f.lpl;
+    auto wavefronts = [&]() { const int64_t per = (int64_t)f.rounds * (64 / f.lpl); return (c->m + per - 1) / per; };
+    while (f.rounds > 2 && wavefronts() < (int64_t)c->num_cu * 16) f.rounds >>= 1;
+    const int64_t waves = wavefronts();
+    f.nw = waves >= (int64_t)c->num_cu * 16 ? 16 : waves >= (int64_t)c->num_cu * 8 ? 8 : 4;
+    const int64_t blocks = (waves + f.nw - 1) / f.nw;
+    f.lds = max_sz((size_t)L.row_bytes + 16, (size_t)f.nw * kk * 8);
+    const int by_lds = (int)((size_t)(160 * 1024) / f.lds), resident = by_lds < 32 / f.nw ? (by_lds < 1 ? 1 : by_lds) : 32 / f.nw;
+    f.grid = (unsigned)(blocks < (int64_t)c->num_cu * resident ? blocks : (int64_t)c->num_cu * resident);   // usl_forward_few_blocks at most: fewer than 16 wavefronts only where there are fewer than that of them
+    f.turns = (waves + (int64_t)f.grid * f.nw - 1) / ((int64_t)f.grid * f.nw);
+    return f;
+}
+
+// Prediction of one instance: the best labels from the forward kernel, or from kernels over its scores?  The forward kernel's workgroups look for theirs when
+// all wavefronts are done, 3 us of chains of maxima, and where two of 16 wavefronts share a compute unit their candidates take longer to
+// merge; the other way costs a launch and a pass of 6 us over scores in the cache, and 1 us of forward less.  usl_predict, from forward and with the pass:
+// smaller workgroups: m = 5000, d = 64, k = 8 10.4 us and 12.9; m = 60 867, d = 1344, k = 16 12.3 and 13.3; one of 16 wavefronts to a compute unit: m = 500k, d = 32k, k = 32 34.8
+// and 37.5; two of them: m = 225 711, d = 118, k = 13 22.0 and 18.8; m = 109 071, d = 7213, k = 32 18.4 and 16.4; m = 720 436, d = 2151, k = 13 33.5 and 29.8; three turns: m = 1.34M, d = 11k,
+// k = 3 22.0 and 24.3; m = 1.27M, k = 32 68.2 and 69.5.
+bool best_from_forward(const usl_ctx* c, const FewShape& f) { return f.nw < 16 || f.grid <= (unsigned)c->num_cu || f.turns >= 3; }
+
 // One group of instances: the streaming kernel.  kk > 0: with the *blocks workgroups' best labels beside the scores.
 usl_status run_forward_few(usl_ctx* c, const Layout& L, const void* x, const int32_t* idx, const void* W, float* out, int b, int kk = 0, int* nblocks = nullptr) {
     const void* xi = nullptr;
     USL_TRY(activations(c, L, x, b, &xi));
-    const int lpl = c->k <= 8 ? 2 : c->k <= 16 ? 4 : c->k <= 32 ? 8 : 16;
-    // fewer labels per wavefront, then workgroups of 4 or 8 wavefronts, so that a small layer still reaches every compute unit
-    int rounds = lpl;
-    auto wavefronts = [&]() { const int64_t per = (int64_t)rounds * (64 / lpl); return (c->m + per - 1) / per; };
-    while (rounds > 2 && wavefronts() < (int64_t)c->num_cu * 16) rounds >>= 1;
-    const int64_t waves = wavefronts();
-    const int nw = waves >= (int64_t)c->num_cu * 16 ? 16 : waves >= (int64_t)c->num_cu * 8 ? 8 : 4;
-    const int64_t blocks = (waves + nw - 1) / nw;
-    const size_t lds = max_sz((size_t)L.row_bytes + 16, (size_t)nw * kk * 8);
-    const int by_lds = (int)((size_t)(160 * 1024) / lds), resident = by_lds < 32 / nw ? (by_lds < 1 ? 1 : by_lds) : 32 / nw;
-    const unsigned grid = (unsigned)(blocks < (int64_t)c->num_cu * resident ? blocks : (int64_t)c->num_cu * resident);   // usl_forward_few_blocks at most: fewer than 16 wavefronts only where there are fewer than that of them
+    const FewShape f = few_shape(c, L, kk);
+    const int lpl = f.lpl, rounds = f.rounds, nw = f.nw;
+    const unsigned grid = f.grid;
+    const size_t lds = f.lds;
     const bool vec = c->k % 4 == 0;
     uint64_t* cand = nullptr;
     if (kk > 0) {
@@ -752,12 +776,13 @@ usl_status run_forward_few(usl_ctx* c, const Layout& L, const void* x, const int
         cand = c->topk_cand;
         *nblocks = (int)grid;
     }
-#define USL_FEW_A(LPL, TS, Q, VEC, AHEAD)                                                                           \
+#define USL_FEW_B(LPL, TS, Q, VEC, AHEAD, BEST)                                                                    \
     do {                                                                                                                \
-        USL_TRY(allow_lds(c, k_forward_few<LPL, TS, Q, VEC, AHEAD>, lds));                                          \
-        hipLaunchKernelGGL((k_forward_few<LPL, TS, Q, VEC, AHEAD>), dim3(grid), dim3((unsigned)nw * 64), lds, c->stream,              \
+        USL_TRY(allow_lds(c, k_forward_few<LPL, TS, Q, VEC, AHEAD, BEST>, lds));                                    \
+        hipLaunchKernelGGL((k_forward_few<LPL, TS, Q, VEC, AHEAD, BEST>), dim3(grid), dim3((unsigned)nw * 64), lds, c->stream,        \
                            (const char*)xi, idx, (const TS*)W, out, c->m, c->k, b, L.row_bytes, rounds, kk, cand);      \
     } while (0)
+#define USL_FEW_A(LPL, TS, Q, VEC, AHEAD) do { if (Q == 1 && kk > 0) USL_FEW_B(LPL, TS, Q, VEC, AHEAD, (Q == 1)); else USL_FEW_B(LPL, TS, Q, VEC, AHEAD, false); } while (0)
 #define USL_FEW(LPL, TS, Q, VEC)                                                                                    \
     do {                                                                                                                \
         if (Q == 1 && LPL >= 4 && rounds >= 4) USL_FEW_A(LPL, TS, Q, VEC, (Q == 1 && LPL >= 4 ? 4 : 2));            \
@@ -784,6 +809,7 @@ usl_status run_forward_few(usl_ctx* c, const Layout& L, const void* x, const int
 #undef USL_FEW_V
 #undef USL_FEW
 #undef USL_FEW_A
+#undef USL_FEW_B
     return usl_check_launch(c, "forward (one group)");
 }
 
@@ -858,7 +884,7 @@ usl_status usl_launch_predict_few(usl_ctx* c, const void* x, const int32_t* idx,
     *done = false;
     if (!fast_path_ok(c, idx, W)) return USL_OK;
     const Layout L = layout_of(c, b, x);
-    if (b > 1 || !streams(c, L, b)) return USL_OK;
+    if (b > 1 || !streams(c, L, b) || !best_from_forward(c, few_shape(c, L, kk))) return USL_OK;
     int blocks = 0;
     USL_TRY(run_forward_few(c, L, x, idx, W, out, b, kk, &blocks));
     USL_TRY(usl_launch_topk_merge(c, blocks, out, b, kk, top_lab, top_val));

@@ -141,21 +141,28 @@ def _predict_case(usl, gu, orc, m, d, k, b, kk, storage):
     np.testing.assert_array_equal(gu.host(val).view(np.uint32), ref_val.view(np.uint32))
 
 
-# forward and the selection in one kernel (batches of up to as many instances as an LDS read brings): turns of a wavefront beyond those it keeps in registers (m = 2 million),
-# workgroups of 4 to 16 wavefronts, the last one ragged, fewer labels than kk to a workgroup, every instance count, ties
+# One instance, forward and the selection in one kernel or, for layers in between, in several: turns of a wavefront beyond those it keeps in registers (five: rows of
+# which a compute unit holds one, m = 1.2 million), workgroups of 4 to 16 wavefronts, the last one ragged, fewer labels than kk to a workgroup, ties.  Two to four instances: the
+# streaming forward, then the selection
 @pytest.mark.parametrize("m,d,k,b,kk,storage", [
     (5, 8, 3, 1, 5, "f32"), (33, 8, 2, 4, 32, "f32"), (1000, 100, 8, 2, 7, "bf16"), (70001, 300, 33, 3, 32, "f32"), (300001, 64, 8, 4, 5, "f32"),
-    (2000003, 64, 4, 1, 32, "f32"), (500000, 32768, 32, 1, 5, "f32"), (131072, 20000, 16, 2, 1, "bf16"), (200000, 40000, 5, 1, 32, "bf16")])
+    (2000003, 64, 4, 1, 32, "f32"), (500000, 32768, 32, 1, 5, "f32"), (131072, 20000, 16, 2, 1, "bf16"), (200000, 40000, 5, 1, 32, "bf16"),
+    (1200001, 21000, 4, 1, 9, "f32"), (225711, 118, 13, 1, 5, "f32"), (1050075, 597, 8, 1, 5, "bf16"), (60867, 300, 16, 1, 32, "f32")])
 def test_predict_of_one_group(usl, gu, orc, m, d, k, b, kk, storage):
     print("predict of one group", m, d, k, b, kk, storage, flush=True)
     cfg = wl.custom(m, d, k, b, storage=storage, positives=min(3, m), index=870)
     idx, x = wl.gen_idx(cfg), wl.gen_x(cfg)
     W = wl.store(np.round(wl.as_f32(wl.gen_W(cfg)) * 4) / 4, storage)      # few values: many scores are alike
     x = wl.store(np.round(wl.as_f32(x)), storage)
+    if m == 1200001:   # the best labels in a wavefront's last turn, whose scores it reads back
+        x, W = np.abs(x), wl.as_f32(W)
+        W[m - 5000:m - 4900] = 9.0
     L = usl.Layer(m, d, k, b, storage)
     d_x, d_idx, d_W = gu.dev(x), gu.dev(idx), gu.dev(W)
     out = gu.empty((b, m))
     L.forward(d_x, d_idx, d_W, out, b)
+    if m == 1200001:
+        assert (orc.topk(gu.host(out), kk)[0] >= m - 5000).all()
     ref_lab, ref_val = orc.topk(gu.host(out), kk)
     for n in (kk, max(1, kk // 2)):
         lab, val = gu.empty((b, n), torch.int32).fill_(-1), gu.empty((b, n)).fill_(float("nan"))
