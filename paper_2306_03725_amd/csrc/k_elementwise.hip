@@ -453,8 +453,9 @@ usl_status usl_launch_adam(usl_ctx* c, void* W, const float* grad_W, float* m1, 
     else
         hipLaunchKernelGGL(k_adam<uint16_t>, dim3((unsigned)blocks + lead), dim3(256), 0, c->stream,
                            (uint16_t*)W, grad_W, m1, m2, n, lr, beta1, beta2, eps, inv_c1, inv_c2, sum, lead);
-    if (sum.targets.off) c->tgt_bits_set = false;
-    return usl_check_launch(c, "adam");
+    USL_TRY(usl_check_launch(c, "adam"));
+    if (sum.targets.off) c->tgt_bits_set = false;   // the launch takes them back
+    return USL_OK;
 }
 
 // blocks of the two kernels that pick up a staged gradient: a multiple of 8 (one eighth of them per XCD)
@@ -490,8 +491,9 @@ usl_status usl_launch_adam_staged(usl_ctx* c, void* W, const usl_staged& st, con
     if (c->storage == USL_F32) USL_STAGED_A(float); else USL_STAGED_A(uint16_t);
 #undef USL_STAGED_A
 #undef USL_STAGED
+    USL_TRY(usl_check_launch(c, "adam (staged gradient)"));
     if (sum.targets.off) c->tgt_bits_set = false;
-    return usl_check_launch(c, "adam (staged gradient)");
+    return USL_OK;
 }
 
 // ---- rows of idx / W picked by a list of label ids (label-subset calls) ----------------------

@@ -1,0 +1,59 @@
+"""What the library does around its launches, with a HIP runtime that launches nothing (stand_in_hip.cpp), on the host: a refused launch leaves no marks that
+the next step takes for targets."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+# x, idx, W, m1, m2, tgt_off, tgt_lab, g, grad_W, grad_x, loss: addresses that nobody follows
+HEAD = """
+import ctypes, sys
+hip = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+hip.stand_in_launched.restype = ctypes.c_char_p
+sys.path.insert(0, %r)
+from paper_2306_03725_amd import usl
+P = dict(x=1 << 20, idx=2 << 20, W=3 << 20, m1=4 << 20, m2=5 << 20, off=6 << 20, lab=7 << 20, g=8 << 20, grad_W=9 << 20, grad_x=10 << 20, loss=11 << 20)
+def step(L, b, refuse="", kind=0, **other):
+    p = dict(P, **other)
+    hip.stand_in_start(refuse.encode())
+    status = 0
+    try:
+        L.train_step(p["x"], p["idx"], p["W"], p["m1"], p["m2"], p["off"], p["lab"], kind, 1.0, 1, 1e-3, 0.9, 0.999, 1e-8, p["g"], p["grad_W"], p["grad_x"], p["loss"], b)
+    except usl.UslError as e:
+        status = e.status
+    return status, hip.stand_in_launched().decode().split()
+def at(names, part):
+    return [n for n, name in enumerate(names) if part in name]
+""" % ROOT
+
+
+@pytest.fixture(scope="module")
+def stand_in(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("hip") / "libstandin.so")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include",
+                           os.path.join(ROOT, "tests", "stand_in_hip.cpp"), "-o", so])
+    return so
+
+
+def run(stand_in, text):
+    r = subprocess.run([sys.executable, "-c", HEAD + text, stand_in], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("adam,grad_x", [("k_adam_staged", "P['grad_x']"), ("k_adam", "None")])
+def test_marks_of_a_step_whose_last_launch_is_refused_are_cleared(stand_in, adam, grad_x):
+    run(stand_in, """
+L = usl.Layer(70000, 512, 16, 40)
+s, names = step(L, 40, grad_x={gx})
+assert s == 0 and at(names, "k_forward") and at(names, "{adam}"), names
+assert at(names, "k_fill_zero"), names            # new scratch
+s, names = step(L, 40, grad_x={gx})
+assert s == 0 and not at(names, "k_fill_zero"), names
+s, names = step(L, 40, refuse="{adam}", grad_x={gx})
+assert s == usl.USL_EHIP, s
+s, names = step(L, 40, grad_x={gx})
+assert s == 0 and at(names, "k_fill_zero") and at(names, "k_fill_zero")[0] < at(names, "k_forward")[0], names
+""".format(adam=adam, gx=grad_x))
