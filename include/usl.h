@@ -25,7 +25,8 @@
  * ERRORS: every call returns a usl_status; nothing aborts or throws across this boundary.
  * Preconditions that can be checked on the host (NULL pointers, batch outside [1, max_b],
  * k > d, fraction outside [0,1], t < 1, ...) are checked before anything is launched, and a
- * failed check launches nothing.  Index CONTENTS are the caller's responsibility on the hot
+ * failed check launches nothing.  usl_adam_step and usl_train_step take W, grad_W, m1 and m2 at
+ * multiples of 16 bytes only (USL_EINVAL).  Index CONTENTS are the caller's responsibility on the hot
  * path (usl_validate_indices checks them).  Target label ids must lie in [0, m).
  * usl_last_error returns a context-owned message for the most recent failure.
  *

@@ -391,6 +391,8 @@ extern "C" usl_status usl_train_step(usl_ctx* c, const void* x, const int32_t* i
     if (!(beta1 >= 0.f && beta1 < 1.f) || !(beta2 >= 0.f && beta2 < 1.f))
         USL_FAIL(c, USL_EINVAL, "beta1, beta2 must lie in [0,1)");
     if (!(eps >= 0.f) || !(lr == lr)) USL_FAIL(c, USL_EINVAL, "eps < 0 or lr is NaN");
+    if ((uintptr_t)W % 16 || (uintptr_t)m1 % 16 || (uintptr_t)m2 % 16 || (uintptr_t)grad_W % 16)   // as usl_adam_step
+        USL_FAIL(c, USL_EINVAL, "W, grad_W, m1, m2 must be 16-byte aligned");
     USL_TRY(check_batch(c, b));
     USL_TRY(usl_prepare_device(c));
     if (usl_step_small_applies(c)) {
@@ -412,7 +414,7 @@ extern "C" usl_status usl_train_step(usl_ctx* c, const void* x, const int32_t* i
                          (lists && (b > usl_bwd_input_group_rows() || usl_sparse_expected(c)));
     const bool fused = by_rows && usl_forward_loss_applies(c, x, idx, W, b);
     // where few nonzeros are expected forward marks them in passing, one bit per score, and no pass over g has to look for them
-    const bool marked = fused && lists && grad_x && (uintptr_t)grad_W % 16 == 0 && usl_sparse_expected(c);
+    const bool marked = fused && lists && grad_x && usl_sparse_expected(c);
     if (fused) {
         USL_TRY(usl_launch_forward_loss(c, x, idx, W, g, b, loss_kind, tgt_off, tgt_lab, scale, loss, &sum, marked ? grad_W : nullptr));
     } else {

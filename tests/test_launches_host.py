@@ -1,5 +1,5 @@
 """What the library does around its launches, with a HIP runtime that launches nothing (stand_in_hip.cpp), on the host: a refused launch leaves no marks that
-the next step takes for targets."""
+the next step takes for targets, and arrays that are not aligned are refused before anything is launched."""
 import os
 import subprocess
 import sys
@@ -57,3 +57,16 @@ assert s == usl.USL_EHIP, s
 s, names = step(L, 40, grad_x={gx})
 assert s == 0 and at(names, "k_fill_zero") and at(names, "k_fill_zero")[0] < at(names, "k_forward")[0], names
 """.format(adam=adam, gx=grad_x))
+
+def test_arrays_that_are_not_aligned_are_refused_before_a_launch(stand_in):
+    run(stand_in, """
+for shape in ((1024, 64, 8, 16, "f32"), (1000, 64, 4, 3, "bf16"), (70000, 512, 16, 40, "f32"), (3000, 70000, 8, 5, "f32")):
+    for kind in (0, 1):
+        L = usl.Layer(*shape)
+        for grad_x in (P["grad_x"], None):
+            for name in ("W", "m1", "m2", "grad_W"):
+                s, names = step(L, shape[3], kind=kind, **{"grad_x": grad_x, name: P[name] + 4})
+                assert s == usl.USL_EINVAL and not names, (shape, kind, name, s, names)
+            s, names = step(L, shape[3], kind=kind, grad_x=grad_x)
+            assert s == 0 and names, (shape, kind, s)
+""")
