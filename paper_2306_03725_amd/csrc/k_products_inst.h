@@ -19,36 +19,46 @@ template <int K, typename TS, int Q, bool HALVES>
 ProductKernel pick(ProductKind kind, int shape) {
     constexpr int L = K == 8 ? 4 : labels_per_lane(K, 64), L2 = labels_per_lane(K, 128);
     constexpr bool WIDE_PAIRS = K == 64 && sizeof(TS) == 2 && Q <= 2;   // 64 packed slots take 64 of the 128 registers
-#define USL_KIND(LPT, NT, EVEN)                                                                                \
-    (kind == WEIGHT_GRADIENT  ? (const void*)k_backward_weight<K, LPT, NT, TS, Q, HALVES, EVEN>                 \
-     : kind == FORWARD_MARKS  ? (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, 2, EVEN, false>               \
+#define USL_FORWARD_KIND(LPT, NT, EVEN)                                                                        \
+    (kind == FORWARD_MARKS    ? (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, 2, EVEN, false>               \
      : kind == FORWARD_LOSS   ? (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, 1, EVEN, false>               \
      : kind == FORWARD_CACHED ? (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, 0, EVEN, (K <= 16 || (K == 24 && Q == 4))> \
                               : (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, 0, EVEN, (K <= 16)>)
-#define USL_PICK(LPT, NT)                                                                                      \
-    ProductKernel{USL_KIND(LPT, NT, false), USL_KIND(LPT, NT, true), K, LPT, NT, transpose_bytes<K, NT>()}
+#define USL_FORWARD(LPT, NT) ProductKernel{USL_FORWARD_KIND(LPT, NT, false), USL_FORWARD_KIND(LPT, NT, true), K, LPT, NT, transpose_bytes<K, NT>()}
+#define USL_GRADIENT(LPT, NT)                                                                                  \
+    ProductKernel{(const void*)k_backward_weight<K, LPT, NT, TS, Q, HALVES, false>, (const void*)k_backward_weight<K, LPT, NT, TS, Q, HALVES, true>, \
+                  K, LPT, NT, transpose_bytes<K, NT>()}
+#define USL_PICK(LPT, NT) (gradient ? USL_GRADIENT(LPT, NT) : USL_FORWARD(LPT, NT))
+    const bool gradient = kind == WEIGHT_GRADIENT;
     if constexpr (Q > 1) {
         if (shape == 0) return USL_PICK(1, 256);
         if (shape == 1) return USL_PICK(L, 512);
         if constexpr (K == 64) {
-            if (shape == 2 && kind != WEIGHT_GRADIENT) return USL_PICK(L2, 512);
+            if (shape == 2) return gradient ? USL_GRADIENT(L, 1024) : USL_FORWARD(L2, 512);
+        } else {
+            if (shape == 2) return USL_PICK(L, 1024);
         }
-        if (shape == 2) return USL_PICK(L, 1024);
-        if constexpr ((L > 1 && K >= 16) || WIDE_PAIRS) {
-            if (shape == 3 && (L > 1 || kind != WEIGHT_GRADIENT)) return USL_PICK(1, 1024);
+        if constexpr (L > 1 && K >= 16) {
+            if (shape == 3) return USL_PICK(1, 1024);
+        } else if constexpr (WIDE_PAIRS) {
+            if (shape == 3 && !gradient) return USL_FORWARD(1, 1024);
         }
     } else if constexpr (K < 64) {
         if (shape == 1) return USL_PICK(1, 1024);
-        if (shape == 2 && L > 1) return USL_PICK(L, 1024);
+        if constexpr (L > 1) {
+            if (shape == 2) return USL_PICK(L, 1024);
+        }
     } else {   // 64 slots in 128 registers would spill
         if (shape == 1) return USL_PICK(1, 512);
         if (shape == 2) return USL_PICK(L2, 512);
         if constexpr (WIDE_PAIRS) {
-            if (shape == 3 && kind != WEIGHT_GRADIENT) return USL_PICK(1, 1024);
+            if (shape == 3 && !gradient) return USL_FORWARD(1, 1024);
         }
     }
 #undef USL_PICK
-#undef USL_KIND
+#undef USL_GRADIENT
+#undef USL_FORWARD
+#undef USL_FORWARD_KIND
     return ProductKernel{nullptr, nullptr, 0, 0, 0, 0};
 }
 
