@@ -10,6 +10,12 @@ from helpers import assert_close
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(autouse=True)
+def general_path(monkeypatch):
+    """Small layers among these have a step of their own otherwise (test_gpu_step_small.py), without a loss in the forward kernel and its marks."""
+    monkeypatch.setenv("USL_TUNE_SMALL", "off")
+
+
 @pytest.mark.parametrize("loss_kind", [0, 1])
 @pytest.mark.parametrize("m,d,k,b,storage", [
     (1000, 64, 8, 5, "f32"), (2051, 300, 33, 9, "bf16"), (2050, 10300, 5, 7, "f32"), (2050, 24000, 48, 6, "f32"),

@@ -26,11 +26,13 @@ def same(a, r):
     assert_close(a[fine], r[fine], 1e-5, "finite scores")
 
 
-@pytest.mark.parametrize("m,d,k,b,storage", SHAPES)
-def test_nonfinite_activations_stay_with_their_labels(orc, m, d, k, b, storage):
+# small: layers that have a step of their own (fewer slots than 32 and short rows, or few instances), which the general path takes too
+@pytest.mark.parametrize("m,d,k,b,storage,small", [s + ("off",) for s in SHAPES] + [s + ("on",) for s in SHAPES if s[1] < 1000 and s[2] <= 32])
+def test_nonfinite_activations_stay_with_their_labels(orc, m, d, k, b, storage, small, monkeypatch):
     import gpu_util as gu
     from paper_2306_03725_amd import usl
-    print("nonfinite activations", m, d, k, b, storage, flush=True)
+    monkeypatch.setenv("USL_TUNE_SMALL", small)
+    print("nonfinite activations", m, d, k, b, storage, small, flush=True)
     cfg = wl.custom(m, d, k, b, storage=storage, positives=3, index=840 + SHAPES.index((m, d, k, b, storage)))
     idx, W, x = wl.gen_idx(cfg), wl.gen_W(cfg), wl.as_f32(wl.gen_x(cfg)).copy()
     x[0, 0], x[0, d - 1], x[b - 1, 7] = np.inf, -np.inf, np.nan

@@ -35,12 +35,14 @@ SHAPES = draw_shapes(24) + [
 ]
 
 
-@pytest.mark.parametrize("m,d,k,b,storage", SHAPES)
-def test_random_shape(orc, m, d, k, b, storage):
+# small: layers of few labels and short rows also by the step of their own that they take if left alone (test_gpu_step_small.py)
+@pytest.mark.parametrize("m,d,k,b,storage,small", [s + ("off",) for s in SHAPES] + [s + ("",) for s in SHAPES if s[0] <= 5000 and s[1] <= 1000 and s[2] <= 32])
+def test_random_shape(orc, m, d, k, b, storage, small, monkeypatch):
     import gpu_util as gu
     from paper_2306_03725_amd import usl
+    monkeypatch.setenv("USL_TUNE_SMALL", small)
     cfg = wl.custom(m, d, k, b, storage=storage, positives=min(2, m), index=100 + SHAPES.index((m, d, k, b, storage)))
-    print("shape", m, d, k, b, storage, flush=True)
+    print("shape", m, d, k, b, storage, small, flush=True)
     hp = wl.ADAM
     idx, W, x, g = wl.gen_idx(cfg), wl.gen_W(cfg), wl.gen_x(cfg), wl.gen_g(cfg)
     off, lab = wl.gen_targets(cfg)

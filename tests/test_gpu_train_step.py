@@ -29,6 +29,16 @@ CASES = [
 
 @pytest.mark.parametrize("m,d,k,b,storage,loss_kind,with_gx,easy", CASES)
 def test_train_step(orc, m, d, k, b, storage, loss_kind, with_gx, easy, monkeypatch):
+    _train_step(orc, m, d, k, b, storage, loss_kind, with_gx, easy, monkeypatch)
+
+
+@pytest.mark.parametrize("m,d,k,b,storage,loss_kind,with_gx,easy", [c for c in CASES if c[0] <= 1024])
+def test_train_step_of_small_layers_by_the_general_path(orc, m, d, k, b, storage, loss_kind, with_gx, easy, monkeypatch):
+    monkeypatch.setenv("USL_TUNE_SMALL", "off")
+    _train_step(orc, m, d, k, b, storage, loss_kind, with_gx, easy, monkeypatch)
+
+
+def _train_step(orc, m, d, k, b, storage, loss_kind, with_gx, easy, monkeypatch):
     import gpu_util as gu
     if easy:      # try the lists of nonzero gradients at once (left alone the library waits for two sparse steps in a row)
         monkeypatch.setenv("USL_TUNE_SPARSE", "always")
