@@ -527,7 +527,7 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
     const int groups = (b + L.Q - 1) / L.Q;
     const double reads_per_clk = unit == 16 ? 8.0 : unit == 8 ? 12.0 : 14.0;
     const int cus = c->num_cu;
-    Launch best;
+    Launch best = {};
     best.kern.fn = nullptr;
     double best_t = 0.0;
     // clocks of wgs workgroups with gpb groups and `labels` labels each, `res` workgroups to a compute unit
@@ -554,6 +554,9 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
         return busy + per_cu * load + rounds * (6000.0 + tiles * (tg.nbuf == 2 ? 600.0 : 1500.0) / (together > 1.0 ? together : 1.0));
     };
     auto sums_of = [&](int parts) { return backward && parts > 1 ? 6000.0 + (double)(parts + 1) * c->m * c->k * 4 / 4000.0 : 0.0; };
+    // parts that there is room for: partial weight gradients of 512 MB at most, and no more of them than most_parts
+    const size_t held = backward ? ((size_t)1 << 29) / ((size_t)c->m * c->k * 4) : (size_t)most_parts;
+    const int room = held < 1 || most_parts < 1 ? 1 : held < (size_t)most_parts ? (int)held : most_parts;
     const int shape_force = tune_shape(), split_force = tune_split(), tail_force = backward ? 0 : tune_tail(), labels_force = tune_labels();
     auto shared_by = [&](int64_t same) {
         const int64_t resident = (int64_t)best.resident * (cus / 8 > 0 ? cus / 8 : 1);   // workgroups on an XCD; they go round-robin to the 8
@@ -622,10 +625,9 @@ Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int mo
         const auto time_of = [&](int64_t wgs, int gpb) { return clocks(kern, tg, res, wgs, gpb, (int)per_block); };
         for (int G = 1; G <= groups; G = G < 8 ? G + 1 : G + (G + 3) / 4) {
             if ((split_force > 0 || tail_force > 0) && G > 1) break;
-            const int split = split_force > 0 ? split_force : G, gpb = (groups + split - 1) / split;
+            const int split = split_force > 0 ? (split_force < room ? split_force : room) : G, gpb = (groups + split - 1) / split;
             const int64_t parts = (groups + gpb - 1) / gpb;   // those that have work
-            if (parts > most_parts && parts > 1) break;
-            if (backward && parts > 1 && (size_t)parts * c->m * c->k * 4 > ((size_t)1 << 29)) break;
+            if (parts > room) break;
             if (with_loss && parts > 1 && (size_t)(nblk * parts) > usl_forward_blocks(c) && split_force <= 0) break;
             const int64_t slots = (int64_t)cus * res;
             double t = time_of(nblk * parts, gpb) + sums_of((int)parts);

@@ -1,5 +1,6 @@
 """What the library does around its launches, with a HIP runtime that launches nothing (stand_in_hip.cpp), on the host: a refused launch leaves no marks that
-the next step takes for targets, and arrays that are not aligned are refused before anything is launched."""
+the next step takes for targets, arrays that are not aligned are refused before anything is launched, and a split of the batch asked for by hand that
+there is no room for is a smaller one."""
 import os
 import subprocess
 import sys
@@ -69,4 +70,21 @@ for shape in ((1024, 64, 8, 16, "f32"), (1000, 64, 4, 3, "bf16"), (70000, 512, 1
                 assert s == usl.USL_EINVAL and not names, (shape, kind, name, s, names)
             s, names = step(L, shape[3], kind=kind, grad_x=grad_x)
             assert s == 0 and names, (shape, kind, s)
+""")
+
+
+def test_a_split_asked_for_that_there_is_no_room_for(stand_in):
+    run(stand_in, """
+import os
+for split in ("2", "32", "1000"):
+    os.environ["USL_TUNE_SPLIT"] = split
+    L = usl.Layer(3000000, 16384, 64, 512)    # one part of the weight gradient takes more than the partial sums may
+    hip.stand_in_start(b"")
+    L.backward_weight(P["g"], P["x"], P["idx"], P["grad_W"], 512)
+    names = hip.stand_in_launched().decode().split()
+    assert at(names, "k_backward_weight") and not at(names, "k_sum_parts"), names
+    L = usl.Layer(30000, 1000, 16, 512)
+    hip.stand_in_start(b"")
+    L.backward_weight(P["g"], P["x"], P["idx"], P["grad_W"], 512)
+    assert at(hip.stand_in_launched().decode().split(), "k_sum_parts")
 """)
