@@ -24,9 +24,9 @@ HBM_PEAK_GBPS = 8000.0   # MI355X published peak
 # They are measured offline (a counter run serialises the kernels) and go stale when a kernel changes: the
 # profile files carry the date of truth, these constants only repeat their per-call totals.
 MEASURED_TRAFFIC_BYTES = {
-    "large": {"backward": 3884554649, "backward_input": 2784703283, "forward": 989226598, "backward_weight": 983564288},
-    "large_wide": {"backward": 17481439641, "backward_input": 8376339660, "forward": 3186203033, "backward_weight": 3052299878},
-    "stress": {"backward": 171694568243, "backward_input": 204216152883, "forward": 29409096499, "backward_weight": 26389302476},
+    "large": {"backward": 3896718131, "backward_input": 2784808141, "forward": 988912026, "backward_weight": 983669146},
+    "large_wide": {"backward": 17537853030, "backward_input": 8377807667, "forward": 3563795251, "backward_weight": 3051880448},
+    "stress": {"backward": 171626935091, "backward_input": 204219613184, "forward": 29540273357, "backward_weight": 26389197619},
 }
 KERNELS_OF_CALL = {
     "forward": "k_interleave where one LDS read serves several instances, k_forward",

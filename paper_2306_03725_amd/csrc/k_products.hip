@@ -519,8 +519,9 @@ struct Launch {
 // per clock with every unit at it).  What a workgroup waits for alone: its prologue, a barrier and copy latency per
 // tile, and, with few wavefronts, the latency of a batch of reads (200 clocks).  The weight gradient of a split batch
 // is written and read once more per part.  Of 40 launches over the range of sizes (profiles/rules_measured.txt) the choice
-// is within 10 % of the best shape and split found by hand in 35, the median 2 %; furthest off is the weight
-// gradient of a small layer with a large batch (m = 1024, d = 64, k = 8, b = 512: 25.5 us, with 16 parts 15).
+// is within 10 % of the best shape and split found by hand in 36, the median the best itself; furthest off is the weight
+// gradient of a small layer with a large batch (m = 1024, d = 64, k = 8, b = 512: 25.5 us, with 16 parts 15), then
+// m = 1e6, d = 2000, k = 16, b = 16 (both products 13 %) and a forward product of b = 200 over m = 5000 (17 %).
 Launch choose(const usl_ctx* c, const Layout& L, int b, ProductKind kind, int most_parts = 65535) {
     const bool backward = kind == WEIGHT_GRADIENT, with_loss = kind == FORWARD_LOSS || kind == FORWARD_MARKS;
     const int es = c->storage == USL_F32 ? 4 : 2, unit = L.Q * es;

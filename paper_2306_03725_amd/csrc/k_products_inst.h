@@ -4,9 +4,12 @@
 // the 128 registers a lane of a full compute unit has; twice the slots in 512 lanes of 256 registers was slower
 // everywhere but in the forward product at K = 64).
 // Rows that leave room for one workgroup per compute unit (Q = 1) come in the wide shapes only.
-// bfloat16 with K = 64 in such rows (Q <= 2) also as 1024 lanes with one label each in the forward product: sixteen wavefronts wait for their
-// reads instead of eight (m = 670k, d = 32k, k = 64, b = 512: 512 lanes with two labels 2362 us, this 2310; the step 8006 and 7756).  Not in
-// shorter rows, where smaller workgroups share a compute unit (m = 300k, d = 4k, k = 60, b = 64: 512 lanes with one 121, this 151).
+// bfloat16 with K = 64 in such rows (Q <= 2) also as 1024 lanes with one label each in the forward product: sixteen
+// wavefronts wait for their reads instead of eight.  64 slots of 4 bytes and what the loop needs are more than the 128
+// registers: 53 to 59 are spilled with Q = 2 and 33 to 35 with Q = 1, as many as 512 lanes with two labels spill of 256
+// (47 to 64), and the scratch they are read back from stays in the caches.  m = 670k, d = 32k, k = 64, b = 512: 512 lanes
+// with two labels 2362 us, this 2310; a step of 8 ms gains less than its own runs differ by (1 to 3 %).  Not in shorter
+// rows, where smaller workgroups share a compute unit (m = 300k, d = 4k, k = 60, b = 64: 512 lanes with one 121, this 151).
 #pragma once
 #include "k_products_common.h"
 #include "k_products.h"
@@ -18,7 +21,7 @@ constexpr int labels_per_lane(int K, int slots) { return slots / K < 1 ? 1 : slo
 template <int K, typename TS, int Q, bool HALVES>
 ProductKernel pick(ProductKind kind, int shape) {
     constexpr int L = K == 8 ? 4 : labels_per_lane(K, 64), L2 = labels_per_lane(K, 128);
-    constexpr bool WIDE_PAIRS = K == 64 && sizeof(TS) == 2 && Q <= 2;   // 64 packed slots take 64 of the 128 registers
+    constexpr bool WIDE_PAIRS = K == 64 && sizeof(TS) == 2 && Q <= 2;
 #define USL_FORWARD_KIND(LPT, NT, EVEN)                                                                        \
     (kind == FORWARD_MARKS    ? (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, 2, EVEN, false>               \
      : kind == FORWARD_LOSS   ? (const void*)k_forward<K, LPT, NT, TS, Q, HALVES, 1, EVEN, false>               \
