@@ -3,8 +3,8 @@
 //
 // A (score, label) pair is packed into one 64-bit key whose unsigned order is the ranking: the upper
 // word is the score's bit pattern made monotone (negative values complemented, the sign bit set on the
-// rest; -0 folded onto +0 first), the lower word is ~label, so equal scores rank the smaller label
-// higher and no two keys of a row are equal.  Key 0 never occurs for a real pair and means "nothing".
+// rest; -0 folded onto +0 first), the lower word is ~label (and whether the score is -0, below it), so equal scores rank
+// the smaller label higher and no two keys of a row are equal.  Key 0 never occurs for a real pair and means "nothing".
 #include "k_topk.h"
 
 namespace {
@@ -112,14 +112,12 @@ k_topk_segments(const float* __restrict__ out, int64_t m, int kk, int nseg, uint
     }
 }
 
-// One workgroup per row: the best kk of the row's nseg*kk candidate keys, unpacked.  The score is read
-// back from out so that it keeps its own bits (a -0 stays -0).  A launch of its own: merged by the workgroup
-// that finishes a row's last segment, one row of 500k scores took 14.6 us when the two launches took 7.5 + 5.2 (the
-// candidates then have to be made visible across the L2s by every workgroup).
+// One workgroup per row: the best kk of the row's nseg*kk candidate keys, unpacked.  A launch of its own: merged by the workgroup
+// that finishes a row's last segment, behind fences, one row of 500k scores took 14.6 us when the two launches took 7.5 + 5.2.  (Without fences it
+// pays for one instance: k_forward_few.)
 template <int NT>
 __global__ void __launch_bounds__(NT)
-k_topk_merge(const uint64_t* __restrict__ cand, int n, int kk, const float* __restrict__ out, int64_t m,
-             int32_t* __restrict__ top_lab, float* __restrict__ top_val) {
+k_topk_merge(const uint64_t* __restrict__ cand, int n, int kk, int32_t* __restrict__ top_lab, float* __restrict__ top_val) {
     __shared__ uint64_t red[2][NT / 64];
     BlockMax<NT> block_max = {red, 0};
     const uint64_t* c = cand + (size_t)blockIdx.x * n;
@@ -138,10 +136,9 @@ k_topk_merge(const uint64_t* __restrict__ cand, int n, int kk, const float* __re
             if (key < prev && key > best) best = key;
         }
         prev = block_max(best);
-        if ((int)threadIdx.x == r) {   // a lane per rank: the reads of the scores do not wait for each other
-            const uint32_t label = ~(uint32_t)prev;
-            top_lab[(size_t)blockIdx.x * kk + r] = (int32_t)label;
-            top_val[(size_t)blockIdx.x * kk + r] = out[(int64_t)blockIdx.x * m + label];
+        if ((int)threadIdx.x == r) {
+            top_lab[(size_t)blockIdx.x * kk + r] = key_label(prev);
+            top_val[(size_t)blockIdx.x * kk + r] = key_score(prev);
         }
     }
 }
@@ -169,6 +166,14 @@ int usl_topk_max(void) { return TK_MAX; }
 
 static int topk_segments(const usl_ctx* c, int ept) { return (int)((c->m + TK_NT * ept - 1) / (TK_NT * ept)); }
 
+// The word that counts finished workgroups of k_forward_few; the one that comes last clears it.
+usl_status usl_reserve_topk_done(usl_ctx* c) {
+    if (c->topk_done) return USL_OK;
+    USL_TRY(usl_reserve(c, (void**)&c->topk_done, &c->topk_done_cap, 64));
+    hipLaunchKernelGGL(k_zero_hits, dim3(1), dim3(64), 0, c->stream, (unsigned long long*)c->topk_done, 8);
+    return usl_check_launch(c, "counter of workgroups");
+}
+
 // Sized once for the largest batch and the largest kk, so that no later call has to grow it (growing waits for the stream).
 usl_status usl_reserve_topk(usl_ctx* c) {
     const size_t most = (size_t)topk_segments(c, TK_EPT) * c->max_b, most_few = (size_t)topk_segments(c, TK_EPT_FEW) * (c->num_cu / topk_segments(c, TK_EPT) + 1);
@@ -177,13 +182,13 @@ usl_status usl_reserve_topk(usl_ctx* c) {
     return usl_reserve(c, (void**)&c->topk_cand, &c->topk_cand_cap, (two > by_forward ? two : by_forward) * TK_MAX * 8);
 }
 
-// The best kk of every row of out from nseg sets of kk candidates each (usl_ctx::topk_cand).
-usl_status usl_launch_topk_merge(usl_ctx* c, int nseg, const float* out, int32_t b, int32_t kk, int32_t* top_lab, float* top_val) {
+// The best kk of every row from nseg sets of kk candidates each (usl_ctx::topk_cand).
+usl_status usl_launch_topk_merge(usl_ctx* c, int nseg, int32_t b, int32_t kk, int32_t* top_lab, float* top_val) {
     const int n = nseg * kk;
     if (n <= 8 * TK_NT)   // what 256 lanes hold in registers
-        hipLaunchKernelGGL(k_topk_merge<TK_NT>, dim3((unsigned)b), dim3(TK_NT), 0, c->stream, c->topk_cand, n, (int)kk, out, c->m, top_lab, top_val);
+        hipLaunchKernelGGL(k_topk_merge<TK_NT>, dim3((unsigned)b), dim3(TK_NT), 0, c->stream, c->topk_cand, n, (int)kk, top_lab, top_val);
     else
-        hipLaunchKernelGGL(k_topk_merge<1024>, dim3((unsigned)b), dim3(1024), 0, c->stream, c->topk_cand, n, (int)kk, out, c->m, top_lab, top_val);
+        hipLaunchKernelGGL(k_topk_merge<1024>, dim3((unsigned)b), dim3(1024), 0, c->stream, c->topk_cand, n, (int)kk, top_lab, top_val);
     return usl_check_launch(c, "topk");
 }
 
@@ -201,7 +206,7 @@ usl_status usl_launch_topk(usl_ctx* c, const float* out, int32_t b, int32_t kk, 
     if (few) { if (vec) USL_TOPK(true, TK_EPT_FEW); else USL_TOPK(false, TK_EPT_FEW); }
     else { if (vec) USL_TOPK(true, TK_EPT); else USL_TOPK(false, TK_EPT); }
 #undef USL_TOPK
-    return usl_launch_topk_merge(c, nseg, out, b, kk, top_lab, top_val);
+    return usl_launch_topk_merge(c, nseg, b, kk, top_lab, top_val);
 }
 
 usl_status usl_launch_precision_hits(usl_ctx* c, const int32_t* top_lab, const int64_t* tgt_off,

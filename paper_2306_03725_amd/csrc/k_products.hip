@@ -195,14 +195,19 @@ __device__ __forceinline__ float moved(float v) { return __int_as_float(__builti
 // VEC: k is a multiple of 4.
 // AHEAD: rounds in flight, a divisor of `rounds`.  Four where there is one instance (four spill where there are four): with two,
 // and the sums of a label's lanes through LDS, the scores of m = 500k took 0.8 us longer.
-// BEST, one instance: the workgroup's kk best labels go to cand[workgroup][kk], best first (0 where there are fewer): each wavefront's
-// from its lanes' scores (read back from where they have just been written, but for the first few), then those of the wavefronts.  A kernel of its own:
-// it takes 10 more registers, with which a compute unit holds one workgroup of 1024 lanes in the place of two where k is no multiple of 4.  Where it is used:
+// BEST, one instance: the kk best labels, by keys (k_topk.h).  Each wavefront finds its own from its lanes' scores (the first few in registers, which then go
+// nowhere else; those of more turns read back from out), then the workgroup its own, which go to cand[workgroup][kk] (0 where there are fewer).  With top_lab the workgroup
+// that comes last merges them: candidates and the count of workgroups go by atomics of the device's scope, which pass the L2s, so no
+// fence writes these back (with a launch of its own for the merge usl_predict took 35.5 us at m = 500k, d = 32k, k = 32, now 33.0; m = 5000, d = 64, k = 8 10.6 and
+// 8.6).  A kernel of its own:
+// it takes 10 more registers, with which a compute unit holds one workgroup of 1024 in the place of two where k is no multiple of 4.  Where it is used:
 // best_from_forward.  (Several instances one after the other took longer than a kernel over the scores: m = 31k, d = 1k, k = 32, b = 4 16.2 and 26.6.)
+constexpr int FEW_HELD = 4;   // turns whose scores, or candidates, a lane keeps in registers
 template <int LPL, typename TS, int Q, bool VEC, int AHEAD, bool BEST>
 __global__ void __launch_bounds__(1024)
 k_forward_few(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS* __restrict__ W, float* __restrict__ out,
-              int64_t m, int k, int b, int row_bytes, int rounds, int kk, uint64_t* __restrict__ cand) {
+              int64_t m, int k, int b, int row_bytes, int rounds, int kk, uint64_t* __restrict__ cand, uint32_t* __restrict__ done,
+              int32_t* __restrict__ top_lab, float* __restrict__ top_val) {
     typedef typename Unit<TS, Q>::T U;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const uint32_t lds0 = lds_base(lds_raw);
@@ -283,7 +288,8 @@ k_forward_few(const char* __restrict__ xi, const int32_t* __restrict__ idx, cons
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    constexpr int HELD = 4;   // turns whose scores a lane keeps in registers
+    constexpr int HELD = FEW_HELD;
+    const int64_t step = waves * per, turns = w0 * per < m ? (m - w0 * per + step - 1) / step : 0;
     float kept[BEST ? HELD : 1] = {};
     int turn = 0;
     for (int64_t wv = w0; wv * per < m; wv += waves, ++turn) {
@@ -310,7 +316,7 @@ k_forward_few(const char* __restrict__ xi, const int32_t* __restrict__ idx, cons
             }
         }
         const int64_t j = j0 + sub * (64 / LPL) + lane / LPL;
-        if (sub < rounds && j < m) {
+        if (sub < rounds && j < m && (!BEST || turns > HELD)) {
 #pragma unroll
             for (int i = 0; i < Q; ++i)
                 if (i < b) out[(size_t)i * m + j] = sum[i];
@@ -321,45 +327,77 @@ k_forward_few(const char* __restrict__ xi, const int32_t* __restrict__ idx, cons
         }
     }
     if constexpr (!BEST) return;
-    const int64_t step = waves * per, turns = w0 * per < m ? (m - w0 * per + step - 1) / step : 0;
     uint64_t* list = reinterpret_cast<uint64_t*>(lds_raw);
     auto label_of = [&](int64_t at) -> int64_t {   // m: none
         const int64_t j = w0 * per + at * step + sub * (64 / LPL) + lane / LPL;
         return at < turns && sub < rounds && j < m ? j : m;
     };
+    // the kk largest keys of the workgroup's lanes, the r-th in lane r of wavefront 0; more(prev): a lane's largest below prev beside those held
+    auto largest = [&](const uint64_t (&held)[HELD], auto more) -> uint64_t {
+        __syncthreads();   // LDS is no longer read
+        uint64_t prev = ~0ull, found = 0;
+        for (int r = 0; r < kk; ++r) {
+            uint64_t best = more(prev);
+#pragma unroll
+            for (int q = 0; q < HELD; ++q)
+                if (held[q] < prev && held[q] > best) best = held[q];
+            prev = wave_max(best);
+            if (lane == 0) list[(threadIdx.x >> 6) * kk + r] = prev;
+        }
+        __syncthreads();
+        if (threadIdx.x >= 64) return 0;
+        const int n = nw * kk;   // at most 16 * 32
+        uint64_t mine[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) mine[q] = q * 64 + lane < n ? list[q * 64 + lane] : 0ull;
+        prev = ~0ull;
+        for (int r = 0; r < kk; ++r) {
+            uint64_t best = 0;
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (mine[q] < prev && mine[q] > best) best = mine[q];
+            prev = wave_max(best);
+            if (lane == r) found = prev;
+        }
+        return found;
+    };
     uint64_t held[HELD];
 #pragma unroll
     for (int q = 0; q < HELD; ++q) held[q] = label_of(q) < m ? score_key(kept[BEST ? q : 0], (uint32_t)label_of(q)) : 0ull;
-    __syncthreads();   // the row is no longer read
-    uint64_t prev = ~0ull;
-    for (int r = 0; r < kk; ++r) {
+    const uint64_t own = largest(held, [&](uint64_t prev) {
         uint64_t best = 0;
-#pragma unroll
-        for (int q = 0; q < HELD; ++q)
-            if (held[q] < prev && held[q] > best) best = held[q];
         for (int64_t at = HELD; at < turns; ++at) {
             const int64_t j = label_of(at);
             const uint64_t key = j < m ? score_key(out[j], (uint32_t)j) : 0ull;
             if (key < prev && key > best) best = key;
         }
-        prev = wave_max(best);
-        if (lane == 0) list[(threadIdx.x >> 6) * kk + r] = prev;
+        return best;
+    });
+    uint64_t* to = cand + (size_t)blockIdx.x * kk + lane;
+    if (!top_lab) {
+        if ((int)threadIdx.x < kk) *to = own;
+        return;
+    }
+    uint32_t* last = reinterpret_cast<uint32_t*>(lds_raw) + 16 * 32 * 2;   // behind the lists
+    if (threadIdx.x < 64) {
+        if (lane < kk) __hip_atomic_store(to, own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the candidates are there before the count says so
+        if (lane == 0) *last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1 ? 1u : 0u;
     }
     __syncthreads();
-    if (threadIdx.x >= 64) return;
-    const int n = nw * kk;   // at most 16 * 32
-    uint64_t mine[8];
+    if (!*last) return;
+    const uint32_t n = gridDim.x * (uint32_t)kk;   // HELD to a lane at most
 #pragma unroll
-    for (int q = 0; q < 8; ++q) mine[q] = q * 64 + lane < n ? list[q * 64 + lane] : 0ull;
-    prev = ~0ull;
-    for (int r = 0; r < kk; ++r) {
-        uint64_t best = 0;
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-            if (mine[q] < prev && mine[q] > best) best = mine[q];
-        prev = wave_max(best);
-        if (lane == 0) cand[(size_t)blockIdx.x * kk + r] = prev;
+    for (int q = 0; q < HELD; ++q) {
+        const uint32_t at = (uint32_t)q * blockDim.x + threadIdx.x;
+        held[q] = at < n ? __hip_atomic_load(cand + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
     }
+    const uint64_t top = largest(held, [](uint64_t) -> uint64_t { return 0; });
+    if ((int)threadIdx.x < kk) {
+        top_lab[lane] = key_label(top);
+        top_val[lane] = key_score(top);
+    }
+    if (threadIdx.x == 0) __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // out[i][:] once more, slot by slot, for the instances whose activation 0 is not finite (see pads_with_column_0): nearly
@@ -749,7 +787,7 @@ FewShape few_shape(const usl_ctx* c, const Layout& L, int kk) {
     const int64_t waves = wavefronts();
     f.nw = waves >= (int64_t)c->num_cu * 16 ? 16 : waves >= (int64_t)c->num_cu * 8 ? 8 : 4;
     const int64_t blocks = (waves + f.nw - 1) / f.nw;
-    f.lds = max_sz((size_t)L.row_bytes + 16, (size_t)f.nw * kk * 8);
+    f.lds = max_sz((size_t)L.row_bytes + 16, kk > 0 ? (size_t)16 * 32 * 8 + 16 : 0);
     const int by_lds = (int)((size_t)(160 * 1024) / f.lds), resident = by_lds < 32 / f.nw ? (by_lds < 1 ? 1 : by_lds) : 32 / f.nw;
     f.grid = (unsigned)(blocks < (int64_t)c->num_cu * resident ? blocks : (int64_t)c->num_cu * resident);   // usl_forward_few_blocks at most: fewer than 16 wavefronts only where there are fewer than that of them
     f.turns = (waves + (int64_t)f.grid * f.nw - 1) / ((int64_t)f.grid * f.nw);
@@ -765,7 +803,8 @@ FewShape few_shape(const usl_ctx* c, const Layout& L, int kk) {
 bool best_from_forward(const usl_ctx* c, const FewShape& f) { return f.nw < 16 || f.grid <= (unsigned)c->num_cu || f.turns >= 3; }
 
 // One group of instances: the streaming kernel.  kk > 0: with the *blocks workgroups' best labels beside the scores.
-usl_status run_forward_few(usl_ctx* c, const Layout& L, const void* x, const int32_t* idx, const void* W, float* out, int b, int kk = 0, int* nblocks = nullptr) {
+usl_status run_forward_few(usl_ctx* c, const Layout& L, const void* x, const int32_t* idx, const void* W, float* out, int b, int kk = 0, int32_t* top_lab = nullptr,
+                           float* top_val = nullptr) {
     const void* xi = nullptr;
     USL_TRY(activations(c, L, x, b, &xi));
     const FewShape f = few_shape(c, L, kk);
@@ -774,16 +813,20 @@ usl_status run_forward_few(usl_ctx* c, const Layout& L, const void* x, const int
     const size_t lds = f.lds;
     const bool vec = c->k % 4 == 0;
     uint64_t* cand = nullptr;
+    bool merge = false;   // by the workgroup that comes last
     if (kk > 0) {
         USL_TRY(usl_reserve_topk(c));
         cand = c->topk_cand;
-        *nblocks = (int)grid;
+        // (Two workgroups to a compute unit: their candidates, twice as many, come late; m = 1.34M, d = 11k, k = 3 25.1 us with a launch for the merge, 26.1 without.)
+        merge = grid <= (unsigned)c->num_cu && (int64_t)grid * kk <= (int64_t)FEW_HELD * nw * 64;
+        if (merge) USL_TRY(usl_reserve_topk_done(c));
     }
 #define USL_FEW_B(LPL, TS, Q, VEC, AHEAD, BEST)                                                                    \
     do {                                                                                                                \
         USL_TRY(allow_lds(c, k_forward_few<LPL, TS, Q, VEC, AHEAD, BEST>, lds));                                    \
         hipLaunchKernelGGL((k_forward_few<LPL, TS, Q, VEC, AHEAD, BEST>), dim3(grid), dim3((unsigned)nw * 64), lds, c->stream,        \
-                           (const char*)xi, idx, (const TS*)W, out, c->m, c->k, b, L.row_bytes, rounds, kk, cand);      \
+                           (const char*)xi, idx, (const TS*)W, out, c->m, c->k, b, L.row_bytes, rounds, kk, cand,      \
+                           c->topk_done, merge ? top_lab : nullptr, top_val);                                                          \
     } while (0)
 #define USL_FEW_A(LPL, TS, Q, VEC, AHEAD) do { if (Q == 1 && kk > 0) USL_FEW_B(LPL, TS, Q, VEC, AHEAD, (Q == 1)); else USL_FEW_B(LPL, TS, Q, VEC, AHEAD, false); } while (0)
 #define USL_FEW(LPL, TS, Q, VEC)                                                                                    \
@@ -813,7 +856,8 @@ usl_status run_forward_few(usl_ctx* c, const Layout& L, const void* x, const int
 #undef USL_FEW
 #undef USL_FEW_A
 #undef USL_FEW_B
-    return usl_check_launch(c, "forward (one group)");
+    USL_TRY(usl_check_launch(c, "forward (one group)"));
+    return kk > 0 && !merge ? usl_launch_topk_merge(c, (int)grid, b, kk, top_lab, top_val) : USL_OK;
 }
 
 }  // namespace
@@ -888,9 +932,7 @@ usl_status usl_launch_predict_few(usl_ctx* c, const void* x, const int32_t* idx,
     if (!fast_path_ok(c, idx, W)) return USL_OK;
     const Layout L = layout_of(c, b, x);
     if (b > 1 || !streams(c, L, b) || !best_from_forward(c, few_shape(c, L, kk))) return USL_OK;
-    int blocks = 0;
-    USL_TRY(run_forward_few(c, L, x, idx, W, out, b, kk, &blocks));
-    USL_TRY(usl_launch_topk_merge(c, blocks, out, b, kk, top_lab, top_val));
+    USL_TRY(run_forward_few(c, L, x, idx, W, out, b, kk, top_lab, top_val));
     *done = true;
     return USL_OK;
 }

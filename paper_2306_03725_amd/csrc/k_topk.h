@@ -2,11 +2,19 @@
 #pragma once
 #include "usl_internal.h"
 
+// The upper word ranks scores (-0 as +0), the lower one equal scores by label (below 2^31, so ~label's top bit says nothing); its last bit says
+// that the score is not -0, so that a key holds the score's own bits and no kernel that merges keys waits for the scores themselves.
 __device__ __forceinline__ uint64_t score_key(float z, uint32_t label) {
     uint32_t u = __float_as_uint(z);
-    if (u == 0x80000000u) u = 0u;
+    const uint32_t minus_zero = u == 0x80000000u;
+    if (minus_zero) u = 0u;
     u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-    return ((uint64_t)u << 32) | (uint64_t)(uint32_t)~label;
+    return ((uint64_t)u << 32) | (uint64_t)(uint32_t)(~label << 1 | (minus_zero ^ 1u));
+}
+__device__ __forceinline__ int32_t key_label(uint64_t key) { return (int32_t)~((uint32_t)key >> 1 | 0x80000000u); }
+__device__ __forceinline__ float key_score(uint64_t key) {
+    const uint32_t u = (uint32_t)(key >> 32), bits = (u & 0x80000000u) ? u ^ 0x80000000u : ~u;
+    return __uint_as_float(bits == 0u && !(key & 1u) ? 0x80000000u : bits);
 }
 
 // Largest v of the wavefront, the same register for all lanes: the upper words, then the lower ones of those that have the largest.

@@ -170,3 +170,38 @@ def test_predict_of_one_group(usl, gu, orc, m, d, k, b, kk, storage):
         np.testing.assert_array_equal(gu.host(lab), ref_lab[:, :n])
         np.testing.assert_array_equal(gu.host(val).view(np.uint32), np.ascontiguousarray(ref_val[:, :n]).view(np.uint32))
     L.close()
+
+
+@pytest.mark.parametrize("m,d,k", [(500000, 32768, 32), (4097, 64, 8), (60867, 1344, 16)])
+def test_merge_by_the_workgroup_that_comes_last(usl, gu, orc, m, d, k):
+    """Calls one behind the other with other inputs and other numbers of labels (beyond some the merge is a launch of its own), then the same from a
+    captured graph: the count of finished workgroups is 0 again after every call."""
+    print("merge", m, d, k, flush=True)
+    cfg = wl.custom(m, d, k, 8, positives=1, index=871)
+    x = wl.gen_x(cfg)
+    L = usl.Layer(m, d, k, 8, stream=torch.cuda.current_stream().cuda_stream)
+    d_idx, d_W, d_out = gu.dev(wl.gen_idx(cfg)), gu.dev(wl.gen_W(cfg)), gu.empty((1, m))
+    rows, want, got = [gu.dev(x[i:i + 1]) for i in range(8)], [], []
+    for row in rows:
+        L.forward(row, d_idx, d_W, d_out, 1)
+        want.append(orc.topk(gu.host(d_out), 32))
+    for i in range(24):
+        kk = (5, 32, 1, 16)[i % 4]
+        lab, val = gu.empty((1, kk), torch.int32).fill_(-1), gu.empty((1, kk))
+        L.predict(rows[i % 8], d_idx, d_W, 1, kk, lab, val)
+        got.append((i % 8, kk, lab, val))
+    for i, kk, lab, val in got:
+        np.testing.assert_array_equal(gu.host(lab), want[i][0][:, :kk])
+        np.testing.assert_array_equal(gu.host(val).view(np.uint32), np.ascontiguousarray(want[i][1][:, :kk]).view(np.uint32))
+    stream, row, lab, val = torch.cuda.Stream(), rows[0].clone(), gu.empty((1, 5), torch.int32), gu.empty((1, 5))
+    torch.cuda.synchronize()
+    L.set_stream(stream.cuda_stream)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        L.predict(row, d_idx, d_W, 1, 5, lab, val)
+    for i in (3, 5, 1):
+        row.copy_(rows[i])
+        graph.replay()
+        np.testing.assert_array_equal(gu.host(lab), want[i][0][:, :5])
+        (row + 1).sum().item()
+    L.close()
