@@ -792,7 +792,7 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
         int jl = (int)threadIdx.x + l * NT;   // rebuilt here: kept, every label's offset would be a register across the gathers
         asm volatile("" : "+v"(jl));
         if (jl < nlab) {
-            float sum = 0.f;
+            float sum = 0.f, logs = 0.f;
             // Targets are few: a wavefront without one among these scores takes the short form of the loss (a step at m = 670k, d = 16k, b = 32:
             // 584 us with the general form for all, 571 with both).  A kernel of its own for the targets, which took their scores once more, cost
             // 8 us a step at m = 31k, d = 1k, b = 128 and at m = 200k, d = 8k, b = 64, 13 at m = 500k, b = 256.
@@ -803,11 +803,12 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
                     if (g * Q + q < b) {
                         float o = z[q];
                         if (LOSS) {
-                            const usl_loss_of r = usl_loss_one(LOSS == 2 ? 1 : loss.kind, o, any_target.value && (hits >> q & 1u) ? 1.f : 0.f, loss.scale);
+                            const usl_loss_parts r = usl_loss_in_parts(LOSS == 2 ? 1 : loss.kind, o, any_target.value && (hits >> q & 1u) ? 1.f : 0.f, loss.scale);
                             o = r.g;
-                            sum += r.l;
+                            sum += r.lin;
+                            logs += r.log2;
                         }
-                        float* to = out + ((size_t)(g * Q + q) * m + j0) + (uint32_t)jl;
+                        float* to = reinterpret_cast<float*>(reinterpret_cast<char*>(out + ((size_t)(g * Q + q) * m + j0)) + (uint32_t)jl * 4u);   // (base in scalar registers)
                         if constexpr (past) __builtin_nontemporal_store(o, to); else *to = o;
                         if constexpr (LOSS == 2) {   // lane 0's word and, where the wavefront has more than 32 labels, lane 1's
                             const uint64_t set = __ballot(o != 0.f);
@@ -819,7 +820,7 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
             };
             if (LOSS == 2 || (LOSS && __builtin_expect(__any(hits != 0u), 0))) finish(std::true_type());
             else finish(std::false_type());
-            lost += (double)sum;
+            lost += (double)fmaf(logs, 0.6931471805599453f, sum);
         }
     };
     walk<NT, (Q > 1), HALVES>(xi, lds0, tg, WarmShare(turn.warm_at, turn.warm_share), g0, g1,
