@@ -912,6 +912,236 @@ __device__ __forceinline__ void gather4_four(float (&acc)[4], float& s0, float& 
         : "s"(four), "v"(p0), "v"(p1), "v"(w0), "v"(w1), "v"(w2), "v"(w3), "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3])
         : "memory", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119", "v120", "v121", "v122", "v123", "v124", "v125", "v126", "v127");
 }
+// A group of four and, where n > most, the next one of its list with four reads in flight throughout, in the same registers: each of the second group's is asked
+// for where the one four before it has been used.  (The branch is in here: two statements that change the same registers on either side of one
+// cost copies and reloads.  Steps with groups of four by themselves and so, on one box each: m = 500k, d = 32k, k = 32, b = 256 1959 of 1972 us and 1964 of 2000 before the loss's
+// change; m = 670k, d = 16k, b = 32 551 and 548; m = 200k, d = 8k, b = 64, bfloat16 210.5 and 209.6.)
+__device__ __forceinline__ void gather8(float (&acc)[2], float* s, const uint32_t* p, const float* w, float* s_far, const uint32_t* p_far, const float* w_far,
+                                        const float (&x)[2], int n, int most) {
+    const uint32_t shift = 3;
+    asm volatile(
+        "v_lshlrev_b32_sdwa v112, %10, %11 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
+        "ds_read_b64 v[112:113], v112\n\t"
+        "v_lshlrev_b32_sdwa v114, %10, %11 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
+        "ds_read_b64 v[114:115], v114\n\t"
+        "v_lshlrev_b32_sdwa v116, %10, %12 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
+        "ds_read_b64 v[116:117], v116\n\t"
+        "v_lshlrev_b32_sdwa v118, %10, %12 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
+        "ds_read_b64 v[118:119], v118\n\t"
+        "s_cmp_le_i32 %25, %26\n\t"
+        "s_cbranch_scc1 .Lnear%=\n\t"
+        "s_waitcnt lgkmcnt(3)\n\t"
+        "v_fmac_f32 %0, %15, v112\n\t"
+        "v_fmac_f32 %1, %15, v113\n\t"
+        "v_fmac_f32 %2, %23, v112\n\t"
+        "v_fmac_f32 %2, %24, v113\n\t"
+        "v_lshlrev_b32_sdwa v112, %10, %13 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
+        "ds_read_b64 v[112:113], v112\n\t"
+        "s_waitcnt lgkmcnt(3)\n\t"
+        "v_fmac_f32 %0, %16, v114\n\t"
+        "v_fmac_f32 %1, %16, v115\n\t"
+        "v_fmac_f32 %3, %23, v114\n\t"
+        "v_fmac_f32 %3, %24, v115\n\t"
+        "v_lshlrev_b32_sdwa v114, %10, %13 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
+        "ds_read_b64 v[114:115], v114\n\t"
+        "s_waitcnt lgkmcnt(3)\n\t"
+        "v_fmac_f32 %0, %17, v116\n\t"
+        "v_fmac_f32 %1, %17, v117\n\t"
+        "v_fmac_f32 %4, %23, v116\n\t"
+        "v_fmac_f32 %4, %24, v117\n\t"
+        "v_lshlrev_b32_sdwa v116, %10, %14 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
+        "ds_read_b64 v[116:117], v116\n\t"
+        "s_waitcnt lgkmcnt(3)\n\t"
+        "v_fmac_f32 %0, %18, v118\n\t"
+        "v_fmac_f32 %1, %18, v119\n\t"
+        "v_fmac_f32 %5, %23, v118\n\t"
+        "v_fmac_f32 %5, %24, v119\n\t"
+        "v_lshlrev_b32_sdwa v118, %10, %14 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
+        "ds_read_b64 v[118:119], v118\n\t"
+        "s_waitcnt lgkmcnt(3)\n\t"
+        "v_fmac_f32 %0, %19, v112\n\t"
+        "v_fmac_f32 %1, %19, v113\n\t"
+        "v_fmac_f32 %6, %23, v112\n\t"
+        "v_fmac_f32 %6, %24, v113\n\t"
+        "s_waitcnt lgkmcnt(2)\n\t"
+        "v_fmac_f32 %0, %20, v114\n\t"
+        "v_fmac_f32 %1, %20, v115\n\t"
+        "v_fmac_f32 %7, %23, v114\n\t"
+        "v_fmac_f32 %7, %24, v115\n\t"
+        "s_waitcnt lgkmcnt(1)\n\t"
+        "v_fmac_f32 %0, %21, v116\n\t"
+        "v_fmac_f32 %1, %21, v117\n\t"
+        "v_fmac_f32 %8, %23, v116\n\t"
+        "v_fmac_f32 %8, %24, v117\n\t"
+        "s_waitcnt lgkmcnt(0)\n\t"
+        "v_fmac_f32 %0, %22, v118\n\t"
+        "v_fmac_f32 %1, %22, v119\n\t"
+        "v_fmac_f32 %9, %23, v118\n\t"
+        "v_fmac_f32 %9, %24, v119\n\t"
+        "s_branch .Lend%=\n"
+        ".Lnear%=:\n\t"
+        "s_waitcnt lgkmcnt(3)\n\t"
+        "v_fmac_f32 %0, %15, v112\n\t"
+        "v_fmac_f32 %1, %15, v113\n\t"
+        "v_fmac_f32 %2, %23, v112\n\t"
+        "v_fmac_f32 %2, %24, v113\n\t"
+        "s_waitcnt lgkmcnt(2)\n\t"
+        "v_fmac_f32 %0, %16, v114\n\t"
+        "v_fmac_f32 %1, %16, v115\n\t"
+        "v_fmac_f32 %3, %23, v114\n\t"
+        "v_fmac_f32 %3, %24, v115\n\t"
+        "s_waitcnt lgkmcnt(1)\n\t"
+        "v_fmac_f32 %0, %17, v116\n\t"
+        "v_fmac_f32 %1, %17, v117\n\t"
+        "v_fmac_f32 %4, %23, v116\n\t"
+        "v_fmac_f32 %4, %24, v117\n\t"
+        "s_waitcnt lgkmcnt(0)\n\t"
+        "v_fmac_f32 %0, %18, v118\n\t"
+        "v_fmac_f32 %1, %18, v119\n\t"
+        "v_fmac_f32 %5, %23, v118\n\t"
+        "v_fmac_f32 %5, %24, v119\n"
+        ".Lend%=:"
+        : "+v"(acc[0]), "+v"(acc[1]), "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]), "+v"(s_far[0]), "+v"(s_far[1]), "+v"(s_far[2]), "+v"(s_far[3])
+        : "s"(shift), "v"(p[0]), "v"(p[1]), "v"(p_far[0]), "v"(p_far[1]), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "v"(w_far[0]), "v"(w_far[1]), "v"(w_far[2]), "v"(w_far[3]), "v"(x[0]), "v"(x[1]), "s"(n), "s"(most)
+        : "memory", "scc", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119");
+}
+__device__ __forceinline__ void gather8(float (&acc)[4], float* s, const uint32_t* p, const float* w, float* s_far, const uint32_t* p_far, const float* w_far,
+                                        const float (&x)[4], int n, int most) {
+    const uint32_t shift = 4;
+    asm volatile(
+        "v_lshlrev_b32_sdwa v112, %12, %13 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
+        "ds_read_b128 v[112:115], v112\n\t"
+        "v_lshlrev_b32_sdwa v116, %12, %13 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
+        "ds_read_b128 v[116:119], v116\n\t"
+        "v_lshlrev_b32_sdwa v120, %12, %14 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
+        "ds_read_b128 v[120:123], v120\n\t"
+        "v_lshlrev_b32_sdwa v124, %12, %14 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
+        "ds_read_b128 v[124:127], v124\n\t"
+        "s_cmp_le_i32 %29, %30\n\t"
+        "s_cbranch_scc1 .Lnear%=\n\t"
+        "s_waitcnt lgkmcnt(3)\n\t"
+        "v_fmac_f32 %0, %17, v112\n\t"
+        "v_fmac_f32 %1, %17, v113\n\t"
+        "v_fmac_f32 %2, %17, v114\n\t"
+        "v_fmac_f32 %3, %17, v115\n\t"
+        "v_fmac_f32 %4, %25, v112\n\t"
+        "v_fmac_f32 %4, %26, v113\n\t"
+        "v_fmac_f32 %4, %27, v114\n\t"
+        "v_fmac_f32 %4, %28, v115\n\t"
+        "v_lshlrev_b32_sdwa v112, %12, %15 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
+        "ds_read_b128 v[112:115], v112\n\t"
+        "s_waitcnt lgkmcnt(3)\n\t"
+        "v_fmac_f32 %0, %18, v116\n\t"
+        "v_fmac_f32 %1, %18, v117\n\t"
+        "v_fmac_f32 %2, %18, v118\n\t"
+        "v_fmac_f32 %3, %18, v119\n\t"
+        "v_fmac_f32 %5, %25, v116\n\t"
+        "v_fmac_f32 %5, %26, v117\n\t"
+        "v_fmac_f32 %5, %27, v118\n\t"
+        "v_fmac_f32 %5, %28, v119\n\t"
+        "v_lshlrev_b32_sdwa v116, %12, %15 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
+        "ds_read_b128 v[116:119], v116\n\t"
+        "s_waitcnt lgkmcnt(3)\n\t"
+        "v_fmac_f32 %0, %19, v120\n\t"
+        "v_fmac_f32 %1, %19, v121\n\t"
+        "v_fmac_f32 %2, %19, v122\n\t"
+        "v_fmac_f32 %3, %19, v123\n\t"
+        "v_fmac_f32 %6, %25, v120\n\t"
+        "v_fmac_f32 %6, %26, v121\n\t"
+        "v_fmac_f32 %6, %27, v122\n\t"
+        "v_fmac_f32 %6, %28, v123\n\t"
+        "v_lshlrev_b32_sdwa v120, %12, %16 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
+        "ds_read_b128 v[120:123], v120\n\t"
+        "s_waitcnt lgkmcnt(3)\n\t"
+        "v_fmac_f32 %0, %20, v124\n\t"
+        "v_fmac_f32 %1, %20, v125\n\t"
+        "v_fmac_f32 %2, %20, v126\n\t"
+        "v_fmac_f32 %3, %20, v127\n\t"
+        "v_fmac_f32 %7, %25, v124\n\t"
+        "v_fmac_f32 %7, %26, v125\n\t"
+        "v_fmac_f32 %7, %27, v126\n\t"
+        "v_fmac_f32 %7, %28, v127\n\t"
+        "v_lshlrev_b32_sdwa v124, %12, %16 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
+        "ds_read_b128 v[124:127], v124\n\t"
+        "s_waitcnt lgkmcnt(3)\n\t"
+        "v_fmac_f32 %0, %21, v112\n\t"
+        "v_fmac_f32 %1, %21, v113\n\t"
+        "v_fmac_f32 %2, %21, v114\n\t"
+        "v_fmac_f32 %3, %21, v115\n\t"
+        "v_fmac_f32 %8, %25, v112\n\t"
+        "v_fmac_f32 %8, %26, v113\n\t"
+        "v_fmac_f32 %8, %27, v114\n\t"
+        "v_fmac_f32 %8, %28, v115\n\t"
+        "s_waitcnt lgkmcnt(2)\n\t"
+        "v_fmac_f32 %0, %22, v116\n\t"
+        "v_fmac_f32 %1, %22, v117\n\t"
+        "v_fmac_f32 %2, %22, v118\n\t"
+        "v_fmac_f32 %3, %22, v119\n\t"
+        "v_fmac_f32 %9, %25, v116\n\t"
+        "v_fmac_f32 %9, %26, v117\n\t"
+        "v_fmac_f32 %9, %27, v118\n\t"
+        "v_fmac_f32 %9, %28, v119\n\t"
+        "s_waitcnt lgkmcnt(1)\n\t"
+        "v_fmac_f32 %0, %23, v120\n\t"
+        "v_fmac_f32 %1, %23, v121\n\t"
+        "v_fmac_f32 %2, %23, v122\n\t"
+        "v_fmac_f32 %3, %23, v123\n\t"
+        "v_fmac_f32 %10, %25, v120\n\t"
+        "v_fmac_f32 %10, %26, v121\n\t"
+        "v_fmac_f32 %10, %27, v122\n\t"
+        "v_fmac_f32 %10, %28, v123\n\t"
+        "s_waitcnt lgkmcnt(0)\n\t"
+        "v_fmac_f32 %0, %24, v124\n\t"
+        "v_fmac_f32 %1, %24, v125\n\t"
+        "v_fmac_f32 %2, %24, v126\n\t"
+        "v_fmac_f32 %3, %24, v127\n\t"
+        "v_fmac_f32 %11, %25, v124\n\t"
+        "v_fmac_f32 %11, %26, v125\n\t"
+        "v_fmac_f32 %11, %27, v126\n\t"
+        "v_fmac_f32 %11, %28, v127\n\t"
+        "s_branch .Lend%=\n"
+        ".Lnear%=:\n\t"
+        "s_waitcnt lgkmcnt(3)\n\t"
+        "v_fmac_f32 %0, %17, v112\n\t"
+        "v_fmac_f32 %1, %17, v113\n\t"
+        "v_fmac_f32 %2, %17, v114\n\t"
+        "v_fmac_f32 %3, %17, v115\n\t"
+        "v_fmac_f32 %4, %25, v112\n\t"
+        "v_fmac_f32 %4, %26, v113\n\t"
+        "v_fmac_f32 %4, %27, v114\n\t"
+        "v_fmac_f32 %4, %28, v115\n\t"
+        "s_waitcnt lgkmcnt(2)\n\t"
+        "v_fmac_f32 %0, %18, v116\n\t"
+        "v_fmac_f32 %1, %18, v117\n\t"
+        "v_fmac_f32 %2, %18, v118\n\t"
+        "v_fmac_f32 %3, %18, v119\n\t"
+        "v_fmac_f32 %5, %25, v116\n\t"
+        "v_fmac_f32 %5, %26, v117\n\t"
+        "v_fmac_f32 %5, %27, v118\n\t"
+        "v_fmac_f32 %5, %28, v119\n\t"
+        "s_waitcnt lgkmcnt(1)\n\t"
+        "v_fmac_f32 %0, %19, v120\n\t"
+        "v_fmac_f32 %1, %19, v121\n\t"
+        "v_fmac_f32 %2, %19, v122\n\t"
+        "v_fmac_f32 %3, %19, v123\n\t"
+        "v_fmac_f32 %6, %25, v120\n\t"
+        "v_fmac_f32 %6, %26, v121\n\t"
+        "v_fmac_f32 %6, %27, v122\n\t"
+        "v_fmac_f32 %6, %28, v123\n\t"
+        "s_waitcnt lgkmcnt(0)\n\t"
+        "v_fmac_f32 %0, %20, v124\n\t"
+        "v_fmac_f32 %1, %20, v125\n\t"
+        "v_fmac_f32 %2, %20, v126\n\t"
+        "v_fmac_f32 %3, %20, v127\n\t"
+        "v_fmac_f32 %7, %25, v124\n\t"
+        "v_fmac_f32 %7, %26, v125\n\t"
+        "v_fmac_f32 %7, %27, v126\n\t"
+        "v_fmac_f32 %7, %28, v127\n"
+        ".Lend%=:"
+        : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]), "+v"(s_far[0]), "+v"(s_far[1]), "+v"(s_far[2]), "+v"(s_far[3])
+        : "s"(shift), "v"(p[0]), "v"(p[1]), "v"(p_far[0]), "v"(p_far[1]), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "v"(w_far[0]), "v"(w_far[1]), "v"(w_far[2]), "v"(w_far[3]), "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "s"(n), "s"(most)
+        : "memory", "scc", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119", "v120", "v121", "v122", "v123", "v124", "v125", "v126", "v127");
+}
 template <int Q>
 __device__ __forceinline__ void gather_group(float (&acc)[Q], float& s0, float& s1, float& s2, float& s3, uint32_t p0, uint32_t p1,
                                              float w0, float w1, float w2, float w3, const float (&x)[Q]) {
@@ -1250,11 +1480,16 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
         int ac = acap, bc = bcap;   // compared afresh in every pass, see k_bwi_lds
         asm volatile("" : "+s"(ac), "+s"(bc));
         if constexpr (Q == 4) unit_of(xbuf + (size_t)(feat_of[(OWN ? NT : 0) + tid] & 0xFFFFu) * 4, xa);
+        auto group = [&](int q, float (&acc)[Q], const float (&xv)[Q]) {
+            gather_group<Q>(acc, gw[q * 4], gw[q * 4 + 1], gw[q * 4 + 2], gw[q * 4 + 3], pk[q * 2], pk[q * 2 + 1],
+                            wt[q * 4], wt[q * 4 + 1], wt[q * 4 + 2], wt[q * 4 + 3], xv);
+        };
+        // by twos from the list's own end
 #pragma unroll
-        for (int q = 0; q < KT / 4; ++q) {
-            if (q * 4 < ac)
-                gather_group<Q>(acc_a, gw[q * 4], gw[q * 4 + 1], gw[q * 4 + 2], gw[q * 4 + 3], pk[q * 2], pk[q * 2 + 1],
-                                wt[q * 4], wt[q * 4 + 1], wt[q * 4 + 2], wt[q * 4 + 3], xa);
+        for (int q = 0; q < KT / 4; q += 2) {
+            if (q * 4 >= ac) continue;
+            if (q + 1 < KT / 4) gather8(acc_a, gw + q * 4, pk + q * 2, wt + q * 4, gw + q * 4 + 4, pk + q * 2 + 2, wt + q * 4 + 4, xa, ac, q * 4 + 4);
+            else group(q, acc_a, xa);
         }
         if constexpr (Q == 4) {   // OWN: the first list's sums leave before the second list begins
             tid = threadIdx.x;
@@ -1268,10 +1503,10 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
             unit_of(xbuf + (size_t)(feat_of[(OWN ? NT : 0) + tid] >> 16) * 4, xb);
         }
 #pragma unroll
-        for (int q = 0; q < KT / 4; ++q) {
-            if (q * 4 >= KT - bc)
-                gather_group<Q>(acc_b, gw[q * 4], gw[q * 4 + 1], gw[q * 4 + 2], gw[q * 4 + 3], pk[q * 2], pk[q * 2 + 1],
-                                wt[q * 4], wt[q * 4 + 1], wt[q * 4 + 2], wt[q * 4 + 3], xb);
+        for (int q = KT / 4 - 1; q >= 0; q -= 2) {
+            if (q * 4 < KT - bc) continue;
+            if (q > 0) gather8(acc_b, gw + q * 4, pk + q * 2, wt + q * 4, gw + q * 4 - 4, pk + q * 2 - 2, wt + q * 4 - 4, xb, bc, KT - q * 4 + 3);
+            else group(q, acc_b, xb);
         }
         tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
