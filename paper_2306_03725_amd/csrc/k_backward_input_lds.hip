@@ -859,152 +859,11 @@ __device__ __forceinline__ void gather4_two(float& acc0, float& acc1, float& s0,
         : "memory", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119");
 }
 
-// The same for four instances: 16-byte reads, eight multiply-adds per slot.
-__device__ __forceinline__ void gather4_four(float (&acc)[4], float& s0, float& s1, float& s2, float& s3, uint32_t p0, uint32_t p1,
-                                             float w0, float w1, float w2, float w3, const float (&x)[4]) {
-    const uint32_t four = 4;
-    asm volatile(
-        "v_lshlrev_b32_sdwa v112, %8, %9 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
-        "v_lshlrev_b32_sdwa v116, %8, %9 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
-        "v_lshlrev_b32_sdwa v120, %8, %10 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
-        "v_lshlrev_b32_sdwa v124, %8, %10 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
-        "ds_read_b128 v[112:115], v112\n\t"
-        "ds_read_b128 v[116:119], v116\n\t"
-        "ds_read_b128 v[120:123], v120\n\t"
-        "ds_read_b128 v[124:127], v124\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %0, %11, v112\n\t"
-        "v_fmac_f32 %1, %11, v113\n\t"
-        "v_fmac_f32 %2, %11, v114\n\t"
-        "v_fmac_f32 %3, %11, v115\n\t"
-        "v_fmac_f32 %4, %15, v112\n\t"
-        "v_fmac_f32 %4, %16, v113\n\t"
-        "v_fmac_f32 %4, %17, v114\n\t"
-        "v_fmac_f32 %4, %18, v115\n\t"
-        "s_waitcnt lgkmcnt(2)\n\t"
-        "v_fmac_f32 %0, %12, v116\n\t"
-        "v_fmac_f32 %1, %12, v117\n\t"
-        "v_fmac_f32 %2, %12, v118\n\t"
-        "v_fmac_f32 %3, %12, v119\n\t"
-        "v_fmac_f32 %5, %15, v116\n\t"
-        "v_fmac_f32 %5, %16, v117\n\t"
-        "v_fmac_f32 %5, %17, v118\n\t"
-        "v_fmac_f32 %5, %18, v119\n\t"
-        "s_waitcnt lgkmcnt(1)\n\t"
-        "v_fmac_f32 %0, %13, v120\n\t"
-        "v_fmac_f32 %1, %13, v121\n\t"
-        "v_fmac_f32 %2, %13, v122\n\t"
-        "v_fmac_f32 %3, %13, v123\n\t"
-        "v_fmac_f32 %6, %15, v120\n\t"
-        "v_fmac_f32 %6, %16, v121\n\t"
-        "v_fmac_f32 %6, %17, v122\n\t"
-        "v_fmac_f32 %6, %18, v123\n\t"
-        "s_waitcnt lgkmcnt(0)\n\t"
-        "v_fmac_f32 %0, %14, v124\n\t"
-        "v_fmac_f32 %1, %14, v125\n\t"
-        "v_fmac_f32 %2, %14, v126\n\t"
-        "v_fmac_f32 %3, %14, v127\n\t"
-        "v_fmac_f32 %7, %15, v124\n\t"
-        "v_fmac_f32 %7, %16, v125\n\t"
-        "v_fmac_f32 %7, %17, v126\n\t"
-        "v_fmac_f32 %7, %18, v127"
-        : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(s0), "+v"(s1), "+v"(s2), "+v"(s3)
-        : "s"(four), "v"(p0), "v"(p1), "v"(w0), "v"(w1), "v"(w2), "v"(w3), "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3])
-        : "memory", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119", "v120", "v121", "v122", "v123", "v124", "v125", "v126", "v127");
-}
-// A group of four and, where n > most, the next one of its list with four reads in flight throughout, in the same registers: each of the second group's is asked
-// for where the one four before it has been used.  (The branch is in here: two statements that change the same registers on either side of one
-// cost copies and reloads.  Steps with groups of four by themselves and so, on one box each: m = 500k, d = 32k, k = 32, b = 256 1959 of 1972 us and 1964 of 2000 before the loss's
-// change; m = 670k, d = 16k, b = 32 551 and 548; m = 200k, d = 8k, b = 64, bfloat16 210.5 and 209.6.)
-__device__ __forceinline__ void gather8(float (&acc)[2], float* s, const uint32_t* p, const float* w, float* s_far, const uint32_t* p_far, const float* w_far,
-                                        const float (&x)[2], int n, int most) {
-    const uint32_t shift = 3;
-    asm volatile(
-        "v_lshlrev_b32_sdwa v112, %10, %11 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
-        "ds_read_b64 v[112:113], v112\n\t"
-        "v_lshlrev_b32_sdwa v114, %10, %11 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
-        "ds_read_b64 v[114:115], v114\n\t"
-        "v_lshlrev_b32_sdwa v116, %10, %12 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
-        "ds_read_b64 v[116:117], v116\n\t"
-        "v_lshlrev_b32_sdwa v118, %10, %12 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
-        "ds_read_b64 v[118:119], v118\n\t"
-        "s_cmp_le_i32 %25, %26\n\t"
-        "s_cbranch_scc1 .Lnear%=\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %0, %15, v112\n\t"
-        "v_fmac_f32 %1, %15, v113\n\t"
-        "v_fmac_f32 %2, %23, v112\n\t"
-        "v_fmac_f32 %2, %24, v113\n\t"
-        "v_lshlrev_b32_sdwa v112, %10, %13 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
-        "ds_read_b64 v[112:113], v112\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %0, %16, v114\n\t"
-        "v_fmac_f32 %1, %16, v115\n\t"
-        "v_fmac_f32 %3, %23, v114\n\t"
-        "v_fmac_f32 %3, %24, v115\n\t"
-        "v_lshlrev_b32_sdwa v114, %10, %13 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
-        "ds_read_b64 v[114:115], v114\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %0, %17, v116\n\t"
-        "v_fmac_f32 %1, %17, v117\n\t"
-        "v_fmac_f32 %4, %23, v116\n\t"
-        "v_fmac_f32 %4, %24, v117\n\t"
-        "v_lshlrev_b32_sdwa v116, %10, %14 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
-        "ds_read_b64 v[116:117], v116\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %0, %18, v118\n\t"
-        "v_fmac_f32 %1, %18, v119\n\t"
-        "v_fmac_f32 %5, %23, v118\n\t"
-        "v_fmac_f32 %5, %24, v119\n\t"
-        "v_lshlrev_b32_sdwa v118, %10, %14 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
-        "ds_read_b64 v[118:119], v118\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %0, %19, v112\n\t"
-        "v_fmac_f32 %1, %19, v113\n\t"
-        "v_fmac_f32 %6, %23, v112\n\t"
-        "v_fmac_f32 %6, %24, v113\n\t"
-        "s_waitcnt lgkmcnt(2)\n\t"
-        "v_fmac_f32 %0, %20, v114\n\t"
-        "v_fmac_f32 %1, %20, v115\n\t"
-        "v_fmac_f32 %7, %23, v114\n\t"
-        "v_fmac_f32 %7, %24, v115\n\t"
-        "s_waitcnt lgkmcnt(1)\n\t"
-        "v_fmac_f32 %0, %21, v116\n\t"
-        "v_fmac_f32 %1, %21, v117\n\t"
-        "v_fmac_f32 %8, %23, v116\n\t"
-        "v_fmac_f32 %8, %24, v117\n\t"
-        "s_waitcnt lgkmcnt(0)\n\t"
-        "v_fmac_f32 %0, %22, v118\n\t"
-        "v_fmac_f32 %1, %22, v119\n\t"
-        "v_fmac_f32 %9, %23, v118\n\t"
-        "v_fmac_f32 %9, %24, v119\n\t"
-        "s_branch .Lend%=\n"
-        ".Lnear%=:\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %0, %15, v112\n\t"
-        "v_fmac_f32 %1, %15, v113\n\t"
-        "v_fmac_f32 %2, %23, v112\n\t"
-        "v_fmac_f32 %2, %24, v113\n\t"
-        "s_waitcnt lgkmcnt(2)\n\t"
-        "v_fmac_f32 %0, %16, v114\n\t"
-        "v_fmac_f32 %1, %16, v115\n\t"
-        "v_fmac_f32 %3, %23, v114\n\t"
-        "v_fmac_f32 %3, %24, v115\n\t"
-        "s_waitcnt lgkmcnt(1)\n\t"
-        "v_fmac_f32 %0, %17, v116\n\t"
-        "v_fmac_f32 %1, %17, v117\n\t"
-        "v_fmac_f32 %4, %23, v116\n\t"
-        "v_fmac_f32 %4, %24, v117\n\t"
-        "s_waitcnt lgkmcnt(0)\n\t"
-        "v_fmac_f32 %0, %18, v118\n\t"
-        "v_fmac_f32 %1, %18, v119\n\t"
-        "v_fmac_f32 %5, %23, v118\n\t"
-        "v_fmac_f32 %5, %24, v119\n"
-        ".Lend%=:"
-        : "+v"(acc[0]), "+v"(acc[1]), "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]), "+v"(s_far[0]), "+v"(s_far[1]), "+v"(s_far[2]), "+v"(s_far[3])
-        : "s"(shift), "v"(p[0]), "v"(p[1]), "v"(p_far[0]), "v"(p_far[1]), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "v"(w_far[0]), "v"(w_far[1]), "v"(w_far[2]), "v"(w_far[3]), "v"(x[0]), "v"(x[1]), "s"(n), "s"(most)
-        : "memory", "scc", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119");
-}
+// The same for four instances, 16-byte reads and eight multiply-adds per slot: a group of four and, where n > most, the next one of its list, with four reads in flight throughout, in the same registers: each of the second group's
+// is asked for where the one four before it has been used.  (The branch is in here: two statements that change the same registers on either side
+// of one cost copies and reloads.)  Steps with groups of four by themselves and so: m = 70k, d = 10k, k = 48, b = 100 187.2 and 185.4 us; m = 31k, d = 1k, k = 32, b = 400
+// 151.2 and 150.0; m = 200k, d = 8k, b = 128, bfloat16 352.7 and 349.0; m = 670k, d = 16k, b = 32 543.9 and 542.1.  Not with two instances: 500k x 32k, b = 256 1940 both, and
+// its code, which every launch has to bring in, costs small batches up to 1 us (58k x 6k, k = 8, b = 8 47.4 and 48.4; 150k x 30k, b = 64 298.8 and 299.9).
 __device__ __forceinline__ void gather8(float (&acc)[4], float* s, const uint32_t* p, const float* w, float* s_far, const uint32_t* p_far, const float* w_far,
                                         const float (&x)[4], int n, int most) {
     const uint32_t shift = 4;
@@ -1142,12 +1001,6 @@ __device__ __forceinline__ void gather8(float (&acc)[4], float* s, const uint32_
         : "s"(shift), "v"(p[0]), "v"(p[1]), "v"(p_far[0]), "v"(p_far[1]), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "v"(w_far[0]), "v"(w_far[1]), "v"(w_far[2]), "v"(w_far[3]), "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "s"(n), "s"(most)
         : "memory", "scc", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119", "v120", "v121", "v122", "v123", "v124", "v125", "v126", "v127");
 }
-template <int Q>
-__device__ __forceinline__ void gather_group(float (&acc)[Q], float& s0, float& s1, float& s2, float& s3, uint32_t p0, uint32_t p1,
-                                             float w0, float w1, float w2, float w3, const float (&x)[Q]) {
-    if constexpr (Q == 2) gather4_two(acc[0], acc[1], s0, s1, s2, s3, p0, p1, w0, w1, w2, w3, x[0], x[1]);
-    else gather4_four(acc, s0, s1, s2, s3, p0, p1, w0, w1, w2, w3, x);
-}
 // The values of Q instances at one place of LDS.
 __device__ __forceinline__ void unit_of(const float* p, float (&v)[2]) { const float2 t = *reinterpret_cast<const float2*>(p); v[0] = t.x; v[1] = t.y; }
 __device__ __forceinline__ void unit_of(const float* p, float (&v)[4]) { const float4 t = *reinterpret_cast<const float4*>(p); v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w; }
@@ -1176,6 +1029,7 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
            float* __restrict__ stage, float* __restrict__ ovgw, int chains, int parts, int rows_per_part, size_t part_stride, size_t ov_stride,
            const uint32_t* __restrict__ gate, int accumulate, const uint32_t* __restrict__ stale) {
     constexpr int KT = Q == 4 ? KT_BOTH4 : KT_BOTH;   // (with four instances 36 slots spill)
+    static_assert(KT_BOTH4 % 8 == 0, "groups by twos");
     constexpr uint32_t ZL = BothLayout<Q, OWN>::zero_label, U = 4 * Q;   // U: bytes of a unit
     extern __shared__ __align__(16) unsigned char lds_raw[];
     if (gate && *gate == 0) return;   // the kernels over the nonzero gradients do this call's work
@@ -1251,6 +1105,16 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
         if (ov_n) ov_raw = W_window[o.slot != PAD_SLOT ? o.slot - first_slot : 0u];
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (sizeof(TS) == 4) {
+            // All slots are waited for here, in one go.  Left to the compiler, each is waited for where its weight is asked for, and where the spills
+            // of this kernel came out so that it does not know the order in which those loads return, every wait is for the weights asked for before
+            // as well: a chain of trips to memory, 5 us of every launch at m = 31k, d = 1k, k = 32, b = 128.  (With two instances the weights of the first slots are
+            // better on their way before the last slots have come: m = 20k, d = 30k, k = 16, b = 64 71.8 and, waited for in one go, 72.6; m = 150k, d = 30k, k = 32, b = 32
+            // 197.5 and 199.2, though m = 500k, d = 32k, b = 256 1951 and 1944.)
+            if constexpr (Q == 4) {
+#pragma unroll
+                for (int u = 0; u < N; ++u) asm volatile("" : "+v"(sl[u]));
+                __builtin_amdgcn_sched_barrier(0);
+            }
 #pragma unroll
             for (int u = 0; u < N; ++u)
                 if (fetches(u))   // (whole wavefronts: at most 63 places behind the last one are written too)
@@ -1480,16 +1344,13 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
         int ac = acap, bc = bcap;   // compared afresh in every pass, see k_bwi_lds
         asm volatile("" : "+s"(ac), "+s"(bc));
         if constexpr (Q == 4) unit_of(xbuf + (size_t)(feat_of[(OWN ? NT : 0) + tid] & 0xFFFFu) * 4, xa);
-        auto group = [&](int q, float (&acc)[Q], const float (&xv)[Q]) {
-            gather_group<Q>(acc, gw[q * 4], gw[q * 4 + 1], gw[q * 4 + 2], gw[q * 4 + 3], pk[q * 2], pk[q * 2 + 1],
-                            wt[q * 4], wt[q * 4 + 1], wt[q * 4 + 2], wt[q * 4 + 3], xv);
-        };
-        // by twos from the list's own end
+        constexpr bool TWOS = Q == 4;   // groups by twos, from the list's own end
 #pragma unroll
-        for (int q = 0; q < KT / 4; q += 2) {
+        for (int q = 0; q < KT / 4; q += TWOS ? 2 : 1) {
             if (q * 4 >= ac) continue;
-            if (q + 1 < KT / 4) gather8(acc_a, gw + q * 4, pk + q * 2, wt + q * 4, gw + q * 4 + 4, pk + q * 2 + 2, wt + q * 4 + 4, xa, ac, q * 4 + 4);
-            else group(q, acc_a, xa);
+            if constexpr (TWOS) gather8(acc_a, gw + q * 4, pk + q * 2, wt + q * 4, gw + q * 4 + 4, pk + q * 2 + 2, wt + q * 4 + 4, xa, ac, q * 4 + 4);
+            else gather4_two(acc_a[0], acc_a[1], gw[q * 4], gw[q * 4 + 1], gw[q * 4 + 2], gw[q * 4 + 3], pk[q * 2], pk[q * 2 + 1],
+                             wt[q * 4], wt[q * 4 + 1], wt[q * 4 + 2], wt[q * 4 + 3], xa[0], xa[1]);
         }
         if constexpr (Q == 4) {   // OWN: the first list's sums leave before the second list begins
             tid = threadIdx.x;
@@ -1503,10 +1364,11 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
             unit_of(xbuf + (size_t)(feat_of[(OWN ? NT : 0) + tid] >> 16) * 4, xb);
         }
 #pragma unroll
-        for (int q = KT / 4 - 1; q >= 0; q -= 2) {
+        for (int q = KT / 4 - 1; q >= 0; q -= TWOS ? 2 : 1) {
             if (q * 4 < KT - bc) continue;
-            if (q > 0) gather8(acc_b, gw + q * 4, pk + q * 2, wt + q * 4, gw + q * 4 - 4, pk + q * 2 - 2, wt + q * 4 - 4, xb, bc, KT - q * 4 + 3);
-            else group(q, acc_b, xb);
+            if constexpr (TWOS) gather8(acc_b, gw + q * 4, pk + q * 2, wt + q * 4, gw + q * 4 - 4, pk + q * 2 - 2, wt + q * 4 - 4, xb, bc, KT - q * 4 + 3);
+            else gather4_two(acc_b[0], acc_b[1], gw[q * 4], gw[q * 4 + 1], gw[q * 4 + 2], gw[q * 4 + 3], pk[q * 2], pk[q * 2 + 1],
+                             wt[q * 4], wt[q * 4 + 1], wt[q * 4 + 2], wt[q * 4 + 3], xb[0], xb[1]);
         }
         tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
