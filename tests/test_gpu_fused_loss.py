@@ -127,3 +127,32 @@ def test_a_context_for_far_larger_batches(orc):
     assert_close(gu.host(gW), orc.backward_weight(ref_g, x, idx), 1e-5, "grad_W")
     assert_close(gu.host(gx), orc.backward_input(ref_g, idx, W, d), 1e-4, "grad_x")
     L.close()
+
+
+@pytest.mark.parametrize("m,d,k,b,storage", [(3001, 300, 32, 21, "f32"), (2049, 9000, 8, 18, "bf16"), (2050, 24000, 48, 19, "f32"), (1500, 50000, 33, 17, "f32")])
+@pytest.mark.parametrize("factor", [0.0, 0.01, 1.0, 12.0, 60.0])
+def test_loss_of_small_and_large_scores(m, d, k, b, storage, factor):
+    """The loss inside forward against float64 of the same scores.  A score's terms carry two roundings of the hardware's exponential and logarithm (an
+    ulp each) and those of up to four scores' sums, at most 8 * 2^-24 of the terms' magnitude together; everything else is float64: 1e-6."""
+    import gpu_util as gu
+    import torch
+    from paper_2306_03725_amd import usl
+    print("loss of scores", m, d, k, b, storage, factor, flush=True)
+    cfg = wl.custom(m, d, k, b, storage=storage, positives=3, index=821)
+    idx, x = wl.gen_idx(cfg), wl.gen_x(cfg)
+    W = wl.store(wl.as_f32(wl.gen_W(cfg)) * np.float32(factor), storage)
+    off = np.arange(b + 1, dtype=np.int64) * 3
+    lab = np.stack([np.random.default_rng(i).choice(m, 3, replace=False) for i in range(b)]).astype(np.int32).reshape(-1)
+    d_x, d_idx, d_W, d_off, d_lab = gu.dev(x), gu.dev(idx), gu.dev(W), gu.dev(off), gu.dev(lab)
+    L = usl.Layer(m, d, k, b, storage)
+    z = gu.empty((b, m))
+    L.forward(d_x, d_idx, d_W, z, b)
+    z64, y = gu.host(z).astype(np.float64), np.zeros((b, m))
+    y[np.repeat(np.arange(b), 3), lab] = 1.0
+    terms = np.maximum(z64, 0.0) - z64 * y + np.log1p(np.exp(-np.abs(z64)))
+    g, gW, gx, loss, m1, m2 = gu.empty((b, m)), gu.empty((m, k)), gu.empty((b, d)), gu.empty((1,)), gu.empty((m, k)).zero_(), gu.empty((m, k)).zero_()
+    L.train_step(d_x, d_idx, d_W, m1, m2, d_off, d_lab, 0, 1.0 / b, 1, 1e-3, 0.9, 0.999, 1e-8, g, gW, gx, loss, b)
+    torch.cuda.synchronize()
+    magnitude = (np.maximum(z64, 0.0) + np.abs(z64) * y + np.log1p(np.exp(-np.abs(z64)))).sum() / b
+    assert abs(float(gu.host(loss)[0]) - terms.sum() / b) <= 1e-6 * magnitude
+    L.close()
