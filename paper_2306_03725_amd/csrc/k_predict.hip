@@ -166,20 +166,29 @@ int usl_topk_max(void) { return TK_MAX; }
 
 static int topk_segments(const usl_ctx* c, int ept) { return (int)((c->m + TK_NT * ept - 1) / (TK_NT * ept)); }
 
-// The word that counts finished workgroups of k_forward_few; the one that comes last clears it.
-usl_status usl_reserve_topk_done(usl_ctx* c) {
-    if (c->topk_done) return USL_OK;
-    USL_TRY(usl_reserve(c, (void**)&c->topk_done, &c->topk_done_cap, 64));
-    hipLaunchKernelGGL(k_zero_hits, dim3(1), dim3(64), 0, c->stream, (unsigned long long*)c->topk_done, 8);
-    return usl_check_launch(c, "counter of workgroups");
-}
-
-// Sized once for the largest batch and the largest kk, so that no later call has to grow it (growing waits for the stream).
+// Sized once for the largest batch and the largest kk, so that no later call has to grow it (growing waits for the stream).  Behind the candidates lies
+// the word that counts finished workgroups of k_forward_few, in the same allocation and cleared by the same first call, whatever its batch and kk: a later
+// call finds both.  A capture only records the clearing, and a plain call may come before the first replay: a context whose first calls are
+// captured has no such word until a plain call (topk_done_clear), and its merges are launches of their own.
 usl_status usl_reserve_topk(usl_ctx* c) {
     const size_t most = (size_t)topk_segments(c, TK_EPT) * c->max_b, most_few = (size_t)topk_segments(c, TK_EPT_FEW) * (c->num_cu / topk_segments(c, TK_EPT) + 1);
     const size_t by_forward = (size_t)usl_forward_few_blocks(c);
     const size_t two = most > most_few ? most : most_few;
-    return usl_reserve(c, (void**)&c->topk_cand, &c->topk_cand_cap, (two > by_forward ? two : by_forward) * TK_MAX * 8);
+    const size_t bytes = (two > by_forward ? two : by_forward) * TK_MAX * 8, had = c->topk_cand_cap;
+    USL_TRY(usl_reserve(c, (void**)&c->topk_cand, &c->topk_cand_cap, bytes + 64));
+    if (had != c->topk_cand_cap) c->topk_done_clear = false;
+    c->topk_done = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(c->topk_cand) + bytes);
+    if (c->topk_done_clear) return USL_OK;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess) {   // (the null stream beside a capture elsewhere)
+        (void)hipGetLastError();
+        return USL_OK;
+    }
+    if (capture != hipStreamCaptureStatusNone) return USL_OK;
+    hipLaunchKernelGGL(k_zero_hits, dim3(1), dim3(64), 0, c->stream, (unsigned long long*)c->topk_done, 8);
+    USL_TRY(usl_check_launch(c, "counter of workgroups"));
+    c->topk_done_clear = true;   // behind a launch that was taken
+    return USL_OK;
 }
 
 // The best kk of every row from nseg sets of kk candidates each (usl_ctx::topk_cand).

@@ -818,8 +818,7 @@ usl_status run_forward_few(usl_ctx* c, const Layout& L, const void* x, const int
         USL_TRY(usl_reserve_topk(c));
         cand = c->topk_cand;
         // (Two workgroups to a compute unit: their candidates, twice as many, come late; m = 1.34M, d = 11k, k = 3 25.1 us with a launch for the merge, 26.1 without.)
-        merge = grid <= (unsigned)c->num_cu && (int64_t)grid * kk <= (int64_t)FEW_HELD * nw * 64;
-        if (merge) USL_TRY(usl_reserve_topk_done(c));
+        merge = c->topk_done_clear && grid <= (unsigned)c->num_cu && (int64_t)grid * kk <= (int64_t)FEW_HELD * nw * 64;
     }
 #define USL_FEW_B(LPL, TS, Q, VEC, AHEAD, BEST)                                                                    \
     do {                                                                                                                \

@@ -32,7 +32,7 @@ extern "C" usl_status usl_destroy(usl_ctx* c) {
     if (c->device >= 0) {
         void* bufs[] = {c->bce_partials, c->sel_hist, c->prune_flags, c->tie_counts, c->counter64,
                         c->csc_ptr, c->csc_cursor, c->csc_order, c->csc_slot, c->csc_w, c->gT, c->gxT, c->nz_flags,
-                        c->slot_order, c->topk_cand, c->topk_done, c->sub_idx, c->sub_W, c->predict_out, c->gw_part,
+                        c->slot_order, c->topk_cand, c->sub_idx, c->sub_W, c->predict_out, c->gw_part,
                         c->nz_state, c->nz_bits, c->nz_lab, c->nz_val, c->idx_print, c->xi, c->xr, c->tgt_bits, c->small_sums, c->small_order};
         (void)hipStreamSynchronize(c->stream);
         for (void* p : bufs)

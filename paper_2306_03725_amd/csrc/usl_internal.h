@@ -64,7 +64,8 @@ struct usl_ctx {
     void* sub_W;              size_t sub_W_cap;
     float* predict_out;       size_t predict_out_cap;   // [chunk][m] scores of usl_predict, one chunk of instances at a time
     uint64_t* topk_cand;      size_t topk_cand_cap;  // [b][segments][kk] packed (score, label) keys
-    uint32_t* topk_done;      size_t topk_done_cap;    // workgroups of a prediction's forward that are done (0 between calls)
+    uint32_t* topk_done;           // behind them: workgroups of a prediction's forward that are done (0 between calls)
+    bool topk_done_clear;          // it has been cleared
     float* gw_part;           size_t gw_part_cap;   // [groups][m*k] partial weight gradients of a split batch
     int gw_parts_most;             // groups that it has room for (0: not known yet)
     float* gxT;               size_t gxT_cap;  // [tiles][d][32] input gradient in the same layout
@@ -280,7 +281,6 @@ usl_status usl_launch_precision_hits(usl_ctx* ctx, const int32_t* top_lab, const
                                      const int32_t* tgt_lab, int32_t b, int32_t kk, int64_t* hits);
 int usl_topk_max(void);
 usl_status usl_reserve_topk(usl_ctx* ctx);
-usl_status usl_reserve_topk_done(usl_ctx* ctx);
 usl_status usl_launch_topk_merge(usl_ctx* ctx, int nseg, int32_t b, int32_t kk, int32_t* top_lab, float* top_val);
 // usl_predict of one instance: forward leaves its workgroups' best labels beside the scores.  *done = false: not such a call.
 usl_status usl_launch_predict_few(usl_ctx* ctx, const void* x, const int32_t* idx, const void* W, float* out, int32_t b, int32_t kk,

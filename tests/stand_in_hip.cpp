@@ -10,10 +10,14 @@
 static std::map<const void*, std::string> kernels;
 static std::string launched, refused;
 static hipError_t last = hipSuccess;
+static int allocated;
+static bool capturing;
 
 extern "C" {
 const char* stand_in_launched() { return launched.c_str(); }   // names, one a line, since the last stand_in_start
-void stand_in_start(const char* refuse) { launched.clear(); refused = refuse; }
+void stand_in_start(const char* refuse) { launched.clear(); refused = refuse; allocated = 0; }
+int stand_in_allocated() { return allocated; }   // calls of hipMalloc since then
+void stand_in_capture(int on) { capturing = on != 0; }
 
 void** __hipRegisterFatBinary(const void*) { static void* module; return &module; }
 void __hipUnregisterFatBinary(void**) {}
@@ -40,7 +44,7 @@ hipError_t hipGetDeviceProperties(hipDeviceProp_t* p, int) {
 hipError_t hipFuncGetAttributes(hipFuncAttributes* a, const void*) { memset(a, 0, sizeof *a); a->numRegs = 64; return hipSuccess; }
 hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
 hipError_t hipGetSymbolAddress(void** p, const void*) { static char place[1 << 16]; *p = place; return hipSuccess; }
-hipError_t hipMalloc(void** p, size_t n) { *p = aligned_alloc(256, (n + 255) / 256 * 256); return *p ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipMalloc(void** p, size_t n) { ++allocated; *p = aligned_alloc(256, (n + 255) / 256 * 256); return *p ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipFree(void* p) { free(p); return hipSuccess; }
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) { *p = calloc(n, 1); return hipSuccess; }
 hipError_t hipHostFree(void* p) { free(p); return hipSuccess; }
@@ -50,4 +54,5 @@ hipError_t hipMemcpy(void*, const void*, size_t, hipMemcpyKind) { return hipSucc
 hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }
 hipError_t hipMemset(void*, int, size_t) { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) { *s = capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone; return hipSuccess; }
 }

@@ -205,3 +205,52 @@ def test_merge_by_the_workgroup_that_comes_last(usl, gu, orc, m, d, k):
         np.testing.assert_array_equal(gu.host(lab), want[i][0][:, :5])
         (row + 1).sum().item()
     L.close()
+
+
+@pytest.mark.parametrize("first", ["plain", "captured"])
+@pytest.mark.parametrize("m,d,k,storage", [(500000, 32768, 32, "f32"), (4097, 64, 8, "bf16")])
+def test_capture_of_the_first_prediction_of_one_instance(usl, gu, orc, m, d, k, storage, first):
+    """A context that has only predicted batches is captured, and a new one in the mode that lets a capture allocate; then plain calls before
+    the first replay, and replays between plain calls: labels and the scores' bits are those of forward and the oracle's search."""
+    print("first prediction captured", m, d, k, storage, first, flush=True)
+    cfg = wl.custom(m, d, k, 8, storage=storage, positives=1, index=872)
+    x = wl.gen_x(cfg)
+    stream = torch.cuda.Stream()
+    L, F = usl.Layer(m, d, k, 8, storage, stream.cuda_stream), usl.Layer(m, d, k, 8, storage)
+    d_x, d_idx, d_W, d_out = gu.dev(x), gu.dev(wl.gen_idx(cfg)), gu.dev(wl.gen_W(cfg)), gu.empty((8, m))
+    rows, want = [gu.dev(x[i:i + 1]) for i in range(4)], []
+    for row in rows:
+        F.forward(row, d_idx, d_W, d_out, 1)
+        want.append(orc.topk(gu.host(d_out)[:1], 5))
+    F.forward(d_x, d_idx, d_W, d_out, 8)
+    ref8 = orc.topk(gu.host(d_out), 32)
+    row, lab, val = rows[0].clone(), gu.empty((1, 5), torch.int32), gu.empty((1, 5))
+    lab2, val2 = gu.empty((1, 5), torch.int32), gu.empty((1, 5))
+    torch.cuda.synchronize()
+
+    def same(i, labels, scores):
+        stream.synchronize()
+        np.testing.assert_array_equal(gu.host(labels), want[i][0])
+        np.testing.assert_array_equal(gu.host(scores).view(np.uint32), want[i][1].view(np.uint32))
+
+    with torch.cuda.stream(stream):
+        if first == "plain":
+            lab8, val8 = gu.empty((8, 32), torch.int32), gu.empty((8, 32))
+            L.predict(d_x, d_idx, d_W, 8, 32, lab8, val8)
+            stream.synchronize()
+            np.testing.assert_array_equal(gu.host(lab8), ref8[0])
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream, capture_error_mode="global" if first == "plain" else "relaxed"):
+            L.predict(row, d_idx, d_W, 1, 5, lab, val)
+        for i in (2, 1):
+            L.predict(rows[i], d_idx, d_W, 1, 5, lab2.fill_(-1), val2)
+            same(i, lab2, val2)
+        for i in (3, 0, 2):
+            row.copy_(rows[i])
+            lab.fill_(-1)
+            graph.replay()
+            same(i, lab, val)
+            L.predict(rows[1], d_idx, d_W, 1, 5, lab2.fill_(-1), val2)
+            same(1, lab2, val2)
+    L.close()
+    F.close()

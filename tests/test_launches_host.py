@@ -1,6 +1,6 @@
 """What the library does around its launches, with a HIP runtime that launches nothing (stand_in_hip.cpp), on the host: a refused launch leaves no marks that
-the next step takes for targets, arrays that are not aligned are refused before anything is launched, and a split of the batch asked for by hand that
-there is no room for is a smaller one."""
+the next step takes for targets, arrays that are not aligned are refused before anything is launched, a split of the batch asked for by hand that
+there is no room for is a smaller one, and the count by which a prediction's last workgroup knows itself is there, and 0, before any launch that uses it."""
 import os
 import subprocess
 import sys
@@ -87,4 +87,60 @@ for split in ("2", "32", "1000"):
     hip.stand_in_start(b"")
     L.backward_weight(P["g"], P["x"], P["idx"], P["grad_W"], 512)
     assert at(hip.stand_in_launched().decode().split(), "k_sum_parts")
+""")
+
+
+# m, d, k, storage: one workgroup of 16 wavefronts to a compute unit; smaller workgroups; bfloat16
+ONE = [(500000, 32768, 32, "f32"), (4097, 64, 8, "f32"), (4097, 64, 8, "bf16")]
+PREDICT = """
+def predict(L, b, kk, refuse="", capture=False):
+    hip.stand_in_start(refuse.encode())
+    hip.stand_in_capture(capture)
+    status = 0
+    try:
+        L.predict(P["x"], P["idx"], P["W"], b, kk, P["off"], P["g"])
+    except usl.UslError as e:
+        status = e.status
+    return status, hip.stand_in_launched().decode().split(), hip.stand_in_allocated()
+L = usl.Layer(%d, %d, %d, 8, "%s")
+"""
+
+
+@pytest.mark.parametrize("shape", ONE)
+def test_a_prediction_of_one_instance_finds_its_scratch(stand_in, shape):
+    """Whatever the batch and kk of the first prediction were, no later one allocates or clears (it may be captured)."""
+    run(stand_in, PREDICT % shape + """
+s, names, n = predict(L, 8, 32)
+assert s == 0 and n and at(names, "k_zero_hits"), names
+for kk in (32, 5, 1):
+    s, names, n = predict(L, 1, kk, capture=kk == 5)
+    assert s == 0 and at(names, "k_forward_few") and not at(names, "k_zero_hits") and n == 0, (kk, names, n)
+    assert kk == 32 or not at(names, "k_topk_merge"), (kk, names)
+""")
+
+
+@pytest.mark.parametrize("shape", ONE)
+def test_a_count_whose_clearing_is_refused_is_cleared_by_the_next_call(stand_in, shape):
+    run(stand_in, PREDICT % shape + """
+s, names, n = predict(L, 1, 5, refuse="k_zero_hits")
+assert s == usl.USL_EHIP and not at(names, "k_forward_few"), (s, names)
+s, names, n = predict(L, 1, 5)
+assert s == 0 and at(names, "k_zero_hits") and at(names, "k_zero_hits")[0] < at(names, "k_forward_few")[0], names
+s, names, n = predict(L, 1, 5)
+assert s == 0 and not at(names, "k_zero_hits") and not at(names, "k_topk_merge"), names
+""")
+
+
+@pytest.mark.parametrize("shape", ONE)
+def test_a_clearing_that_is_only_recorded_does_not_count(stand_in, shape):
+    """The first predictions of a context under a capture: they use no count, and the first plain call clears it before it does."""
+    run(stand_in, PREDICT % shape + """
+for kk in (5, 1):
+    s, names, n = predict(L, 1, kk, capture=True)
+    assert s == 0 and at(names, "k_forward_few") and not at(names, "k_zero_hits") and at(names, "k_topk_merge"), (kk, names)
+s, names, n = predict(L, 1, 5)
+assert s == 0 and n == 0 and not at(names, "k_topk_merge"), (names, n)
+assert at(names, "k_zero_hits") and at(names, "k_zero_hits")[0] < at(names, "k_forward_few")[0], names
+s, names, n = predict(L, 1, 5, capture=True)
+assert s == 0 and n == 0 and not at(names, "k_zero_hits") and not at(names, "k_topk_merge"), (names, n)
 """)
