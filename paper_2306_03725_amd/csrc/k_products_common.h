@@ -788,6 +788,12 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
     // cost both (80 and 40.5 us).  So labels of up to 16 slots go through the caches, of 24 where scores_through_caches says so.  Not where the loss
     // is part of it: there is more between the stores (steps at these sizes 2 to 4 % slower through the caches).
     constexpr bool past = LOSS || !CACHED;
+    // Addresses of the scores: a base in scalar registers and a lane's 32-bit offset or, where scores leave alone and a read brings 4 bytes, one address a
+    // lane (16 to 48 slots; of bfloat16 32 and 48): the compiler's registers and spills come out otherwise.  Forward with the base and with one address a
+    // lane, us: m = 500k, d = 32k, k = 32, b = 256 756.3 and 749.8; m = 210 007, d = 40k, b = 60, k = 32 114.9 and 111.1, k = 16 78.7 and 77.0, k = 48 183.4 and 182.1;
+    // m = 500k, d = 36k, k = 32, b = 100, bfloat16 206.0 and 201.9.  The others, the same way round: m = 400k, d = 18k, k = 16, b = 48 82.4 and 89.1; d = 6k, k = 32, bfloat16
+    // 77.1 and 81.0; two halves of rows, m = 250k, d = 65 536, k = 48, b = 64 337 and 346; the step with the loss inside at m = 500k, d = 32k, b = 256 1950.5 and 1955.4.
+    constexpr bool LANE_ADDRESSES = LOSS == 0 && !HALVES && Q * sizeof(TS) == 4 && K >= (sizeof(TS) == 4 ? 16 : 32) && K < 64;
     auto put = [&](int g, int l, const float (&z)[Q]) {
         int jl = (int)threadIdx.x + l * NT;   // rebuilt here: kept, every label's offset would be a register across the gathers
         asm volatile("" : "+v"(jl));
@@ -808,7 +814,8 @@ k_forward(const char* __restrict__ xi, const int32_t* __restrict__ idx, const TS
                             sum += r.lin;
                             logs += r.log2;
                         }
-                        float* to = reinterpret_cast<float*>(reinterpret_cast<char*>(out + ((size_t)(g * Q + q) * m + j0)) + (uint32_t)jl * 4u);   // (base in scalar registers)
+                        float* row = out + ((size_t)(g * Q + q) * m + j0);
+                        float* to = LANE_ADDRESSES ? row + (uint32_t)jl : reinterpret_cast<float*>(reinterpret_cast<char*>(row) + (uint32_t)jl * 4u);
                         if constexpr (past) __builtin_nontemporal_store(o, to); else *to = o;
                         if constexpr (LOSS == 2) {   // lane 0's word and, where the wavefront has more than 32 labels, lane 1's
                             const uint64_t set = __ballot(o != 0.f);
