@@ -30,7 +30,10 @@
  * path (usl_validate_indices checks them).  Target label ids must lie in [0, m).
  * usl_last_error returns a context-owned message for the most recent failure.
  *
- * THREADS: a context is not thread-safe; use one context per host thread / stream.
+ * THREADS: a context is not thread-safe; use one context per host thread / stream.  Its scratch serves one call
+ * at a time: kernels of two calls must not overlap on the device, replays of captured graphs included.  A caller that
+ * moves a context to another stream (usl_set_stream, which neither waits nor orders the two) or replays a graph on
+ * another stream orders that behind the earlier work.  Results of calls that overlap are undefined; later calls are not affected.
  */
 #ifndef USL_H
 #define USL_H

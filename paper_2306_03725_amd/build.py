@@ -127,7 +127,7 @@ def build(force=True, verbose=False):
     objs = []
     procs = []
     os.makedirs(os.path.join(HERE, "_build"), exist_ok=True)
-    deps = [os.path.join(CSRC, "usl_internal.h"), os.path.join(CSRC, "k_lists_cut.h"), os.path.join(CSRC, "k_matching.h"), os.path.join(CSRC, "k_lanes.h"), os.path.join(CSRC, "k_adam.h"), os.path.join(CSRC, "k_sums.h"), os.path.join(CSRC, "k_topk.h"), os.path.join(CSRC, "k_step_small.h"), os.path.join(CSRC, "k_products_common.h"), os.path.join(CSRC, "k_products_inst.h"),
+    deps = [os.path.join(CSRC, "usl_internal.h"), os.path.join(CSRC, "k_lists_cut.h"), os.path.join(CSRC, "k_count.h"), os.path.join(CSRC, "k_matching.h"), os.path.join(CSRC, "k_lanes.h"), os.path.join(CSRC, "k_adam.h"), os.path.join(CSRC, "k_sums.h"), os.path.join(CSRC, "k_topk.h"), os.path.join(CSRC, "k_step_small.h"), os.path.join(CSRC, "k_products_common.h"), os.path.join(CSRC, "k_products_inst.h"),
             os.path.join(CSRC, "k_products.h"), os.path.join(HERE, "..", "include", "usl.h")]
     newest_dep = max(os.path.getmtime(p) for p in deps)
     for src in SOURCES:

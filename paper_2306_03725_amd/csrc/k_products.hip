@@ -5,6 +5,7 @@
 
 #include "k_products.h"
 #include "k_products_common.h"
+#include "k_count.h"
 #include "k_topk.h"
 
 using namespace usl_products;
@@ -382,7 +383,8 @@ k_forward_few(const char* __restrict__ xi, const int32_t* __restrict__ idx, cons
     if (threadIdx.x < 64) {
         if (lane < kk) __hip_atomic_store(to, own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the candidates are there before the count says so
-        if (lane == 0) *last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1 ? 1u : 0u;
+        const uint32_t share = usl_count_share(blockIdx.x, gridDim.x);
+        if (lane == 0) *last = usl_count_is_last(__hip_atomic_fetch_add(done, share, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), share) ? 1u : 0u;
     }
     __syncthreads();
     if (!*last) return;
@@ -397,7 +399,6 @@ k_forward_few(const char* __restrict__ xi, const int32_t* __restrict__ idx, cons
         top_lab[lane] = key_label(top);
         top_val[lane] = key_score(top);
     }
-    if (threadIdx.x == 0) __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // out[i][:] once more, slot by slot, for the instances whose activation 0 is not finite (see pads_with_column_0): nearly

@@ -64,7 +64,7 @@ struct usl_ctx {
     void* sub_W;              size_t sub_W_cap;
     float* predict_out;       size_t predict_out_cap;   // [chunk][m] scores of usl_predict, one chunk of instances at a time
     uint64_t* topk_cand;      size_t topk_cand_cap;  // [b][segments][kk] packed (score, label) keys
-    uint32_t* topk_done;           // behind them: workgroups of a prediction's forward that are done (0 between calls)
+    uint32_t* topk_done;           // behind them: the count of a prediction's forward (k_count.h; 0 between calls)
     bool topk_done_clear;          // it has been cleared
     float* gw_part;           size_t gw_part_cap;   // [groups][m*k] partial weight gradients of a split batch
     int gw_parts_most;             // groups that it has room for (0: not known yet)

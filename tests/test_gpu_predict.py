@@ -254,3 +254,40 @@ def test_capture_of_the_first_prediction_of_one_instance(usl, gu, orc, m, d, k, 
             same(1, lab2, val2)
     L.close()
     F.close()
+
+
+@pytest.mark.parametrize("m,d,k", [(500000, 32768, 32), (4097, 64, 8), (30000, 64, 8)])
+def test_predictions_that_overlap_spoil_no_later_one(usl, gu, orc, m, d, k):
+    """Two graphs of one context replayed on two streams at a time: what they write is undefined, what calls after a wait write is not."""
+    print("overlapping predictions", m, d, k, flush=True)
+    cfg = wl.custom(m, d, k, 4, positives=1, index=873)
+    x = wl.gen_x(cfg)
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    L = usl.Layer(m, d, k, 1, stream=torch.cuda.current_stream().cuda_stream)
+    d_idx, d_W, d_out = gu.dev(wl.gen_idx(cfg)), gu.dev(wl.gen_W(cfg)), gu.empty((1, m))
+    rows, want = [gu.dev(x[i:i + 1]) for i in range(4)], []
+    for row in rows:
+        L.forward(row, d_idx, d_W, d_out, 1)
+        want.append(orc.topk(gu.host(d_out), 5))
+    lab, val = gu.empty((1, 5), torch.int32), gu.empty((1, 5))
+    L.predict(rows[0], d_idx, d_W, 1, 5, lab, val)
+    torch.cuda.synchronize()
+    graphs, spare = [], [(gu.empty((1, 5), torch.int32), gu.empty((1, 5))) for _ in streams]
+    for stream, to in zip(streams, spare):
+        graphs.append(torch.cuda.CUDAGraph())
+        L.set_stream(stream.cuda_stream)
+        with torch.cuda.graph(graphs[-1], stream=stream):
+            for _ in range(50):
+                L.predict(rows[0], d_idx, d_W, 1, 5, *to)
+    L.set_stream(torch.cuda.current_stream().cuda_stream)
+    for turn in range(20):
+        for stream, graph in zip(streams, graphs):
+            with torch.cuda.stream(stream):
+                graph.replay()
+        torch.cuda.synchronize()
+        for i in (1, 2, 3):
+            lab.fill_(-1), val.fill_(-1.0)
+            L.predict(rows[i], d_idx, d_W, 1, 5, lab, val)
+            np.testing.assert_array_equal(gu.host(lab), want[i][0])
+            np.testing.assert_array_equal(gu.host(val).view(np.uint32), want[i][1].view(np.uint32))
+    L.close()
