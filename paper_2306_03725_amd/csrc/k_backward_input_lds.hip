@@ -822,8 +822,10 @@ k_bwi_lds(const float* __restrict__ g, const TS* __restrict__ W, int64_t m, int 
 // half of that with bank conflicts (profiles/products_large_f32_lds_bank_conflicts.txt), the row copies take a third of a
 // pass at the L2 -> LDS rate, and copy, gathers and sums of a pass follow one another, with barriers between them.
 // The sums of overflow entries live in LDS (ov_sum) or, beyond the NEAR2 that LDS holds, in memory (ovgw).
-__device__ __forceinline__ void gather4_two(float& acc0, float& acc1, float& s0, float& s1, float& s2, float& s3,
-                                            uint32_t p0, uint32_t p1, float w0, float w1, float w2, float w3, float x0, float x1) {
+// acc and x are arrays on purpose: handed over one by one, the second list's activations are asked for in a branch of their own, and every group of the
+// first list begins with a wait for all LDS reads (m = 500k, d = 32k, k = 32, b = 256: the step 1965 us, so 1956).
+__device__ __forceinline__ void gather4_two(float (&acc)[2], float& s0, float& s1, float& s2, float& s3,
+                                            uint32_t p0, uint32_t p1, float w0, float w1, float w2, float w3, const float (&x)[2]) {
     const uint32_t three = 3;
     asm volatile(
         "v_lshlrev_b32_sdwa v112, %6, %7 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
@@ -854,8 +856,8 @@ __device__ __forceinline__ void gather4_two(float& acc0, float& acc1, float& s0,
         "v_fmac_f32 %1, %12, v119\n\t"
         "v_fmac_f32 %5, %13, v118\n\t"
         "v_fmac_f32 %5, %14, v119"
-        : "+v"(acc0), "+v"(acc1), "+v"(s0), "+v"(s1), "+v"(s2), "+v"(s3)
-        : "s"(three), "v"(p0), "v"(p1), "v"(w0), "v"(w1), "v"(w2), "v"(w3), "v"(x0), "v"(x1)
+        : "+v"(acc[0]), "+v"(acc[1]), "+v"(s0), "+v"(s1), "+v"(s2), "+v"(s3)
+        : "s"(three), "v"(p0), "v"(p1), "v"(w0), "v"(w1), "v"(w2), "v"(w3), "v"(x[0]), "v"(x[1])
         : "memory", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119");
 }
 
@@ -1344,13 +1346,13 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
         int ac = acap, bc = bcap;   // compared afresh in every pass, see k_bwi_lds
         asm volatile("" : "+s"(ac), "+s"(bc));
         if constexpr (Q == 4) unit_of(xbuf + (size_t)(feat_of[(OWN ? NT : 0) + tid] & 0xFFFFu) * 4, xa);
-        constexpr bool TWOS = Q == 4;   // groups by twos, from the list's own end
 #pragma unroll
-        for (int q = 0; q < KT / 4; q += TWOS ? 2 : 1) {
-            if (q * 4 >= ac) continue;
-            if constexpr (TWOS) gather8(acc_a, gw + q * 4, pk + q * 2, wt + q * 4, gw + q * 4 + 4, pk + q * 2 + 2, wt + q * 4 + 4, xa, ac, q * 4 + 4);
-            else gather4_two(acc_a[0], acc_a[1], gw[q * 4], gw[q * 4 + 1], gw[q * 4 + 2], gw[q * 4 + 3], pk[q * 2], pk[q * 2 + 1],
-                             wt[q * 4], wt[q * 4 + 1], wt[q * 4 + 2], wt[q * 4 + 3], xa[0], xa[1]);
+        for (int q = 0; q < KT / 4; q += Q == 4 ? 2 : 1) {
+            if (q * 4 < ac) {
+                if constexpr (Q == 4) gather8(acc_a, gw + q * 4, pk + q * 2, wt + q * 4, gw + q * 4 + 4, pk + q * 2 + 2, wt + q * 4 + 4, xa, ac, q * 4 + 4);
+                else gather4_two(acc_a, gw[q * 4], gw[q * 4 + 1], gw[q * 4 + 2], gw[q * 4 + 3], pk[q * 2], pk[q * 2 + 1],
+                                 wt[q * 4], wt[q * 4 + 1], wt[q * 4 + 2], wt[q * 4 + 3], xa);
+            }
         }
         if constexpr (Q == 4) {   // OWN: the first list's sums leave before the second list begins
             tid = threadIdx.x;
@@ -1364,11 +1366,13 @@ k_both_lds(const float* __restrict__ g, const TS* __restrict__ W, const TS* __re
             unit_of(xbuf + (size_t)(feat_of[(OWN ? NT : 0) + tid] >> 16) * 4, xb);
         }
 #pragma unroll
-        for (int q = KT / 4 - 1; q >= 0; q -= TWOS ? 2 : 1) {
-            if (q * 4 < KT - bc) continue;
-            if constexpr (TWOS) gather8(acc_b, gw + q * 4, pk + q * 2, wt + q * 4, gw + q * 4 - 4, pk + q * 2 - 2, wt + q * 4 - 4, xb, bc, KT - q * 4 + 3);
-            else gather4_two(acc_b[0], acc_b[1], gw[q * 4], gw[q * 4 + 1], gw[q * 4 + 2], gw[q * 4 + 3], pk[q * 2], pk[q * 2 + 1],
-                             wt[q * 4], wt[q * 4 + 1], wt[q * 4 + 2], wt[q * 4 + 3], xb[0], xb[1]);
+        for (int n = 0; n < KT / 4; n += Q == 4 ? 2 : 1) {   // by twos from the list's own end
+            const int q = Q == 4 ? KT / 4 - 1 - n : n;
+            if (q * 4 >= KT - bc) {
+                if constexpr (Q == 4) gather8(acc_b, gw + q * 4, pk + q * 2, wt + q * 4, gw + q * 4 - 4, pk + q * 2 - 2, wt + q * 4 - 4, xb, bc, KT - q * 4 + 3);
+                else gather4_two(acc_b, gw[q * 4], gw[q * 4 + 1], gw[q * 4 + 2], gw[q * 4 + 3], pk[q * 2], pk[q * 2 + 1],
+                                 wt[q * 4], wt[q * 4 + 1], wt[q * 4 + 2], wt[q * 4 + 3], xb);
+            }
         }
         tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
