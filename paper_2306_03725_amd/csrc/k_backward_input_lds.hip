@@ -670,7 +670,7 @@ __device__ __forceinline__ void gather4(float& acc, uint32_t p0, uint32_t p1, fl
         "v_fmac_f32 %0, %10, %3\n\t"
         "s_waitcnt lgkmcnt(0)\n\t"
         "v_fmac_f32 %0, %11, %4"
-        : "+v"(acc), "=&v"(a0), "=&v"(a1), "=&v"(a2), "=&v"(a3)
+        : "+&v"(acc), "=&v"(a0), "=&v"(a1), "=&v"(a2), "=&v"(a3)
         : "s"(two), "v"(p0), "v"(p1), "v"(w0), "v"(w1), "v"(w2), "v"(w3)
         : "memory");
 }
@@ -856,7 +856,7 @@ __device__ __forceinline__ void gather4_two(float (&acc)[2], float& s0, float& s
         "v_fmac_f32 %1, %12, v119\n\t"
         "v_fmac_f32 %5, %13, v118\n\t"
         "v_fmac_f32 %5, %14, v119"
-        : "+v"(acc[0]), "+v"(acc[1]), "+v"(s0), "+v"(s1), "+v"(s2), "+v"(s3)
+        : "+&v"(acc[0]), "+&v"(acc[1]), "+&v"(s0), "+&v"(s1), "+&v"(s2), "+&v"(s3)
         : "s"(three), "v"(p0), "v"(p1), "v"(w0), "v"(w1), "v"(w2), "v"(w3), "v"(x[0]), "v"(x[1])
         : "memory", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119");
 }
@@ -999,7 +999,7 @@ __device__ __forceinline__ void gather8(float (&acc)[4], float* s, const uint32_
         "v_fmac_f32 %7, %27, v126\n\t"
         "v_fmac_f32 %7, %28, v127\n"
         ".Lend%=:"
-        : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]), "+v"(s_far[0]), "+v"(s_far[1]), "+v"(s_far[2]), "+v"(s_far[3])
+        : "+&v"(acc[0]), "+&v"(acc[1]), "+&v"(acc[2]), "+&v"(acc[3]), "+&v"(s[0]), "+&v"(s[1]), "+&v"(s[2]), "+&v"(s[3]), "+&v"(s_far[0]), "+&v"(s_far[1]), "+&v"(s_far[2]), "+&v"(s_far[3])
         : "s"(shift), "v"(p[0]), "v"(p[1]), "v"(p_far[0]), "v"(p_far[1]), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "v"(w_far[0]), "v"(w_far[1]), "v"(w_far[2]), "v"(w_far[3]), "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "s"(n), "s"(most)
         : "memory", "scc", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119", "v120", "v121", "v122", "v123", "v124", "v125", "v126", "v127");
 }
