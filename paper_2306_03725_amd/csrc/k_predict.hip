@@ -194,7 +194,7 @@ usl_status usl_reserve_topk(usl_ctx* c) {
 // The best kk of every row from nseg sets of kk candidates each (usl_ctx::topk_cand).
 usl_status usl_launch_topk_merge(usl_ctx* c, int nseg, int32_t b, int32_t kk, int32_t* top_lab, float* top_val) {
     const int n = nseg * kk;
-    if (n <= 8 * TK_NT)   // what 256 lanes hold in registers
+    if (n <= TOPK_SHORT_MERGE)
         hipLaunchKernelGGL(k_topk_merge<TK_NT>, dim3((unsigned)b), dim3(TK_NT), 0, c->stream, c->topk_cand, n, (int)kk, top_lab, top_val);
     else
         hipLaunchKernelGGL(k_topk_merge<1024>, dim3((unsigned)b), dim3(1024), 0, c->stream, c->topk_cand, n, (int)kk, top_lab, top_val);

@@ -803,6 +803,20 @@ FewShape few_shape(const usl_ctx* c, const Layout& L, int kk) {
 // k = 3 22.0 and 24.3; m = 1.27M, k = 32 68.2 and 69.5.
 bool best_from_forward(const usl_ctx* c, const FewShape& f) { return f.nw < 16 || f.grid <= (unsigned)c->num_cu || f.turns >= 3; }
 
+// ... and who merges the workgroups' candidates: the one that comes last, or a launch of its own?  The last one has waited for the others at the count, which
+// takes 11.5 ns of each, and saves a launch; a launch of more than TOPK_SHORT_MERGE candidates takes 3 to 6 us longer.  So it is the last one with few workgroups (the more, the
+// more labels are asked for), with many candidates, and where the stream of idx and W lasts so long that the workgroups come in spread out.  usl_predict, last workgroup and
+// launch, from captured graphs | call by call, us: 47 workgroups, 1 label 5.55 and 5.40 | 6.2 and 8.8; 79, 3 labels 7.5 and 7.3 | 7.6 and 8.4; 79, 10 labels 13.4 and 14.1 | 13.2 and 14.1;
+// not so 118, 1 label 6.3 and 5.4 | 7.0 and 8.8; 157, 5 labels 9.9 and 9.3 | 9.9 and 9.9; 254, 2 labels 8.6 and 6.5 | 8.6 and 8.3; 256 of 8 wavefronts (m = 131k, d = 25k, k = 16), 5 labels 12.8 and
+// 10.8 | 12.7 and 11.0; 256 of 16 wavefronts with 29 MB (m = 114k, d = 34k, k = 32), 5 labels 14.5 and 13.0 | 14.3 and 13.1, 10 labels 19.7 and 22.5 | 19.5 and 22.4; with 45 MB (m = 175k, d = 33k) 5 labels
+// 19.9 and 19.7 | 18.4 and 18.7; with 128 MB (m = 500k, d = 32k) 30.0 and 29.8 | 30.1 and 30.0, 10 labels 33.9 and 37.4 | 35.3 and 39.4.  (Two workgroups to a compute unit: their candidates, twice as many,
+// come late; m = 1.34M, d = 11k, k = 3 25.1 us with a launch for the merge, 26.1 without.)
+bool last_one_merges(const usl_ctx* c, const FewShape& f, int kk) {
+    const int64_t n = (int64_t)f.grid * kk, stream = c->m * c->k * (c->storage == USL_F32 ? 8 : 6);
+    if (f.grid > (unsigned)c->num_cu || n > (int64_t)FEW_HELD * f.nw * 64) return false;
+    return (int)f.grid <= 32 + 16 * kk || n > TOPK_SHORT_MERGE || stream >= 40000000;
+}
+
 // One group of instances: the streaming kernel.  kk > 0: with the *blocks workgroups' best labels beside the scores.
 usl_status run_forward_few(usl_ctx* c, const Layout& L, const void* x, const int32_t* idx, const void* W, float* out, int b, int kk = 0, int32_t* top_lab = nullptr,
                            float* top_val = nullptr) {
@@ -818,8 +832,7 @@ usl_status run_forward_few(usl_ctx* c, const Layout& L, const void* x, const int
     if (kk > 0) {
         USL_TRY(usl_reserve_topk(c));
         cand = c->topk_cand;
-        // (Two workgroups to a compute unit: their candidates, twice as many, come late; m = 1.34M, d = 11k, k = 3 25.1 us with a launch for the merge, 26.1 without.)
-        merge = c->topk_done_clear && grid <= (unsigned)c->num_cu && (int64_t)grid * kk <= (int64_t)FEW_HELD * nw * 64;
+        merge = c->topk_done_clear && last_one_merges(c, f, kk);
     }
 #define USL_FEW_B(LPL, TS, Q, VEC, AHEAD, BEST)                                                                    \
     do {                                                                                                                \

@@ -119,6 +119,21 @@ for kk in (32, 5, 1):
 """)
 
 
+# labels, features, fan-in, labels asked for; whether the last workgroup merges: few workgroups (47, 48 and 64 with 1 label, 112 and 113 with 5), 256 of 8 wavefronts, of 16 with a
+# short stream, with many candidates, with too many, with a long stream, two workgroups to a compute unit
+MERGES = [(12000, 600, 8, 1, True), (12288, 600, 8, 1, True), (12289, 600, 8, 1, False), (28672, 600, 8, 5, True), (28673, 600, 8, 5, False),
+          (131000, 25000, 16, 5, False), (113590, 34460, 32, 5, False), (113590, 34460, 32, 8, False), (113590, 34460, 32, 9, True),
+          (113590, 34460, 32, 16, True), (113590, 34460, 32, 17, False), (175219, 33043, 32, 1, True), (500000, 32768, 32, 16, True), (1340000, 11000, 3, 5, False)]
+
+
+@pytest.mark.parametrize("m,d,k,kk,last", MERGES)
+def test_who_merges_the_candidates(stand_in, m, d, k, kk, last):
+    run(stand_in, PREDICT % (m, d, k, "f32") + """
+s, names, n = predict(L, 1, %d)
+assert s == 0 and at(names, "k_forward_few") and bool(at(names, "k_topk_merge")) != %r, names
+""" % (kk, last))
+
+
 @pytest.mark.parametrize("shape", ONE)
 def test_a_count_whose_clearing_is_refused_is_cleared_by_the_next_call(stand_in, shape):
     run(stand_in, PREDICT % shape + """
