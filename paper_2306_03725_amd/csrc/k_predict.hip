@@ -12,6 +12,7 @@ namespace {
 constexpr int TK_NT = 256;             // lanes per workgroup
 // scores a lane holds in registers: 64, or 8 where that would leave most of the chip without a workgroup
 constexpr int TK_EPT = 64, TK_EPT_FEW = 8;
+static_assert(TK_NT * TK_EPT_FEW == TOPK_SHORT_SEGMENT, "what the choice of a prediction's path counts with");
 constexpr int TK_MAX = 32;             // largest kk
 
 // Largest v of the workgroup, returned to every lane.  red: two sets used in turn, so one barrier is enough.

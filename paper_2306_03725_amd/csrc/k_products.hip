@@ -796,12 +796,21 @@ FewShape few_shape(const usl_ctx* c, const Layout& L, int kk) {
 }
 
 // Prediction of one instance: the best labels from the forward kernel, or from kernels over its scores?  The forward kernel's workgroups look for theirs when
-// all wavefronts are done, 3 us of chains of maxima, and where two of 16 wavefronts share a compute unit their candidates take longer to
-// merge; the other way costs a launch and a pass of 6 us over scores in the cache, and 1 us of forward less.  usl_predict, from forward and with the pass:
-// smaller workgroups: m = 5000, d = 64, k = 8 10.4 us and 12.9; m = 60 867, d = 1344, k = 16 12.3 and 13.3; one of 16 wavefronts to a compute unit: m = 500k, d = 32k, k = 32 34.8
-// and 37.5; two of them: m = 225 711, d = 118, k = 13 22.0 and 18.8; m = 109 071, d = 7213, k = 32 18.4 and 16.4; m = 720 436, d = 2151, k = 13 33.5 and 29.8; three turns: m = 1.34M, d = 11k,
-// k = 3 22.0 and 24.3; m = 1.27M, k = 32 68.2 and 69.5.
-bool best_from_forward(const usl_ctx* c, const FewShape& f) { return f.nw < 16 || f.grid <= (unsigned)c->num_cu || f.turns >= 3; }
+// all wavefronts are done, 3 us of chains of maxima for 5 labels, and where two of 16 wavefronts share a compute unit or many labels are asked for their candidates take longer to
+// merge; the other way costs a launch and a pass of 6 us over scores in the cache, and 1 us of forward less.  usl_predict, from forward and with the pass, us (captured graphs):
+// smaller workgroups: m = 5000, d = 64, k = 8, 5 labels 8.5 and 11.2, 32 labels 31.1 and 41.8; m = 60 867, d = 1344, k = 16, 5 labels 11.7 and 12.0, not so 10 labels 18.9 and 18.0, 32 labels 76.8 and
+// 42.9; m = 49k, d = 1762, k = 32, 5 labels 12.9 and 14.5, not so 8 labels 19.2 and 18.1; m = 100k, d = 600, k = 8, 5 labels 9.6 and 11.9, not so 16 labels 27.5 and 24.6; m = 262k, d = 25k, k = 8, 32
+// labels (8192 candidates and 4096) 50.7 and 57.8;
+// one of 16 wavefronts to a compute unit: m = 500k, d = 32k, k = 32, 5 labels 28.6 and 30.8, 32 labels 70.0 and 74.7; m = 114k, d = 34k, k = 32, 5 labels 12.7 and 14.4 (32 labels 54.7 and 45.8);
+// not so two of them: m = 225 711, d = 118, k = 13, 5 labels 22.0 and 18.0; m = 109 071, d = 7213, k = 32 17.8 and 15.9; m = 720 436, d = 2151, k = 13 33.1 and 29.7 (m = 1.02M, d = 2473, k = 8 24.2 and 25.7);
+// three turns: m = 1.27M, d = 11k, k = 32, 5 labels 63.7 and 68.4, 32 labels 145 and 156; m = 1.32M, d = 561, k = 56, bfloat16 95.3 and 99.6 (m = 1.34M, d = 11k, k = 3 24.5 and 23.6).
+bool best_from_forward(const usl_ctx* c, const FewShape& f, int kk) {
+    if (f.nw < 16) {
+        const int64_t n = (int64_t)f.grid * kk, by_pass = (c->m + TOPK_SHORT_SEGMENT - 1) / TOPK_SHORT_SEGMENT * kk;   // candidates
+        return kk <= 5 || n <= TOPK_SHORT_MERGE || (by_pass > TOPK_SHORT_MERGE && n <= by_pass * 2);
+    }
+    return f.grid <= (unsigned)c->num_cu || f.turns >= 3;
+}
 
 // ... and who merges the workgroups' candidates: the one that comes last, or a launch of its own?  The last one has waited for the others at the count, which
 // takes 11.5 ns of each, and saves a launch; a launch of more than TOPK_SHORT_MERGE candidates takes 3 to 6 us longer.  So it is the last one with few workgroups (the more, the
@@ -817,7 +826,7 @@ bool last_one_merges(const usl_ctx* c, const FewShape& f, int kk) {
     return (int)f.grid <= 32 + 16 * kk || n > TOPK_SHORT_MERGE || stream >= 40000000;
 }
 
-// One group of instances: the streaming kernel.  kk > 0: with the *blocks workgroups' best labels beside the scores.
+// One group of instances: the streaming kernel.  kk > 0, one instance: its best labels; out is scratch then, written only by wavefronts of more than FEW_HELD turns.
 usl_status run_forward_few(usl_ctx* c, const Layout& L, const void* x, const int32_t* idx, const void* W, float* out, int b, int kk = 0, int32_t* top_lab = nullptr,
                            float* top_val = nullptr) {
     const void* xi = nullptr;
@@ -944,7 +953,7 @@ usl_status usl_launch_predict_few(usl_ctx* c, const void* x, const int32_t* idx,
     *done = false;
     if (!fast_path_ok(c, idx, W)) return USL_OK;
     const Layout L = layout_of(c, b, x);
-    if (b > 1 || !streams(c, L, b) || !best_from_forward(c, few_shape(c, L, kk))) return USL_OK;
+    if (b > 1 || !streams(c, L, b) || !best_from_forward(c, few_shape(c, L, kk), kk)) return USL_OK;
     USL_TRY(run_forward_few(c, L, x, idx, W, out, b, kk, top_lab, top_val));
     *done = true;
     return USL_OK;

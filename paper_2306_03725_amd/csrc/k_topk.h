@@ -3,6 +3,7 @@
 #include "usl_internal.h"
 
 constexpr int TOPK_SHORT_MERGE = 8 * 256;   // candidates that a merge of 256 lanes holds in registers; more take it 1024
+constexpr int TOPK_SHORT_SEGMENT = 8 * 256;  // scores of a workgroup of the pass over them where rows are few
 
 // The upper word ranks scores (-0 as +0), the lower one equal scores by label (below 2^31, so ~label's top bit says nothing); its last bit says
 // that the score is not -0, so that a key holds the score's own bits and no kernel that merges keys waits for the scores themselves.

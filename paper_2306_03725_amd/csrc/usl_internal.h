@@ -282,7 +282,7 @@ usl_status usl_launch_precision_hits(usl_ctx* ctx, const int32_t* top_lab, const
 int usl_topk_max(void);
 usl_status usl_reserve_topk(usl_ctx* ctx);
 usl_status usl_launch_topk_merge(usl_ctx* ctx, int nseg, int32_t b, int32_t kk, int32_t* top_lab, float* top_val);
-// usl_predict of one instance: forward leaves its workgroups' best labels beside the scores.  *done = false: not such a call.
+// usl_predict of one instance: the best labels from the forward kernel's workgroups (out: scratch, not to be read afterwards).  *done = false: not such a call.
 usl_status usl_launch_predict_few(usl_ctx* ctx, const void* x, const int32_t* idx, const void* W, float* out, int32_t b, int32_t kk,
                                   int32_t* top_lab, float* top_val, bool* done);
 static inline int usl_forward_few_blocks(const usl_ctx* c) { return c->num_cu * 2; }   // workgroups of its forward at most

@@ -159,3 +159,17 @@ assert at(names, "k_zero_hits") and at(names, "k_zero_hits")[0] < at(names, "k_f
 s, names, n = predict(L, 1, 5, capture=True)
 assert s == 0 and n == 0 and not at(names, "k_zero_hits") and not at(names, "k_topk_merge"), (names, n)
 """)
+
+
+# labels, features, fan-in, labels asked for; whether the forward kernel looks for the best ones: workgroups of 4 wavefronts, 5 and 6 labels of 424, 8 of
+# as many as a short merge holds and of one more, 32 of many with the pass's candidates too many for a short merge as well; one of 16 wavefronts to a compute unit, two, two with three turns
+FROM_FORWARD = [(5000, 64, 8, 32, True), (54181, 600, 16, 5, True), (54181, 600, 16, 6, False), (65536, 600, 8, 8, True), (65537, 600, 8, 8, False), (60867, 1344, 16, 32, False), (262000, 25000, 8, 32, True), (200460, 188, 8, 32, False),
+                (113590, 34460, 32, 32, True), (109071, 7213, 32, 1, False), (1270000, 11000, 32, 32, True)]
+
+
+@pytest.mark.parametrize("m,d,k,kk,forward", FROM_FORWARD)
+def test_where_the_best_labels_come_from(stand_in, m, d, k, kk, forward):
+    run(stand_in, PREDICT % (m, d, k, "f32") + """
+s, names, n = predict(L, 1, %d)
+assert s == 0 and at(names, "k_forward_few") and bool(at(names, "k_topk_segments")) != %r, names
+""" % (kk, forward))
