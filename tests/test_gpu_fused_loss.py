@@ -132,8 +132,10 @@ def test_a_context_for_far_larger_batches(orc):
 @pytest.mark.parametrize("m,d,k,b,storage", [(3001, 300, 32, 21, "f32"), (2049, 9000, 8, 18, "bf16"), (2050, 24000, 48, 19, "f32"), (1500, 50000, 33, 17, "f32")])
 @pytest.mark.parametrize("factor", [0.0, 0.01, 1.0, 12.0, 60.0])
 def test_loss_of_small_and_large_scores(m, d, k, b, storage, factor):
-    """The loss inside forward against float64 of the same scores.  A score's terms carry two roundings of the hardware's exponential and logarithm (an
-    ulp each) and those of up to four scores' sums, at most 8 * 2^-24 of the terms' magnitude together; everything else is float64: 1e-6."""
+    """The loss inside forward against float64 of the same scores.  A score's term carries the roundings of the hardware's exponential and logarithm (an ulp
+    each), of 1 + e, which is 2^-24 of the term's own size or absolutely, whichever is more, and those of up to four scores' sums; everything else is
+    float64.  These scores lie on both sides of 0, so that a score's magnitude is 0.3 or more on average and all of that stays below 16 * 2^-24 of the magnitudes: 1e-6.
+    Scores that are all negative: the test below."""
     import gpu_util as gu
     import torch
     from paper_2306_03725_amd import usl
@@ -155,4 +157,30 @@ def test_loss_of_small_and_large_scores(m, d, k, b, storage, factor):
     torch.cuda.synchronize()
     magnitude = (np.maximum(z64, 0.0) + np.abs(z64) * y + np.log1p(np.exp(-np.abs(z64)))).sum() / b
     assert abs(float(gu.host(loss)[0]) - terms.sum() / b) <= 1e-6 * magnitude
+    L.close()
+
+
+@pytest.mark.parametrize("m,d,k,b,storage", [(3001, 300, 32, 21, "f32"), (2049, 9000, 8, 18, "bf16"), (2050, 24000, 48, 19, "f32"), (1500, 50000, 33, 17, "f32")])
+@pytest.mark.parametrize("mean", [-4.5, -10.0, -14.0, -17.0, -40.0])
+def test_loss_of_scores_that_are_all_negative(m, d, k, b, storage, mean):
+    """A trained layer without a target among its scores: every term is log(1 + e) of a small e.  1 + e is rounded to 2^-24 (all of an e below that is lost),
+    the logarithm of what is left to an ulp of itself: at most 2^-24 + 8 * 2^-24 of the term for a score, whatever the term is.  The sum over instances is divided by b."""
+    import gpu_util as gu
+    import torch
+    from paper_2306_03725_amd import usl
+    print("loss of negative scores", m, d, k, b, storage, mean, flush=True)
+    cfg = wl.custom(m, d, k, b, storage=storage, positives=3, index=822)
+    idx, x = wl.gen_idx(cfg), wl.gen_x(cfg)
+    W = wl.store((mean / (0.4 * k) * (1.0 + 0.1 * np.random.default_rng(5).standard_normal((m, k)))).astype(np.float32), storage)
+    d_x, d_idx, d_W, d_off, d_lab = gu.dev(x), gu.dev(idx), gu.dev(W), gu.dev(np.zeros(b + 1, dtype=np.int64)), gu.dev(np.zeros(1, dtype=np.int32))
+    L = usl.Layer(m, d, k, b, storage)
+    z = gu.empty((b, m))
+    L.forward(d_x, d_idx, d_W, z, b)
+    z64 = gu.host(z).astype(np.float64)
+    assert (z64 <= 0.0).all()
+    terms = np.log1p(np.exp(z64)).sum() / b
+    g, gW, gx, loss, m1, m2 = gu.empty((b, m)), gu.empty((m, k)), gu.empty((b, d)), gu.empty((1,)), gu.empty((m, k)).zero_(), gu.empty((m, k)).zero_()
+    L.train_step(d_x, d_idx, d_W, m1, m2, d_off, d_lab, 0, 1.0 / b, 1, 1e-3, 0.9, 0.999, 1e-8, g, gW, gx, loss, b)
+    torch.cuda.synchronize()
+    assert abs(float(gu.host(loss)[0]) - terms) <= 2.0 ** -24 * m + 8 * 2.0 ** -24 * terms
     L.close()

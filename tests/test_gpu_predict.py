@@ -172,14 +172,16 @@ def test_predict_of_one_group(usl, gu, orc, m, d, k, b, kk, storage):
     L.close()
 
 
-@pytest.mark.parametrize("m,d,k", [(500000, 32768, 32), (4097, 64, 8), (60867, 1344, 16)])
-def test_merge_by_the_workgroup_that_comes_last(usl, gu, orc, m, d, k):
+# Merged by the last workgroup: 256 of 16 wavefronts for 5, 1 and 16 labels, 17 of 4 wavefronts for all, both in bfloat16 too.  A launch of its own: 32 labels of the former, all of
+# (60867, 1344, 16), 476 workgroups
+@pytest.mark.parametrize("m,d,k,storage", [(500000, 32768, 32, "f32"), (4097, 64, 8, "f32"), (60867, 1344, 16, "f32"), (4097, 64, 8, "bf16"), (300001, 60000, 32, "bf16")])
+def test_merge_by_the_workgroup_that_comes_last(usl, gu, orc, m, d, k, storage):
     """Calls one behind the other with other inputs and other numbers of labels (beyond some the merge is a launch of its own), then the same from a
     captured graph: the count of finished workgroups is 0 again after every call."""
-    print("merge", m, d, k, flush=True)
-    cfg = wl.custom(m, d, k, 8, positives=1, index=871)
+    print("merge", m, d, k, storage, flush=True)
+    cfg = wl.custom(m, d, k, 8, storage=storage, positives=1, index=871)
     x = wl.gen_x(cfg)
-    L = usl.Layer(m, d, k, 8, stream=torch.cuda.current_stream().cuda_stream)
+    L = usl.Layer(m, d, k, 8, storage, torch.cuda.current_stream().cuda_stream)
     d_idx, d_W, d_out = gu.dev(wl.gen_idx(cfg)), gu.dev(wl.gen_W(cfg)), gu.empty((1, m))
     rows, want, got = [gu.dev(x[i:i + 1]) for i in range(8)], [], []
     for row in rows:
@@ -201,8 +203,11 @@ def test_merge_by_the_workgroup_that_comes_last(usl, gu, orc, m, d, k):
         L.predict(row, d_idx, d_W, 1, 5, lab, val)
     for i in (3, 5, 1):
         row.copy_(rows[i])
+        lab.fill_(-1), val.fill_(-1.0)
+        torch.cuda.synchronize()
         graph.replay()
         np.testing.assert_array_equal(gu.host(lab), want[i][0][:, :5])
+        np.testing.assert_array_equal(gu.host(val).view(np.uint32), np.ascontiguousarray(want[i][1][:, :5]).view(np.uint32))
         (row + 1).sum().item()
     L.close()
 
