@@ -863,9 +863,10 @@ __device__ __forceinline__ void gather4_two(float (&acc)[2], float& s0, float& s
 
 // The same for four instances, 16-byte reads and eight multiply-adds per slot: a group of four and, where n > most, the next one of its list, with four reads in flight throughout, in the same registers: each of the second group's
 // is asked for where the one four before it has been used.  (The branch is in here: two statements that change the same registers on either side
-// of one cost copies and reloads.)  Steps with groups of four by themselves and so: m = 70k, d = 10k, k = 48, b = 100 187.2 and 185.4 us; m = 31k, d = 1k, k = 32, b = 400
-// 151.2 and 150.0; m = 200k, d = 8k, b = 128, bfloat16 352.7 and 349.0; m = 670k, d = 16k, b = 32 543.9 and 542.1.  Not with two instances: 500k x 32k, b = 256 1940 both, and
-// its code, which every launch has to bring in, costs small batches up to 1 us (58k x 6k, k = 8, b = 8 47.4 and 48.4; 150k x 30k, b = 64 298.8 and 299.9).
+// of one cost copies and reloads.)  Steps with groups of four by themselves and so: m = 200k, d = 8k, k = 32, b = 64, bfloat16 213.0 and 211.1 us, b = 128 352.7 and 349.0; m = 70k,
+// d = 10k, k = 48, b = 100 193.5 and 193.2; m = 670k, d = 16k, k = 32, b = 32 549.9 and 548.1; m = 31k, d = 1k, b = 128 81.6 both (two runs of one side differ by up to 0.2 %).  Not
+// with two instances: 500k x 32k, b = 256 1940 both, and its code, which every launch has to bring in, costs small batches up to 1 us (58k x 6k, k = 8, b = 8 47.4 and
+// 48.4; 150k x 30k, b = 64 298.8 and 299.9).
 __device__ __forceinline__ void gather8(float (&acc)[4], float* s, const uint32_t* p, const float* w, float* s_far, const uint32_t* p_far, const float* w_far,
                                         const float (&x)[4], int n, int most) {
     const uint32_t shift = 4;

@@ -198,9 +198,10 @@ __device__ __forceinline__ float moved(float v) { return __int_as_float(__builti
 // and the sums of a label's lanes through LDS, the scores of m = 500k took 0.8 us longer.
 // BEST, one instance: the kk best labels, by keys (k_topk.h).  Each wavefront finds its own from its lanes' scores (the first few in registers, which then go
 // nowhere else; those of more turns read back from out), then the workgroup its own, which go to cand[workgroup][kk] (0 where there are fewer).  With top_lab the workgroup
-// that comes last merges them: candidates and the count of workgroups go by atomics of the device's scope, which pass the L2s, so no
-// fence writes these back (with a launch of its own for the merge usl_predict took 35.5 us at m = 500k, d = 32k, k = 32, now 33.0; m = 5000, d = 64, k = 8 10.6 and
-// 8.6).  A kernel of its own:
+// that comes last may merge them (last_one_merges): candidates and the count of workgroups go by atomics of the device's scope, so no fence writes back an L2.  What it reads
+// is what was written: a store of that scope passes its XCD's L2 and is there when the wait behind it ends, before the workgroup adds to the count; the loads are asked
+// for after the addition has returned and a barrier, and pass the L2 too, so that no older line answers them.  (With a launch of its own for the merge and the scores
+// read back for it usl_predict took 35.5 us at m = 500k, d = 32k, k = 32, so 33.0; m = 5000, d = 64, k = 8 10.6 and 8.6.)  A kernel of its own:
 // it takes 10 more registers, with which a compute unit holds one workgroup of 1024 in the place of two where k is no multiple of 4.  Where it is used:
 // best_from_forward.  (Several instances one after the other took longer than a kernel over the scores: m = 31k, d = 1k, k = 32, b = 4 16.2 and 26.6.)
 constexpr int FEW_HELD = 4;   // turns whose scores, or candidates, a lane keeps in registers

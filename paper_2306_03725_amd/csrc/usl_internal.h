@@ -328,8 +328,8 @@ __device__ __forceinline__ usl_loss_of usl_loss_one(int kind, float z, float y, 
 }
 // The same in parts, for kernels that are bound by this arithmetic: l = lin + ln(2) * log2, so that many scores' logarithms are scaled at once.  p lies in
 // [1, 2], so the hardware's logarithm needs neither the scaling of denormal numbers nor the tests for infinities that the standard library's has around it (12 of 27
-// instructions a score; steps at m = 200k, d = 8k, k = 32, b = 64, bfloat16 214.5 us, now 210.5; m = 670k, d = 32k, k = 64, b = 512, bfloat16 8349 and 8182; m = 500k, d = 32k, b = 256 1972
-// and 1959; m = 670k, d = 16k, b = 32 556.4 and 551.0).  g has the bits of usl_loss_one's.
+// instructions a score; steps at m = 200k, d = 8k, k = 32, b = 64, bfloat16 214.5 us, now 210.5; m = 670k, d = 16k, b = 32 556.4 and 551.0; at the larger
+// sizes the gain is within what two runs of one side differ by).  g has the bits of usl_loss_one's.
 struct usl_loss_parts { float g, lin, log2; };
 __device__ __forceinline__ usl_loss_parts usl_loss_in_parts(int kind, float z, float y, float scale) {
     usl_loss_parts o;
