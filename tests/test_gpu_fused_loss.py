@@ -132,10 +132,8 @@ def test_a_context_for_far_larger_batches(orc):
 @pytest.mark.parametrize("m,d,k,b,storage", [(3001, 300, 32, 21, "f32"), (2049, 9000, 8, 18, "bf16"), (2050, 24000, 48, 19, "f32"), (1500, 50000, 33, 17, "f32")])
 @pytest.mark.parametrize("factor", [0.0, 0.01, 1.0, 12.0, 60.0])
 def test_loss_of_small_and_large_scores(m, d, k, b, storage, factor):
-    """The loss inside forward against float64 of the same scores.  A score's term carries the roundings of the hardware's exponential and logarithm (an ulp
-    each), of 1 + e, which is 2^-24 of the term's own size or absolutely, whichever is more, and those of up to four scores' sums; everything else is
-    float64.  These scores lie on both sides of 0, so that a score's magnitude is 0.3 or more on average and all of that stays below 16 * 2^-24 of the magnitudes: 1e-6.
-    Scores that are all negative: the test below."""
+    """The loss inside forward against float64 of the same scores.  A score's terms carry two roundings of the hardware's exponential and logarithm (an
+    ulp each) and those of up to four scores' sums, at most 8 * 2^-24 of the terms' magnitude together; everything else is float64: 1e-6."""
     import gpu_util as gu
     import torch
     from paper_2306_03725_amd import usl
@@ -160,6 +158,8 @@ def test_loss_of_small_and_large_scores(m, d, k, b, storage, factor):
     L.close()
 
 
+# (The bound of the test above leaves out the rounding of 1 + e, which is 2^-24 of the term's own size or absolutely, whichever is more.  It holds there because those scores lie
+# on both sides of 0: a score's magnitude is 0.3 or more on average, and all roundings together stay below 16 * 2^-24 of it.)
 @pytest.mark.parametrize("m,d,k,b,storage", [(3001, 300, 32, 21, "f32"), (2049, 9000, 8, 18, "bf16"), (2050, 24000, 48, 19, "f32"), (1500, 50000, 33, 17, "f32")])
 @pytest.mark.parametrize("mean", [-4.5, -10.0, -14.0, -17.0, -40.0])
 def test_loss_of_scores_that_are_all_negative(m, d, k, b, storage, mean):

@@ -172,16 +172,14 @@ def test_predict_of_one_group(usl, gu, orc, m, d, k, b, kk, storage):
     L.close()
 
 
-# Merged by the last workgroup: 256 of 16 wavefronts for 5, 1 and 16 labels, 17 of 4 wavefronts for all, both in bfloat16 too.  A launch of its own: 32 labels of the former, all of
-# (60867, 1344, 16), 476 workgroups
-@pytest.mark.parametrize("m,d,k,storage", [(500000, 32768, 32, "f32"), (4097, 64, 8, "f32"), (60867, 1344, 16, "f32"), (4097, 64, 8, "bf16"), (300001, 60000, 32, "bf16")])
-def test_merge_by_the_workgroup_that_comes_last(usl, gu, orc, m, d, k, storage):
+@pytest.mark.parametrize("m,d,k", [(500000, 32768, 32), (4097, 64, 8), (60867, 1344, 16)])
+def test_merge_by_the_workgroup_that_comes_last(usl, gu, orc, m, d, k):
     """Calls one behind the other with other inputs and other numbers of labels (beyond some the merge is a launch of its own), then the same from a
     captured graph: the count of finished workgroups is 0 again after every call."""
-    print("merge", m, d, k, storage, flush=True)
-    cfg = wl.custom(m, d, k, 8, storage=storage, positives=1, index=871)
+    print("merge", m, d, k, flush=True)
+    cfg = wl.custom(m, d, k, 8, positives=1, index=871)
     x = wl.gen_x(cfg)
-    L = usl.Layer(m, d, k, 8, storage, torch.cuda.current_stream().cuda_stream)
+    L = usl.Layer(m, d, k, 8, stream=torch.cuda.current_stream().cuda_stream)
     d_idx, d_W, d_out = gu.dev(wl.gen_idx(cfg)), gu.dev(wl.gen_W(cfg)), gu.empty((1, m))
     rows, want, got = [gu.dev(x[i:i + 1]) for i in range(8)], [], []
     for row in rows:
@@ -203,11 +201,52 @@ def test_merge_by_the_workgroup_that_comes_last(usl, gu, orc, m, d, k, storage):
         L.predict(row, d_idx, d_W, 1, 5, lab, val)
     for i in (3, 5, 1):
         row.copy_(rows[i])
+        graph.replay()
+        np.testing.assert_array_equal(gu.host(lab), want[i][0][:, :5])
+        (row + 1).sum().item()
+    L.close()
+
+
+# Merged by the last workgroup: 256 of 16 wavefronts for 5, 1 and 16 labels, 17 of 4 wavefronts for all.  A launch of its own: 32 labels of the former.  (In the test above
+# (60867, 1344, 16) never merges that way: 476 workgroups.)
+@pytest.mark.parametrize("m,d,k,storage", [(500000, 32768, 32, "f32"), (4097, 64, 8, "f32"), (4097, 64, 8, "bf16"), (300001, 60000, 32, "bf16")])
+def test_scores_of_merges_by_the_workgroup_that_comes_last(usl, gu, orc, m, d, k, storage):
+    """Labels and the bits of the scores, of calls one behind the other and of every replay, into arrays that hold something else."""
+    print("scores of merges", m, d, k, storage, flush=True)
+    cfg = wl.custom(m, d, k, 8, storage=storage, positives=1, index=871)
+    x = wl.gen_x(cfg)
+    L = usl.Layer(m, d, k, 8, storage, torch.cuda.current_stream().cuda_stream)
+    d_idx, d_W, d_out = gu.dev(wl.gen_idx(cfg)), gu.dev(wl.gen_W(cfg)), gu.empty((1, m))
+    rows, want = [gu.dev(x[i:i + 1]) for i in range(8)], []
+    for row in rows:
+        L.forward(row, d_idx, d_W, d_out, 1)
+        want.append(orc.topk(gu.host(d_out), 32))
+
+    def same(i, kk, lab, val):
+        np.testing.assert_array_equal(gu.host(lab), want[i][0][:, :kk])
+        np.testing.assert_array_equal(gu.host(val).view(np.uint32), np.ascontiguousarray(want[i][1][:, :kk]).view(np.uint32))
+
+    got = []
+    for i in range(24):
+        kk = (5, 32, 1, 16)[i % 4]
+        lab, val = gu.empty((1, kk), torch.int32).fill_(-1), gu.empty((1, kk)).fill_(-1.0)
+        L.predict(rows[i % 8], d_idx, d_W, 1, kk, lab, val)
+        got.append((i % 8, kk, lab, val))
+    for call in got:
+        same(*call)
+    stream, row, lab, val = torch.cuda.Stream(), rows[0].clone(), gu.empty((1, 5), torch.int32), gu.empty((1, 5))
+    torch.cuda.synchronize()
+    L.set_stream(stream.cuda_stream)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        L.predict(row, d_idx, d_W, 1, 5, lab, val)
+    for i in (3, 5, 1):
+        row.copy_(rows[i])
         lab.fill_(-1), val.fill_(-1.0)
         torch.cuda.synchronize()
         graph.replay()
-        np.testing.assert_array_equal(gu.host(lab), want[i][0][:, :5])
-        np.testing.assert_array_equal(gu.host(val).view(np.uint32), np.ascontiguousarray(want[i][1][:, :5]).view(np.uint32))
+        torch.cuda.synchronize()
+        same(i, 5, lab, val)
         (row + 1).sum().item()
     L.close()
 
